@@ -150,6 +150,9 @@ extern "C" int32_t ds_sliced_conv(const void* x, int32_t dtype, int32_t layout, 
         DS_FAIL(DS_EWORKSPACE, "%s: workspace needs %zu bytes", who, ds_sliced_conv_workspace(B, Ho, Wo, g->T));
     hipStream_t s = (hipStream_t)stream;
     if (f32) {
+        rc = ds_launch_conv_f32_mfma((const float*)x, (const float*)w, scale, shift, C_O, (const float*)residual, (float*)y,
+                                     g->offsets, g->perm, gt, B, C_I, C_O, H, W, K, stride, pad, act, s);
+        if (rc != DS_EUNSUPPORTED) return rc;
         int32_t* slot_group = (int32_t*)ws;
         rc = ds_launch_expand_groups(g->offsets, g->T, slot_group, s);
         if (rc) return rc;

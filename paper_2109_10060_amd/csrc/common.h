@@ -215,6 +215,11 @@ int32_t ds_launch_conv_f32_nchw(const float* x, const float* w, const float* sca
                                 const int32_t* perm, const GroupTable& gt, int32_t B, int32_t C_I, int32_t C_O,
                                 int32_t H, int32_t W, int32_t K, int32_t stride, int32_t pad, int32_t act,
                                 hipStream_t s);
+// 1x1 and 3x3 filters on the fp32 matrix cores, the slot's group read from the offsets; DS_EUNSUPPORTED otherwise
+int32_t ds_launch_conv_f32_mfma(const float* x, const float* w, const float* scale, const float* shift, int32_t tab_ld,
+                                const float* residual, float* y, const int32_t* offsets, const int32_t* perm,
+                                const GroupTable& gt, int32_t B, int32_t C_I, int32_t C_O, int32_t H, int32_t W, int32_t K,
+                                int32_t stride, int32_t pad, int32_t act, hipStream_t s);
 int32_t ds_launch_compose_index(const int32_t* inner, const int32_t* outer, int32_t* out, int32_t B, hipStream_t s);
 int32_t ds_launch_lookup(const int32_t* idx, const GroupTable& gt, int32_t which, int32_t* out, int32_t B, hipStream_t s);
 
