@@ -92,11 +92,39 @@ struct GemmArgs {
     int32_t Kw, stride_w;    // filter width and horizontal stride where they differ from K / stride (0 = the same)
     // schedule
     const int32_t* offsets;  // device [T+1] slots
-    const int4* mtiles;      // device [(group, first row inside group, first slot, rows of group)]
+    const int4* mtiles;      // device [(group, first row inside group, first slot, rows of group)]; nullable: the kernels
+                             // work the record out from the offsets (saves the launch that builds the list)
     const int32_t* n_mtiles; // device scalar
     int32_t act, out_f32;
+    int32_t B;               // samples of the launch, at most (0: unknown)
+    int32_t ordered;         // 1: every sum in channel order, as the 128-row kernels take it, whatever the batch size
     GroupTable gt;
 };
+
+#ifdef __HIPCC__
+// Record of 128-row tile mt: read from the list, or (no list) found in the group offsets by the 64 lanes of the calling
+// wavefront side by side, groups from the last to the first as the list has them.  .x < 0: there is no such tile.
+__device__ __forceinline__ int4 ds_tile_record(const GemmArgs& a, int mt) {
+    if (a.mtiles) {
+        const int4 me = a.mtiles[mt];            // in bounds even beyond the live count; checked next
+        return mt < *a.n_mtiles ? me : make_int4(-1, 0, 0, 0);
+    }
+    const int lane = (int)(threadIdx.x & 63), g = a.gt.T - 1 - lane;
+    const int o0 = g >= 0 ? a.offsets[g] : 0, o1 = g >= 0 ? a.offsets[g + 1] : 0;
+    const int rg = (o1 - o0) * a.rows, n = (rg + DS_GEMM_BM - 1) / DS_GEMM_BM;
+    int upto = n;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int t = __shfl_up(upto, d, 64);
+        if (lane >= d) upto += t;
+    }
+    const unsigned long long past = __ballot(upto > mt);
+    if (past == 0) return make_int4(-1, 0, 0, 0);
+    const int q = __builtin_ctzll(past);
+    const int before = __builtin_amdgcn_readlane(upto - n, q);
+    return make_int4(a.gt.T - 1 - q, (mt - before) * DS_GEMM_BM, __builtin_amdgcn_readlane(o0, q), __builtin_amdgcn_readlane(rg, q));
+}
+#endif
 
 size_t ds_mtile_capacity(int32_t B, int32_t rows, int32_t T);
 // builds the m-tile list for (offsets, rows); list needs ds_mtile_capacity()*16 + 16 bytes
@@ -116,6 +144,8 @@ struct ThinChain {
     int32_t k_out[DS_MAX_GROUPS];  // per group; <= 0: the group ends with the first layer
 };
 int32_t ds_launch_thin_chain(const GemmArgs& a, const ThinChain& ch, int32_t max_mtiles, int32_t max_kout, hipStream_t s);
+// launches too small for 128-row tiles: short tiles and a reduction dealt to several wavefronts; DS_EUNSUPPORTED otherwise
+int32_t ds_launch_gemm_small(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s);
 // 3x3 stride-1 padding-1 layers on maps up to 59 pixels wide; DS_EUNSUPPORTED for any other shape
 int32_t ds_launch_conv3(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s);
 

@@ -49,8 +49,8 @@ __global__ __launch_bounds__(NT) void conv3_kernel(const GemmArgs a, const int n
     const int jm = j / ny, y = j - jm * ny;
     const int mt = jm * 8 + (int)(blockIdx.x & 7);
     if (mt >= max_mtiles) return;
-    const int4 me = a.mtiles[mt];
-    if (mt >= *a.n_mtiles) return;
+    const int4 me = ds_tile_record(a, mt);
+    if (me.x < 0) return;
     const int g = me.x, grow0 = me.y, slot0 = me.z, rows_g = me.w;
     const int k_in = a.gt.k_in[g], k_out = a.gt.k_out[g];
     if (k_in <= 0 || k_out <= 0) return;

@@ -52,6 +52,7 @@ struct MList {  // m-tile list of one (bucketing, rows-per-sample) pair
     void* list;
     int cap;
     int rows;
+    int B;
 };
 
 #define RC(x)                  \
@@ -115,7 +116,11 @@ int32_t conv_gemm(const bf16_t* A, const int32_t* a_index, int64_t a_sstride, in
     a.w_ld = (int64_t)K * K * C_I_full; a.w_tap_stride = C_I_full; a.n_seg = 1;
     a.H = H; a.W = W; a.Ho = Ho; a.Wo = Wo; a.K = K; a.stride = stride; a.pad = pad; a.rows = Ho * Wo;
     a.offsets = offsets; a.mtiles = ds_mtile_entries(ml.list); a.n_mtiles = ds_mtile_count(ml.list);
-    a.act = act; a.out_f32 = 0; a.gt = gt;
+    a.act = act; a.out_f32 = 0; a.gt = gt; a.B = ml.B;
+    {
+        const int32_t rc = ds_launch_gemm_small(a, ml.cap, max_out(gt), s);
+        if (rc != DS_EUNSUPPORTED) return rc;
+    }
     if (chain) {
         // the layer that reads exactly these output rows rides along where the shapes allow
         const int32_t rc = ds_launch_thin_chain(a, *chain, ml.cap, max_out(gt), s);
@@ -230,7 +235,7 @@ int32_t forward_mb(const ds_net* net, const MbDesc& d, const bf16_t* images, int
                       d.image, 3, 2, 1, d.stem_out, s));
     bf16_t *cur = p.bufA, *oth = p.bufB;
     int li = -1, last_rows = -1, last_phase = -1, fused_lists = 0;
-    MList ml = {nullptr, 0, 0};
+    MList ml = {nullptr, 0, 0, B};
     for (int i = 0; i < d.nb; ++i) {
         const int ci = d.blk[3 * i], co = d.blk[3 * i + 1], st = d.blk[3 * i + 2];
         const void* const* Q = P + 3 + 6 * i;
@@ -482,8 +487,8 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
         ba.inv_prev = st > 0 ? p.inv[st - 1] : nullptr;
         ba.src_index = p.src_index;          // slot of this stage -> slot of the previous stage's layout
         // the same launch builds the tile lists at both resolutions and the per-slot output width of the stage
-        MList ml_in = {p.lists[2 * st], (int)ds_mtile_capacity(B, rin * rin, G), rin * rin};
-        MList ml_out = {p.lists[2 * st + 1], (int)ds_mtile_capacity(B, rout * rout, G), rout * rout};
+        MList ml_in = {p.lists[2 * st], (int)ds_mtile_capacity(B, rin * rin, G), rin * rin, B};
+        MList ml_out = {p.lists[2 * st + 1], (int)ds_mtile_capacity(B, rout * rout, G), rout * rout, B};
         ba.n_lists = 2;
         ba.list_rows[0] = rin * rin; ba.lists[0] = ml_in.list;
         ba.list_rows[1] = rout * rout; ba.lists[1] = ml_out.list;
@@ -678,6 +683,9 @@ void plan_vit(const VitDesc& d, int B, Bump& bp, VitPlan* p) {
     p->list_t = bp.take<char>(16 + ds_mtile_capacity(B, d.N, d.T) * 16);
 }
 
+// Token networks amplify rounding differences from layer to layer (a last-bit change in one early sum moves the logits by
+// about 1 %), so their linear layers keep one order of summation for every batch size: an image's logits do not depend on
+// the batch it comes in.
 int32_t linear_gemm(const bf16_t* A, int64_t a_ss, int a_ld, const bf16_t* Wt, int64_t w_ld, const float* bias,
                     const bf16_t* R, int64_t r_ss, int r_ld, int r_use_index, bf16_t* C, int64_t c_ss, int c_ld,
                     int c_row0, int rows, int n_seg, int64_t w_seg, int64_t c_seg, int tab_seg, const int32_t* offsets,
@@ -691,7 +699,7 @@ int32_t linear_gemm(const bf16_t* A, int64_t a_ss, int a_ld, const bf16_t* Wt, i
     a.w_ld = w_ld; a.w_seg_stride = w_seg; a.c_seg_stride = c_seg; a.n_seg = n_seg;
     a.H = 1; a.W = rows; a.Ho = 1; a.Wo = rows; a.K = 1; a.stride = 1; a.pad = 0; a.rows = rows;
     a.offsets = offsets; a.mtiles = ds_mtile_entries(ml.list); a.n_mtiles = ds_mtile_count(ml.list);
-    a.act = act; a.out_f32 = 0; a.gt = gt;
+    a.act = act; a.out_f32 = 0; a.gt = gt; a.B = ml.B; a.ordered = 1;
     return ds_launch_gemm(a, ml.cap, max_out(gt), s);
 }
 
@@ -717,7 +725,7 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
         RC(ds_launch_set_offsets(p.off1, B, s));
         RC(ds_launch_stem(images, nullptr, p.sa, (const bf16_t*)S[0], (const float*)S[1], (const float*)S[2], B, d.image,
                           d.image, 7, 2, 3, C, s));
-        MList ml_s = {p.list_s, (int)ds_mtile_capacity(B, sr * sr, 1), sr * sr};
+        MList ml_s = {p.list_s, (int)ds_mtile_capacity(B, sr * sr, 1), sr * sr, B};
         RC(ds_build_mtiles(p.off1, 1, sr * sr, ml_s.list, s));
         const GroupTable g1c = table1(C, C);
         for (int i = 0; i < 2; ++i) {
@@ -750,8 +758,8 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
     }
     RC(ds_launch_gate(g, s));
     // one launch: bucket order, the tile lists for the patch rows and the token rows, the embedding width per slot
-    MList ml_p = {p.list_p, (int)ds_mtile_capacity(B, np, T), np};
-    MList ml_t = {p.list_t, (int)ds_mtile_capacity(B, d.N, T), d.N};
+    MList ml_p = {p.list_p, (int)ds_mtile_capacity(B, np, T), np, B};
+    MList ml_t = {p.list_t, (int)ds_mtile_capacity(B, d.N, T), d.N, B};
     BucketArgs ba = {};
     ba.route = route; ba.mul = 1; ba.B = B; ba.T = T;
     ba.perm = p.perm; ba.inv_perm = p.inv; ba.offsets = p.offs; ba.slot_group = p.slot_group;
@@ -793,7 +801,7 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
         a.H = sr; a.W = gw; a.Ho = gw; a.Wo = gw; a.K = d.patch; a.Kw = 1; a.stride = d.patch; a.stride_w = 1; a.pad = 0;
         a.rows = np;
         a.offsets = p.offs; a.mtiles = ds_mtile_entries(ml_p.list); a.n_mtiles = ds_mtile_count(ml_p.list);
-        a.act = DS_ACT_NONE; a.out_f32 = 0; a.gt = ge;
+        a.act = DS_ACT_NONE; a.out_f32 = 0; a.gt = ge; a.B = B; a.ordered = 1;
         for (int t = 0; t < T; ++t) a.gt.k_in[t] = d.patch * C;
         RC(ds_launch_gemm(a, ml_p.cap, max_out(ge), s));
     } else {

@@ -82,8 +82,8 @@ __global__ __launch_bounds__(NT, BK == 128 ? 3 : (WMT * WNT == 2 && !CONV) ? (BK
     const int jm = j / ny, y = j - jm * ny;
     const int mt = jm * 8 + (int)(blockIdx.x & 7);
     if (mt >= max_mtiles) return;
-    const int4 me = a.mtiles[mt];            // in-bounds even beyond the live count; checked next
-    if (mt >= *a.n_mtiles) return;
+    const int4 me = ds_tile_record(a, mt);
+    if (me.x < 0) return;
     const int g = me.x, grow0 = me.y, slot0 = me.z, rows_g = me.w;
     const int k_in = a.gt.k_in[g], k_out = a.gt.k_out[g];
     if (k_in <= 0 || k_out <= 0) return;
@@ -389,8 +389,12 @@ int32_t launch(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStrea
 
 }  // namespace
 
+// The most tiles B samples of `rows` rows can make in T groups: every non-empty group (at most min(B, T)) adds at most
+// one partly filled tile to what its rows need.
 size_t ds_mtile_capacity(int32_t B, int32_t rows, int32_t T) {
-    return (size_t)(((int64_t)B * rows + BM - 1) / BM + T);
+    if (B <= 0 || rows <= 0) return 1;
+    const int64_t n = (int64_t)B * rows, g = B < T ? B : T;
+    return (size_t)((n - g) / BM + g);
 }
 
 int32_t ds_build_mtiles(const int32_t* offsets, int32_t T, int32_t rows, void* list, hipStream_t s) {
@@ -422,6 +426,10 @@ int32_t ds_launch_gemm(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, 
     if (((long long)a.n_seg * a.w_seg_stride + (long long)max_kout * a.w_ld + taps * a.w_tap_stride + kmax) * 2 >= 0x7fffffffLL)
         DS_FAIL(DS_EUNSUPPORTED, "sliced gemm: weight tensor spans 2 GiB or more");
     const bool conv = a.K > 1 || a.stride > 1 || a.pad > 0;
+    {
+        const int32_t rc = ds_launch_gemm_small(a, max_mtiles, max_kout, s);
+        if (rc != DS_EUNSUPPORTED) return rc;
+    }
     if (conv) {
         const int32_t rc = ds_launch_conv3(a, max_mtiles, max_kout, s);
         if (rc != DS_EUNSUPPORTED) return rc;

@@ -1,0 +1,314 @@
+// Grouped prefix-slice GEMM / implicit-GEMM convolution for launches too small for the 128-row tile.
+//
+// With one to a few dozen samples a layer has 49 to a few thousand rows: gemm_kernel's 128 x 64 tiles then leave most of
+// the 256 compute units without a workgroup, and the workgroups that exist walk the whole reduction alone (one image,
+// last ResNet stage: 8 workgroups, 36 dependent 128-deep slabs, 30 us for a 3x3 layer).  What bounds such a launch is
+// the length of that chain, so here the reduction is cut as well: a wavefront owns a WM*32 x WN*32 tile and every KS-th
+// 64-deep slab of its reduction, the KS partial tiles are added in LDS in wavefront order, and a wavefront keeps PD
+// slabs travelling in registers.  Its operand slabs go through an LDS region of its own (global loads cover whole
+// 128-byte lines, the matrix operands want one row per lane), so there is no workgroup barrier before the final sum.
+// Same tile list, row addressing, slices and epilogue as gemm_kernel; a list tile of 128 rows is walked in parts of
+// WM*32 rows and a part beyond the group's rows ends at once.
+// Column tiles are the fastest index of the launch: neighbouring workgroups land on different dies, so a die's L2 holds
+// an eighth of the weights, which are most of what such a launch reads.
+#include "common.h"
+
+namespace {
+
+constexpr uint32_t OOB = 0x80000000u;
+
+// 16-byte chunk c of a 128-byte LDS row r is stored at chunk position c ^ key(r): the row-major stores (8 lanes a row)
+// and the operand reads (32 consecutive rows, one chunk column) are free of bank conflicts
+__device__ __forceinline__ int key(int r) { return (r ^ (r >> 3)) & 7; }
+__device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
+
+// NW wavefronts: KS shares of the reduction x NW / KS column tiles
+template <int WM, int WN, int NW, int KS, int PD, bool CONV, bool HASR>
+__global__ __launch_bounds__(64 * NW) void gemm_small_kernel(const GemmArgs a, const int ny, const int max_mtiles) {
+    constexpr int BM = WM * 32, WBN = WN * 32, NC = NW / KS, BN = NC * WBN, BK = 64;
+    constexpr int NSUB = DS_GEMM_BM / BM;
+    constexpr int NA = BM / 8, NB = WBN / 8;                  // 16-byte loads of a lane per slab
+    constexpr int WAVE_BYTES = (BM + WBN) * BK * 2;
+    constexpr int ST_LD = WBN + 4;                            // staging: one fp32 tile per wavefront
+    constexpr int STAGE_BYTES = BM * ST_LD * 4;
+    constexpr int PER_WAVE = WAVE_BYTES > STAGE_BYTES ? WAVE_BYTES : STAGE_BYTES;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    long long* rowC = (long long*)(smem + NW * PER_WAVE);     // [BM] output row, -1: no such row
+    long long* rowR = rowC + BM;
+
+    const int bid = (int)blockIdx.x;
+    const int y = bid % ny, mi = bid / ny;
+    const int mt = mi / NSUB, sub = mi - mt * NSUB;
+    if (mt >= max_mtiles) return;
+    const int4 me = ds_tile_record(a, mt);
+    if (me.x < 0) return;
+    const int g = me.x, grow0 = me.y + sub * BM, slot0 = me.z, rows_g = me.w;
+    if (grow0 >= rows_g) return;
+    const int k_in = a.gt.k_in[g], k_out = a.gt.k_out[g];
+    if (k_in <= 0 || k_out <= 0) return;
+    const int ntiles = (k_out + BN - 1) / BN;
+    const int seg = y / ntiles;
+    if (seg >= a.n_seg) return;
+    const int n0 = (y - seg * ntiles) * BN;
+
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
+    const int ks = wave % KS, wc = wave / KS;                 // share of the reduction, column tile
+    const int nw0 = n0 + wc * WBN;
+    const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc((void*)a.A, 0, 0x7fffffff, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc((void*)a.Wt, 0, 0x7fffffff, 0x00020000);
+    const int a_ld = a.a_ld > 0 ? a.a_ld : k_in;
+    const int c_ld = a.c_ld > 0 ? a.c_ld : k_out;
+    const int r_ld = a.r_ld > 0 ? a.r_ld : k_out;
+
+    // ---- rows: lane r works out row r of the tile, the lanes that load it fetch the result from lane r
+    uint32_t my_a = OOB;
+    int my_yx = 0;
+    if (lane < BM) {
+        const int m = grow0 + lane;
+        long long rc = -1, rr = 0;
+        if (m < rows_g) {
+            const int sl = m / a.rows, p = m - sl * a.rows, slot = slot0 + sl;
+            const int sa = a.a_index ? a.a_index[slot] : slot;
+            const int cs = a.c_index ? a.c_index[slot] : slot;
+            if constexpr (CONV) {
+                const int oy = p / a.Wo, ox = p - oy * a.Wo;
+                const int iy = oy * a.stride - a.pad, ix = ox * (a.stride_w > 0 ? a.stride_w : a.stride) - a.pad;
+                my_yx = (iy << 16) | (ix & 0xffff);
+            }
+            my_a = (uint32_t)(((long long)sa * a.a_sample_stride + (CONV ? 0 : (long long)p * a_ld)) * 2);
+            const long long pc = p + a.c_row0;
+            rc = (long long)cs * a.c_sample_stride + pc * c_ld + (long long)seg * a.c_seg_stride;
+            rr = (long long)(a.r_use_index ? cs : 0) * a.r_sample_stride + pc * r_ld;
+        }
+        if (wave == 0) {
+            rowC[lane] = rc;
+            rowR[lane] = rr;
+        }
+    }
+    const int lrow = lane >> 3, lchunk = lane & 7, kc8 = lchunk * 8;
+    uint32_t aoff[NA], woff[NB];
+    int ayx[CONV ? NA : 1];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        aoff[i] = (uint32_t)__shfl((int)my_a, lrow + 8 * i, 64);
+        if constexpr (CONV) ayx[i] = __shfl(my_yx, lrow + 8 * i, 64);
+        else if (aoff[i] != OOB) aoff[i] += kc8 * 2;
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int n = nw0 + lrow + 8 * i;
+        woff[i] = n < k_out ? (uint32_t)(((long long)seg * a.w_seg_stride + (long long)n * a.w_ld + kc8) * 2) : OOB;
+    }
+
+    const int kchunks = (k_in + BK - 1) / BK;
+    const int kw = a.Kw > 0 ? a.Kw : a.K;
+    const int nk = CONV ? a.K * kw * kchunks : kchunks;
+    uint4 ra[PD][NA], rb[PD][NB];
+    // slab being fetched next: tap and 64-channel chunk (this wavefront takes every KS-th slab)
+    int ltap = 0, lkc = ks;
+    auto fetch = [&](uint4 (&va)[NA], uint4 (&vb)[NB]) {
+        if constexpr (CONV)
+            while (lkc >= kchunks) { lkc -= kchunks; ++ltap; }
+        const bool kok = lkc * BK + kc8 < k_in;
+        const int u = CONV ? ltap / kw : 0, v = CONV ? ltap - u * kw : 0;
+        const int soff_a = lkc * BK * 2;
+        const int soff_w = (int)((ltap * a.w_tap_stride + lkc * BK) * 2);
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            uint32_t o = aoff[i];
+            if constexpr (CONV) {
+                const int iy = (ayx[i] >> 16) + u, ix = (int)(short)(ayx[i] & 0xffff) + v;
+                o = o != OOB && iy >= 0 && iy < a.H && ix >= 0 && ix < a.W ? o + (uint32_t)(((iy * a.W + ix) * a_ld + kc8) * 2) : OOB;
+            }
+            const auto t = __builtin_amdgcn_raw_buffer_load_b128(rsrc_a, (int)(kok ? o : OOB), soff_a, 0);
+            va[i] = make_uint4(t[0], t[1], t[2], t[3]);
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const auto t = __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, (int)(kok ? woff[i] : OOB), soff_w, 0);
+            vb[i] = make_uint4(t[0], t[1], t[2], t[3]);
+        }
+        lkc += KS;
+    };
+#pragma unroll
+    for (int st = 0; st < PD; ++st)
+        if (ks + KS * st < nk) fetch(ra[st], rb[st]);
+
+    f32x16_t acc[WM][WN];
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+    // LDS written and read by one wavefront: its accesses complete in order, only the compiler has to be kept in line
+    auto wave_sync = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    bf16_t* As = (bf16_t*)(smem + wave * PER_WAVE);
+    bf16_t* Bs = As + BM * BK;
+    auto stage = [&](const uint4 (&va)[NA], const uint4 (&vb)[NB]) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int r = lrow + 8 * i;
+            *(uint4*)(As + r * BK + ((lchunk ^ key(r)) * 8)) = va[i];
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int r = lrow + 8 * i;
+            *(uint4*)(Bs + r * BK + ((lchunk ^ key(r)) * 8)) = vb[i];
+        }
+        wave_sync();
+    };
+    bf16x8_t af[BK / 16][WM], bf[BK / 16][WN];
+    auto operands = [&]() {
+#pragma unroll
+        for (int kk = 0; kk < BK / 16; ++kk) {
+            const int c = kk * 2 + lhi;
+#pragma unroll
+            for (int t = 0; t < WM; ++t) af[kk][t] = *(const bf16x8_t*)(As + (t * 32 + l32) * BK + ((c ^ key(t * 32 + l32)) * 8));
+#pragma unroll
+            for (int t = 0; t < WN; ++t) bf[kk][t] = *(const bf16x8_t*)(Bs + (t * 32 + l32) * BK + ((c ^ key(t * 32 + l32)) * 8));
+        }
+        wave_sync();
+    };
+    for (int base = ks; base < nk; base += KS * PD) {
+#pragma unroll
+        for (int st = 0; st < PD; ++st) {
+            const int kt = base + KS * st;
+            if (kt >= nk) break;                              // uniform over the wavefront
+            stage(ra[st], rb[st]);
+            if (kt + KS * PD < nk) fetch(ra[st], rb[st]);
+            operands();
+#pragma unroll
+            for (int kk = 0; kk < BK / 16; ++kk)
+#pragma unroll
+                for (int i = 0; i < WM; ++i)
+#pragma unroll
+                    for (int j = 0; j < WN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk][i], bf[kk][j], acc[i][j], 0, 0, 0);
+        }
+    }
+
+    // ---- partial tiles to LDS, summed in wavefront order; a lane finishes 4 consecutive channels of one row
+    float* st = (float*)(smem + wave * PER_WAVE);
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                st[(i * 32 + 8 * (v >> 2) + 4 * lhi + (v & 3)) * ST_LD + j * 32 + l32] = acc[i][j][v];
+    __syncthreads();
+    constexpr int GPR = BN / 4;                               // groups of 4 channels per row
+    for (int e = tid; e < BM * GPR; e += 64 * NW) {
+        const int r = e / GPR, c4 = (e - r * GPR) * 4, ct = c4 / WBN, cl = c4 - ct * WBN;
+        const int n = n0 + c4;
+        const long long coff = rowC[r];
+        if (n >= k_out || coff < 0) continue;
+        const long long ti = (long long)a.gt.row[g] * a.tab_ld + (long long)seg * a.tab_seg_stride + n;
+        float vs[4] = {1.f, 1.f, 1.f, 1.f}, vh[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (a.scale) vs[q] = a.scale[ti + q];
+            if (a.shift) vh[q] = a.shift[ti + q];
+        }
+        uint2 res = make_uint2(0, 0);
+        if constexpr (HASR) res = *(const uint2*)(a.R + rowR[r] + n);
+        float val[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < KS; ++w) {
+            const float4 t = *(const float4*)((const float*)(smem + (ct * KS + w) * PER_WAVE) + r * ST_LD + cl);
+            val[0] += t.x; val[1] += t.y; val[2] += t.z; val[3] += t.w;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) val[q] = val[q] * vs[q] + vh[q];
+        if constexpr (HASR) {
+            val[0] += __uint_as_float(res.x << 16);
+            val[1] += __uint_as_float(res.x & 0xffff0000u);
+            val[2] += __uint_as_float(res.y << 16);
+            val[3] += __uint_as_float(res.y & 0xffff0000u);
+        }
+        if (a.act == DS_ACT_RELU) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) val[q] = fmaxf(val[q], 0.f);
+        } else if (a.act == DS_ACT_GELU) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) val[q] = gelu_erf(val[q]);
+        }
+        if (a.out_f32) {
+            *(float4*)((float*)a.C + coff + n) = make_float4(val[0], val[1], val[2], val[3]);
+        } else {
+            uint2 q;
+            q.x = f2bf2(val[0], val[1]);
+            q.y = f2bf2(val[2], val[3]);
+            *(uint2*)((bf16_t*)a.C + coff + n) = q;
+        }
+    }
+}
+
+template <int WM, int WN, int NW, int KS, int PD, bool CONV, bool HASR>
+int32_t launch(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
+    constexpr int BM = WM * 32, WBN = WN * 32, BN = (NW / KS) * WBN;
+    constexpr int W1 = (BM + WBN) * 128, W2 = BM * (WBN + 4) * 4;
+    constexpr int SMEM = NW * (W1 > W2 ? W1 : W2) + BM * 16;
+    auto kern = gemm_small_kernel<WM, WN, NW, KS, PD, CONV, HASR>;
+    const int32_t rc = ds_reserve_lds((const void*)kern, SMEM, "small sliced gemm");
+    if (rc) return rc;
+    const int ny = a.n_seg * ((max_kout + BN - 1) / BN);
+    ProfScope prof(a.K > 1 ? DS_K_GEMM_TAPS : DS_K_GEMM, s);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(max_mtiles * (DS_GEMM_BM / BM) * ny)), dim3(64 * NW), SMEM, s, a, ny, max_mtiles);
+    DS_CHECK_LAUNCH("small sliced gemm");
+    return DS_OK;
+}
+
+}  // namespace
+
+// Which tile, by the number t of 32 x 32 tiles the launch can have and the number nk of 64-deep slabs of its reduction.
+// Measured on single layers of the networks at 1 to 33 samples, kernel time in us, general kernels -> here:
+//   t <= 340    one tile and 8 shares of the reduction per workgroup: every compute unit gets at most one or two, so the
+//               length of a share is all that counts (3x3 512 channels, one sample 30.1 -> 13.8; 1x1 2048 -> 512 17.1 -> 7.8;
+//               six- and seven-slab linear layers of one sample 10.8 -> 6.1)
+//   t <= 500    32 x 64 tiles, 8 shares (24-slab linear layer of 5 samples 15.7 -> 8.6), 32 x 32 and 4 shares when
+//               there are fewer slabs than shares
+//   t <= 700    32 x 32, 4 shares (1x1 2048 -> 512 of 16 samples 22.0 -> 10.8, 3x3 512 37.7 -> 21.8)
+//   t <= 1000   64 x 64 tiles, 8 shares, for 24 slabs and more (3x3 256 of 16 samples 22.2 -> 16.8), 32 x 64 tiles and 4
+//               shares (1x1 1024 -> 256 14.5 -> 10.6), two column tiles and 2 shares up to four slabs (10.0 -> 6.9)
+//   ordered     one wavefront walks a tile's whole reduction, three slabs ahead, two tiles per workgroup, up to 1700 tiles
+//               (linear layers of 1 / 5 / 16 images of 197 tokens: 24 slabs 11.5 -> 9.5 / 15.5 -> 11.7 / 16.2 -> 15.3, six
+//               slabs 8.4 -> 6.8 / 10.9 -> 7.7 / 11.1 -> 10.1)
+//   beyond      the 128-row kernels have enough workgroups and read less per product -- except the strided KxK layers
+//               (no staged patch for them), which stay here up to 1700 tiles (33 samples: 49.3 -> 26.7, 30.2 -> 25.2)
+int32_t ds_launch_gemm_small(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
+    if (max_mtiles <= 0 || max_kout <= 0 || a.B <= 0 || a.H > 32767 || a.W > 32767) return DS_EUNSUPPORTED;
+    const bool conv = a.K > 1 || a.stride > 1 || a.pad > 0;
+    const int taps = a.K * (a.Kw > 0 ? a.Kw : a.K);
+    int kmax = 0;
+    for (int t = 0; t < a.gt.T; ++t) kmax = a.gt.k_in[t] > kmax ? a.gt.k_in[t] : kmax;
+    const int nk = taps * ((kmax + 63) / 64);
+    const long long groups = a.B < a.gt.T ? a.B : a.gt.T, rows = (long long)a.B * a.rows;
+    const long long t = ((rows - groups) / 32 + groups) * a.n_seg * ((max_kout + 31) / 32);
+    const bool strided = taps > 1 && a.stride > 1;
+    if (t > 1700 || (t > 1000 && !a.ordered && !(strided && nk >= 24))) return DS_EUNSUPPORTED;
+    // 32-bit byte offsets inside the kernel
+    const long long slots = (long long)max_mtiles * DS_GEMM_BM / (a.rows > 0 ? a.rows : 1) + 1;
+    if (slots * a.a_sample_stride * 2 >= 0x7fffffffLL) return DS_EUNSUPPORTED;
+    if (((long long)a.n_seg * a.w_seg_stride + (long long)max_kout * a.w_ld + taps * a.w_tap_stride + kmax) * 2 >= 0x7fffffffLL)
+        return DS_EUNSUPPORTED;
+#define DS_SMALL(...)                                                                       \
+    (conv ? (a.R ? launch<__VA_ARGS__, true, true>(a, max_mtiles, max_kout, s)               \
+                 : launch<__VA_ARGS__, true, false>(a, max_mtiles, max_kout, s))             \
+          : (a.R ? launch<__VA_ARGS__, false, true>(a, max_mtiles, max_kout, s)              \
+                 : launch<__VA_ARGS__, false, false>(a, max_mtiles, max_kout, s)))
+    if (a.ordered) return DS_SMALL(1, 1, 2, 1, 3);
+    if (t <= 340 && nk > 2) return DS_SMALL(1, 1, 8, 8, 4);
+    if (t > 340 && t <= 500 && nk >= 5) return DS_SMALL(1, 2, 8, 8, 2);
+    if (t <= 700) return DS_SMALL(1, 1, 4, 4, 4);
+    if (nk >= 24) return DS_SMALL(2, 2, 8, 8, 1);
+    if (nk > 4) return DS_SMALL(1, 2, 4, 4, 2);
+    return DS_SMALL(1, 1, 4, 2, 4);
+#undef DS_SMALL
+}
