@@ -61,6 +61,36 @@ class ds_net(ctypes.Structure):
 
 _lib = None
 
+# argument types of the calls a program makes per batch: with a prototype ctypes converts plain integers itself, which
+# costs a fraction of wrapping each pointer and size in an object first
+_P, _I, _L, _Z = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_size_t
+_PROTOTYPES = {
+    "ds_gate": (_P, _I, _I, _I, _I, _I, _P, _P, _P, _I, _P, _P, _I, _P, _P, _P, _P, _Z, _P),
+    "ds_route_bucket": (_P, _I, _I, _P, _P, _P, _P),
+    "ds_sliced_linear": (_P, _L, _P, _L, _I, _I, _P, _P, _I, _I, _I, _P, _L, _P, _I, _L, _P, _Z, _P),
+    "ds_sliced_conv": (_P, _I, _I, _I, _I, _I, _I, _P, _I, _I, _P, _P, _P, _I, _I, _I, _P, _P, _P, _Z, _P),
+    "ds_forward": (_P, _P, _I, _P, _P, _P, _P, _P, _Z, _P),
+    "ds_forward_parts": (_P, _P, _I, _P, _P, _P, _P, _P, _Z, _I, _P),
+}
+
+
+class _Calls:
+    """The library's entry points of _PROTOTYPES with their argument types set (the library object's own attributes stay
+    untyped)."""
+
+    def __init__(self, lib):
+        for name, args in _PROTOTYPES.items():
+            setattr(self, name, ctypes.CFUNCTYPE(_I, *args)((name, lib)))
+
+
+def _calls():
+    lib = _lib or load()
+    try:
+        return lib.ds_typed
+    except AttributeError:
+        lib.ds_typed = _Calls(lib)
+        return lib.ds_typed
+
 
 def load(path: Optional[str] = None):
     """Load libdsnet.so; raises if it has not been built."""
@@ -95,8 +125,21 @@ def _ptr(t: Optional[torch.Tensor], dtype=None):
     return ctypes.c_void_p(t.data_ptr())
 
 
+def _addr(t: Optional[torch.Tensor], dtype=None):
+    """_ptr as a plain integer, for the calls with a prototype."""
+    if t is None:
+        return None
+    assert t.is_cuda and t.is_contiguous(), "device tensors must be contiguous CUDA tensors"
+    assert dtype is None or t.dtype == dtype, f"expected {dtype}, got {t.dtype}"
+    return t.data_ptr()
+
+
+def _raw_stream() -> int:
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_raw_stream())
 
 
 def _ws(nbytes: int, like: torch.Tensor) -> torch.Tensor:
@@ -109,12 +152,11 @@ def make_groups(offsets: torch.Tensor, perm: Optional[torch.Tensor], k_in: Seque
     T = len(k_in)
     assert T <= DS_MAX_GROUPS
     g.T = T
-    g.offsets = _ptr(offsets, torch.int32).value
-    g.perm = _ptr(perm, torch.int32).value if perm is not None else None
-    k_out = k_in if k_out is None else k_out
-    table_row = range(T) if table_row is None else table_row
-    for t in range(T):
-        g.k_in[t], g.k_out[t], g.table_row[t] = int(k_in[t]), int(k_out[t]), int(table_row[t])
+    g.offsets = _addr(offsets, torch.int32)
+    g.perm = _addr(perm, torch.int32)
+    g.k_in[:T] = k_in = [int(v) for v in k_in]
+    g.k_out[:T] = k_in if k_out is None else [int(v) for v in k_out[:T]]
+    g.table_row[:T] = range(T) if table_row is None else [int(v) for v in table_row[:T]]
     return g
 
 
@@ -169,10 +211,12 @@ def ds_gate(x, layout, w1, b1, w2, b2, T: int, logit_bias=None, c_in=None, B: Op
         B = logit_bias.shape[0] if B is None else B
     logits = torch.empty((B, T), dtype=torch.float32, device=dev)
     route = torch.empty((B,), dtype=torch.int32, device=dev)
-    nb = lib.ds_gate_workspace(B, C)
-    ws = _ws(nb, logits)
-    _chk(lib.ds_gate(_ptr(x), dt, layout, B, C, HW, _ptr(c_in), _ptr(w1), _ptr(b1), C_mlp, _ptr(w2), _ptr(b2), T,
-                     _ptr(logit_bias), _ptr(logits), _ptr(route), _ptr(ws), ctypes.c_size_t(ws.numel()), _stream()))
+    nb = max(lib.ds_gate_workspace(B, C), 256)
+    ws = torch.empty(nb, dtype=torch.uint8, device=dev)
+    rc = _calls().ds_gate(_addr(x), dt, layout, B, C, HW, _addr(c_in), _addr(w1), _addr(b1), C_mlp, _addr(w2), _addr(b2), T,
+                          _addr(logit_bias), logits.data_ptr(), route.data_ptr(), ws.data_ptr(), nb, _raw_stream())
+    if rc:
+        _chk(rc)
     return logits, route
 
 
@@ -202,10 +246,11 @@ def ds_gate_double(x, layout, w1, b1, w3, b3=None, w2=None, b2=None, T: int = 0,
 def ds_route_bucket(route: torch.Tensor, T: int):
     """Returns (perm, inv_perm, offsets[T+1]) as int32 device tensors."""
     B = route.shape[0]
-    perm = torch.empty((B,), dtype=torch.int32, device=route.device)
-    inv = torch.empty((B,), dtype=torch.int32, device=route.device)
-    off = torch.empty((T + 1,), dtype=torch.int32, device=route.device)
-    _chk(load().ds_route_bucket(_ptr(route, torch.int32), B, T, _ptr(perm), _ptr(inv), _ptr(off), _stream()))
+    src = _addr(route, torch.int32)
+    perm, inv, off = route.new_empty(B), route.new_empty(B), route.new_empty(T + 1)
+    rc = _calls().ds_route_bucket(src, B, T, perm.data_ptr(), inv.data_ptr(), off.data_ptr(), _raw_stream())
+    if rc:
+        _chk(rc)
     return perm, inv, off
 
 
@@ -218,11 +263,13 @@ def ds_sliced_linear(x, w, bias, groups: ds_groups, act=DS_ACT_NONE, residual=No
     if y is None:
         y = torch.zeros((B, rows, N_full), dtype=y_dtype, device=x.device)
     ws = _ws(lib.ds_sliced_linear_workspace(B, rows, groups.T), x)
-    _chk(lib.ds_sliced_linear(_ptr(x, torch.bfloat16), ctypes.c_int64(x_ld), _ptr(w, torch.bfloat16),
-                              ctypes.c_int64(w.stride(0)), N_full, K_full, _ptr(bias), ctypes.byref(groups), B, rows,
-                              act, _ptr(residual), ctypes.c_int64(residual.shape[-1] if residual is not None else 0),
-                              _ptr(y), DS_BF16 if y.dtype == torch.bfloat16 else DS_F32, ctypes.c_int64(y.shape[-1]),
-                              _ptr(ws), ctypes.c_size_t(ws.numel()), _stream()))
+    rc = _calls().ds_sliced_linear(_addr(x, torch.bfloat16), x_ld, _addr(w, torch.bfloat16), w.stride(0), N_full, K_full,
+                                   _addr(bias), ctypes.byref(groups), B, rows, act, _addr(residual),
+                                   residual.shape[-1] if residual is not None else 0, _addr(y),
+                                   DS_BF16 if y.dtype == torch.bfloat16 else DS_F32, y.shape[-1], ws.data_ptr(), ws.numel(),
+                                   _raw_stream())
+    if rc:
+        _chk(rc)
     return y
 
 
@@ -256,9 +303,11 @@ def ds_sliced_conv(x, w, scale, shift, groups: ds_groups, stride: int, pad: int,
         shp = (B, C_O, Ho, Wo) if layout == DS_NCHW else (B, Ho, Wo, C_O)
         y = torch.zeros(shp, dtype=x.dtype, device=x.device)
     ws = _ws(lib.ds_sliced_conv_workspace(B, Ho, Wo, groups.T), x)
-    _chk(lib.ds_sliced_conv(_ptr(x), dt, layout, B, C_I, H, W, _ptr(w, x.dtype), C_O, K, _ptr(scale), _ptr(shift),
-                            ctypes.byref(groups), stride, pad, act, _ptr(residual), _ptr(y), _ptr(ws),
-                            ctypes.c_size_t(ws.numel()), _stream()))
+    rc = _calls().ds_sliced_conv(_addr(x), dt, layout, B, C_I, H, W, _addr(w, x.dtype), C_O, K, _addr(scale), _addr(shift),
+                                 ctypes.byref(groups), stride, pad, act, _addr(residual), _addr(y), ws.data_ptr(),
+                                 ws.numel(), _raw_stream())
+    if rc:
+        _chk(rc)
     return y
 
 
@@ -357,8 +406,10 @@ def ds_forward(net: "Net", images, route_override=None, logit_bias=None, logits=
         routes = torch.empty((net.n_gates, B), dtype=torch.int32, device=images.device)
     if ws is None:
         ws = net.workspace(B)
-    _chk(lib.ds_forward(ctypes.byref(net.c_struct), _ptr(images, torch.bfloat16), B, _ptr(route_override),
-                        _ptr(logit_bias), _ptr(logits), _ptr(routes), _ptr(ws), ctypes.c_size_t(ws.numel()), _stream()))
+    rc = _calls().ds_forward(ctypes.byref(net.c_struct), _addr(images, torch.bfloat16), B, _addr(route_override),
+                             _addr(logit_bias), _addr(logits), _addr(routes), _addr(ws), ws.numel(), _raw_stream())
+    if rc:
+        _chk(rc)
     return logits, routes
 
 
@@ -391,9 +442,11 @@ def ds_forward_parts(net: "Net", images, parts: int, route_override=None, logit_
         routes = torch.empty((net.n_gates, B), dtype=torch.int32, device=images.device)
     if ws is None:
         ws = net.workspace(B, parts)
-    _chk(lib.ds_forward_parts(ctypes.byref(net.c_struct), _ptr(images, torch.bfloat16), B, _ptr(route_override),
-                              _ptr(logit_bias), _ptr(logits), _ptr(routes), _ptr(ws), ctypes.c_size_t(ws.numel()),
-                              int(parts), _stream()))
+    rc = _calls().ds_forward_parts(ctypes.byref(net.c_struct), _addr(images, torch.bfloat16), B, _addr(route_override),
+                                   _addr(logit_bias), _addr(logits), _addr(routes), _addr(ws), ws.numel(), int(parts),
+                                   _raw_stream())
+    if rc:
+        _chk(rc)
     return logits, routes
 
 

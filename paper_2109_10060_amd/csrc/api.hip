@@ -98,8 +98,6 @@ extern "C" int32_t ds_sliced_linear(const void* x, int64_t x_ld, const void* w, 
     if (!ws || ws_bytes < ds_sliced_linear_workspace(B, rows, g->T))
         DS_FAIL(DS_EWORKSPACE, "%s: workspace needs %zu bytes", who, ds_sliced_linear_workspace(B, rows, g->T));
     hipStream_t s = (hipStream_t)stream;
-    rc = ds_build_mtiles(g->offsets, g->T, rows, ws, s);
-    if (rc) return rc;
     GemmArgs a;
     memset(&a, 0, sizeof(a));
     a.A = (const bf16_t*)x; a.Wt = (const bf16_t*)w; a.C = y; a.R = (const bf16_t*)residual;
@@ -111,9 +109,9 @@ extern "C" int32_t ds_sliced_linear(const void* x, int64_t x_ld, const void* w, 
     a.c_row0 = 0; a.r_use_index = 1;
     a.w_ld = w_ld; a.w_tap_stride = 0; a.w_seg_stride = 0; a.c_seg_stride = 0; a.n_seg = 1;
     linear_geometry(a, rows);
-    a.offsets = g->offsets; a.mtiles = ds_mtile_entries(ws); a.n_mtiles = ds_mtile_count(ws);
+    a.offsets = g->offsets; a.mtiles = nullptr; a.n_mtiles = nullptr;
     a.act = act; a.out_f32 = y_dtype == DS_F32;
-    a.gt = gt;
+    a.gt = gt; a.B = B;
     {
         // thin reductions with several column passes have a kernel of their own
         const int32_t rt = ds_launch_thin(a, (int32_t)ds_mtile_capacity(B, rows, g->T), mo, s);
@@ -162,8 +160,6 @@ extern "C" int32_t ds_sliced_conv(const void* x, int32_t dtype, int32_t layout, 
     if ((C_I % 8) || (C_O % 8) || !ds_aligned16(x) || !ds_aligned16(w) || !ds_aligned16(y) || !ds_aligned16(residual))
         DS_FAIL(DS_EALIGN, "%s: bf16 path needs 16-byte aligned pointers and channel counts multiples of 8", who);
     const int rows = Ho * Wo;
-    rc = ds_build_mtiles(g->offsets, g->T, rows, ws, s);
-    if (rc) return rc;
     GemmArgs a;
     memset(&a, 0, sizeof(a));
     a.A = (const bf16_t*)x; a.Wt = (const bf16_t*)w; a.C = y; a.R = (const bf16_t*)residual;
@@ -174,9 +170,9 @@ extern "C" int32_t ds_sliced_conv(const void* x, int32_t dtype, int32_t layout, 
     a.a_ld = C_I; a.c_ld = C_O; a.r_ld = C_O; a.c_row0 = 0; a.r_use_index = 1;
     a.w_ld = (int64_t)K * K * C_I; a.w_tap_stride = C_I; a.n_seg = 1;
     a.H = H; a.W = W; a.Ho = Ho; a.Wo = Wo; a.K = K; a.stride = stride; a.pad = pad; a.rows = rows;
-    a.offsets = g->offsets; a.mtiles = ds_mtile_entries(ws); a.n_mtiles = ds_mtile_count(ws);
+    a.offsets = g->offsets; a.mtiles = nullptr; a.n_mtiles = nullptr;
     a.act = act; a.out_f32 = 0;
-    a.gt = gt;
+    a.gt = gt; a.B = B;
     {
         // thin reductions with several column passes have a kernel of their own
         const int32_t rt = ds_launch_thin(a, (int32_t)ds_mtile_capacity(B, rows, g->T), mo, s);
@@ -308,15 +304,12 @@ extern "C" int32_t ds_sliced_mhsa(const void* x, int32_t B, int32_t N, int32_t D
         DS_FAIL(DS_EWORKSPACE, "%s: workspace needs %zu bytes", who, ds_sliced_mhsa_workspace(B, N, H, head_dim, g->T));
     hipStream_t s = (hipStream_t)stream;
     char* p = (char*)ws;
-    void* mlist = p;
     p += ds_align_up(16 + ds_mtile_capacity(B, N, g->T) * 16, 256);
     int32_t* slot_group = (int32_t*)p;
     p += ds_slot_workspace(B);
     const size_t bufsz = ds_align_up((size_t)B * N * Hd * sizeof(bf16_t), 256);
     bf16_t* qkv = (bf16_t*)p;          // [3][B][N][Hd], slot order
     bf16_t* obuf = (bf16_t*)(p + 3 * bufsz);
-    rc = ds_build_mtiles(g->offsets, g->T, N, mlist, s);
-    if (rc) return rc;
     rc = ds_launch_expand_groups(g->offsets, g->T, slot_group, s);
     if (rc) return rc;
     const int cap = (int)ds_mtile_capacity(B, N, g->T);
@@ -331,8 +324,8 @@ extern "C" int32_t ds_sliced_mhsa(const void* x, int32_t B, int32_t N, int32_t D
     a.w_ld = D_e; a.w_tap_stride = 0; a.w_seg_stride = (int64_t)Hd * D_e; a.n_seg = 3;
     a.c_seg_stride = (int64_t)(bufsz / sizeof(bf16_t));
     linear_geometry(a, N);
-    a.offsets = g->offsets; a.mtiles = ds_mtile_entries(mlist); a.n_mtiles = ds_mtile_count(mlist);
-    a.act = DS_ACT_NONE; a.out_f32 = 0; a.gt = gt;
+    a.offsets = g->offsets; a.mtiles = nullptr; a.n_mtiles = nullptr;
+    a.act = DS_ACT_NONE; a.out_f32 = 0; a.gt = gt; a.B = B;
     rc = ds_launch_gemm(a, cap, mo, s);
     if (rc) return rc;
 
@@ -353,8 +346,8 @@ extern "C" int32_t ds_sliced_mhsa(const void* x, int32_t B, int32_t N, int32_t D
     b.r_sample_stride = (int64_t)N * D_e; b.r_ld = D_e; b.r_use_index = 1;
     b.w_ld = Hd; b.n_seg = 1;
     linear_geometry(b, N);
-    b.offsets = g->offsets; b.mtiles = ds_mtile_entries(mlist); b.n_mtiles = ds_mtile_count(mlist);
-    b.act = DS_ACT_NONE; b.out_f32 = 0; b.gt = gp;
+    b.offsets = g->offsets; b.mtiles = nullptr; b.n_mtiles = nullptr;
+    b.act = DS_ACT_NONE; b.out_f32 = 0; b.gt = gp; b.B = B;
     return ds_launch_gemm(b, cap, mi, s);
 }
 
