@@ -30,7 +30,7 @@ __device__ __forceinline__ void load8<float>(const float* p, float* v) {
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
 
-// NHWC: grid (items, splits), block 256.  The block is shaped to the channel count: CL = 2^lcl lanes
+// NHWC: grid (items, splits, channel runs of 8 CL), block 256.  The block is shaped to the channel count: CL = 2^lcl lanes
 // (8 channels each) across the channels, 256 / CL rows of the map in flight per step, so narrow maps
 // (24 or 64 channels) keep every lane loading.
 template <typename T>
@@ -45,7 +45,8 @@ __global__ __launch_bounds__(256) void pool_nhwc_kernel(const GateArgs a, int sp
     const int lane_c = threadIdx.x & (CL - 1), lane_r = threadIdx.x >> lcl;
     const int per = (a.HW + splits - 1) / splits;
     const int r0 = sp * per, r1 = min(a.HW, r0 + per);
-    for (int c0 = 0; c0 < c; c0 += CL * 8) {
+    const int c0 = blockIdx.z * CL * 8;
+    if (c0 < c) {
         const int ch = c0 + lane_c * 8;
         float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
         if (ch < c) {
@@ -76,7 +77,6 @@ __global__ __launch_bounds__(256) void pool_nhwc_kernel(const GateArgs a, int sp
             for (int r = 0; r < R; ++r) t += red[r * red_ld + threadIdx.x];
             a.partial[((int64_t)item * splits + sp) * a.C + cc] = t;
         }
-        __syncthreads();
     }
 }
 
@@ -143,6 +143,168 @@ __global__ __launch_bounds__(64) void gate_out_kernel(const GateArgs a, const fl
         if (oh && (!have || ob > best || (ob == best && oa < arg))) { best = ob; arg = oa; have = true; }
     }
     if (lane == 0) a.route[out] = a.route_override ? a.route_override[out] : arg;
+}
+
+// ---- the whole gate of one item in one workgroup ------------------------------------------------
+// Encoder, both MLP layers and the argmax as one launch instead of three: a gate's arithmetic is a few microseconds at
+// most, so three dependent launches cost more than they compute.  16 wavefronts; the pooled vector (fp64) and the hidden
+// units stay in LDS.  POOLED = false reads the pool kernel's partial sums instead of the map: a map of megabytes is too
+// much for one compute unit (~100 GB/s) while other compute units idle.
+// An output unit belongs to 16 neighbouring lanes, which stride over its weight row with 16-byte loads, so the 64 units of
+// a pass read whole lines; sums are fp64 in a fixed order.
+constexpr int GF_NT = 1024, GF_CMAX = 2048, GF_HMAX = 1024;
+
+template <typename T, bool NHWC, bool POOLED>
+__global__ __launch_bounds__(GF_NT) void gate_fused_kernel(const GateArgs a, const int splits, const int lcl) {
+    __shared__ __attribute__((aligned(16))) double pooled[GF_CMAX];
+    __shared__ float hid[GF_HMAX];
+    __shared__ float score[64];
+    __shared__ float red[POOLED && NHWC ? GF_NT / 64 * 512 : 1];
+    const int item = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c = a.c_in ? a.c_in[item] : a.C;
+    const double inv = (double)(1.0f / (float)a.HW);
+    if constexpr (!POOLED) {
+        for (int ch = tid; ch < c; ch += GF_NT) {
+            double s = 0.0;
+            for (int sp = 0; sp < splits; ++sp) s += (double)a.partial[((int64_t)item * splits + sp) * a.C + ch];
+            pooled[ch] = (double)(float)(s * inv);
+        }
+    } else {
+        const int sample = a.x_index ? a.x_index[item] : item;
+        const T* x = (const T*)a.x + (int64_t)sample * a.x_sample_stride;
+        if constexpr (NHWC) {
+            // 2^lcl lanes across the channels (8 each; a wavefront at most), the other lanes across the pixels, eight
+            // pixels of a lane in flight; lanes of a wavefront with the same channels are added by exchange, the
+            // wavefronts in LDS
+            const int ld = a.x_ld > 0 ? a.x_ld : c;
+            const int CL = 1 << lcl, R = GF_NT >> lcl;
+            const int lane_c = tid & (CL - 1), lane_r = tid >> lcl;
+            for (int c0 = 0; c0 < c; c0 += CL * 8) {
+                const int ch = c0 + lane_c * 8;
+                float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+                if (ch < c) {
+                    int r = lane_r;
+                    for (; r + 7 * R < a.HW; r += 8 * R) {
+                        float v[8][8];
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) load8<T>(x + (int64_t)(r + R * k) * ld + ch, v[k]);
+#pragma unroll
+                        for (int k = 0; k < 8; ++k)
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) s[i] += v[k][i];
+                    }
+#pragma unroll 4
+                    for (; r < a.HW; r += R) {
+                        float v[8];
+                        load8<T>(x + (int64_t)r * ld + ch, v);
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) s[i] += v[i];
+                    }
+                }
+                for (int o = 32; o >= CL; o >>= 1)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) s[i] += __shfl_xor(s[i], o, 64);
+                if (lane < CL)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) red[(wave << lcl) * 8 + lane * 8 + i] = s[i];
+                __syncthreads();
+                if (tid < CL * 8 && c0 + tid < c) {
+                    double t = 0.0;
+#pragma unroll
+                    for (int w = 0; w < GF_NT / 64; ++w) t += (double)red[(w << lcl) * 8 + tid];
+                    pooled[c0 + tid] = (double)(float)(t * inv);
+                }
+                __syncthreads();
+            }
+        } else {
+            // one channel plane per wavefront
+            for (int ch = wave; ch < c; ch += GF_NT / 64) {
+                const T* xc = x + (int64_t)ch * a.HW;
+                float s = 0.f;
+                for (int i = lane; i < a.HW; i += 64) {
+                    if constexpr (sizeof(T) == 2) s += bf2f(xc[i]);
+                    else s += xc[i];
+                }
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+                if (lane == 0) pooled[ch] = (double)(float)((double)s * inv);
+            }
+        }
+    }
+    __syncthreads();
+    // ---- hidden layer: 16 lanes per unit
+    const int grp = tid >> 4, sub = tid & 15;
+    const bool vec = (a.C & 3) == 0 && ((((uintptr_t)a.w1) & 15) == 0);
+    for (int j = grp; j < a.C_mlp; j += GF_NT / 16) {
+        const float* wr = a.w1 + (int64_t)j * a.C;
+        double s = 0.0;
+        if (vec) {
+            // four 16-byte pieces of the row in flight; a piece past the channels is fetched from the last one and dropped
+            const int n4 = (c + 3) >> 2;
+            for (int q0 = sub; q0 < n4; q0 += 64) {
+                float4 w4[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w4[i] = *(const float4*)(wr + min(q0 + 16 * i, n4 - 1) * 4);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int k = (q0 + 16 * i) * 4;
+                    if (k + 3 < c) {
+                        const double2 p0 = *(const double2*)(pooled + k), p1 = *(const double2*)(pooled + k + 2);
+                        s += (double)w4[i].x * p0.x;
+                        s += (double)w4[i].y * p0.y;
+                        s += (double)w4[i].z * p1.x;
+                        s += (double)w4[i].w * p1.y;
+                    } else if (k < c) {
+                        s += (double)w4[i].x * pooled[k];
+                        if (k + 1 < c) s += (double)w4[i].y * pooled[k + 1];
+                        if (k + 2 < c) s += (double)w4[i].z * pooled[k + 2];
+                    }
+                }
+            }
+        } else {
+            for (int k = sub; k < c; k += 16) s += (double)wr[k] * pooled[k];
+        }
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 16);
+        if (sub == 0) {
+            if (a.b1) s += (double)a.b1[j];
+            hid[j] = (float)(s < 0.0 ? 0.0 : s);
+        }
+    }
+    __syncthreads();
+    // ---- route scores: 16 lanes per route
+    const int out = a.out_index ? a.out_index[item] : item;
+    for (int t = grp; t < a.T; t += GF_NT / 16) {
+        const float* wr = a.w2 + (int64_t)t * a.C_mlp;
+        double s = 0.0;
+        for (int k = sub; k < a.C_mlp; k += 16) s += (double)wr[k] * (double)hid[k];
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 16);
+        if (sub == 0) {
+            if (a.b2) s += (double)a.b2[t];
+            if (a.logit_bias) s += (double)a.logit_bias[(int64_t)out * a.T + t];
+            const float v = (float)s;
+            a.logits[(int64_t)out * a.T + t] = v;
+            score[t] = v;
+        }
+    }
+    __syncthreads();
+    if (wave == 0) {
+        // argmax as in gate_out_kernel: NaN never wins, ties go to the lowest index
+        const bool in = lane < a.T;
+        float best = in ? score[lane] : 0.f;
+        int arg = in ? lane : 0;
+        bool have = in && best == best;
+        if (!have) arg = 0;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const float ob = __shfl_xor(best, o, 64);
+            const int oa = __shfl_xor(arg, o, 64);
+            const bool oh = __shfl_xor((int)have, o, 64) != 0;
+            if (oh && (!have || ob > best || (ob == best && oa < arg))) { best = ob; arg = oa; have = true; }
+        }
+        if (lane == 0) a.route[out] = a.route_override ? a.route_override[out] : arg;
+    }
 }
 
 // ---- bucketing ----------------------------------------------------------------
@@ -350,9 +512,9 @@ int32_t ds_launch_pool(const GateArgs& a, int32_t kind, int32_t* splits_out, hip
     ProfScope prof(kind, s);
     if (a.layout == DS_NHWC) {
         splits = a.HW >= 2048 ? 8 : (a.HW >= 512 ? 4 : (a.HW >= 128 ? 2 : 1));
-        dim3 grid(a.B, splits);
         int lcl = 0;
         while ((8 << lcl) < a.C && lcl < 5) ++lcl;   // lanes across the channels: 2^lcl * 8 >= C, at most 32
+        dim3 grid(a.B, splits, (unsigned)((a.C + (8 << lcl) - 1) / (8 << lcl)));
         if (a.dtype == DS_BF16) hipLaunchKernelGGL(pool_nhwc_kernel<bf16_t>, grid, dim3(256), 0, s, a, splits, lcl);
         else hipLaunchKernelGGL(pool_nhwc_kernel<float>, grid, dim3(256), 0, s, a, splits, lcl);
     } else {
@@ -368,6 +530,31 @@ int32_t ds_launch_pool(const GateArgs& a, int32_t kind, int32_t* splits_out, hip
 int32_t ds_launch_gate(const GateArgs& a, hipStream_t s) {
     if (a.B <= 0) return DS_OK;
     float* hidden = nullptr;
+    // (16-byte rows of the map: NHWC strides are multiples of 8 channels wherever the entry points let a map in)
+    const bool rows16 = a.layout != DS_NHWC || ((a.C % 8) == 0 && (a.x_ld <= 0 || (a.x_ld % 8) == 0) && (a.x_sample_stride % 8) == 0);
+    if (a.x && a.C <= GF_CMAX && a.C_mlp <= GF_HMAX && a.T <= 64 && rows16) {
+        const int64_t map_bytes = (int64_t)a.C * a.HW * (a.dtype == DS_BF16 ? 2 : 4);
+        // one compute unit pools up to 512 KiB and 512 channels in less time than a launch costs (9 us with the MLP, against
+        // 16-26 us for pool, hidden layer and output layer one after the other); above, the pool kernel's several workgroups
+        // per item first (196 x 1024 channels: 25 us in one workgroup, 21 in two launches)
+        const bool pooled = map_bytes <= (512 << 10) && a.C <= 512;
+        int splits = 1;
+        if (!pooled) {
+            const int32_t rc = ds_launch_pool(a, DS_K_GATE, &splits, s);
+            if (rc) return rc;
+        }
+        int lcl = 0;
+        while ((8 << lcl) < a.C && lcl < 6) ++lcl;
+        ProfScope prof(DS_K_GATE, s);
+        const dim3 grid((unsigned)a.B), block(GF_NT);
+        if (!pooled) hipLaunchKernelGGL((gate_fused_kernel<float, false, false>), grid, block, 0, s, a, splits, lcl);
+        else if (a.layout == DS_NHWC && a.dtype == DS_BF16) hipLaunchKernelGGL((gate_fused_kernel<bf16_t, true, true>), grid, block, 0, s, a, splits, lcl);
+        else if (a.layout == DS_NHWC) hipLaunchKernelGGL((gate_fused_kernel<float, true, true>), grid, block, 0, s, a, splits, lcl);
+        else if (a.dtype == DS_BF16) hipLaunchKernelGGL((gate_fused_kernel<bf16_t, false, true>), grid, block, 0, s, a, splits, lcl);
+        else hipLaunchKernelGGL((gate_fused_kernel<float, false, true>), grid, block, 0, s, a, splits, lcl);
+        DS_CHECK_LAUNCH("fused gate");
+        return DS_OK;
+    }
     if (a.x) {
         int splits = 1;
         int32_t rc = ds_launch_pool(a, DS_K_GATE, &splits, s);

@@ -1,0 +1,148 @@
+"""GPU parity of the kernels a dispatch picks by size, at the sizes where each can go wrong: the edges of its tiles, the
+remainders of its reduction, the smallest and largest of its range.  Reference: the oracle, or torch in float64 on the CPU."""
+import numpy as np
+import pytest
+import torch
+import torch.nn.functional as F
+
+import workloads as WL
+from oracle import ds_oracle as O
+from tests.parity import relerr
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+TOL_F32, TOL_BF16 = 1e-5, 2e-2
+
+
+def dev(a, dtype=torch.float32):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV).to(dtype).contiguous()
+
+
+def host(t):
+    return t.detach().to(torch.float64).cpu().numpy()
+
+
+def _conv_reference(x, w, bn, t, stride, pad, resid):
+    y = F.conv2d(torch.from_numpy(x).double()[None], torch.from_numpy(w).double(), stride=stride, padding=pad)[0].numpy()
+    co = w.shape[0]
+    s = bn["gamma"][:co].astype(np.float64) / np.sqrt(bn["var"][t, :co].astype(np.float64) + 1e-5)
+    y = y * s[:, None, None] + (bn["beta"][:co] - bn["mean"][t, :co] * s)[:, None, None]
+    return y if resid is None else y + resid
+
+
+def _conv_case(gpu_lib, B, K, stride, pad, H, W, c_in, c_out, res, f32):
+    T = len(c_in)
+    CI, CO = max(c_in), max(c_out)
+    d = WL.nets.Draw(7000 + B + 10 * K + H + CI)
+    cast = (lambda a: a) if f32 else WL.nets.as_bf16_values
+    x = cast(d.normal((B, CI, H, W)))
+    w = cast(d.normal((CO, CI, K, K), std=(2.0 / (CI * K * K)) ** 0.5))
+    bn = WL.bn_tables(d, T, CO)
+    route = d.randint(B, T)
+    Ho, Wo = (H + 2 * pad - K) // stride + 1, (W + 2 * pad - K) // stride + 1
+    resid = cast(d.normal((B, CO, Ho, Wo))) if res else None
+    perm, inv, off = gpu_lib.ds_route_bucket(dev(route, torch.int32), T)
+    scale, shift = gpu_lib.ds_bn_fold(dev(bn["gamma"]), dev(bn["beta"]), dev(bn["mean"]), dev(bn["var"]), 1e-5)
+    g = gpu_lib.make_groups(off, perm, c_in, c_out)
+    lay = (lambda a: dev(a)) if f32 else (lambda a: dev(a.transpose(0, 2, 3, 1), torch.bfloat16))
+    y = torch.full((B, CO, Ho, Wo) if f32 else (B, Ho, Wo, CO), float("nan"), dtype=torch.float32 if f32 else torch.bfloat16,
+                   device=DEV)
+    gpu_lib.ds_sliced_conv(lay(x), lay(w), scale, shift, g, stride, pad, residual=lay(resid) if res else None, y=y)
+    yh = host(y) if f32 else host(y).transpose(0, 3, 1, 2)
+    for b in range(B):
+        t = int(route[b])
+        ci, co = c_in[t], c_out[t]
+        want = np.maximum(_conv_reference(x[b, :ci], w[:co, :ci], bn, t, stride, pad, resid[b, :co] if res else None), 0.0)
+        if not f32:
+            want = O.bf16_round(want)
+        assert relerr(yh[b, :co], want) < (TOL_F32 if f32 else TOL_BF16), (b, t)
+        assert np.all(np.isnan(yh[b, co:]))
+
+
+# fp32: the matrix-core kernel for 1x1 and 3x3 filters (slices of 8 or 16 channels, 32-pixel and 32-filter tiles, rows of
+# weights that are and are not whole 16-byte pieces), the plain kernel for other filters
+@pytest.mark.parametrize("B,K,stride,pad,H,W,c_in,c_out,res", [
+    (1, 3, 1, 1, 1, 1, (1, 1), (1, 1), False), (5, 3, 1, 1, 8, 8, (32, 8), (32, 1), True),
+    (3, 3, 1, 1, 9, 7, (33, 5), (33, 31), False), (4, 3, 2, 1, 11, 13, (64, 48), (64, 16), True),
+    (2, 3, 1, 0, 10, 17, (130, 66), (70, 33), False), (3, 1, 1, 0, 5, 9, (64, 17), (40, 32), True),
+    (2, 1, 2, 0, 9, 9, (3, 130), (65, 8), False), (2, 5, 1, 2, 8, 8, (12, 4), (10, 6), True)])
+def test_sliced_conv_fp32(gpu_lib, B, K, stride, pad, H, W, c_in, c_out, res):
+    _conv_case(gpu_lib, B, K, stride, pad, H, W, c_in, c_out, res, True)
+
+
+# bf16: every tile of the small-launch kernel and the first launch beyond it.  32 x 32 tiles of a launch, 64-deep slabs:
+@pytest.mark.parametrize("B,K,stride,pad,H,W,c_in,c_out,res", [
+    (1, 1, 1, 0, 1, 1, (8,), (8,), False),                           # 1 tile, 1 slab
+    (1, 3, 1, 1, 7, 7, (512, 128), (512, 136), False),               # 32 tiles, 72 slabs: 32 x 32, 8 shares
+    (2, 1, 1, 0, 13, 13, (72, 264), (1032, 40), True),               # 363 tiles, 5 slabs: 32 x 64, 8 shares
+    (1, 1, 1, 0, 28, 28, (128, 40), (512, 8), True),                 # 400 tiles, 2 slabs: 32 x 32, 4 shares
+    (3, 3, 2, 1, 27, 27, (64, 24), (1000, 72), False),               # 608 tiles, 9 slabs: 32 x 32, 4 shares
+    (9, 3, 1, 1, 15, 14, (256, 96), (456, 200), True),               # 900 tiles, 36 slabs: 64 x 64, 8 shares
+    (5, 3, 1, 1, 28, 30, (64, 8), (200, 104), False),                # 931 tiles, 9 slabs: 32 x 64, 4 shares
+    (2, 1, 1, 0, 56, 57, (64, 56), (128, 120), True),                # 796 tiles, 1 slab: two column tiles, 2 shares
+    (31, 3, 2, 1, 14, 14, (160, 152), (1024, 8), False),             # 1552 tiles, 27 slabs, strided: 64 x 64, 8 shares
+    (40, 1, 1, 0, 37, 37, (64, 24), (136, 128), False),              # 430 row tiles: the streaming kernel
+    (40, 1, 1, 0, 37, 37, (128, 72), (264, 128), True)])             # 430 row tiles of 128 channels: not yet
+def test_sliced_conv_bf16_tiles(gpu_lib, B, K, stride, pad, H, W, c_in, c_out, res):
+    _conv_case(gpu_lib, B, K, stride, pad, H, W, c_in, c_out, res, False)
+
+
+# the tile records worked out from the offsets: groups without samples, one group, as many groups as lanes
+@pytest.mark.parametrize("B,T,rows", [(1, 1, 1), (3, 64, 130), (70, 64, 33), (64, 5, 197), (300, 7, 128)])
+def test_sliced_linear_tile_records(gpu_lib, B, T, rows):
+    K, N = 72, 136
+    d = WL.nets.Draw(B + T)
+    x, w = WL.nets.as_bf16_values(d.normal((B, rows, K))), WL.nets.as_bf16_values(d.normal((N, K), std=0.1))
+    bias = d.normal((N,))
+    k_in, k_out = [8 + 8 * (t % 9) for t in range(T)], [8 + 8 * (t * 5 % 17) for t in range(T)]
+    route = (d.randint(B, T) if T != 5 else np.full(B, 2)).astype(np.int32)
+    perm, inv, off = gpu_lib.ds_route_bucket(dev(route, torch.int32), T)
+    y = torch.full((B, rows, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+    gpu_lib.ds_sliced_linear(dev(x, torch.bfloat16), dev(w, torch.bfloat16), dev(bias), gpu_lib.make_groups(off, perm, k_in, k_out),
+                             y=y)
+    yh = host(y)
+    for b in range(B):
+        ki, ko = k_in[route[b]], k_out[route[b]]
+        want = O.bf16_round(x[b, :, :ki].astype(np.float64) @ w[:ko, :ki].T.astype(np.float64) + bias[:ko])
+        assert relerr(yh[b, :, :ko], want) < TOL_BF16
+        assert np.all(np.isnan(yh[b, :, ko:]))
+
+
+# one workgroup per item with and without the pool in front, channel counts that leave lanes and 16-byte pieces over
+@pytest.mark.parametrize("layout,dtype,B,C,HW,hid,T", [
+    ("nchw", "f32", 1, 1, 1, 1, 1), ("nchw", "f32", 5, 66, 100, 16, 64), ("nchw", "bf16", 3, 128, 77, 32, 5),
+    ("nhwc", "f32", 4, 24, 49, 6, 3), ("nhwc", "bf16", 2, 512, 196, 128, 14), ("nhwc", "bf16", 3, 520, 130, 130, 4),
+    ("nhwc", "bf16", 2, 8, 5, 8, 2), ("nhwc", "bf16", 1, 256, 3136, 64, 4), ("nhwc", "bf16", 2, 2056, 9, 64, 4)])
+def test_gate_shapes(gpu_lib, layout, dtype, B, C, HW, hid, T):
+    d = WL.nets.Draw(31 + C + HW)
+    x = d.normal((B, C, HW))
+    if dtype == "bf16":
+        x = WL.nets.as_bf16_values(x)
+    w1, b1 = d.normal((hid, C), std=C ** -0.5), d.normal((hid,), std=0.1)
+    w2, b2 = d.normal((T, hid), std=hid ** -0.5), d.normal((T,), std=0.1)
+    c_in = np.maximum(1, C - 8 * (np.arange(B) % 2) * (C > 8)).astype(np.int32)
+    xg = x if layout == "nchw" else x.transpose(0, 2, 1)
+    xg = dev(xg.reshape(B, C, HW, 1) if layout == "nchw" else xg, torch.float32 if dtype == "f32" else torch.bfloat16)
+    logits, route = gpu_lib.ds_gate(xg, gpu_lib.DS_NCHW if layout == "nchw" else gpu_lib.DS_NHWC, dev(w1), dev(b1), dev(w2),
+                                    dev(b2), T, c_in=dev(c_in, torch.int32))
+    want = np.stack([O.gate_logits(O.gate_encoder(x[b, :c_in[b]].reshape(c_in[b], HW, 1)), w1, b1, w2, b2) for b in range(B)])
+    assert relerr(host(logits), want) < TOL_F32
+    assert route.cpu().numpy().tolist() == [O.gate_route(z) for z in host(logits)]
+
+
+# classifier: a wavefront per output up to 8 items and 2048 channels, the 32-item tile beyond
+@pytest.mark.parametrize("B,C,n_out", [(1, 8, 1), (1, 2048, 1000), (8, 520, 37), (9, 264, 66), (3, 2056, 5)])
+def test_pool_head_shapes(gpu_lib, B, C, n_out):
+    HW, T = 49, 2
+    d = WL.nets.Draw(B + C)
+    x, w = WL.nets.as_bf16_values(d.normal((B, HW, C))), WL.nets.as_bf16_values(d.normal((n_out, C), std=C ** -0.5))
+    bias = d.normal((n_out,))
+    k = [C, max(8, C // 2 // 8 * 8)]
+    route = (np.arange(B) % T).astype(np.int32)
+    perm, inv, off = gpu_lib.ds_route_bucket(dev(route, torch.int32), T)
+    got = host(gpu_lib.ds_pool_head(dev(x, torch.bfloat16), dev(w, torch.bfloat16), dev(bias), gpu_lib.make_groups(off, perm, k)))
+    for b in range(B):
+        c = k[route[b]]
+        want = x[b, :, :c].astype(np.float64).mean(axis=0) @ w[:, :c].T.astype(np.float64) + bias
+        assert relerr(got[b], want) < 1e-4
