@@ -212,8 +212,9 @@ def run_linear(args):
     print(json.dumps(out))
 
 
-GEMM_CLASSES = ("gemm", "gemm_taps", "conv3", "thin")          # kernel classes whose launches are the cost model's gemm / gemm_taps records
-KERNEL_OF = {"gemm": "gemm_kernel", "gemm_taps": "gemm_kernel", "conv3": "conv3_kernel", "thin": "thin_kernel"}
+GEMM_CLASSES = ("gemm", "gemm_taps", "conv3", "thin", "tail")          # kernel classes whose launches are the cost model's gemm / gemm_taps records
+KERNEL_OF = {"gemm": "gemm_kernel", "gemm_taps": "gemm_kernel", "conv3": "conv3_kernel", "thin": "thin_kernel",
+             "tail": "vit_tail_kernel"}
 RIDGE = PEAK_MFMA_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9)     # flop per byte above which the matrix peak is the roof
 
 
@@ -339,7 +340,7 @@ def run_net(workload, args, steps, warmup, with_cpu_baseline):
             # ... and each of its three kernels against the roof its own launches select: the launches whose flop per byte
             # lies above the ridge against the matrix peak, the others against HBM bandwidth
             per_kernel = {}
-            for kern in ("gemm_kernel", "conv3_kernel", "thin_kernel"):
+            for kern in ("gemm_kernel", "conv3_kernel", "thin_kernel", "vit_tail_kernel"):
                 mine = [r for r in gsel if r["kernel"] == kern]
                 if not mine:
                     continue
@@ -371,7 +372,7 @@ def run_net(workload, args, steps, warmup, with_cpu_baseline):
             if not cnt:
                 continue
             ck = {"conv3": "gemm_taps", "thin": "gemm"}.get(k, k)
-            c = cost.get(ck, {"flops": 0.0, "bytes": 0.0}) if k not in ("conv3", "thin", "gemm", "gemm_taps") else None
+            c = cost.get(ck, {"flops": 0.0, "bytes": 0.0}) if k not in ("conv3", "thin", "tail", "gemm", "gemm_taps") else None
             if c is None:
                 mine = [r for r in gsel if (r["kernel"], r["kind"]) == (KERNEL_OF[k], "gemm_taps" if k in ("gemm_taps", "conv3") else "gemm")
                         or (k == "conv3" and r["kernel"] == "conv3_kernel") or (k == "thin" and r["kernel"] == "thin_kernel")]

@@ -159,14 +159,15 @@ def vit_cost(arch, routes) -> Cost:
             break
         de, h, hid = full[:, 0] * on, full[:, 1] * on, full[:, 2] * on
         hd = h * arch["head_dim"]
-        c.add("layernorm", 8.0 * N * de.sum(), 4.0 * N * de.sum(), name=f"l{l}.ln1")
+        # everything behind the attention and the next block's LayerNorm is one launch
+        c.add("layernorm", 8.0 * N * de.sum(), 4.0 * N * de.sum(), name=f"l{l}.ln1", merge=l > 0)
         k_in, k_out = de, 3 * hd
         _gemm(c, "gemm", N, N, 1, k_in, k_out, name=f"l{l}.qkv")
         c.add("attention", 4.0 * N * N * hd.sum(), 2.0 * 4 * N * hd.sum(), name=f"l{l}.attention")
         _gemm(c, "gemm", N, N, 1, hd, de, residual=True, name=f"l{l}.proj+res")
-        c.add("layernorm", 8.0 * N * de.sum(), 4.0 * N * de.sum(), name=f"l{l}.ln2")
-        _gemm(c, "gemm", N, N, 1, de, hid, name=f"l{l}.fc1+gelu")
-        _gemm(c, "gemm", N, N, 1, hid, de, residual=True, name=f"l{l}.fc2+res")
+        c.add("layernorm", 8.0 * N * de.sum(), 4.0 * N * de.sum(), name=f"l{l}.ln2", merge=True)
+        _gemm(c, "gemm", N, N, 1, de, hid, name=f"l{l}.fc1+gelu", chained=True)
+        _gemm(c, "gemm", N, N, 1, hid, de, residual=True, name=f"l{l}.fc2+res", chained=True)
     de = full[:, 0]
     c.add("layernorm", 8.0 * de.sum(), 4.0 * de.sum(), name="final ln (class token)")
     c.add("head", 2.0 * arch["num_classes"] * de.sum(), 2.0 * de.sum() + 2.0 * arch["num_classes"] * de.max(), name="classifier")

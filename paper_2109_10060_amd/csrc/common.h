@@ -102,16 +102,12 @@ struct GemmArgs {
 };
 
 #ifdef __HIPCC__
-// Record of 128-row tile mt: read from the list, or (no list) found in the group offsets by the 64 lanes of the calling
-// wavefront side by side, groups from the last to the first as the list has them.  .x < 0: there is no such tile.
-__device__ __forceinline__ int4 ds_tile_record(const GemmArgs& a, int mt) {
-    if (a.mtiles) {
-        const int4 me = a.mtiles[mt];            // in bounds even beyond the live count; checked next
-        return mt < *a.n_mtiles ? me : make_int4(-1, 0, 0, 0);
-    }
-    const int lane = (int)(threadIdx.x & 63), g = a.gt.T - 1 - lane;
-    const int o0 = g >= 0 ? a.offsets[g] : 0, o1 = g >= 0 ? a.offsets[g + 1] : 0;
-    const int rg = (o1 - o0) * a.rows, n = (rg + DS_GEMM_BM - 1) / DS_GEMM_BM;
+// Record of the bm-row tile mt, found in the group offsets by the 64 lanes of the calling wavefront side by side; groups
+// from the last to the first, as the tile lists have them.  .x < 0: there is no such tile.
+__device__ __forceinline__ int4 ds_tile_record_of(const int32_t* offsets, int T, int rows, int mt, int bm) {
+    const int lane = (int)(threadIdx.x & 63), g = T - 1 - lane;
+    const int o0 = g >= 0 ? offsets[g] : 0, o1 = g >= 0 ? offsets[g + 1] : 0;
+    const int rg = (o1 - o0) * rows, n = (rg + bm - 1) / bm;
     int upto = n;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -122,7 +118,15 @@ __device__ __forceinline__ int4 ds_tile_record(const GemmArgs& a, int mt) {
     if (past == 0) return make_int4(-1, 0, 0, 0);
     const int q = __builtin_ctzll(past);
     const int before = __builtin_amdgcn_readlane(upto - n, q);
-    return make_int4(a.gt.T - 1 - q, (mt - before) * DS_GEMM_BM, __builtin_amdgcn_readlane(o0, q), __builtin_amdgcn_readlane(rg, q));
+    return make_int4(T - 1 - q, (mt - before) * bm, __builtin_amdgcn_readlane(o0, q), __builtin_amdgcn_readlane(rg, q));
+}
+// Record of 128-row tile mt: read from the list, or worked out where there is none
+__device__ __forceinline__ int4 ds_tile_record(const GemmArgs& a, int mt) {
+    if (a.mtiles) {
+        const int4 me = a.mtiles[mt];            // in bounds even beyond the live count; checked next
+        return mt < *a.n_mtiles ? me : make_int4(-1, 0, 0, 0);
+    }
+    return ds_tile_record_of(a.offsets, a.gt.T, a.rows, mt, DS_GEMM_BM);
 }
 #endif
 
@@ -260,6 +264,24 @@ int32_t ds_launch_attention(const bf16_t* q, const bf16_t* k, const bf16_t* v, b
                             int32_t ld, int32_t o_ld, int64_t o_sample_stride, const int32_t* slot_group,
                             const GroupTable& gt, int32_t B, int32_t N, int32_t H, int32_t head_dim, hipStream_t s);
 
+// everything of a transformer block behind its attention, and the next block's LayerNorm.  Weights in operand order:
+// [ceil(N / 32)][ceil(K / 16)] tiles of 1 KiB, element (half h, row r, i) of a tile = W[32 nb + r][16 kb + 8 h + i], zeros
+// beyond the stored matrix
+struct VitTailArgs {
+    const bf16_t* o;                     // attention output [slot][rows][o_ld]
+    int64_t o_ss, x_ss;                  // elements per slot
+    int32_t o_ld, rows;
+    bf16_t *x, *a;                       // residual stream (in place) and LN1 output of the next block (nullable), packed rows
+    const bf16_t *wp, *w1, *w2;          // projection, fc1, fc2
+    int32_t wp_bytes, w1_bytes, w2_bytes, kbp, kb1, kb2;   // size and 16-channel tiles per 32-row block
+    const float *bp, *b1, *b2, *g2, *be2, *gn, *ben;
+    float eps;
+    const int32_t* offsets;
+    GroupTable gt;                       // k_in = heads * head_dim, k_out = embedding slice, row = hidden slice
+};
+// DS_EUNSUPPORTED where a slice exceeds 416 channels (hidden: any) or its alignment
+int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s);
+
 // ---- small index helpers ---------------------------------------------------------
 int32_t ds_launch_set_offsets(int32_t* offsets, int32_t B, hipStream_t s);  // offsets[0..1] = {0, B}
 // key[b] = hi[b] * mul + (lo ? lo[b] : 0)
@@ -280,6 +302,7 @@ enum {
     DS_K_MISC,
     DS_K_CONV3,      // conv3_kernel (3x3 stride-1 layers with the input patch staged once)
     DS_K_THIN,       // thin_kernel (short reductions, one workgroup per row tile; with or without a chained second layer)
+    DS_K_TAIL,       // vit_tail_kernel (projection, MLP and LayerNorms of a transformer block)
     DS_K_COUNT
 };
 struct ProfScope {

@@ -33,7 +33,7 @@ __global__ __launch_bounds__(256, 2) void conv_f32_mfma_kernel(const float* x, c
 
     const int bid = blockIdx.x;
     const int pt = bid % n_ptiles, ot = (bid / n_ptiles) % n_otiles, slot = bid / (n_ptiles * n_otiles);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     // group of the slot: the number of groups that end at or before it (T <= 64)
     const bool past = lane < gt.T && offsets[lane + 1] <= slot;
     const int g = __builtin_popcountll(__ballot(past));

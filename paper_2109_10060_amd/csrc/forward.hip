@@ -613,6 +613,7 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
 struct VitDesc {
     int image, patch, D, H, dh, M, depth, N, T, classes;
     int rs;                  // entries per route: 3 (d_e, heads, hidden) or 4 (+ number of blocks the route runs)
+    int tiled;               // index of the tiled weights behind pbase, 0: none
     int stem_dim, gate_hidden, pbase;   // stem width (0: none), gate MLP width, index of embed.w in params
     const int32_t* routes;
 };
@@ -638,7 +639,10 @@ bool parse_vit(const ds_net* net, VitDesc* d) {
         else return false;
         d->routes = v + 10;
     }
-    return net->n_params == d->pbase + 4 + 12 * d->depth + 4;
+    // the linear weights once more in operand order: optional, three per block behind the other parameters
+    const int plain = d->pbase + 4 + 12 * d->depth + 4;
+    d->tiled = net->n_params == plain + 3 * d->depth ? plain - d->pbase : 0;
+    return net->n_params == plain || d->tiled;
 }
 
 struct VitPlan {
@@ -814,6 +818,7 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
     RC(ds_launch_cls_rows(xv, (const bf16_t*)P[2], (const bf16_t*)P[3], p.slot_group, gq, B, s));
     const float eps = 1e-6f;
     const GroupTable fq = gq;      // every route, for the final LayerNorm and the classifier
+    bool normed = false;           // p.a already holds this block's LN1 output
     for (int l = 0; l < d.depth; ++l) {
         const void* const* L = P + 4 + 12 * l;
         // dynamic depth: a route that runs fewer than l + 1 blocks gets empty slices from here on, so
@@ -830,12 +835,38 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
             }
             if (!any) break;
         }
-        RC(ds_launch_layernorm(xv, av, (const float*)L[0], (const float*)L[1], eps, p.slot_group, gq, B, d.N, 0, d.N, s));
+        if (!normed)
+            RC(ds_launch_layernorm(xv, av, (const float*)L[0], (const float*)L[1], eps, p.slot_group, gq, B, d.N, 0, d.N, s));
+        normed = false;
         RC(linear_gemm(p.a, x_ss, 0, (const bf16_t*)L[2], d.D, (const float*)L[3], nullptr, 0, 0, 0, p.qkv,
                        (int64_t)d.N * Hd, Hd, 0, d.N, 3, (int64_t)Hd * d.D, (int64_t)p.qkv_seg, Hd, p.offs, ml_t, gq,
                        DS_ACT_NONE, s));
         RC(ds_launch_attention(p.qkv, p.qkv + p.qkv_seg, p.qkv + 2 * p.qkv_seg, p.o, (int64_t)d.N * Hd, Hd, Hd,
                                (int64_t)d.N * Hd, p.slot_group, gq, B, d.N, d.H, d.dh, s));
+        if (d.tiled) {
+            const void* const* Q = P + d.tiled + 3 * l;
+            VitTailArgs ta;
+            memset(&ta, 0, sizeof(ta));
+            ta.o = p.o; ta.o_ss = (int64_t)d.N * Hd; ta.o_ld = Hd; ta.x = p.x; ta.x_ss = x_ss; ta.rows = d.N;
+            ta.a = l + 1 < d.depth ? p.a : nullptr;
+            ta.kbp = (Hd + 15) / 16 | 1; ta.kb1 = (d.D + 15) / 16 | 1; ta.kb2 = (d.M + 15) / 16 | 1;
+            ta.wp = (const bf16_t*)Q[0]; ta.w1 = (const bf16_t*)Q[1]; ta.w2 = (const bf16_t*)Q[2];
+            ta.wp_bytes = (d.D + 31) / 32 * ta.kbp * 1024; ta.w1_bytes = (d.M + 31) / 32 * ta.kb1 * 1024;
+            ta.w2_bytes = (d.D + 31) / 32 * ta.kb2 * 1024;
+            ta.bp = (const float*)L[5]; ta.g2 = (const float*)L[6]; ta.be2 = (const float*)L[7];
+            ta.b1 = (const float*)L[9]; ta.b2 = (const float*)L[11];
+            if (l + 1 < d.depth) { ta.gn = (const float*)L[12]; ta.ben = (const float*)L[13]; }
+            ta.eps = eps; ta.offsets = p.offs;
+            ta.gt = gp;
+            for (int t = 0; t < T; ++t) ta.gt.row[t] = gp.k_out[t] > 0 ? g1.k_out[t] : 0;
+            const int32_t rc = ds_launch_vit_tail(ta, B, s);
+            if (rc == DS_OK) {
+                normed = l + 1 < d.depth;
+                RC(tap_block(taps, l, p.x, x_ss, 0, p.perm, p.slot_group, g2, B, d.N, d.D, s));
+                continue;
+            }
+            if (rc != DS_EUNSUPPORTED) return rc;
+        }
         RC(linear_gemm(p.o, (int64_t)d.N * Hd, Hd, (const bf16_t*)L[4], Hd, (const float*)L[5], p.x, x_ss, 0, 1, p.x, x_ss,
                        0, 0, d.N, 1, 0, 0, 0, p.offs, ml_t, gp, DS_ACT_NONE, s));
         RC(ds_launch_layernorm(xv, av, (const float*)L[6], (const float*)L[7], eps, p.slot_group, gq, B, d.N, 0, d.N, s));

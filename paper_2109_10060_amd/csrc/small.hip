@@ -51,7 +51,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(const GemmArgs a, c
     if (seg >= a.n_seg) return;
     const int n0 = (y - seg * ntiles) * BN;
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int ks = wave % KS, wc = wave / KS;                 // share of the reduction, column tile
     const int nw0 = n0 + wc * WBN;
     const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc((void*)a.A, 0, 0x7fffffff, 0x00020000);

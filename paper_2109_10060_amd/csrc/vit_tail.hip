@@ -1,0 +1,369 @@
+// The rest of a transformer block behind its attention, in one kernel (Section 3.2, Eq. 15-19):
+//   x += proj(o);  x += fc2(gelu(fc1(LN2(x))));  a = LN1 of the next block(x)
+// for every route group, slices as everywhere: the leading block of the stored weights.
+//
+// As five launches (projection, LayerNorm, two linear layers, next LayerNorm) a block moved the residual stream seven
+// times and the hidden activations twice through memory, and its reductions of 192..416 channels spent their time in the
+// head and the epilogue of the workgroups.  Here a workgroup owns BM = 32 R rows from the attention output to the next
+// block's normalised input; the hidden layer never leaves the compute unit (256 columns at a time in LDS).
+//
+// What bounds it: the weights' way from L2 into a compute unit (about 50 bytes a clock, all of the block's weights once per
+// workgroup), the matrix pipes and the vector ALU (GELU, LayerNorm), in that order and only partly side by side.  So the
+// weights are kept in operand order (32 rows x 16 channels = 64 lanes x 16 bytes, tiles of 1 KiB): a wavefront reads each
+// operand as one contiguous kilobyte straight into registers, D of them in flight, and LDS serves the activations alone.
+// Each of the NW = 12 (13 above 384 channels) wavefronts owns one 32-column block of the block's width and of every
+// HC = 32 NW columns of the hidden layer; R row blocks share every weight operand.
+// DS-ViT, 256 images: 161 us (projection 29, LayerNorms 12 + 12, fc1 66, fc2 54, less launch overlap) -> 131 us per block;
+// 64 images 76 -> 55 us; 16 images 48 -> 36 us.
+//
+// Sums run in the order of gemm_kernel's and layernorm16_kernel's, so the results are the same bits.
+#include <type_traits>
+
+#include "gelu.h"
+
+namespace {
+
+constexpr int PA = 424;        // row pitch in elements of the activation tile (<= 416 channels); like the hidden tile's an odd
+                               // number of 16-byte chunks, so 32 rows read without conflicts
+
+__device__ __forceinline__ void unpack8(const uint4 q, float* v) {
+    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[2 * i] = __uint_as_float(w[i] << 16);
+        v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+    }
+}
+__device__ __forceinline__ uint4 pack8(const float* v) {
+    return make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]), f2bf2(v[4], v[5]), f2bf2(v[6], v[7]));
+}
+
+// LayerNorm of one row held by 16 lanes, lane l with the 8-channel chunks l, l + 16, l + 32, l + 48; the arithmetic and
+// the order of layernorm16_kernel
+__device__ __forceinline__ void row_norm(const float (&v)[4][8], int d, int l16, float eps, const float* gamma,
+                                         const float* beta, uint4 (&out)[4]) {
+    float s = 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if ((k * 16 + l16) * 8 < d) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s += v[k][i];
+        }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 16);
+    const float mu = s / (float)d;
+    float q = 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if ((k * 16 + l16) * 8 < d) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float t = v[k][i] - mu;
+                q += t * t;
+            }
+        }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) q += __shfl_xor(q, o, 16);
+    const float rstd = 1.0f / sqrtf(q / (float)d + eps);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int ch = (k * 16 + l16) * 8;
+        if (ch < d) {
+            const float4 g0 = *(const float4*)(gamma + ch), g1 = *(const float4*)(gamma + ch + 4);
+            const float4 b0 = *(const float4*)(beta + ch), b1 = *(const float4*)(beta + ch + 4);
+            const float gm[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+            const float bt[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+            float o8[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) o8[i] = (v[k][i] - mu) * rstd * gm[i] + bt[i];
+            out[k] = pack8(o8);
+        }
+    }
+}
+
+// NW wavefronts (one column block of 32 each), 32 R rows, D operands of a wavefront in flight
+template <int NW, int R, int D>
+__global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const VitTailArgs a) {
+    constexpr int BM = 32 * R, HC = 32 * NW, PH = HC + 8, RP = 4 * NW, NI = (BM + RP - 1) / RP;   // RP: rows of a row phase
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    bf16_t* As = (bf16_t*)smem;                         // [BM][PA]
+    bf16_t* Hs = As + BM * PA;                          // [BM][PH]
+
+    const int4 me = ds_tile_record_of(a.offsets, a.gt.T, a.rows, (int)blockIdx.x, BM);
+    if (me.x < 0) return;
+    const int g = me.x, grow0 = me.y, slot0 = me.z, rows_g = me.w;
+    const int kin = a.gt.k_in[g], de = a.gt.k_out[g], hid = a.gt.row[g];
+    if (de <= 0) return;
+
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
+    const int l16 = tid & 15, prow = tid >> 4;          // row phases: 16 lanes a row, RP rows at a time
+    const bool con = w * 32 < de;                        // this wavefront has a column block
+    const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc((void*)a.wp, 0, a.wp_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t r1 = __builtin_amdgcn_make_buffer_rsrc((void*)a.w1, 0, a.w1_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t r2 = __builtin_amdgcn_make_buffer_rsrc((void*)a.w2, 0, a.w2_bytes, 0x00020000);
+    auto tile = [&](const __amdgpu_buffer_rsrc_t& rs, uint32_t vo, int t) -> bf16x8_t {   // a whole kilobyte per wavefront
+        const auto q = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)vo, t * 1024, 0);
+        return __builtin_bit_cast(bf16x8_t, q);
+    };
+
+    // ---- rows of this thread's 16-lane group: attention output to LDS, residual rows to registers ----------------------
+    int64_t xoff[NI];
+    bool live[NI];
+    uint4 xr[NI][4];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        const bool in = BM % RP == 0 || prow + RP * i < BM;
+        const int m = grow0 + prow + RP * i;
+        live[i] = in && m < rows_g;
+        const int mm = live[i] ? m : grow0;
+        const int sl = mm / a.rows, p = mm - sl * a.rows, slot = slot0 + sl;
+        xoff[i] = (int64_t)slot * a.x_ss + (int64_t)p * de;
+        const bf16_t* orow = a.o + (int64_t)slot * a.o_ss + (int64_t)p * a.o_ld;
+        uint4 q[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int ch = (k * 16 + l16) * 8;
+            q[k] = make_uint4(0, 0, 0, 0);
+            if (ch < kin) q[k] = *(const uint4*)(orow + ch);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int ch = (k * 16 + l16) * 8;
+            if (in && ch < PA) *(uint4*)(As + (prow + RP * i) * PA + ch) = q[k];   // zeros beyond the slice
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int ch = (k * 16 + l16) * 8;
+            xr[i][k] = make_uint4(0, 0, 0, 0);
+            if (ch < de) xr[i][k] = *(const uint4*)(a.x + xoff[i] + ch);
+        }
+    }
+
+    // ---- acc2[r] += W[column block w] . act^T over KK 16-channel steps -----------------------------------------------------
+    f32x16_t acc2[R];
+    auto clear2 = [&]() {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc2[r][v] = 0.f;
+    };
+    // Every step is straight-line code: operand requests are unconditional (a step past the end asks for an address out of
+    // range and gets zeros without traffic), so the number in flight is known where a product waits for the oldest, and the
+    // LDS reads of a step are issued ahead of the products of the step before it.  The number of steps is rounded up to D; the
+    // extra steps multiply zero weights with finite LDS contents (of the neighbouring rows, at the end of the tile).
+    const uint32_t lane16 = (uint32_t)lane * 16;
+    constexpr uint32_t OOB = 0x7fff0000u;                // or-ed into the lane offset
+    bf16x8_t ring[D];
+    auto start = [&](bf16x8_t (&ring)[D], const __amdgpu_buffer_rsrc_t& rs, int t0, int KK) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) ring[j] = tile(rs, lane16 | (j < KK ? 0u : OOB), t0 + j);
+    };
+    auto walk = [&](f32x16_t (&acc)[R], bf16x8_t (&ring)[D], const __amdgpu_buffer_rsrc_t& rs, int t0, int KK, const bf16_t* act, int pitch) {
+        const bf16_t* base = act + l32 * pitch + lhi * 8;
+        bf16x8_t f[2][R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) f[0][r] = *(const bf16x8_t*)(base + r * 32 * pitch);
+        for (int k0 = 0; k0 < KK; k0 += D) {
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                const int kk = k0 + j;
+#pragma unroll
+                for (int r = 0; r < R; ++r) f[(j + 1) & 1][r] = *(const bf16x8_t*)(base + r * 32 * pitch + (kk + 1) * 16);
+#pragma unroll
+                for (int r = 0; r < R; ++r) acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[j], f[j & 1][r], acc[r], 0, 0, 0);
+                ring[j] = tile(rs, lane16 | (kk + D < KK ? 0u : OOB), t0 + kk + D);
+                __builtin_amdgcn_sched_barrier(0);       // (the compiler would sink the reads to their use)
+            }
+        }
+    };
+    // tile (in LDS, bf16) = tile + acc2 + bias on the elements this lane accumulated: 4 channels of one row at a time
+    auto add_columns = [&](const float* bias) {
+        if (!con) return;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int ch = w * 32 + 8 * q + 4 * lhi;
+            if (ch >= de) continue;
+            const float4 h = *(const float4*)(bias + ch);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                uint2* p = (uint2*)(As + (r * 32 + l32) * PA + ch);
+                const uint2 res = *p;
+                const f32x16_t& t = acc2[r];
+                float v0 = t[4 * q] + h.x, v1 = t[4 * q + 1] + h.y, v2 = t[4 * q + 2] + h.z, v3 = t[4 * q + 3] + h.w;
+                v0 += __uint_as_float(res.x << 16);
+                v1 += __uint_as_float(res.x & 0xffff0000u);
+                v2 += __uint_as_float(res.y << 16);
+                v3 += __uint_as_float(res.y & 0xffff0000u);
+                *p = make_uint2(f2bf2(v0, v1), f2bf2(v2, v3));
+            }
+        }
+    };
+    auto rows_to_lds = [&]() {
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int ch = (k * 16 + l16) * 8;
+                if (ch < de && (BM % RP == 0 || prow + RP * i < BM)) *(uint4*)(As + (prow + RP * i) * PA + ch) = xr[i][k];
+            }
+    };
+
+    // ---- projection + residual ------------------------------------------------------------------------------------------
+    for (int i = tid; i < BM; i += 64 * NW) *(uint4*)(Hs + i * PH + HC) = make_uint4(0, 0, 0, 0);   // pads: read by extra steps
+    if (tid < 16) *(uint2*)(Hs + 4 * tid) = make_uint2(0, 0);
+    clear2();
+    if (con) start(ring, rp, w * a.kbp, kin >> 4);
+    __syncthreads();
+    if (con) walk(acc2, ring, rp, w * a.kbp, kin >> 4, As, PA);
+    __syncthreads();
+    rows_to_lds();
+    __syncthreads();
+    add_columns(a.bp);
+    __syncthreads();
+    // ---- x to memory, LN2 in place ---------------------------------------------------------------------------------------
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        if (BM % RP != 0 && prow + RP * i >= BM) continue;     // whole 16-lane groups
+        float v[4][8];
+        uint4 o[4];
+        bf16_t* row = As + (prow + RP * i) * PA;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int ch = (k * 16 + l16) * 8;
+            if (ch < de) {
+                const uint4 q = *(const uint4*)(row + ch);
+                if (live[i]) *(uint4*)(a.x + xoff[i] + ch) = q;
+                unpack8(q, v[k]);
+            }
+        }
+        row_norm(v, de, l16, a.eps, a.g2, a.be2, o);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int ch = (k * 16 + l16) * 8;
+            if (ch < de) *(uint4*)(row + ch) = o[k];
+            else if (ch < PA) *(uint4*)(row + ch) = make_uint4(0, 0, 0, 0);
+        }
+    }
+    __syncthreads();
+
+    // ---- MLP, HC hidden columns at a time ----------------------------------------------------------------------------------
+    clear2();
+    const int KB = (de + 15) >> 4, nchunk = (hid + HC - 1) / HC;
+    if (w * 32 < hid) start(ring, r1, w * a.kb1, KB);
+    for (int hc = 0; hc < nchunk; ++hc) {
+        const int hb = hc * NW + w;                      // 32-column block of the hidden layer
+        const bool hon = hb * 32 < hid;
+        const int KK = (min(HC, hid - hc * HC) + 15) >> 4, t2 = w * a.kb2 + hc * 2 * NW;
+        f32x16_t acc1[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc1[r][v] = 0.f;
+        if (hon) walk(acc1, ring, r1, hb * a.kb1, KB, As, PA);
+        if (con) start(ring, r2, t2, KK);                // under way during the GELU and the barriers
+        uint2 ho[4][R];
+        auto gelu = [&](auto put) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int ch = hb * 32 + 8 * q + 4 * lhi;    // (4 channels are inside the hidden slice or outside it)
+                const bool ok = ch < hid;
+                float4 h = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (ok) h = *(const float4*)(a.b1 + ch);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    uint2 o = make_uint2(0, 0);
+                    if (ok)
+                        o = gelu_bf16x4(acc1[r][4 * q] + h.x, acc1[r][4 * q + 1] + h.y, acc1[r][4 * q + 2] + h.z, acc1[r][4 * q + 3] + h.w);
+                    put(q, r, o);
+                }
+            }
+        };
+        auto write = [&](int q, int r, uint2 o) { *(uint2*)(Hs + (r * 32 + l32) * PH + w * 32 + 8 * q + 4 * lhi) = o; };
+        if constexpr (R < 3) gelu([&](int q, int r, uint2 o) { ho[q][r] = o; });
+        __syncthreads();                                 // the previous columns have been read
+        if constexpr (R < 3) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int r = 0; r < R; ++r) write(q, r, ho[q][r]);
+        } else {
+            gelu(write);
+        }
+        __syncthreads();
+        if (con) walk(acc2, ring, r2, t2, KK, Hs, PH);
+        if ((hb + NW) * 32 < hid) start(ring, r1, (hb + NW) * a.kb1, KB);
+    }
+    // the residual rows of the last sum: this thread wrote them itself after the projection
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int ch = (k * 16 + l16) * 8;
+            xr[i][k] = make_uint4(0, 0, 0, 0);
+            if (ch < de && live[i]) xr[i][k] = *(const uint4*)(a.x + xoff[i] + ch);
+        }
+    rows_to_lds();                                       // every wavefront is past its last read of the activation tile
+    __syncthreads();
+    add_columns(a.b2);
+    __syncthreads();
+    // ---- x, and the next block's LN1 -------------------------------------------------------------------------------------------
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        if (BM % RP != 0 && prow + RP * i >= BM) continue;     // whole 16-lane groups
+        float v[4][8];
+        uint4 o[4];
+        const bf16_t* row = As + (prow + RP * i) * PA;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int ch = (k * 16 + l16) * 8;
+            if (ch < de) {
+                const uint4 q = *(const uint4*)(row + ch);
+                if (live[i]) *(uint4*)(a.x + xoff[i] + ch) = q;
+                unpack8(q, v[k]);
+            }
+        }
+        if (a.a) {
+            row_norm(v, de, l16, a.eps, a.gn, a.ben, o);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int ch = (k * 16 + l16) * 8;
+                if (ch < de && live[i]) *(uint4*)(a.a + xoff[i] + ch) = o[k];
+            }
+        }
+    }
+}
+
+template <int NW, int R, int D>
+int32_t launch(const VitTailArgs& a, int64_t tiles, hipStream_t s) {
+    constexpr int SMEM = 32 * R * (PA + 32 * NW + 8) * 2 + 64;   // (a step's operands are read one step ahead)
+    const int32_t rc = ds_reserve_lds((const void*)vit_tail_kernel<NW, R, D>, SMEM, "transformer block tail");
+    if (rc) return rc;
+    ProfScope prof(DS_K_TAIL, s);
+    hipLaunchKernelGGL((vit_tail_kernel<NW, R, D>), dim3((unsigned)tiles), dim3(64 * NW), SMEM, s, a);
+    DS_CHECK_LAUNCH("transformer block tail");
+    return DS_OK;
+}
+
+}  // namespace
+
+// Rows per workgroup.  A workgroup streams all weights of the block whatever its rows (2.7 MB at full width, ~25 us at what
+// one compute unit takes in), so many rows each are better -- as long as there is a workgroup for every compute unit.
+// Measured per launch on DS-ViT: 16 images 35.6 / 43.0 / 54.8 us with 32 / 64 / 96 rows, 64 images 56.4 / 54.7 / 67.2,
+// 256 images 181 / 136 / 131.
+int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {
+    int dmax = 0;
+    for (int t = 0; t < a.gt.T; ++t) {
+        if (a.gt.k_out[t] <= 0) continue;
+        dmax = a.gt.k_out[t] > dmax ? a.gt.k_out[t] : dmax;
+        if (a.gt.k_in[t] > PA - 8 || a.gt.k_out[t] > PA - 8 || a.gt.row[t] <= 0 || (a.gt.k_in[t] % 16) || (a.gt.k_out[t] % 8) ||
+            (a.gt.row[t] % 8))
+            return DS_EUNSUPPORTED;
+    }
+    const int64_t groups = B < a.gt.T ? B : a.gt.T, n = (int64_t)B * a.rows;
+    auto tiles = [&](int bm) { return (n - groups) / bm + groups; };
+    const bool two = tiles(64) >= 224;
+    if (dmax > 384)                                      // 13 column blocks: 128 registers per lane, at most 64 rows
+        return two ? launch<13, 2, 4>(a, tiles(64), s) : launch<13, 1, 4>(a, tiles(32), s);
+    if (tiles(96) >= 448) return launch<12, 3, 4>(a, tiles(96), s);
+    return two ? launch<12, 2, 4>(a, tiles(64), s) : launch<12, 1, 8>(a, tiles(32), s);
+}

@@ -61,6 +61,17 @@ def _stem(w, device):
     return _dev(np.transpose(w, (2, 3, 1, 0)).reshape(-1, co), torch.bfloat16, device)
 
 
+def _operand_tiles(w):
+    """[N, K] bf16 -> [ceil(N/32)][ceil(K/16) | 1] tiles of 32 x 16 in the order of a matrix instruction's lanes: half of the
+    16 channels, row, 8 channels.  The odd number of 1 KiB tiles per row of tiles keeps the rows, which the wavefronts of a
+    workgroup stream side by side, off the same L2 channels."""
+    n, k = w.shape
+    nb, kb = (n + 31) // 32, (k + 15) // 16 | 1
+    t = torch.zeros((nb * 32, kb * 16), dtype=w.dtype, device=w.device)
+    t[:n, :k] = w
+    return t.view(nb, 32, kb, 2, 8).permute(0, 2, 3, 1, 4).contiguous()
+
+
 def build_mbnet(arch: dict, p: dict, device="cuda:0") -> Net:
     from . import DS_ARCH_MBNET
     bf, f32 = torch.bfloat16, torch.float32
@@ -140,4 +151,8 @@ def build_vit(arch: dict, p: dict, device="cuda:0") -> Net:
               _dev(p[q + ".fc2.w"], bf, device), _dev(p[q + ".fc2.b"], f32, device)]
     t += [_dev(p["ln.g"], f32, device), _dev(p["ln.b"], f32, device), _dev(p["head.w"], bf, device),
           _dev(p["head.b"], f32, device)]
+    # the weights behind the attention once more in the order in which the fused block tail reads them
+    first = len(t) - 4 - 12 * arch["depth"]
+    for l in range(arch["depth"]):
+        t += [_operand_tiles(t[first + 12 * l + i]) for i in (4, 8, 10)]
     return Net(DS_ARCH_VIT_STEM if C else DS_ARCH_VIT, ints, t, arch["num_classes"], 1, arch["T"])

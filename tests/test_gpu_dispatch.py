@@ -146,3 +146,48 @@ def test_pool_head_shapes(gpu_lib, B, C, n_out):
         c = k[route[b]]
         want = x[b, :, :c].astype(np.float64).mean(axis=0) @ w[:, :c].T.astype(np.float64) + bias
         assert relerr(got[b], want) < 1e-4
+
+
+# Token networks: an image's logits are the same bits in every batch size (tiles of 32, 64 and 96 rows behind the attention,
+# short and 128-row linear layers, 12 and 13 wavefronts), and with or without the weights in operand order.
+@pytest.mark.parametrize("big", [False, True])
+def test_vit_logits_do_not_depend_on_the_batch(gpu_lib, big):
+    kw = dict(embed=416, heads=8, head_dim=48, mlp=1664, depth=2, routes="pp", stem_dim=24, patch=8) if big else dict(depth=2)
+    arch = WL.vit_arch(**kw)
+    net = gpu_lib.build_vit(arch, WL.vit_params(arch, 5), DEV)
+    B = 225
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(3)
+    imgs = torch.randn((B, 3, arch["image"], arch["image"]), generator=gen, device=DEV).to(torch.bfloat16)
+    over = (torch.arange(B, device=DEV, dtype=torch.int32) * 7 % arch["T"])[None].contiguous()
+    full, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
+    assert torch.isfinite(full).all() and full.abs().max() > 0
+    for lo, hi in ((0, 1), (3, 8), (20, 60), (100, 190)):
+        part, _ = gpu_lib.ds_forward(net, imgs[lo:hi].contiguous(), route_override=over[:, lo:hi].contiguous())
+        # (the classifier sums in another order for a few images)
+        assert relerr(host(part), host(full[lo:hi])) < 1e-5, (lo, hi)
+    net.c_struct.n_params -= 3 * arch["depth"]
+    plain, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
+    assert torch.equal(plain, full)
+
+
+# hidden activations around the limits of the GELU's short evaluation: every bf16 result equals the exact one's
+def test_gelu_rounding_matches_the_linear_layer(gpu_lib):
+    arch = WL.vit_arch(depth=1)
+    p = WL.vit_params(arch, 6)
+    for k in ("l0.fc1.w", "l0.fc1.b"):
+        p[k] = p[k] * 8.0                                   # pre-activations far beyond +-2.5 beside small ones
+    net = gpu_lib.build_vit(arch, p, DEV)
+    B = 48
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(4)
+    imgs = torch.randn((B, 3, arch["image"], arch["image"]), generator=gen, device=DEV).to(torch.bfloat16)
+    over = torch.arange(B, device=DEV, dtype=torch.int32)[None].contiguous()
+    out = []
+    for tiled in (True, False):
+        if not tiled:
+            net.c_struct.n_params -= 3 * arch["depth"]
+        tap = torch.zeros((B, arch["tokens"], arch["embed"]), dtype=torch.bfloat16, device=DEV)
+        logits, _ = gpu_lib.ds_forward_taps(net, imgs, {0: tap}, route_override=over)
+        out.append((logits, tap))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
