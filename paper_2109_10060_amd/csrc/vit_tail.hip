@@ -26,6 +26,10 @@ namespace {
 constexpr int PA = 424;        // row pitch in elements of the activation tile (<= 416 channels); like the hidden tile's an odd
                                // number of 16-byte chunks, so 32 rows read without conflicts
 
+// elements behind the hidden tile: its last row's extra steps and the read-ahead end there (26 steps of 13 wavefronts, rounded
+// up to 28, and one more: column 479 of a pitch of 424)
+constexpr int TAIL = 64;
+
 __device__ __forceinline__ void unpack8(const uint4 q, float* v) {
     const uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
@@ -211,6 +215,7 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     // ---- projection + residual ------------------------------------------------------------------------------------------
     for (int i = tid; i < BM; i += 64 * NW) *(uint4*)(Hs + i * PH + HC) = make_uint4(0, 0, 0, 0);   // pads: read by extra steps
     if (tid < 16) *(uint2*)(Hs + 4 * tid) = make_uint2(0, 0);
+    if (tid < TAIL / 8) *(uint4*)(Hs + BM * PH + 8 * tid) = make_uint4(0, 0, 0, 0);
     clear2();
     if (con) start(ring, rp, w * a.kbp, kin >> 4);
     __syncthreads();
@@ -335,7 +340,7 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
 
 template <int NW, int R, int D>
 int32_t launch(const VitTailArgs& a, int64_t tiles, hipStream_t s) {
-    constexpr int SMEM = 32 * R * (PA + 32 * NW + 8) * 2 + 64;   // (a step's operands are read one step ahead)
+    constexpr int SMEM = 32 * R * (PA + 32 * NW + 8) * 2 + TAIL * 2;
     const int32_t rc = ds_reserve_lds((const void*)vit_tail_kernel<NW, R, D>, SMEM, "transformer block tail");
     if (rc) return rc;
     ProfScope prof(DS_K_TAIL, s);

@@ -162,7 +162,7 @@ def test_vit_logits_do_not_depend_on_the_batch(gpu_lib, big):
     over = (torch.arange(B, device=DEV, dtype=torch.int32) * 7 % arch["T"])[None].contiguous()
     full, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
     assert torch.isfinite(full).all() and full.abs().max() > 0
-    for lo, hi in ((0, 1), (3, 8), (20, 60), (100, 190)):
+    for lo, hi in ((0, 1), (1, 2), (3, 8), (7, 10), (20, 60), (100, 190)):
         part, _ = gpu_lib.ds_forward(net, imgs[lo:hi].contiguous(), route_override=over[:, lo:hi].contiguous())
         # (the classifier sums in another order for a few images)
         assert relerr(host(part), host(full[lo:hi])) < 1e-5, (lo, hi)
