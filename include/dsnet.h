@@ -287,8 +287,8 @@ int32_t ds_sliced_mhsa(const void* x, int32_t B, int32_t N, int32_t D_e, const v
  *             wproj bf16 [embed][heads*head_dim], bproj, ln2.g, ln2.b, fc1.w bf16 [mlp][embed], fc1.b,
  *             fc2.w bf16 [embed][mlp], fc2.b,
  *           ln.g, ln.b, head.w bf16 [num_classes][embed], head.b,
- *           optionally, per layer: wproj, fc1.w, fc2.w once more as [ceil(N/32)][ceil(K/16) | 1] tiles of 1 KiB (bf16,
- *             [k half][32 rows][8 channels], zeros beyond the matrix); the layers behind the attention then run as one launch
+ *           optionally, per layer: wproj, fc1.w, fc2.w, wqkv (segment by segment) once more as [ceil(N/32)][ceil(K/16) | 1] tiles of 1 KiB (bf16,
+ *             [k half][32 rows][8 channels], zeros beyond the matrix); the block's layers then run fused around the attention
  *   Routes come from logit_bias (argmax) or route_override; one of them is required. */
 #define DS_ARCH_VIT    3
 /* DS_ARCH_VIT_STEM: DS_ARCH_VIT behind the convolutional stem of Section 3.4 (blocks [c, ds, ds, c]): a 7x7

@@ -264,21 +264,38 @@ int32_t ds_launch_attention(const bf16_t* q, const bf16_t* k, const bf16_t* v, b
                             int32_t ld, int32_t o_ld, int64_t o_sample_stride, const int32_t* slot_group,
                             const GroupTable& gt, int32_t B, int32_t N, int32_t H, int32_t head_dim, hipStream_t s);
 
-// everything of a transformer block behind its attention, and the next block's LayerNorm.  Weights in operand order:
-// [ceil(N / 32)][ceil(K / 16)] tiles of 1 KiB, element (half h, row r, i) of a tile = W[32 nb + r][16 kb + 8 h + i], zeros
+// everything of a transformer block behind its attention.  Weights in operand order: [ceil(N / 32)][kb] tiles of 1 KiB, element (half h, row r, i) of a tile = W[32 nb + r][16 kb + 8 h + i], zeros
 // beyond the stored matrix
 struct VitTailArgs {
     const bf16_t* o;                     // attention output [slot][rows][o_ld]
     int64_t o_ss, x_ss;                  // elements per slot
     int32_t o_ld, rows;
-    bf16_t *x, *a;                       // residual stream (in place) and LN1 output of the next block (nullable), packed rows
+    bf16_t* x;                           // residual stream, in place, packed rows
     const bf16_t *wp, *w1, *w2;          // projection, fc1, fc2
     int32_t wp_bytes, w1_bytes, w2_bytes, kbp, kb1, kb2;   // size and 16-channel tiles per 32-row block
-    const float *bp, *b1, *b2, *g2, *be2, *gn, *ben;
+    const float *bp, *b1, *b2, *g2, *be2;
     float eps;
     const int32_t* offsets;
     GroupTable gt;                       // k_in = heads * head_dim, k_out = embedding slice, row = hidden slice
 };
+// y = act(LN(x) W^T + b) + residual on tiled weights
+struct VitLinearArgs {
+    const bf16_t* x;
+    int64_t x_ss, y_ss, y_seg;           // elements per slot, per output segment
+    int32_t x_ld, y_ld, rows;            // <= 0: packed rows
+    const float *gamma, *beta;           // LayerNorm of the rows (nullable)
+    float eps;
+    const bf16_t* w;
+    int32_t w_bytes, kb, seg_blocks, n_seg;   // 16-channel tiles and 32-row blocks per segment as stored
+    const float* bias;
+    int32_t bias_seg, act;
+    const bf16_t* res;                   // addressed like y, nullable; may be y
+    bf16_t* y;
+    const int32_t* offsets;
+    GroupTable gt;
+};
+// DS_EUNSUPPORTED beyond 416 input channels with a LayerNorm, 1664 without
+int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s);
 // DS_EUNSUPPORTED where a slice exceeds 416 channels (hidden: any) or its alignment
 int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s);
 

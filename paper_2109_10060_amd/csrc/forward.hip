@@ -639,9 +639,9 @@ bool parse_vit(const ds_net* net, VitDesc* d) {
         else return false;
         d->routes = v + 10;
     }
-    // the linear weights once more in operand order: optional, three per block behind the other parameters
+    // the linear weights once more in operand order: optional, four per block behind the other parameters
     const int plain = d->pbase + 4 + 12 * d->depth + 4;
-    d->tiled = net->n_params == plain + 3 * d->depth ? plain - d->pbase : 0;
+    d->tiled = net->n_params == plain + 4 * d->depth ? plain - d->pbase : 0;
     return net->n_params == plain || d->tiled;
 }
 
@@ -705,6 +705,49 @@ int32_t linear_gemm(const bf16_t* A, int64_t a_ss, int a_ld, const bf16_t* Wt, i
     a.offsets = offsets; a.mtiles = ds_mtile_entries(ml.list); a.n_mtiles = ds_mtile_count(ml.list);
     a.act = act; a.out_f32 = 0; a.gt = gt; a.B = ml.B; a.ordered = 1;
     return ds_launch_gemm(a, ml.cap, max_out(gt), s);
+}
+
+// projection, LN2 and MLP of one block on the tiled weights Q; L: the block's other parameters
+int32_t vit_behind_attention(const VitDesc& d, const void* const* L, const void* const* Q, const VitPlan& p, const GroupTable& gp,
+                             const GroupTable& g1, const GroupTable& g2, int B, float eps, hipStream_t s) {
+    const int Hd = d.H * d.dh;
+    const int64_t x_ss = (int64_t)d.N * d.D;
+    const int kbp = (Hd + 15) / 16 | 1, kb1 = (d.D + 15) / 16 | 1, kb2 = (d.M + 15) / 16 | 1;
+    const int nbd = (d.D + 31) / 32, nbm = (d.M + 31) / 32;
+    // up to about 56 tiles of 32 rows three launches over many workgroups beat one whose every workgroup streams all weights
+    // (5 images 29 against 35 us); above, they cost what their extra passes and workgroups do (16 images 40 against 33 us)
+    const int groups = B < d.T ? B : d.T;
+    const bool few = d.M <= 1664 && ((int64_t)B * d.N - groups) / 32 + groups <= 56;
+    if (!few) {
+        VitTailArgs ta;
+        memset(&ta, 0, sizeof(ta));
+        ta.o = p.o; ta.o_ss = (int64_t)d.N * Hd; ta.o_ld = Hd; ta.x = p.x; ta.x_ss = x_ss; ta.rows = d.N;
+        ta.kbp = kbp; ta.kb1 = kb1; ta.kb2 = kb2;
+        ta.wp = (const bf16_t*)Q[0]; ta.w1 = (const bf16_t*)Q[1]; ta.w2 = (const bf16_t*)Q[2];
+        ta.wp_bytes = nbd * kbp * 1024; ta.w1_bytes = nbm * kb1 * 1024; ta.w2_bytes = nbd * kb2 * 1024;
+        ta.bp = (const float*)L[5]; ta.g2 = (const float*)L[6]; ta.be2 = (const float*)L[7];
+        ta.b1 = (const float*)L[9]; ta.b2 = (const float*)L[11];
+        ta.eps = eps; ta.offsets = p.offs;
+        ta.gt = gp;
+        for (int t = 0; t < d.T; ++t) ta.gt.row[t] = gp.k_out[t] > 0 ? g1.k_out[t] : 0;
+        return ds_launch_vit_tail(ta, B, s);
+    }
+    VitLinearArgs la;
+    memset(&la, 0, sizeof(la));
+    la.rows = d.N; la.offsets = p.offs; la.n_seg = 1;
+    la.x = p.o; la.x_ss = (int64_t)d.N * Hd; la.x_ld = Hd; la.kb = kbp; la.seg_blocks = nbd; la.w = (const bf16_t*)Q[0];
+    la.w_bytes = nbd * kbp * 1024; la.bias = (const float*)L[5]; la.res = p.x; la.y = p.x; la.y_ss = x_ss; la.gt = gp;
+    int32_t rc = ds_launch_vit_linear(la, B, s);
+    if (rc) return rc;
+    la.x = p.x; la.x_ss = x_ss; la.x_ld = 0; la.gamma = (const float*)L[6]; la.beta = (const float*)L[7]; la.eps = eps;
+    la.kb = kb1; la.seg_blocks = nbm; la.w = (const bf16_t*)Q[1]; la.w_bytes = nbm * kb1 * 1024; la.bias = (const float*)L[9];
+    la.res = nullptr; la.y = p.h; la.y_ss = (int64_t)d.N * d.M; la.act = DS_ACT_GELU; la.gt = g1;
+    rc = ds_launch_vit_linear(la, B, s);
+    if (rc) return rc;
+    la.x = p.h; la.x_ss = (int64_t)d.N * d.M; la.gamma = la.beta = nullptr; la.kb = kb2; la.seg_blocks = nbd;
+    la.w = (const bf16_t*)Q[2]; la.w_bytes = nbd * kb2 * 1024; la.bias = (const float*)L[11]; la.res = p.x; la.y = p.x;
+    la.y_ss = x_ss; la.act = DS_ACT_NONE; la.gt = g2;
+    return ds_launch_vit_linear(la, B, s);
 }
 
 int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, int B, const int32_t* route_override,
@@ -818,7 +861,6 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
     RC(ds_launch_cls_rows(xv, (const bf16_t*)P[2], (const bf16_t*)P[3], p.slot_group, gq, B, s));
     const float eps = 1e-6f;
     const GroupTable fq = gq;      // every route, for the final LayerNorm and the classifier
-    bool normed = false;           // p.a already holds this block's LN1 output
     for (int l = 0; l < d.depth; ++l) {
         const void* const* L = P + 4 + 12 * l;
         // dynamic depth: a route that runs fewer than l + 1 blocks gets empty slices from here on, so
@@ -835,33 +877,33 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
             }
             if (!any) break;
         }
-        if (!normed)
+        bool qkv = false;
+        if (d.tiled) {
+            // LN1 in the Q/K/V layer, the rest of the block behind the attention as one or three launches
+            const void* const* Q = P + d.tiled + 4 * l;
+            VitLinearArgs la;
+            memset(&la, 0, sizeof(la));
+            la.x = p.x; la.x_ss = x_ss; la.gamma = (const float*)L[0]; la.beta = (const float*)L[1]; la.eps = eps;
+            la.rows = d.N; la.offsets = p.offs; la.n_seg = 3; la.seg_blocks = (Hd + 31) / 32; la.kb = (d.D + 15) / 16 | 1;
+            la.w = (const bf16_t*)Q[3]; la.w_bytes = 3 * la.seg_blocks * la.kb * 1024;
+            la.bias = (const float*)L[3]; la.bias_seg = Hd;
+            la.y = p.qkv; la.y_ss = (int64_t)d.N * Hd; la.y_ld = Hd; la.y_seg = (int64_t)p.qkv_seg; la.gt = gq;
+            const int32_t rc = ds_launch_vit_linear(la, B, s);
+            if (rc != DS_OK && rc != DS_EUNSUPPORTED) return rc;
+            qkv = rc == DS_OK;
+        }
+        if (!qkv) {
             RC(ds_launch_layernorm(xv, av, (const float*)L[0], (const float*)L[1], eps, p.slot_group, gq, B, d.N, 0, d.N, s));
-        normed = false;
-        RC(linear_gemm(p.a, x_ss, 0, (const bf16_t*)L[2], d.D, (const float*)L[3], nullptr, 0, 0, 0, p.qkv,
-                       (int64_t)d.N * Hd, Hd, 0, d.N, 3, (int64_t)Hd * d.D, (int64_t)p.qkv_seg, Hd, p.offs, ml_t, gq,
-                       DS_ACT_NONE, s));
+            RC(linear_gemm(p.a, x_ss, 0, (const bf16_t*)L[2], d.D, (const float*)L[3], nullptr, 0, 0, 0, p.qkv,
+                           (int64_t)d.N * Hd, Hd, 0, d.N, 3, (int64_t)Hd * d.D, (int64_t)p.qkv_seg, Hd, p.offs, ml_t, gq,
+                           DS_ACT_NONE, s));
+        }
         RC(ds_launch_attention(p.qkv, p.qkv + p.qkv_seg, p.qkv + 2 * p.qkv_seg, p.o, (int64_t)d.N * Hd, Hd, Hd,
                                (int64_t)d.N * Hd, p.slot_group, gq, B, d.N, d.H, d.dh, s));
-        if (d.tiled) {
-            const void* const* Q = P + d.tiled + 3 * l;
-            VitTailArgs ta;
-            memset(&ta, 0, sizeof(ta));
-            ta.o = p.o; ta.o_ss = (int64_t)d.N * Hd; ta.o_ld = Hd; ta.x = p.x; ta.x_ss = x_ss; ta.rows = d.N;
-            ta.a = l + 1 < d.depth ? p.a : nullptr;
-            ta.kbp = (Hd + 15) / 16 | 1; ta.kb1 = (d.D + 15) / 16 | 1; ta.kb2 = (d.M + 15) / 16 | 1;
-            ta.wp = (const bf16_t*)Q[0]; ta.w1 = (const bf16_t*)Q[1]; ta.w2 = (const bf16_t*)Q[2];
-            ta.wp_bytes = (d.D + 31) / 32 * ta.kbp * 1024; ta.w1_bytes = (d.M + 31) / 32 * ta.kb1 * 1024;
-            ta.w2_bytes = (d.D + 31) / 32 * ta.kb2 * 1024;
-            ta.bp = (const float*)L[5]; ta.g2 = (const float*)L[6]; ta.be2 = (const float*)L[7];
-            ta.b1 = (const float*)L[9]; ta.b2 = (const float*)L[11];
-            if (l + 1 < d.depth) { ta.gn = (const float*)L[12]; ta.ben = (const float*)L[13]; }
-            ta.eps = eps; ta.offsets = p.offs;
-            ta.gt = gp;
-            for (int t = 0; t < T; ++t) ta.gt.row[t] = gp.k_out[t] > 0 ? g1.k_out[t] : 0;
-            const int32_t rc = ds_launch_vit_tail(ta, B, s);
+        if (qkv) {
+            const void* const* Q = P + d.tiled + 4 * l;
+            const int32_t rc = vit_behind_attention(d, L, Q, p, gp, g1, g2, B, eps, s);
             if (rc == DS_OK) {
-                normed = l + 1 < d.depth;
                 RC(tap_block(taps, l, p.x, x_ss, 0, p.perm, p.slot_group, g2, B, d.N, d.D, s));
                 continue;
             }

@@ -1,0 +1,206 @@
+// Linear layers of a transformer block over tiled weights: rows stay in LDS, weights stream into registers.
+//
+//   y = act(LN(x) W^T + b) [+ residual], LayerNorm optional, up to three stacked segments (Q, K, V)
+//
+// A workgroup owns BM = 32 R token rows (whole rows: the LayerNorm is computed in place, the arithmetic of
+// layernorm16_kernel) and a run of 32-column blocks of the output, NW at a time, one per wavefront.  A wavefront reads its
+// weight operands as contiguous kilobytes straight into registers, D in flight, so neither the weights nor the partial
+// sums touch LDS; finished blocks leave through an LDS tile as 16-byte pieces of whole row runs.
+// Two uses.  Large batches: the Q/K/V layer with 12 wavefronts and 96 or 64 rows, all columns in one workgroup (the rows
+// are read once; gemm_kernel read them once per 64 columns).  Few images: all four layers of a block with 4 wavefronts and
+// 32 rows, where a launch is bound by latency and by how many compute units share the weights' way in; the LayerNorm
+// launches disappear.  Sums are in gemm_kernel's order: the same bits.
+#include "gelu.h"
+#include "vit_rows.h"
+
+namespace {
+
+// PITCH: row pitch in elements (reduction up to PITCH - 8 channels), an odd number of 16-byte chunks
+template <int NW, int R, int D, int PITCH>
+__global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const VitLinearArgs a, const int runs, const int run_blocks) {
+    constexpr int BM = 32 * R, SP = 32 * NW + 8, RP = 4 * NW, NI = (BM + RP - 1) / RP, KIT = (PITCH + 127) / 128, NS = 4 * NW;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    bf16_t* As = (bf16_t*)smem;                          // [BM][PITCH], then one row of zeros for the read-ahead
+    bf16_t* Ss = As + (BM + 1) * PITCH;                  // [BM][SP] output stage
+
+    const int run = (int)blockIdx.x % runs;
+    const int4 me = ds_tile_record_of(a.offsets, a.gt.T, a.rows, (int)blockIdx.x / runs, BM);
+    if (me.x < 0) return;
+    const int g = me.x, grow0 = me.y, slot0 = me.z, rows_g = me.w;
+    const int kin = a.gt.k_in[g], k_out = a.gt.k_out[g];
+    if (kin <= 0 || k_out <= 0) return;
+    const int nb = (k_out + 31) / 32, total = nb * a.n_seg;      // column blocks of a segment, of the layer
+    const int blk0 = run * run_blocks, blk1 = min(total, blk0 + run_blocks);
+    if (blk0 >= total) return;
+
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
+    const int l16 = tid & 15, prow = tid >> 4;
+    const uint32_t lane16 = (uint32_t)lane * 16;
+    const int x_ld = a.x_ld > 0 ? a.x_ld : kin, y_ld = a.y_ld > 0 ? a.y_ld : k_out;
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, a.w_bytes, 0x00020000);
+
+    const int KK = (kin + 15) >> 4;
+    bf16x8_t ring[D];
+    auto tile0 = [&](int p) { return ((p / nb) * a.seg_blocks + p % nb) * a.kb; };
+    auto start = [&](int p) {
+        const int t0 = tile0(p);
+#pragma unroll
+        for (int j = 0; j < D; ++j) ring[j] = weight_tile(rw, lane16 | (j < KK ? 0u : DS_TILE_OOB), t0 + j);
+    };
+    if (blk0 + w < blk1) start(blk0 + w);                // the weights are under way while the rows are fetched
+
+    // ---- rows -------------------------------------------------------------------------------------------------------------
+    int64_t yoff[NI];
+    bool live[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        const bool in = BM % RP == 0 || prow + RP * i < BM;
+        const int m = grow0 + prow + RP * i;
+        live[i] = in && m < rows_g;
+        const int mm = live[i] ? m : grow0;
+        const int sl = mm / a.rows, p = mm - sl * a.rows, slot = slot0 + sl;
+        yoff[i] = (int64_t)slot * a.y_ss + (int64_t)p * y_ld;
+        const bf16_t* xrow = a.x + (int64_t)slot * a.x_ss + (int64_t)p * x_ld;
+        uint4 q[KIT];
+#pragma unroll
+        for (int k = 0; k < KIT; ++k) {
+            const int ch = (k * 16 + l16) * 8;
+            q[k] = make_uint4(0, 0, 0, 0);
+            if (ch < kin) q[k] = *(const uint4*)(xrow + ch);
+        }
+        if constexpr (KIT <= 4) {
+            if (a.gamma) {
+                float v[4][8];
+                uint4 o[4];
+#pragma unroll
+                for (int k = 0; k < KIT; ++k) unpack8(q[k], v[k]);
+                row_norm(v, kin, l16, a.eps, a.gamma, a.beta, o);
+#pragma unroll
+                for (int k = 0; k < KIT; ++k)
+                    if ((k * 16 + l16) * 8 < kin) q[k] = o[k];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < KIT; ++k) {
+            const int ch = (k * 16 + l16) * 8;
+            if (in && ch < PITCH) *(uint4*)(As + (prow + RP * i) * PITCH + ch) = q[k];     // zeros beyond the slice
+        }
+    }
+    for (int c = tid; c < PITCH / 8; c += 64 * NW) *(uint4*)(As + BM * PITCH + c * 8) = make_uint4(0, 0, 0, 0);
+
+    // ---- column blocks, NW at a time ------------------------------------------------------------------------------------------
+    for (int b0 = blk0; b0 < blk1; b0 += NW) {
+        const int p = b0 + w, seg = p / nb, n0 = (p - seg * nb) * 32;
+        const bool on = p < blk1;
+        if (a.res) {
+            // the residual of these columns waits in the stage, where the sums are added in place
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int k = 0; k < (NS + 15) / 16; ++k) {
+                    const int c = k * 16 + l16, n = (b0 + (c >> 2)) * 32 + (c & 3) * 8;
+                    if (c < NS && live[i] && n < k_out)
+                        *(uint4*)(Ss + (prow + RP * i) * SP + c * 8) = *(const uint4*)(a.res + yoff[i] + n);
+                }
+        }
+        __syncthreads();                                 // rows (and residual) are in place
+        f32x16_t acc[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[r][v] = 0.f;
+        if (on) {
+            const int t0 = tile0(p);
+            const bf16_t* base = As + l32 * PITCH + lhi * 8;
+            bf16x8_t f[2][R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) f[0][r] = *(const bf16x8_t*)(base + r * 32 * PITCH);
+            for (int k0 = 0; k0 < KK; k0 += D) {         // rounded up to D: zero weights
+#pragma unroll
+                for (int j = 0; j < D; ++j) {
+                    const int kk = k0 + j;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) f[(j + 1) & 1][r] = *(const bf16x8_t*)(base + r * 32 * PITCH + (kk + 1) * 16);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[j], f[j & 1][r], acc[r], 0, 0, 0);
+                    ring[j] = weight_tile(rw, lane16 | (kk + D < KK ? 0u : DS_TILE_OOB), t0 + kk + D);
+                    __builtin_amdgcn_sched_barrier(0);   // (the compiler would sink the reads to their use)
+                }
+            }
+            if (p + NW < blk1) start(p + NW);
+            const float* bias = a.bias + (int64_t)seg * a.bias_seg;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int n = n0 + 8 * q + 4 * lhi;
+                if (n >= k_out) continue;
+                const float4 h = *(const float4*)(bias + n);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    uint2* s = (uint2*)(Ss + (r * 32 + l32) * SP + w * 32 + 8 * q + 4 * lhi);
+                    float v0 = acc[r][4 * q] + h.x, v1 = acc[r][4 * q + 1] + h.y, v2 = acc[r][4 * q + 2] + h.z, v3 = acc[r][4 * q + 3] + h.w;
+                    if (a.act == DS_ACT_GELU) {
+                        *s = gelu_bf16x4(v0, v1, v2, v3);
+                        continue;
+                    }
+                    if (a.res) {
+                        const uint2 t = *s;
+                        v0 += __uint_as_float(t.x << 16);
+                        v1 += __uint_as_float(t.x & 0xffff0000u);
+                        v2 += __uint_as_float(t.y << 16);
+                        v3 += __uint_as_float(t.y & 0xffff0000u);
+                    }
+                    *s = make_uint2(f2bf2(v0, v1), f2bf2(v2, v3));
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int k = 0; k < (NS + 15) / 16; ++k) {
+                const int c = k * 16 + l16, pb = b0 + (c >> 2);
+                if (c >= NS || pb >= blk1 || !live[i]) continue;
+                const int sg = pb / nb, n = (pb - sg * nb) * 32 + (c & 3) * 8;
+                if (n < k_out) *(uint4*)(a.y + yoff[i] + (int64_t)sg * a.y_seg + n) = *(const uint4*)(Ss + (prow + RP * i) * SP + c * 8);
+            }
+        if (b0 + NW < blk1) __syncthreads();             // the stage is free again
+    }
+}
+
+template <int NW, int R, int D, int PITCH>
+int32_t launch(const VitLinearArgs& a, int64_t tiles, int max_blocks, int run_blocks, hipStream_t s) {
+    constexpr int SMEM = ((32 * R + 1) * PITCH + 32 * R * (32 * NW + 8)) * 2;
+    const int32_t rc = ds_reserve_lds((const void*)vit_linear_kernel<NW, R, D, PITCH>, SMEM, "tiled linear layer");
+    if (rc) return rc;
+    const int runs = (max_blocks + run_blocks - 1) / run_blocks;
+    ProfScope prof(DS_K_GEMM, s);
+    hipLaunchKernelGGL((vit_linear_kernel<NW, R, D, PITCH>), dim3((unsigned)(tiles * runs)), dim3(64 * NW), SMEM, s, a, runs, run_blocks);
+    DS_CHECK_LAUNCH("tiled linear layer");
+    return DS_OK;
+}
+
+}  // namespace
+
+// Measured on DS-ViT's Q/K/V layer with its LayerNorm (us): 1 / 5 / 16 images with 4 wavefronts and 4 blocks a workgroup 8.7 /
+// 9.7 / 16.4, 8 blocks 11.0 / 11.4 / 14.8; 64 images with 12 wavefronts and 64 rows 25, 96 rows 30; 256 images 64 and 60
+// (gemm_kernel 55 and its LayerNorm 12).  Reductions beyond 416 channels (fc2) are for the few-image path alone: 107 KB of rows.
+int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s) {
+    int kmax = 0, nmax = 0;
+    for (int t = 0; t < a.gt.T; ++t) {
+        kmax = a.gt.k_in[t] > kmax ? a.gt.k_in[t] : kmax;
+        nmax = a.gt.k_out[t] > nmax ? a.gt.k_out[t] : nmax;
+        if ((a.gt.k_in[t] % 8) || (a.gt.k_out[t] % 8)) return DS_EUNSUPPORTED;
+    }
+    if (kmax <= 0 || nmax <= 0) return DS_OK;
+    if (a.n_seg > 1 && a.res) return DS_EUNSUPPORTED;
+    const int64_t groups = B < a.gt.T ? B : a.gt.T, n = (int64_t)B * a.rows;
+    auto tiles = [&](int bm) { return (n - groups) / bm + groups; };
+    const int blocks = (nmax + 31) / 32 * a.n_seg;
+    if (kmax <= 416) {
+        if (tiles(96) >= 448) return launch<12, 3, 4, 424>(a, tiles(96), blocks, blocks, s);
+        if (tiles(64) >= 160) return launch<12, 2, 4, 424>(a, tiles(64), blocks, blocks, s);
+        return launch<4, 1, 8, 424>(a, tiles(32), blocks, tiles(32) > 64 ? 8 : 4, s);
+    }
+    if (kmax > 1664 || a.gamma) return DS_EUNSUPPORTED;
+    return launch<4, 1, 16, 1688>(a, tiles(32), blocks, 4, s);
+}

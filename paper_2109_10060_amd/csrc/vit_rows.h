@@ -1,0 +1,67 @@
+// Row helpers shared by the transformer-block kernels that keep a tile of token rows in LDS.
+#pragma once
+
+#include "common.h"
+
+__device__ __forceinline__ void unpack8(const uint4 q, float* v) {
+    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[2 * i] = __uint_as_float(w[i] << 16);
+        v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+    }
+}
+__device__ __forceinline__ uint4 pack8(const float* v) {
+    return make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]), f2bf2(v[4], v[5]), f2bf2(v[6], v[7]));
+}
+
+// LayerNorm of one row held by 16 lanes, lane l with the 8-channel chunks l, l + 16, l + 32, l + 48; the arithmetic and
+// the order of layernorm16_kernel
+__device__ __forceinline__ void row_norm(const float (&v)[4][8], int d, int l16, float eps, const float* gamma,
+                                         const float* beta, uint4 (&out)[4]) {
+    float s = 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if ((k * 16 + l16) * 8 < d) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s += v[k][i];
+        }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 16);
+    const float mu = s / (float)d;
+    float q = 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if ((k * 16 + l16) * 8 < d) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float t = v[k][i] - mu;
+                q += t * t;
+            }
+        }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) q += __shfl_xor(q, o, 16);
+    const float rstd = 1.0f / sqrtf(q / (float)d + eps);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int ch = (k * 16 + l16) * 8;
+        if (ch < d) {
+            const float4 g0 = *(const float4*)(gamma + ch), g1 = *(const float4*)(gamma + ch + 4);
+            const float4 b0 = *(const float4*)(beta + ch), b1 = *(const float4*)(beta + ch + 4);
+            const float gm[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+            const float bt[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+            float o8[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) o8[i] = (v[k][i] - mu) * rstd * gm[i] + bt[i];
+            out[k] = pack8(o8);
+        }
+    }
+}
+
+// One 1 KiB weight tile (32 rows x 16 channels in operand order), a whole kilobyte per wavefront; an offset or-ed with
+// DS_TILE_OOB is out of range: zeros, no traffic
+constexpr uint32_t DS_TILE_OOB = 0x7fff0000u;
+__device__ __forceinline__ bf16x8_t weight_tile(const __amdgpu_buffer_rsrc_t& rs, uint32_t lane_off, int t) {
+    const auto q = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)lane_off, t * 1024, 0);
+    return __builtin_bit_cast(bf16x8_t, q);
+}

@@ -1,11 +1,11 @@
 // The rest of a transformer block behind its attention, in one kernel (Section 3.2, Eq. 15-19):
-//   x += proj(o);  x += fc2(gelu(fc1(LN2(x))));  a = LN1 of the next block(x)
+//   x += proj(o);  x += fc2(gelu(fc1(LN2(x))))
 // for every route group, slices as everywhere: the leading block of the stored weights.
 //
-// As five launches (projection, LayerNorm, two linear layers, next LayerNorm) a block moved the residual stream seven
-// times and the hidden activations twice through memory, and its reductions of 192..416 channels spent their time in the
-// head and the epilogue of the workgroups.  Here a workgroup owns BM = 32 R rows from the attention output to the next
-// block's normalised input; the hidden layer never leaves the compute unit (256 columns at a time in LDS).
+// As four launches (projection, LayerNorm, two linear layers) a block moved the residual stream five times and the hidden
+// activations twice through memory, and its reductions of 192..416 channels spent their time in the head and the epilogue
+// of the workgroups.  Here a workgroup owns BM = 32 R rows from the attention output to the block's own; the hidden layer
+// never leaves the compute unit (HC columns at a time in LDS).
 //
 // What bounds it: the weights' way from L2 into a compute unit (about 50 bytes a clock, all of the block's weights once per
 // workgroup), the matrix pipes and the vector ALU (GELU, LayerNorm), in that order and only partly side by side.  So the
@@ -13,13 +13,12 @@
 // operand as one contiguous kilobyte straight into registers, D of them in flight, and LDS serves the activations alone.
 // Each of the NW = 12 (13 above 384 channels) wavefronts owns one 32-column block of the block's width and of every
 // HC = 32 NW columns of the hidden layer; R row blocks share every weight operand.
-// DS-ViT, 256 images: 161 us (projection 29, LayerNorms 12 + 12, fc1 66, fc2 54, less launch overlap) -> 131 us per block;
-// 64 images 76 -> 55 us; 16 images 48 -> 36 us.
+// DS-ViT, 256 images: 149 us (projection 29, LayerNorm 12, fc1 66, fc2 54, less launch overlap) -> 121 us per block;
+// 64 images 71 -> 51 us; 16 images 44 -> 33 us.
 //
 // Sums run in the order of gemm_kernel's and layernorm16_kernel's, so the results are the same bits.
-#include <type_traits>
-
 #include "gelu.h"
+#include "vit_rows.h"
 
 namespace {
 
@@ -29,61 +28,6 @@ constexpr int PA = 424;        // row pitch in elements of the activation tile (
 // elements behind the hidden tile: its last row's extra steps and the read-ahead end there (26 steps of 13 wavefronts, rounded
 // up to 28, and one more: column 479 of a pitch of 424)
 constexpr int TAIL = 64;
-
-__device__ __forceinline__ void unpack8(const uint4 q, float* v) {
-    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        v[2 * i] = __uint_as_float(w[i] << 16);
-        v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-    }
-}
-__device__ __forceinline__ uint4 pack8(const float* v) {
-    return make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]), f2bf2(v[4], v[5]), f2bf2(v[6], v[7]));
-}
-
-// LayerNorm of one row held by 16 lanes, lane l with the 8-channel chunks l, l + 16, l + 32, l + 48; the arithmetic and
-// the order of layernorm16_kernel
-__device__ __forceinline__ void row_norm(const float (&v)[4][8], int d, int l16, float eps, const float* gamma,
-                                         const float* beta, uint4 (&out)[4]) {
-    float s = 0.f;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-        if ((k * 16 + l16) * 8 < d) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) s += v[k][i];
-        }
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 16);
-    const float mu = s / (float)d;
-    float q = 0.f;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-        if ((k * 16 + l16) * 8 < d) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float t = v[k][i] - mu;
-                q += t * t;
-            }
-        }
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) q += __shfl_xor(q, o, 16);
-    const float rstd = 1.0f / sqrtf(q / (float)d + eps);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int ch = (k * 16 + l16) * 8;
-        if (ch < d) {
-            const float4 g0 = *(const float4*)(gamma + ch), g1 = *(const float4*)(gamma + ch + 4);
-            const float4 b0 = *(const float4*)(beta + ch), b1 = *(const float4*)(beta + ch + 4);
-            const float gm[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-            const float bt[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-            float o8[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) o8[i] = (v[k][i] - mu) * rstd * gm[i] + bt[i];
-            out[k] = pack8(o8);
-        }
-    }
-}
 
 // NW wavefronts (one column block of 32 each), 32 R rows, D operands of a wavefront in flight
 template <int NW, int R, int D>
@@ -105,10 +49,6 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc((void*)a.wp, 0, a.wp_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t r1 = __builtin_amdgcn_make_buffer_rsrc((void*)a.w1, 0, a.w1_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t r2 = __builtin_amdgcn_make_buffer_rsrc((void*)a.w2, 0, a.w2_bytes, 0x00020000);
-    auto tile = [&](const __amdgpu_buffer_rsrc_t& rs, uint32_t vo, int t) -> bf16x8_t {   // a whole kilobyte per wavefront
-        const auto q = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)vo, t * 1024, 0);
-        return __builtin_bit_cast(bf16x8_t, q);
-    };
 
     // ---- rows of this thread's 16-lane group: attention output to LDS, residual rows to registers ----------------------
     int64_t xoff[NI];
@@ -156,11 +96,10 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     // LDS reads of a step are issued ahead of the products of the step before it.  The number of steps is rounded up to D; the
     // extra steps multiply zero weights with finite LDS contents (of the neighbouring rows, at the end of the tile).
     const uint32_t lane16 = (uint32_t)lane * 16;
-    constexpr uint32_t OOB = 0x7fff0000u;                // or-ed into the lane offset
     bf16x8_t ring[D];
     auto start = [&](bf16x8_t (&ring)[D], const __amdgpu_buffer_rsrc_t& rs, int t0, int KK) {
 #pragma unroll
-        for (int j = 0; j < D; ++j) ring[j] = tile(rs, lane16 | (j < KK ? 0u : OOB), t0 + j);
+        for (int j = 0; j < D; ++j) ring[j] = weight_tile(rs, lane16 | (j < KK ? 0u : DS_TILE_OOB), t0 + j);
     };
     auto walk = [&](f32x16_t (&acc)[R], bf16x8_t (&ring)[D], const __amdgpu_buffer_rsrc_t& rs, int t0, int KK, const bf16_t* act, int pitch) {
         const bf16_t* base = act + l32 * pitch + lhi * 8;
@@ -175,7 +114,7 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
                 for (int r = 0; r < R; ++r) f[(j + 1) & 1][r] = *(const bf16x8_t*)(base + r * 32 * pitch + (kk + 1) * 16);
 #pragma unroll
                 for (int r = 0; r < R; ++r) acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[j], f[j & 1][r], acc[r], 0, 0, 0);
-                ring[j] = tile(rs, lane16 | (kk + D < KK ? 0u : OOB), t0 + kk + D);
+                ring[j] = weight_tile(rs, lane16 | (kk + D < KK ? 0u : DS_TILE_OOB), t0 + kk + D);
                 __builtin_amdgcn_sched_barrier(0);       // (the compiler would sink the reads to their use)
             }
         }
@@ -311,29 +250,15 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     __syncthreads();
     add_columns(a.b2);
     __syncthreads();
-    // ---- x, and the next block's LN1 -------------------------------------------------------------------------------------------
+    // ---- x to memory ------------------------------------------------------------------------------------------------------
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-        if (BM % RP != 0 && prow + RP * i >= BM) continue;     // whole 16-lane groups
-        float v[4][8];
-        uint4 o[4];
+        if (!live[i]) continue;
         const bf16_t* row = As + (prow + RP * i) * PA;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int ch = (k * 16 + l16) * 8;
-            if (ch < de) {
-                const uint4 q = *(const uint4*)(row + ch);
-                if (live[i]) *(uint4*)(a.x + xoff[i] + ch) = q;
-                unpack8(q, v[k]);
-            }
-        }
-        if (a.a) {
-            row_norm(v, de, l16, a.eps, a.gn, a.ben, o);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int ch = (k * 16 + l16) * 8;
-                if (ch < de && live[i]) *(uint4*)(a.a + xoff[i] + ch) = o[k];
-            }
+            if (ch < de) *(uint4*)(a.x + xoff[i] + ch) = *(const uint4*)(row + ch);
         }
     }
 }

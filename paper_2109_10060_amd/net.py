@@ -151,8 +151,9 @@ def build_vit(arch: dict, p: dict, device="cuda:0") -> Net:
               _dev(p[q + ".fc2.w"], bf, device), _dev(p[q + ".fc2.b"], f32, device)]
     t += [_dev(p["ln.g"], f32, device), _dev(p["ln.b"], f32, device), _dev(p["head.w"], bf, device),
           _dev(p["head.b"], f32, device)]
-    # the weights behind the attention once more in the order in which the fused block tail reads them
+    # the block's linear weights once more in the order in which a matrix instruction's lanes read them
     first = len(t) - 4 - 12 * arch["depth"]
     for l in range(arch["depth"]):
         t += [_operand_tiles(t[first + 12 * l + i]) for i in (4, 8, 10)]
+        t.append(torch.stack([_operand_tiles(w) for w in t[first + 12 * l + 2]]))
     return Net(DS_ARCH_VIT_STEM if C else DS_ARCH_VIT, ints, t, arch["num_classes"], 1, arch["T"])

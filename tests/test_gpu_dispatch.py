@@ -166,7 +166,7 @@ def test_vit_logits_do_not_depend_on_the_batch(gpu_lib, big):
         part, _ = gpu_lib.ds_forward(net, imgs[lo:hi].contiguous(), route_override=over[:, lo:hi].contiguous())
         # (the classifier sums in another order for a few images)
         assert relerr(host(part), host(full[lo:hi])) < 1e-5, (lo, hi)
-    net.c_struct.n_params -= 3 * arch["depth"]
+    net.c_struct.n_params -= 4 * arch["depth"]
     plain, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
     assert torch.equal(plain, full)
 
@@ -186,7 +186,7 @@ def test_gelu_rounding_matches_the_linear_layer(gpu_lib):
     out = []
     for tiled in (True, False):
         if not tiled:
-            net.c_struct.n_params -= 3 * arch["depth"]
+            net.c_struct.n_params -= 4 * arch["depth"]
         tap = torch.zeros((B, arch["tokens"], arch["embed"]), dtype=torch.bfloat16, device=DEV)
         logits, _ = gpu_lib.ds_forward_taps(net, imgs, {0: tap}, route_override=over)
         out.append((logits, tap))
