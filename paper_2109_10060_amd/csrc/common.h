@@ -91,7 +91,7 @@ struct GemmArgs {
     int32_t H, W, Ho, Wo, K, stride, pad, rows;
     int32_t Kw, stride_w;    // filter width and horizontal stride where they differ from K / stride (0 = the same)
     // schedule
-    const int32_t* offsets;  // device [T+1] slots
+    const int32_t* offsets;  // device [T+1] slots; nullable: one group of B samples
     const int4* mtiles;      // device [(group, first row inside group, first slot, rows of group)]; nullable: the kernels
                              // work the record out from the offsets (saves the launch that builds the list)
     const int32_t* n_mtiles; // device scalar
@@ -120,19 +120,19 @@ __device__ __forceinline__ int4 ds_tile_record_of(const int32_t* offsets, int T,
     const int before = __builtin_amdgcn_readlane(upto - n, q);
     return make_int4(T - 1 - q, (mt - before) * bm, __builtin_amdgcn_readlane(o0, q), __builtin_amdgcn_readlane(rg, q));
 }
-// Record of 128-row tile mt: read from the list, or worked out where there is none
+// Record of 128-row tile mt: read from the list, or worked out where there is none (no offsets either: one group of B
+// samples in slot order)
 __device__ __forceinline__ int4 ds_tile_record(const GemmArgs& a, int mt) {
     if (a.mtiles) {
         const int4 me = a.mtiles[mt];            // in bounds even beyond the live count; checked next
         return mt < *a.n_mtiles ? me : make_int4(-1, 0, 0, 0);
     }
+    if (!a.offsets) return mt * DS_GEMM_BM < a.B * a.rows ? make_int4(0, mt * DS_GEMM_BM, 0, a.B * a.rows) : make_int4(-1, 0, 0, 0);
     return ds_tile_record_of(a.offsets, a.gt.T, a.rows, mt, DS_GEMM_BM);
 }
 #endif
 
 size_t ds_mtile_capacity(int32_t B, int32_t rows, int32_t T);
-// builds the m-tile list for (offsets, rows); list needs ds_mtile_capacity()*16 + 16 bytes
-int32_t ds_build_mtiles(const int32_t* offsets, int32_t T, int32_t rows, void* list, hipStream_t s);
 int32_t ds_launch_gemm(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s);
 // 1x1 / linear layers with input slices of at most 64 channels and several 64-column passes: one workgroup per 128 rows
 // and all their columns; DS_EUNSUPPORTED otherwise
@@ -187,8 +187,8 @@ struct BucketArgs {
     int32_t *perm, *inv_perm, *offsets, *slot_group;   // inv_perm, slot_group nullable
     const int32_t* inv_prev;  // with src_index: src_index[slot] = inv_prev ? inv_prev[sample] : sample
     int32_t* src_index;       // nullable
-    // optional extras done by the same launch (T <= DS_MAX_GROUPS): up to two m-tile lists for the new offsets
-    // (as ds_build_mtiles writes them, for list_rows[i] rows per sample) and slot_lut[slot] = lut[group of slot]
+    // optional extras done by the same launch (T <= DS_MAX_GROUPS): up to two m-tile lists for the new offsets (count, then
+    // from byte 16 on one record per tile, ds_mtile_capacity() at most; list_rows[i] rows per sample) and slot_lut[slot] = lut[group of slot]
     int32_t n_lists, list_rows[2];
     void* lists[2];
     int32_t* slot_lut;        // nullable
@@ -300,7 +300,6 @@ int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s);
 int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s);
 
 // ---- small index helpers ---------------------------------------------------------
-int32_t ds_launch_set_offsets(int32_t* offsets, int32_t B, hipStream_t s);  // offsets[0..1] = {0, B}
 // key[b] = hi[b] * mul + (lo ? lo[b] : 0)
 int32_t ds_launch_make_key(const int32_t* hi, const int32_t* lo, int32_t mul, int32_t* key, int32_t B, hipStream_t s);
 

@@ -421,57 +421,91 @@ __global__ __launch_bounds__(256) void fc_mfma64_kernel(const FcArgs a) {
     }
 }
 
-// A few items (the classifier of one to eight images, bf16 weights, fp32 sums): bound by the one read of the weights and by
-// latency, so every output gets a wavefront of its own and its whole weight row is requested at once (C <= 2048: four
-// 16-byte pieces per lane), kept in registers over the items.  The tiled kernel walks the reduction 64 channels at a time
-// on n_out / 16 workgroups: 1000 outputs of 2048 channels for one image 42.9 us, here under 5.
-template <bool ROWS>
+// A few items: bound by the one read of the weights and by latency, so every output gets a wavefront of its own and its
+// whole weight row is requested at once (C <= 2048: PIECES 16-byte pieces per lane), kept in registers while the items, IG
+// at a time, are multiplied with it and reduced side by side.  The tiled kernels walk the reduction 64 channels at a time on
+// n_out / 16 workgroups: 1000 outputs of 2048 channels (bf16) for one image 42.9 us, here under 5; the gate's 256 hidden
+// units of 1024 channels (fp32 weights, fp64 sums, SRC = 2: the pool's partial sums) 22 us, here 4.
+// SRC: 0 bf16 rows, 1 one fp32 sum per channel, 2 several
+template <typename WT, typename ACC, int SRC, int IG>
 __global__ __launch_bounds__(256) void fc_few_kernel(const FcArgs a) {
+    constexpr int EPL = 16 / sizeof(WT), PIECES = 2048 / (64 * EPL);
     const int o = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (o >= a.n_out) return;
-    const bf16_t* wr = (const bf16_t*)a.w + (int64_t)o * a.w_ld;
-    uint4 w[4];
+    const WT* wr = (const WT*)a.w + (int64_t)o * a.w_ld;
+    uint4 w[PIECES];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int k = lane * 8 + 512 * i;
+    for (int i = 0; i < PIECES; ++i) {
+        const int k = (lane + 64 * i) * EPL;
         w[i] = k < a.C ? *(const uint4*)(wr + k) : make_uint4(0, 0, 0, 0);
     }
-    const float bias = a.bias ? a.bias[o] : 0.f;
-#pragma unroll 2
-    for (int item = 0; item < a.items; ++item) {
-        const int c = a.c_item ? a.c_item[item] : a.C;
-        float s = 0.f;
+    const ACC bias = a.bias ? (ACC)a.bias[o] : (ACC)0;
+    for (int i0 = 0; i0 < a.items; i0 += IG) {
+        ACC s[IG];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int k = lane * 8 + 512 * i;
-            if (k >= c) continue;
-            float v[8];
-            if constexpr (ROWS) {
-                const uint4 q = *(const uint4*)(a.v_rows + (int64_t)item * a.v_row_stride + k);
-                const uint32_t q4[4] = {q.x, q.y, q.z, q.w};
+        for (int t = 0; t < IG; ++t) {
+            const int item = min(i0 + t, a.items - 1);
+            const int c = a.c_item ? a.c_item[item] : a.C;
+            s[t] = 0;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    v[2 * j] = __uint_as_float(q4[j] << 16);
-                    v[2 * j + 1] = __uint_as_float(q4[j] & 0xffff0000u);
+            for (int i = 0; i < PIECES; ++i) {
+                const int k = (lane + 64 * i) * EPL;
+                if (k >= c) continue;
+                float v[EPL];
+                if constexpr (SRC == 0) {
+                    static_assert(SRC != 0 || EPL == 8, "bf16 rows go with bf16 weights");
+                    const uint4 q = *(const uint4*)(a.v_rows + (int64_t)item * a.v_row_stride + k);
+                    const uint32_t q4[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        v[2 * j] = __uint_as_float(q4[j] << 16);
+                        v[2 * j + 1] = __uint_as_float(q4[j] & 0xffff0000u);
+                    }
+                } else if constexpr (SRC == 1) {
+                    const float* p = a.v_partial + (int64_t)item * a.C + k;
+#pragma unroll
+                    for (int j = 0; j < EPL; j += 4) {
+                        const float4 t4 = *(const float4*)(p + j);
+                        v[j] = t4.x * a.v_scale; v[j + 1] = t4.y * a.v_scale; v[j + 2] = t4.z * a.v_scale; v[j + 3] = t4.w * a.v_scale;
+                    }
+                } else {
+                    double d[EPL];
+#pragma unroll
+                    for (int j = 0; j < EPL; ++j) d[j] = 0.0;
+                    static_assert(SRC != 2 || EPL == 4, "several sums go with fp32 weights");
+                    float4 t4[POOL_SPLIT_MAX];               // all requested before the first is added
+#pragma unroll
+                    for (int sp = 0; sp < POOL_SPLIT_MAX; ++sp)
+                        t4[sp] = *(const float4*)(a.v_partial + ((int64_t)item * a.splits + min(sp, a.splits - 1)) * a.C + k);
+#pragma unroll
+                    for (int sp = 0; sp < POOL_SPLIT_MAX; ++sp)
+                        if (sp < a.splits) {
+                            d[0] += (double)t4[sp].x; d[1] += (double)t4[sp].y; d[2] += (double)t4[sp].z; d[3] += (double)t4[sp].w;
+                        }
+#pragma unroll
+                    for (int j = 0; j < EPL; ++j) v[j] = (float)(d[j] * (double)a.v_scale);
                 }
-            } else {
-                const float* p = a.v_partial + (int64_t)item * a.C + k;
-                const float4 t0 = *(const float4*)p, t1 = *(const float4*)(p + 4);
-                v[0] = t0.x * a.v_scale; v[1] = t0.y * a.v_scale; v[2] = t0.z * a.v_scale; v[3] = t0.w * a.v_scale;
-                v[4] = t1.x * a.v_scale; v[5] = t1.y * a.v_scale; v[6] = t1.z * a.v_scale; v[7] = t1.w * a.v_scale;
-            }
-            const uint32_t w4[4] = {w[i].x, w[i].y, w[i].z, w[i].w};
+                const uint32_t w4[4] = {w[i].x, w[i].y, w[i].z, w[i].w};
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (k + 2 * j < c) s += v[2 * j] * __uint_as_float(w4[j] << 16);
-                if (k + 2 * j + 1 < c) s += v[2 * j + 1] * __uint_as_float(w4[j] & 0xffff0000u);
+                for (int j = 0; j < EPL; ++j) {
+                    const float wf = EPL == 4 ? __uint_as_float(w4[j & 3])
+                                              : __uint_as_float((j & 1) ? w4[j >> 1] & 0xffff0000u : w4[j >> 1] << 16);
+                    if (k + j < c) s[t] += (ACC)v[j] * (ACC)wf;
+                }
             }
         }
 #pragma unroll
-        for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
-        if (lane == 0) {
+        for (int d = 32; d > 0; d >>= 1)
+#pragma unroll
+            for (int t = 0; t < IG; ++t) s[t] += __shfl_xor(s[t], d, 64);
+#pragma unroll
+        for (int t = 0; t < IG; ++t) {
+            const int item = i0 + t;
+            if (lane != t || item >= a.items) continue;
             const int row = a.out_index ? a.out_index[item] : item;
-            a.out[(int64_t)row * a.out_ld + o] = s + bias;
+            ACC v = s[t] + bias;
+            if (a.relu == 1 && v < (ACC)0) v = (ACC)0;
+            a.out[(int64_t)row * a.out_ld + o] = (float)v;
         }
     }
 }
@@ -489,9 +523,17 @@ int32_t ds_launch_fc(const FcArgs& a, int32_t w_bf16, int32_t acc_f64, int32_t k
     // up to 8 items a wavefront per output; from there on the 32-item tile pays, half empty or not
     if (head && a.items <= 8 && a.C <= 2048) {
         const dim3 grid((unsigned)((a.n_out + 3) / 4));
-        if (a.v_rows) hipLaunchKernelGGL((fc_few_kernel<true>), grid, dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((fc_few_kernel<false>), grid, dim3(256), 0, s, a);
+        if (a.v_rows && a.items == 1) hipLaunchKernelGGL((fc_few_kernel<bf16_t, float, 0, 1>), grid, dim3(256), 0, s, a);
+        else if (a.v_rows) hipLaunchKernelGGL((fc_few_kernel<bf16_t, float, 0, 4>), grid, dim3(256), 0, s, a);
+        else if (a.items == 1) hipLaunchKernelGGL((fc_few_kernel<bf16_t, float, 1, 1>), grid, dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((fc_few_kernel<bf16_t, float, 1, 4>), grid, dim3(256), 0, s, a);
         DS_CHECK_LAUNCH("fc (few items)");
+        return DS_OK;
+    }
+    if (vec && !w_bf16 && acc_f64 && !a.v_rows && a.relu != 2 && a.items <= 2 && a.C <= 2048) {
+        const dim3 grid((unsigned)((a.n_out + 3) / 4));
+        hipLaunchKernelGGL((fc_few_kernel<float, double, 2, 1>), grid, dim3(256), 0, s, a);
+        DS_CHECK_LAUNCH("fc (few items, fp64)");
         return DS_OK;
     }
     if (head) {

@@ -115,7 +115,8 @@ int32_t conv_gemm(const bf16_t* A, const int32_t* a_index, int64_t a_sstride, in
     a.a_ld = a_ld; a.c_ld = c_ld; a.r_ld = c_ld; a.r_use_index = 1;
     a.w_ld = (int64_t)K * K * C_I_full; a.w_tap_stride = C_I_full; a.n_seg = 1;
     a.H = H; a.W = W; a.Ho = Ho; a.Wo = Wo; a.K = K; a.stride = stride; a.pad = pad; a.rows = Ho * Wo;
-    a.offsets = offsets; a.mtiles = ds_mtile_entries(ml.list); a.n_mtiles = ds_mtile_count(ml.list);
+    a.offsets = offsets; a.mtiles = ml.list ? ds_mtile_entries(ml.list) : nullptr;
+    a.n_mtiles = ml.list ? ds_mtile_count(ml.list) : nullptr;
     a.act = act; a.out_f32 = 0; a.gt = gt; a.B = ml.B;
     {
         const int32_t rc = ds_launch_gemm_small(a, ml.cap, max_out(gt), s);
@@ -182,9 +183,9 @@ struct MbPlan {
     bf16_t *bufA, *bufB;
     float *gate_logits, *gate_partial;
     float* head_partial;
-    int32_t *off1, *offs, *perm, *inv, *slot_group, *route, *slot_c;
-    void* lists[2 * 64 + 2];      // one tile list per (resolution, before / after the gate): at most one per block and phase
-    int n_lists;
+    int32_t *offs, *perm, *inv, *slot_group, *route, *slot_c;
+    void* lists[2];               // tile lists of the first two resolutions behind the gate
+    int list_rows[2], n_lists;
 };
 
 void plan_mb(const MbDesc& d, int B, Bump& bp, MbPlan* p) {
@@ -202,7 +203,6 @@ void plan_mb(const MbDesc& d, int B, Bump& bp, MbPlan* p) {
     const int cg = d.blk[3 * (d.gate_after - 1) + 1];
     p->gate_logits = bp.take<float>((size_t)B * d.T);
     p->gate_partial = bp.take<float>(ds_gate_partial_bytes(B, cg) / sizeof(float));
-    p->off1 = bp.take<int32_t>(2);
     p->offs = bp.take<int32_t>(d.T + 1);
     p->perm = bp.take<int32_t>(B);
     p->inv = bp.take<int32_t>(B);
@@ -210,18 +210,13 @@ void plan_mb(const MbDesc& d, int B, Bump& bp, MbPlan* p) {
     p->route = bp.take<int32_t>(B);
     p->slot_c = bp.take<int32_t>(B);
     p->head_partial = bp.take<float>(ds_gate_partial_bytes(B, d.blk[3 * (d.nb - 1) + 1]) / sizeof(float));
-    // one m-tile list per distinct (bucketing, resolution)
     p->n_lists = 0;
     r = r1;
-    int last_rows = -1, last_phase = -1;
     for (int i = 0; i < d.nb; ++i) {
         r = (r + 2 - 3) / d.blk[3 * i + 2] + 1;
-        const int phase = i >= d.gate_after;
-        if (r * r != last_rows || phase != last_phase) {
-            p->lists[p->n_lists++] = bp.take<char>(16 + ds_mtile_capacity(B, r * r, phase ? d.T : 1) * 16);
-            last_rows = r * r;
-            last_phase = phase;
-        }
+        if (i < d.gate_after || p->n_lists == 2 || (p->n_lists && p->list_rows[p->n_lists - 1] == r * r)) continue;
+        p->list_rows[p->n_lists] = r * r;
+        p->lists[p->n_lists++] = bp.take<char>(16 + ds_mtile_capacity(B, r * r, d.T) * 16);
     }
 }
 
@@ -230,12 +225,9 @@ int32_t forward_mb(const ds_net* net, const MbDesc& d, const bf16_t* images, int
                    const Taps* taps) {
     const void* const* P = net->params;
     int r = (d.image + 2 - 3) / 2 + 1;
-    RC(ds_launch_set_offsets(p.off1, B, s));
     RC(ds_launch_stem(images, nullptr, p.bufA, (const bf16_t*)P[0], (const float*)P[1], (const float*)P[2], B, d.image,
                       d.image, 3, 2, 1, d.stem_out, s));
     bf16_t *cur = p.bufA, *oth = p.bufB;
-    int li = -1, last_rows = -1, last_phase = -1, fused_lists = 0;
-    MList ml = {nullptr, 0, 0, B};
     for (int i = 0; i < d.nb; ++i) {
         const int ci = d.blk[3 * i], co = d.blk[3 * i + 1], st = d.blk[3 * i + 2];
         const void* const* Q = P + 3 + 6 * i;
@@ -257,17 +249,11 @@ int32_t forward_mb(const ds_net* net, const MbDesc& d, const bf16_t* images, int
             BucketArgs ba = {};
             ba.route = g.route; ba.mul = 1; ba.B = B; ba.T = d.T;
             ba.perm = p.perm; ba.inv_perm = p.inv; ba.offsets = p.offs; ba.slot_group = p.slot_group;
-            int rr = rin, lrows = -1;
-            for (int k = i; k < d.nb && ba.n_lists < 2; ++k) {
-                rr = (rr + 2 - 3) / d.blk[3 * k + 2] + 1;
-                if (rr * rr != lrows) {
-                    lrows = rr * rr;
-                    ba.list_rows[ba.n_lists] = lrows;
-                    ba.lists[ba.n_lists] = p.lists[li + 1 + ba.n_lists];
-                    ++ba.n_lists;
-                }
+            ba.n_lists = p.n_lists;
+            for (int k = 0; k < p.n_lists; ++k) {
+                ba.list_rows[k] = p.list_rows[k];
+                ba.lists[k] = p.lists[k];
             }
-            fused_lists = ba.n_lists;
             ba.slot_lut = p.slot_c;
             for (int t = 0; t < d.T; ++t) ba.lut[t] = d.cout[t * d.nb + d.nb - 1];
             RC(ds_launch_bucket_ex(ba, s));
@@ -298,17 +284,11 @@ int32_t forward_mb(const ds_net* net, const MbDesc& d, const bf16_t* images, int
             }
             if (rc != DS_EUNSUPPORTED) return rc;
         }
-        const int32_t* offsets = phase ? p.offs : p.off1;
-        if (r * r != last_rows || phase != last_phase) {
-            ++li;
-            ml.list = p.lists[li];
-            ml.cap = (int)ds_mtile_capacity(B, r * r, phase ? d.T : 1);
-            ml.rows = r * r;
-            if (phase && fused_lists > 0) --fused_lists;      // built together with the bucket order
-            else RC(ds_build_mtiles(offsets, phase ? d.T : 1, r * r, ml.list, s));
-            last_rows = r * r;
-            last_phase = phase;
-        }
+        // in front of the gate one group of all samples; a third resolution behind it has no list
+        const int32_t* offsets = phase ? p.offs : nullptr;
+        MList ml = {nullptr, (int)ds_mtile_capacity(B, r * r, phase ? d.T : 1), r * r, B};
+        for (int k = 0; phase && k < p.n_lists; ++k)
+            if (p.list_rows[k] == r * r) ml.list = p.lists[k];
         // depthwise: the first sliced block reads the fixed-width, original-order feature map through perm
         const bool first = (i == d.gate_after);
         ActView xv = {cur, first ? p.perm : nullptr, (int64_t)rin * rin * ci, (!phase || first) ? ci : 0};
@@ -390,7 +370,7 @@ bool parse_rn(const ds_net* net, RnDesc* d) {
 struct RnPlan {
     bf16_t* buf[5];
     float *gate_logits, *gate_partial;
-    int32_t *off1, *offs[4], *perm[4], *inv[4], *slot_group[4], *route[4], *key, *src_index, *slot_c;
+    int32_t *offs[4], *perm[4], *inv[4], *slot_group[4], *route[4], *key, *src_index, *slot_c;
     void* lists[8];
 };
 
@@ -410,7 +390,6 @@ void plan_rn(const RnDesc& d, int B, Bump& bp, RnPlan* p) {
     for (int s = 0; s < 4; ++s) cmax = cmax > 4 * d.widths[s] ? cmax : 4 * d.widths[s];
     p->gate_logits = bp.take<float>((size_t)B * d.T);
     p->gate_partial = bp.take<float>(ds_gate_partial_bytes(B, cmax) / sizeof(float));
-    p->off1 = bp.take<int32_t>(2);
     for (int s = 0; s < 4; ++s) {
         p->offs[s] = bp.take<int32_t>(rn_groups(d) + 1);
         p->perm[s] = bp.take<int32_t>(B);
@@ -650,8 +629,8 @@ struct VitPlan {
     bf16_t *sa, *sb;          // the stem's two feature maps
     size_t qkv_seg;
     float *gate_logits, *gate_partial;
-    int32_t *off1, *offs, *perm, *inv, *slot_group, *route, *slot_c;
-    void *list_p, *list_t, *list_s;
+    int32_t *offs, *perm, *inv, *slot_group, *route, *slot_c;
+    void *list_p, *list_t;
 };
 
 inline int vit_stem_res(const VitDesc& d) { return (d.image + 6 - 7) / 2 + 1; }
@@ -659,14 +638,12 @@ inline int vit_stem_res(const VitDesc& d) { return (d.image + 6 - 7) / 2 + 1; }
 void plan_vit(const VitDesc& d, int B, Bump& bp, VitPlan* p) {
     const int np = d.N - 1, kp = 3 * d.patch * d.patch, Hd = d.H * d.dh;
     p->patches = p->sa = p->sb = nullptr;
-    p->gate_partial = nullptr; p->off1 = nullptr; p->list_s = nullptr;
+    p->gate_partial = nullptr;
     if (d.stem_dim) {
         const int r = vit_stem_res(d);
         p->sa = bp.take<bf16_t>((size_t)B * r * r * d.stem_dim);
         p->sb = bp.take<bf16_t>((size_t)B * r * r * d.stem_dim);
         p->gate_partial = bp.take<float>(ds_gate_partial_bytes(B, d.stem_dim) / sizeof(float));
-        p->off1 = bp.take<int32_t>(2);
-        p->list_s = bp.take<char>(16 + ds_mtile_capacity(B, r * r, 1) * 16);
     } else {
         p->patches = bp.take<bf16_t>((size_t)B * np * kp);
     }
@@ -769,11 +746,9 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
         const void* const* S = net->params;
         const int C = d.stem_dim;
         const int64_t map = (int64_t)sr * sr * C;
-        RC(ds_launch_set_offsets(p.off1, B, s));
         RC(ds_launch_stem(images, nullptr, p.sa, (const bf16_t*)S[0], (const float*)S[1], (const float*)S[2], B, d.image,
                           d.image, 7, 2, 3, C, s));
-        MList ml_s = {p.list_s, (int)ds_mtile_capacity(B, sr * sr, 1), sr * sr, B};
-        RC(ds_build_mtiles(p.off1, 1, sr * sr, ml_s.list, s));
+        MList ml_s = {nullptr, (int)ds_mtile_capacity(B, sr * sr, 1), sr * sr, B};
         const GroupTable g1c = table1(C, C);
         for (int i = 0; i < 2; ++i) {
             const void* const* Q = S + 3 + 6 * i;
@@ -795,7 +770,7 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
             RC(ds_launch_dwconv(xv, yv, (const bf16_t*)Q[0], (const float*)Q[1], (const float*)Q[2], C, nullptr, g1c, B, C,
                                 sr, sr, 1, DS_ACT_RELU, s));
             RC(conv_gemm(p.sb, nullptr, map, C, (const bf16_t*)Q[3], C, 1, 1, 0, sr, sr, (const float*)Q[4],
-                         (const float*)Q[5], C, nullptr, p.sa, map, C, p.off1, ml_s, g1c, DS_ACT_RELU, s));
+                         (const float*)Q[5], C, nullptr, p.sa, map, C, nullptr, ml_s, g1c, DS_ACT_RELU, s));
         }
         const void* const* G = S + 15;
         g.x = p.sa; g.dtype = DS_BF16; g.layout = DS_NHWC; g.C = C; g.HW = sr * sr;

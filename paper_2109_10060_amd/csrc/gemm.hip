@@ -346,31 +346,6 @@ __global__ __launch_bounds__(NT, BK == 128 ? 3 : (WMT * WNT == 2 && !CONV) ? (BK
     }
 }
 
-// The list walks the groups from the last to the first: route tables are ordered from the narrowest
-// to the widest slice, so the longest work items are dispatched first and the short ones fill the
-// tail of the launch.
-__global__ void build_mtiles_kernel(const int32_t* offsets, int T, int rows, int32_t* count, int4* entries) {
-    __shared__ int pre[DS_MAX_GROUPS + 1];
-    if (threadIdx.x == 0) {
-        int acc = 0;
-        for (int q = 0; q < T; ++q) {
-            const int g = T - 1 - q;
-            pre[q] = acc;
-            const int rg = (offsets[g + 1] - offsets[g]) * rows;
-            acc += (rg + BM - 1) / BM;
-        }
-        pre[T] = acc;
-        *count = acc;
-    }
-    __syncthreads();
-    for (int q = 0; q < T; ++q) {
-        const int g = T - 1 - q;
-        const int n = pre[q + 1] - pre[q];
-        const int slot0 = offsets[g], rg = (offsets[g + 1] - slot0) * rows;
-        for (int i = threadIdx.x; i < n; i += blockDim.x) entries[pre[q] + i] = make_int4(g, i * BM, slot0, rg);
-    }
-}
-
 template <int WROWS, int WCOLS, int WMT, int WNT, int BK, bool CONV, bool HASR>
 int32_t launch(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
     using TL = Tile<WROWS, WCOLS, WMT, WNT, BK>;
@@ -395,14 +370,6 @@ size_t ds_mtile_capacity(int32_t B, int32_t rows, int32_t T) {
     if (B <= 0 || rows <= 0) return 1;
     const int64_t n = (int64_t)B * rows, g = B < T ? B : T;
     return (size_t)((n - g) / BM + g);
-}
-
-int32_t ds_build_mtiles(const int32_t* offsets, int32_t T, int32_t rows, void* list, hipStream_t s) {
-    ProfScope prof(DS_K_MISC, s);
-    hipLaunchKernelGGL(build_mtiles_kernel, dim3(1), dim3(256), 0, s, offsets, T, rows, (int32_t*)list,
-                       (int4*)((char*)list + 16));
-    DS_CHECK_LAUNCH("build_mtiles");
-    return DS_OK;
 }
 
 int32_t ds_launch_gemm(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
