@@ -216,6 +216,10 @@ int32_t ds_launch_dwconv(ActView x, ActView y, const bf16_t* w, const float* sca
 int32_t ds_launch_dwconv_spatial(ActView x, ActView y, const bf16_t* w, int32_t KS, const float* scale, const float* shift,
                                  int32_t tab_ld, const int32_t* slot_group, const GroupTable& gt, const SpatialTable& st,
                                  int32_t B, int32_t C, int32_t H, int32_t W, int32_t stride, int32_t act, hipStream_t s);
+// the same without dilation at stride 1 or 2, on the matrix cores; DS_EUNSUPPORTED otherwise
+int32_t ds_launch_dwband(ActView x, ActView y, const bf16_t* w, int32_t KS, const float* scale, const float* shift, int32_t tab_ld,
+                         const int32_t* slot_group, const GroupTable& gt, const SpatialTable& st, int32_t B, int32_t C, int32_t H,
+                         int32_t W, int32_t stride, int32_t act, hipStream_t s);
 int32_t ds_launch_layernorm(ActView x, ActView y, const float* gamma, const float* beta, float eps,
                             const int32_t* slot_group, const GroupTable& gt, int32_t B, int32_t rows,
                             int32_t row0, int32_t n_rows, hipStream_t s);

@@ -732,6 +732,9 @@ int32_t ds_launch_dwconv_spatial(ActView x, ActView y, const bf16_t* w, int32_t 
         nmax = n > nmax ? n : nmax;
     }
     if (nmax <= 0) return DS_OK;
+    // undilated odd filters at stride 1 or 2; dilated, even and wider-stepped ones stay here
+    const int32_t rc = ds_launch_dwband(x, y, w, KS, scale, shift, tab_ld, slot_group, gt, st, B, C, H, W, stride, act, s);
+    if (rc != DS_EUNSUPPORTED) return rc;
     const int slots8 = (B + 7) & ~7;
     const int64_t nwg = ((nmax + 255) / 256) * slots8;
     if (nwg > 0x7fffffffll) DS_FAIL(DS_ESHAPE, "spatial depthwise conv: %lld workgroups exceed the launch limit", (long long)nwg);

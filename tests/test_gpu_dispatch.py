@@ -191,3 +191,35 @@ def test_gelu_rounding_matches_the_linear_layer(gpu_lib):
         logits, _ = gpu_lib.ds_forward_taps(net, imgs, {0: tap}, route_override=over)
         out.append((logits, tap))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+# spatial depthwise filters without dilation: rows of 14 outputs per lane, 16 or 32 channels per lane group
+@pytest.mark.parametrize("B,K,stride,H,W,C", [(3, 7, 1, 1, 1, 8), (9, 7, 1, 7, 7, 640), (5, 7, 1, 14, 15, 72), (4, 5, 1, 13, 29, 288),
+                                              (2, 5, 1, 112, 112, 48), (5, 7, 2, 14, 14, 288), (3, 5, 2, 29, 31, 24),
+                                              (2, 3, 2, 57, 113, 96), (2, 7, 2, 224, 224, 8), (1, 7, 1, 9, 700, 40)])
+def test_sliced_dwconv_spatial_pairs(gpu_lib, B, K, stride, H, W, C):
+    d = WL.nets.Draw(7100 + stride + C + K + W)
+    x = WL.nets.as_bf16_values(d.normal((B, C, H, W)))
+    w = WL.nets.as_bf16_values(d.normal((C, 1, K, K), std=0.3))
+    spec = [(k, p) for k, p in [(K, K // 2), (1, 0), (K - 2, K // 2 - 1), (K, K // 2 + 1), (3, 2), (K, K // 2 - 1)]
+            if H + 2 * p >= k and W + 2 * p >= k]
+    T = len(spec)
+    bn = WL.bn_tables(d, T, C)
+    route = np.arange(B, dtype=np.int32) % T
+    cs = [max(8, C * (4 - t % 4) // 4 // 8 * 8) for t in range(T)]
+    perm, _, off = gpu_lib.ds_route_bucket(dev(route, torch.int32), T)
+    scale, shift = gpu_lib.ds_bn_fold(dev(bn["gamma"]), dev(bn["beta"]), dev(bn["mean"]), dev(bn["var"]), 1e-5)
+    rows = max(((H + 2 * p - k) // stride + 1) * ((W + 2 * p - k) // stride + 1) for k, p in spec)
+    y = torch.full((B, rows, C), float("nan"), dtype=torch.bfloat16, device=DEV)
+    gpu_lib.ds_sliced_dwconv_spatial(dev(x.transpose(0, 2, 3, 1), torch.bfloat16), dev(w[:, 0].transpose(1, 2, 0), torch.bfloat16),
+                                     scale, shift, gpu_lib.make_groups(off, perm, cs), [k for k, _ in spec], [1] * T,
+                                     [p for _, p in spec], stride, y=y)
+    yh = host(y)
+    for b in range(B):
+        t = int(route[b])
+        k, p = spec[t]
+        c = cs[t]
+        want = O.bf16_round(O.relu(O.re_sbn(O.spatial_dwconv2d(x[b, :c], w, k, 1, stride, p), bn, t, 1e-5)))
+        n = want.shape[1] * want.shape[2]
+        assert relerr(yh[b, :n, :c].T.reshape(want.shape), want) < 1e-2, (b, spec[t])
+        assert np.all(np.isnan(yh[b, :n, c:])) and np.all(np.isnan(yh[b, n:]))
