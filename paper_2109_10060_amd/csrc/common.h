@@ -220,6 +220,11 @@ int32_t ds_launch_dwconv_spatial(ActView x, ActView y, const bf16_t* w, int32_t 
 int32_t ds_launch_dwband(ActView x, ActView y, const bf16_t* w, int32_t KS, const float* scale, const float* shift, int32_t tab_ld,
                          const int32_t* slot_group, const GroupTable& gt, const SpatialTable& st, int32_t B, int32_t C, int32_t H,
                          int32_t W, int32_t stride, int32_t act, hipStream_t s);
+// depthwise (3 x 3 or 5 x 5, stride 1 or 2, padding (taps - 1) / 2) and pointwise layer of a separable block in front of the
+// gate with their batch-norms and ReLUs as one kernel; wp in operand tiles.  DS_EUNSUPPORTED for shapes it is not written for
+int32_t ds_launch_bandpw(const bf16_t* x, int32_t B, int32_t H, int32_t W, int32_t C, const bf16_t* wd, int32_t KS, int32_t taps,
+                         int32_t stride, const float* sd, const float* hd, const bf16_t* wp, int32_t F, const float* sp,
+                         const float* hp, bf16_t* y, hipStream_t s);
 int32_t ds_launch_layernorm(ActView x, ActView y, const float* gamma, const float* beta, float eps,
                             const int32_t* slot_group, const GroupTable& gt, int32_t B, int32_t rows,
                             int32_t row0, int32_t n_rows, hipStream_t s);

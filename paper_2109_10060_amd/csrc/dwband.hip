@@ -13,15 +13,13 @@
 // Bound: memory at large maps (256 images, 112x112: 80 us for 300 MB), a workgroup's chain of loads, LDS and stores at
 // small ones (6..8 us for 8 images).  288..640 channels of 14x14, filters of 3 / 5 / 7 taps, 96 images: 18 us (29 us with
 // dot products on channel pairs read straight from memory, 24 us with tap pairs from LDS).
-#include "common.h"
-
 #include <algorithm>
+
+#include "band.h"
 
 namespace {
 
 constexpr int RO = 7;          // output rows of a pass
-constexpr uint32_t OOB = 0x80000000u;
-typedef __attribute__((ext_vector_type(4))) short short4_t;
 
 struct BandArgs {
     ActView x, y;
@@ -33,45 +31,15 @@ struct BandArgs {
     SpatialTable st;
 };
 
-// pixel quads of a staged row, steps of K = 4 of a filter row
-__host__ __device__ constexpr int steps_of(int n, int stride) { return (3 * stride + n + 3) / 4; }
-__host__ __device__ constexpr int quads_of(int strips, int n, int stride) { return (strips - 1) * stride + steps_of(n, stride); }
-// bytes of a channel's window: the rows back to back, then up to an odd multiple of 32, so that the 16 lanes of an LDS
-// phase (4 channels x 4 strips of 8 bytes) meet every bank once
-__host__ __device__ constexpr int chan_pitch(int rows, int quads) { return ((rows * quads * 8 + 95) & ~63) - 32; }
-// and 16 more behind every 8 channels, for the 8-byte stores of 2..8 channel octets x neighbouring quads
-__host__ __device__ constexpr int window_bytes(int cw, int pitch) { return cw * pitch + cw / 8 * 16; }
-// a channel's filter: its rows between zeros, so that row m of a band is a window of it, m strides further left; an odd
-// number of dwords per channel against conflicts
-__host__ __device__ constexpr int lead_of(int stride) { return 3 * stride; }
-__host__ __device__ constexpr int frow_dwords(int stride) { return stride == 1 ? 8 : 11; }
-__host__ __device__ constexpr int filter_pitch(int n, int stride) { return (n * frow_dwords(stride) | 1) * 4; }
-
 template <int N, int STRIDE, int CW>
-__device__ __forceinline__ void band_rows(const BandArgs& a, const char* win, const char* wts, int nq, int pitch, int strips,
+__device__ __forceinline__ void dwband_rows(const BandArgs& a, const char* win, const char* wts, int nq, int pitch, int strips,
                                           int slot, int g, int c, int cb, int oy0, int ox0, int Ho, int Wo) {
-    constexpr int T = steps_of(N, STRIDE), ROWS = (RO - 1) * STRIDE + N, WH = 4 / (CW / 16);   // WH wavefronts per 16 channels
+    constexpr int WH = 4 / (CW / 16);   // WH wavefronts per 16 channels
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int b = lane >> 2, cl = (wave / WH) * 16 + b, ch = cb * CW + cl;
     if (cb * CW + (wave / WH) * 16 >= c) return;
-    short4_t A[N][T];
-    {
-        const int e = lead_of(STRIDE) - (lane & 3) * STRIDE;    // row m of the band starts here
-        const uint32_t* p = (const uint32_t*)(wts + cl * filter_pitch(N, STRIDE)) + (e >> 1);
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            uint32_t v[2 * T];
-#pragma unroll
-            for (int k = 0; k < 2 * T; ++k) v[k] = p[i * frow_dwords(STRIDE) + k];
-            if constexpr (STRIDE == 1) {
-                const uint32_t last = p[i * frow_dwords(STRIDE) + 2 * T];
-#pragma unroll
-                for (int k = 0; k < 2 * T; ++k) v[k] = __builtin_amdgcn_alignbit(k + 1 < 2 * T ? v[k + 1] : last, v[k], (e & 1) * 16);
-            }
-#pragma unroll
-            for (int t = 0; t < T; ++t) A[i][t] = __builtin_bit_cast(short4_t, make_uint2(v[2 * t], v[2 * t + 1]));
-        }
-    }
+    short4_t A[N][band_steps(N, STRIDE)];
+    band_operand<N, STRIDE>(A, wts + cl * band_filter_pitch(N, STRIDE));
     const int64_t ti = (int64_t)a.gt.row[g] * a.tab_ld + min(ch, a.tab_ld - 1);
     const float sc = a.scale[ti], sh = a.shift[ti];
     const int ys = a.y.index ? a.y.index[slot] : slot, yld = a.y.ld > 0 ? a.y.ld : c;
@@ -84,20 +52,7 @@ __device__ __forceinline__ void band_rows(const BandArgs& a, const char* win, co
         const int rc = s1 / strips, st = s1 - rc * strips;
         const char* p = win + cl * pitch + (cl >> 3) * 16 + (rc * RO * STRIDE * nq + st * STRIDE) * 8;
         f32x4_t acc[RO];
-#pragma unroll
-        for (int y = 0; y < RO; ++y) acc[y] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            short4_t B[T];
-#pragma unroll
-            for (int t = 0; t < T; ++t) B[t] = *(const short4_t*)(p + (r * nq + t) * 8);
-#pragma unroll
-            for (int t = 0; t < T; ++t)
-#pragma unroll
-                for (int y = 0; y < RO; ++y)
-                    if (r - y * STRIDE >= 0 && r - y * STRIDE < N)
-                        acc[y] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(A[r - y * STRIDE][t], B[t], acc[y], 0, 0, 0);
-        }
+        band_rows<N, STRIDE, RO>(acc, A, p, nq);
         // a lane has 4 outputs of a channel; with its neighbour channel's lane it trades 2 of them, for 4-byte stores
         const int ox = ox0 + st * 4 + (odd ? 2 : 0), oy = oy0 + rc * RO;
 #pragma unroll
@@ -108,14 +63,11 @@ __device__ __forceinline__ void band_rows(const BandArgs& a, const char* win, co
                 v[k] = acc[y][k] * sc + sh;
                 if (a.act == DS_ACT_RELU) v[k] = fmaxf(v[k], 0.f);
             }
-            const uint32_t lo = f2bf2(v[0], v[1]), hi = f2bf2(v[2], v[3]);
-            const uint32_t own = odd ? hi : lo, give = odd ? lo : hi;
-            const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)give, 0x141, 0xf, 0xf, true);   // lane 7 - i of 8
-            const uint32_t even_ch = odd ? got : own, odd_ch = odd ? own : got;
+            const uint2 t = band_trade(v, odd);
             if (sid >= count || oy + y >= Ho || ch >= c) continue;
             bf16_t* yp = yb + (int64_t)((oy + y) * Wo + ox) * yld;
-            if (ox < Wo) *(uint32_t*)yp = __builtin_amdgcn_perm(odd_ch, even_ch, 0x05040100);
-            if (ox + 1 < Wo) *(uint32_t*)(yp + yld) = __builtin_amdgcn_perm(odd_ch, even_ch, 0x07060302);
+            if (ox < Wo) *(uint32_t*)yp = t.x;
+            if (ox + 1 < Wo) *(uint32_t*)(yp + yld) = t.y;
         }
     }
 }
@@ -133,11 +85,11 @@ __global__ __launch_bounds__(256) void dwband_kernel(const BandArgs a, const int
     const int j = blockIdx.x / a.slots8, cb = j % cblocks, tile = j / cblocks;
     const int oy0 = tile / xtiles * a.TY, ox0 = tile % xtiles * a.TXS * 4;
     if (cb * CW >= c || oy0 >= Ho || ox0 >= Wo) return;
-    const int strips = min(a.TXS, (Wo - ox0 + 3) / 4), nq = quads_of(strips, n, STRIDE);
-    const int rows = (a.TY - 1) * STRIDE + n, pitch = chan_pitch(rows, nq);
+    const int strips = min(a.TXS, (Wo - ox0 + 3) / 4), nq = band_quads(strips, n, STRIDE);
+    const int rows = (a.TY - 1) * STRIDE + n, pitch = band_pitch(rows, nq);
     char *wts = smem, *win = smem + a.wbytes;
     constexpr int CH8 = CW / 8;
-    const int fp = filter_pitch(n, STRIDE);
+    const int fp = band_filter_pitch(n, STRIDE);
     // the filter's taps: at most 49 x CH8 octets, one or two a lane
     constexpr int WL = (49 * CH8 + 255) / 256;
     uint4 wv[WL];
@@ -164,27 +116,21 @@ __global__ __launch_bounds__(256) void dwband_kernel(const BandArgs a, const int
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const auto t = __builtin_amdgcn_raw_buffer_load_b128(
-                    rsrc, (int)(ok && ix + k >= 0 && ix + k < a.W ? (uint32_t)(o + k * xld * 2) : OOB), 0, 0);
+                    rsrc, (int)(ok && ix + k >= 0 && ix + k < a.W ? (uint32_t)(o + k * xld * 2) : BAND_OOB), 0, 0);
                 px[h][k] = make_uint4(t[0], t[1], t[2], t[3]);
             }
         }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             if (h && e0 + 256 >= total) break;
-            char* t = wp + (e0 + h * 256) / CH8 * 8;
-            const uint32_t *p0 = &px[h][0].x, *p1 = &px[h][1].x, *p2 = &px[h][2].x, *p3 = &px[h][3].x;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                *(uint2*)(t + 2 * q * pitch) = make_uint2(__builtin_amdgcn_perm(p1[q], p0[q], 0x05040100), __builtin_amdgcn_perm(p3[q], p2[q], 0x05040100));
-                *(uint2*)(t + (2 * q + 1) * pitch) = make_uint2(__builtin_amdgcn_perm(p1[q], p0[q], 0x07060302), __builtin_amdgcn_perm(p3[q], p2[q], 0x07060302));
-            }
+            band_store_quads(wp + (e0 + h * 256) / CH8 * 8, pitch, px[h]);
         }
     }
 #pragma unroll
     for (int q = 0; q < WL; ++q) {
         const int e = tid + q * 256, t = e / CH8, i = t / n;
         if (e < n * n * CH8) {
-            bf16_t* p = (bf16_t*)(wts + e % CH8 * 8 * fp) + i * frow_dwords(STRIDE) * 2 + lead_of(STRIDE) + t - i * n;
+            bf16_t* p = (bf16_t*)(wts + e % CH8 * 8 * fp) + i * band_row_dwords(STRIDE) * 2 + band_lead(STRIDE) + t - i * n;
             const uint32_t* v = &wv[q].x;
 #pragma unroll
             for (int k = 0; k < 8; ++k) p[k * (fp / 2)] = (bf16_t)(v[k / 2] >> (k & 1) * 16);
@@ -192,10 +138,10 @@ __global__ __launch_bounds__(256) void dwband_kernel(const BandArgs a, const int
     }
     __syncthreads();
     switch (n) {
-        case 1: band_rows<1, STRIDE, CW>(a, win, wts, nq, pitch, strips, slot, g, c, cb, oy0, ox0, Ho, Wo); break;
-        case 3: band_rows<3, STRIDE, CW>(a, win, wts, nq, pitch, strips, slot, g, c, cb, oy0, ox0, Ho, Wo); break;
-        case 5: band_rows<5, STRIDE, CW>(a, win, wts, nq, pitch, strips, slot, g, c, cb, oy0, ox0, Ho, Wo); break;
-        default: band_rows<7, STRIDE, CW>(a, win, wts, nq, pitch, strips, slot, g, c, cb, oy0, ox0, Ho, Wo); break;
+        case 1: dwband_rows<1, STRIDE, CW>(a, win, wts, nq, pitch, strips, slot, g, c, cb, oy0, ox0, Ho, Wo); break;
+        case 3: dwband_rows<3, STRIDE, CW>(a, win, wts, nq, pitch, strips, slot, g, c, cb, oy0, ox0, Ho, Wo); break;
+        case 5: dwband_rows<5, STRIDE, CW>(a, win, wts, nq, pitch, strips, slot, g, c, cb, oy0, ox0, Ho, Wo); break;
+        default: dwband_rows<7, STRIDE, CW>(a, win, wts, nq, pitch, strips, slot, g, c, cb, oy0, ox0, Ho, Wo); break;
     }
 }
 
@@ -221,7 +167,7 @@ int32_t ds_launch_dwband(ActView x, ActView y, const bf16_t* w, int32_t KS, cons
     // wide, at the smallest batches up to 8), so that every wavefront has one (800..1152 channels of 7x7: 35 us, 41 with 32).
     const int sx = (wo + 3) / 4, xt = (sx + 6) / 7, txs = (sx + xt - 1) / xt;
     const auto bytes = [&](int cw, int ty) {
-        return window_bytes(cw, chan_pitch((ty - 1) * stride + nmax, quads_of(txs, nmax, stride))) + ((cw * filter_pitch(nmax, stride) + 15) & ~15);
+        return band_window(cw, band_pitch((ty - 1) * stride + nmax, band_quads(txs, nmax, stride))) + ((cw * band_filter_pitch(nmax, stride) + 15) & ~15);
     };
     const int slots8 = (B + 7) & ~7;
     int cw = 32, ty = RO;
@@ -232,7 +178,7 @@ int32_t ds_launch_dwband(ActView x, ActView y, const bf16_t* w, int32_t KS, cons
     if (nwg > 0x7fffffffLL) return DS_EUNSUPPORTED;
     BandArgs a;
     a.x = x; a.y = y; a.w = w; a.scale = scale; a.shift = shift; a.slot_group = slot_group;
-    a.tab_ld = tab_ld; a.KS = KS; a.C = C; a.H = H; a.W = W; a.act = act; a.B = B; a.slots8 = slots8; a.TY = ty; a.TXS = txs; a.wbytes = (cw * filter_pitch(nmax, stride) + 15) & ~15;
+    a.tab_ld = tab_ld; a.KS = KS; a.C = C; a.H = H; a.W = W; a.act = act; a.B = B; a.slots8 = slots8; a.TY = ty; a.TXS = txs; a.wbytes = (cw * band_filter_pitch(nmax, stride) + 15) & ~15;
     a.gt = gt; a.st = st;
     ProfScope prof(DS_K_DWCONV, s);
     const int smem = bytes(cw, ty);

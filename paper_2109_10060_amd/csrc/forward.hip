@@ -150,6 +150,7 @@ struct MbDesc {
     int image, stem_out, nb, gate_after, gate_hidden, T, classes;
     const int32_t *blk, *cin, *cout;
     const int32_t *kfull, *ksize;   // null unless the depthwise filters are spatially sliced
+    bool tiled;                     // the pointwise filters are there in operand order too
 };
 
 bool parse_mb(const ds_net* net, MbDesc* d) {
@@ -160,7 +161,8 @@ bool parse_mb(const ds_net* net, MbDesc* d) {
     if (d->nb < 1 || d->nb > 64 || d->T < 1 || d->T > DS_MAX_GROUPS) return false;
     const int plain = 7 + 3 * d->nb + 2 * d->T * d->nb;
     if (net->n_ints != plain && net->n_ints != plain + d->nb + d->T * d->nb) return false;
-    if (net->n_params != 3 + 6 * d->nb + 6) return false;
+    d->tiled = net->n_params == 3 + 7 * d->nb + 6;
+    if (!d->tiled && net->n_params != 3 + 6 * d->nb + 6) return false;
     d->blk = v + 7;
     d->cin = d->blk + 3 * d->nb;
     d->cout = d->cin + d->T * d->nb;
@@ -272,11 +274,16 @@ int32_t forward_mb(const ds_net* net, const MbDesc& d, const bf16_t* images, int
             gpw = gdw;
             for (int t = 0; t < d.T; ++t) gpw.k_out[t] = d.cout[t * d.nb + i];
         }
-        if (!phase && !d.kfull) {
-            // an unsliced block: depthwise and pointwise in one kernel where the shape allows, the depthwise map stays in LDS
-            const int32_t rc = ds_launch_dwpw(cur, B, rin, rin, ci, st, (const bf16_t*)Q[0], (const float*)Q[1],
-                                              (const float*)Q[2], (const bf16_t*)Q[3], ci, co, (const float*)Q[4],
-                                              (const float*)Q[5], oth, s);
+        if (!phase) {
+            // an unsliced block: depthwise and pointwise in one kernel where the shape allows, the depthwise map stays on the chip
+            int32_t rc = DS_EUNSUPPORTED;
+            if (d.tiled)
+                rc = ds_launch_bandpw(cur, B, rin, rin, ci, (const bf16_t*)Q[0], d.kfull ? d.kfull[i] : 3, d.kfull ? d.ksize[i] : 3, st,
+                                      (const float*)Q[1], (const float*)Q[2], (const bf16_t*)P[3 + 6 * d.nb + 6 + i], co,
+                                      (const float*)Q[4], (const float*)Q[5], oth, s);
+            if (rc == DS_EUNSUPPORTED && !d.kfull)
+                rc = ds_launch_dwpw(cur, B, rin, rin, ci, st, (const bf16_t*)Q[0], (const float*)Q[1], (const float*)Q[2],
+                                    (const bf16_t*)Q[3], ci, co, (const float*)Q[4], (const float*)Q[5], oth, s);
             if (rc == DS_OK) {
                 bf16_t* t = cur; cur = oth; oth = t;
                 RC(tap_block(taps, i, cur, (int64_t)r * r * co, co, nullptr, nullptr, gpw, B, r * r, co, s));

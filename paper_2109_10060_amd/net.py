@@ -72,6 +72,17 @@ def _operand_tiles(w):
     return t.view(nb, 32, kb, 2, 8).permute(0, 2, 3, 1, 4).contiguous()
 
 
+def _pointwise_tiles(w):
+    """[N, K] bf16 -> [ceil(N/32)][ceil(K/32) | 1] pairs of 16 x 32 tiles in the order of a matrix instruction's lanes: quarter
+    of the 32 channels, row, 8 channels.  The first tile of a pair has filters 0..3 of every eight, the second 4..7, so that
+    a lane ends with eight neighbouring outputs of a pixel."""
+    n, k = w.shape
+    nb, kb = (n + 31) // 32, (k + 31) // 32 | 1
+    t = torch.zeros((nb * 32, kb * 32), dtype=w.dtype, device=w.device)
+    t[:n, :k] = w
+    return t.view(nb, 4, 2, 4, kb, 4, 8).permute(0, 4, 2, 5, 1, 3, 6).contiguous()
+
+
 def build_mbnet(arch: dict, p: dict, device="cuda:0") -> Net:
     from . import DS_ARCH_MBNET
     bf, f32 = torch.bfloat16, torch.float32
@@ -91,6 +102,7 @@ def build_mbnet(arch: dict, p: dict, device="cuda:0") -> Net:
         t += list(_fold(p[f"ds{i}.pw.bn"], eps, device))
     t += [_dev(p[k], f32, device) for k in ("gate.w1", "gate.b1", "gate.w2", "gate.b2")]
     t += [_dev(p["fc.w"], bf, device), _dev(p["fc.b"], f32, device)]
+    t += [_pointwise_tiles(t[3 + 6 * i + 3]) for i in range(nb)]
     return Net(DS_ARCH_MBNET, ints, t, arch["num_classes"], 1, T)
 
 

@@ -223,3 +223,34 @@ def test_sliced_dwconv_spatial_pairs(gpu_lib, B, K, stride, H, W, C):
         n = want.shape[1] * want.shape[2]
         assert relerr(yh[b, :n, :c].T.reshape(want.shape), want) < 1e-2, (b, spec[t])
         assert np.all(np.isnan(yh[b, :n, c:])) and np.all(np.isnan(yh[b, n:]))
+
+
+# blocks in front of the gate in one kernel (pointwise filters in operand order) against the layers apart: tiles with a ragged
+# last row and column, 16- and 14-column tiles, one sample to more than the workgroups at once, 3 and 5 taps, both strides
+@pytest.mark.parametrize("pp", [False, True])
+@pytest.mark.parametrize("image,B", [(224, 2), (150, 3), (150, 41), (66, 1), (34, 9)])
+def test_mbnet_front_blocks(gpu_lib, pp, image, B):
+    arch = (WL.mbnet_pp_arch if pp else WL.mbnet_arch)(image=image)
+    net = gpu_lib.build_mbnet(arch, WL.mbnet_params(arch, 12), DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(image + B)
+    imgs = torch.randn((B, 3, image, image), generator=gen, device=DEV).to(torch.bfloat16)
+    over = (torch.arange(B, device=DEV, dtype=torch.int32) % arch["T"])[None].contiguous()
+
+    def run():
+        r, taps = (image + 1) // 2, {}
+        for i, (_, co, s) in enumerate(arch["blocks"][:5]):
+            r = (r - 1) // s + 1
+            taps[i] = torch.full((B, r * r, co), float("nan"), dtype=torch.bfloat16, device=DEV)
+        out = gpu_lib.ds_forward_taps(net, imgs, taps, route_override=over)
+        return taps, out[0]
+
+    fused, logits = run()
+    net.c_struct.n_params -= len(arch["blocks"])
+    apart, want = run()
+    for i in range(5):
+        assert torch.isfinite(apart[i]).all() and apart[i].abs().max() > 0
+        # single elements may round the other way in every layer before
+        a, b = host(fused[i]), host(apart[i])
+        assert np.linalg.norm(a - b) < 2e-3 * np.linalg.norm(b) and relerr(a, b) < 4e-2, i
+    assert relerr(host(logits), host(want)) < 1e-2
