@@ -15,13 +15,14 @@
 
 namespace {
 
-// PITCH: row pitch in elements (reduction up to PITCH - 8 channels), an odd number of 16-byte chunks
-template <int NW, int R, int D, int PITCH>
+// KM: channels of the reduction, at most
+template <int NW, int R, int D, int KM>
 __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const VitLinearArgs a, const int runs, const int run_blocks) {
-    constexpr int BM = 32 * R, SP = 32 * NW + 8, RP = 4 * NW, NI = (BM + RP - 1) / RP, KIT = (PITCH + 127) / 128, NS = 4 * NW;
+    constexpr int PITCH = tile_pitch(KM, D);
+    constexpr int BM = 32 * R, SP = 32 * NW + 8, RP = 4 * NW, NI = (BM + RP - 1) / RP, KIT = (PITCH - 8 + 127) / 128, NS = 4 * NW;
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    bf16_t* As = (bf16_t*)smem;                          // [BM][PITCH], then one row of zeros for the read-ahead
-    bf16_t* Ss = As + (BM + 1) * PITCH;                  // [BM][SP] output stage
+    bf16_t* As = (bf16_t*)smem;                          // [BM][PITCH]
+    bf16_t* Ss = As + BM * PITCH;                        // [BM][SP] output stage
 
     const int run = (int)blockIdx.x % runs;
     const int4 me = ds_tile_record_of(a.offsets, a.gt.T, a.rows, (int)blockIdx.x / runs, BM);
@@ -86,7 +87,6 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
             if (in && ch < PITCH) *(uint4*)(As + (prow + RP * i) * PITCH + ch) = q[k];     // zeros beyond the slice
         }
     }
-    for (int c = tid; c < PITCH / 8; c += 64 * NW) *(uint4*)(As + BM * PITCH + c * 8) = make_uint4(0, 0, 0, 0);
 
     // ---- column blocks, NW at a time ------------------------------------------------------------------------------------------
     for (int b0 = blk0; b0 < blk1; b0 += NW) {
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
             bf16x8_t f[2][R];
 #pragma unroll
             for (int r = 0; r < R; ++r) f[0][r] = *(const bf16x8_t*)(base + r * 32 * PITCH);
-            for (int k0 = 0; k0 < KK; k0 += D) {         // rounded up to D: zero weights
+            for (int k0 = 0; k0 < KK; k0 += D) {         // rounded up to D: zero weights, zeros behind the slice (tile_pitch)
 #pragma unroll
                 for (int j = 0; j < D; ++j) {
                     const int kk = k0 + j;
@@ -167,14 +167,15 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
     }
 }
 
-template <int NW, int R, int D, int PITCH>
+template <int NW, int R, int D, int KM>
 int32_t launch(const VitLinearArgs& a, int64_t tiles, int max_blocks, int run_blocks, hipStream_t s) {
-    constexpr int SMEM = ((32 * R + 1) * PITCH + 32 * R * (32 * NW + 8)) * 2;
-    const int32_t rc = ds_reserve_lds((const void*)vit_linear_kernel<NW, R, D, PITCH>, SMEM, "tiled linear layer");
+    constexpr int SMEM = 32 * R * (tile_pitch(KM, D) + 32 * NW + 8) * 2;
+    static_assert(SMEM <= 160 * 1024, "LDS of a compute unit");
+    const int32_t rc = ds_reserve_lds((const void*)vit_linear_kernel<NW, R, D, KM>, SMEM, "tiled linear layer");
     if (rc) return rc;
     const int runs = (max_blocks + run_blocks - 1) / run_blocks;
     ProfScope prof(DS_K_GEMM, s);
-    hipLaunchKernelGGL((vit_linear_kernel<NW, R, D, PITCH>), dim3((unsigned)(tiles * runs)), dim3(64 * NW), SMEM, s, a, runs, run_blocks);
+    hipLaunchKernelGGL((vit_linear_kernel<NW, R, D, KM>), dim3((unsigned)(tiles * runs)), dim3(64 * NW), SMEM, s, a, runs, run_blocks);
     DS_CHECK_LAUNCH("tiled linear layer");
     return DS_OK;
 }
@@ -196,11 +197,11 @@ int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s) {
     const int64_t groups = B < a.gt.T ? B : a.gt.T, n = (int64_t)B * a.rows;
     auto tiles = [&](int bm) { return (n - groups) / bm + groups; };
     const int blocks = (nmax + 31) / 32 * a.n_seg;
-    if (kmax <= 416) {
-        if (tiles(96) >= 448) return launch<12, 3, 4, 424>(a, tiles(96), blocks, blocks, s);
-        if (tiles(64) >= 160) return launch<12, 2, 4, 424>(a, tiles(64), blocks, blocks, s);
-        return launch<4, 1, 8, 424>(a, tiles(32), blocks, tiles(32) > 64 ? 8 : 4, s);
+    if (kmax <= VIT_K_MAX) {
+        if (tiles(96) >= 448) return launch<12, 3, 4, VIT_K_MAX>(a, tiles(96), blocks, blocks, s);
+        if (tiles(64) >= 160) return launch<12, 2, 4, VIT_K_MAX>(a, tiles(64), blocks, blocks, s);
+        return launch<4, 1, 8, VIT_K_MAX>(a, tiles(32), blocks, tiles(32) > 64 ? 8 : 4, s);
     }
     if (kmax > 1664 || a.gamma) return DS_EUNSUPPORTED;
-    return launch<4, 1, 16, 1688>(a, tiles(32), blocks, 4, s);
+    return launch<4, 1, 16, 1664>(a, tiles(32), blocks, 4, s);
 }

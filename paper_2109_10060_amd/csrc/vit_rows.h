@@ -58,6 +58,12 @@ __device__ __forceinline__ void row_norm(const float (&v)[4][8], int d, int l16,
     }
 }
 
+// Row pitch in elements of an activation tile of up to k channels that is multiplied in turns of d 16-channel steps: the row
+// holds every step of the last turn, those past the slice as zeros (what follows in LDS is another sample's row, which need
+// not be finite, and zero weights alone do not undo that).  An odd number of 16-byte chunks, so 32 rows read without conflicts.
+__host__ __device__ constexpr int tile_pitch(int k, int d) { return (k + 16 * d - 1) / (16 * d) * (16 * d) + 8; }
+constexpr int VIT_K_MAX = 416;      // channels of a row that is normalised or multiplied in one tile
+
 // One 1 KiB weight tile (32 rows x 16 channels in operand order), a whole kilobyte per wavefront; an offset or-ed with
 // DS_TILE_OOB is out of range: zeros, no traffic
 constexpr uint32_t DS_TILE_OOB = 0x7fff0000u;

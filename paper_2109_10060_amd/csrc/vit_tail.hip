@@ -22,17 +22,18 @@
 
 namespace {
 
-constexpr int PA = 424;        // row pitch in elements of the activation tile (<= 416 channels); like the hidden tile's an odd
-                               // number of 16-byte chunks, so 32 rows read without conflicts
-
-// elements behind the hidden tile: its last row's extra steps and the read-ahead end there (26 steps of 13 wavefronts, rounded
-// up to 28, and one more: column 479 of a pitch of 424)
-constexpr int TAIL = 64;
+// pitches of the activation and the hidden tile; 8 elements behind the hidden tile for the read-ahead of its last row
+template <int NW, int R, int D>
+struct TailTile {
+    static constexpr int PA = tile_pitch(VIT_K_MAX, D), PH = tile_pitch(32 * NW, D);
+    static constexpr int SMEM = (32 * R * (PA + PH) + 8) * 2;
+};
 
 // NW wavefronts (one column block of 32 each), 32 R rows, D operands of a wavefront in flight
 template <int NW, int R, int D>
 __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const VitTailArgs a) {
-    constexpr int BM = 32 * R, HC = 32 * NW, PH = HC + 8, RP = 4 * NW, NI = (BM + RP - 1) / RP;   // RP: rows of a row phase
+    using Tile = TailTile<NW, R, D>;
+    constexpr int BM = 32 * R, HC = 32 * NW, PA = Tile::PA, PH = Tile::PH, RP = 4 * NW, NI = (BM + RP - 1) / RP;   // RP: rows of a row phase
     extern __shared__ __attribute__((aligned(16))) char smem[];
     bf16_t* As = (bf16_t*)smem;                         // [BM][PA]
     bf16_t* Hs = As + BM * PA;                          // [BM][PH]
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     // Every step is straight-line code: operand requests are unconditional (a step past the end asks for an address out of
     // range and gets zeros without traffic), so the number in flight is known where a product waits for the oldest, and the
     // LDS reads of a step are issued ahead of the products of the step before it.  The number of steps is rounded up to D; the
-    // extra steps multiply zero weights with finite LDS contents (of the neighbouring rows, at the end of the tile).
+    // extra steps multiply zero weights with the zeros behind the slice (tile_pitch).
     const uint32_t lane16 = (uint32_t)lane * 16;
     bf16x8_t ring[D];
     auto start = [&](bf16x8_t (&ring)[D], const __amdgpu_buffer_rsrc_t& rs, int t0, int KK) {
@@ -152,9 +153,10 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     };
 
     // ---- projection + residual ------------------------------------------------------------------------------------------
-    for (int i = tid; i < BM; i += 64 * NW) *(uint4*)(Hs + i * PH + HC) = make_uint4(0, 0, 0, 0);   // pads: read by extra steps
-    if (tid < 16) *(uint2*)(Hs + 4 * tid) = make_uint2(0, 0);
-    if (tid < TAIL / 8) *(uint4*)(Hs + BM * PH + 8 * tid) = make_uint4(0, 0, 0, 0);
+    // the columns behind the hidden tile's own, which the extra steps of a full width multiply
+    constexpr int PADS = (PH - 8 - HC) / 8;
+    if constexpr (PADS > 0)
+        for (int i = tid; i < BM * PADS; i += 64 * NW) *(uint4*)(Hs + i / PADS * PH + HC + i % PADS * 8) = make_uint4(0, 0, 0, 0);
     clear2();
     if (con) start(ring, rp, w * a.kbp, kin >> 4);
     __syncthreads();
@@ -265,7 +267,8 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
 
 template <int NW, int R, int D>
 int32_t launch(const VitTailArgs& a, int64_t tiles, hipStream_t s) {
-    constexpr int SMEM = 32 * R * (PA + 32 * NW + 8) * 2 + TAIL * 2;
+    constexpr int SMEM = TailTile<NW, R, D>::SMEM;
+    static_assert(SMEM <= 160 * 1024, "LDS of a compute unit");
     const int32_t rc = ds_reserve_lds((const void*)vit_tail_kernel<NW, R, D>, SMEM, "transformer block tail");
     if (rc) return rc;
     ProfScope prof(DS_K_TAIL, s);
@@ -285,7 +288,7 @@ int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {
     for (int t = 0; t < a.gt.T; ++t) {
         if (a.gt.k_out[t] <= 0) continue;
         dmax = a.gt.k_out[t] > dmax ? a.gt.k_out[t] : dmax;
-        if (a.gt.k_in[t] > PA - 8 || a.gt.k_out[t] > PA - 8 || a.gt.row[t] <= 0 || (a.gt.k_in[t] % 16) || (a.gt.k_out[t] % 8) ||
+        if (a.gt.k_in[t] > VIT_K_MAX || a.gt.k_out[t] > VIT_K_MAX || a.gt.row[t] <= 0 || (a.gt.k_in[t] % 16) || (a.gt.k_out[t] % 8) ||
             (a.gt.row[t] % 8))
             return DS_EUNSUPPORTED;
     }
