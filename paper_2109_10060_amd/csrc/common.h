@@ -281,7 +281,7 @@ struct VitTailArgs {
     int32_t o_ld, rows;
     bf16_t* x;                           // residual stream, in place, packed rows
     const bf16_t *wp, *w1, *w2;          // projection, fc1, fc2
-    int32_t wp_bytes, w1_bytes, w2_bytes, kbp, kb1, kb2;   // size and 16-channel tiles per 32-row block
+    int32_t kbp, kb1, kb2;               // 16-channel tiles per 32-row block
     const float *bp, *b1, *b2, *g2, *be2;
     float eps;
     const int32_t* offsets;
@@ -295,7 +295,7 @@ struct VitLinearArgs {
     const float *gamma, *beta;           // LayerNorm of the rows (nullable)
     float eps;
     const bf16_t* w;
-    int32_t w_bytes, kb, seg_blocks, n_seg;   // 16-channel tiles and 32-row blocks per segment as stored
+    int32_t kb, seg_blocks, n_seg;       // 16-channel tiles and 32-row blocks per segment as stored
     const float* bias;
     int32_t bias_seg, act;
     const bf16_t* res;                   // addressed like y, nullable; may be y

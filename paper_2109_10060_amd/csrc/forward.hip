@@ -708,7 +708,6 @@ int32_t vit_behind_attention(const VitDesc& d, const void* const* L, const void*
         ta.o = p.o; ta.o_ss = (int64_t)d.N * Hd; ta.o_ld = Hd; ta.x = p.x; ta.x_ss = x_ss; ta.rows = d.N;
         ta.kbp = kbp; ta.kb1 = kb1; ta.kb2 = kb2;
         ta.wp = (const bf16_t*)Q[0]; ta.w1 = (const bf16_t*)Q[1]; ta.w2 = (const bf16_t*)Q[2];
-        ta.wp_bytes = nbd * kbp * 1024; ta.w1_bytes = nbm * kb1 * 1024; ta.w2_bytes = nbd * kb2 * 1024;
         ta.bp = (const float*)L[5]; ta.g2 = (const float*)L[6]; ta.be2 = (const float*)L[7];
         ta.b1 = (const float*)L[9]; ta.b2 = (const float*)L[11];
         ta.eps = eps; ta.offsets = p.offs;
@@ -720,16 +719,16 @@ int32_t vit_behind_attention(const VitDesc& d, const void* const* L, const void*
     memset(&la, 0, sizeof(la));
     la.rows = d.N; la.offsets = p.offs; la.n_seg = 1;
     la.x = p.o; la.x_ss = (int64_t)d.N * Hd; la.x_ld = Hd; la.kb = kbp; la.seg_blocks = nbd; la.w = (const bf16_t*)Q[0];
-    la.w_bytes = nbd * kbp * 1024; la.bias = (const float*)L[5]; la.res = p.x; la.y = p.x; la.y_ss = x_ss; la.gt = gp;
+    la.bias = (const float*)L[5]; la.res = p.x; la.y = p.x; la.y_ss = x_ss; la.gt = gp;
     int32_t rc = ds_launch_vit_linear(la, B, s);
     if (rc) return rc;
     la.x = p.x; la.x_ss = x_ss; la.x_ld = 0; la.gamma = (const float*)L[6]; la.beta = (const float*)L[7]; la.eps = eps;
-    la.kb = kb1; la.seg_blocks = nbm; la.w = (const bf16_t*)Q[1]; la.w_bytes = nbm * kb1 * 1024; la.bias = (const float*)L[9];
+    la.kb = kb1; la.seg_blocks = nbm; la.w = (const bf16_t*)Q[1]; la.bias = (const float*)L[9];
     la.res = nullptr; la.y = p.h; la.y_ss = (int64_t)d.N * d.M; la.act = DS_ACT_GELU; la.gt = g1;
     rc = ds_launch_vit_linear(la, B, s);
     if (rc) return rc;
     la.x = p.h; la.x_ss = (int64_t)d.N * d.M; la.gamma = la.beta = nullptr; la.kb = kb2; la.seg_blocks = nbd;
-    la.w = (const bf16_t*)Q[2]; la.w_bytes = nbd * kb2 * 1024; la.bias = (const float*)L[11]; la.res = p.x; la.y = p.x;
+    la.w = (const bf16_t*)Q[2]; la.bias = (const float*)L[11]; la.res = p.x; la.y = p.x;
     la.y_ss = x_ss; la.act = DS_ACT_NONE; la.gt = g2;
     return ds_launch_vit_linear(la, B, s);
 }
@@ -867,7 +866,7 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
             memset(&la, 0, sizeof(la));
             la.x = p.x; la.x_ss = x_ss; la.gamma = (const float*)L[0]; la.beta = (const float*)L[1]; la.eps = eps;
             la.rows = d.N; la.offsets = p.offs; la.n_seg = 3; la.seg_blocks = (Hd + 31) / 32; la.kb = (d.D + 15) / 16 | 1;
-            la.w = (const bf16_t*)Q[3]; la.w_bytes = 3 * la.seg_blocks * la.kb * 1024;
+            la.w = (const bf16_t*)Q[3];
             la.bias = (const float*)L[3]; la.bias_seg = Hd;
             la.y = p.qkv; la.y_ss = (int64_t)d.N * Hd; la.y_ld = Hd; la.y_seg = (int64_t)p.qkv_seg; la.gt = gq;
             const int32_t rc = ds_launch_vit_linear(la, B, s);

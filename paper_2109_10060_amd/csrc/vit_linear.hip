@@ -38,15 +38,13 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
     const int l16 = tid & 15, prow = tid >> 4;
     const uint32_t lane16 = (uint32_t)lane * 16;
     const int x_ld = a.x_ld > 0 ? a.x_ld : kin, y_ld = a.y_ld > 0 ? a.y_ld : k_out;
-    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, a.w_bytes, 0x00020000);
 
-    const int KK = (kin + 15) >> 4;
     bf16x8_t ring[D];
-    auto tile0 = [&](int p) { return ((p / nb) * a.seg_blocks + p % nb) * a.kb; };
+    auto weights = [&](int p) { return weight_row(a.w, ((p / nb) * a.seg_blocks + p % nb) * a.kb, kin); };
     auto start = [&](int p) {
-        const int t0 = tile0(p);
+        const __amdgpu_buffer_rsrc_t rw = weights(p);
 #pragma unroll
-        for (int j = 0; j < D; ++j) ring[j] = weight_tile(rw, lane16 | (j < KK ? 0u : DS_TILE_OOB), t0 + j);
+        for (int j = 0; j < D; ++j) ring[j] = weight_tile(rw, lane16 + j * 1024);
     };
     if (blk0 + w < blk1) start(blk0 + w);                // the weights are under way while the rows are fetched
 
@@ -110,20 +108,20 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[r][v] = 0.f;
         if (on) {
-            const int t0 = tile0(p);
+            const __amdgpu_buffer_rsrc_t rw = weights(p);
             const bf16_t* base = As + l32 * PITCH + lhi * 8;
             bf16x8_t f[2][R];
 #pragma unroll
             for (int r = 0; r < R; ++r) f[0][r] = *(const bf16x8_t*)(base + r * 32 * PITCH);
-            for (int k0 = 0; k0 < KK; k0 += D) {         // rounded up to D: zero weights, zeros behind the slice (tile_pitch)
+            uint32_t off = lane16 + D * 1024;
+            for (int k0 = 0; k0 < kin; k0 += 16 * D, off += D * 1024) {   // rounded up to D: zero weights, zeros behind the slice (tile_pitch)
 #pragma unroll
                 for (int j = 0; j < D; ++j) {
-                    const int kk = k0 + j;
 #pragma unroll
-                    for (int r = 0; r < R; ++r) f[(j + 1) & 1][r] = *(const bf16x8_t*)(base + r * 32 * PITCH + (kk + 1) * 16);
+                    for (int r = 0; r < R; ++r) f[(j + 1) & 1][r] = *(const bf16x8_t*)(base + r * 32 * PITCH + k0 + (j + 1) * 16);
 #pragma unroll
                     for (int r = 0; r < R; ++r) acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[j], f[j & 1][r], acc[r], 0, 0, 0);
-                    ring[j] = weight_tile(rw, lane16 | (kk + D < KK ? 0u : DS_TILE_OOB), t0 + kk + D);
+                    ring[j] = weight_tile(rw, off + j * 1024);
                     __builtin_amdgcn_sched_barrier(0);   // (the compiler would sink the reads to their use)
                 }
             }

@@ -64,10 +64,14 @@ __device__ __forceinline__ void row_norm(const float (&v)[4][8], int d, int l16,
 __host__ __device__ constexpr int tile_pitch(int k, int d) { return (k + 16 * d - 1) / (16 * d) * (16 * d) + 8; }
 constexpr int VIT_K_MAX = 416;      // channels of a row that is normalised or multiplied in one tile
 
-// One 1 KiB weight tile (32 rows x 16 channels in operand order), a whole kilobyte per wavefront; an offset or-ed with
-// DS_TILE_OOB is out of range: zeros, no traffic
-constexpr uint32_t DS_TILE_OOB = 0x7fff0000u;
-__device__ __forceinline__ bf16x8_t weight_tile(const __amdgpu_buffer_rsrc_t& rs, uint32_t lane_off, int t) {
-    const auto q = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)lane_off, t * 1024, 0);
+// Weights in operand order: 1 KiB tiles of 32 rows x 16 channels, the upper 8 channels behind the lower ones.  A descriptor of
+// the tiles of one row block from tile t0 on that ends with the slice of k channels (a multiple of 8): lanes past it get zeros
+// without traffic, also the upper half of a slice's last step -- the stored weights go on there and need not be finite.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_row(const bf16_t* w, int t0, int k) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)(w + (int64_t)t0 * 512), 0, k * 64, 0x00020000);
+}
+// a whole kilobyte per wavefront; off: lane * 16 plus 1024 a tile
+__device__ __forceinline__ bf16x8_t weight_tile(const __amdgpu_buffer_rsrc_t& rs, uint32_t off) {
+    const auto q = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0);
     return __builtin_bit_cast(bf16x8_t, q);
 }

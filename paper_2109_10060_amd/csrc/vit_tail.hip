@@ -47,9 +47,6 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int l16 = tid & 15, prow = tid >> 4;          // row phases: 16 lanes a row, RP rows at a time
     const bool con = w * 32 < de;                        // this wavefront has a column block
-    const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc((void*)a.wp, 0, a.wp_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t r1 = __builtin_amdgcn_make_buffer_rsrc((void*)a.w1, 0, a.w1_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t r2 = __builtin_amdgcn_make_buffer_rsrc((void*)a.w2, 0, a.w2_bytes, 0x00020000);
 
     // ---- rows of this thread's 16-lane group: attention output to LDS, residual rows to registers ----------------------
     int64_t xoff[NI];
@@ -84,7 +81,7 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
         }
     }
 
-    // ---- acc2[r] += W[column block w] . act^T over KK 16-channel steps -----------------------------------------------------
+    // ---- acc2[r] += W[column block w] . act^T over K channels, 16 a step -----------------------------------------------------
     f32x16_t acc2[R];
     auto clear2 = [&]() {
 #pragma unroll
@@ -98,24 +95,24 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     // extra steps multiply zero weights with the zeros behind the slice (tile_pitch).
     const uint32_t lane16 = (uint32_t)lane * 16;
     bf16x8_t ring[D];
-    auto start = [&](bf16x8_t (&ring)[D], const __amdgpu_buffer_rsrc_t& rs, int t0, int KK) {
+    auto start = [&](bf16x8_t (&ring)[D], const __amdgpu_buffer_rsrc_t& rs) {
 #pragma unroll
-        for (int j = 0; j < D; ++j) ring[j] = weight_tile(rs, lane16 | (j < KK ? 0u : DS_TILE_OOB), t0 + j);
+        for (int j = 0; j < D; ++j) ring[j] = weight_tile(rs, lane16 + j * 1024);
     };
-    auto walk = [&](f32x16_t (&acc)[R], bf16x8_t (&ring)[D], const __amdgpu_buffer_rsrc_t& rs, int t0, int KK, const bf16_t* act, int pitch) {
+    auto walk = [&](f32x16_t (&acc)[R], bf16x8_t (&ring)[D], const __amdgpu_buffer_rsrc_t& rs, int K, const bf16_t* act, int pitch) {
         const bf16_t* base = act + l32 * pitch + lhi * 8;
         bf16x8_t f[2][R];
 #pragma unroll
         for (int r = 0; r < R; ++r) f[0][r] = *(const bf16x8_t*)(base + r * 32 * pitch);
-        for (int k0 = 0; k0 < KK; k0 += D) {
+        uint32_t off = lane16 + D * 1024;
+        for (int k0 = 0; k0 < K; k0 += 16 * D, off += D * 1024) {
 #pragma unroll
             for (int j = 0; j < D; ++j) {
-                const int kk = k0 + j;
 #pragma unroll
-                for (int r = 0; r < R; ++r) f[(j + 1) & 1][r] = *(const bf16x8_t*)(base + r * 32 * pitch + (kk + 1) * 16);
+                for (int r = 0; r < R; ++r) f[(j + 1) & 1][r] = *(const bf16x8_t*)(base + r * 32 * pitch + k0 + (j + 1) * 16);
 #pragma unroll
                 for (int r = 0; r < R; ++r) acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[j], f[j & 1][r], acc[r], 0, 0, 0);
-                ring[j] = weight_tile(rs, lane16 | (kk + D < KK ? 0u : DS_TILE_OOB), t0 + kk + D);
+                ring[j] = weight_tile(rs, off + j * 1024);
                 __builtin_amdgcn_sched_barrier(0);       // (the compiler would sink the reads to their use)
             }
         }
@@ -158,9 +155,10 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     if constexpr (PADS > 0)
         for (int i = tid; i < BM * PADS; i += 64 * NW) *(uint4*)(Hs + i / PADS * PH + HC + i % PADS * 8) = make_uint4(0, 0, 0, 0);
     clear2();
-    if (con) start(ring, rp, w * a.kbp, kin >> 4);
+    const __amdgpu_buffer_rsrc_t rp = weight_row(a.wp, w * a.kbp, kin);
+    if (con) start(ring, rp);
     __syncthreads();
-    if (con) walk(acc2, ring, rp, w * a.kbp, kin >> 4, As, PA);
+    if (con) walk(acc2, ring, rp, kin, As, PA);
     __syncthreads();
     rows_to_lds();
     __syncthreads();
@@ -194,19 +192,20 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
 
     // ---- MLP, HC hidden columns at a time ----------------------------------------------------------------------------------
     clear2();
-    const int KB = (de + 15) >> 4, nchunk = (hid + HC - 1) / HC;
-    if (w * 32 < hid) start(ring, r1, w * a.kb1, KB);
+    const int nchunk = (hid + HC - 1) / HC;
+    if (w * 32 < hid) start(ring, weight_row(a.w1, w * a.kb1, de));
     for (int hc = 0; hc < nchunk; ++hc) {
         const int hb = hc * NW + w;                      // 32-column block of the hidden layer
         const bool hon = hb * 32 < hid;
-        const int KK = (min(HC, hid - hc * HC) + 15) >> 4, t2 = w * a.kb2 + hc * 2 * NW;
+        const int K2 = min(HC, hid - hc * HC);
+        const __amdgpu_buffer_rsrc_t r1 = weight_row(a.w1, hb * a.kb1, de), r2 = weight_row(a.w2, w * a.kb2 + hc * 2 * NW, K2);
         f32x16_t acc1[R];
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc1[r][v] = 0.f;
-        if (hon) walk(acc1, ring, r1, hb * a.kb1, KB, As, PA);
-        if (con) start(ring, r2, t2, KK);                // under way during the GELU and the barriers
+        if (hon) walk(acc1, ring, r1, de, As, PA);
+        if (con) start(ring, r2);                        // under way during the GELU and the barriers
         uint2 ho[4][R];
         auto gelu = [&](auto put) {
 #pragma unroll
@@ -236,8 +235,8 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
             gelu(write);
         }
         __syncthreads();
-        if (con) walk(acc2, ring, r2, t2, KK, Hs, PH);
-        if ((hb + NW) * 32 < hid) start(ring, r1, (hb + NW) * a.kb1, KB);
+        if (con) walk(acc2, ring, r2, K2, Hs, PH);
+        if ((hb + NW) * 32 < hid) start(ring, weight_row(a.w1, (hb + NW) * a.kb1, de));
     }
     // the residual rows of the last sum: this thread wrote them itself after the projection
 #pragma unroll

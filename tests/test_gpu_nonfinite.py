@@ -73,3 +73,22 @@ def _samples_stay_apart(gpu_lib, net, B, image):
         keep = torch.ones(B, dtype=torch.bool, device=DEV)
         keep[bad] = False
         assert torch.equal(got[keep], want[keep]), value
+
+
+# Weights beyond a route's slice are never part of its sums, whatever they hold; slices that end inside a 16-channel step
+@pytest.mark.parametrize("B", [3, 120, 900, 2600])
+def test_vit_weights_outside_the_slice(gpu_lib, B):
+    arch, params = _vit(gpu_lib, dict(routes="diag"))
+    arch["routes"] = np.array([[200, 3, 808], [384, 6, 1536]], np.int32)
+    arch["T"] = 2
+    de, hd, hid = 200, 3 * arch["head_dim"], 808
+    outside = {k: v.copy() for k, v in params.items()}
+    for l in range(arch["depth"]):
+        for name, rows, cols in [(f"l{l}.w{c}", hd, de) for c in "qkv"] + [(f"l{l}.wproj", de, hd), (f"l{l}.fc1.w", hid, de),
+                                                                            (f"l{l}.fc2.w", de, hid)]:
+            outside[name][rows:] = np.nan
+            outside[name][:, cols:] = np.inf
+    imgs = _randn((B, 3, 64, 64), B)
+    over = torch.zeros((1, B), dtype=torch.int32, device=DEV)
+    want, got = (gpu_lib.ds_forward(gpu_lib.build_vit(arch, p, DEV), imgs, route_override=over)[0] for p in (params, outside))
+    assert torch.isfinite(want).all() and torch.equal(got, want)
