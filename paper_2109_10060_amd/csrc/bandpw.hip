@@ -164,17 +164,24 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 ? BandPw<N, S, NW, PT, KT, NP>::A
             else if (item + gridDim.x < a.items) fetch(item + gridDim.x, 0);
             {
                 f32x4_t d[RO];
-                if constexpr (!HOLD) band_operand<N, S>(A[q], flt + (q * 16 + b) * FP);
-                band_rows<N, S, RO>(d, A[q], win + own * WIN + cl * PITCH + (cl >> 3) * 16 + st * S * 8, NQ);
+                uint2 o[RO];
+                const char *f = flt + (q * 16 + b) * FP, *p = win + own * WIN + cl * PITCH + (cl >> 3) * 16 + st * S * 8;
+                if constexpr (!HOLD) band_operand<N, S>(A[q], f);
+                band_rows<N, S, RO>(d, A[q], p, NQ);
+                const float chk = band_finish<RO>(o, d, sc[q], sh[q], true);
                 const int x = st * 4 + (odd ? 2 : 0), octet = sub * 2 + (b >> 3), in8 = (b & 6) * 2;
+                const auto put = [&] {
 #pragma unroll
-                for (int y = 0; y < RO; ++y) {
-                    float v[4];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) v[k] = fmaxf(d[y][k] * sc[q] + sh[q], 0.f);
-                    const uint2 t = band_trade(v, odd);
-                    *(uint32_t*)(ops + (y * 16 + x) * (CK * 2) + turn<CK>(octet, x) * 16 + in8) = t.x;
-                    *(uint32_t*)(ops + (y * 16 + x + 1) * (CK * 2) + turn<CK>(octet, x + 1) * 16 + in8) = t.y;
+                    for (int y = 0; y < RO; ++y) {
+                        const uint2 t = band_trade(o[y], odd);
+                        *(uint32_t*)(ops + (y * 16 + x) * (CK * 2) + turn<CK>(octet, x) * 16 + in8) = t.x;
+                        *(uint32_t*)(ops + (y * 16 + x + 1) * (CK * 2) + turn<CK>(octet, x + 1) * 16 + in8) = t.y;
+                    }
+                };
+                put();
+                if (__ballot(chk != 0.f)) {
+                    if (chk != 0.f) band_exact<N, S, RO>(o, sc[q], sh[q], true, f, p, NQ);
+                    put();
                 }
             }
             __syncthreads();

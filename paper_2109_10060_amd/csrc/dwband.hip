@@ -39,7 +39,8 @@ __device__ __forceinline__ void dwband_rows(const BandArgs& a, const char* win, 
     const int b = lane >> 2, cl = (wave / WH) * 16 + b, ch = cb * CW + cl;
     if (cb * CW + (wave / WH) * 16 >= c) return;
     short4_t A[N][band_steps(N, STRIDE)];
-    band_operand<N, STRIDE>(A, wts + cl * band_filter_pitch(N, STRIDE));
+    const char* f = wts + cl * band_filter_pitch(N, STRIDE);
+    band_operand<N, STRIDE>(A, f);
     const int64_t ti = (int64_t)a.gt.row[g] * a.tab_ld + min(ch, a.tab_ld - 1);
     const float sc = a.scale[ti], sh = a.shift[ti];
     const int ys = a.y.index ? a.y.index[slot] : slot, yld = a.y.ld > 0 ? a.y.ld : c;
@@ -53,21 +54,25 @@ __device__ __forceinline__ void dwband_rows(const BandArgs& a, const char* win, 
         const char* p = win + cl * pitch + (cl >> 3) * 16 + (rc * RO * STRIDE * nq + st * STRIDE) * 8;
         f32x4_t acc[RO];
         band_rows<N, STRIDE, RO>(acc, A, p, nq);
+        uint2 o[RO];
+        const bool relu = a.act == DS_ACT_RELU;
+        const float chk = band_finish<RO>(o, acc, sc, sh, relu);
         // a lane has 4 outputs of a channel; with its neighbour channel's lane it trades 2 of them, for 4-byte stores
         const int ox = ox0 + st * 4 + (odd ? 2 : 0), oy = oy0 + rc * RO;
+        const auto put = [&] {
 #pragma unroll
-        for (int y = 0; y < RO; ++y) {
-            float v[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                v[k] = acc[y][k] * sc + sh;
-                if (a.act == DS_ACT_RELU) v[k] = fmaxf(v[k], 0.f);
+            for (int y = 0; y < RO; ++y) {
+                const uint2 t = band_trade(o[y], odd);
+                if (sid >= count || oy + y >= Ho || ch >= c) continue;
+                bf16_t* yp = yb + (int64_t)((oy + y) * Wo + ox) * yld;
+                if (ox < Wo) *(uint32_t*)yp = t.x;
+                if (ox + 1 < Wo) *(uint32_t*)(yp + yld) = t.y;
             }
-            const uint2 t = band_trade(v, odd);
-            if (sid >= count || oy + y >= Ho || ch >= c) continue;
-            bf16_t* yp = yb + (int64_t)((oy + y) * Wo + ox) * yld;
-            if (ox < Wo) *(uint32_t*)yp = t.x;
-            if (ox + 1 < Wo) *(uint32_t*)(yp + yld) = t.y;
+        };
+        put();
+        if (__ballot(chk != 0.f)) {
+            if (chk != 0.f) band_exact<N, STRIDE, RO>(o, sc, sh, relu, f, p, nq);
+            put();
         }
     }
 }

@@ -92,3 +92,77 @@ def test_vit_weights_outside_the_slice(gpu_lib, B):
     over = torch.zeros((1, B), dtype=torch.int32, device=DEV)
     want, got = (gpu_lib.ds_forward(gpu_lib.build_vit(arch, p, DEV), imgs, route_override=over)[0] for p in (params, outside))
     assert torch.isfinite(want).all() and torch.equal(got, want)
+
+
+# Depthwise filters: an output sees the pixels under its taps and no others, channel by channel
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("H,W,C,k", [(14, 14, 72, 3), (14, 15, 40, 7), (29, 31, 24, 5), (7, 7, 136, 7), (9, 60, 8, 1)])
+def test_depthwise_pixels_stay_apart(gpu_lib, H, W, C, k, stride):
+    B, K, pad = 3, 7, k // 2
+    x = _randn((B, H, W, C), 31 + C)
+    w = _randn((K, K, C), 32 + C)
+    one, zero = torch.ones((1, C), device=DEV), torch.zeros((1, C), device=DEV)
+    off = torch.tensor([0, B], dtype=torch.int32, device=DEV)
+    g = gpu_lib.make_groups(off, None, [C])
+
+    def run(x, act):
+        y, res = gpu_lib.ds_sliced_dwconv_spatial(x, w, one, zero, g, [k], [1], [pad], stride, act=act)
+        ho, wo = res[0]
+        return y[:, :ho * wo].reshape(B, ho, wo, C)
+
+    for value in (float("nan"), float("inf"), float("-inf")):
+        b, c, i, j = 1, C - 3, H // 2, W // 2
+        bad = x.clone()
+        bad[b, i, j, c] = value
+        want, got, relu = run(x, gpu_lib.DS_ACT_NONE), run(bad, gpu_lib.DS_ACT_NONE), run(bad, gpu_lib.DS_ACT_RELU)
+        oy = torch.arange(want.shape[1], device=DEV) * stride - pad
+        ox = torch.arange(want.shape[2], device=DEV) * stride - pad
+        reach = torch.zeros_like(want, dtype=torch.bool)
+        reach[b, :, :, c] = ((oy <= i) & (i < oy + k))[:, None] & ((ox <= j) & (j < ox + k))[None, :]
+        assert not torch.isfinite(got[reach]).any()
+        # a strip with such a pixel is summed tap by tap: the order of a sum differs there, bits elsewhere do not
+        strip = torch.zeros_like(reach)
+        strip[b, :, :, c] = True
+        assert torch.equal(got[~strip], want[~strip])
+        near = strip & ~reach
+        assert torch.allclose(got[near].float(), want[near].float(), rtol=1e-2, atol=1e-2), value
+        assert torch.equal(relu[~reach], got[~reach].clamp(min=0))
+        expect = got[reach].clamp(min=0)
+        assert torch.equal(relu[reach], torch.where(torch.isnan(expect), torch.zeros_like(expect), expect))
+
+
+# The same in the separable blocks in front of the gate: an image's pixel that overflows the stem reaches no further than the
+# filters do
+@pytest.mark.parametrize("pp", [False, True])
+@pytest.mark.parametrize("image", [224, 66])
+def test_front_block_pixels_stay_apart(gpu_lib, pp, image):
+    arch = (WL.mbnet_pp_arch if pp else WL.mbnet_arch)(image=image)
+    net = gpu_lib.build_mbnet(arch, WL.mbnet_params(arch, 12), DEV)
+    B, half = 2, (image + 1) // 2
+    imgs = _randn((B, 3, image, image), image)
+    over = torch.zeros((1, B), dtype=torch.int32, device=DEV)
+    sizes, r = [], half
+    for _, co, s in arch["blocks"][:5]:
+        r = (r - 1) // s + 1
+        sizes.append((r, co, s))
+
+    def run(x):
+        taps = {i: torch.full((B, r * r, co), float("nan"), dtype=torch.bfloat16, device=DEV) for i, (r, co, _) in enumerate(sizes)}
+        gpu_lib.ds_forward_taps(net, x, taps, route_override=over)
+        return [taps[i].reshape(B, r, r, co) for i, (r, co, _) in enumerate(sizes)]
+
+    want = run(imgs)
+    lo, hi = image // 2, image // 2                       # image rows and columns that hold the value
+    bad = imgs.clone()
+    bad[1, :, lo, lo] = 3e38
+    got = run(bad)
+    lo, hi = lo // 2 - 1, hi // 2 + 1                     # of the stem's map: a 3x3 filter at stride 2, a little generous
+    n = 5 if pp else 3
+    for i, (r, co, s) in enumerate(sizes):
+        assert not torch.equal(want[i], got[i])
+        lo, hi = -(-(lo - n // 2) // s), (hi + n // 2) // s
+        reach = torch.zeros((r, r), dtype=torch.bool, device=DEV)
+        reach[max(lo, 0):hi + 1, max(lo, 0):hi + 1] = True
+        assert torch.equal(want[i][0], got[i][0]), i
+        a, b = want[i][1][~reach].float(), got[i][1][~reach].float()
+        assert torch.isfinite(b).all() and (a - b).norm() <= 4e-3 * a.norm(), i
