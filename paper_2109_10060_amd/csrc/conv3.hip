@@ -11,7 +11,7 @@
 // linear pixel order needs no per-sample bookkeeping.  The weights of one filter row (3 taps) are
 // staged per phase: 12 matrix instructions per wavefront between barriers instead of 4, and the
 // activation traffic from L2 drops from 9 x 128 rows per chunk to 128 + 2 (W+1).
-#include "common.h"
+#include "gelu.h"
 
 namespace {
 
@@ -32,7 +32,6 @@ constexpr int NR = (RMAX * 4 + NT - 1) / NT;   // 16-byte patch loads per thread
 // 8 lanes (128 bytes) and of 16 lanes (256 bytes) alike -- a key of (r >> 1) & 3 serves only the former
 // and cost 40 % of the LDS cycles in conflicts
 __device__ __forceinline__ int sw(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
-__device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 
 template <bool HASR>
 __global__ __launch_bounds__(NT) void conv3_kernel(const GemmArgs a, const int ny, const int max_mtiles) {

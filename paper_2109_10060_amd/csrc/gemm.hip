@@ -26,7 +26,7 @@
 // index is dealt round-robin to the 8 XCDs by the hardware, so each XCD is given
 // a contiguous run of work items and the blocks that share an activation tile hit
 // the same L2.
-#include "common.h"
+#include "gelu.h"
 
 namespace {
 
@@ -40,7 +40,6 @@ __device__ __forceinline__ int swz(int r) {
     return BK == 128 ? (r & 15) : BK == 64 ? ((r ^ (r >> 3)) & 7) : (((r >> 1) ^ (r >> 2)) & 3);
 }
 
-__device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 
 template <int WROWS, int WCOLS, int WMT, int WNT, int BK>
 struct Tile {

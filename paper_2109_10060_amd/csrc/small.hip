@@ -11,7 +11,7 @@
 // WM*32 rows and a part beyond the group's rows ends at once.
 // Column tiles are the fastest index of the launch: neighbouring workgroups land on different dies, so a die's L2 holds
 // an eighth of the weights, which are most of what such a launch reads.
-#include "common.h"
+#include "gelu.h"
 
 namespace {
 
@@ -20,7 +20,6 @@ constexpr uint32_t OOB = 0x80000000u;
 // 16-byte chunk c of a 128-byte LDS row r is stored at chunk position c ^ key(r): the row-major stores (8 lanes a row)
 // and the operand reads (32 consecutive rows, one chunk column) are free of bank conflicts
 __device__ __forceinline__ int key(int r) { return (r ^ (r >> 3)) & 7; }
-__device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 
 // NW wavefronts: KS shares of the reduction x NW / KS column tiles
 template <int WM, int WN, int NW, int KS, int PD, bool CONV, bool HASR>
