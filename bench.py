@@ -212,9 +212,10 @@ def run_linear(args):
     print(json.dumps(out))
 
 
-GEMM_CLASSES = ("gemm", "gemm_taps", "conv3", "thin", "tail")          # kernel classes whose launches are the cost model's gemm / gemm_taps records
+# kernel classes whose launches are the cost model's gemm / gemm_taps records
+GEMM_CLASSES = ("gemm", "gemm_taps", "conv3", "thin", "tail", "small", "vit_linear")
 KERNEL_OF = {"gemm": "gemm_kernel", "gemm_taps": "gemm_kernel", "conv3": "conv3_kernel", "thin": "thin_kernel",
-             "tail": "vit_tail_kernel"}
+             "tail": "vit_tail_kernel", "small": "gemm_small_kernel", "vit_linear": "vit_linear_kernel"}
 RIDGE = PEAK_MFMA_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9)     # flop per byte above which the matrix peak is the roof
 
 
@@ -232,7 +233,7 @@ def rates(flops, nbytes, ms, contraction):
 
 def match_launches(cost, launches, sampled):
     """Joins the recorded launches (class, ms) of `sampled` identical steps with the cost model's per-launch records, class
-    by class in launch order.  Returns the cost records with 'kernel' and 'us' (mean over the sampled steps) filled in."""
+    by class in launch order.  Returns the cost records with 'class', 'kernel' and 'us' (mean over the sampled steps) filled in."""
     per_step = len(launches) // sampled
     rows = [dict(r) for r in cost.launches]
     want = {}
@@ -244,6 +245,7 @@ def match_launches(cost, launches, sampled):
         if any(len(g) != len(idx) for g in got):
             continue                                   # this class is launched differently from the model (gate, head): totals only
         for k, i in enumerate(idx):
+            rows[i]["class"] = got[0][k][0]
             rows[i]["kernel"] = KERNEL_OF.get(got[0][k][0], got[0][k][0])
             rows[i]["us"] = 1e3 * sum(g[k][1] for g in got) / sampled
     return rows
@@ -331,16 +333,16 @@ def run_net(workload, args, steps, warmup, with_cpu_baseline):
         if n and ms > 0:
             tf = flops / (ms * 1e-3) / 1e12
             gbs = nbytes / (ms * 1e-3) / 1e9
-            roofline = {"kernel": "gemm_kernel+conv3_kernel+thin_kernel", "bound": "mfma", "achieved": tf, "peak": PEAK_MFMA_BF16_TFLOPS,
+            roofline = {"kernel": "+".join(dict.fromkeys(KERNEL_OF[k] for k in GEMM_CLASSES if prof[k][1])), "bound": "mfma", "achieved": tf, "peak": PEAK_MFMA_BF16_TFLOPS,
                         "unit": "TFLOP/s", "frac": tf / PEAK_MFMA_BF16_TFLOPS, "traffic": traffic,
                         "algorithmic_bytes_per_launch": nbytes / n,
                         "launches_per_step": n / sampled, "avg_launch_us": ms * 1e3 / n,
                         "steps_sampled": sampled, "share_of_step": ms / (ms_per_step * sampled),
                         "hbm_view": {"achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": gbs / PEAK_HBM_GBS}}
-            # ... and each of its three kernels against the roof its own launches select: the launches whose flop per byte
+            # ... and each of its kernels against the roof its own launches select: the launches whose flop per byte
             # lies above the ridge against the matrix peak, the others against HBM bandwidth
             per_kernel = {}
-            for kern in ("gemm_kernel", "conv3_kernel", "thin_kernel", "vit_tail_kernel"):
+            for kern in dict.fromkeys(KERNEL_OF.values()):
                 mine = [r for r in gsel if r["kernel"] == kern]
                 if not mine:
                     continue
@@ -367,16 +369,14 @@ def run_net(workload, args, steps, warmup, with_cpu_baseline):
                                      "frac": rr["frac_mfma"] if roof == "mfma" else rr["frac_hbm"]}
             roofline["by_roof"] = by_roof
         # every kernel class with its algorithmic rates (same events, same sampled steps)
-        merged = dict(prof)
-        for k, (t, cnt) in merged.items():
+        for k, (t, cnt) in prof.items():
             if not cnt:
                 continue
-            ck = {"conv3": "gemm_taps", "thin": "gemm"}.get(k, k)
-            c = cost.get(ck, {"flops": 0.0, "bytes": 0.0}) if k not in ("conv3", "thin", "tail", "gemm", "gemm_taps") else None
-            if c is None:
-                mine = [r for r in gsel if (r["kernel"], r["kind"]) == (KERNEL_OF[k], "gemm_taps" if k in ("gemm_taps", "conv3") else "gemm")
-                        or (k == "conv3" and r["kernel"] == "conv3_kernel") or (k == "thin" and r["kernel"] == "thin_kernel")]
+            if k in GEMM_CLASSES:
+                mine = [r for r in gsel if r["class"] == k]
                 c = {"flops": sum(r["flops"] for r in mine), "bytes": sum(r["bytes"] for r in mine)}
+            else:
+                c = cost.get(k, {"flops": 0.0, "bytes": 0.0})
             per_step_ms = t / sampled
             kernels[k] = {"ms_per_step": per_step_ms, "launches_per_step": cnt / sampled,
                           **{kk: vv for kk, vv in rates(c["flops"], c["bytes"], per_step_ms, k in GEMM_CLASSES or k == "attention").items()

@@ -348,7 +348,10 @@ int32_t ds_forward_parts(const ds_net* net, const void* images, int32_t B, const
  * milliseconds and launch count of one kernel class: 0 grouped GEMM on linear/1x1 layers,
  * 1 grouped GEMM walking KxK taps, 2 attention, 3 depthwise conv, 4 LayerNorm, 5 stem conv,
  * 6 max-pool, 7 pool+classifier, 8 gate, 9 bucket, 10 index helpers, 11 3x3 stride-1 convolution with the
- * patch staged once, 12 short-reduction 1x1 layers (one workgroup per row tile).  ds_profile_launches gives the
+ * patch staged once, 12 short-reduction 1x1 layers (one workgroup per row tile),
+ * 13 projection and MLP of a transformer block in one kernel, 14 convolutions and linear layers of a few samples,
+ * 15 linear layers on weights in operand order.  A depthwise layer that runs in one kernel with the pointwise layer behind
+ * it counts as 3.  ds_profile_launches gives the
  * recorded launches one by one in launch order: kinds[i] and ms[i] for i < min(*count, capacity), *count = the number
  * recorded.  Not thread-safe; host pointers. */
 int32_t ds_profile_enable(int32_t on);

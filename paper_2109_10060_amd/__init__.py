@@ -451,7 +451,7 @@ def ds_forward_parts(net: "Net", images, parts: int, route_override=None, logit_
 
 
 KERNEL_CLASSES = ["gemm", "gemm_taps", "attention", "dwconv", "layernorm", "stem", "maxpool", "head", "gate",
-                  "bucket", "index", "conv3", "thin", "tail"]
+                  "bucket", "index", "conv3", "thin", "tail", "small", "vit_linear"]
 
 
 def ds_profile_enable(on: bool):

@@ -4,6 +4,10 @@ flops: 2 x multiply-adds the method itself must do on the valid slices (not the 
 it avoids).  bytes: each kernel reads its valid input once and writes its valid output once
 (bf16), reads a residual once where it has one, and reads the union of the weight slices
 once per launch.  These are the numerators of the roofline fractions bench.py reports.
+
+The records follow the launches: which layers run as one kernel depends on sizes, and the rules of the library's dispatch
+are repeated here (_tiles, _few_samples, _separable, _tail).  Work that happens inside a launch of another class (the
+LayerNorms of a transformer block) is kept under "inside", without bytes or launches of its own.
 """
 from __future__ import annotations
 
@@ -19,11 +23,14 @@ class Cost(defaultdict):
         super().__init__(lambda: {"flops": 0.0, "bytes": 0.0, "launches": 0})
         self.launches = []
 
-    def add(self, kind, flops, nbytes, name="", shape="", merge=False):
-        """merge: the work rides along in the previous launch of this kind (a chained layer): no new launch."""
+    def add(self, kind, flops, nbytes, name="", shape="", merge=False, launch=True):
+        """merge: the work rides along in the previous launch of this kind (a chained layer): no new launch.
+        launch=False: totals only, the work happens inside a launch of another kind."""
         e = self[kind]
         e["flops"] += float(flops)
         e["bytes"] += float(nbytes)
+        if not launch:
+            return
         if merge:
             last = next(r for r in reversed(self.launches) if r["kind"] == kind)
             last["flops"] += float(flops)
@@ -36,6 +43,29 @@ class Cost(defaultdict):
 
 def _osz(n, k, s, p):
     return (n + 2 * p - k) // s + 1
+
+
+def _tiles(B, rows, groups, bm=128):
+    """Row tiles of a launch, at most."""
+    g = min(B, groups)
+    return (B * rows - g) // bm + g
+
+
+def _few_samples(B, rows, groups, n):
+    """A 1x1 layer at stride 1 that the kernel for few samples takes (it has no layer chained behind it)."""
+    return _tiles(B, rows, groups, 32) * -(-n // 32) <= 1000
+
+
+def _separable(r, ci, co, s, k, kfull, tiled):
+    """An unsliced depthwise + pointwise block that runs as one kernel: output size, channels, stride, filter size."""
+    if ci % 8 or co % 8:
+        return False
+    if tiled and r > 8 and k in (3, 5) and (kfull - k) % 2 == 0:
+        limits = [(32, 64), (64, 128)] + ([(128, 128)] if s == 1 else []) + \
+            ([(128, 256) if s == 2 else (256, 256)] if k == 3 else [])
+        if any(ci <= a and co <= b for a, b in limits):
+            return True
+    return k == 3 and kfull == 3 and ci <= 128 and co <= 128 and r % (4 if s == 1 else 2) == 0
 
 
 def _gemm(cost, kind, rows_in, rows_out, kk, k_in, k_out, residual=False, out_bytes=2, chained=False, name=""):
@@ -64,8 +94,8 @@ def mbnet_cost(arch, routes) -> Cost:
         ci, co = arch["cin"][routes, i].astype(np.float64), arch["cout"][routes, i].astype(np.float64)
         kk = arch["ksize"][routes, i].astype(np.float64) ** 2 if "ksize" in arch else 9.0
         cif, cof = int(_ci), int(_co)
-        if (i < arch["gate_after"] and "ksize" not in arch and cif % 8 == 0 and cif <= 128 and cof % 8 == 0
-                and cof <= 128 and r % (4 if s == 1 else 2) == 0):
+        k = int(arch["ksize"][0, i]) if "ksize" in arch else 3
+        if i < arch["gate_after"] and _separable(r, cif, cof, s, k, arch["kfull"][i] if "ksize" in arch else 3, True):
             # an unsliced block the library runs as one kernel (depthwise map kept in LDS): counted as one launch
             # of the depthwise class that reads the block's input and writes the pointwise output
             c.add("dwconv", 2.0 * r * r * (kk * ci).sum() + 2.0 * r * r * np.sum(ci * co),
@@ -89,9 +119,13 @@ def resnet_cost(arch, routes) -> Cost:
     c = Cost()
     r1 = _osz(arch["image"], 7, 2, 3)
     so = arch["stem_out"]
-    c.add("stem", 2.0 * B * r1 * r1 * 147 * so, B * (3 * arch["image"] ** 2 * 2 + r1 * r1 * so * 2), name="stem 7x7/2 (+ max-pool)")
     r = _osz(r1, 3, 2, 1)
-    c.add("maxpool", 0.0, 2.0 * B * so * (r1 * r1 + r * r), name="max-pool")
+    pooled = so == 64 and arch["image"] % 4 == 0        # stem and max-pool in one kernel
+    c.add("stem", 2.0 * B * r1 * r1 * 147 * so, B * (3 * arch["image"] ** 2 * 2 + (r * r if pooled else r1 * r1) * so * 2),
+          name="stem 7x7/2" + (" + max-pool" if pooled else ""))
+    if not pooled:
+        c.add("maxpool", 0.0, 2.0 * B * so * (r1 * r1 + r * r), name="max-pool")
+    groups = arch["T"] if arch.get("single_gate") else arch["T"] ** 2
     cprev = np.full(B, so, np.float64)
     for s, nb in enumerate(arch["blocks"]):
         mid = arch["mid"][s][routes[s]].astype(np.float64)
@@ -101,7 +135,10 @@ def resnet_cost(arch, routes) -> Cost:
         # stages with slices of at most 128 channels run a block's last convolution and the next block's first one
         # as one launch (the wide map is written once and not read back)
         mids, outs = arch["mid"][s], arch["out"][s]
-        chain = bool(mids.max() <= 128 and outs.max() >= 128 and not (mids % 8).any() and not (outs % 8).any())
+        rs = r if s == 0 else _osz(r, 3, 2, 1)
+        chain = bool(mids.max() <= 128 and outs.max() >= 128 and not (mids % 8).any() and not (outs % 8).any()
+                     and not _few_samples(B, rs * rs, groups, int(outs.max()))
+                     and _tiles(B, rs * rs, groups) >= (150 if mids.max() <= 64 else 400))
         for b in range(nb):
             # dynamic depth: samples whose route has run its blocks of this stage contribute nothing
             on = (arch["nblk"][s][routes[s]] > b).astype(np.float64) if arch.get("nblk") is not None else np.ones(B)
@@ -123,6 +160,16 @@ def resnet_cost(arch, routes) -> Cost:
     return c
 
 
+def _tail(arch, live, B):
+    """(Q/K/V with its LayerNorm inside, launches behind the attention: "one", "three" or "four" and a LayerNorm)."""
+    de, hd, hid = live[:, 0], live[:, 1] * arch["head_dim"], live[:, 2]
+    if de.max() > 416:
+        return False, "four"
+    if arch["mlp"] <= 1664 and _tiles(B, arch["tokens"], arch["T"], 32) <= 56:
+        return True, "three"
+    return True, "one" if hd.max() <= 416 and not (hd % 16).any() else "four"
+
+
 def vit_cost(arch, routes) -> Cost:
     routes = np.asarray(routes).reshape(-1)
     tab = arch["routes"][routes].astype(np.float64)
@@ -136,7 +183,7 @@ def vit_cost(arch, routes) -> Cost:
         full = np.full(B, C, np.float64)
         c.add("stem", 2.0 * B * r * r * 147 * C, B * (3 * arch["image"] ** 2 * 2 + r * r * C * 2), name="stem 7x7/2")
         for _ in range(2):
-            if C % 8 == 0 and C <= 128 and r % 4 == 0:
+            if _separable(r, C, C, 1, 3, 3, False):
                 # the block runs as one kernel (depthwise map kept in LDS): one launch of the depthwise class
                 c.add("dwconv", 2.0 * B * r * r * 9 * C + 2.0 * B * r * r * C * C, 2.0 * 2 * B * r * r * C + 2.0 * C * C,
                       name="stem dw+pw fused")
@@ -145,8 +192,8 @@ def vit_cost(arch, routes) -> Cost:
                 _gemm(c, "gemm", r * r, r * r, 1, full, full, name="stem pw")
         c.add("gate", 2.0 * B * r * r * C, 2.0 * B * r * r * C, name="gate pool + MLP")
         # the patch projection reads every pixel of the stem's map once
-        _gemm(c, "gemm_taps", (N - 1) * arch["patch"] ** 2, N - 1, 1, full, de, name="patch embed conv")
-        c["gemm_taps"]["flops"] += 2.0 * (N - 1) * (arch["patch"] ** 2 - 1) * C * de.sum()
+        taps = arch["patch"] ** 2
+        _gemm(c, "gemm_taps", (N - 1) * taps, N - 1, taps, full, de, name="patch embed conv")
     else:
         kp = 3 * arch["patch"] ** 2
         c.add("index", 0.0, 2.0 * 2 * B * (N - 1) * kp, name="patch extraction")
@@ -159,15 +206,31 @@ def vit_cost(arch, routes) -> Cost:
             break
         de, h, hid = full[:, 0] * on, full[:, 1] * on, full[:, 2] * on
         hd = h * arch["head_dim"]
-        # everything behind the attention and the next block's LayerNorm is one launch
-        c.add("layernorm", 8.0 * N * de.sum(), 4.0 * N * de.sum(), name=f"l{l}.ln1", merge=l > 0)
-        k_in, k_out = de, 3 * hd
-        _gemm(c, "gemm", N, N, 1, k_in, k_out, name=f"l{l}.qkv")
+        live = arch["routes"] if tab.shape[1] < 4 else arch["routes"][arch["routes"][:, 3] > l]
+        fused, behind = _tail(arch, live, B)
+        ln = (8.0 * N * de.sum(), 4.0 * N * de.sum())
+        if fused:
+            c.add("inside", ln[0], 0.0, name=f"l{l}.ln1", launch=False)
+        else:
+            c.add("layernorm", *ln, name=f"l{l}.ln1")
+        _gemm(c, "gemm", N, N, 1, de, 3 * hd, name=("" if not fused else f"l{l}.ln1+") + f"l{l}.qkv")
         c.add("attention", 4.0 * N * N * hd.sum(), 2.0 * 4 * N * hd.sum(), name=f"l{l}.attention")
+        if behind == "one":
+            # rows in, the residual stream read and written; both hidden maps stay in the compute unit
+            w = hd.max() * de.max() + 2.0 * de.max() * hid.max()
+            c.add("inside", ln[0], 0.0, name=f"l{l}.ln2", launch=False)
+            c.add("gemm", 2.0 * N * (np.sum(hd * de) + 2.0 * np.sum(de * hid)), 2.0 * N * (hd.sum() + 2.0 * de.sum()) + 2.0 * w,
+                  name=f"l{l}.proj+res + ln2 + fc1+gelu + fc2+res",
+                  shape=f"rows {int(N) * int((de > 0).sum())} k {int(hd[de > 0].min())}..{int(hd.max())} n "
+                        f"{int(de[de > 0].min())}..{int(de.max())} hidden {int(hid[de > 0].min())}..{int(hid.max())}")
+            continue
         _gemm(c, "gemm", N, N, 1, hd, de, residual=True, name=f"l{l}.proj+res")
-        c.add("layernorm", 8.0 * N * de.sum(), 4.0 * N * de.sum(), name=f"l{l}.ln2", merge=True)
-        _gemm(c, "gemm", N, N, 1, de, hid, name=f"l{l}.fc1+gelu", chained=True)
-        _gemm(c, "gemm", N, N, 1, hid, de, residual=True, name=f"l{l}.fc2+res", chained=True)
+        if behind == "three":
+            c.add("inside", ln[0], 0.0, name=f"l{l}.ln2", launch=False)
+        else:
+            c.add("layernorm", *ln, name=f"l{l}.ln2")
+        _gemm(c, "gemm", N, N, 1, de, hid, name=("" if behind != "three" else f"l{l}.ln2+") + f"l{l}.fc1+gelu")
+        _gemm(c, "gemm", N, N, 1, hid, de, residual=True, name=f"l{l}.fc2+res")
     de = full[:, 0]
     c.add("layernorm", 8.0 * de.sum(), 4.0 * de.sum(), name="final ln (class token)")
     c.add("head", 2.0 * arch["num_classes"] * de.sum(), 2.0 * de.sum() + 2.0 * arch["num_classes"] * de.max(), name="classifier")

@@ -317,7 +317,7 @@ enum {
     DS_K_GEMM = 0,   // gemm_kernel on linear / 1x1 layers
     DS_K_GEMM_TAPS,  // gemm_kernel walking KxK taps (implicit-GEMM convolution)
     DS_K_ATTENTION,
-    DS_K_DWCONV,
+    DS_K_DWCONV,     // depthwise layers, alone or with the pointwise layer behind them in one kernel
     DS_K_LAYERNORM,
     DS_K_STEM,
     DS_K_MAXPOOL,
@@ -328,6 +328,8 @@ enum {
     DS_K_CONV3,      // conv3_kernel (3x3 stride-1 layers with the input patch staged once)
     DS_K_THIN,       // thin_kernel (short reductions, one workgroup per row tile; with or without a chained second layer)
     DS_K_TAIL,       // vit_tail_kernel (projection, MLP and LayerNorms of a transformer block)
+    DS_K_SMALL,      // gemm_small_kernel (launches of a few samples, any filter size)
+    DS_K_VIT_LINEAR, // vit_linear_kernel (linear layers on tiled weights, with or without the LayerNorm)
     DS_K_COUNT
 };
 struct ProfScope {

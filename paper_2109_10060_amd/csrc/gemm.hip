@@ -40,7 +40,6 @@ __device__ __forceinline__ int swz(int r) {
     return BK == 128 ? (r & 15) : BK == 64 ? ((r ^ (r >> 3)) & 7) : (((r >> 1) ^ (r >> 2)) & 3);
 }
 
-
 template <int WROWS, int WCOLS, int WMT, int WNT, int BK>
 struct Tile {
     static constexpr int BN = WCOLS * WNT * 32, LDS_LD = BK;

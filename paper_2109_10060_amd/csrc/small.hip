@@ -258,7 +258,7 @@ int32_t launch(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStrea
     const int32_t rc = ds_reserve_lds((const void*)kern, SMEM, "small sliced gemm");
     if (rc) return rc;
     const int ny = a.n_seg * ((max_kout + BN - 1) / BN);
-    ProfScope prof(a.K > 1 ? DS_K_GEMM_TAPS : DS_K_GEMM, s);
+    ProfScope prof(DS_K_SMALL, s);
     hipLaunchKernelGGL(kern, dim3((unsigned)(max_mtiles * (DS_GEMM_BM / BM) * ny)), dim3(64 * NW), SMEM, s, a, ny, max_mtiles);
     DS_CHECK_LAUNCH("small sliced gemm");
     return DS_OK;

@@ -172,7 +172,7 @@ int32_t launch(const VitLinearArgs& a, int64_t tiles, int max_blocks, int run_bl
     const int32_t rc = ds_reserve_lds((const void*)vit_linear_kernel<NW, R, D, KM>, SMEM, "tiled linear layer");
     if (rc) return rc;
     const int runs = (max_blocks + run_blocks - 1) / run_blocks;
-    ProfScope prof(DS_K_GEMM, s);
+    ProfScope prof(DS_K_VIT_LINEAR, s);
     hipLaunchKernelGGL((vit_linear_kernel<NW, R, D, KM>), dim3((unsigned)(tiles * runs)), dim3(64 * NW), SMEM, s, a, runs, run_blocks);
     DS_CHECK_LAUNCH("tiled linear layer");
     return DS_OK;

@@ -30,11 +30,13 @@ import os
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ["csrc/gemm.hip", "csrc/conv3.hip", "csrc/thin.hip", "csrc/common.h"]
-# the grouped GEMM is three kernels: gemm_kernel (linear, 1x1, strided and KxK layers), conv3_kernel (3x3 stride-1
-# layers) and thin_kernel (1x1 layers with at most 64 / 128 input channels); the summaries treat them as one kernel
-# class, as bench.py does
-GEMM_KERNELS = ("gemm_kernel", "conv3_kernel", "thin_kernel")
+KERNEL_SOURCES = ["csrc/gemm.hip", "csrc/conv3.hip", "csrc/thin.hip", "csrc/small.hip", "csrc/vit_linear.hip", "csrc/vit_tail.hip",
+                  "csrc/vit_rows.h", "csrc/gelu.h", "csrc/common.h"]
+# the grouped GEMM is several kernels: gemm_kernel (linear, 1x1, strided and KxK layers), conv3_kernel (3x3 stride-1
+# layers), thin_kernel (1x1 layers with at most 64 / 128 input channels), gemm_small_kernel (launches of a few samples),
+# vit_linear_kernel and vit_tail_kernel (transformer blocks on weights in operand order); the summaries treat them as one
+# kernel class, as bench.py does
+GEMM_KERNELS = ("gemm_kernel", "conv3_kernel", "thin_kernel", "gemm_small_kernel", "vit_linear_kernel", "vit_tail_kernel")
 
 
 def kernel_source_hash() -> str:
@@ -81,7 +83,7 @@ def traffic(fetch_csv, write_csv, copy_fetch_csv, copy_write_csv, copy_bytes, ou
     ff, fw = copy_kib / cf, copy_kib / cw
     gf, n = _per_launch(fetch_csv, "FETCH_SIZE", GEMM_KERNELS)
     gw, _ = _per_launch(write_csv, "WRITE_SIZE", GEMM_KERNELS)
-    out = {"kernel": "gemm_kernel+conv3_kernel+thin_kernel", "source_hash": kernel_source_hash(), "launches_sampled": n,
+    out = {"kernel": "+".join(GEMM_KERNELS), "source_hash": kernel_source_hash(), "launches_sampled": n,
            "fetch_kib_per_launch": gf, "write_kib_per_launch": gw, "fetch_factor": ff, "write_factor": fw,
            "hbm_bytes_per_launch": (gf * ff + gw * fw) * 1024.0, "commands": commands}
     json.dump(out, open(out_json, "w"), indent=1)
@@ -90,6 +92,7 @@ def traffic(fetch_csv, write_csv, copy_fetch_csv, copy_write_csv, copy_bytes, ou
 
 # kernel-name fragments -> class of the per-launch work list (cost.py)
 CLASS_OF = (("attention_kernel", "attention"), ("layernorm", "layernorm"), ("dwconv", "dwconv"), ("dwpw_kernel", "dwconv"),
+            ("dwband_kernel", "dwconv"), ("bandpw_kernel", "dwconv"),
             ("stem_", "stem"), ("maxpool_kernel", "maxpool"))
 PEAK_TFLOPS, PEAK_GBS = 2500.0, 8000.0
 

@@ -61,3 +61,21 @@ def test_gemm_bytes_count_each_operand_once():
 def test_bench_refuses_more_than_one_gpu():
     p = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert p.returncode != 0 and "one GPU" in (p.stderr + p.stdout)
+
+
+def test_records_add_up_to_the_class_totals_and_name_no_work_twice():
+    v = WL.vit_arch()
+    for arch, work, gates in ((WL.mbnet_arch(), C.mbnet_cost, 1), (WL.mbnet_pp_arch(), C.mbnet_cost, 1),
+                              (WL.resnet_arch(), C.resnet_cost, 4), (v, C.vit_cost, 1),
+                              (WL.vit_arch(stem_dim=24, patch=8), C.vit_cost, 1)):
+        for B in (1, 64, 256):
+            c = work(arch, np.stack([np.arange(B) % arch["T"]] * gates))
+            for kind, total in c.items():
+                mine = [r for r in c.launches if r["kind"] == kind]
+                assert len(mine) == total["launches"]
+                for key in ("flops", "bytes"):
+                    assert abs(sum(r[key] for r in mine) - total[key]) <= 1e-9 * total[key] or kind == "inside"
+    # the LayerNorms of the blocks run inside other launches and move nothing of their own; the final one reads 64 class tokens
+    c = C.vit_cost(v, np.full(64, v["T"] - 1))
+    assert c["layernorm"]["bytes"] == 4 * 64 * 384 and c["layernorm"]["launches"] == 1
+    assert c["inside"]["bytes"] == 0 and c["inside"]["flops"] == 8 * 64 * v["tokens"] * 384 * 24
