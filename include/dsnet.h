@@ -261,7 +261,11 @@ int32_t ds_sliced_mhsa(const void* x, int32_t B, int32_t N, int32_t D_e, const v
  *           per block: dw.w bf16 [k][k][C_in] (k = 3, or kfull[i]), dw.scale, dw.shift fp32 [Tb][C_in], pw.w bf16 [C_out][C_in],
  *           pw.scale, pw.shift fp32 [Tb][C_out] (Tb = 1 before the gate, T after),
  *           gate.w1 [gate_hidden][C], gate.b1, gate.w2 [T][gate_hidden], gate.b2 (fp32),
- *           fc.w bf16 [num_classes][C_last], fc.b fp32. */
+ *           fc.w bf16 [num_classes][C_last], fc.b fp32,
+ *           optionally, per block: pw.w once more as [ceil(C_out/32)][ceil(C_in/32) | 1] pairs of 1 KiB tiles (bf16, [quarter
+ *             of the 32 channels][16 rows][8 channels], the first tile of a pair with rows 0..3 of every eight, the second with
+ *             4..7, zeros beyond the matrix); the blocks in front of the gate then run as one kernel each.  The entries of
+ *             the blocks behind it are not read (any aligned pointer, such as pw.w itself). */
 #define DS_ARCH_MBNET  1
 /* DS_ARCH_RESNET: bottleneck ResNet, a gate in the first block of each of 4 stages (DS-ResNet).
  *   ints:   image, stem_out, T, num_classes, widths[4], blocks[4], gate_hidden[4], mid[4][T], out[4][T],
@@ -289,6 +293,7 @@ int32_t ds_sliced_mhsa(const void* x, int32_t B, int32_t N, int32_t D_e, const v
  *           ln.g, ln.b, head.w bf16 [num_classes][embed], head.b,
  *           optionally, per layer: wproj, fc1.w, fc2.w, wqkv (segment by segment) once more as [ceil(N/32)][ceil(K/16) | 1] tiles of 1 KiB (bf16,
  *             [k half][32 rows][8 channels], zeros beyond the matrix); the block's layers then run fused around the attention
+ *             where no slice exceeds 416 channels (embedding, heads * head_dim); the row-major weights serve all other cases
  *   Routes come from logit_bias (argmax) or route_override; one of them is required. */
 #define DS_ARCH_VIT    3
 /* DS_ARCH_VIT_STEM: DS_ARCH_VIT behind the convolutional stem of Section 3.4 (blocks [c, ds, ds, c]): a 7x7
