@@ -152,12 +152,9 @@ int32_t ds_sliced_linear(const void* x, int64_t x_ld, const void* w, int64_t w_l
 
 /* ds_sliced_linear for callers that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): same arguments, results and errors, without the
- * workspace.  The row-tile list the kernels read is kept in a device array built into the library
- * (DS_NOALLOC_MAX_TILES records of 16 bytes, 512 KiB + 256 bytes per GPU the library has run on, held
- * until the process ends); the call allocates and frees nothing and switches the ds_profile_* recording
- * off for its duration.  (B * rows + 127) / 128 + T must not exceed DS_NOALLOC_MAX_TILES
- * (DS_EWORKSPACE otherwise, before any launch).  All calls on one GPU share the array: calls that
- * overlap in time on one GPU (different streams or threads) race and must be ordered by the caller. */
+ * workspace.  The call allocates and frees nothing, shares no state with other calls and switches the
+ * ds_profile_* recording off for its duration.  A call may have at most DS_NOALLOC_MAX_TILES row tiles of
+ * 128 rows, counted as (B * rows - min(B, T)) / 128 + min(B, T) (DS_EWORKSPACE otherwise, before any launch). */
 #define DS_NOALLOC_MAX_TILES 32768
 int32_t ds_sliced_linear_noalloc(const void* x, int64_t x_ld, const void* w, int64_t w_ld, int32_t N_full,
                                  int32_t K_full, const float* bias, const ds_groups* g, int32_t B,

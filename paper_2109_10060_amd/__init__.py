@@ -274,7 +274,7 @@ def ds_sliced_linear(x, w, bias, groups: ds_groups, act=DS_ACT_NONE, residual=No
 
 
 def ds_sliced_linear_noalloc(x, w, bias, groups: ds_groups, y, act=DS_ACT_NONE, residual=None):
-    """ds_sliced_linear without a workspace (the library's built-in scratch); y is required, nothing is allocated."""
+    """ds_sliced_linear without a workspace; y is required, nothing is allocated."""
     B, rows, x_ld = x.shape
     N_full, K_full = w.shape
     _chk(load().ds_sliced_linear_noalloc(_ptr(x, torch.bfloat16), ctypes.c_int64(x_ld), _ptr(w, torch.bfloat16),

@@ -72,6 +72,7 @@ void linear_geometry(GemmArgs& a, int rows) {
 extern "C" size_t ds_gate_workspace(int32_t B, int32_t C) { return B > 0 && C > 0 ? ds_gate_partial_bytes(B, C) : 0; }
 extern "C" size_t ds_slot_workspace(int32_t B) { return ds_align_up((size_t)(B > 0 ? B : 0) * 4 + 4, 256); }
 
+// (the layer keeps nothing in it any more -- its kernels find their row tiles in the offsets -- but callers rely on the size)
 extern "C" size_t ds_sliced_linear_workspace(int32_t B, int32_t rows, int32_t T) {
     if (B < 0 || rows < 0 || T < 0) return 0;
     return ds_align_up(16 + ds_mtile_capacity(B, rows, T) * 16, 256);
@@ -81,7 +82,14 @@ extern "C" int32_t ds_sliced_linear(const void* x, int64_t x_ld, const void* w, 
                                     int32_t K_full, const float* bias, const ds_groups* g, int32_t B, int32_t rows,
                                     int32_t act, const void* residual, int64_t r_ld, void* y, int32_t y_dtype,
                                     int64_t y_ld, void* ws, size_t ws_bytes, void* stream) {
-    const char* who = "ds_sliced_linear";
+    return ds_sliced_linear_on("ds_sliced_linear", x, x_ld, w, w_ld, N_full, K_full, bias, g, B, rows, act, residual, r_ld, y,
+                               y_dtype, y_ld, ws, ws_bytes, true, (hipStream_t)stream);
+}
+
+int32_t ds_sliced_linear_on(const char* who, const void* x, int64_t x_ld, const void* w, int64_t w_ld, int32_t N_full,
+                            int32_t K_full, const float* bias, const ds_groups* g, int32_t B, int32_t rows, int32_t act,
+                            const void* residual, int64_t r_ld, void* y, int32_t y_dtype, int64_t y_ld, const void* ws,
+                            size_t ws_bytes, bool with_ws, hipStream_t s) {
     if (B < 0 || rows < 0 || N_full < 1 || K_full < 1) DS_FAIL(DS_EINVAL, "%s: negative or zero size", who);
     GroupTable gt;
     int mi, mo;
@@ -95,9 +103,8 @@ extern "C" int32_t ds_sliced_linear(const void* x, int64_t x_ld, const void* w, 
     if ((x_ld % 8) || (w_ld % 8) || (y_ld % 8) || (residual && (r_ld % 8)) || !ds_aligned16(x) || !ds_aligned16(w) ||
         !ds_aligned16(y) || !ds_aligned16(residual))
         DS_FAIL(DS_EALIGN, "%s: pointers need 16-byte alignment and strides multiples of 8", who);
-    if (!ws || ws_bytes < ds_sliced_linear_workspace(B, rows, g->T))
+    if (with_ws && (!ws || ws_bytes < ds_sliced_linear_workspace(B, rows, g->T)))
         DS_FAIL(DS_EWORKSPACE, "%s: workspace needs %zu bytes", who, ds_sliced_linear_workspace(B, rows, g->T));
-    hipStream_t s = (hipStream_t)stream;
     GemmArgs a;
     memset(&a, 0, sizeof(a));
     a.A = (const bf16_t*)x; a.Wt = (const bf16_t*)w; a.C = y; a.R = (const bf16_t*)residual;
@@ -122,7 +129,7 @@ extern "C" int32_t ds_sliced_linear(const void* x, int64_t x_ld, const void* w, 
 
 extern "C" size_t ds_sliced_conv_workspace(int32_t B, int32_t Ho, int32_t Wo, int32_t T) {
     if (B < 0 || Ho < 0 || Wo < 0 || T < 0) return 0;
-    return ds_align_up(16 + ds_mtile_capacity(B, Ho * Wo, T) * 16, 256) + ds_slot_workspace(B);
+    return ds_slot_workspace(B);
 }
 
 extern "C" int32_t ds_sliced_conv(const void* x, int32_t dtype, int32_t layout, int32_t B, int32_t C_I, int32_t H,
@@ -277,8 +284,7 @@ extern "C" int32_t ds_sliced_layernorm(const void* x, int64_t x_ld, const float*
 
 extern "C" size_t ds_sliced_mhsa_workspace(int32_t B, int32_t N, int32_t H, int32_t head_dim, int32_t T) {
     if (B < 0 || N < 0 || H < 0 || head_dim < 0 || T < 0) return 0;
-    return ds_align_up(16 + ds_mtile_capacity(B, N, T) * 16, 256) + ds_slot_workspace(B) +
-           4 * ds_align_up((size_t)B * N * H * head_dim * sizeof(bf16_t), 256);
+    return ds_slot_workspace(B) + 4 * ds_align_up((size_t)B * N * H * head_dim * sizeof(bf16_t), 256);
 }
 
 extern "C" int32_t ds_sliced_mhsa(const void* x, int32_t B, int32_t N, int32_t D_e, const void* wqkv,
@@ -304,7 +310,6 @@ extern "C" int32_t ds_sliced_mhsa(const void* x, int32_t B, int32_t N, int32_t D
         DS_FAIL(DS_EWORKSPACE, "%s: workspace needs %zu bytes", who, ds_sliced_mhsa_workspace(B, N, H, head_dim, g->T));
     hipStream_t s = (hipStream_t)stream;
     char* p = (char*)ws;
-    p += ds_align_up(16 + ds_mtile_capacity(B, N, g->T) * 16, 256);
     int32_t* slot_group = (int32_t*)p;
     p += ds_slot_workspace(B);
     const size_t bufsz = ds_align_up((size_t)B * N * Hd * sizeof(bf16_t), 256);

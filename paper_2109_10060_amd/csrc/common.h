@@ -133,6 +133,11 @@ __device__ __forceinline__ int4 ds_tile_record(const GemmArgs& a, int mt) {
 #endif
 
 size_t ds_mtile_capacity(int32_t B, int32_t rows, int32_t T);
+// ds_sliced_linear; with_ws: a workspace is demanded
+int32_t ds_sliced_linear_on(const char* who, const void* x, int64_t x_ld, const void* w, int64_t w_ld, int32_t N_full,
+                            int32_t K_full, const float* bias, const ds_groups* g, int32_t B, int32_t rows, int32_t act,
+                            const void* residual, int64_t r_ld, void* y, int32_t y_dtype, int64_t y_ld, const void* ws,
+                            size_t ws_bytes, bool with_ws, hipStream_t s);
 int32_t ds_launch_gemm(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s);
 // 1x1 / linear layers with input slices of at most 64 channels and several 64-column passes: one workgroup per 128 rows
 // and all their columns; DS_EUNSUPPORTED otherwise

@@ -1,6 +1,6 @@
 """ds_sliced_linear_noalloc (the entry point for callers that cannot allocate device memory) against
-ds_sliced_linear and the CPU oracle: two calls in a row on the library's built-in scratch, the second
-with a smaller input, so that stale records of the first call's row-tile list would show."""
+ds_sliced_linear and the CPU oracle: two calls in a row, the second with a smaller input, so that anything a call
+left behind for the next one would show."""
 import ctypes
 
 import numpy as np
@@ -32,7 +32,7 @@ def _case(gpu_lib, c, act, with_res):
     y_ref = torch.full((B, N, 4 * K), float("nan"), dtype=torch.bfloat16, device=DEV)
     y_new = torch.full((B, N, 4 * K), float("nan"), dtype=torch.bfloat16, device=DEV)
     gpu_lib.ds_sliced_linear(x, w, bias, g, act=act, residual=res, y=y_ref)
-    if not _case.warm:          # the first call on a device looks up the scratch array (and loads its code object)
+    if not _case.warm:          # the first call on a device loads its code object
         gpu_lib.ds_sliced_linear_noalloc(x, w, bias, g, y_new, act=act, residual=res)
         y_new.fill_(float("nan"))
         _case.warm = True
