@@ -148,10 +148,12 @@ def _ws(nbytes: int, like: torch.Tensor) -> torch.Tensor:
 
 def make_groups(offsets: torch.Tensor, perm: Optional[torch.Tensor], k_in: Sequence[int],
                 k_out: Optional[Sequence[int]] = None, table_row: Optional[Sequence[int]] = None) -> ds_groups:
+    """Host table of a layer's route groups; it keeps the offsets and the permutation alive."""
     g = ds_groups()
     T = len(k_in)
     assert T <= DS_MAX_GROUPS
     g.T = T
+    g.tensors = (offsets, perm)          # the structure itself holds addresses only
     g.offsets = _addr(offsets, torch.int32)
     g.perm = _addr(perm, torch.int32)
     g.k_in[:T] = k_in = [int(v) for v in k_in]
