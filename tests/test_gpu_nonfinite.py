@@ -166,3 +166,78 @@ def test_front_block_pixels_stay_apart(gpu_lib, pp, image):
         assert torch.equal(want[i][0], got[i][0]), i
         a, b = want[i][1][~reach].float(), got[i][1][~reach].float()
         assert torch.isfinite(b).all() and (a - b).norm() <= 4e-3 * a.norm(), i
+
+
+# Whatever is stored beyond a slice -- weights, channels of the activations, table entries -- takes no part in its results
+def _outside(t, *keep):
+    """t with everything beyond the leading keep[i] entries of axis i set to NaN."""
+    inside = torch.zeros(t.shape, dtype=torch.bool, device=t.device)
+    inside[tuple(slice(k) for k in keep)] = True
+    return torch.where(inside, t, torch.full_like(t, float("nan")))
+
+
+def _one_group(gpu_lib, B, k_in, k_out=None):
+    off = torch.tensor([0, B], dtype=torch.int32, device=DEV)
+    return gpu_lib.make_groups(off, None, [k_in], [k_out] if k_out else None)
+
+
+@pytest.mark.parametrize("B,rows,K,N,k_in,k_out", [(1, 5, 384, 512, 200, 328), (3, 197, 384, 512, 200, 328), (64, 197, 384, 1536, 200, 1080),
+                                                   (300, 197, 128, 256, 56, 136), (40, 197, 1536, 384, 808, 200)])
+@pytest.mark.parametrize("act", [0, 2])
+def test_linear_outside_the_slice(gpu_lib, B, rows, K, N, k_in, k_out, act):
+    x, w, res = _randn((B, rows, K), 1), _randn((N, K), 2), _randn((B, rows, N), 3)
+    bias = torch.randn(N, device=DEV)
+    g = _one_group(gpu_lib, B, k_in, k_out)
+    for r in (None, res):
+        want = gpu_lib.ds_sliced_linear(x, w, bias, g, act=act, residual=r)
+        got = gpu_lib.ds_sliced_linear(_outside(x, B, rows, k_in), _outside(w, k_out, k_in), _outside(bias, k_out), g, act=act,
+                                       residual=None if r is None else _outside(r, B, rows, k_out))
+        assert torch.isfinite(want).all() and torch.equal(got, want)
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("B,K,stride,H,C,N,c_in,c_out", [
+    (1, 3, 1, 14, 128, 128, 72, 40), (2, 1, 1, 14, 264, 512, 136, 264), (3, 3, 2, 15, 64, 96, 24, 56), (64, 3, 1, 28, 128, 128, 72, 104),
+    (64, 1, 1, 56, 64, 256, 40, 136), (33, 1, 2, 28, 256, 512, 136, 264), (2, 5, 1, 9, 32, 32, 8, 24)])
+def test_conv_outside_the_slice(gpu_lib, f32, B, K, stride, H, C, N, c_in, c_out):
+    if f32 and B > 4:
+        B = 4
+    nhwc, pad = (lambda t: t if f32 else t.permute(0, 2, 3, 1).contiguous()), K // 2
+    dt = torch.float32 if f32 else torch.bfloat16
+    x, w = _randn((B, C, H, H), 4).to(dt), (0.1 * _randn((N, C, K, K), 5)).to(dt)
+    scale, shift = torch.randn((1, N), device=DEV), torch.randn((1, N), device=DEV)
+    g = _one_group(gpu_lib, B, c_in, c_out)
+    want = gpu_lib.ds_sliced_conv(nhwc(x), nhwc(w), scale, shift, g, stride, pad)
+    got = gpu_lib.ds_sliced_conv(nhwc(_outside(x, B, c_in)), nhwc(_outside(w, c_out, c_in)), _outside(scale, 1, c_out),
+                                 _outside(shift, 1, c_out), g, stride, pad)
+    assert torch.isfinite(want).all() and want.abs().max() > 0 and torch.equal(got, want)
+
+
+@pytest.mark.parametrize("B,H,C,c", [(2, 14, 72, 40), (33, 28, 136, 72), (3, 7, 1024, 520)])
+def test_depthwise_and_rows_outside_the_slice(gpu_lib, B, H, C, c):
+    x, w, w7 = _randn((B, H, H, C), 6), _randn((3, 3, C), 7), _randn((7, 7, C), 8)
+    one, shift = torch.ones((1, C), device=DEV), torch.randn((1, C), device=DEV)
+    g = _one_group(gpu_lib, B, c)
+    bad = [_outside(t, *t.shape[:-1], c) for t in (x, w, w7, one, shift)]
+    for stride in (1, 2):
+        assert torch.equal(gpu_lib.ds_sliced_dwconv(x, w, one, shift, g, stride),
+                           gpu_lib.ds_sliced_dwconv(bad[0], bad[1], bad[3], bad[4], g, stride))
+        for k, l in ((3, 1), (5, 1), (7, 1), (7, 2)):
+            a, b = (gpu_lib.ds_sliced_dwconv_spatial(v[0], v[2], v[3], v[4], g, [k], [l], [k // 2], stride)[0]
+                    for v in ((x, w, w7, one, shift), bad))
+            assert torch.equal(a, b)
+    rows, beta = x.reshape(B, H * H, C), shift[0]
+    assert torch.equal(gpu_lib.ds_sliced_layernorm(rows, one[0], beta, 1e-6, g),
+                       gpu_lib.ds_sliced_layernorm(bad[0].reshape(B, H * H, C), bad[3][0], bad[4][0], 1e-6, g))
+
+
+@pytest.mark.parametrize("B,N", [(2, 17), (33, 197)])
+def test_attention_outside_the_slice(gpu_lib, B, N):
+    D, H, dh, de, h = 192, 6, 48, 104, 3
+    x, wqkv, wproj = _randn((B, N, D), 9), 0.1 * _randn((3, H * dh, D), 10), 0.1 * _randn((D, H * dh), 11)
+    bqkv, bproj, res = torch.randn((3, H * dh), device=DEV), torch.randn(D, device=DEV), _randn((B, N, D), 12)
+    g = _one_group(gpu_lib, B, de, h * dh)
+    want = gpu_lib.ds_sliced_mhsa(x, wqkv, bqkv, wproj, bproj, H, dh, g, residual=res)
+    got = gpu_lib.ds_sliced_mhsa(_outside(x, B, N, de), _outside(wqkv, 3, h * dh, de), _outside(bqkv, 3, h * dh),
+                                 _outside(wproj, de, h * dh), _outside(bproj, de), H, dh, g, residual=_outside(res, B, N, de))
+    assert torch.isfinite(want).all() and torch.equal(got, want)
