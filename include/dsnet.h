@@ -24,6 +24,12 @@
  *    ds_last_error() gives a thread-local message.  B == 0 is a valid no-op.
  *  - bf16 tensors need 16-byte aligned base pointers and slice sizes, leading
  *    strides and channel counts that are multiples of 8 (DS_EALIGN otherwise).
+ *  - Infinities and NaN: samples never mix, and nothing stored beyond a slice
+ *    takes part in a result.  Padding counts as zeros that are multiplied, so a
+ *    weight that is not finite makes border outputs NaN.  ReLU gives 0 for NaN.
+ *    The depthwise kernels for plain 3 x 3 filters and for dilated or wider-stepped
+ *    ones multiply channels in pairs: there a pixel that is not finite in channel c
+ *    also reaches channel c ^ 1 of the same outputs.
  */
 #ifndef DSNET_H
 #define DSNET_H

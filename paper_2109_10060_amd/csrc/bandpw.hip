@@ -6,12 +6,13 @@
 // two layers apart, and a workgroup per tile, lose is the map in between and every tile's chain of load, depthwise, product
 // and store.  A workgroup here stays, goes over tiles of RO rows x up to 16 columns (PT at a time), and has the next tile's
 // pixels on their way from the moment that the present ones are in LDS; both layers' filters stay in registers and LDS.
-// 7 rows at stride 1, 4 at stride 2.  256 images (both layers before -> here; what moving input and output once takes):
-//   112x112, 32 -> 64                  161 -> 143 (130) us      112x112, 64 -> 128, stride 2   149 -> 130 (130)
-//   56x56, 128 -> 128                  154 ->  98 (86)          56x56, 128 -> 256, stride 2     97 ->  63 (65)
-//   28x28, 256 -> 256                  116 ->  68 (43)
-// and for 5x5 filters, 96 images: 112x112, 16 -> 32 68 -> 36 (24); 112x112, 32 -> 48, stride 2 45 -> 25 (22); 56x56, 48 -> 48
-// 40 -> 23 (12).  The thinnest layers are bound by the vector instructions around the products (batch-norm, packing).
+// 7 rows at stride 1, 4 at stride 2.  256 images (both layers before -> here; what moving input and output once takes at the
+// 5.1 TB/s of a large copy; profiles/layers_mbnet_b256.txt, layers_mbnet_pp_b96.txt):
+//   112x112, 32 -> 64                  141 -> 135 (121) us      112x112, 64 -> 128, stride 2   143 -> 148 (121)
+//   56x56, 128 -> 128                  134 ->  95 (81)          56x56, 128 -> 256, stride 2     88 ->  70 (60)
+//   28x28, 256 -> 256                  102 ->  64 (40)
+// and for 5x5 filters, 96 images: 112x112, 16 -> 32 70 -> 34 (23); 112x112, 32 -> 48, stride 2 41 -> 25 (21); 56x56, 48 -> 48
+// 44 -> 22 (11).  The thinnest layers are bound by the vector instructions around the products (batch-norm, packing).
 //   windows       pixels x channels of a chunk (16 NW / PT channels), by channel, in LDS;
 //   depthwise     a wavefront takes 16 channels of a tile: filter rows as band matrices (band.h), batch-norm, ReLU, bf16 into
 //                 the operand tile [pixel][channel];

@@ -10,6 +10,8 @@
 // channels.  All loads of a slice are requested before the first is used.  The four partial tiles are added in LDS in
 // wavefront order; every lane then stores four results of one pixel column (128-byte runs over the lanes).
 // The kernel finds a slot's route group in the offsets itself, so no slot table has to be built first.
+// Padding is zeros that are multiplied, as in every other convolution here except conv_f32_kernel, which skips it: with a
+// weight that is not finite the outputs at the border are NaN.
 #include "common.h"
 
 namespace {

@@ -10,9 +10,9 @@
 // with zeros around its rows.  A wavefront holds 16 channels' bands in registers and goes over 7 output rows of four strips
 // at a time: every input row is read once and added to the (up to 7) output rows that it touches.  Maps are multiples of
 // 7 high.
-// Bound: memory at large maps (256 images, 112x112: 80 us for 300 MB), a workgroup's chain of loads, LDS and stores at
-// small ones (6..8 us for 8 images).  288..640 channels of 14x14, filters of 3 / 5 / 7 taps, 96 images: 18 us (29 us with
-// dot products on channel pairs read straight from memory, 24 us with tap pairs from LDS).
+// Bound: memory at large batches (288..640 channels of 14x14, filters of 3 / 5 / 7 taps, 256 images: 34 us for 93 MB), a
+// workgroup's chain of loads, LDS and stores at small ones (6 us for 8 images).  96 images: 17 us, against 28 us with dot
+// products on channel pairs read straight from memory.
 #include <algorithm>
 
 #include "band.h"
@@ -168,8 +168,9 @@ int32_t ds_launch_dwband(ActView x, ActView y, const bf16_t* w, int32_t KS, cons
     if (B <= 0 || cmax <= 0 || ho <= 0 || wo <= 0) return DS_OK;
     // Tiles of at most 7 strips (28 outputs, or equal parts of a row) by 7 or 14 rows: three to five workgroups' windows
     // in a compute unit.  14 rows where that leaves 1024 workgroups and the window is under 48 KiB (288..640 channels of
-    // 14x14, 256 images: 34 us, 44 in 7 rows).  64 channels where 7 rows of 16 channels are one pass only (maps up to 16
-    // wide, at the smallest batches up to 8), so that every wavefront has one (800..1152 channels of 7x7: 35 us, 41 with 32).
+    // 14x14, 256 images: 34 us, 43 in 7 rows; 96 images 17 and 21).  64 channels where 7 rows of 16 channels are one pass only
+    // (maps up to 16 wide, at the smallest batches up to 8), so that every wavefront has one (800..1152 channels of 7x7, 256
+    // images: 35 us, 39 with 32; 96 images 17 and 18; profiles/dispatch_choices.txt).
     const int sx = (wo + 3) / 4, xt = (sx + 6) / 7, txs = (sx + xt - 1) / xt;
     const auto bytes = [&](int cw, int ty) {
         return band_window(cw, band_pitch((ty - 1) * stride + nmax, band_quads(txs, nmax, stride))) + ((cw * band_filter_pitch(nmax, stride) + 15) & ~15);

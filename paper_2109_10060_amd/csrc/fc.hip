@@ -424,8 +424,8 @@ __global__ __launch_bounds__(256) void fc_mfma64_kernel(const FcArgs a) {
 // A few items: bound by the one read of the weights and by latency, so every output gets a wavefront of its own and its
 // whole weight row is requested at once (C <= 2048: PIECES 16-byte pieces per lane), kept in registers while the items, IG
 // at a time, are multiplied with it and reduced side by side.  The tiled kernels walk the reduction 64 channels at a time on
-// n_out / 16 workgroups: 1000 outputs of 2048 channels (bf16) for one image 42.9 us, here under 5; the gate's 256 hidden
-// units of 1024 channels (fp32 weights, fp64 sums, SRC = 2: the pool's partial sums) 22 us, here 4.
+// n_out / 16 workgroups: DS-ResNet's classifier (1000 outputs, bf16) for one image of the benchmark 15.6 us, here 3.6; the
+// last gate's 256 hidden units (fp32 weights, fp64 sums, SRC = 2: the pool's partial sums) 9.6 us, here 4.4.
 // SRC: 0 bf16 rows, 1 one fp32 sum per channel, 2 several
 template <typename WT, typename ACC, int SRC, int IG>
 __global__ __launch_bounds__(256) void fc_few_kernel(const FcArgs a) {

@@ -698,8 +698,11 @@ int32_t vit_behind_attention(const VitDesc& d, const void* const* L, const void*
     const int64_t x_ss = (int64_t)d.N * d.D;
     const int kbp = (Hd + 15) / 16 | 1, kb1 = (d.D + 15) / 16 | 1, kb2 = (d.M + 15) / 16 | 1;
     const int nbd = (d.D + 31) / 32, nbm = (d.M + 31) / 32;
-    // up to about 56 tiles of 32 rows three launches over many workgroups beat one whose every workgroup streams all weights
-    // (5 images 29 against 35 us); above, they cost what their extra passes and workgroups do (16 images 40 against 33 us)
+    // Up to about 56 tiles of 32 rows three launches over many workgroups instead of one whose every workgroup streams all
+    // weights.  The routes are on the device, so this cannot depend on them: a pass of 5 images takes 620 against 773 us on the
+    // widest route, 590 against 668 on five different ones, and 521 against 416 on the narrowest, where the block's weights
+    // are a tenth.  Above, the launches cost what their extra passes and workgroups do (16 images 34 against 25 us a block;
+    // profiles/dispatch_choices.txt).
     const int groups = B < d.T ? B : d.T;
     const bool few = d.M <= 1664 && ((int64_t)B * d.N - groups) / 32 + groups <= 56;
     if (!few) {

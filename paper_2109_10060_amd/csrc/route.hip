@@ -313,7 +313,7 @@ __global__ __launch_bounds__(GF_NT) void gate_fused_kernel(const GateArgs a, con
 // with the same key (stable), so the scatter is parallel over samples.
 // Up to 64 groups (bucket64_kernel) nothing is counted serially: the scans run over the lanes of a wavefront, and a rank is
 // the number of earlier lanes with the same key -- six ballots, one per key bit -- plus the counts of the earlier
-// wavefronts.  16 / 48 groups of 256 samples with two tile lists: 11 / 20 -> 5 us; one sample 5.8 -> 3.4 us.
+// wavefronts.  16 / 48 groups of 256 samples with two tile lists: 11 / 20 -> 5 to 8 / 5 us; one sample 6 -> 4 us.
 __global__ __launch_bounds__(1024) void bucket64_kernel(const BucketArgs a) {
     __shared__ int cnt[16][64];                          // samples per wavefront and key of the current 1024
     __shared__ int base[65], start[65];                  // next free slot of a key; first slot of a key
@@ -639,8 +639,9 @@ int32_t ds_launch_gate(const GateArgs& a, hipStream_t s) {
     if (a.x && a.C <= GF_CMAX && a.C_mlp <= GF_HMAX && a.T <= 64 && rows16) {
         const int64_t map_bytes = (int64_t)a.C * a.HW * (a.dtype == DS_BF16 ? 2 : 4);
         // one compute unit pools up to 512 KiB and 512 channels in less time than a launch costs (9 us with the MLP, against
-        // 16-26 us for pool, hidden layer and output layer one after the other); above, the pool kernel's several workgroups
-        // per item first (196 x 1024 channels: 25 us in one workgroup, 21 in two launches)
+        // 14 us and two launches more for pool, hidden layer and output layer one after the other; 256 images 20 against
+        // 30); above, the pool kernel's several workgroups per item first (second gate of DS-ResNet, 1 / 33 images: 16.3 / 17.0 us
+        // in two launches, 18.8 / 21.8 in one workgroup; 256 images 65 and 57; profiles/dispatch_choices.txt)
         const bool pooled = map_bytes <= (512 << 10) && a.C <= 512;
         int splits = 1;
         if (!pooled) {
@@ -649,7 +650,7 @@ int32_t ds_launch_gate(const GateArgs& a, hipStream_t s) {
         }
         int lcl = 0;
         while ((8 << lcl) < a.C && lcl < 6) ++lcl;
-        // one or two items with 1 MiB of hidden weights: 18 us in one workgroup, about 10 with a wavefront per unit
+        // one or two items with 1 MiB of hidden weights: 10.3 / 14.9 us in one workgroup, 9.5 / 12.8 with a wavefront per unit
         if (!pooled && a.B <= 2 && (int64_t)a.C * a.C_mlp >= (256 << 10)) {
             float* hid = a.partial + (size_t)a.B * a.C * POOL_SPLIT_MAX;
             FcArgs f = {};

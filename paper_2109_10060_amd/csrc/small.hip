@@ -2,7 +2,7 @@
 //
 // With one to a few dozen samples a layer has 49 to a few thousand rows: gemm_kernel's 128 x 64 tiles then leave most of
 // the 256 compute units without a workgroup, and the workgroups that exist walk the whole reduction alone (one image,
-// last ResNet stage: 8 workgroups, 36 dependent 128-deep slabs, 30 us for a 3x3 layer).  What bounds such a launch is
+// last ResNet stage: 8 workgroups, up to 36 dependent 128-deep slabs).  What bounds such a launch is
 // the length of that chain, so here the reduction is cut as well: a wavefront owns a WM*32 x WN*32 tile and every KS-th
 // 64-deep slab of its reduction, the KS partial tiles are added in LDS in wavefront order, and a wavefront keeps PD
 // slabs travelling in registers.  Its operand slabs go through an LDS region of its own (global loads cover whole
@@ -267,20 +267,20 @@ int32_t launch(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStrea
 }  // namespace
 
 // Which tile, by the number t of 32 x 32 tiles the launch can have and the number nk of 64-deep slabs of its reduction.
-// Measured on single layers of the networks at 1 to 33 samples, kernel time in us, general kernels -> here:
+// Measured on the layers of DS-ResNet with the benchmark's routes, kernel time in us, general kernels -> here
+// (profiles/dispatch_choices.txt; stages counted from 1):
 //   t <= 340    one tile and 8 shares of the reduction per workgroup: every compute unit gets at most one or two, so the
-//               length of a share is all that counts (3x3 512 channels, one sample 30.1 -> 13.8; 1x1 2048 -> 512 17.1 -> 7.8;
-//               six- and seven-slab linear layers of one sample 10.8 -> 6.1)
-//   t <= 500    32 x 64 tiles, 8 shares (24-slab linear layer of 5 samples 15.7 -> 8.6), 32 x 32 and 4 shares when
-//               there are fewer slabs than shares
-//   t <= 700    32 x 32, 4 shares (1x1 2048 -> 512 of 16 samples 22.0 -> 10.8, 3x3 512 37.7 -> 21.8)
-//   t <= 1000   64 x 64 tiles, 8 shares, for 24 slabs and more (3x3 256 of 16 samples 22.2 -> 16.8), 32 x 64 tiles and 4
-//               shares (1x1 1024 -> 256 14.5 -> 10.6), two column tiles and 2 shares up to four slabs (10.0 -> 6.9)
+//               length of a share is all that counts (stage 4, one sample: 3x3 13.2 -> 6.7, first 1x1 9.6 -> 5.0; four samples
+//               38.8 -> 13.2, 21.8 -> 8.3; DS-MBNet's pointwise layers, one sample 7.3 -> 5.2)
+//   t <= 500    32 x 64 tiles, 8 shares (stage 3, eight samples: 3x3 23.0 -> 12.4, 1x1 14.0 -> 8.6), 32 x 32 and 4 shares
+//               when there are fewer slabs than shares (stage 4, four samples, last 1x1 10.7 -> 6.0)
+//   t <= 700    32 x 32, 4 shares (stage 4, 16 samples: 1x1 21.5 -> 10.2, 3x3 39.0 -> 17.8)
+//   t <= 1000   64 x 64 tiles, 8 shares, for 24 slabs and more (stage 3, 16 samples: 3x3 22.8 -> 14.8), 32 x 64 tiles and 4
+//               shares (1x1 14.6 -> 11.0), two column tiles and 2 shares up to four slabs (four samples 9.2 -> 7.2)
 //   ordered     one wavefront walks a tile's whole reduction, three slabs ahead, two tiles per workgroup, up to 1700 tiles
-//               (linear layers of 1 / 5 / 16 images of 197 tokens: 24 slabs 11.5 -> 9.5 / 15.5 -> 11.7 / 16.2 -> 15.3, six
-//               slabs 8.4 -> 6.8 / 10.9 -> 7.7 / 11.1 -> 10.1)
+//               (patch embedding of DS-ViT, twelve slabs, 1 / 5 / 16 images 13.8 -> 11.5 / 14.8 -> 11.5 / 14.1 -> 12.1)
 //   beyond      the 128-row kernels have enough workgroups and read less per product -- except the strided KxK layers
-//               (no staged patch for them), which stay here up to 1700 tiles (33 samples: 49.3 -> 26.7, 30.2 -> 25.2)
+//               (no staged patch for them), which stay here up to 1700 tiles (stage 4, 33 samples 48.0 -> 23.1)
 int32_t ds_launch_gemm_small(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
     if (max_mtiles <= 0 || max_kout <= 0 || a.B <= 0 || a.H > 32767 || a.W > 32767) return DS_EUNSUPPORTED;
     const bool conv = a.K > 1 || a.stride > 1 || a.pad > 0;

@@ -180,9 +180,9 @@ int32_t launch(const VitLinearArgs& a, int64_t tiles, int max_blocks, int run_bl
 
 }  // namespace
 
-// Measured on DS-ViT's Q/K/V layer with its LayerNorm (us): 1 / 5 / 16 images with 4 wavefronts and 4 blocks a workgroup 8.7 /
-// 9.7 / 16.4, 8 blocks 11.0 / 11.4 / 14.8; 64 images with 12 wavefronts and 64 rows 25, 96 rows 30; 256 images 64 and 60
-// (gemm_kernel 55 and its LayerNorm 12).  Reductions beyond 416 channels (fc2) are for the few-image path alone: 107 KB of rows.
+// Measured on DS-ViT's Q/K/V layer with its LayerNorm (us, profiles/dispatch_choices.txt): 1 / 5 / 16 images with 4 wavefronts
+// and 4 blocks a workgroup 8.3 / 8.8 / 14.6, 8 blocks 10.2 / 10.4 / 12.9; 64 images with 12 wavefronts and 64 rows 23, 96 rows
+// 28; 256 images 59 and 57 (gemm_kernel 53 and its LayerNorm 12).  Reductions beyond 416 channels (fc2) are for the few-image path alone: 107 KB of rows.
 int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s) {
     int kmax = 0, nmax = 0;
     for (int t = 0; t < a.gt.T; ++t) {

@@ -13,8 +13,8 @@
 // operand as one contiguous kilobyte straight into registers, D of them in flight, and LDS serves the activations alone.
 // Each of the NW = 12 (13 above 384 channels) wavefronts owns one 32-column block of the block's width and of every
 // HC = 32 NW columns of the hidden layer; R row blocks share every weight operand.
-// DS-ViT, 256 images: 149 us (projection 29, LayerNorm 12, fc1 66, fc2 54, less launch overlap) -> 121 us per block;
-// 64 images 71 -> 51 us; 16 images 44 -> 33 us.
+// DS-ViT, kernel time per block (profiles/layers_vit_*): 256 images 158 us (projection 29, LayerNorm 12, fc1 64, fc2 54) -> 124
+// to 132 us; 64 images 66 -> 48 us; 16 images 41 -> 25 us.
 //
 // Sums run in the order of gemm_kernel's and layernorm16_kernel's, so the results are the same bits.
 #include "gelu.h"
@@ -278,10 +278,11 @@ int32_t launch(const VitTailArgs& a, int64_t tiles, hipStream_t s) {
 
 }  // namespace
 
-// Rows per workgroup.  A workgroup streams all weights of the block whatever its rows (2.7 MB at full width, ~25 us at what
-// one compute unit takes in), so many rows each are better -- as long as there is a workgroup for every compute unit.
-// Measured per launch on DS-ViT: 16 images 35.6 / 43.0 / 54.8 us with 32 / 64 / 96 rows, 64 images 56.4 / 54.7 / 67.2,
-// 256 images 181 / 136 / 131.
+// Rows per workgroup.  A workgroup streams all weights of the block whatever its rows (2.7 MB at full width), so more rows
+// each are better -- as long as there is a workgroup for every compute unit.  Measured per launch on DS-ViT
+// (profiles/dispatch_choices.txt): 16 images 25 / 31 / 37 us with 32 / 64 / 96 rows, 64 images 49 / 48 / 61, 256 images
+// 155 / 112 / 125.  The line at 448 tiles of 96 rows dates from weights addressed through one descriptor (136 against 131 us
+// there); with a descriptor per row block 64 rows are the better choice at 256 images too (2669 against 2733 us a pass).
 int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {
     int dmax = 0;
     for (int t = 0; t < a.gt.T; ++t) {
