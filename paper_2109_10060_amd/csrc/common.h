@@ -268,7 +268,6 @@ int32_t ds_launch_conv_f32_mfma(const float* x, const float* w, const float* sca
                                 const float* residual, float* y, const int32_t* offsets, const int32_t* perm,
                                 const GroupTable& gt, int32_t B, int32_t C_I, int32_t C_O, int32_t H, int32_t W, int32_t K,
                                 int32_t stride, int32_t pad, int32_t act, hipStream_t s);
-int32_t ds_launch_compose_index(const int32_t* inner, const int32_t* outer, int32_t* out, int32_t B, hipStream_t s);
 int32_t ds_launch_lookup(const int32_t* idx, const GroupTable& gt, int32_t which, int32_t* out, int32_t B, hipStream_t s);
 
 // ---- attention ----------------------------------------------------------------
@@ -312,10 +311,6 @@ struct VitLinearArgs {
 int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s);
 // DS_EUNSUPPORTED where a slice exceeds 416 channels (hidden: any) or its alignment
 int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s);
-
-// ---- small index helpers ---------------------------------------------------------
-// key[b] = hi[b] * mul + (lo ? lo[b] : 0)
-int32_t ds_launch_make_key(const int32_t* hi, const int32_t* lo, int32_t mul, int32_t* key, int32_t B, hipStream_t s);
 
 // ---- per-kernel timing with HIP events (off unless ds_profile_enable(1)) ---------
 enum {

@@ -36,55 +36,10 @@ __global__ void expand_groups_kernel(const int32_t* offsets, int T, int32_t* slo
 }
 
 // ---- depthwise 3x3 + scale/shift + activation ---------------------------------
-// grid (ceil(Ho*Wo*C/8 / 256), B); thread = (output pixel, 8-channel chunk)
-__global__ __launch_bounds__(256) void dwconv_kernel(ActView x, ActView y, const bf16_t* w, const float* scale,
-                                                     const float* shift, int tab_ld, const int32_t* slot_group,
-                                                     const GroupTable gt, int C, int H, int W, int Ho, int Wo,
-                                                     int stride, int act) {
-    const int slot = blockIdx.y;
-    const int g = slot_group ? slot_group[slot] : 0;
-    const int c = gt.k_in[g];
-    const int chunks = c >> 3;
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= Ho * Wo * chunks) return;
-    const int pix = idx / chunks, ch = (idx - pix * chunks) * 8;
-    const int oy = pix / Wo, ox = pix - oy * Wo;
-    const int xs = x.index ? x.index[slot] : slot;
-    const int ys = y.index ? y.index[slot] : slot;
-    const int xld = x.ld > 0 ? x.ld : c, yld = y.ld > 0 ? y.ld : c;
-    const bf16_t* xp = (const bf16_t*)x.p + (int64_t)xs * x.sample_stride + ch;
-    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int u = 0; u < 3; ++u) {
-        const int iy = oy * stride + u - 1;
-        if (iy < 0 || iy >= H) continue;
-#pragma unroll
-        for (int v = 0; v < 3; ++v) {
-            const int ix = ox * stride + v - 1;
-            if (ix < 0 || ix >= W) continue;
-            float xv[8], wv[8];
-            unpack8(*(const uint4*)(xp + (int64_t)(iy * W + ix) * xld), xv);
-            unpack8(*(const uint4*)(w + (u * 3 + v) * C + ch), wv);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc[i] = fmaf(xv[i], wv[i], acc[i]);
-        }
-    }
-    const int64_t ti = (int64_t)gt.row[g] * tab_ld + ch;
-    float sc[8], sh[8];
-    loadf8(scale + ti, sc);
-    loadf8(shift + ti, sh);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        acc[i] = acc[i] * sc[i] + sh[i];
-        if (act == DS_ACT_RELU) acc[i] = fmaxf(acc[i], 0.f);
-    }
-    *(uint4*)((bf16_t*)y.p + (int64_t)ys * y.sample_stride + (int64_t)pix * yld + ch) = pack8(acc);
-}
-
 constexpr int DW_PX_S2 = 2;   // output pixels per thread at stride 2 (4 at stride 1)
 
-// Same layer, PX consecutive output pixels of a row per thread: the 3 x (3 + 3 STRIDE) input window
-// and the 9 filter chunks are loaded once for 4 outputs, which cuts the load instructions per
+// PX consecutive output pixels of a row per thread: the 3 x (3 + (PX - 1) STRIDE) input window
+// and the 9 filter chunks are loaded once for PX outputs, which cuts the load instructions per
 // output from 18 to 6.75 (stride 1) / 9 (stride 2).
 // one-dimensional grid of ceil(Ho * ceil(Wo/PX) * C/8 / 256) tiles x (B rounded up to 8) slots, slot fastest
 template <int STRIDE, int PX>
@@ -658,11 +613,6 @@ __global__ __launch_bounds__(256) void conv_f32_kernel(const float* x, const flo
     y[yi] = val;
 }
 
-__global__ void compose_index_kernel(const int32_t* inner, const int32_t* outer, int32_t* out, int B) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < B) out[j] = inner[outer[j]];
-}
-
 __global__ void lookup_kernel(const int32_t* idx, const GroupTable gt, int which, int32_t* out, int B) {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= B) return;
@@ -670,20 +620,7 @@ __global__ void lookup_kernel(const int32_t* idx, const GroupTable gt, int which
     out[j] = which == 0 ? gt.k_in[g] : (which == 1 ? gt.k_out[g] : gt.row[g]);
 }
 
-__global__ void make_key_kernel(const int32_t* hi, const int32_t* lo, int mul, int32_t* key, int B) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < B) key[j] = hi[j] * mul + (lo ? lo[j] : 0);
-}
-
 }  // namespace
-
-int32_t ds_launch_make_key(const int32_t* hi, const int32_t* lo, int32_t mul, int32_t* key, int32_t B, hipStream_t s) {
-    if (B <= 0) return DS_OK;
-    ProfScope prof(DS_K_MISC, s);
-    hipLaunchKernelGGL(make_key_kernel, dim3((B + 255) / 256), dim3(256), 0, s, hi, lo, mul, key, B);
-    DS_CHECK_LAUNCH("make key");
-    return DS_OK;
-}
 
 int32_t ds_launch_expand_groups(const int32_t* offsets, int32_t T, int32_t* slot_group, hipStream_t s) {
     ProfScope prof(DS_K_MISC, s);
@@ -881,14 +818,6 @@ int32_t ds_launch_conv_f32_nchw(const float* x, const float* w, const float* sca
     hipLaunchKernelGGL(conv_f32_kernel, grid, dim3(256), 0, s, x, w, scale, shift, tab_ld, residual, y, slot_group,
                        perm, gt, C_I, C_O, H, W, Ho, Wo, K, stride, pad, act);
     DS_CHECK_LAUNCH("fp32 conv");
-    return DS_OK;
-}
-
-int32_t ds_launch_compose_index(const int32_t* inner, const int32_t* outer, int32_t* out, int32_t B, hipStream_t s) {
-    if (B <= 0) return DS_OK;
-    ProfScope prof(DS_K_MISC, s);
-    hipLaunchKernelGGL(compose_index_kernel, dim3((B + 255) / 256), dim3(256), 0, s, inner, outer, out, B);
-    DS_CHECK_LAUNCH("compose index");
     return DS_OK;
 }
 
