@@ -2,7 +2,7 @@
 // Eq. 10 with one channel per group) with split batch-norm (Eq. 14), LayerNorm over
 // the valid embedding slice, the unsliced stem convolution, max-pool, the
 // pool + classifier head with sliced input width, patch extraction, and the fp32
-// NCHW direct convolution used by the single-block configuration (Eq. 9).
+// NCHW direct convolution for the filters conv_f32.hip is not written for (Eq. 9).
 // All bf16 kernels move 8 channels (16 bytes) per lane and keep lanes of a
 // wavefront on consecutive channels of one pixel so that global accesses coalesce.
 #include "common.h"
