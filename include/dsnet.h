@@ -26,7 +26,8 @@
  *    strides and channel counts that are multiples of 8 (DS_EALIGN otherwise).
  *  - Infinities and NaN: samples never mix, and nothing stored beyond a slice
  *    takes part in a result.  Padding counts as zeros that are multiplied, so a
- *    weight that is not finite makes border outputs NaN.  ReLU gives 0 for NaN.
+ *    weight that is not finite makes border outputs NaN.  A layer's ReLU gives 0
+ *    for NaN; a gate's hidden units keep it, and a NaN score is never selected.
  *    The depthwise kernels for plain 3 x 3 filters and for dilated or wider-stepped
  *    ones multiply channels in pairs: there a pixel that is not finite in channel c
  *    also reaches channel c ^ 1 of the same outputs.
