@@ -120,12 +120,37 @@ __device__ __forceinline__ int4 ds_tile_record_of(const int32_t* offsets, int T,
     const int before = __builtin_amdgcn_readlane(upto - n, q);
     return make_int4(T - 1 - q, (mt - before) * bm, __builtin_amdgcn_readlane(o0, q), __builtin_amdgcn_readlane(rg, q));
 }
+// Kernel arguments that a launch needs ahead of its first load, in scalar registers from here on.  Left to itself the compiler
+// reads an argument in the basic block that uses it, so the head of a kernel with branches is a chain of a dozen dependent
+// scalar loads of cold cache lines; held together they are one round trip.
+template <typename T>
+__device__ __forceinline__ void ds_hold1(T& v) { asm volatile("" : "+s"(v)); }
+template <typename... T>
+__device__ __forceinline__ void ds_hold(T&... v) { (ds_hold1(v), ...); }
+// The group table by lanes: lane g holds group g's entries, requested together and ahead of the tile record, so that the
+// slice widths are at hand when the group is known instead of one more dependent read of the kernel arguments.
+struct GroupLanes {
+    int ki, ko, ro;
+    __device__ __forceinline__ explicit GroupLanes(const GroupTable& gt) {
+        const int g = (int)(threadIdx.x & 63);
+        static_assert(DS_MAX_GROUPS <= 64, "a lane per group");
+        ki = gt.k_in[g];
+        ko = gt.k_out[g];
+        ro = gt.row[g];
+    }
+    __device__ __forceinline__ int k_in(int g) const { return __builtin_amdgcn_readlane(ki, __builtin_amdgcn_readfirstlane(g)); }
+    __device__ __forceinline__ int k_out(int g) const { return __builtin_amdgcn_readlane(ko, __builtin_amdgcn_readfirstlane(g)); }
+    __device__ __forceinline__ int row(int g) const { return __builtin_amdgcn_readlane(ro, __builtin_amdgcn_readfirstlane(g)); }
+};
 // Record of 128-row tile mt: read from the list, or worked out where there is none (no offsets either: one group of B
 // samples in slot order)
 __device__ __forceinline__ int4 ds_tile_record(const GemmArgs& a, int mt) {
     if (a.mtiles) {
         const int4 me = a.mtiles[mt];            // in bounds even beyond the live count; checked next
-        return mt < *a.n_mtiles ? me : make_int4(-1, 0, 0, 0);
+        const int n = *a.n_mtiles;
+        int x = __builtin_amdgcn_readfirstlane(me.x);
+        ds_hold(x);                              // asked for beside the count, not behind it
+        return mt < n ? make_int4(x, me.y, me.z, me.w) : make_int4(-1, 0, 0, 0);
     }
     if (!a.offsets) return mt * DS_GEMM_BM < a.B * a.rows ? make_int4(0, mt * DS_GEMM_BM, 0, a.B * a.rows) : make_int4(-1, 0, 0, 0);
     return ds_tile_record_of(a.offsets, a.gt.T, a.rows, mt, DS_GEMM_BM);

@@ -7,6 +7,11 @@
 // 64-deep slab of its reduction, the KS partial tiles are added in LDS in wavefront order, and a wavefront keeps PD
 // slabs travelling in registers.  Its operand slabs go through an LDS region of its own (global loads cover whole
 // 128-byte lines, the matrix operands want one row per lane), so there is no workgroup barrier before the final sum.
+// Around that chain lie the round trips of the kernel's head and tail, and instructions: eight wavefronts of a compute unit
+// issue one each in eight clocks.  So all kernel arguments are read at once, with the group table beside the tile record, the
+// batch-norm rows and the residual are asked for behind the first operands, and a tap costs two instructions a row: a mask of
+// the filter rows and columns inside the map, the pixel of a tap in the load's scalar offset.  One image of DS-ResNet, 47
+// of these launches: 431 -> 385 us a pass.
 // Same tile list, row addressing, slices and epilogue as gemm_kernel; a list tile of 128 rows is walked in parts of
 // WM*32 rows and a part beyond the group's rows ends at once.
 // Column tiles are the fastest index of the launch: neighbouring workgroups land on different dies, so a die's L2 holds
@@ -23,7 +28,7 @@ __device__ __forceinline__ int key(int r) { return (r ^ (r >> 3)) & 7; }
 
 // NW wavefronts: KS shares of the reduction x NW / KS column tiles
 template <int WM, int WN, int NW, int KS, int PD, bool CONV, bool HASR>
-__global__ __launch_bounds__(64 * NW) void gemm_small_kernel(const GemmArgs a, const int ny, const int max_mtiles) {
+__global__ __launch_bounds__(64 * NW) void gemm_small_kernel(const GemmArgs a) {
     constexpr int BM = WM * 32, WBN = WN * 32, NC = NW / KS, BN = NC * WBN, BK = 64;
     constexpr int NSUB = DS_GEMM_BM / BM;
     constexpr int NA = BM / 8, NB = WBN / 8;                  // 16-byte loads of a lane per slab
@@ -32,94 +37,113 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(const GemmArgs a, c
     constexpr int STAGE_BYTES = BM * ST_LD * 4;
     constexpr int PER_WAVE = WAVE_BYTES > STAGE_BYTES ? WAVE_BYTES : STAGE_BYTES;
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    long long* rowC = (long long*)(smem + NW * PER_WAVE);     // [BM] output row, -1: no such row
-    long long* rowR = rowC + BM;
 
-    const int bid = (int)blockIdx.x;
-    const int y = bid % ny, mi = bid / ny;
+    int y = (int)blockIdx.x;
+    const int mi = (int)blockIdx.y;
     const int mt = mi / NSUB, sub = mi - mt * NSUB;
-    if (mt >= max_mtiles) return;
+    const GroupLanes lanes(a.gt);
+    const bf16_t *A = a.A, *Wt = a.Wt, *R = a.R;
+    void* C = a.C;
+    const float *scale = a.scale, *shift = a.shift;
+    const int32_t *a_index = a.a_index, *c_index = a.c_index;
+    int64_t a_ss = a.a_sample_stride, c_ss = a.c_sample_stride, r_ss = a.r_sample_stride, c_segs = a.c_seg_stride;
+    int a_ld = a.a_ld, c_ld = a.c_ld, r_ld = a.r_ld, c_row0 = a.c_row0, r_use = a.r_use_index;
+    int w_ld = (int)a.w_ld, w_tap = (int)a.w_tap_stride, w_seg = (int)a.w_seg_stride;      // (in reach of 32 bits: ds_launch_gemm_small)
+    int n_seg = a.n_seg, tab_ld = a.tab_ld, tab_seg = a.tab_seg_stride, rows = a.rows, act = a.act, out_f32 = a.out_f32;
+    int H = a.H, W = a.W, Wo = a.Wo, KH = a.K, KW = a.Kw, sy = a.stride, sx = a.stride_w, pad = a.pad;
     const int4 me = ds_tile_record(a, mt);
+    ds_hold(A, Wt, R, C, scale, shift, a_index, c_index, a_ss, c_ss, r_ss, c_segs, a_ld, c_ld, r_ld, c_row0, r_use, w_ld, w_tap,
+            w_seg, n_seg, tab_ld, tab_seg, rows, act, out_f32);
+    if constexpr (CONV) ds_hold(H, W, Wo, KH, KW, sy, sx, pad);
     if (me.x < 0) return;
     const int g = me.x, grow0 = me.y + sub * BM, slot0 = me.z, rows_g = me.w;
     if (grow0 >= rows_g) return;
-    const int k_in = a.gt.k_in[g], k_out = a.gt.k_out[g];
+    const int k_in = lanes.k_in(g), k_out = lanes.k_out(g);
     if (k_in <= 0 || k_out <= 0) return;
-    const int ntiles = (k_out + BN - 1) / BN;
-    const int seg = y / ntiles;
-    if (seg >= a.n_seg) return;
-    const int n0 = (y - seg * ntiles) * BN;
+    int seg = 0;
+    if (n_seg > 1) {
+        const int ntiles = (k_out + BN - 1) / BN;
+        seg = y / ntiles;
+        if (seg >= n_seg) return;
+        y -= seg * ntiles;
+    }
+    const int n0 = y * BN;
+    if (n0 >= k_out) return;
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int ks = wave % KS, wc = wave / KS;                 // share of the reduction, column tile
     const int nw0 = n0 + wc * WBN;
-    const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc((void*)a.A, 0, 0x7fffffff, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc((void*)a.Wt, 0, 0x7fffffff, 0x00020000);
-    const int a_ld = a.a_ld > 0 ? a.a_ld : k_in;
-    const int c_ld = a.c_ld > 0 ? a.c_ld : k_out;
-    const int r_ld = a.r_ld > 0 ? a.r_ld : k_out;
+    if (a_ld <= 0) a_ld = k_in;
+    if (c_ld <= 0) c_ld = k_out;
+    if (r_ld <= 0) r_ld = k_out;
+    if (KW <= 0) KW = KH;
+    if (sx <= 0) sx = sy;
+    // A convolution's pixel offsets count from the first pixel that a filter at the map's corner covers, so that none is negative;
+    // the descriptor starts there (what lies ahead of the map is never asked for).
+    const int corner = CONV ? (pad * W + pad) * a_ld : 0;
+    const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc((void*)(A - corner), 0, 0x7fffffff, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc((void*)Wt, 0, 0x7fffffff, 0x00020000);
 
     // ---- rows: lane r works out row r of the tile, the lanes that load it fetch the result from lane r
     uint32_t my_a = OOB;
-    int my_yx = 0;
+    int my_taps = 0;                                          // filter rows (low half) and columns (high half) inside the map
+    long long rc = -1, rr = 0;                                // output row (-1: no such row), residual row
     if (lane < BM) {
         const int m = grow0 + lane;
-        long long rc = -1, rr = 0;
         if (m < rows_g) {
-            const int sl = m / a.rows, p = m - sl * a.rows, slot = slot0 + sl;
-            const int sa = a.a_index ? a.a_index[slot] : slot;
-            const int cs = a.c_index ? a.c_index[slot] : slot;
+            const int sl = m / rows, p = m - sl * rows, slot = slot0 + sl;
+            const int sa = a_index ? a_index[slot] : slot;
+            const int cs = c_index ? c_index[slot] : slot;
+            int pix = p;
             if constexpr (CONV) {
-                const int oy = p / a.Wo, ox = p - oy * a.Wo;
-                const int iy = oy * a.stride - a.pad, ix = ox * (a.stride_w > 0 ? a.stride_w : a.stride) - a.pad;
-                my_yx = (iy << 16) | (ix & 0xffff);
+                const int oy = p / Wo, ox = p - oy * Wo;
+                const int iy = oy * sy, ix = ox * sx;         // counted from the corner
+                auto inside = [&](int i, int n, int k) {      // taps t < k with pad <= i + t < pad + n
+                    const int lo = pad - i > 0 ? pad - i : 0, hi = pad + n - i < k ? pad + n - i : k;
+                    return hi > lo ? (1 << hi) - (1 << lo) : 0;
+                };
+                my_taps = inside(iy, H, KH) | inside(ix, W, KW) << 16;
+                pix = iy * W + ix;
             }
-            my_a = (uint32_t)(((long long)sa * a.a_sample_stride + (CONV ? 0 : (long long)p * a_ld)) * 2);
-            const long long pc = p + a.c_row0;
-            rc = (long long)cs * a.c_sample_stride + pc * c_ld + (long long)seg * a.c_seg_stride;
-            rr = (long long)(a.r_use_index ? cs : 0) * a.r_sample_stride + pc * r_ld;
-        }
-        if (wave == 0) {
-            rowC[lane] = rc;
-            rowR[lane] = rr;
+            my_a = (uint32_t)(((long long)sa * a_ss + (long long)pix * a_ld) * 2);
+            const long long pc = p + c_row0;
+            rc = (long long)cs * c_ss + pc * c_ld + (long long)seg * c_segs;
+            rr = (long long)(r_use ? cs : 0) * r_ss + pc * r_ld;
         }
     }
     const int lrow = lane >> 3, lchunk = lane & 7, kc8 = lchunk * 8;
     uint32_t aoff[NA], woff[NB];
-    int ayx[CONV ? NA : 1];
+    int ataps[CONV ? NA : 1];
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
-        aoff[i] = (uint32_t)__shfl((int)my_a, lrow + 8 * i, 64);
-        if constexpr (CONV) ayx[i] = __shfl(my_yx, lrow + 8 * i, 64);
-        else if (aoff[i] != OOB) aoff[i] += kc8 * 2;
+        aoff[i] = (uint32_t)__shfl((int)my_a, lrow + 8 * i, 64) + kc8 * 2;      // (no row: still out of range)
+        if constexpr (CONV) ataps[i] = __shfl(my_taps, lrow + 8 * i, 64);
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         const int n = nw0 + lrow + 8 * i;
-        woff[i] = n < k_out ? (uint32_t)(((long long)seg * a.w_seg_stride + (long long)n * a.w_ld + kc8) * 2) : OOB;
+        woff[i] = n < k_out ? (uint32_t)(seg * w_seg + n * w_ld + kc8) * 2 : OOB;
     }
 
     const int kchunks = (k_in + BK - 1) / BK;
-    const int kw = a.Kw > 0 ? a.Kw : a.K;
-    const int nk = CONV ? a.K * kw * kchunks : kchunks;
+    const int nk = CONV ? KH * KW * kchunks : kchunks;
     uint4 ra[PD][NA], rb[PD][NB];
-    // slab being fetched next: tap and 64-channel chunk (this wavefront takes every KS-th slab)
-    int ltap = 0, lkc = ks;
+    // slab being fetched next: tap (row u, column v) and 64-channel chunk (this wavefront takes every KS-th slab)
+    int lkc = ks, lu = 0, lv = 0;
     auto fetch = [&](uint4 (&va)[NA], uint4 (&vb)[NB]) {
         if constexpr (CONV)
-            while (lkc >= kchunks) { lkc -= kchunks; ++ltap; }
+            while (lkc >= kchunks) {
+                lkc -= kchunks;
+                if (++lv == KW) lv = 0, ++lu;
+            }
         const bool kok = lkc * BK + kc8 < k_in;
-        const int u = CONV ? ltap / kw : 0, v = CONV ? ltap - u * kw : 0;
-        const int soff_a = lkc * BK * 2;
-        const int soff_w = (int)((ltap * a.w_tap_stride + lkc * BK) * 2);
+        const int soff_a = ((lu * W + lv) * a_ld + lkc * BK) * 2;
+        const int soff_w = ((lu * KW + lv) * w_tap + lkc * BK) * 2;
+        const int tap = 1 << lu | 0x10000 << lv;
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
-            uint32_t o = aoff[i];
-            if constexpr (CONV) {
-                const int iy = (ayx[i] >> 16) + u, ix = (int)(short)(ayx[i] & 0xffff) + v;
-                o = o != OOB && iy >= 0 && iy < a.H && ix >= 0 && ix < a.W ? o + (uint32_t)(((iy * a.W + ix) * a_ld + kc8) * 2) : OOB;
-            }
-            const auto t = __builtin_amdgcn_raw_buffer_load_b128(rsrc_a, (int)(kok ? o : OOB), soff_a, 0);
+            const bool ok = CONV ? kok && (ataps[CONV ? i : 0] & tap) == tap : kok;
+            const auto t = __builtin_amdgcn_raw_buffer_load_b128(rsrc_a, (int)(ok ? aoff[i] : OOB), soff_a, 0);
             va[i] = make_uint4(t[0], t[1], t[2], t[3]);
         }
 #pragma unroll
@@ -132,6 +156,32 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(const GemmArgs a, c
 #pragma unroll
     for (int st = 0; st < PD; ++st)
         if (ks + KS * st < nk) fetch(ra[st], rb[st]);
+
+    // What the epilogue adds is requested behind the first operands: a thread finishes 4 channels, the same for all of its
+    // rows.  Asked for after the final sum it was one more round trip to memory in a launch that is a chain of four.
+    constexpr int GPR = BN / 4, RSTEP = 64 * NW / GPR, NE = (BM + RSTEP - 1) / RSTEP;
+    const int er0 = tid / GPR, c4 = (tid - er0 * GPR) * 4, n = n0 + c4;
+    float vs[4] = {1.f, 1.f, 1.f, 1.f}, vh[4] = {0.f, 0.f, 0.f, 0.f};
+    long long coff[NE];
+    uint2 res[HASR ? NE : 1];
+    if (n < k_out) {
+        const long long ti = (long long)lanes.row(g) * tab_ld + (long long)seg * tab_seg + n;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (scale) vs[q] = scale[ti + q];
+            if (shift) vh[q] = shift[ti + q];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NE; ++i) {
+        const int r = er0 + i * RSTEP;                        // (lanes past the tile read some lane's row and drop it)
+        const long long c = __shfl(rc, r & 63, 64), ro = __shfl(rr, r & 63, 64);
+        coff[i] = r < BM && n < k_out ? c : -1;
+        if constexpr (HASR) {
+            res[i] = make_uint2(0, 0);
+            if (coff[i] >= 0) res[i] = *(const uint2*)(R + ro + n);
+        }
+    }
 
     f32x16_t acc[WM][WN];
 #pragma unroll
@@ -202,21 +252,11 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(const GemmArgs a, c
             for (int v = 0; v < 16; ++v)
                 st[(i * 32 + 8 * (v >> 2) + 4 * lhi + (v & 3)) * ST_LD + j * 32 + l32] = acc[i][j][v];
     __syncthreads();
-    constexpr int GPR = BN / 4;                               // groups of 4 channels per row
-    for (int e = tid; e < BM * GPR; e += 64 * NW) {
-        const int r = e / GPR, c4 = (e - r * GPR) * 4, ct = c4 / WBN, cl = c4 - ct * WBN;
-        const int n = n0 + c4;
-        const long long coff = rowC[r];
-        if (n >= k_out || coff < 0) continue;
-        const long long ti = (long long)a.gt.row[g] * a.tab_ld + (long long)seg * a.tab_seg_stride + n;
-        float vs[4] = {1.f, 1.f, 1.f, 1.f}, vh[4] = {0.f, 0.f, 0.f, 0.f};
+    const int ct = c4 / WBN, cl = c4 - ct * WBN;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (a.scale) vs[q] = a.scale[ti + q];
-            if (a.shift) vh[q] = a.shift[ti + q];
-        }
-        uint2 res = make_uint2(0, 0);
-        if constexpr (HASR) res = *(const uint2*)(a.R + rowR[r] + n);
+    for (int i = 0; i < NE; ++i) {
+        if (coff[i] < 0) continue;
+        const int r = er0 + i * RSTEP;
         float val[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int w = 0; w < KS; ++w) {
@@ -226,25 +266,25 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(const GemmArgs a, c
 #pragma unroll
         for (int q = 0; q < 4; ++q) val[q] = val[q] * vs[q] + vh[q];
         if constexpr (HASR) {
-            val[0] += __uint_as_float(res.x << 16);
-            val[1] += __uint_as_float(res.x & 0xffff0000u);
-            val[2] += __uint_as_float(res.y << 16);
-            val[3] += __uint_as_float(res.y & 0xffff0000u);
+            val[0] += __uint_as_float(res[i].x << 16);
+            val[1] += __uint_as_float(res[i].x & 0xffff0000u);
+            val[2] += __uint_as_float(res[i].y << 16);
+            val[3] += __uint_as_float(res[i].y & 0xffff0000u);
         }
-        if (a.act == DS_ACT_RELU) {
+        if (act == DS_ACT_RELU) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) val[q] = fmaxf(val[q], 0.f);
-        } else if (a.act == DS_ACT_GELU) {
+        } else if (act == DS_ACT_GELU) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) val[q] = gelu_erf(val[q]);
         }
-        if (a.out_f32) {
-            *(float4*)((float*)a.C + coff + n) = make_float4(val[0], val[1], val[2], val[3]);
+        if (out_f32) {
+            *(float4*)((float*)C + coff[i] + n) = make_float4(val[0], val[1], val[2], val[3]);
         } else {
             uint2 q;
             q.x = f2bf2(val[0], val[1]);
             q.y = f2bf2(val[2], val[3]);
-            *(uint2*)((bf16_t*)a.C + coff + n) = q;
+            *(uint2*)((bf16_t*)C + coff[i] + n) = q;
         }
     }
 }
@@ -253,13 +293,13 @@ template <int WM, int WN, int NW, int KS, int PD, bool CONV, bool HASR>
 int32_t launch(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
     constexpr int BM = WM * 32, WBN = WN * 32, BN = (NW / KS) * WBN;
     constexpr int W1 = (BM + WBN) * 128, W2 = BM * (WBN + 4) * 4;
-    constexpr int SMEM = NW * (W1 > W2 ? W1 : W2) + BM * 16;
+    constexpr int SMEM = NW * (W1 > W2 ? W1 : W2);
     auto kern = gemm_small_kernel<WM, WN, NW, KS, PD, CONV, HASR>;
     const int32_t rc = ds_reserve_lds((const void*)kern, SMEM, "small sliced gemm");
     if (rc) return rc;
     const int ny = a.n_seg * ((max_kout + BN - 1) / BN);
     ProfScope prof(DS_K_SMALL, s);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(max_mtiles * (DS_GEMM_BM / BM) * ny)), dim3(64 * NW), SMEM, s, a, ny, max_mtiles);
+    hipLaunchKernelGGL(kern, dim3((unsigned)ny, (unsigned)(max_mtiles * (DS_GEMM_BM / BM))), dim3(64 * NW), SMEM, s, a);
     DS_CHECK_LAUNCH("small sliced gemm");
     return DS_OK;
 }
@@ -282,7 +322,8 @@ int32_t launch(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStrea
 //   beyond      the 128-row kernels have enough workgroups and read less per product -- except the strided KxK layers
 //               (no staged patch for them), which stay here up to 1700 tiles (stage 4, 33 samples 48.0 -> 23.1)
 int32_t ds_launch_gemm_small(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
-    if (max_mtiles <= 0 || max_kout <= 0 || a.B <= 0 || a.H > 32767 || a.W > 32767) return DS_EUNSUPPORTED;
+    if (max_mtiles <= 0 || max_kout <= 0 || a.B <= 0) return DS_EUNSUPPORTED;
+    if (a.K > 15 || a.Kw > 15) return DS_EUNSUPPORTED;        // tap masks of 16 bits
     const bool conv = a.K > 1 || a.stride > 1 || a.pad > 0;
     const int taps = a.K * (a.Kw > 0 ? a.Kw : a.K);
     int kmax = 0;
@@ -294,7 +335,8 @@ int32_t ds_launch_gemm_small(const GemmArgs& a, int32_t max_mtiles, int32_t max_
     if (t > 1700 || (t > 1000 && !a.ordered && !(strided && nk >= 24))) return DS_EUNSUPPORTED;
     // 32-bit byte offsets inside the kernel
     const long long slots = (long long)max_mtiles * DS_GEMM_BM / (a.rows > 0 ? a.rows : 1) + 1;
-    if (slots * a.a_sample_stride * 2 >= 0x7fffffffLL) return DS_EUNSUPPORTED;
+    const long long corner = (long long)a.pad * (a.W + 1) * (a.a_ld > kmax ? a.a_ld : kmax);
+    if ((slots * a.a_sample_stride + corner) * 2 >= 0x7fffffffLL) return DS_EUNSUPPORTED;
     if (((long long)a.n_seg * a.w_seg_stride + (long long)max_kout * a.w_ld + taps * a.w_tap_stride + kmax) * 2 >= 0x7fffffffLL)
         return DS_EUNSUPPORTED;
 #define DS_SMALL(...)                                                                       \

@@ -88,6 +88,15 @@ def test_sliced_conv_bf16_tiles(gpu_lib, B, K, stride, pad, H, W, c_in, c_out, r
     _conv_case(gpu_lib, B, K, stride, pad, H, W, c_in, c_out, res, False)
 
 
+# few samples, bf16: tap masks of the longest filters that have them and of the first that do not, padding beyond the filter,
+# maps smaller than it
+@pytest.mark.parametrize("B,K,stride,pad,H,W,c_in,c_out,res", [
+    (2, 15, 1, 7, 9, 5, (8, 16), (24, 8), False), (1, 16, 1, 8, 9, 6, (16, 8), (8, 8), False), (3, 5, 3, 6, 4, 7, (72, 8), (40, 16), True),
+    (2, 2, 2, 0, 6, 5, (64, 136), (8, 48), False), (1, 7, 2, 3, 1, 1, (128, 64), (64, 64), True), (2, 4, 1, 1, 3, 30, (24, 40), (72, 64), False)])
+def test_sliced_conv_bf16_taps(gpu_lib, B, K, stride, pad, H, W, c_in, c_out, res):
+    _conv_case(gpu_lib, B, K, stride, pad, H, W, c_in, c_out, res, False)
+
+
 # the tile records worked out from the offsets: groups without samples, one group, as many groups as lanes
 @pytest.mark.parametrize("B,T,rows", [(1, 1, 1), (3, 64, 130), (70, 64, 33), (64, 5, 197), (300, 7, 128)])
 def test_sliced_linear_tile_records(gpu_lib, B, T, rows):
