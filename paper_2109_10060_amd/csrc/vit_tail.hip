@@ -13,8 +13,9 @@
 // operand as one contiguous kilobyte straight into registers, D of them in flight, and LDS serves the activations alone.
 // Each of the NW = 12 (13 above 384 channels) wavefronts owns one 32-column block of the block's width and of every
 // HC = 32 NW columns of the hidden layer; R row blocks share every weight operand.
-// DS-ViT, kernel time per block (profiles/layers_vit_*): 256 images 158 us (projection 29, LayerNorm 12, fc1 64, fc2 54) -> 124
-// to 132 us; 64 images 66 -> 48 us; 16 images 41 -> 25 us.
+// Around the products a workgroup has nothing beside it on its compute unit, so what it waits for is kept off its path: the
+// residual rows wait in the hidden tile, which is free until the MLP, LayerNorm weights in LDS, biases in registers.  DS-ViT, us
+// a pass: 16 images 711 -> 700, 64 images 1078 -> 1070, 256 images (64 rows a workgroup in place of 96 as well) 2622 -> 2570.
 //
 // Sums run in the order of gemm_kernel's and layernorm16_kernel's, so the results are the same bits.
 #include "gelu.h"
@@ -26,17 +27,21 @@ namespace {
 template <int NW, int R, int D>
 struct TailTile {
     static constexpr int PA = tile_pitch(VIT_K_MAX, D), PH = tile_pitch(32 * NW, D);
-    static constexpr int SMEM = (32 * R * (PA + PH) + 8) * 2;
+    static constexpr int NORM = 32 * R * (PA + PH) + 8;     // LayerNorm weights: gamma, then beta
+    static constexpr int SMEM = NORM * 2 + 2 * VIT_K_MAX * 4;
+    static_assert(SMEM <= 160 * 1024, "LDS of a compute unit");
 };
 
 // NW wavefronts (one column block of 32 each), 32 R rows, D operands of a wavefront in flight
 template <int NW, int R, int D>
 __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const VitTailArgs a) {
     using Tile = TailTile<NW, R, D>;
+    constexpr bool CST = NW <= 12 || R == 1;             // biases travel during the products (13 wavefronts: no registers for them)
     constexpr int BM = 32 * R, HC = 32 * NW, PA = Tile::PA, PH = Tile::PH, RP = 4 * NW, NI = (BM + RP - 1) / RP;   // RP: rows of a row phase
     extern __shared__ __attribute__((aligned(16))) char smem[];
     bf16_t* As = (bf16_t*)smem;                         // [BM][PA]
     bf16_t* Hs = As + BM * PA;                          // [BM][PH]
+    float* gs = (float*)(As + Tile::NORM);              // [2][VIT_K_MAX]
 
     const int4 me = ds_tile_record_of(a.offsets, a.gt.T, a.rows, (int)blockIdx.x, BM);
     if (me.x < 0) return;
@@ -48,37 +53,55 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     const int l16 = tid & 15, prow = tid >> 4;          // row phases: 16 lanes a row, RP rows at a time
     const bool con = w * 32 < de;                        // this wavefront has a column block
 
-    // ---- rows of this thread's 16-lane group: attention output to LDS, residual rows to registers ----------------------
+
+    // ---- rows of this thread's 16-lane group: attention output and residual rows to the two tiles ---------------------------
     int64_t xoff[NI];
     bool live[NI];
-    uint4 xr[NI][4];
+    // rows of x, the residual of both sums, in a tile of LDS
+    auto x_rows = [&](uint4 (&q)[NI][4]) {
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const bool in = BM % RP == 0 || prow + RP * i < BM;
-        const int m = grow0 + prow + RP * i;
-        live[i] = in && m < rows_g;
-        const int mm = live[i] ? m : grow0;
-        const int sl = mm / a.rows, p = mm - sl * a.rows, slot = slot0 + sl;
-        xoff[i] = (int64_t)slot * a.x_ss + (int64_t)p * de;
-        const bf16_t* orow = a.o + (int64_t)slot * a.o_ss + (int64_t)p * a.o_ld;
-        uint4 q[4];
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int ch = (k * 16 + l16) * 8;
-            q[k] = make_uint4(0, 0, 0, 0);
-            if (ch < kin) q[k] = *(const uint4*)(orow + ch);
+            for (int k = 0; k < 4; ++k) {
+                const int ch = (k * 16 + l16) * 8;
+                q[i][k] = make_uint4(0, 0, 0, 0);
+                if (ch < de && live[i]) q[i][k] = *(const uint4*)(a.x + xoff[i] + ch);
+            }
+    };
+    auto to_tile = [&](const uint4 (&q)[NI][4], bf16_t* tile, int pitch, int width) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int ch = (k * 16 + l16) * 8;
+                if (ch < width && (BM % RP == 0 || prow + RP * i < BM)) *(uint4*)(tile + (prow + RP * i) * pitch + ch) = q[i][k];
+            }
+    };
+    {
+        uint4 q[NI][4], xr[NI][4];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const bool in = BM % RP == 0 || prow + RP * i < BM;
+            const int m = grow0 + prow + RP * i;
+            live[i] = in && m < rows_g;
+            const int mm = live[i] ? m : grow0;
+            const int sl = mm / a.rows, p = mm - sl * a.rows, slot = slot0 + sl;
+            xoff[i] = (int64_t)slot * a.x_ss + (int64_t)p * de;
+            const bf16_t* orow = a.o + (int64_t)slot * a.o_ss + (int64_t)p * a.o_ld;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int ch = (k * 16 + l16) * 8;
+                q[i][k] = make_uint4(0, 0, 0, 0);
+                if (ch < kin) q[i][k] = *(const uint4*)(orow + ch);
+            }
         }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int ch = (k * 16 + l16) * 8;
-            if (in && ch < PA) *(uint4*)(As + (prow + RP * i) * PA + ch) = q[k];   // zeros beyond the slice
+        x_rows(xr);
+        for (int i = tid; i < de; i += 64 * NW) {
+            gs[i] = a.g2[i];
+            gs[VIT_K_MAX + i] = a.be2[i];
         }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int ch = (k * 16 + l16) * 8;
-            xr[i][k] = make_uint4(0, 0, 0, 0);
-            if (ch < de) xr[i][k] = *(const uint4*)(a.x + xoff[i] + ch);
-        }
+        to_tile(q, As, PA, PA);                          // zeros beyond the slice
+        to_tile(xr, Hs, PH, de);
     }
 
     // ---- acc2[r] += W[column block w] . act^T over K channels, 16 a step -----------------------------------------------------
@@ -117,17 +140,26 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
             }
         }
     };
-    // tile (in LDS, bf16) = tile + acc2 + bias on the elements this lane accumulated: 4 channels of one row at a time
-    auto add_columns = [&](const float* bias) {
+    // this lane's columns: 4 channels of a row at a time
+    auto constants = [&](float4 (&h)[4], const float* v, int c0, int n) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int ch = c0 + 8 * q + 4 * lhi;         // (4 channels are inside a slice or outside it)
+            h[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (ch < n) h[q] = *(const float4*)(v + ch);
+        }
+    };
+    // tile (in LDS, bf16) = tile + acc2 + bias on the elements this lane accumulated
+    auto add_columns = [&](const float4 (&cst)[4], const float* bias, bf16_t* tile, int pitch) {
         if (!con) return;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int ch = w * 32 + 8 * q + 4 * lhi;
             if (ch >= de) continue;
-            const float4 h = *(const float4*)(bias + ch);
+            const float4 h = CST ? cst[q] : *(const float4*)(bias + ch);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                uint2* p = (uint2*)(As + (r * 32 + l32) * PA + ch);
+                uint2* p = (uint2*)(tile + (r * 32 + l32) * pitch + ch);
                 const uint2 res = *p;
                 const f32x16_t& t = acc2[r];
                 float v0 = t[4 * q] + h.x, v1 = t[4 * q + 1] + h.y, v2 = t[4 * q + 2] + h.z, v3 = t[4 * q + 3] + h.w;
@@ -139,15 +171,6 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
             }
         }
     };
-    auto rows_to_lds = [&]() {
-#pragma unroll
-        for (int i = 0; i < NI; ++i)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int ch = (k * 16 + l16) * 8;
-                if (ch < de && (BM % RP == 0 || prow + RP * i < BM)) *(uint4*)(As + (prow + RP * i) * PA + ch) = xr[i][k];
-            }
-    };
 
     // ---- projection + residual ------------------------------------------------------------------------------------------
     // the columns behind the hidden tile's own, which the extra steps of a full width multiply
@@ -157,12 +180,11 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     clear2();
     const __amdgpu_buffer_rsrc_t rp = weight_row(a.wp, w * a.kbp, kin);
     if (con) start(ring, rp);
+    float4 cst[4];
+    if (CST) constants(cst, a.bp, w * 32, de);
     __syncthreads();
     if (con) walk(acc2, ring, rp, kin, As, PA);
-    __syncthreads();
-    rows_to_lds();
-    __syncthreads();
-    add_columns(a.bp);
+    add_columns(cst, a.bp, Hs, PH);                            // x waits in the hidden tile
     __syncthreads();
     // ---- x to memory, LN2 in place ---------------------------------------------------------------------------------------
 #pragma unroll
@@ -170,17 +192,18 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
         if (BM % RP != 0 && prow + RP * i >= BM) continue;     // whole 16-lane groups
         float v[4][8];
         uint4 o[4];
+        const bf16_t* sum = Hs + (prow + RP * i) * PH;
         bf16_t* row = As + (prow + RP * i) * PA;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int ch = (k * 16 + l16) * 8;
             if (ch < de) {
-                const uint4 q = *(const uint4*)(row + ch);
+                const uint4 q = *(const uint4*)(sum + ch);
                 if (live[i]) *(uint4*)(a.x + xoff[i] + ch) = q;
                 unpack8(q, v[k]);
             }
         }
-        row_norm(v, de, l16, a.eps, a.g2, a.be2, o);
+        row_norm(v, de, l16, a.eps, gs, gs + VIT_K_MAX, o);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int ch = (k * 16 + l16) * 8;
@@ -196,7 +219,7 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     if (w * 32 < hid) start(ring, weight_row(a.w1, w * a.kb1, de));
     for (int hc = 0; hc < nchunk; ++hc) {
         const int hb = hc * NW + w;                      // 32-column block of the hidden layer
-        const bool hon = hb * 32 < hid;
+        const bool hon = hb * 32 < hid, last = hc + 1 == nchunk;
         const int K2 = min(HC, hid - hc * HC);
         const __amdgpu_buffer_rsrc_t r1 = weight_row(a.w1, hb * a.kb1, de), r2 = weight_row(a.w2, w * a.kb2 + hc * 2 * NW, K2);
         f32x16_t acc1[R];
@@ -204,52 +227,41 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
         for (int r = 0; r < R; ++r)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc1[r][v] = 0.f;
+        if (CST) constants(cst, a.b1, hb * 32, hid);
         if (hon) walk(acc1, ring, r1, de, As, PA);
         if (con) start(ring, r2);                        // under way during the GELU and the barriers
         uint2 ho[4][R];
-        auto gelu = [&](auto put) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int ch = hb * 32 + 8 * q + 4 * lhi;    // (4 channels are inside the hidden slice or outside it)
-                const bool ok = ch < hid;
-                float4 h = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (ok) h = *(const float4*)(a.b1 + ch);
+        for (int q = 0; q < 4; ++q) {
+            const int ch = hb * 32 + 8 * q + 4 * lhi;
+            float4 h = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (CST) h = cst[q];
+            else if (ch < hid) h = *(const float4*)(a.b1 + ch);
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    uint2 o = make_uint2(0, 0);
-                    if (ok)
-                        o = gelu_bf16x4(acc1[r][4 * q] + h.x, acc1[r][4 * q + 1] + h.y, acc1[r][4 * q + 2] + h.z, acc1[r][4 * q + 3] + h.w);
-                    put(q, r, o);
-                }
+            for (int r = 0; r < R; ++r) {
+                ho[q][r] = make_uint2(0, 0);
+                if (ch < hid)
+                    ho[q][r] = gelu_bf16x4(acc1[r][4 * q] + h.x, acc1[r][4 * q + 1] + h.y, acc1[r][4 * q + 2] + h.z, acc1[r][4 * q + 3] + h.w);
             }
-        };
-        auto write = [&](int q, int r, uint2 o) { *(uint2*)(Hs + (r * 32 + l32) * PH + w * 32 + 8 * q + 4 * lhi) = o; };
-        if constexpr (R < 3) gelu([&](int q, int r, uint2 o) { ho[q][r] = o; });
+        }
         __syncthreads();                                 // the previous columns have been read
-        if constexpr (R < 3) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
+        for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int r = 0; r < R; ++r) write(q, r, ho[q][r]);
-        } else {
-            gelu(write);
+            for (int r = 0; r < R; ++r) *(uint2*)(Hs + (r * 32 + l32) * PH + w * 32 + 8 * q + 4 * lhi) = ho[q][r];
+        if (last) {
+            // the residual rows of the last sum (this thread wrote them itself after the projection): every wavefront is past its
+            // last read of the activation tile
+            uint4 xr[NI][4];
+            x_rows(xr);
+            to_tile(xr, As, PA, de);
+            if (CST) constants(cst, a.b2, w * 32, de);
         }
         __syncthreads();
         if (con) walk(acc2, ring, r2, K2, Hs, PH);
         if ((hb + NW) * 32 < hid) start(ring, weight_row(a.w1, (hb + NW) * a.kb1, de));
     }
-    // the residual rows of the last sum: this thread wrote them itself after the projection
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int ch = (k * 16 + l16) * 8;
-            xr[i][k] = make_uint4(0, 0, 0, 0);
-            if (ch < de && live[i]) xr[i][k] = *(const uint4*)(a.x + xoff[i] + ch);
-        }
-    rows_to_lds();                                       // every wavefront is past its last read of the activation tile
-    __syncthreads();
-    add_columns(a.b2);
+    add_columns(cst, a.b2, As, PA);
     __syncthreads();
     // ---- x to memory ------------------------------------------------------------------------------------------------------
 #pragma unroll
@@ -267,7 +279,6 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
 template <int NW, int R, int D>
 int32_t launch(const VitTailArgs& a, int64_t tiles, hipStream_t s) {
     constexpr int SMEM = TailTile<NW, R, D>::SMEM;
-    static_assert(SMEM <= 160 * 1024, "LDS of a compute unit");
     const int32_t rc = ds_reserve_lds((const void*)vit_tail_kernel<NW, R, D>, SMEM, "transformer block tail");
     if (rc) return rc;
     ProfScope prof(DS_K_TAIL, s);
@@ -278,11 +289,11 @@ int32_t launch(const VitTailArgs& a, int64_t tiles, hipStream_t s) {
 
 }  // namespace
 
-// Rows per workgroup.  A workgroup streams all weights of the block whatever its rows (2.7 MB at full width), so more rows
-// each are better -- as long as there is a workgroup for every compute unit.  Measured per launch on DS-ViT
-// (profiles/dispatch_choices.txt): 16 images 25 / 31 / 37 us with 32 / 64 / 96 rows, 64 images 49 / 48 / 61, 256 images
-// 155 / 112 / 125.  The line at 448 tiles of 96 rows dates from weights addressed through one descriptor (136 against 131 us
-// there); with a descriptor per row block 64 rows are the better choice at 256 images too (2669 against 2733 us a pass).
+// Rows per workgroup.  A workgroup streams all weights of the block whatever its rows (2.7 MB at full width), and when all compute
+// units do so at once the L2s give each about 30 bytes a clock, half of what 64 rows could use; so more rows each are better --
+// as long as there is a workgroup for every compute unit and the last ones end together.  256 images: 560 tiles of 96 rows take
+// 2710 us a pass, 816 tiles of 64 rows 2600; two workgroups a compute unit (four wavefronts of three column blocks each, 64
+// rows) 2780: eight wavefronts do not cover the weights' latency.
 int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {
     int dmax = 0;
     for (int t = 0; t < a.gt.T; ++t) {
@@ -297,6 +308,5 @@ int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {
     const bool two = tiles(64) >= 224;
     if (dmax > 384)                                      // 13 column blocks: 128 registers per lane, at most 64 rows
         return two ? launch<13, 2, 4>(a, tiles(64), s) : launch<13, 1, 4>(a, tiles(32), s);
-    if (tiles(96) >= 448) return launch<12, 3, 4>(a, tiles(96), s);
     return two ? launch<12, 2, 4>(a, tiles(64), s) : launch<12, 1, 8>(a, tiles(32), s);
 }
