@@ -260,7 +260,8 @@ int32_t ds_sliced_mhsa(const void* x, int32_t B, int32_t N, int32_t D_e, const v
  *           optionally kfull[n_blocks], ksize[T][n_blocks] (DS-MBNet++, Eq. 11): block i stores a
  *           kfull[i] x kfull[i] depthwise filter (odd, at most 7) and route t uses its centred
  *           ksize[t][i] x ksize[t][i] block at padding (ksize - 1) / 2, so the resolution does not
- *           depend on the route; blocks before the gate use row 0
+ *           depend on the route; blocks before the gate use row 0;
+ *           or optionally one flags word: bit 0 = the tiled pw.w below are there for every block
  *   params: stem.w bf16 [3*3*3][stem_out] (tap-major, input channel, then filters), stem.scale, stem.shift,
  *           per block: dw.w bf16 [k][k][C_in] (k = 3, or kfull[i]), dw.scale, dw.shift fp32 [Tb][C_in], pw.w bf16 [C_out][C_in],
  *           pw.scale, pw.shift fp32 [Tb][C_out] (Tb = 1 before the gate, T after),
@@ -268,8 +269,8 @@ int32_t ds_sliced_mhsa(const void* x, int32_t B, int32_t N, int32_t D_e, const v
  *           fc.w bf16 [num_classes][C_last], fc.b fp32,
  *           optionally, per block: pw.w once more as [ceil(C_out/32)][ceil(C_in/32) | 1] pairs of 1 KiB tiles (bf16, [quarter
  *             of the 32 channels][16 rows][8 channels], the first tile of a pair with rows 0..3 of every eight, the second with
- *             4..7, zeros beyond the matrix); the blocks in front of the gate then run as one kernel each.  The entries of
- *             the blocks behind it are not read (any aligned pointer, such as pw.w itself). */
+ *             4..7, zeros beyond the matrix); the blocks in front of the gate then run as one kernel each, with the flag those
+ *             behind it too.  Without the flag the entries behind the gate are not read (any aligned pointer, such as pw.w itself). */
 #define DS_ARCH_MBNET  1
 /* DS_ARCH_RESNET: bottleneck ResNet, a gate in the first block of each of 4 stages (DS-ResNet).
  *   ints:   image, stem_out, T, num_classes, widths[4], blocks[4], gate_hidden[4], mid[4][T], out[4][T],

@@ -68,6 +68,11 @@ def _separable(r, ci, co, s, k, kfull, tiled):
     return k == 3 and kfull == 3 and ci <= 128 and co <= 128 and r % (4 if s == 1 else 2) == 0
 
 
+def _sliced_separable(r, ci):
+    """A block behind the gate (3x3 filters) that runs as one kernel: output size, stored channels."""
+    return r <= 32 and -(-ci // 64) * 64 <= 2048
+
+
 def _gemm(cost, kind, rows_in, rows_out, kk, k_in, k_out, residual=False, out_bytes=2, chained=False, name=""):
     """k_in, k_out: per-sample arrays of valid widths.  chained: the layer runs inside the launch that
     produced its input rows, so it adds flops, its output and its weights, but no input read and no launch."""
@@ -95,12 +100,14 @@ def mbnet_cost(arch, routes) -> Cost:
         kk = arch["ksize"][routes, i].astype(np.float64) ** 2 if "ksize" in arch else 9.0
         cif, cof = int(_ci), int(_co)
         k = int(arch["ksize"][0, i]) if "ksize" in arch else 3
-        if i < arch["gate_after"] and _separable(r, cif, cof, s, k, arch["kfull"][i] if "ksize" in arch else 3, True):
-            # an unsliced block the library runs as one kernel (depthwise map kept in LDS): counted as one launch
+        if (_separable(r, cif, cof, s, k, arch["kfull"][i] if "ksize" in arch else 3, True) if i < arch["gate_after"]
+                else "ksize" not in arch and _sliced_separable(r, cif)):
+            # a block the library runs as one kernel (depthwise map kept in LDS): counted as one launch
             # of the depthwise class that reads the block's input and writes the pointwise output
+            span = lambda v: f"{int(v.min())}..{int(v.max())}" if v.min() < v.max() else f"{int(v.max())}"  # noqa: E731
             c.add("dwconv", 2.0 * r * r * (kk * ci).sum() + 2.0 * r * r * np.sum(ci * co),
-                  2.0 * rin * rin * ci.sum() + 2.0 * r * r * co.sum() + 2.0 * cif * cof, name=f"ds{i} dw+pw fused",
-                  shape=f"{rin}x{rin}x{cif} -> {r}x{r}x{cof}")
+                  2.0 * rin * rin * ci.sum() + 2.0 * r * r * co.sum() + 2.0 * ci.max() * co.max(), name=f"ds{i} dw+pw fused",
+                  shape=f"{rin}x{rin}x{span(ci)} -> {r}x{r}x{span(co)}")
         else:
             c.add("dwconv", 2.0 * r * r * (kk * ci).sum(), 2.0 * (rin * rin + r * r) * ci.sum(), name=f"ds{i} dw",
                   shape=f"{rin}x{rin} s{s} c {int(ci.min())}..{int(ci.max())}")

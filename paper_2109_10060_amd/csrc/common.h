@@ -255,6 +255,12 @@ int32_t ds_launch_dwband(ActView x, ActView y, const bf16_t* w, int32_t KS, cons
 int32_t ds_launch_bandpw(const bf16_t* x, int32_t B, int32_t H, int32_t W, int32_t C, const bf16_t* wd, int32_t KS, int32_t taps,
                          int32_t stride, const float* sd, const float* hd, const bf16_t* wp, int32_t F, const float* sp,
                          const float* hp, bf16_t* y, hipStream_t s);
+// depthwise (3 x 3, padding 1, stride 1 or 2) and pointwise layer of a block behind the gate with their split batch-norms and
+// ReLUs as one kernel; gt: k_in, k_out, table row of a route; wp in operand tiles, y [slot][pixel][k_out].  DS_EUNSUPPORTED
+// for maps wider than a tile and slices beyond what LDS holds
+int32_t ds_launch_sepconv(ActView x, bf16_t* y, int64_t y_ss, const bf16_t* wd, const float* sd, const float* hd, int32_t C,
+                          const bf16_t* wp, const float* sp, const float* hp, int32_t F, const int32_t* slot_group,
+                          const GroupTable& gt, int32_t B, int32_t H, int32_t W, int32_t stride, hipStream_t s);
 int32_t ds_launch_layernorm(ActView x, ActView y, const float* gamma, const float* beta, float eps,
                             const int32_t* slot_group, const GroupTable& gt, int32_t B, int32_t rows,
                             int32_t row0, int32_t n_rows, hipStream_t s);

@@ -141,6 +141,7 @@ int32_t conv_gemm(const bf16_t* A, const int32_t* a_index, int64_t a_sstride, in
 //  ints:   image, stem_out, n_blocks, gate_after, gate_hidden, T, num_classes,
 //          n_blocks x (C_in, C_out, stride), cin[T][n_blocks], cout[T][n_blocks]
 //          [, kfull[n_blocks], ksize[T][n_blocks]]   (DS-MBNet++: stored depthwise filter size, route's kernel size)
+//          or [, flags]   (bit 0: the tiled filters behind the parameters are those of every block)
 //  params: stem.w [27][stem_out] bf16, stem.scale, stem.shift,
 //          per block: dw.w [k][k][C_in] bf16 (k = 3, or kfull of the block), dw.scale, dw.shift [Tb][C_in], pw.w [C_out][C_in] bf16,
 //                     pw.scale, pw.shift [Tb][C_out]   (Tb = 1 before the gate, T after),
@@ -150,7 +151,7 @@ struct MbDesc {
     int image, stem_out, nb, gate_after, gate_hidden, T, classes;
     const int32_t *blk, *cin, *cout;
     const int32_t *kfull, *ksize;   // null unless the depthwise filters are spatially sliced
-    bool tiled;                     // the pointwise filters are there in operand order too
+    int tiled;                      // the pointwise filters are there in operand order too: 1 in front of the gate, 2 of every block
 };
 
 bool parse_mb(const ds_net* net, MbDesc* d) {
@@ -160,14 +161,14 @@ bool parse_mb(const ds_net* net, MbDesc* d) {
     d->classes = v[6];
     if (d->nb < 1 || d->nb > 64 || d->T < 1 || d->T > DS_MAX_GROUPS) return false;
     const int plain = 7 + 3 * d->nb + 2 * d->T * d->nb;
-    if (net->n_ints != plain && net->n_ints != plain + d->nb + d->T * d->nb) return false;
-    d->tiled = net->n_params == 3 + 7 * d->nb + 6;
+    if (net->n_ints != plain && net->n_ints != plain + 1 && net->n_ints != plain + d->nb + d->T * d->nb) return false;
+    d->tiled = net->n_params == 3 + 7 * d->nb + 6 ? (net->n_ints == plain + 1 && (v[plain] & 1) ? 2 : 1) : 0;
     if (!d->tiled && net->n_params != 3 + 6 * d->nb + 6) return false;
     d->blk = v + 7;
     d->cin = d->blk + 3 * d->nb;
     d->cout = d->cin + d->T * d->nb;
     d->kfull = d->ksize = nullptr;
-    if (net->n_ints != plain) {
+    if (net->n_ints > plain + 1) {
         d->kfull = d->cout + d->T * d->nb;
         d->ksize = d->kfull + d->nb;
     }
@@ -287,6 +288,19 @@ int32_t forward_mb(const ds_net* net, const MbDesc& d, const bf16_t* images, int
             if (rc == DS_OK) {
                 bf16_t* t = cur; cur = oth; oth = t;
                 RC(tap_block(taps, i, cur, (int64_t)r * r * co, co, nullptr, nullptr, gpw, B, r * r, co, s));
+                continue;
+            }
+            if (rc != DS_EUNSUPPORTED) return rc;
+        }
+        if (phase && d.tiled == 2 && !d.kfull) {
+            // a block behind the gate: both layers in one kernel; the first one reads the unsliced map through the permutation
+            const ActView xv = {cur, i == d.gate_after ? p.perm : nullptr, (int64_t)rin * rin * ci, i == d.gate_after ? ci : 0};
+            const int32_t rc = ds_launch_sepconv(xv, oth, (int64_t)r * r * co, (const bf16_t*)Q[0], (const float*)Q[1], (const float*)Q[2], ci,
+                                                 (const bf16_t*)P[3 + 6 * d.nb + 6 + i], (const float*)Q[4],
+                                                 (const float*)Q[5], co, p.slot_group, gpw, B, rin, rin, st, s);
+            if (rc == DS_OK) {
+                bf16_t* t = cur; cur = oth; oth = t;
+                RC(tap_block(taps, i, cur, (int64_t)r * r * co, 0, p.perm, p.slot_group, gpw, B, r * r, co, s));
                 continue;
             }
             if (rc != DS_EUNSUPPORTED) return rc;

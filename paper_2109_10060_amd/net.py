@@ -94,6 +94,8 @@ def build_mbnet(arch: dict, p: dict, device="cuda:0") -> Net:
     ints += arch["cin"].reshape(-1).tolist() + arch["cout"].reshape(-1).tolist()
     if "ksize" in arch:
         ints += [int(k) for k in arch["kfull"]] + arch["ksize"].reshape(-1).tolist()
+    else:
+        ints.append(1)
     t = [_stem(p["stem.w"], device), *_fold(p["stem.bn"], eps, device)]
     for i in range(nb):
         t.append(_dev(np.transpose(p[f"ds{i}.dw.w"][:, 0], (1, 2, 0)), bf, device))
@@ -102,8 +104,9 @@ def build_mbnet(arch: dict, p: dict, device="cuda:0") -> Net:
         t += list(_fold(p[f"ds{i}.pw.bn"], eps, device))
     t += [_dev(p[k], f32, device) for k in ("gate.w1", "gate.b1", "gate.w2", "gate.b2")]
     t += [_dev(p["fc.w"], bf, device), _dev(p["fc.b"], f32, device)]
-    # the pointwise filters in front of the gate once more in operand order (behind it the entries are not read)
-    t += [_pointwise_tiles(t[3 + 6 * i + 3]) if i < arch["gate_after"] else t[3 + 6 * i + 3] for i in range(nb)]
+    # the pointwise filters once more in operand order; behind the gate only where the depthwise filters are not sliced (else the
+    # entries are not read)
+    t += [_pointwise_tiles(t[3 + 6 * i + 3]) if i < arch["gate_after"] or "ksize" not in arch else t[3 + 6 * i + 3] for i in range(nb)]
     return Net(DS_ARCH_MBNET, ints, t, arch["num_classes"], 1, T)
 
 

@@ -7,7 +7,7 @@ import torch.nn.functional as F
 
 import workloads as WL
 from oracle import ds_oracle as O
-from tests.parity import relerr
+from tests.parity import relerr, relerr_max
 
 pytestmark = pytest.mark.gpu
 
@@ -263,3 +263,36 @@ def test_mbnet_front_blocks(gpu_lib, pp, image, B):
         a, b = host(fused[i]), host(apart[i])
         assert np.linalg.norm(a - b) < 2e-3 * np.linalg.norm(b) and relerr(a, b) < 4e-2, i
     assert relerr(host(logits), host(want)) < 1e-2
+
+
+# blocks behind the gate in one kernel against the layers apart: the four tiles (32 pixels and 256 or 512 filters, 64 and 112
+# pixels), maps of one row and one pixel, odd maps, a map too wide for a tile next to one that is not
+@pytest.mark.parametrize("image,B", [(224, 2), (224, 20), (224, 50), (224, 70), (224, 140), (150, 33), (34, 9), (640, 1)])
+def test_mbnet_sliced_blocks(gpu_lib, image, B):
+    arch = WL.mbnet_arch(image=image)
+    net = gpu_lib.build_mbnet(arch, WL.mbnet_params(arch, 13), DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(image + B)
+    imgs = torch.randn((B, 3, image, image), generator=gen, device=DEV).to(torch.bfloat16)
+    over = (torch.arange(B, device=DEV, dtype=torch.int32) % arch["T"])[None].contiguous()
+
+    def run():
+        r, taps = (image + 1) // 2, {}
+        for i, (_, co, s) in enumerate(arch["blocks"]):
+            r = (r - 1) // s + 1
+            if i >= arch["gate_after"]:
+                taps[i] = torch.full((B, r * r, co), float("nan"), dtype=torch.bfloat16, device=DEV)
+        out = gpu_lib.ds_forward_taps(net, imgs, taps, route_override=over)
+        return taps, out[0]
+
+    fused, logits = run()
+    net.c_struct.n_ints -= 1                                       # without the flag
+    apart, want = run()
+    for i, t in apart.items():
+        # the pointwise sums are taken in another order, so elements may round the other way at each of up to 16 roundings before
+        # (two a block): 2^-9 of an element each, 2^-9 sqrt(16) together in the 2-norm if all of them did
+        n = torch.isfinite(t)
+        assert torch.equal(n, torch.isfinite(fused[i])) and t[n].abs().max() > 0      # written on the slices alone
+        a, b = host(torch.where(n, fused[i], 0)), host(torch.where(n, t, 0))
+        assert np.linalg.norm(a - b) < 2.0 ** -7 * np.linalg.norm(b) and relerr_max(a, b) < TOL_BF16, i
+    assert relerr_max(host(logits), host(want)) < TOL_BF16
