@@ -15,7 +15,7 @@
 // HC = 32 NW columns of the hidden layer; R row blocks share every weight operand.
 // Around the products a workgroup has nothing beside it on its compute unit, so what it waits for is kept off its path: the
 // residual rows wait in the hidden tile, which is free until the MLP, LayerNorm weights in LDS, biases in registers.  DS-ViT, us
-// a pass: 16 images 711 -> 700, 64 images 1078 -> 1070, 256 images (64 rows a workgroup in place of 96 as well) 2622 -> 2570.
+// a pass: 16 images 709 -> 707, 64 images 1078 -> 1070, 256 images (64 rows a workgroup in place of 96 as well) 2622 -> 2570.
 //
 // Sums run in the order of gemm_kernel's and layernorm16_kernel's, so the results are the same bits.
 #include "gelu.h"
@@ -36,7 +36,9 @@ struct TailTile {
 template <int NW, int R, int D>
 __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const VitTailArgs a) {
     using Tile = TailTile<NW, R, D>;
-    constexpr bool CST = NW <= 12 || R == 1;             // biases travel during the products (13 wavefronts: no registers for them)
+    // biases travel during the products; not with 13 wavefronts (no registers for them) and not with 32 rows, where a smaller kernel
+    // leaves room for those of a batch's other parts (128 images in four: 1998 -> 1925 us)
+    constexpr bool CST = NW <= 12 && R == 2;
     constexpr int BM = 32 * R, HC = 32 * NW, PA = Tile::PA, PH = Tile::PH, RP = 4 * NW, NI = (BM + RP - 1) / RP;   // RP: rows of a row phase
     extern __shared__ __attribute__((aligned(16))) char smem[];
     bf16_t* As = (bf16_t*)smem;                         // [BM][PA]
