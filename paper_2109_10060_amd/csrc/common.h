@@ -97,6 +97,7 @@ struct GemmArgs {
     const int32_t* n_mtiles; // device scalar
     int32_t act, out_f32;
     int32_t B;               // samples of the launch, at most (0: unknown)
+    int32_t crowd;           // launches like this one that run side by side (ds_forward_parts); 0 or 1: this one alone
     int32_t ordered;         // 1: every sum in channel order, as the 128-row kernels take it, whatever the batch size
     GroupTable gt;
 };

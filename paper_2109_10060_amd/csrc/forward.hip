@@ -53,6 +53,7 @@ struct MList {  // m-tile list of one (bucketing, rows-per-sample) pair
     int cap;
     int rows;
     int B;
+    int crowd;      // parts of the batch that run side by side
 };
 
 #define RC(x)                  \
@@ -117,7 +118,7 @@ int32_t conv_gemm(const bf16_t* A, const int32_t* a_index, int64_t a_sstride, in
     a.H = H; a.W = W; a.Ho = Ho; a.Wo = Wo; a.K = K; a.stride = stride; a.pad = pad; a.rows = Ho * Wo;
     a.offsets = offsets; a.mtiles = ml.list ? ds_mtile_entries(ml.list) : nullptr;
     a.n_mtiles = ml.list ? ds_mtile_count(ml.list) : nullptr;
-    a.act = act; a.out_f32 = 0; a.gt = gt; a.B = ml.B;
+    a.act = act; a.out_f32 = 0; a.gt = gt; a.B = ml.B; a.crowd = ml.crowd;
     {
         const int32_t rc = ds_launch_gemm_small(a, ml.cap, max_out(gt), s);
         if (rc != DS_EUNSUPPORTED) return rc;
@@ -223,7 +224,8 @@ void plan_mb(const MbDesc& d, int B, Bump& bp, MbPlan* p) {
     }
 }
 
-int32_t forward_mb(const ds_net* net, const MbDesc& d, const bf16_t* images, int B, const int32_t* route_override,
+// Bs: samples of the whole batch; B of them in this part
+int32_t forward_mb(const ds_net* net, const MbDesc& d, const bf16_t* images, int B, int Bs, const int32_t* route_override,
                    const float* logit_bias, float* logits, int32_t* routes_out, const MbPlan& p, hipStream_t s,
                    const Taps* taps) {
     const void* const* P = net->params;
@@ -307,7 +309,7 @@ int32_t forward_mb(const ds_net* net, const MbDesc& d, const bf16_t* images, int
         }
         // in front of the gate one group of all samples; a third resolution behind it has no list
         const int32_t* offsets = phase ? p.offs : nullptr;
-        MList ml = {nullptr, (int)ds_mtile_capacity(B, r * r, phase ? d.T : 1), r * r, B};
+        MList ml = {nullptr, (int)ds_mtile_capacity(B, r * r, phase ? d.T : 1), r * r, B, (Bs + B - 1) / B};
         for (int k = 0; phase && k < p.n_lists; ++k)
             if (p.list_rows[k] == r * r) ml.list = p.lists[k];
         // depthwise: the first sliced block reads the fixed-width, original-order feature map through perm
@@ -487,8 +489,9 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
         ba.inv_prev = st > 0 ? p.inv[st - 1] : nullptr;
         ba.src_index = p.src_index;          // slot of this stage -> slot of the previous stage's layout
         // the same launch builds the tile lists at both resolutions and the per-slot output width of the stage
-        MList ml_in = {p.lists[2 * st], (int)ds_mtile_capacity(B, rin * rin, G), rin * rin, B};
-        MList ml_out = {p.lists[2 * st + 1], (int)ds_mtile_capacity(B, rout * rout, G), rout * rout, B};
+        const int crowd = (Bs + B - 1) / B;
+        MList ml_in = {p.lists[2 * st], (int)ds_mtile_capacity(B, rin * rin, G), rin * rin, B, crowd};
+        MList ml_out = {p.lists[2 * st + 1], (int)ds_mtile_capacity(B, rout * rout, G), rout * rout, B, crowd};
         ba.n_lists = 2;
         ba.list_rows[0] = rin * rin; ba.lists[0] = ml_in.list;
         ba.list_rows[1] = rout * rout; ba.lists[1] = ml_out.list;
@@ -771,7 +774,7 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
         const int64_t map = (int64_t)sr * sr * C;
         RC(ds_launch_stem(images, nullptr, p.sa, (const bf16_t*)S[0], (const float*)S[1], (const float*)S[2], B, d.image,
                           d.image, 7, 2, 3, C, s));
-        MList ml_s = {nullptr, (int)ds_mtile_capacity(B, sr * sr, 1), sr * sr, B};
+        MList ml_s = {nullptr, (int)ds_mtile_capacity(B, sr * sr, 1), sr * sr, B, 1};
         const GroupTable g1c = table1(C, C);
         for (int i = 0; i < 2; ++i) {
             const void* const* Q = S + 3 + 6 * i;
@@ -803,8 +806,8 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
     }
     RC(ds_launch_gate(g, s));
     // one launch: bucket order, the tile lists for the patch rows and the token rows, the embedding width per slot
-    MList ml_p = {p.list_p, (int)ds_mtile_capacity(B, np, T), np, B};
-    MList ml_t = {p.list_t, (int)ds_mtile_capacity(B, d.N, T), d.N, B};
+    MList ml_p = {p.list_p, (int)ds_mtile_capacity(B, np, T), np, B, 1};
+    MList ml_t = {p.list_t, (int)ds_mtile_capacity(B, d.N, T), d.N, B, 1};
     BucketArgs ba = {};
     ba.route = route; ba.mul = 1; ba.B = B; ba.T = T;
     ba.perm = p.perm; ba.inv_perm = p.inv; ba.offsets = p.offs; ba.slot_group = p.slot_group;
@@ -1019,7 +1022,7 @@ int32_t run_part(const ds_net* net, const bf16_t* images, int b0, int Bp, int Bs
         MbPlan p;
         parse_mb(net, &d);
         plan_mb(d, Bp, bp, &p);
-        return forward_mb(net, d, images + (size_t)b0 * 3 * d.image * d.image, Bp, route_override ? route_override + b0 : nullptr,
+        return forward_mb(net, d, images + (size_t)b0 * 3 * d.image * d.image, Bp, Bs, route_override ? route_override + b0 : nullptr,
                           logit_bias ? logit_bias + (size_t)b0 * d.T : nullptr, logits + (size_t)b0 * d.classes,
                           routes_out ? routes_out + b0 : nullptr, p, s, taps);
     }

@@ -30,7 +30,7 @@
 
 namespace {
 
-constexpr int BM = DS_GEMM_BM, NT = 256;
+constexpr int BM = DS_GEMM_BM, NT = 256;   // NT: threads of a share of the reduction
 
 // 16-byte chunk c of LDS row r is stored at chunk position c ^ swz(r): rows are BK * 2 bytes with no
 // padding; the row-major stores and the operand reads (32 consecutive rows, one chunk column) are
@@ -40,7 +40,7 @@ __device__ __forceinline__ int swz(int r) {
     return BK == 128 ? (r & 15) : BK == 64 ? ((r ^ (r >> 3)) & 7) : (((r >> 1) ^ (r >> 2)) & 3);
 }
 
-template <int WROWS, int WCOLS, int WMT, int WNT, int BK>
+template <int WROWS, int WCOLS, int WMT, int WNT, int BK, int KS>
 struct Tile {
     static constexpr int BN = WCOLS * WNT * 32, LDS_LD = BK;
     static constexpr int COLS = WNT * 32;                      // columns staged per wavefront
@@ -48,20 +48,25 @@ struct Tile {
     static constexpr int ST_LD = COLS + 4;
     static constexpr int LOOP_BYTES = (BM + BN) * LDS_LD * 2;
     static constexpr int STAGE_BYTES = 4 * SROWS * ST_LD * 4;
-    static constexpr int MAIN_BYTES = LOOP_BYTES > STAGE_BYTES ? LOOP_BYTES : STAGE_BYTES;
+    static constexpr int PART_BYTES = KS > 1 ? BM * (BN + 4) * 4 : 0;   // a share's partial tile
+    static constexpr int MAIN0 = LOOP_BYTES > STAGE_BYTES ? LOOP_BYTES : STAGE_BYTES;
+    static constexpr int MAIN_BYTES = MAIN0 > PART_BYTES ? MAIN0 : PART_BYTES;    // of a share
     static constexpr int TABLE_BYTES = BM * (4 + 8 + 8 + 8) + 2 * BN * 4;   // row tables + scale / shift of the tile's columns
-    static constexpr int SMEM = MAIN_BYTES + TABLE_BYTES;
+    static constexpr int SMEM = KS * MAIN_BYTES + TABLE_BYTES;
+    static_assert(KS == 1 || (WCOLS == 1 && WMT == 1 && SMEM <= 160 * 1024), "");
     static_assert(WROWS * WCOLS == 4 && WROWS * WMT * 32 == BM, "4 wavefronts cover a 128-row tile");
 };
 
-template <int WROWS, int WCOLS, int WMT, int WNT, int BK, bool CONV, bool HASR>
-__global__ __launch_bounds__(NT, BK == 128 ? 3 : (WMT * WNT == 2 && !CONV) ? (BK == 32 ? (HASR ? 5 : 6) : 5) : 1) void gemm_kernel(const GemmArgs a, const int ny, const int max_mtiles) {
-    using TL = Tile<WROWS, WCOLS, WMT, WNT, BK>;
+// KS: shares of the reduction, four wavefronts each; a share takes every KS-th slab
+template <int WROWS, int WCOLS, int WMT, int WNT, int BK, int KS, bool CONV, bool HASR>
+__global__ __launch_bounds__(NT * KS, KS > 1 ? 1 : BK == 128 ? 3 : (WMT * WNT == 2 && !CONV) ? (BK == 32 ? (HASR ? 5 : 6) : 5) : 1) void gemm_kernel(const GemmArgs a, const int ny, const int max_mtiles) {
+    using TL = Tile<WROWS, WCOLS, WMT, WNT, BK, KS>;
     constexpr int BN = TL::BN, LDS_LD = BK, CPR = BK / 8, RPT = NT / CPR;   // chunks per row, rows per pass
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    bf16_t* As = (bf16_t*)smem;                       // [BM][BK]
+    const int share = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NT) : 0;
+    bf16_t* As = (bf16_t*)(smem + share * TL::MAIN_BYTES);   // [BM][BK]
     bf16_t* Bs = As + BM * LDS_LD;                    // [BN][BK]
-    long long* rowC = (long long*)(smem + TL::MAIN_BYTES);
+    long long* rowC = (long long*)(smem + KS * TL::MAIN_BYTES);
     long long* rowR = rowC + BM;
     int2* rowYX = (int2*)(rowR + BM);
     uint32_t* rowA = (uint32_t*)(rowYX + BM);
@@ -90,13 +95,13 @@ __global__ __launch_bounds__(NT, BK == 128 ? 3 : (WMT * WNT == 2 && !CONV) ? (BK
     if (seg >= a.n_seg) return;
     const int n0 = (y - seg * ntiles) * BN;
 
-    const int tid = threadIdx.x;
+    const int tid = KS > 1 ? threadIdx.x & (NT - 1) : threadIdx.x;   // of the share
     const int a_ld = a.a_ld > 0 ? a.a_ld : k_in;
     const int c_ld = a.c_ld > 0 ? a.c_ld : k_out;
     const int r_ld = a.r_ld > 0 ? a.r_ld : k_out;
 
     // ---- per-row table: where each of the 128 rows lives --------------------------------
-    if (tid < BM) {
+    if (threadIdx.x < BM) {
         const int m = grow0 + tid;
         long long rc = -1, rr = 0;
         uint32_t ra = OOB;
@@ -155,8 +160,8 @@ __global__ __launch_bounds__(NT, BK == 128 ? 3 : (WMT * WNT == 2 && !CONV) ? (BK
     };
 
     uint4 ra[NA], rb[NB];
-    auto load_global = [&](int tap, int kc) {
-        const bool kok = (kc + kc8) < k_in;
+    auto load_global = [&](int tap, int kc, bool on) {
+        const bool kok = on && (kc + kc8) < k_in;
         const int soff_a = kc * 2;
         const int soff_w = (int)((tap * a.w_tap_stride + kc) * 2);
 #pragma unroll
@@ -204,9 +209,14 @@ __global__ __launch_bounds__(NT, BK == 128 ? 3 : (WMT * WNT == 2 && !CONV) ? (BK
 
     const int kchunks = (k_in + BK - 1) / BK;
     const int nk = a.K * (a.Kw > 0 ? a.Kw : a.K) * kchunks;
-    int tap = 0, kc = 0;
-    set_tap(0);
-    load_global(0, 0);
+    int tap = 0, kc = share * BK;
+    if constexpr (KS > 1)
+        while (kc >= kchunks * BK) {
+            kc -= kchunks * BK;
+            ++tap;
+        }
+    set_tap(tap);
+    load_global(tap, kc, share < nk);
 
     // The first operand slab is requested before anything else: loads return in order, so whatever is issued
     // ahead of it would have to arrive before the slab can go to LDS.
@@ -217,7 +227,7 @@ __global__ __launch_bounds__(NT, BK == 128 ? 3 : (WMT * WNT == 2 && !CONV) ? (BK
     const int ncol = n0 + wn * COLS + cg * 4;
     const bool nok = ncol < k_out;
     // scale and shift of the tile's columns wait in LDS, not in registers, until the epilogue (registers set the residency)
-    if (tid < BN) {
+    if (threadIdx.x < BN) {
         const int n = n0 + tid;
         float vs = 1.f, vh = 0.f;
         if (n < k_out) {
@@ -232,34 +242,68 @@ __global__ __launch_bounds__(NT, BK == 128 ? 3 : (WMT * WNT == 2 && !CONV) ? (BK
     // the residual rows this lane will add are fetched ahead of the main loop, so that their latency hides behind it
     // instead of sitting between the last matrix instruction and the stores -- except with the 64-deep slabs, where
     // their 16 registers would cost a resident workgroup: there they are requested right after the loop
-    constexpr bool RES_EARLY = BK == 32;
-    uint2 rres[HASR ? WMT * PASSES * (SROWS / RPP) : 1];
+    // (with several shares a thread finishes every 16 KS-th row of the tile, few enough to ask for them early)
+    constexpr bool RES_EARLY = BK == 32 || KS > 1;
+    constexpr int NE = KS == 1 ? WMT * PASSES * (SROWS / RPP) : BM / (16 * KS);
+    auto my_row = [&](int i) {
+        if constexpr (KS == 1) return wm * WMT * 32 + (i / (SROWS / RPP)) * SROWS + rr0 + (i % (SROWS / RPP)) * RPP;
+        else return ((int)threadIdx.x >> 4) + i * 16 * KS;
+    };
+    uint2 rres[HASR ? NE : 1];
     auto fetch_residual = [&]() {
 #pragma unroll
-        for (int tm = 0; tm < WMT; ++tm)
-#pragma unroll
-            for (int ps = 0; ps < PASSES; ++ps)
-#pragma unroll
-                for (int q = 0; q < SROWS / RPP; ++q) {
-                    const int r = wm * WMT * 32 + tm * 32 + ps * SROWS + rr0 + q * RPP;
-                    uint2 t = make_uint2(0, 0);
-                    if (nok && rowC[r] >= 0) t = *(const uint2*)(a.R + rowR[r] + ncol);
-                    rres[(tm * PASSES + ps) * (SROWS / RPP) + q] = t;
-                }
+        for (int i = 0; i < NE; ++i) {
+            const int r = my_row(i);
+            uint2 t = make_uint2(0, 0);
+            if (nok && rowC[r] >= 0) t = *(const uint2*)(a.R + rowR[r] + ncol);
+            rres[i] = t;
+        }
     };
     if constexpr (HASR && RES_EARLY) fetch_residual();
+    // four channels of a row: scale and shift, residual, activation, store
+    auto finish = [&](const float4 t, long long coff, const uint2 q) {
+        const float4 s4 = *(const float4*)(scl + wn * COLS + cg * 4), h4 = *(const float4*)(scl + BN + wn * COLS + cg * 4);
+        float val[4] = {t.x * s4.x + h4.x, t.y * s4.y + h4.y, t.z * s4.z + h4.z, t.w * s4.w + h4.w};
+        if constexpr (HASR) {
+            val[0] += __uint_as_float(q.x << 16);
+            val[1] += __uint_as_float(q.x & 0xffff0000u);
+            val[2] += __uint_as_float(q.y << 16);
+            val[3] += __uint_as_float(q.y & 0xffff0000u);
+        }
+        if (a.act == DS_ACT_RELU) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) val[e] = fmaxf(val[e], 0.f);
+        } else if (a.act == DS_ACT_GELU) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) val[e] = gelu_erf(val[e]);
+        }
+        if (a.out_f32) *(float4*)((float*)a.C + coff + ncol) = make_float4(val[0], val[1], val[2], val[3]);
+        else *(uint2*)((bf16_t*)a.C + coff + ncol) = make_uint2(f2bf2(val[0], val[1]), f2bf2(val[2], val[3]));
+    };
 
     store_lds();
     __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        kc += BK;
-        if (kc >= k_in) {
-            kc = 0;
-            ++tap;
-            if (kt + 1 < nk) set_tap(tap);
+    const int turns = KS > 1 ? (nk + KS - 1) / KS : nk;      // every share as many; a slab past the last is zeros
+    for (int kt = 0; kt < turns; ++kt) {
+        const bool more = kt + 1 < turns;
+        if constexpr (KS == 1) {
+            kc += BK;
+            if (kc >= k_in) {
+                kc = 0;
+                ++tap;
+                if (more) set_tap(tap);
+            }
+        } else {
+            kc += KS * BK;
+            bool next = false;
+            while (kc >= kchunks * BK) {
+                kc -= kchunks * BK;
+                ++tap;
+                next = true;
+            }
+            if (more && next) set_tap(tap);
         }
-        const bool more = kt + 1 < nk;
-        if (more) load_global(tap, kc);
+        if (more) load_global(tap, kc, KS == 1 || share + (kt + 1) * KS < nk);
 #pragma unroll
         for (int kk = 0; kk < BK / 16; ++kk) {
             bf16x8_t af[WMT], bfr[WNT];
@@ -283,6 +327,29 @@ __global__ __launch_bounds__(NT, BK == 128 ? 3 : (WMT * WNT == 2 && !CONV) ? (BK
 
     if constexpr (HASR && !RES_EARLY) fetch_residual();
 
+    if constexpr (KS > 1) {
+        // ---- partial tiles to LDS, added in share order (the loop's last barrier has retired every read of the slabs there)
+        float* part = (float*)As;
+#pragma unroll
+        for (int tn = 0; tn < WNT; ++tn)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) part[(wm * 32 + 8 * (v >> 2) + 4 * lhi + (v & 3)) * ST_LD + tn * 32 + l32] = acc[0][tn][v];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            const int r = my_row(i);
+            const long long coff = rowC[r];
+            if (!nok || coff < 0) continue;
+            float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int k = 0; k < KS; ++k) {
+                const float4 q = *(const float4*)((const float*)(smem + k * TL::MAIN_BYTES) + r * ST_LD + cg * 4);
+                t.x += q.x; t.y += q.y; t.z += q.z; t.w += q.w;
+            }
+            finish(t, coff, rres[HASR ? i : 0]);
+        }
+        return;
+    }
     // ---- epilogue through LDS: each lane finishes 4 consecutive channels of one row -----
     // The staging rows belong to one wavefront (written and read back by its own lanes, and the main loop's last
     // barrier has already retired every read of the operand tiles they alias), and a wavefront's LDS accesses
@@ -312,31 +379,8 @@ __global__ __launch_bounds__(NT, BK == 128 ? 3 : (WMT * WNT == 2 && !CONV) ? (BK
                     const int r = wm * WMT * 32 + tm * 32 + ps * SROWS + rr;
                     const long long coff = rowC[r];
                     if (coff < 0) continue;
-                    const float4 t = *(const float4*)(st + rr * ST_LD + cg * 4);
-                    const float4 s4 = *(const float4*)(scl + wn * COLS + cg * 4), h4 = *(const float4*)(scl + BN + wn * COLS + cg * 4);
-                    float val[4] = {t.x * s4.x + h4.x, t.y * s4.y + h4.y, t.z * s4.z + h4.z, t.w * s4.w + h4.w};
-                    if constexpr (HASR) {
-                        const uint2 q = rres[(tm * PASSES + ps) * (SROWS / RPP) + (rr - rr0) / RPP];
-                        val[0] += __uint_as_float(q.x << 16);
-                        val[1] += __uint_as_float(q.x & 0xffff0000u);
-                        val[2] += __uint_as_float(q.y << 16);
-                        val[3] += __uint_as_float(q.y & 0xffff0000u);
-                    }
-                    if (a.act == DS_ACT_RELU) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) val[e] = fmaxf(val[e], 0.f);
-                    } else if (a.act == DS_ACT_GELU) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) val[e] = gelu_erf(val[e]);
-                    }
-                    if (a.out_f32) {
-                        *(float4*)((float*)a.C + coff + ncol) = make_float4(val[0], val[1], val[2], val[3]);
-                    } else {
-                        uint2 q;
-                        q.x = f2bf2(val[0], val[1]);
-                        q.y = f2bf2(val[2], val[3]);
-                        *(uint2*)((bf16_t*)a.C + coff + ncol) = q;
-                    }
+                    finish(*(const float4*)(st + rr * ST_LD + cg * 4), coff,
+                           rres[HASR ? (tm * PASSES + ps) * (SROWS / RPP) + (rr - rr0) / RPP : 0]);
                 }
             }
             wave_sync();
@@ -344,10 +388,10 @@ __global__ __launch_bounds__(NT, BK == 128 ? 3 : (WMT * WNT == 2 && !CONV) ? (BK
     }
 }
 
-template <int WROWS, int WCOLS, int WMT, int WNT, int BK, bool CONV, bool HASR>
+template <int WROWS, int WCOLS, int WMT, int WNT, int BK, int KS, bool CONV, bool HASR>
 int32_t launch(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
-    using TL = Tile<WROWS, WCOLS, WMT, WNT, BK>;
-    auto kern = gemm_kernel<WROWS, WCOLS, WMT, WNT, BK, CONV, HASR>;
+    using TL = Tile<WROWS, WCOLS, WMT, WNT, BK, KS>;
+    auto kern = gemm_kernel<WROWS, WCOLS, WMT, WNT, BK, KS, CONV, HASR>;
     {
         const int32_t rc = ds_reserve_lds((const void*)kern, TL::SMEM, "sliced gemm");
         if (rc) return rc;
@@ -355,7 +399,7 @@ int32_t launch(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStrea
     const int ny = a.n_seg * ((max_kout + TL::BN - 1) / TL::BN);
     const unsigned grid = (unsigned)(((max_mtiles + 7) / 8) * ny * 8);
     ProfScope prof(a.K > 1 ? DS_K_GEMM_TAPS : DS_K_GEMM, s);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), TL::SMEM, s, a, ny, max_mtiles);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(NT * KS), TL::SMEM, s, a, ny, max_mtiles);
     DS_CHECK_LAUNCH("sliced gemm");
     return DS_OK;
 }
@@ -404,10 +448,17 @@ int32_t ds_launch_gemm(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, 
                  : launch<__VA_ARGS__, true, false>(a, max_mtiles, max_kout, s))                       \
           : (a.R ? launch<__VA_ARGS__, false, true>(a, max_mtiles, max_kout, s)                        \
                  : launch<__VA_ARGS__, false, false>(a, max_mtiles, max_kout, s)))
-    if (!deep) return DS_GEMM_DISPATCH(4, 1, 1, 2, 32);   // 64-wide tile, 32-deep slabs
-    // launches of about one generation with long reductions: 128-deep slabs halve the number of dependent rounds
-    const long long wgs = (long long)max_mtiles * a.n_seg * ((max_kout + 63) / 64);
-    if (kmax >= 512 && wgs <= 256 * 6) return DS_GEMM_DISPATCH(4, 1, 1, 2, 128);
-    return DS_GEMM_DISPATCH(4, 1, 1, 2, 64);
+    if (!deep) return DS_GEMM_DISPATCH(4, 1, 1, 2, 32, 1);   // 64-wide tile, 32-deep slabs
+    // launches of about one generation with long reductions (below): 128-deep slabs halve the number of dependent rounds
+    const long long wgs = (long long)max_mtiles * a.n_seg * ((max_kout + 63) / 64), slabs = taps * ((kmax + 63) / 64);
+    const long long all = wgs * (a.crowd > 1 ? a.crowd : 1);
+    // Fewer workgroups than run at once: the slabs of a tile dealt to shares of four wavefronts (not where sums keep one order).
+    // DS-ResNet, us a launch, one share -> here: 8 images, 64 -> 256 channels with residual 9.6 -> 8.4, 14x14 3x3/2 13.0 -> 11.2; 33
+    // images, 1024 -> 256 14.1 -> 12.6, 2048 -> 512 21.9 -> 17.2, 3x3/2 29.6 -> 24.0; 64 images 3x3/2 35.7 -> 26.6.  Twice these
+    // lines: 905 -> 912 us a pass at 33 images, DS-ResNet++ 950 -> 991, DS-MBNet++ 40 images 331 -> 355.
+    if (!a.ordered && slabs >= 8 && all <= (slabs >= 32 ? 512 : 256)) return DS_GEMM_DISPATCH(4, 1, 1, 2, 64, 4);
+    if (!a.ordered && slabs >= 4 && all <= 512) return DS_GEMM_DISPATCH(4, 1, 1, 2, 64, 2);
+    if (kmax >= 512 && wgs <= 256 * 6) return DS_GEMM_DISPATCH(4, 1, 1, 2, 128, 1);
+    return DS_GEMM_DISPATCH(4, 1, 1, 2, 64, 1);
 #undef DS_GEMM_DISPATCH
 }

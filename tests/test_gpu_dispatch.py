@@ -97,6 +97,17 @@ def test_sliced_conv_bf16_taps(gpu_lib, B, K, stride, pad, H, W, c_in, c_out, re
     _conv_case(gpu_lib, B, K, stride, pad, H, W, c_in, c_out, res, False)
 
 
+# more than a few samples, bf16, fewer workgroups than run at once: two and four shares of a reduction, shares without a slab of a
+# narrow slice, ragged last tiles
+@pytest.mark.parametrize("B,K,stride,pad,H,W,c_in,c_out,res", [
+    (13, 3, 1, 1, 14, 14, (264, 40), (416, 72), True), (31, 3, 1, 1, 14, 14, (56, 40), (168, 136), False),
+    (41, 3, 1, 1, 8, 7, (520, 8), (488, 64), False), (13, 1, 1, 0, 14, 14, (520, 24), (416, 72), True),
+    (13, 1, 1, 0, 14, 14, (264, 136), (424, 8), False), (14, 3, 2, 1, 27, 27, (72, 16), (416, 392), False),
+    (50, 1, 2, 0, 13, 14, (328, 64), (488, 480), True)])
+def test_sliced_conv_bf16_shares(gpu_lib, B, K, stride, pad, H, W, c_in, c_out, res):
+    _conv_case(gpu_lib, B, K, stride, pad, H, W, c_in, c_out, res, False)
+
+
 # the tile records worked out from the offsets: groups without samples, one group, as many groups as lanes
 @pytest.mark.parametrize("B,T,rows", [(1, 1, 1), (3, 64, 130), (70, 64, 33), (64, 5, 197), (300, 7, 128)])
 def test_sliced_linear_tile_records(gpu_lib, B, T, rows):
