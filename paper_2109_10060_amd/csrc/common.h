@@ -337,6 +337,7 @@ struct VitLinearArgs {
     const bf16_t* res;                   // addressed like y, nullable; may be y
     bf16_t* y;
     const int32_t* offsets;
+    int32_t crowd;                       // as in GemmArgs
     GroupTable gt;
 };
 // DS_EUNSUPPORTED beyond 416 input channels with a LayerNorm, 1664 without

@@ -710,7 +710,7 @@ int32_t linear_gemm(const bf16_t* A, int64_t a_ss, int a_ld, const bf16_t* Wt, i
 
 // projection, LN2 and MLP of one block on the tiled weights Q; L: the block's other parameters
 int32_t vit_behind_attention(const VitDesc& d, const void* const* L, const void* const* Q, const VitPlan& p, const GroupTable& gp,
-                             const GroupTable& g1, const GroupTable& g2, int B, float eps, hipStream_t s) {
+                             const GroupTable& g1, const GroupTable& g2, int B, int crowd, float eps, hipStream_t s) {
     const int Hd = d.H * d.dh;
     const int64_t x_ss = (int64_t)d.N * d.D;
     const int kbp = (Hd + 15) / 16 | 1, kb1 = (d.D + 15) / 16 | 1, kb2 = (d.M + 15) / 16 | 1;
@@ -737,7 +737,7 @@ int32_t vit_behind_attention(const VitDesc& d, const void* const* L, const void*
     }
     VitLinearArgs la;
     memset(&la, 0, sizeof(la));
-    la.rows = d.N; la.offsets = p.offs; la.n_seg = 1;
+    la.rows = d.N; la.offsets = p.offs; la.n_seg = 1; la.crowd = crowd;
     la.x = p.o; la.x_ss = (int64_t)d.N * Hd; la.x_ld = Hd; la.kb = kbp; la.seg_blocks = nbd; la.w = (const bf16_t*)Q[0];
     la.bias = (const float*)L[5]; la.res = p.x; la.y = p.x; la.y_ss = x_ss; la.gt = gp;
     int32_t rc = ds_launch_vit_linear(la, B, s);
@@ -753,7 +753,7 @@ int32_t vit_behind_attention(const VitDesc& d, const void* const* L, const void*
     return ds_launch_vit_linear(la, B, s);
 }
 
-int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, int B, const int32_t* route_override,
+int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, int B, int Bs, const int32_t* route_override,
                     const float* logit_bias, float* logits, int32_t* routes_out, const VitPlan& p, hipStream_t s,
                     const Taps* taps) {
     const void* const* P = net->params + d.pbase;
@@ -886,6 +886,7 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
             memset(&la, 0, sizeof(la));
             la.x = p.x; la.x_ss = x_ss; la.gamma = (const float*)L[0]; la.beta = (const float*)L[1]; la.eps = eps;
             la.rows = d.N; la.offsets = p.offs; la.n_seg = 3; la.seg_blocks = (Hd + 31) / 32; la.kb = (d.D + 15) / 16 | 1;
+            la.crowd = (Bs + B - 1) / B;
             la.w = (const bf16_t*)Q[3];
             la.bias = (const float*)L[3]; la.bias_seg = Hd;
             la.y = p.qkv; la.y_ss = (int64_t)d.N * Hd; la.y_ld = Hd; la.y_seg = (int64_t)p.qkv_seg; la.gt = gq;
@@ -903,7 +904,7 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
                                (int64_t)d.N * Hd, p.slot_group, gq, B, d.N, d.H, d.dh, s));
         if (qkv) {
             const void* const* Q = P + d.tiled + 4 * l;
-            const int32_t rc = vit_behind_attention(d, L, Q, p, gp, g1, g2, B, eps, s);
+            const int32_t rc = vit_behind_attention(d, L, Q, p, gp, g1, g2, B, (Bs + B - 1) / B, eps, s);
             if (rc == DS_OK) {
                 RC(tap_block(taps, l, p.x, x_ss, 0, p.perm, p.slot_group, g2, B, d.N, d.D, s));
                 continue;
@@ -1039,7 +1040,7 @@ int32_t run_part(const ds_net* net, const bf16_t* images, int b0, int Bp, int Bs
     VitPlan p;
     parse_vit(net, &d);
     plan_vit(d, Bp, bp, &p);
-    return forward_vit(net, d, images + (size_t)b0 * 3 * d.image * d.image, Bp, route_override ? route_override + b0 : nullptr,
+    return forward_vit(net, d, images + (size_t)b0 * 3 * d.image * d.image, Bp, Bs, route_override ? route_override + b0 : nullptr,
                        logit_bias ? logit_bias + (size_t)b0 * d.T : nullptr, logits + (size_t)b0 * d.classes,
                        routes_out ? routes_out + b0 : nullptr, p, s, taps);
 }

@@ -9,14 +9,16 @@
 // Two uses.  Large batches: the Q/K/V layer with 12 wavefronts and 96 or 64 rows, all columns in one workgroup (the rows
 // are read once; gemm_kernel read them once per 64 columns).  Few images: all four layers of a block with 4 wavefronts and
 // 32 rows, where a launch is bound by latency and by how many compute units share the weights' way in; the LayerNorm
-// launches disappear.  Sums are in gemm_kernel's order: the same bits.
+// launches disappear.  A LayerNorm there is a chain in front of the products: its weights are asked for beside the rows and its sums
+// run over rotations within 16 lanes instead of exchanges through LDS (rows and LayerNorm 3.4 -> 2 us of a launch of 7.5).
+// Sums are in gemm_kernel's order: the same bits.
 #include "gelu.h"
 #include "vit_rows.h"
 
 namespace {
 
-// KM: channels of the reduction, at most
-template <int NW, int R, int D, int KM>
+// KM: channels of the reduction, at most.  FEW: a launch of a few images, a chain of latencies: everything asked for as early as it can be
+template <int NW, int R, int D, int KM, bool FEW>
 __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const VitLinearArgs a, const int runs, const int run_blocks) {
     constexpr int PITCH = tile_pitch(KM, D);
     constexpr int BM = 32 * R, SP = 32 * NW + 8, RP = 4 * NW, NI = (BM + RP - 1) / RP, KIT = (PITCH - 8 + 127) / 128, NS = 4 * NW;
@@ -25,22 +27,32 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
     bf16_t* Ss = As + BM * PITCH;                        // [BM][SP] output stage
 
     const int run = (int)blockIdx.x % runs;
-    const int4 me = ds_tile_record_of(a.offsets, a.gt.T, a.rows, (int)blockIdx.x / runs, BM);
+    const GroupLanes lanes(a.gt);
+    const bf16_t *x = a.x, *wt = a.w, *res = a.res;
+    bf16_t* y = a.y;
+    const float *gamma = a.gamma, *beta = a.beta, *bias0 = a.bias;
+    int64_t x_ss = a.x_ss, y_ss = a.y_ss, y_seg = a.y_seg;
+    int x_ld = a.x_ld, y_ld = a.y_ld, rows = a.rows, kb = a.kb, seg_blocks = a.seg_blocks, n_seg = a.n_seg, bias_seg = a.bias_seg, act = a.act;
+    float eps = a.eps;
+    const int4 me = ds_tile_record_of(a.offsets, a.gt.T, rows, (int)blockIdx.x / runs, BM);
+    if constexpr (FEW)
+        ds_hold(x, wt, res, y, gamma, beta, bias0, x_ss, y_ss, y_seg, x_ld, y_ld, rows, kb, seg_blocks, n_seg, bias_seg, act, eps);
     if (me.x < 0) return;
     const int g = me.x, grow0 = me.y, slot0 = me.z, rows_g = me.w;
-    const int kin = a.gt.k_in[g], k_out = a.gt.k_out[g];
+    const int kin = lanes.k_in(g), k_out = lanes.k_out(g);
     if (kin <= 0 || k_out <= 0) return;
-    const int nb = (k_out + 31) / 32, total = nb * a.n_seg;      // column blocks of a segment, of the layer
+    const int nb = (k_out + 31) / 32, total = nb * n_seg;      // column blocks of a segment, of the layer
     const int blk0 = run * run_blocks, blk1 = min(total, blk0 + run_blocks);
     if (blk0 >= total) return;
 
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int l16 = tid & 15, prow = tid >> 4;
     const uint32_t lane16 = (uint32_t)lane * 16;
-    const int x_ld = a.x_ld > 0 ? a.x_ld : kin, y_ld = a.y_ld > 0 ? a.y_ld : k_out;
+    if (x_ld <= 0) x_ld = kin;
+    if (y_ld <= 0) y_ld = k_out;
 
     bf16x8_t ring[D];
-    auto weights = [&](int p) { return weight_row(a.w, ((p / nb) * a.seg_blocks + p % nb) * a.kb, kin); };
+    auto weights = [&](int p) { return weight_row(wt, ((p / nb) * seg_blocks + p % nb) * kb, kin); };
     auto start = [&](int p) {
         const __amdgpu_buffer_rsrc_t rw = weights(p);
 #pragma unroll
@@ -51,15 +63,19 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
     // ---- rows -------------------------------------------------------------------------------------------------------------
     int64_t yoff[NI];
     bool live[NI];
+    NormWeights nw;
+    if constexpr (FEW && KIT <= 4) {
+        if (gamma) nw.load(gamma, beta, kin, l16);
+    }
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
         const bool in = BM % RP == 0 || prow + RP * i < BM;
         const int m = grow0 + prow + RP * i;
         live[i] = in && m < rows_g;
         const int mm = live[i] ? m : grow0;
-        const int sl = mm / a.rows, p = mm - sl * a.rows, slot = slot0 + sl;
-        yoff[i] = (int64_t)slot * a.y_ss + (int64_t)p * y_ld;
-        const bf16_t* xrow = a.x + (int64_t)slot * a.x_ss + (int64_t)p * x_ld;
+        const int sl = mm / rows, p = mm - sl * rows, slot = slot0 + sl;
+        yoff[i] = (int64_t)slot * y_ss + (int64_t)p * y_ld;
+        const bf16_t* xrow = x + (int64_t)slot * x_ss + (int64_t)p * x_ld;
         uint4 q[KIT];
 #pragma unroll
         for (int k = 0; k < KIT; ++k) {
@@ -68,12 +84,13 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
             if (ch < kin) q[k] = *(const uint4*)(xrow + ch);
         }
         if constexpr (KIT <= 4) {
-            if (a.gamma) {
+            if (gamma) {
                 float v[4][8];
                 uint4 o[4];
 #pragma unroll
                 for (int k = 0; k < KIT; ++k) unpack8(q[k], v[k]);
-                row_norm(v, kin, l16, a.eps, a.gamma, a.beta, o);
+                if constexpr (FEW) row_norm(v, kin, l16, eps, nw, o);
+                else row_norm(v, kin, l16, eps, gamma, beta, o);
 #pragma unroll
                 for (int k = 0; k < KIT; ++k)
                     if ((k * 16 + l16) * 8 < kin) q[k] = o[k];
@@ -90,7 +107,7 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
     for (int b0 = blk0; b0 < blk1; b0 += NW) {
         const int p = b0 + w, seg = p / nb, n0 = (p - seg * nb) * 32;
         const bool on = p < blk1;
-        if (a.res) {
+        if (res) {
             // the residual of these columns waits in the stage, where the sums are added in place
 #pragma unroll
             for (int i = 0; i < NI; ++i)
@@ -98,7 +115,7 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
                 for (int k = 0; k < (NS + 15) / 16; ++k) {
                     const int c = k * 16 + l16, n = (b0 + (c >> 2)) * 32 + (c & 3) * 8;
                     if (c < NS && live[i] && n < k_out)
-                        *(uint4*)(Ss + (prow + RP * i) * SP + c * 8) = *(const uint4*)(a.res + yoff[i] + n);
+                        *(uint4*)(Ss + (prow + RP * i) * SP + c * 8) = *(const uint4*)(res + yoff[i] + n);
                 }
         }
         __syncthreads();                                 // rows (and residual) are in place
@@ -109,6 +126,15 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
             for (int v = 0; v < 16; ++v) acc[r][v] = 0.f;
         if (on) {
             const __amdgpu_buffer_rsrc_t rw = weights(p);
+            const float* bias = bias0 + (int64_t)seg * bias_seg;
+            float4 hb[FEW ? 4 : 1];
+            if constexpr (FEW) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int n = n0 + 8 * q + 4 * lhi;
+                    hb[q] = n < k_out ? *(const float4*)(bias + n) : make_float4(0.f, 0.f, 0.f, 0.f);
+                }
+            }
             const bf16_t* base = As + l32 * PITCH + lhi * 8;
             bf16x8_t f[2][R];
 #pragma unroll
@@ -126,21 +152,20 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
                 }
             }
             if (p + NW < blk1) start(p + NW);
-            const float* bias = a.bias + (int64_t)seg * a.bias_seg;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int n = n0 + 8 * q + 4 * lhi;
                 if (n >= k_out) continue;
-                const float4 h = *(const float4*)(bias + n);
+                const float4 h = FEW ? hb[FEW ? q : 0] : *(const float4*)(bias + n);
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     uint2* s = (uint2*)(Ss + (r * 32 + l32) * SP + w * 32 + 8 * q + 4 * lhi);
                     float v0 = acc[r][4 * q] + h.x, v1 = acc[r][4 * q + 1] + h.y, v2 = acc[r][4 * q + 2] + h.z, v3 = acc[r][4 * q + 3] + h.w;
-                    if (a.act == DS_ACT_GELU) {
+                    if (act == DS_ACT_GELU) {
                         *s = gelu_bf16x4(v0, v1, v2, v3);
                         continue;
                     }
-                    if (a.res) {
+                    if (res) {
                         const uint2 t = *s;
                         v0 += __uint_as_float(t.x << 16);
                         v1 += __uint_as_float(t.x & 0xffff0000u);
@@ -159,21 +184,21 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
                 const int c = k * 16 + l16, pb = b0 + (c >> 2);
                 if (c >= NS || pb >= blk1 || !live[i]) continue;
                 const int sg = pb / nb, n = (pb - sg * nb) * 32 + (c & 3) * 8;
-                if (n < k_out) *(uint4*)(a.y + yoff[i] + (int64_t)sg * a.y_seg + n) = *(const uint4*)(Ss + (prow + RP * i) * SP + c * 8);
+                if (n < k_out) *(uint4*)(y + yoff[i] + (int64_t)sg * y_seg + n) = *(const uint4*)(Ss + (prow + RP * i) * SP + c * 8);
             }
         if (b0 + NW < blk1) __syncthreads();             // the stage is free again
     }
 }
 
-template <int NW, int R, int D, int KM>
+template <int NW, int R, int D, int KM, bool FEW>
 int32_t launch(const VitLinearArgs& a, int64_t tiles, int max_blocks, int run_blocks, hipStream_t s) {
     constexpr int SMEM = 32 * R * (tile_pitch(KM, D) + 32 * NW + 8) * 2;
     static_assert(SMEM <= 160 * 1024, "LDS of a compute unit");
-    const int32_t rc = ds_reserve_lds((const void*)vit_linear_kernel<NW, R, D, KM>, SMEM, "tiled linear layer");
+    const int32_t rc = ds_reserve_lds((const void*)vit_linear_kernel<NW, R, D, KM, FEW>, SMEM, "tiled linear layer");
     if (rc) return rc;
     const int runs = (max_blocks + run_blocks - 1) / run_blocks;
     ProfScope prof(DS_K_VIT_LINEAR, s);
-    hipLaunchKernelGGL((vit_linear_kernel<NW, R, D, KM>), dim3((unsigned)(tiles * runs)), dim3(64 * NW), SMEM, s, a, runs, run_blocks);
+    hipLaunchKernelGGL((vit_linear_kernel<NW, R, D, KM, FEW>), dim3((unsigned)(tiles * runs)), dim3(64 * NW), SMEM, s, a, runs, run_blocks);
     DS_CHECK_LAUNCH("tiled linear layer");
     return DS_OK;
 }
@@ -196,10 +221,14 @@ int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s) {
     auto tiles = [&](int bm) { return (n - groups) / bm + groups; };
     const int blocks = (nmax + 31) / 32 * a.n_seg;
     if (kmax <= VIT_K_MAX) {
-        if (tiles(96) >= 448) return launch<12, 3, 4, VIT_K_MAX>(a, tiles(96), blocks, blocks, s);
-        if (tiles(64) >= 160) return launch<12, 2, 4, VIT_K_MAX>(a, tiles(64), blocks, blocks, s);
-        return launch<4, 1, 8, VIT_K_MAX>(a, tiles(32), blocks, tiles(32) > 64 ? 8 : 4, s);
+        if (tiles(96) >= 448) return launch<12, 3, 4, VIT_K_MAX, false>(a, tiles(96), blocks, blocks, s);
+        if (tiles(64) >= 160) return launch<12, 2, 4, VIT_K_MAX, false>(a, tiles(64), blocks, blocks, s);
+        // (the early requests cost 50 registers, a third of the workgroups a compute unit holds: not where there are enough of them,
+        // nor beside the launches of a batch's other parts -- 16 images 677 us a pass against 696, 64 images in four parts 1193 and 1115)
+        const int run = tiles(32) > 64 ? 8 : 4;
+        if (a.crowd <= 1 && tiles(32) <= 128) return launch<4, 1, 8, VIT_K_MAX, true>(a, tiles(32), blocks, run, s);
+        return launch<4, 1, 8, VIT_K_MAX, false>(a, tiles(32), blocks, run, s);
     }
     if (kmax > 1664 || a.gamma) return DS_EUNSUPPORTED;
-    return launch<4, 1, 16, 1664>(a, tiles(32), blocks, 4, s);
+    return launch<4, 1, 16, 1664, true>(a, tiles(32), blocks, 4, s);
 }

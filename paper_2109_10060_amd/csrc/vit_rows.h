@@ -15,10 +15,39 @@ __device__ __forceinline__ uint4 pack8(const float* v) {
     return make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]), f2bf2(v[4], v[5]), f2bf2(v[6], v[7]));
 }
 
+// sum over 16 neighbouring lanes, all of them get it: rotations within the row of 16, the same pairs as exchanges over lane bits 3, 2,
+// 1, 0 (after the first step the values repeat every 8 lanes, then every 4, 2) and so the same bits, without LDS round trips
+__device__ __forceinline__ float row16_sum(float s) {
+    s += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(s), 0x128, 0xf, 0xf, true));
+    s += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(s), 0x124, 0xf, 0xf, true));
+    s += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(s), 0x122, 0xf, 0xf, true));
+    s += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(s), 0x121, 0xf, 0xf, true));
+    return s;
+}
+// LayerNorm weights of a lane's chunks, asked for beside the rows: behind the statistics they are one more round trip
+struct NormWeights {
+    float g[4][8], b[4][8];
+    __device__ __forceinline__ void load(const float* gamma, const float* beta, int d, int l16) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int ch = (k * 16 + l16) * 8;
+#pragma unroll
+            for (int i = 0; i < 8; i += 4) {
+                float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
+                if (ch < d) {
+                    x = *(const float4*)(gamma + ch + i);
+                    y = *(const float4*)(beta + ch + i);
+                }
+                g[k][i] = x.x; g[k][i + 1] = x.y; g[k][i + 2] = x.z; g[k][i + 3] = x.w;
+                b[k][i] = y.x; b[k][i + 1] = y.y; b[k][i + 2] = y.z; b[k][i + 3] = y.w;
+            }
+        }
+    }
+};
+
 // LayerNorm of one row held by 16 lanes, lane l with the 8-channel chunks l, l + 16, l + 32, l + 48; the arithmetic and
 // the order of layernorm16_kernel
-__device__ __forceinline__ void row_norm(const float (&v)[4][8], int d, int l16, float eps, const float* gamma,
-                                         const float* beta, uint4 (&out)[4]) {
+__device__ __forceinline__ float row_stats(const float (&v)[4][8], int d, int l16, float eps, float* mean) {
     float s = 0.f;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
@@ -26,9 +55,8 @@ __device__ __forceinline__ void row_norm(const float (&v)[4][8], int d, int l16,
 #pragma unroll
             for (int i = 0; i < 8; ++i) s += v[k][i];
         }
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 16);
-    const float mu = s / (float)d;
+    const float mu = row16_sum(s) / (float)d;
+    *mean = mu;
     float q = 0.f;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
@@ -39,9 +67,24 @@ __device__ __forceinline__ void row_norm(const float (&v)[4][8], int d, int l16,
                 q += t * t;
             }
         }
+    return 1.0f / sqrtf(row16_sum(q) / (float)d + eps);
+}
+__device__ __forceinline__ void row_norm(const float (&v)[4][8], int d, int l16, float eps, const NormWeights& w, uint4 (&out)[4]) {
+    float mu;
+    const float rstd = row_stats(v, d, l16, eps, &mu);
 #pragma unroll
-    for (int o = 8; o > 0; o >>= 1) q += __shfl_xor(q, o, 16);
-    const float rstd = 1.0f / sqrtf(q / (float)d + eps);
+    for (int k = 0; k < 4; ++k)
+        if ((k * 16 + l16) * 8 < d) {
+            float o8[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) o8[i] = (v[k][i] - mu) * rstd * w.g[k][i] + w.b[k][i];
+            out[k] = pack8(o8);
+        }
+}
+__device__ __forceinline__ void row_norm(const float (&v)[4][8], int d, int l16, float eps, const float* gamma,
+                                         const float* beta, uint4 (&out)[4]) {
+    float mu;
+    const float rstd = row_stats(v, d, l16, eps, &mu);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int ch = (k * 16 + l16) * 8;
