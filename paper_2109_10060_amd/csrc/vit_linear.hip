@@ -226,6 +226,10 @@ int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s) {
         // (the early requests cost 50 registers, a third of the workgroups a compute unit holds: not where there are enough of them,
         // nor beside the launches of a batch's other parts -- 16 images 677 us a pass against 696, 64 images in four parts 1193 and 1115)
         const int run = tiles(32) > 64 ? 8 : 4;
+        // up to a workgroup a compute unit eight wavefronts: half as many rows each to fetch and normalise, four of them multiply
+        // (1 image 503 -> 483 us a pass, 3 images 540 -> 520; 5 images, with two workgroups for some, 567 -> 620)
+        if (a.crowd <= 1 && run == 4 && tiles(32) * ((blocks + 3) / 4) <= 256)
+            return launch<8, 1, 8, VIT_K_MAX, true>(a, tiles(32), blocks, run, s);
         if (a.crowd <= 1 && tiles(32) <= 128) return launch<4, 1, 8, VIT_K_MAX, true>(a, tiles(32), blocks, run, s);
         return launch<4, 1, 8, VIT_K_MAX, false>(a, tiles(32), blocks, run, s);
     }
