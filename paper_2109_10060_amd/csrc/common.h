@@ -207,7 +207,6 @@ struct GateArgs {
     float* partial;           // [B][splits][C] scratch
 };
 size_t ds_gate_partial_bytes(int32_t B, int32_t C);
-int32_t ds_launch_gate(const GateArgs& a, hipStream_t s);
 // y[b][p][c] = x[b][p][c] * scale[b][c] on the valid channels (NHWC) / y[b][c][p] (NCHW); fp32 or bf16
 int32_t ds_launch_channel_scale(const void* x, void* y, const float* scale, const int32_t* c_in, int32_t dtype,
                                 int32_t layout, int32_t B, int32_t C, int32_t HW, hipStream_t s);
@@ -226,6 +225,8 @@ struct BucketArgs {
     int32_t lut[DS_MAX_GROUPS];
 };
 int32_t ds_launch_bucket_ex(const BucketArgs& a, hipStream_t s);
+// bucket (one sample, T <= 64): made by the gate's last launch itself, its route field is not read
+int32_t ds_launch_gate(const GateArgs& a, hipStream_t s, const BucketArgs* bucket = nullptr);
 int32_t ds_launch_bucket(const int32_t* route, int32_t B, int32_t T, int32_t* perm, int32_t* inv_perm,
                          int32_t* offsets, int32_t* slot_group, hipStream_t s);
 

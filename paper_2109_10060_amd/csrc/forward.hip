@@ -101,6 +101,14 @@ int32_t tap_block(const Taps* taps, int id, const bf16_t* x, int64_t x_sstride, 
     return DS_OK;
 }
 
+// a gate and the bucketing of its routes; a single sample is bucketed by the gate's own last launch (every network
+// has DS_MAX_GROUPS groups at most)
+int32_t gate_and_bucket(const GateArgs& g, const BucketArgs& ba, hipStream_t s) {
+    if (g.B == 1) return ds_launch_gate(g, s, &ba);
+    const int32_t rc = ds_launch_gate(g, s);
+    return rc ? rc : ds_launch_bucket_ex(ba, s);
+}
+
 // pointwise / KxK convolution through the grouped GEMM
 int32_t conv_gemm(const bf16_t* A, const int32_t* a_index, int64_t a_sstride, int a_ld, const bf16_t* Wt, int C_I_full,
                   int K, int stride, int pad, int H, int W, const float* scale, const float* shift, int tab_ld,
@@ -248,7 +256,6 @@ int32_t forward_mb(const ds_net* net, const MbDesc& d, const bf16_t* images, int
             g.w1 = (const float*)G[0]; g.b1 = (const float*)G[1]; g.w2 = (const float*)G[2]; g.b2 = (const float*)G[3];
             g.C_mlp = d.gate_hidden; g.T = d.T; g.logit_bias = logit_bias; g.route_override = route_override;
             g.logits = p.gate_logits; g.route = routes_out ? routes_out : p.route; g.partial = p.gate_partial;
-            RC(ds_launch_gate(g, s));
             // one launch: bucket order, the tile lists of the (up to two) resolutions the sliced blocks run at, and
             // the classifier's input width per slot
             BucketArgs ba = {};
@@ -261,7 +268,7 @@ int32_t forward_mb(const ds_net* net, const MbDesc& d, const bf16_t* images, int
             }
             ba.slot_lut = p.slot_c;
             for (int t = 0; t < d.T; ++t) ba.lut[t] = d.cout[t * d.nb + d.nb - 1];
-            RC(ds_launch_bucket_ex(ba, s));
+            RC(gate_and_bucket(g, ba, s));
         }
         GroupTable gdw, gpw;
         memset(&gdw, 0, sizeof(gdw));
@@ -479,7 +486,6 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
             g.x = nullptr; g.logit_bias = nullptr; g.out_index = nullptr;
             g.route_override = routes_out ? routes_out : p.route[0];
         }
-        RC(ds_launch_gate(g, s));
         Q += 4;
         // ---- bucket by (this stage's route, previous stage's route)
         const int32_t* route_prev = st > 0 ? (routes_out ? routes_out + (size_t)(st - 1) * Bs : p.route[st - 1]) : nullptr;
@@ -497,7 +503,7 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
         ba.list_rows[1] = rout * rout; ba.lists[1] = ml_out.list;
         ba.slot_lut = p.slot_c;
         for (int id = 0; id < G; ++id) ba.lut[id] = d.out[st * T + (pairs ? id / T : id)];
-        RC(ds_launch_bucket_ex(ba, s));
+        RC(gate_and_bucket(g, ba, s));
         const int32_t* src = p.src_index;
         // ---- group tables: group id = q * T + q_prev
         GroupTable g1f, gpj, g1, g2, g3;
@@ -804,7 +810,6 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
         g.w1 = (const float*)G[0]; g.b1 = (const float*)G[1]; g.w2 = (const float*)G[2]; g.b2 = (const float*)G[3];
         g.C_mlp = d.gate_hidden; g.partial = p.gate_partial;
     }
-    RC(ds_launch_gate(g, s));
     // one launch: bucket order, the tile lists for the patch rows and the token rows, the embedding width per slot
     MList ml_p = {p.list_p, (int)ds_mtile_capacity(B, np, T), np, B, 1};
     MList ml_t = {p.list_t, (int)ds_mtile_capacity(B, d.N, T), d.N, B, 1};
@@ -816,7 +821,7 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
     ba.list_rows[1] = d.N; ba.lists[1] = ml_t.list;
     ba.slot_lut = p.slot_c;
     for (int t = 0; t < T; ++t) ba.lut[t] = d.routes[d.rs * t];
-    RC(ds_launch_bucket_ex(ba, s));
+    RC(gate_and_bucket(g, ba, s));
     GroupTable ge, gq, gp, g1, g2;
     memset(&ge, 0, sizeof(ge));
     ge.T = T;

@@ -5,10 +5,34 @@
 // valid channels, followed at inference by an argmax over the route scores
 // (Eq. 22).  Bucketing turns the per-sample route ids into a stable bucket-major
 // permutation so that every route group is a contiguous range of slots.
+#include <type_traits>
+
 #include "common.h"
 
 namespace {
 
+// Bucket of a single sample by the wavefront that found its route: what bucket64_kernel writes for B = 1, without a launch of its own.
+// One image, first gate of DS-ResNet: 8.9 + 3.8 us in two launches, 10.2 in one, and a gap between launches less.
+__device__ __forceinline__ void bucket_one(const BucketArgs& a, int route) {
+    const int lane = threadIdx.x & 63;
+    int k = route * a.mul + (a.lo ? a.lo[0] : 0);
+    if (k < 0 || k >= a.T) k = -1;
+    for (int t = lane; t <= a.T; t += 64) a.offsets[t] = k >= 0 && t > k;
+    for (int li = 0; li < a.n_lists; ++li) {
+        const int rows = a.list_rows[li], n = k >= 0 ? (rows + DS_GEMM_BM - 1) / DS_GEMM_BM : 0;
+        int4* entries = (int4*)((char*)a.lists[li] + 16);
+        if (lane == 0) *(int32_t*)a.lists[li] = n;
+        for (int i = lane; i < n; i += 64) entries[i] = make_int4(k, i * DS_GEMM_BM, 0, rows);
+    }
+    if (lane == 0 && k >= 0) {
+        const int src = a.inv_prev ? a.inv_prev[0] : 0;
+        a.perm[0] = 0;
+        if (a.inv_perm) a.inv_perm[0] = 0;
+        if (a.slot_group) a.slot_group[0] = k;
+        if (a.src_index) a.src_index[0] = src;
+        if (a.slot_lut) a.slot_lut[0] = a.lut[k];
+    }
+}
 
 // ---- encoder: partial spatial sums -------------------------------------------
 // NHWC: grid (items, splits); block 256 = 32 channel chunks of 8 x 8 row lanes.
@@ -30,14 +54,17 @@ __device__ __forceinline__ void load8<float>(const float* p, float* v) {
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
 
-// NHWC: grid (items, splits, channel runs of 8 CL), block 256.  The block is shaped to the channel count: CL = 2^lcl lanes
-// (8 channels each) across the channels, 256 / CL rows of the map in flight per step, so narrow maps
-// (24 or 64 channels) keep every lane loading.
+// NHWC: grid (items, splits, channel runs of 8 CL), block 256.  The block is shaped to the item's own channel count: CL = 2^lcl lanes
+// (8 channels each, at most 256 in all) across the channels, 256 / CL rows of the map in flight per step, so narrow maps
+// and slices keep every lane loading.  A share of a map is a chain of loads: 8 of a lane in flight.
+// One image, second gate of DS-ResNet (64 of 256 channels, 56 x 56): 9.2 -> 4.2 us with both.
 template <typename T>
-__global__ __launch_bounds__(256) void pool_nhwc_kernel(const GateArgs a, int splits, int lcl) {
+__global__ __launch_bounds__(256) void pool_nhwc_kernel(const GateArgs a, int splits) {
     __shared__ float red[256 * 16];   // (256 >> lcl) rows of (8 << lcl) + 8 floats
     const int item = blockIdx.x, sp = blockIdx.y;
     const int c = a.c_in ? a.c_in[item] : a.C;
+    int lcl = 0;
+    while ((8 << lcl) < c && lcl < 5) ++lcl;
     const int sample = a.x_index ? a.x_index[item] : item;
     const int ld = a.x_ld > 0 ? a.x_ld : c;
     const T* x = (const T*)a.x + (int64_t)sample * a.x_sample_stride;
@@ -50,17 +77,22 @@ __global__ __launch_bounds__(256) void pool_nhwc_kernel(const GateArgs a, int sp
         const int ch = c0 + lane_c * 8;
         float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
         if (ch < c) {
-            // four rows in flight per lane: the loads are independent, only the adds chain
+            // eight rows in flight per lane, then four: the loads are independent, only the adds chain
             int r = r0 + lane_r;
-            for (; r + 3 * R < r1; r += 4 * R) {
-                float v[4][8];
+            auto rows = [&](auto n) {
+                constexpr int NR = decltype(n)::value;
+                for (; r + (NR - 1) * R < r1; r += NR * R) {
+                    float v[NR][8];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) load8<T>(x + (int64_t)(r + R * k) * ld + ch, v[k]);
+                    for (int k = 0; k < NR; ++k) load8<T>(x + (int64_t)(r + R * k) * ld + ch, v[k]);
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
+                    for (int k = 0; k < NR; ++k)
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) s[i] += v[k][i];
-            }
+                        for (int i = 0; i < 8; ++i) s[i] += v[k][i];
+                }
+            };
+            rows(std::integral_constant<int, 8>{});
+            rows(std::integral_constant<int, 4>{});
             for (; r < r1; r += R) {
                 float v[8];
                 load8<T>(x + (int64_t)r * ld + ch, v);
@@ -106,7 +138,7 @@ __global__ __launch_bounds__(256) void pool_nchw_kernel(const GateArgs a) {
 // outputs (up to 64 per pass) are computed side by side: a group strides over the hidden units and
 // adds its partial sums with a butterfly.  The argmax (NaN never wins, ties go to the lowest index)
 // is a butterfly over (value, index) pairs.
-__global__ __launch_bounds__(64) void gate_out_kernel(const GateArgs a, const float* hidden, int lg) {
+__global__ __launch_bounds__(64) void gate_out_kernel(const GateArgs a, const float* hidden, int lg, const BucketArgs bucket) {
     const int item = blockIdx.x;
     const int out = a.out_index ? a.out_index[item] : item;
     const int lane = threadIdx.x;
@@ -142,7 +174,9 @@ __global__ __launch_bounds__(64) void gate_out_kernel(const GateArgs a, const fl
         const bool oh = __shfl_xor((int)have, o, 64) != 0;
         if (oh && (!have || ob > best || (ob == best && oa < arg))) { best = ob; arg = oa; have = true; }
     }
-    if (lane == 0) a.route[out] = a.route_override ? a.route_override[out] : arg;
+    const int route = a.route_override ? a.route_override[out] : __builtin_amdgcn_readfirstlane(arg);
+    if (lane == 0) a.route[out] = route;
+    if (bucket.B == 1) bucket_one(bucket, route);
 }
 
 // ---- the whole gate of one item in one workgroup ------------------------------------------------
@@ -155,7 +189,7 @@ __global__ __launch_bounds__(64) void gate_out_kernel(const GateArgs a, const fl
 constexpr int GF_NT = 1024, GF_CMAX = 2048, GF_HMAX = 1024;
 
 template <typename T, bool NHWC, bool POOLED>
-__global__ __launch_bounds__(GF_NT) void gate_fused_kernel(const GateArgs a, const int splits, const int lcl) {
+__global__ __launch_bounds__(GF_NT) void gate_fused_kernel(const GateArgs a, const int splits, const int lcl, const BucketArgs bucket) {
     __shared__ __attribute__((aligned(16))) double pooled[GF_CMAX];
     __shared__ float hid[GF_HMAX];
     __shared__ float score[64];
@@ -303,7 +337,9 @@ __global__ __launch_bounds__(GF_NT) void gate_fused_kernel(const GateArgs a, con
             const bool oh = __shfl_xor((int)have, o, 64) != 0;
             if (oh && (!have || ob > best || (ob == best && oa < arg))) { best = ob; arg = oa; have = true; }
         }
-        if (lane == 0) a.route[out] = a.route_override ? a.route_override[out] : arg;
+        const int route = a.route_override ? a.route_override[out] : __builtin_amdgcn_readfirstlane(arg);
+        if (lane == 0) a.route[out] = route;
+        if (bucket.B == 1) bucket_one(bucket, route);
     }
 }
 
@@ -313,7 +349,7 @@ __global__ __launch_bounds__(GF_NT) void gate_fused_kernel(const GateArgs a, con
 // with the same key (stable), so the scatter is parallel over samples.
 // Up to 64 groups (bucket64_kernel) nothing is counted serially: the scans run over the lanes of a wavefront, and a rank is
 // the number of earlier lanes with the same key -- six ballots, one per key bit -- plus the counts of the earlier
-// wavefronts.  16 / 48 groups of 256 samples with two tile lists: 11 / 20 -> 5 to 8 / 5 us; one sample 6 -> 4 us.
+// wavefronts.  16 / 48 groups of 256 samples with two tile lists: 11 / 20 -> 5 to 8 / 5 us; one sample 6 -> 4 us (a forward of one sample: bucket_one).
 __global__ __launch_bounds__(1024) void bucket64_kernel(const BucketArgs a) {
     __shared__ int cnt[16][64];                          // samples per wavefront and key of the current 1024
     __shared__ int base[65], start[65];                  // next free slot of a key; first slot of a key
@@ -607,9 +643,10 @@ int32_t ds_launch_pool(const GateArgs& a, int32_t kind, int32_t* splits_out, hip
         splits = a.HW >= 2048 ? 8 : (a.HW >= 512 ? 4 : (a.HW >= 128 ? 2 : 1));
         int lcl = 0;
         while ((8 << lcl) < a.C && lcl < 5) ++lcl;   // lanes across the channels: 2^lcl * 8 >= C, at most 32
+        // (an item whose slice asks for narrower runs has 256 channels at most: its first run is all of it)
         dim3 grid(a.B, splits, (unsigned)((a.C + (8 << lcl) - 1) / (8 << lcl)));
-        if (a.dtype == DS_BF16) hipLaunchKernelGGL(pool_nhwc_kernel<bf16_t>, grid, dim3(256), 0, s, a, splits, lcl);
-        else hipLaunchKernelGGL(pool_nhwc_kernel<float>, grid, dim3(256), 0, s, a, splits, lcl);
+        if (a.dtype == DS_BF16) hipLaunchKernelGGL(pool_nhwc_kernel<bf16_t>, grid, dim3(256), 0, s, a, splits);
+        else hipLaunchKernelGGL(pool_nhwc_kernel<float>, grid, dim3(256), 0, s, a, splits);
     } else {
         dim3 grid(a.B, (a.C + 3) / 4);
         if (a.dtype == DS_BF16) hipLaunchKernelGGL(pool_nchw_kernel<bf16_t>, grid, dim3(256), 0, s, a);
@@ -621,18 +658,23 @@ int32_t ds_launch_pool(const GateArgs& a, int32_t kind, int32_t* splits_out, hip
 }
 
 namespace {
-int32_t launch_gate_out(const GateArgs& a, const float* hidden, hipStream_t s) {
+int32_t launch_gate_out(const GateArgs& a, const float* hidden, const BucketArgs& bucket, hipStream_t s) {
     ProfScope prof(DS_K_GATE, s);
     int lg = 0;
     while ((1 << lg) < a.T && lg < 6) ++lg;   // 2^lg outputs side by side, 64 >> lg lanes each
-    hipLaunchKernelGGL(gate_out_kernel, dim3(a.B), dim3(64), 0, s, a, hidden, lg);
+    hipLaunchKernelGGL(gate_out_kernel, dim3(a.B), dim3(64), 0, s, a, hidden, lg, bucket);
     DS_CHECK_LAUNCH("gate head");
     return DS_OK;
 }
 }  // namespace
 
-int32_t ds_launch_gate(const GateArgs& a, hipStream_t s) {
+int32_t ds_launch_gate(const GateArgs& a, hipStream_t s, const BucketArgs* bucket_of_one) {
     if (a.B <= 0) return DS_OK;
+    BucketArgs bucket = {};                              // B = 0: none
+    if (bucket_of_one) {
+        if (a.B != 1 || bucket_of_one->B != 1 || bucket_of_one->T > 64) DS_FAIL(DS_EINVAL, "gate: only one sample is bucketed by the gate itself");
+        bucket = *bucket_of_one;
+    }
     float* hidden = nullptr;
     // (16-byte rows of the map: NHWC strides are multiples of 8 channels wherever the entry points let a map in)
     const bool rows16 = a.layout != DS_NHWC || ((a.C % 8) == 0 && (a.x_ld <= 0 || (a.x_ld % 8) == 0) && (a.x_sample_stride % 8) == 0);
@@ -641,7 +683,8 @@ int32_t ds_launch_gate(const GateArgs& a, hipStream_t s) {
         // one compute unit pools up to 512 KiB and 512 channels in less time than a launch costs (9 us with the MLP, against
         // 14 us and two launches more for pool, hidden layer and output layer one after the other; 256 images 20 against
         // 30); above, the pool kernel's several workgroups per item first (second gate of DS-ResNet, 1 / 33 images: 16.3 / 17.0 us
-        // in two launches, 18.8 / 21.8 in one workgroup; 256 images 65 and 57; profiles/dispatch_choices.txt)
+        // in two launches, 18.8 / 21.8 in one workgroup; 256 images 65 and 57; profiles/dispatch_choices.txt; taken before the
+        // pool followed the slice, which has the two launches at 12.4 for 1 image, its bucket included)
         const bool pooled = map_bytes <= (512 << 10) && a.C <= 512;
         int splits = 1;
         if (!pooled) {
@@ -659,15 +702,15 @@ int32_t ds_launch_gate(const GateArgs& a, hipStream_t s) {
             f.out = hid; f.out_ld = a.C_mlp; f.items = a.B;
             const int32_t rc = ds_launch_fc(f, 0, 1, DS_K_GATE, s);
             if (rc) return rc;
-            return launch_gate_out(a, hid, s);
+            return launch_gate_out(a, hid, bucket, s);
         }
         ProfScope prof(DS_K_GATE, s);
         const dim3 grid((unsigned)a.B), block(GF_NT);
-        if (!pooled) hipLaunchKernelGGL((gate_fused_kernel<float, false, false>), grid, block, 0, s, a, splits, lcl);
-        else if (a.layout == DS_NHWC && a.dtype == DS_BF16) hipLaunchKernelGGL((gate_fused_kernel<bf16_t, true, true>), grid, block, 0, s, a, splits, lcl);
-        else if (a.layout == DS_NHWC) hipLaunchKernelGGL((gate_fused_kernel<float, true, true>), grid, block, 0, s, a, splits, lcl);
-        else if (a.dtype == DS_BF16) hipLaunchKernelGGL((gate_fused_kernel<bf16_t, false, true>), grid, block, 0, s, a, splits, lcl);
-        else hipLaunchKernelGGL((gate_fused_kernel<float, false, true>), grid, block, 0, s, a, splits, lcl);
+        if (!pooled) hipLaunchKernelGGL((gate_fused_kernel<float, false, false>), grid, block, 0, s, a, splits, lcl, bucket);
+        else if (a.layout == DS_NHWC && a.dtype == DS_BF16) hipLaunchKernelGGL((gate_fused_kernel<bf16_t, true, true>), grid, block, 0, s, a, splits, lcl, bucket);
+        else if (a.layout == DS_NHWC) hipLaunchKernelGGL((gate_fused_kernel<float, true, true>), grid, block, 0, s, a, splits, lcl, bucket);
+        else if (a.dtype == DS_BF16) hipLaunchKernelGGL((gate_fused_kernel<bf16_t, false, true>), grid, block, 0, s, a, splits, lcl, bucket);
+        else hipLaunchKernelGGL((gate_fused_kernel<float, false, true>), grid, block, 0, s, a, splits, lcl, bucket);
         DS_CHECK_LAUNCH("fused gate");
         return DS_OK;
     }
@@ -684,7 +727,7 @@ int32_t ds_launch_gate(const GateArgs& a, hipStream_t s) {
         rc = ds_launch_fc(f, 0, 1, DS_K_GATE, s);
         if (rc) return rc;
     }
-    return launch_gate_out(a, hidden, s);
+    return launch_gate_out(a, hidden, bucket, s);
 }
 
 int32_t ds_launch_bucket_ex(const BucketArgs& a, hipStream_t s) {
@@ -850,7 +893,7 @@ extern "C" int32_t ds_gate_double(const void* x, int32_t x_dtype, int32_t x_layo
         ProfScope prof(DS_K_GATE, s);
         int lg = 0;
         while ((1 << lg) < T && lg < 6) ++lg;
-        hipLaunchKernelGGL(gate_out_kernel, dim3(B), dim3(64), 0, s, a, (const float*)hidden, lg);
+        hipLaunchKernelGGL(gate_out_kernel, dim3(B), dim3(64), 0, s, a, (const float*)hidden, lg, BucketArgs{});
         DS_CHECK_LAUNCH("gate head");
     }
     // attention head: factor[b][c] = 1 + tanh(W3[c, :] . hidden[b] + b3[c]); rows beyond the

@@ -307,3 +307,25 @@ def test_mbnet_sliced_blocks(gpu_lib, image, B):
         a, b = host(torch.where(n, fused[i], 0)), host(torch.where(n, t, 0))
         assert np.linalg.norm(a - b) < 2.0 ** -7 * np.linalg.norm(b) and relerr_max(a, b) < TOL_BF16, i
     assert relerr_max(host(logits), host(want)) < TOL_BF16
+
+
+# one sample is bucketed by the gate's last launch, two by the bucket kernel: every (route, previous route) pair of DS-ResNet,
+# every route of the others
+@pytest.mark.parametrize("which", ["mbnet", "resnet", "vit"])
+def test_single_sample_bucketed_by_the_gate(gpu_lib, which):
+    arch = getattr(WL, which + "_arch")()
+    net = getattr(gpu_lib, "build_" + which)(arch, getattr(WL, which + "_params")(arch, 29), DEV)
+    T = arch["T"]
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(29)
+    x = torch.randn((1, 3, 224, 224), generator=gen, device=DEV).to(torch.bfloat16)
+    two = x.repeat(2, 1, 1, 1).contiguous()
+    stages = 4 if which == "resnet" else 1
+    for q in range(T):
+        for prev in range(T if which == "resnet" else 1):
+            over = torch.tensor([[q if st % 2 else prev] if stages > 1 else [q] for st in range(stages)], dtype=torch.int32, device=DEV)
+            one, r1 = gpu_lib.ds_forward(net, x, route_override=over)
+            want, r2 = gpu_lib.ds_forward(net, two, route_override=over.repeat(1, 2).contiguous())
+            assert torch.equal(r1.reshape(-1), over.reshape(-1)) and torch.equal(r2.reshape(stages, 2)[:, 0], over[:, 0])
+            # the layers may be other kernels at two samples: the networks' own bound against the oracle
+            assert torch.isfinite(one).all() and relerr_max(host(one), host(want)[:1]) < TOL_BF16, (q, prev)
