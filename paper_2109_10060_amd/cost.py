@@ -68,6 +68,11 @@ def _separable(r, ci, co, s, k, kfull, tiled):
     return k == 3 and kfull == 3 and ci <= 128 and co <= 128 and r % (4 if s == 1 else 2) == 0
 
 
+def _few_separable(r, ci, co, B):
+    """A block in front of the gate (3x3 filters) of so few samples that the kernel of the sliced blocks runs it."""
+    return _sliced_separable(r, ci) and -(-B // 8) * -(-r // (32 // r)) * -(-co // 256) <= 32
+
+
 def _sliced_separable(r, ci):
     """A block behind the gate (3x3 filters) that runs as one kernel: output size, stored channels."""
     return r <= 32 and -(-ci // 64) * 64 <= 2048
@@ -100,7 +105,8 @@ def mbnet_cost(arch, routes) -> Cost:
         kk = arch["ksize"][routes, i].astype(np.float64) ** 2 if "ksize" in arch else 9.0
         cif, cof = int(_ci), int(_co)
         k = int(arch["ksize"][0, i]) if "ksize" in arch else 3
-        if (_separable(r, cif, cof, s, k, arch["kfull"][i] if "ksize" in arch else 3, True) if i < arch["gate_after"]
+        if (_separable(r, cif, cof, s, k, arch["kfull"][i] if "ksize" in arch else 3, True)
+                or "ksize" not in arch and _few_separable(r, cif, cof, B) if i < arch["gate_after"]
                 else "ksize" not in arch and _sliced_separable(r, cif)):
             # a block the library runs as one kernel (depthwise map kept in LDS): counted as one launch
             # of the depthwise class that reads the block's input and writes the pointwise output

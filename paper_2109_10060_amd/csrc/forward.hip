@@ -287,7 +287,16 @@ int32_t forward_mb(const ds_net* net, const MbDesc& d, const bf16_t* images, int
         if (!phase) {
             // an unsliced block: depthwise and pointwise in one kernel where the shape allows, the depthwise map stays on the chip
             int32_t rc = DS_EUNSUPPORTED;
-            if (d.tiled)
+            // Few samples: the kernel of the sliced blocks, whose tiles of 32 pixels and 256 filters are smaller than bandpw's 7 rows
+            // of 16 columns, while no die (every eighth sample; all parts counted) has more of them than its 32 compute units.
+            // DS-MBNet, us a launch, bandpw / here: 28x28, 256 -> 256 one image (8 / 28 workgroups) 9.8 / 7.2, 8 images 12.4 / 10.3;
+            // 56x56 / 2, 128 -> 256 one image 6.9 / 6.0.  A pass of 1 / 5 / 8 images 122.3 / 151.7 / 157.8 -> 119.3 / 149.1 / 155.8;
+            // beyond the line 9 images 162.9 -> 167.9, 12 images 168.5 -> 176.0, 64 images 299 -> 310.
+            if (d.tiled && !d.kfull && r <= 32 && (int64_t)((Bs + 7) / 8) * ((r + 32 / r - 1) / (32 / r)) * ((co + 255) / 256) <= 32)
+                rc = ds_launch_sepconv(ActView{cur, nullptr, (int64_t)rin * rin * ci, ci}, oth, (int64_t)r * r * co, (const bf16_t*)Q[0], (const float*)Q[1],
+                                       (const float*)Q[2], ci, (const bf16_t*)P[3 + 6 * d.nb + 6 + i], (const float*)Q[4], (const float*)Q[5], co,
+                                       nullptr, gpw, B, rin, rin, st, s);
+            if (d.tiled && rc == DS_EUNSUPPORTED)
                 rc = ds_launch_bandpw(cur, B, rin, rin, ci, (const bf16_t*)Q[0], d.kfull ? d.kfull[i] : 3, d.kfull ? d.ksize[i] : 3, st,
                                       (const float*)Q[1], (const float*)Q[2], (const bf16_t*)P[3 + 6 * d.nb + 6 + i], co,
                                       (const float*)Q[4], (const float*)Q[5], oth, s);

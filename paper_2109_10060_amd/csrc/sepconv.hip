@@ -33,7 +33,7 @@ struct SepArgs {
     bf16_t* y;                    // [slot][pixel][k_out]
     const bf16_t *wd, *wp;        // [9][C]; operand tiles
     const float *sd, *hd, *sp, *hp;
-    const int32_t* slot_group;
+    const int32_t* slot_group;    // nullable: one group
     int32_t x_ld, C, F, kb, H, W, Ho, Wo, B, RO, tiles, runs;
     GroupTable gt;
 };
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(64 * NW, 2) void sepconv_kernel(const SepArgs a) {
     bf16_t* y = a.y;
     int64_t x_ss = a.x_ss, y_ss = a.y_ss;
     int x_ld = a.x_ld, C = a.C, F = a.F, kb = a.kb, H = a.H, W = a.W, Ho = a.Ho, Wo = a.Wo, RO = a.RO;
-    const int g = a.slot_group[slot];
+    const int g = a.slot_group ? a.slot_group[slot] : 0;
     const int sample = a.xi ? a.xi[slot] : slot;
     ds_hold(x, wd, wp, sd, hd, sp, hp, y, x_ss, y_ss, x_ld, C, F, kb, H, W, Ho, Wo, RO);
     const int K = lanes.k_in(g), N = lanes.k_out(g), trow = lanes.row(g);

@@ -329,3 +329,33 @@ def test_single_sample_bucketed_by_the_gate(gpu_lib, which):
             assert torch.equal(r1.reshape(-1), over.reshape(-1)) and torch.equal(r2.reshape(stages, 2)[:, 0], over[:, 0])
             # the layers may be other kernels at two samples: the networks' own bound against the oracle
             assert torch.isfinite(one).all() and relerr_max(host(one), host(want)[:1]) < TOL_BF16, (q, prev)
+
+
+# blocks in front of the gate with few samples (tiles of the sliced blocks' kernel) against the kernels of larger batches: both sides
+# of the line at 224 (8 and 9 samples), maps of a few pixels, odd maps
+@pytest.mark.parametrize("image,B", [(224, 1), (224, 8), (224, 9), (150, 3), (34, 2), (17, 5)])
+def test_mbnet_unsliced_blocks_few_samples(gpu_lib, image, B):
+    arch = WL.mbnet_arch(image=image)
+    net = gpu_lib.build_mbnet(arch, WL.mbnet_params(arch, 17), DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(image + B)
+    few = torch.randn((B, 3, image, image), generator=gen, device=DEV).to(torch.bfloat16)
+    # the line is at 32 tiles for every eighth sample: a map of one tile crosses it with 257 samples
+    many = few.repeat(-(-300 // B), 1, 1, 1).contiguous()
+
+    def run(x):
+        over = (torch.arange(len(x), device=DEV, dtype=torch.int32) % B % arch["T"])[None].contiguous()
+        r, taps = (image + 1) // 2, {}
+        for i, (_, co, s) in enumerate(arch["blocks"][:arch["gate_after"]]):
+            r = (r - 1) // s + 1
+            taps[i] = torch.full((len(x), r * r, co), float("nan"), dtype=torch.bfloat16, device=DEV)
+        return taps, gpu_lib.ds_forward_taps(net, x, taps, route_override=over)[0]
+
+    got, logits = run(few)
+    ref, want = run(many)
+    for i, t in got.items():
+        # two roundings a block may go the other way, 2^-9 of an element each: 2^-9 sqrt(10) together in the 2-norm at the most
+        assert torch.isfinite(t).all() and t.abs().max() > 0
+        a, b = host(t), host(ref[i][:B])
+        assert np.linalg.norm(a - b) < 2.0 ** -9 * 10 ** 0.5 * np.linalg.norm(b) and relerr_max(a, b) < TOL_BF16, i
+    assert relerr_max(host(logits), host(want)[:B]) < TOL_BF16
