@@ -281,16 +281,18 @@ int32_t launch(SepArgs& a, int kmax, int groups, hipStream_t s) {
 //                        64 images 26.9 / 18.2 / 16.6 / 22.8, 128 images 47.6 / 35.6 / 26.5 / 26.0, 256 images 89 / 61 / 48 / 40
 //   7x7, 1024 -> 1024    24 images 13.2 / 17.5 / 23.0, 48 images 18.3 / 17.8 / 23.4, 64 images 21.4 / 18.4 / 23.5, 128 images 40.5 / 31.2 / 27.3
 // so the smaller tile ends where its workgroups are one for every compute unit (a third more where only the tile grows), and 64
-// pixels end at two.
+// pixels end at two.  Counted on the die that has the most, as a sample stays on one: of 17 samples it has three.  Against the same
+// lines on the whole chip: 17 / 18 images 196.9 / 199.4 -> 191.8 / 192.9 us a pass, 9 to 256 others the same.
 template <int STRIDE>
 int32_t dispatch(SepArgs& a, int kmax, int groups, hipStream_t s) {
-    auto tiles = [&](int rf) { return (int64_t)a.B * ((a.Ho + rf * 16 / a.Wo - 1) / (rf * 16 / a.Wo)); };
+    // on the die with the most samples (32 compute units)
+    auto tiles = [&](int rf) { return (int64_t)((a.B + 7) / 8) * ((a.Ho + rf * 16 / a.Wo - 1) / (rf * 16 / a.Wo)); };
     const int64_t t2 = tiles(2);
     const int r16 = (groups + 15) / 16;
-    if (t2 * ((groups + 7) / 8) > 256) {
+    if (t2 * ((groups + 7) / 8) > 32) {
         int32_t rc = DS_EUNSUPPORTED;
-        if (t2 * r16 > 340) {
-            if (tiles(4) > 512 && a.Ho * a.Wo > 64) rc = launch<STRIDE, 7, 2>(a, kmax, groups, s);
+        if (t2 * r16 > 42) {
+            if (tiles(4) > 64 && a.Ho * a.Wo > 64) rc = launch<STRIDE, 7, 2>(a, kmax, groups, s);
             if (rc == DS_EUNSUPPORTED) rc = launch<STRIDE, 4, 2>(a, kmax, groups, s);
         }
         if (rc == DS_EUNSUPPORTED) rc = launch<STRIDE, 2, 2>(a, kmax, groups, s);
