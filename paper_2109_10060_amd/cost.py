@@ -56,6 +56,13 @@ def _few_samples(B, rows, groups, n):
     return _tiles(B, rows, groups, 32) * -(-n // 32) <= 1000
 
 
+def _paired(ta, tb, nk):
+    """Two 1x1 layers of ta and tb 32 x 32 tiles and nk 64-deep slabs that run as one launch: the same kernel variant alone."""
+    choice = lambda t: 0 if t <= 340 and nk > 2 else 1 if 340 < t <= 500 and nk >= 5 else 2 if t <= 700 else 3 if nk >= 24 else 4 if nk > 4 else 5  # noqa: E731
+    big = choice(max(ta, tb))
+    return ta + tb <= 1000 and big != 3 and (nk <= 1 or choice(ta) == choice(tb))
+
+
 def _separable(r, ci, co, s, k, kfull, tiled):
     """An unsliced depthwise + pointwise block that runs as one kernel: output size, channels, stride, filter size."""
     if ci % 8 or co % 8:
@@ -163,7 +170,11 @@ def resnet_cost(arch, routes) -> Cost:
             m, o = mid * on, out * on
             if b == 0:
                 _gemm(c, "gemm", ro * ro, ro * ro, 1, cin, o, name=f"s{s}.b{b}.proj")      # 1x1 projection reads only the strided pixels
-            _gemm(c, "gemm", r * r, r * r, 1, cin, m, chained=chain and b > 0, name=f"s{s}.b{b}.c1")
+            # few samples: the first layer of a stage is one launch with the projection
+            paired = b == 0 and _paired(_tiles(B, ro * ro, groups, 32) * -(-int(outs.max()) // 32),
+                                        _tiles(B, r * r, groups, 32) * -(-int(mids.max()) // 32),
+                                        -(-int(arch["out"][s - 1].max() if s else so) // 64))
+            _gemm(c, "gemm", r * r, r * r, 1, cin, m, chained=chain and b > 0 or paired, name=f"s{s}.b{b}.c1")
             _gemm(c, "gemm_taps", r * r, ro * ro, 9, m, m, name=f"s{s}.b{b}.c2 3x3" + ("/2" if stride == 2 else ""))
             _gemm(c, "gemm", ro * ro, ro * ro, 1, m, o, residual=True, name=f"s{s}.b{b}.c3+res")
             r = ro

@@ -181,6 +181,9 @@ struct ThinChain {
 int32_t ds_launch_thin_chain(const GemmArgs& a, const ThinChain& ch, int32_t max_mtiles, int32_t max_kout, hipStream_t s);
 // launches too small for 128-row tiles: short tiles and a reduction dealt to several wavefronts; DS_EUNSUPPORTED otherwise
 int32_t ds_launch_gemm_small(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s);
+// two 1x1 layers of a few samples as one launch; neither reads what the other writes
+int32_t ds_launch_gemm_small_pair(const GemmArgs& a, int32_t mtiles_a, int32_t kout_a, const GemmArgs& b, int32_t mtiles_b, int32_t kout_b,
+                                  hipStream_t s);
 // 3x3 stride-1 padding-1 layers on maps up to 59 pixels wide; DS_EUNSUPPORTED for any other shape
 int32_t ds_launch_conv3(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s);
 

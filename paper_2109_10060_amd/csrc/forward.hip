@@ -110,10 +110,10 @@ int32_t gate_and_bucket(const GateArgs& g, const BucketArgs& ba, hipStream_t s) 
 }
 
 // pointwise / KxK convolution through the grouped GEMM
-int32_t conv_gemm(const bf16_t* A, const int32_t* a_index, int64_t a_sstride, int a_ld, const bf16_t* Wt, int C_I_full,
-                  int K, int stride, int pad, int H, int W, const float* scale, const float* shift, int tab_ld,
-                  const bf16_t* R, bf16_t* C, int64_t c_sstride, int c_ld, const int32_t* offsets, const MList& ml,
-                  const GroupTable& gt, int act, hipStream_t s, const ThinChain* chain = nullptr, bool* chained = nullptr) {
+GemmArgs conv_args(const bf16_t* A, const int32_t* a_index, int64_t a_sstride, int a_ld, const bf16_t* Wt, int C_I_full,
+                   int K, int stride, int pad, int H, int W, const float* scale, const float* shift, int tab_ld,
+                   const bf16_t* R, bf16_t* C, int64_t c_sstride, int c_ld, const int32_t* offsets, const MList& ml,
+                   const GroupTable& gt, int act) {
     GemmArgs a;
     memset(&a, 0, sizeof(a));
     const int Ho = (H + 2 * pad - K) / stride + 1, Wo = (W + 2 * pad - K) / stride + 1;
@@ -127,6 +127,11 @@ int32_t conv_gemm(const bf16_t* A, const int32_t* a_index, int64_t a_sstride, in
     a.offsets = offsets; a.mtiles = ml.list ? ds_mtile_entries(ml.list) : nullptr;
     a.n_mtiles = ml.list ? ds_mtile_count(ml.list) : nullptr;
     a.act = act; a.out_f32 = 0; a.gt = gt; a.B = ml.B; a.crowd = ml.crowd;
+    return a;
+}
+
+int32_t launch_conv(const GemmArgs& a, const MList& ml, hipStream_t s, const ThinChain* chain = nullptr, bool* chained = nullptr) {
+    const GroupTable& gt = a.gt;
     {
         const int32_t rc = ds_launch_gemm_small(a, ml.cap, max_out(gt), s);
         if (rc != DS_EUNSUPPORTED) return rc;
@@ -143,6 +148,14 @@ int32_t conv_gemm(const bf16_t* A, const int32_t* a_index, int64_t a_sstride, in
         if (rc != DS_EUNSUPPORTED) return rc;
     }
     return ds_launch_gemm(a, ml.cap, max_out(gt), s);
+}
+
+int32_t conv_gemm(const bf16_t* A, const int32_t* a_index, int64_t a_sstride, int a_ld, const bf16_t* Wt, int C_I_full,
+                  int K, int stride, int pad, int H, int W, const float* scale, const float* shift, int tab_ld,
+                  const bf16_t* R, bf16_t* C, int64_t c_sstride, int c_ld, const int32_t* offsets, const MList& ml,
+                  const GroupTable& gt, int act, hipStream_t s, const ThinChain* chain = nullptr, bool* chained = nullptr) {
+    return launch_conv(conv_args(A, a_index, a_sstride, a_ld, Wt, C_I_full, K, stride, pad, H, W, scale, shift, tab_ld, R, C, c_sstride,
+                                 c_ld, offsets, ml, gt, act), ml, s, chain, chained);
 }
 
 // =====================================================================================
@@ -562,9 +575,17 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
             const int in_full = first ? c_prev_full : 4 * w;
             const bf16_t* shortcut;
             if (first) {
-                RC(conv_gemm(in, in_idx, in_ss, 0, (const bf16_t*)L[9], in_full, 1, bs, 0, rb, rb, (const float*)L[10],
-                             (const float*)L[11], 4 * w, nullptr, Pj, (int64_t)rout * rout * 4 * w, 0, p.offs[st], ml_out,
-                             gpj, DS_ACT_NONE, s));
+                const GemmArgs pj = conv_args(in, in_idx, in_ss, 0, (const bf16_t*)L[9], in_full, 1, bs, 0, rb, rb, (const float*)L[10],
+                                              (const float*)L[11], 4 * w, nullptr, Pj, (int64_t)rout * rout * 4 * w, 0, p.offs[st],
+                                              ml_out, gpj, DS_ACT_NONE);
+                // few samples: both layers that read the stage's input as one launch
+                const GemmArgs c1 = conv_args(in, in_idx, in_ss, 0, (const bf16_t*)L[0], in_full, 1, 1, 0, rb, rb, (const float*)L[1],
+                                              (const float*)L[2], w, nullptr, Y1, (int64_t)rb * rb * w, 0, p.offs[st], ml_in, g1f,
+                                              DS_ACT_RELU);
+                const int32_t rc = ds_launch_gemm_small_pair(pj, ml_out.cap, max_out(gpj), c1, ml_in.cap, max_out(g1f), s);
+                if (rc != DS_OK && rc != DS_EUNSUPPORTED) return rc;
+                y1_ready = rc == DS_OK;
+                if (!y1_ready) RC(launch_conv(pj, ml_out, s));
                 shortcut = Pj;
             } else {
                 shortcut = Z;

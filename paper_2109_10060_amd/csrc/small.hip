@@ -28,7 +28,7 @@ __device__ __forceinline__ int key(int r) { return (r ^ (r >> 3)) & 7; }
 
 // NW wavefronts: KS shares of the reduction x NW / KS column tiles
 template <int WM, int WN, int NW, int KS, int PD, bool CONV, bool HASR>
-__global__ __launch_bounds__(64 * NW) void gemm_small_kernel(const GemmArgs a) {
+__device__ __forceinline__ void small_tile(const GemmArgs& a, char* smem, int y, const int mi) {
     constexpr int BM = WM * 32, WBN = WN * 32, NC = NW / KS, BN = NC * WBN, BK = 64;
     constexpr int NSUB = DS_GEMM_BM / BM;
     constexpr int NA = BM / 8, NB = WBN / 8;                  // 16-byte loads of a lane per slab
@@ -36,10 +36,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(const GemmArgs a) {
     constexpr int ST_LD = WBN + 4;                            // staging: one fp32 tile per wavefront
     constexpr int STAGE_BYTES = BM * ST_LD * 4;
     constexpr int PER_WAVE = WAVE_BYTES > STAGE_BYTES ? WAVE_BYTES : STAGE_BYTES;
-    extern __shared__ __attribute__((aligned(16))) char smem[];
 
-    int y = (int)blockIdx.x;
-    const int mi = (int)blockIdx.y;
     const int mt = mi / NSUB, sub = mi - mt * NSUB;
     const GroupLanes lanes(a.gt);
     const bf16_t *A = a.A, *Wt = a.Wt, *R = a.R;
@@ -290,10 +287,52 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(const GemmArgs a) {
 }
 
 template <int WM, int WN, int NW, int KS, int PD, bool CONV, bool HASR>
+__global__ __launch_bounds__(64 * NW) void gemm_small_kernel(const GemmArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    small_tile<WM, WN, NW, KS, PD, CONV, HASR>(a, smem, (int)blockIdx.x, (int)blockIdx.y);
+}
+
+// two launches that do not wait for one another as one: the workgroups [0, split) are those of p[0], the others those of p[1], each
+// with its own number of column tiles (on a grid as wide as the wider one, the workgroups that only end cost more than the launch:
+// one image of DS-ResNet 371 -> 385 us a pass)
+struct SmallPair {
+    GemmArgs p[2];
+    int32_t split, ny[2];
+};
+
+template <int WM, int WN, int NW, int KS, int PD, bool CONV>
+__global__ __launch_bounds__(64 * NW) void gemm_small_pair_kernel(const SmallPair a) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const unsigned second = (int)blockIdx.x >= a.split, i = blockIdx.x - (second ? a.split : 0), ny = second ? a.ny[1] : a.ny[0], mi = i / ny;
+    small_tile<WM, WN, NW, KS, PD, CONV, false>(a.p[second], smem, (int)(i - mi * ny), (int)mi);
+}
+
+template <int WM, int WN, int NW, int KS>
+struct SmallTile {
+    static constexpr int BM = WM * 32, WBN = WN * 32, BN = (NW / KS) * WBN;
+    static constexpr int W1 = (BM + WBN) * 128, W2 = BM * (WBN + 4) * 4;
+    static constexpr int SMEM = NW * (W1 > W2 ? W1 : W2);
+};
+
+template <int WM, int WN, int NW, int KS, int PD, bool CONV>
+int32_t launch_pair(SmallPair& a, int32_t tiles0, int32_t kout0, int32_t tiles1, int32_t kout1, hipStream_t s) {
+    using K = SmallTile<WM, WN, NW, KS>;
+    auto kern = gemm_small_pair_kernel<WM, WN, NW, KS, PD, CONV>;
+    const int32_t rc = ds_reserve_lds((const void*)kern, K::SMEM, "pair of small sliced gemms");
+    if (rc) return rc;
+    a.ny[0] = (kout0 + K::BN - 1) / K::BN;
+    a.ny[1] = (kout1 + K::BN - 1) / K::BN;
+    a.split = tiles0 * (DS_GEMM_BM / K::BM) * a.ny[0];
+    ProfScope prof(DS_K_SMALL, s);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.split + tiles1 * (DS_GEMM_BM / K::BM) * a.ny[1])), dim3(64 * NW), K::SMEM, s, a);
+    DS_CHECK_LAUNCH("pair of small sliced gemms");
+    return DS_OK;
+}
+
+template <int WM, int WN, int NW, int KS, int PD, bool CONV, bool HASR>
 int32_t launch(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
-    constexpr int BM = WM * 32, WBN = WN * 32, BN = (NW / KS) * WBN;
-    constexpr int W1 = (BM + WBN) * 128, W2 = BM * (WBN + 4) * 4;
-    constexpr int SMEM = NW * (W1 > W2 ? W1 : W2);
+    using K = SmallTile<WM, WN, NW, KS>;
+    constexpr int BM = K::BM, BN = K::BN, SMEM = K::SMEM;
     auto kern = gemm_small_kernel<WM, WN, NW, KS, PD, CONV, HASR>;
     const int32_t rc = ds_reserve_lds((const void*)kern, SMEM, "small sliced gemm");
     if (rc) return rc;
@@ -302,6 +341,35 @@ int32_t launch(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStrea
     hipLaunchKernelGGL(kern, dim3((unsigned)ny, (unsigned)(max_mtiles * (DS_GEMM_BM / BM))), dim3(64 * NW), SMEM, s, a);
     DS_CHECK_LAUNCH("small sliced gemm");
     return DS_OK;
+}
+
+// 32 x 32 tiles a launch can have and 64-deep slabs of its reduction
+struct SmallSize {
+    int kmax, taps, nk;
+    long long t;
+};
+SmallSize small_size(const GemmArgs& a, int32_t max_kout) {
+    SmallSize z;
+    z.kmax = 0;
+    for (int t = 0; t < a.gt.T; ++t) z.kmax = a.gt.k_in[t] > z.kmax ? a.gt.k_in[t] : z.kmax;
+    z.taps = a.K * (a.Kw > 0 ? a.Kw : a.K);
+    z.nk = z.taps * ((z.kmax + 63) / 64);
+    const long long groups = a.B < a.gt.T ? a.B : a.gt.T, rows = (long long)a.B * a.rows;
+    z.t = ((rows - groups) / 32 + groups) * a.n_seg * ((max_kout + 31) / 32);
+    return z;
+}
+int small_choice(long long t, int nk) {
+    if (t <= 340 && nk > 2) return 0;
+    if (t > 340 && t <= 500 && nk >= 5) return 1;
+    if (t <= 700) return 2;
+    return nk >= 24 ? 3 : nk > 4 ? 4 : 5;
+}
+// 32-bit byte offsets inside the kernel
+bool small_in_reach(const GemmArgs& a, const SmallSize& z, int32_t max_mtiles, int32_t max_kout) {
+    const long long slots = (long long)max_mtiles * DS_GEMM_BM / (a.rows > 0 ? a.rows : 1) + 1;
+    const long long corner = (long long)a.pad * (a.W + 1) * (a.a_ld > z.kmax ? a.a_ld : z.kmax);
+    if ((slots * a.a_sample_stride + corner) * 2 >= 0x7fffffffLL) return false;
+    return ((long long)a.n_seg * a.w_seg_stride + (long long)max_kout * a.w_ld + z.taps * a.w_tap_stride + z.kmax) * 2 < 0x7fffffffLL;
 }
 
 }  // namespace
@@ -325,31 +393,55 @@ int32_t ds_launch_gemm_small(const GemmArgs& a, int32_t max_mtiles, int32_t max_
     if (max_mtiles <= 0 || max_kout <= 0 || a.B <= 0) return DS_EUNSUPPORTED;
     if (a.K > 15 || a.Kw > 15) return DS_EUNSUPPORTED;        // tap masks of 16 bits
     const bool conv = a.K > 1 || a.stride > 1 || a.pad > 0;
-    const int taps = a.K * (a.Kw > 0 ? a.Kw : a.K);
-    int kmax = 0;
-    for (int t = 0; t < a.gt.T; ++t) kmax = a.gt.k_in[t] > kmax ? a.gt.k_in[t] : kmax;
-    const int nk = taps * ((kmax + 63) / 64);
-    const long long groups = a.B < a.gt.T ? a.B : a.gt.T, rows = (long long)a.B * a.rows;
-    const long long t = ((rows - groups) / 32 + groups) * a.n_seg * ((max_kout + 31) / 32);
-    const bool strided = taps > 1 && a.stride > 1;
+    const SmallSize z = small_size(a, max_kout);
+    const int nk = z.nk;
+    const long long t = z.t;
+    const bool strided = z.taps > 1 && a.stride > 1;
     if (t > 1700 || (t > 1000 && !a.ordered && !(strided && nk >= 24))) return DS_EUNSUPPORTED;
-    // 32-bit byte offsets inside the kernel
-    const long long slots = (long long)max_mtiles * DS_GEMM_BM / (a.rows > 0 ? a.rows : 1) + 1;
-    const long long corner = (long long)a.pad * (a.W + 1) * (a.a_ld > kmax ? a.a_ld : kmax);
-    if ((slots * a.a_sample_stride + corner) * 2 >= 0x7fffffffLL) return DS_EUNSUPPORTED;
-    if (((long long)a.n_seg * a.w_seg_stride + (long long)max_kout * a.w_ld + taps * a.w_tap_stride + kmax) * 2 >= 0x7fffffffLL)
-        return DS_EUNSUPPORTED;
+    if (!small_in_reach(a, z, max_mtiles, max_kout)) return DS_EUNSUPPORTED;
 #define DS_SMALL(...)                                                                       \
     (conv ? (a.R ? launch<__VA_ARGS__, true, true>(a, max_mtiles, max_kout, s)               \
                  : launch<__VA_ARGS__, true, false>(a, max_mtiles, max_kout, s))             \
           : (a.R ? launch<__VA_ARGS__, false, true>(a, max_mtiles, max_kout, s)              \
                  : launch<__VA_ARGS__, false, false>(a, max_mtiles, max_kout, s)))
     if (a.ordered) return DS_SMALL(1, 1, 2, 1, 3);
-    if (t <= 340 && nk > 2) return DS_SMALL(1, 1, 8, 8, 4);
-    if (t > 340 && t <= 500 && nk >= 5) return DS_SMALL(1, 2, 8, 8, 2);
-    if (t <= 700) return DS_SMALL(1, 1, 4, 4, 4);
-    if (nk >= 24) return DS_SMALL(2, 2, 8, 8, 1);
-    if (nk > 4) return DS_SMALL(1, 2, 4, 4, 2);
-    return DS_SMALL(1, 1, 4, 2, 4);
+    switch (small_choice(t, nk)) {
+        case 0: return DS_SMALL(1, 1, 8, 8, 4);
+        case 1: return DS_SMALL(1, 2, 8, 8, 2);
+        case 2: return DS_SMALL(1, 1, 4, 4, 4);
+        case 3: return DS_SMALL(2, 2, 8, 8, 1);
+        case 4: return DS_SMALL(1, 2, 4, 4, 2);
+        default: return DS_SMALL(1, 1, 4, 2, 4);
+    }
 #undef DS_SMALL
+}
+
+// A stage's projection and first layer both read its input and one waits for neither; with a few samples each is mostly the 4 to 6 us
+// of a launch that has one before it.  Paired where the two have as many tiles together as one launch here may have.  DS-ResNet,
+// two launches -> here: 1 image 370 -> 362 us a pass, 2 / 4 / 8 images 437.6 / 509.5 / 596.7 -> 436.5 / 507.8 / 594.1 (fewer stages
+// pair); DS-ResNet++ 1 image 311 -> 299.5.
+int32_t ds_launch_gemm_small_pair(const GemmArgs& a, int32_t mtiles_a, int32_t kout_a, const GemmArgs& b, int32_t mtiles_b, int32_t kout_b,
+                                  hipStream_t s) {
+    if (mtiles_a <= 0 || mtiles_b <= 0 || kout_a <= 0 || kout_b <= 0 || a.B <= 0 || b.B <= 0) return DS_EUNSUPPORTED;
+    // 1x1 layers without residual and segments
+    for (const GemmArgs* p : {&a, &b})
+        if (p->K != 1 || p->Kw > 1 || p->pad || p->R || p->ordered || p->n_seg != 1) return DS_EUNSUPPORTED;
+    const SmallSize za = small_size(a, kout_a), zb = small_size(b, kout_b);
+    if (za.t + zb.t > 1000 || !small_in_reach(a, za, mtiles_a, kout_a) || !small_in_reach(b, zb, mtiles_b, kout_b)) return DS_EUNSUPPORTED;
+    SmallPair p;
+    p.p[0] = a; p.p[1] = b;
+    const bool conv = a.stride > 1 || b.stride > 1;
+    // The tile that either layer takes alone, so that pairing changes no sum; one slab is summed the same way in every tile.
+    const int ca = small_choice(za.t, za.nk), cb = small_choice(zb.t, zb.nk);
+    if (ca != cb && (za.nk > 1 || zb.nk > 1)) return DS_EUNSUPPORTED;
+#define DS_PAIR(...) (conv ? launch_pair<__VA_ARGS__, true>(p, mtiles_a, kout_a, mtiles_b, kout_b, s) : launch_pair<__VA_ARGS__, false>(p, mtiles_a, kout_a, mtiles_b, kout_b, s))
+    switch (za.t > zb.t ? ca : cb) {
+        case 0: return DS_PAIR(1, 1, 8, 8, 4);
+        case 1: return DS_PAIR(1, 2, 8, 8, 2);
+        case 2: return DS_PAIR(1, 1, 4, 4, 4);
+        case 4: return DS_PAIR(1, 2, 4, 4, 2);
+        case 5: return DS_PAIR(1, 1, 4, 2, 4);
+        default: return DS_EUNSUPPORTED;
+    }
+#undef DS_PAIR
 }

@@ -359,3 +359,35 @@ def test_mbnet_unsliced_blocks_few_samples(gpu_lib, image, B):
         a, b = host(t), host(ref[i][:B])
         assert np.linalg.norm(a - b) < 2.0 ** -9 * 10 ** 0.5 * np.linalg.norm(b) and relerr_max(a, b) < TOL_BF16, i
     assert relerr_max(host(logits), host(want)[:B]) < TOL_BF16
+
+
+# a stage's projection and first layer in one launch (few samples) against the two launches of a large batch: every kernel variant
+# that pairs, stages on either side of the line, odd maps and maps of a few pixels
+@pytest.mark.parametrize("image,B", [(224, 1), (224, 2), (224, 4), (150, 3), (34, 1), (34, 7)])
+def test_resnet_paired_layers(gpu_lib, image, B):
+    arch = WL.resnet_arch(image=image)
+    net = gpu_lib.build_resnet(arch, WL.resnet_params(arch, 23), DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(image + B)
+    few = torch.randn((B, 3, image, image), generator=gen, device=DEV).to(torch.bfloat16)
+    many = few.repeat(-(-64 // B), 1, 1, 1).contiguous()
+
+    def run(x):
+        n = torch.arange(len(x), device=DEV, dtype=torch.int32) % B
+        over = torch.stack([(n + st) % arch["T"] for st in range(4)]).contiguous()
+        r, taps, block = ((image + 1) // 2 + 1) // 2, {}, 0
+        for st, nb in enumerate(arch["blocks"]):
+            r = r if st == 0 else (r - 1) // 2 + 1
+            taps[block] = torch.full((len(x), r * r, int(arch["out"][st].max())), float("nan"), dtype=torch.bfloat16, device=DEV)
+            block += nb
+        return taps, gpu_lib.ds_forward_taps(net, x, taps, route_override=over)[0]
+
+    got, logits = run(few)
+    ref, want = run(many)
+    for i, t in got.items():
+        # up to 4 roundings a block before it may go the other way: 2^-9 sqrt(4 (i + 1)) in the 2-norm if all of them did
+        n = torch.isfinite(t)
+        assert torch.equal(n, torch.isfinite(ref[i][:B])) and t[n].abs().max() > 0      # written on the slices alone
+        a, b = host(torch.where(n, t, 0)), host(torch.where(n, ref[i][:B], 0))
+        assert np.linalg.norm(a - b) < 2.0 ** -9 * (4 * (i + 1)) ** 0.5 * np.linalg.norm(b) and relerr_max(a, b) < TOL_BF16, i
+    assert relerr_max(host(logits), host(want)[:B]) < TOL_BF16
