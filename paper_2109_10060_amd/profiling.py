@@ -33,10 +33,11 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 KERNEL_SOURCES = ["csrc/gemm.hip", "csrc/conv3.hip", "csrc/thin.hip", "csrc/small.hip", "csrc/vit_linear.hip", "csrc/vit_tail.hip",
                   "csrc/vit_rows.h", "csrc/gelu.h", "csrc/gelu_poly.h", "csrc/common.h"]
 # the grouped GEMM is several kernels: gemm_kernel (linear, 1x1, strided and KxK layers), conv3_kernel (3x3 stride-1
-# layers), thin_kernel (1x1 layers with at most 64 / 128 input channels), gemm_small_kernel (launches of a few samples),
-# vit_linear_kernel and vit_tail_kernel (transformer blocks on weights in operand order); the summaries treat them as one
-# kernel class, as bench.py does
-GEMM_KERNELS = ("gemm_kernel", "conv3_kernel", "thin_kernel", "gemm_small_kernel", "vit_linear_kernel", "vit_tail_kernel")
+# layers), thin_kernel (1x1 layers with at most 64 / 128 input channels), gemm_small_kernel and gemm_small_pair_kernel (launches
+# of a few samples), vit_linear_kernel and vit_tail_kernel (transformer blocks on weights in operand order); the summaries treat
+# them as one kernel class, as bench.py does
+GEMM_KERNELS = ("gemm_kernel", "conv3_kernel", "thin_kernel", "gemm_small_kernel", "gemm_small_pair_kernel", "vit_linear_kernel",
+                "vit_tail_kernel")
 
 
 def kernel_source_hash() -> str:
@@ -127,6 +128,8 @@ def layers(trace_csv, layers_json, out_path, title, command):
         n = len(idx)
         if not got or len(got) < n or cls in ("gate", "head", "index"):
             continue
+        if len(got) % n:
+            raise SystemExit(f"{cls}: {len(got)} launches are no whole number of passes of {n}: a kernel without a class?")
         passes = min(len(got) // n, 8)           # the last passes of the run: warm, and aligned to the end of the trace
         tail = got[len(got) - passes * n:]
         for k, i in enumerate(idx):
