@@ -33,6 +33,9 @@ __device__ __forceinline__ void bucket_one(const BucketArgs& a, int route) {
         if (a.slot_lut) a.slot_lut[0] = a.lut[k];
     }
 }
+// Every other gate, ds_gate's among them: no bucket, and none of its 376 bytes among the launch's arguments.
+struct NoBucket {};
+__device__ __forceinline__ void bucket_one(const NoBucket&, int) {}
 
 // ---- encoder: partial spatial sums -------------------------------------------
 // NHWC: grid (items, splits); block 256 = 32 channel chunks of 8 x 8 row lanes.
@@ -138,7 +141,8 @@ __global__ __launch_bounds__(256) void pool_nchw_kernel(const GateArgs a) {
 // outputs (up to 64 per pass) are computed side by side: a group strides over the hidden units and
 // adds its partial sums with a butterfly.  The argmax (NaN never wins, ties go to the lowest index)
 // is a butterfly over (value, index) pairs.
-__global__ __launch_bounds__(64) void gate_out_kernel(const GateArgs a, const float* hidden, int lg, const BucketArgs bucket) {
+template <typename Bucket>
+__global__ __launch_bounds__(64) void gate_out_kernel(const GateArgs a, const float* hidden, int lg, const Bucket bucket) {
     const int item = blockIdx.x;
     const int out = a.out_index ? a.out_index[item] : item;
     const int lane = threadIdx.x;
@@ -176,7 +180,7 @@ __global__ __launch_bounds__(64) void gate_out_kernel(const GateArgs a, const fl
     }
     const int route = a.route_override ? a.route_override[out] : __builtin_amdgcn_readfirstlane(arg);
     if (lane == 0) a.route[out] = route;
-    if (bucket.B == 1) bucket_one(bucket, route);
+    bucket_one(bucket, route);
 }
 
 // ---- the whole gate of one item in one workgroup ------------------------------------------------
@@ -188,8 +192,8 @@ __global__ __launch_bounds__(64) void gate_out_kernel(const GateArgs a, const fl
 // a pass read whole lines; sums are fp64 in a fixed order.
 constexpr int GF_NT = 1024, GF_CMAX = 2048, GF_HMAX = 1024;
 
-template <typename T, bool NHWC, bool POOLED>
-__global__ __launch_bounds__(GF_NT) void gate_fused_kernel(const GateArgs a, const int splits, const int lcl, const BucketArgs bucket) {
+template <typename T, bool NHWC, bool POOLED, typename Bucket>
+__global__ __launch_bounds__(GF_NT) void gate_fused_kernel(const GateArgs a, const int splits, const int lcl, const Bucket bucket) {
     __shared__ __attribute__((aligned(16))) double pooled[GF_CMAX];
     __shared__ float hid[GF_HMAX];
     __shared__ float score[64];
@@ -339,7 +343,7 @@ __global__ __launch_bounds__(GF_NT) void gate_fused_kernel(const GateArgs a, con
         }
         const int route = a.route_override ? a.route_override[out] : __builtin_amdgcn_readfirstlane(arg);
         if (lane == 0) a.route[out] = route;
-        if (bucket.B == 1) bucket_one(bucket, route);
+        bucket_one(bucket, route);
     }
 }
 
@@ -658,23 +662,18 @@ int32_t ds_launch_pool(const GateArgs& a, int32_t kind, int32_t* splits_out, hip
 }
 
 namespace {
-int32_t launch_gate_out(const GateArgs& a, const float* hidden, const BucketArgs& bucket, hipStream_t s) {
+template <typename Bucket>
+int32_t launch_gate_out(const GateArgs& a, const float* hidden, const Bucket& bucket, hipStream_t s) {
     ProfScope prof(DS_K_GATE, s);
     int lg = 0;
     while ((1 << lg) < a.T && lg < 6) ++lg;   // 2^lg outputs side by side, 64 >> lg lanes each
-    hipLaunchKernelGGL(gate_out_kernel, dim3(a.B), dim3(64), 0, s, a, hidden, lg, bucket);
+    hipLaunchKernelGGL(gate_out_kernel<Bucket>, dim3(a.B), dim3(64), 0, s, a, hidden, lg, bucket);
     DS_CHECK_LAUNCH("gate head");
     return DS_OK;
 }
-}  // namespace
 
-int32_t ds_launch_gate(const GateArgs& a, hipStream_t s, const BucketArgs* bucket_of_one) {
-    if (a.B <= 0) return DS_OK;
-    BucketArgs bucket = {};                              // B = 0: none
-    if (bucket_of_one) {
-        if (a.B != 1 || bucket_of_one->B != 1 || bucket_of_one->T > 64) DS_FAIL(DS_EINVAL, "gate: only one sample is bucketed by the gate itself");
-        bucket = *bucket_of_one;
-    }
+template <typename Bucket>
+int32_t launch_gate(const GateArgs& a, const Bucket& bucket, hipStream_t s) {
     float* hidden = nullptr;
     // (16-byte rows of the map: NHWC strides are multiples of 8 channels wherever the entry points let a map in)
     const bool rows16 = a.layout != DS_NHWC || ((a.C % 8) == 0 && (a.x_ld <= 0 || (a.x_ld % 8) == 0) && (a.x_sample_stride % 8) == 0);
@@ -706,11 +705,15 @@ int32_t ds_launch_gate(const GateArgs& a, hipStream_t s, const BucketArgs* bucke
         }
         ProfScope prof(DS_K_GATE, s);
         const dim3 grid((unsigned)a.B), block(GF_NT);
-        if (!pooled) hipLaunchKernelGGL((gate_fused_kernel<float, false, false>), grid, block, 0, s, a, splits, lcl, bucket);
-        else if (a.layout == DS_NHWC && a.dtype == DS_BF16) hipLaunchKernelGGL((gate_fused_kernel<bf16_t, true, true>), grid, block, 0, s, a, splits, lcl, bucket);
-        else if (a.layout == DS_NHWC) hipLaunchKernelGGL((gate_fused_kernel<float, true, true>), grid, block, 0, s, a, splits, lcl, bucket);
-        else if (a.dtype == DS_BF16) hipLaunchKernelGGL((gate_fused_kernel<bf16_t, false, true>), grid, block, 0, s, a, splits, lcl, bucket);
-        else hipLaunchKernelGGL((gate_fused_kernel<float, false, true>), grid, block, 0, s, a, splits, lcl, bucket);
+#define DS_GATE(...) hipLaunchKernelGGL((gate_fused_kernel<__VA_ARGS__, Bucket>), grid, block, 0, s, a, splits, lcl, bucket)
+        if (!pooled) DS_GATE(float, false, false);
+        else if (a.layout == DS_NHWC && a.dtype == DS_BF16) DS_GATE(bf16_t, true, true);
+        else if constexpr (std::is_same_v<Bucket, NoBucket>) {
+            if (a.layout == DS_NHWC) DS_GATE(float, true, true);
+            else if (a.dtype == DS_BF16) DS_GATE(bf16_t, false, true);
+            else DS_GATE(float, false, true);
+        }
+#undef DS_GATE
         DS_CHECK_LAUNCH("fused gate");
         return DS_OK;
     }
@@ -728,6 +731,15 @@ int32_t ds_launch_gate(const GateArgs& a, hipStream_t s, const BucketArgs* bucke
         if (rc) return rc;
     }
     return launch_gate_out(a, hidden, bucket, s);
+}
+}  // namespace
+
+int32_t ds_launch_gate(const GateArgs& a, hipStream_t s, const BucketArgs* bucket_of_one) {
+    if (a.B <= 0) return DS_OK;
+    if (!bucket_of_one) return launch_gate(a, NoBucket{}, s);
+    if (a.B != 1 || bucket_of_one->B != 1 || bucket_of_one->T > 64) DS_FAIL(DS_EINVAL, "gate: only one sample is bucketed by the gate itself");
+    if (a.x && (a.layout != DS_NHWC || a.dtype != DS_BF16)) DS_FAIL(DS_EINVAL, "gate: only networks' maps (bf16, NHWC) are bucketed by the gate itself");
+    return launch_gate(a, *bucket_of_one, s);
 }
 
 int32_t ds_launch_bucket_ex(const BucketArgs& a, hipStream_t s) {
@@ -893,7 +905,7 @@ extern "C" int32_t ds_gate_double(const void* x, int32_t x_dtype, int32_t x_layo
         ProfScope prof(DS_K_GATE, s);
         int lg = 0;
         while ((1 << lg) < T && lg < 6) ++lg;
-        hipLaunchKernelGGL(gate_out_kernel, dim3(B), dim3(64), 0, s, a, (const float*)hidden, lg, BucketArgs{});
+        hipLaunchKernelGGL(gate_out_kernel<NoBucket>, dim3(B), dim3(64), 0, s, a, (const float*)hidden, lg, NoBucket{});
         DS_CHECK_LAUNCH("gate head");
     }
     // attention head: factor[b][c] = 1 + tanh(W3[c, :] . hidden[b] + b3[c]); rows beyond the
