@@ -14,6 +14,7 @@
 // Sums are in gemm_kernel's order: the same bits.
 #include "gelu.h"
 #include "vit_rows.h"
+#include "vit_run.h"
 
 namespace {
 
@@ -108,13 +109,14 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
         const int p = b0 + w, seg = p / nb, n0 = (p - seg * nb) * 32;
         const bool on = p < blk1;
         if (res) {
-            // the residual of these columns waits in the stage, where the sums are added in place
+            // the residual of these columns waits in the stage, where the sums are added in place; this run's columns only: res may be
+            // y, and the next workgroup's columns are being written
 #pragma unroll
             for (int i = 0; i < NI; ++i)
 #pragma unroll
                 for (int k = 0; k < (NS + 15) / 16; ++k) {
                     const int c = k * 16 + l16, n = (b0 + (c >> 2)) * 32 + (c & 3) * 8;
-                    if (c < NS && live[i] && n < k_out)
+                    if (run_chunk(c, NW, b0, blk1) && live[i] && n < k_out)
                         *(uint4*)(Ss + (prow + RP * i) * SP + c * 8) = *(const uint4*)(res + yoff[i] + n);
                 }
         }
@@ -182,7 +184,7 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
 #pragma unroll
             for (int k = 0; k < (NS + 15) / 16; ++k) {
                 const int c = k * 16 + l16, pb = b0 + (c >> 2);
-                if (c >= NS || pb >= blk1 || !live[i]) continue;
+                if (!run_chunk(c, NW, b0, blk1) || !live[i]) continue;
                 const int sg = pb / nb, n = (pb - sg * nb) * 32 + (c & 3) * 8;
                 if (n < k_out) *(uint4*)(y + yoff[i] + (int64_t)sg * y_seg + n) = *(const uint4*)(Ss + (prow + RP * i) * SP + c * 8);
             }
