@@ -18,7 +18,7 @@
 namespace {
 
 // V_LD: 228 elements put the eight channel octets that a wavefront scatters at once on four groups of banks (232: on two) and the 32
-// channels of a product's operand on different ones; 64 images 1058 -> 1046 us a pass, 5 images 562 -> 558
+// channels of a product's operand on different ones; 256 images of DS-ViT 38.1 -> 36.4 us a launch, 64 images 1056 -> 1043 us a pass, 5 images 563 -> 559
 constexpr int NKT = 7, KEYS = NKT * 32, V_LD = KEYS + 4;
 
 // DH: head dimension, a multiple of 16.  The output tiles are 32 channels tall, so V^T is padded with
@@ -53,9 +53,10 @@ __global__ __launch_bounds__(448) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     const int nthreads = blockDim.x;          // one wavefront per 32-query tile
     if constexpr (DH % 32 != 0)
         for (int c = tid; c < (DT * 32 - DH) * V_LD / 2; c += nthreads) ((uint32_t*)(Vt + DH * V_LD))[c] = 0u;
-    // a lane's pieces of K and V are all asked for before the first is written (four at a time: all there are with seven wavefronts
-    // of a 64-wide head); one after the other they were four round trips
-    // (rows past the sequence are past the descriptor: zeros)
+    // A lane's pieces of K and V, four at a time (all there are with seven wavefronts of a 64-wide head), without a branch around a
+    // request: rows past the sequence are past the descriptor and give zeros.  That is what lets them travel together; one at a time
+    // measures the same (256 images 36.4 and 36.6 us a launch), one at a time behind a test of the row, at the pitch of
+    // 232, 40.0.
     constexpr int AT = 4;
     const int bytes = ((N - 1) * ld + DH) * 2;
     const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc((void*)(k + base), 0, bytes, 0x00020000);

@@ -751,11 +751,13 @@ int32_t vit_behind_attention(const VitDesc& d, const void* const* L, const void*
     const int64_t x_ss = (int64_t)d.N * d.D;
     const int kbp = (Hd + 15) / 16 | 1, kb1 = (d.D + 15) / 16 | 1, kb2 = (d.M + 15) / 16 | 1;
     const int nbd = (d.D + 31) / 32, nbm = (d.M + 31) / 32;
-    // Up to about 56 tiles of 32 rows three launches over many workgroups instead of one whose every workgroup streams all
-    // weights.  The routes are on the device, so this cannot depend on them: a pass of 5 images takes 620 against 773 us on the
-    // widest route, 590 against 668 on five different ones, and 521 against 416 on the narrowest, where the block's weights
-    // are a tenth.  Above, the launches cost what their extra passes and workgroups do (16 images 34 against 25 us a block;
-    // profiles/dispatch_choices.txt).
+    // Up to 56 tiles of 32 rows (7 images) three launches over many workgroups instead of one whose every workgroup streams all
+    // weights.  The routes are on the device, so this cannot depend on them.  Us a pass, three launches / one: 5 images 558 / 647 on
+    // routes evenly spread, 596 / 755 on the widest one, 478 / 394 on the narrowest, where the block's weights are a tenth.  Beyond
+    // the line the launches cost what their extra passes and workgroups do (16 images 802 / 673), but not at once: evenly spread, 8
+    // images take 557 / 555, 9 to 13 images 635..697 / 663..760 (DS-ViT++ 781..952 / 967..1019), 14 and 15 images 732 / 699 and 739 / 672;
+    // all on the widest route 8 images 684 / 751, 13 images 755 / 785, on the narrowest 505 / 398 and 602 / 436.  The line stands where
+    // no mix of routes loses more than a quarter by it (profiles/dispatch_choices.txt).
     const int groups = B < d.T ? B : d.T;
     const bool few = d.M <= 1664 && ((int64_t)B * d.N - groups) / 32 + groups <= 56;
     if (!few) {

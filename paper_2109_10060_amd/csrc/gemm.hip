@@ -454,8 +454,12 @@ int32_t ds_launch_gemm(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, 
     const long long all = wgs * (a.crowd > 1 ? a.crowd : 1);
     // Fewer workgroups than run at once: the slabs of a tile dealt to shares of four wavefronts (not where sums keep one order).
     // DS-ResNet, us a launch, one share -> here: 8 images, 64 -> 256 channels with residual 9.6 -> 8.4, 14x14 3x3/2 13.0 -> 11.2; 33
-    // images, 1024 -> 256 14.1 -> 12.6, 2048 -> 512 21.9 -> 17.2, 3x3/2 29.6 -> 24.0; 64 images 3x3/2 35.7 -> 26.6.  Twice these
-    // lines: 905 -> 912 us a pass at 33 images, DS-ResNet++ 950 -> 991, DS-MBNet++ 40 images 331 -> 355.
+    // images, 1024 -> 256 14.1 -> 12.6, 2048 -> 512 21.9 -> 17.2, 3x3/2 29.6 -> 24.0; 64 images 3x3/2 35.7 -> 26.6.  A workgroup of four
+    // shares has a compute unit to itself, so beyond 256 of them there are two generations: worth it only where a share of half the
+    // slabs is a long chain, from 32 slabs on.  Us a pass, four shares up to 256 workgroups whatever the slabs / here / up to 512
+    // whatever the slabs: DS-ResNet 33 images 903 / 901 / 913, 64 images 1261 / 1253 / 1264, 96 images 1544 / 1533 / 1532; DS-ResNet++ 33
+    // images 948 / 948 / 970, 64 images 1351 / 1356 / 1379; DS-MBNet++ 40 images 332 / 332 / 343.  Twice all these lines: DS-ResNet 16 / 33 / 64 / 96
+    // images 715 / 905 / 1248 / 1523 -> 701 / 912 / 1265 / 1537, DS-ResNet++ 33 images 948 -> 990, DS-MBNet++ 40 images 331 -> 356.
     if (!a.ordered && slabs >= 8 && all <= (slabs >= 32 ? 512 : 256)) return DS_GEMM_DISPATCH(4, 1, 1, 2, 64, 4);
     if (!a.ordered && slabs >= 4 && all <= 512) return DS_GEMM_DISPATCH(4, 1, 1, 2, 64, 2);
     if (kmax >= 512 && wgs <= 256 * 6) return DS_GEMM_DISPATCH(4, 1, 1, 2, 128, 1);

@@ -679,11 +679,11 @@ int32_t launch_gate(const GateArgs& a, const Bucket& bucket, hipStream_t s) {
     const bool rows16 = a.layout != DS_NHWC || ((a.C % 8) == 0 && (a.x_ld <= 0 || (a.x_ld % 8) == 0) && (a.x_sample_stride % 8) == 0);
     if (a.x && a.C <= GF_CMAX && a.C_mlp <= GF_HMAX && a.T <= 64 && rows16) {
         const int64_t map_bytes = (int64_t)a.C * a.HW * (a.dtype == DS_BF16 ? 2 : 4);
-        // one compute unit pools up to 512 KiB and 512 channels in less time than a launch costs (9 us with the MLP, against
-        // 14 us and two launches more for pool, hidden layer and output layer one after the other; 256 images 20 against
-        // 30); above, the pool kernel's several workgroups per item first (second gate of DS-ResNet, 1 / 33 images: 16.3 / 17.0 us
-        // in two launches, 18.8 / 21.8 in one workgroup; 256 images 65 and 57; profiles/dispatch_choices.txt; taken before the
-        // pool followed the slice, which has the two launches at 12.4 for 1 image, its bucket included)
+        // One workgroup pools up to 512 KiB and 512 channels in less time than the pool as a launch of its own costs: gate of DS-MBNet
+        // (256 channels of 28x28, 392 KiB), us, one launch against two: 1 image 9.7 / 3.8 + 6.4, 256 images 20.4 / 16.4 + 8.1 (a pass 120.0 / 120.4 and 923 /
+        // 928); first gate of DS-ResNet (64 channels of 56x56), 1 image 10.4 / 4.0 + 6.9.  Above, the pool kernel's several workgroups
+        // per item first: its second gate (up to 256 channels of 56x56, 1.5 MiB), 1 / 33 images 20.0 / 22.1 against 3.8 + 8.2 / 7.6 + 8.4, 256 images
+        // 49.3 / 46.4 + 9.2; its third (784 KiB) 16.4 / 17.3 / 26.9 against 3.5 + 9.2 / 5.3 + 9.8 / 20.5 + 11.3 (profiles/dispatch_choices.txt).
         const bool pooled = map_bytes <= (512 << 10) && a.C <= 512;
         int splits = 1;
         if (!pooled) {
@@ -692,7 +692,7 @@ int32_t launch_gate(const GateArgs& a, const Bucket& bucket, hipStream_t s) {
         }
         int lcl = 0;
         while ((8 << lcl) < a.C && lcl < 6) ++lcl;
-        // one or two items with 1 MiB of hidden weights: 10.3 / 14.9 us in one workgroup, 9.5 / 12.8 with a wavefront per unit
+        // one or two items with 1 MiB of hidden weights: 12.9 / 15.0 us in one workgroup, 4.4 + 6.6 / 6.9 + 5.8 with a wavefront per unit
         if (!pooled && a.B <= 2 && (int64_t)a.C * a.C_mlp >= (256 << 10)) {
             float* hid = a.partial + (size_t)a.B * a.C * POOL_SPLIT_MAX;
             FcArgs f = {};

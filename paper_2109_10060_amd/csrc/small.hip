@@ -10,8 +10,8 @@
 // Around that chain lie the round trips of the kernel's head and tail, and instructions: eight wavefronts of a compute unit
 // issue one each in eight clocks.  So all kernel arguments are read at once, with the group table beside the tile record, the
 // batch-norm rows and the residual are asked for behind the first operands, and a tap costs two instructions a row: a mask of
-// the filter rows and columns inside the map, the pixel of a tap in the load's scalar offset.  One image of DS-ResNet, 47
-// of these launches: 431 -> 385 us a pass.
+// the filter rows and columns inside the map, the pixel of a tap in the load's scalar offset.  One image of DS-ResNet, 52
+// of these launches (44 and 4 pairs since): 431 -> 385 us a pass.
 // Same tile list, row addressing, slices and epilogue as gemm_kernel; a list tile of 128 rows is walked in parts of
 // WM*32 rows and a part beyond the group's rows ends at once.
 // Column tiles are the fastest index of the launch: neighbouring workgroups land on different dies, so a die's L2 holds
@@ -378,17 +378,18 @@ bool small_in_reach(const GemmArgs& a, const SmallSize& z, int32_t max_mtiles, i
 // Measured on the layers of DS-ResNet with the benchmark's routes, kernel time in us, general kernels -> here
 // (profiles/dispatch_choices.txt; stages counted from 1):
 //   t <= 340    one tile and 8 shares of the reduction per workgroup: every compute unit gets at most one or two, so the
-//               length of a share is all that counts (stage 4, one sample: 3x3 13.2 -> 6.7, first 1x1 9.6 -> 5.0; four samples
-//               38.8 -> 13.2, 21.8 -> 8.3; DS-MBNet's pointwise layers, one sample 7.3 -> 5.2)
-//   t <= 500    32 x 64 tiles, 8 shares (stage 3, eight samples: 3x3 23.0 -> 12.4, 1x1 14.0 -> 8.6), 32 x 32 and 4 shares
-//               when there are fewer slabs than shares (stage 4, four samples, last 1x1 10.7 -> 6.0)
-//   t <= 700    32 x 32, 4 shares (stage 4, 16 samples: 1x1 21.5 -> 10.2, 3x3 39.0 -> 17.8)
-//   t <= 1000   64 x 64 tiles, 8 shares, for 24 slabs and more (stage 3, 16 samples: 3x3 22.8 -> 14.8), 32 x 64 tiles and 4
-//               shares (1x1 14.6 -> 11.0), two column tiles and 2 shares up to four slabs (four samples 9.2 -> 7.2)
+//               length of a share is all that counts (stage 4, one sample: 3x3 8.9 -> 5.7, first 1x1 6.9 -> 4.4; four samples
+//               22.9 -> 11.0, 16.0 -> 7.8)
+//   t <= 500    32 x 64 tiles, 8 shares (stage 3, eight samples: 3x3 15.7 -> 10.7, 1x1 11.3 -> 8.0), 32 x 32 and 4 shares
+//               when there are fewer slabs than shares (stage 4, four samples, last 1x1 8.1 -> 6.2)
+//   t <= 700    32 x 32, 4 shares (stage 4, 16 samples: 1x1 17.0 -> 9.4, 3x3 23.8 -> 14.0)
+//   t <= 1000   64 x 64 tiles, 8 shares, for 24 slabs and more (stage 3, 16 samples: 3x3 15.2 -> 12.6), 32 x 64 tiles and 4
+//               shares (1x1 11.6 -> 9.3; stage 1, four samples: 3x3 8.3 -> 9.4, the one layer that loses), two column tiles and 2 shares
+//               up to four slabs (stage 3, four samples, last 1x1 7.8 -> 6.6)
 //   ordered     one wavefront walks a tile's whole reduction, three slabs ahead, two tiles per workgroup, up to 1700 tiles
-//               (patch embedding of DS-ViT, twelve slabs, 1 / 5 / 16 images 13.8 -> 11.5 / 14.8 -> 11.5 / 14.1 -> 12.1)
+//               (patch embedding of DS-ViT, twelve slabs, 1 / 5 / 16 images 13.6 -> 9.3 / 15.6 -> 10.5 / 14.6 -> 10.5)
 //   beyond      the 128-row kernels have enough workgroups and read less per product -- except the strided KxK layers
-//               (no staged patch for them), which stay here up to 1700 tiles (stage 4, 33 samples 48.0 -> 23.1)
+//               (no staged patch for them), which stay here up to 1700 tiles (stage 4, 33 samples 34.3 -> 20.1)
 int32_t ds_launch_gemm_small(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
     if (max_mtiles <= 0 || max_kout <= 0 || a.B <= 0) return DS_EUNSUPPORTED;
     if (a.K > 15 || a.Kw > 15) return DS_EUNSUPPORTED;        // tap masks of 16 bits

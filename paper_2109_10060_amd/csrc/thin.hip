@@ -353,8 +353,8 @@ int32_t ds_launch_thin(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, 
     int kmax = 0;
     if (thin_supported(a, max_mtiles, max_kout, &kmax) != DS_OK) return DS_EUNSUPPORTED;
     // a workgroup walks all columns of its rows one pass after the other, which needs enough row tiles to hide: below these
-    // counts the general kernel's (row, column) tiles are faster (64 channels: 203 tiles 11.6 against 9.2 us, 407 tiles
-    // 12.7 / 12.2, 824 tiles 15.2 / 17.8; 128 channels: 218 tiles 25.1 against 12.7 us; profiles/dispatch_choices.txt)
+    // counts the general kernel's (row, column) tiles are faster (64 channels: 203 tiles 11.6 against 9.0 us, 407 tiles
+    // 12.8 / 12.0, 824 tiles 15.1 / 17.7; 128 channels: 218 tiles 25.1 against 12.6 us; profiles/dispatch_choices.txt)
     if (max_mtiles < (kmax <= 64 ? 400 : 800)) return DS_EUNSUPPORTED;
     const int32_t rc = thin_configure();
     if (rc != DS_OK) return rc;
@@ -386,8 +386,8 @@ int32_t ds_launch_thin_chain(const GemmArgs& a, const ThinChain& ch, int32_t max
     if ((ch.c_sample_stride % 8) || (ch.c_ld > 0 && ch.c_ld % 8) || (ch.w_ld % 8) ||
         (((uintptr_t)ch.scale | (uintptr_t)ch.shift | (uintptr_t)ch.C | (uintptr_t)ch.Wt) & 15))
         return DS_EUNSUPPORTED;
-    // (as above, for the pair: 64 channels 101 tiles 16.2 against 16.4 us as two launches, 203 tiles 17.0 / 19.7, 407 tiles
-    // 18.0 / 26.3; 128 channels 218 tiles 32.9 against 25.0)
+    // (as above, for the pair: 64 channels 101 tiles 16.2 against 15.8 us as two launches, 203 tiles 16.9 / 19.4, 407 tiles
+    // 17.8 / 26.0; 128 channels 218 tiles 32.7 against 23.6)
     if (max_mtiles < (kmax <= 64 ? 150 : 400)) return DS_EUNSUPPORTED;
     int k2max = 0;
     for (int t = 0; t < a.gt.T; ++t) {

@@ -207,9 +207,9 @@ int32_t launch(const VitLinearArgs& a, int64_t tiles, int max_blocks, int run_bl
 
 }  // namespace
 
-// Measured on DS-ViT's Q/K/V layer with its LayerNorm (us, profiles/dispatch_choices.txt): 1 / 5 / 16 images with 4 wavefronts
-// and 4 blocks a workgroup 8.3 / 8.8 / 14.6, 8 blocks 10.2 / 10.4 / 12.9; 64 images with 12 wavefronts and 64 rows 23, 96 rows
-// 28; 256 images 59 and 57 (gemm_kernel 53 and its LayerNorm 12).  Reductions beyond 416 channels (fc2) are for the few-image path alone: 107 KB of rows.
+// Measured on DS-ViT's Q/K/V layer with its LayerNorm (us, profiles/dispatch_choices.txt): 1 / 5 / 9 / 16 images with 4 column blocks
+// a workgroup 6.6 / 8.0 / 9.6 / 15.0, 8 blocks 9.2 / 9.6 / 10.8 / 12.3; 64 images with 12 wavefronts and 64 rows 23.2, 96 rows
+// 27.0, 4 wavefronts and 32 rows 29.9; 256 images 57.5 with 64 rows, 54.5 with 96.  Reductions beyond 416 channels (fc2) are for the few-image path alone: 107 KB of rows.
 int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s) {
     int kmax = 0, nmax = 0;
     for (int t = 0; t < a.gt.T; ++t) {
@@ -226,10 +226,11 @@ int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s) {
         if (tiles(96) >= 448) return launch<12, 3, 4, VIT_K_MAX, false>(a, tiles(96), blocks, blocks, s);
         if (tiles(64) >= 160) return launch<12, 2, 4, VIT_K_MAX, false>(a, tiles(64), blocks, blocks, s);
         // (the early requests cost 50 registers, a third of the workgroups a compute unit holds: not where there are enough of them,
-        // nor beside the launches of a batch's other parts -- 16 images 677 us a pass against 696, 64 images in four parts 1193 and 1115)
+        // nor beside the launches of a batch's other parts -- 1 / 5 / 16 images 494 / 562 / 673 us a pass, 506 / 569 / 690 without them; 64
+        // images in four parts 1181 with them, 1101 without; 24 images, beyond the line, 805 either way)
         const int run = tiles(32) > 64 ? 8 : 4;
         // up to a workgroup a compute unit eight wavefronts: half as many rows each to fetch and normalise, four of them multiply
-        // (1 image 503 -> 483 us a pass, 3 images 540 -> 520; 5 images, with two workgroups for some, 567 -> 620)
+        // (1 / 3 / 5 images 494 / 535 / 562 -> 474 / 515 / 558 us a pass; with two workgroups for some compute units 5 / 8 images 617 / 592)
         if (a.crowd <= 1 && run == 4 && tiles(32) * ((blocks + 3) / 4) <= 256)
             return launch<8, 1, 8, VIT_K_MAX, true>(a, tiles(32), blocks, run, s);
         if (a.crowd <= 1 && tiles(32) <= 128) return launch<4, 1, 8, VIT_K_MAX, true>(a, tiles(32), blocks, run, s);

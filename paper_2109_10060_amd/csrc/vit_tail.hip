@@ -15,7 +15,8 @@
 // HC = 32 NW columns of the hidden layer; R row blocks share every weight operand.
 // Around the products a workgroup has nothing beside it on its compute unit, so what it waits for is kept off its path: the
 // residual rows wait in the hidden tile, which is free until the MLP, LayerNorm weights in LDS, biases in registers.  DS-ViT, us
-// a pass: 16 images 709 -> 707, 64 images 1078 -> 1070, 256 images (64 rows a workgroup in place of 96 as well) 2622 -> 2570.
+// a pass: LayerNorm weights from memory -> from LDS 16 images 676 -> 672, 64 images 1047 -> 1043, 256 images 2509 -> 2485 (DS-ViT++
+// 3688 -> 3666); biases where they are used -> in registers 64 images 1050 -> 1043, 128 images 1472 -> 1468, 256 images no change.
 //
 // Sums run in the order of gemm_kernel's and layernorm16_kernel's, so the results are the same bits.
 #include "gelu.h"
@@ -37,7 +38,7 @@ template <int NW, int R, int D>
 __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const VitTailArgs a) {
     using Tile = TailTile<NW, R, D>;
     // biases travel during the products; not with 13 wavefronts (no registers for them) and not with 32 rows, where a smaller kernel
-    // leaves room for those of a batch's other parts (128 images in four: 1998 -> 1925 us)
+    // leaves room for those of a batch's other parts (128 images in four parts 1888 us a pass, 1959 with them; 16 images alone 672 and 666)
     constexpr bool CST = NW <= 12 && R == 2;
     constexpr int BM = 32 * R, HC = 32 * NW, PA = Tile::PA, PH = Tile::PH, RP = 4 * NW, NI = (BM + RP - 1) / RP;   // RP: rows of a row phase
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -293,9 +294,13 @@ int32_t launch(const VitTailArgs& a, int64_t tiles, hipStream_t s) {
 
 // Rows per workgroup.  A workgroup streams all weights of the block whatever its rows (2.7 MB at full width), and when all compute
 // units do so at once the L2s give each about 30 bytes a clock, half of what 64 rows could use; so more rows each are better --
-// as long as there is a workgroup for every compute unit and the last ones end together.  256 images: 560 tiles of 96 rows take
-// 2710 us a pass, 816 tiles of 64 rows 2600; two workgroups a compute unit (four wavefronts of three column blocks each, 64
-// rows) 2780: eight wavefronts do not cover the weights' latency.
+// as long as there is a workgroup for nearly every compute unit and the last ones end together.  Us a pass of DS-ViT, 32 / 64 rows: 56
+// images (219 tiles of 64 rows) 1012 / 1036, 60 images (231) 1074 / 1039, 96 images 1421 / 1251, 256 images 3135 / 2530; DS-ViT++ 64 images
+// (202) 1417 / 1493, 96 images (299) 1893 / 1718: the line is at 224.  96 rows leave no LDS for the LayerNorm weights: 64 images 1267 us against 1046
+// with 64 rows, 192 images 2016 against 2039, 256 images 2587 against 2530 on one card and 2492 against 2485 on another.  (Profiles:
+// dispatch_choices.txt.  The parts of a batch are not counted together here: 128 images in four take 1886 us, 1664 with 64 rows.)
+// Two workgroups a compute unit (four wavefronts of three column blocks each, 64 rows) were slower, 2780 us when 64 rows took 2600 and
+// 96 rows 2710: eight wavefronts do not cover the weights' latency.
 int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {
     int dmax = 0;
     for (int t = 0; t < a.gt.T; ++t) {
