@@ -31,6 +31,10 @@
  *    The depthwise kernels for plain 3 x 3 filters and for dilated or wider-stepped
  *    ones multiply channels in pairs: there a pixel that is not finite in channel c
  *    also reaches channel c ^ 1 of the same outputs.
+ *  - Repeated calls give the same bits.  Across batch sizes they need not: the
+ *    order in which an fp32 sum is taken belongs to the kernel that a launch's size
+ *    selects (few samples, or fewer workgroups than run at once, deal a reduction to
+ *    several wavefronts), and bf16 roundings behind it may then go the other way.
  */
 #ifndef DSNET_H
 #define DSNET_H
@@ -341,7 +345,8 @@ int32_t ds_forward_taps(const ds_net* net, const void* images, int32_t B, const 
  * on streams the library creates on first use (up to 3 per device, default priority, kept until the process ends) —
  * and the launch ramps and tails of one share's kernels are filled by the other's.  The side streams start after the
  * work already queued on `stream` and `stream` continues after them, so to the caller the call is one piece of work
- * on `stream`.  Arguments, results and errors as ds_forward (every output is per sample, hence identical); ws needs
+ * on `stream`.  Arguments, results and errors as ds_forward (every output is per sample; where a share is
+ * so small that other kernels run it, within the order of their sums); ws needs
  * ds_forward_parts_workspace(net, B, parts) bytes (0 for parts outside 1..4).  parts = 1 is ds_forward.
  * Calls that overlap in time on one device share the side streams and are serialised by them. */
 size_t ds_forward_parts_workspace(const ds_net* net, int32_t B, int32_t parts);
