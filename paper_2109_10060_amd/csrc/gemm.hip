@@ -418,15 +418,16 @@ int32_t ds_launch_gemm(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, 
     if (max_mtiles <= 0 || max_kout <= 0) return DS_OK;
     // ragged route slices favour the narrow 128x64 tile at high occupancy in every layer of the batch-256 networks.
     // Its slabs are 32 deep for short reductions and 64 deep from 256 reduction steps on: half the barriers and
-    // twice the bytes in flight per workgroup outweigh the lower residency there (measured per layer: ViT MLP
-    // down-projection 62 -> 52 us, ResNet stage-4 strided 3x3 83 -> 66 us; 128-step layers 44 -> 48 us the other way)
-    // (a slab never crosses a filter tap: with fewer than 64 channels per tap the deep slab would be mostly padding --
-    // the 8x8 patch embedding over 24 channels ran 144 -> 226 us with it)
+    // twice the bytes in flight per workgroup outweigh the lower residency there.  256 images, us a launch, 32 -> 64 deep: DS-ResNet
+    // stage 3, first 1x1 44.2 -> 40.0, strided 3x3 61.4 -> 57.3, stage 4, last 1x1 36.0 -> 30.5, DS-MBNet++ 288..640 channels 51.7 ->
+    // 45.5 (passes 3131 -> 3013, 955 -> 921); its 96-channel layer 26.0 -> 28.7 the other way.
+    // (a slab never crosses a filter tap: with fewer than 64 channels per tap the deep slab would be mostly padding)
     int kmax = 0;
     for (int t = 0; t < a.gt.T; ++t) kmax = a.gt.k_in[t] > kmax ? a.gt.k_in[t] : kmax;
     const long long taps = (long long)a.K * (a.Kw > 0 ? a.Kw : a.K);
-    // (exactly 256 steps: the 64-deep slabs pay only where a residual is streamed as well -- without one the 32-deep
-    // kernel keeps six workgroups per compute unit: DS-MBNet's 256-channel pointwise layers -1.1 % per step, DS-ResNet -0.4 %)
+    // (exactly 256 steps: the 64-deep slabs pay only where a residual is streamed as well -- without one the 32-deep kernel keeps six
+    // workgroups per compute unit: DS-ResNet stage 2, 256 images, projection 83.9 -> 76.2 us with 32, first 1x1 105.3 -> 112.7; passes of
+    // 64 images 1264 -> 1251, DS-ResNet++ 33 images 972 -> 961, 256 images 3006 / 3013)
     const bool deep = kmax >= 64 && (kmax * taps >= 320 || (kmax * taps >= 256 && a.R != nullptr));
     // 32-bit byte offsets inside the kernel: activations and weights must each span less than 2 GiB
     const long long slots = (long long)max_mtiles * BM / (a.rows > 0 ? a.rows : 1) + 1;
@@ -449,7 +450,9 @@ int32_t ds_launch_gemm(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, 
           : (a.R ? launch<__VA_ARGS__, false, true>(a, max_mtiles, max_kout, s)                        \
                  : launch<__VA_ARGS__, false, false>(a, max_mtiles, max_kout, s)))
     if (!deep) return DS_GEMM_DISPATCH(4, 1, 1, 2, 32, 1);   // 64-wide tile, 32-deep slabs
-    // launches of about one generation with long reductions (below): 128-deep slabs halve the number of dependent rounds
+    // launches of about one generation with long reductions (below): 128-deep slabs halve the number of dependent rounds (256 images of
+    // DS-ResNet, stage 4: strided 3x3 64.3 -> 55.7 us, first 1x1 32.3 -> 28.5, pass 3028 -> 3013; without the bound of six workgroups a compute
+    // unit its projections 49.0 -> 58.7 and 45.3 -> 50.1, pass 3070, DS-MBNet++ 921 -> 970)
     const long long wgs = (long long)max_mtiles * a.n_seg * ((max_kout + 63) / 64), slabs = taps * ((kmax + 63) / 64);
     const long long all = wgs * (a.crowd > 1 ? a.crowd : 1);
     // Fewer workgroups than run at once: the slabs of a tile dealt to shares of four wavefronts (not where sums keep one order).

@@ -322,8 +322,9 @@ int32_t thin_supported(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, 
         kmax = a.gt.k_in[t] > kmax ? a.gt.k_in[t] : kmax;
         if ((a.gt.k_in[t] % 8) || (a.gt.k_out[t] % 8)) return DS_EUNSUPPORTED;
     }
-    // measured: up to 64 input channels always wins (-27..-33 % per layer), 65..128 only where a residual is streamed too
-    // (2 workgroups per compute unit there); one pass per workgroup gains nothing over the general kernel
+    // measured: up to 64 input channels wins 25..33 % a layer (256 images of DS-ResNet, us a launch, gemm_kernel -> here: projection 101 ->
+    // 76, last layer with residual 162 -> 108), 65..128 only where a residual is streamed too (67 -> 65, two workgroups per compute unit
+    // there, but 103 -> 87 with the next layer chained); one pass per workgroup gains nothing over the general kernel
     if (kmax > 128 || (kmax > 64 && !a.R) || max_kout < 128) return DS_EUNSUPPORTED;
     const long long slots = (long long)max_mtiles * BM / (a.rows > 0 ? a.rows : 1) + 1;
     if (slots * a.a_sample_stride * 2 >= 0x7fffffffLL) return DS_EUNSUPPORTED;

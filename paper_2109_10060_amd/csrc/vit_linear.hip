@@ -209,7 +209,7 @@ int32_t launch(const VitLinearArgs& a, int64_t tiles, int max_blocks, int run_bl
 
 // Measured on DS-ViT's Q/K/V layer with its LayerNorm (us, profiles/dispatch_choices.txt): 1 / 5 / 9 / 16 images with 4 column blocks
 // a workgroup 6.6 / 8.0 / 9.6 / 15.0, 8 blocks 9.2 / 9.6 / 10.8 / 12.3; 64 images with 12 wavefronts and 64 rows 23.2, 96 rows
-// 27.0, 4 wavefronts and 32 rows 29.9; 256 images 57.5 with 64 rows, 54.5 with 96.  Reductions beyond 416 channels (fc2) are for the few-image path alone: 107 KB of rows.
+// 27.0, 4 wavefronts and 32 rows 29.9; 256 images 57.5 with 64 rows, 54.5 with 96.  Reductions beyond 416 channels (fc2) are for the few-image path alone: 113 KiB of rows.
 int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s) {
     int kmax = 0, nmax = 0;
     for (int t = 0; t < a.gt.T; ++t) {

@@ -52,7 +52,7 @@ def _short(name: str) -> str:
     for k in GEMM_KERNELS:
         if k in name:
             return k
-    name = name.split("(")[0]
+    name = name.split("(")[0].removeprefix("void ")
     return name[-60:]
 
 
