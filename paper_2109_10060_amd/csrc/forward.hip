@@ -757,7 +757,7 @@ int32_t vit_behind_attention(const VitDesc& d, const void* const* L, const void*
     // the line the launches cost what their extra passes and workgroups do (16 images 802 / 673), but not at once: evenly spread, 8
     // images take 557 / 555, 9 to 13 images 635..697 / 663..760 (DS-ViT++ 781..952 / 967..1019), 14 and 15 images 732 / 699 and 739 / 672;
     // all on the widest route 8 images 684 / 751, 13 images 755 / 785, on the narrowest 505 / 398 and 602 / 436.  The line stands where
-    // no mix of routes loses more than a quarter by it (profiles/dispatch_choices.txt).
+    // none of the measured mixes loses more than a quarter by it (profiles/dispatch_choices.txt).
     const int groups = B < d.T ? B : d.T;
     const bool few = d.M <= 1664 && ((int64_t)B * d.N - groups) / 32 + groups <= 56;
     if (!few) {

@@ -452,7 +452,7 @@ int32_t ds_launch_gemm(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, 
     if (!deep) return DS_GEMM_DISPATCH(4, 1, 1, 2, 32, 1);   // 64-wide tile, 32-deep slabs
     // launches of about one generation with long reductions (below): 128-deep slabs halve the number of dependent rounds (256 images of
     // DS-ResNet, stage 4: strided 3x3 64.3 -> 55.7 us, first 1x1 32.3 -> 28.5, pass 3028 -> 3013; without the bound of six workgroups a compute
-    // unit its projections 49.0 -> 58.7 and 45.3 -> 50.1, pass 3070, DS-MBNet++ 921 -> 970)
+    // unit the projections of stages 3 and 4 49.0 -> 58.7 and 45.3 -> 50.1, pass 3070, DS-MBNet++ 921 -> 970)
     const long long wgs = (long long)max_mtiles * a.n_seg * ((max_kout + 63) / 64), slabs = taps * ((kmax + 63) / 64);
     const long long all = wgs * (a.crowd > 1 ? a.crowd : 1);
     // Fewer workgroups than run at once: the slabs of a tile dealt to shares of four wavefronts (not where sums keep one order).

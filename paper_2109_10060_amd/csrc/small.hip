@@ -384,7 +384,7 @@ bool small_in_reach(const GemmArgs& a, const SmallSize& z, int32_t max_mtiles, i
 //               when there are fewer slabs than shares (stage 4, four samples, last 1x1 8.1 -> 6.2)
 //   t <= 700    32 x 32, 4 shares (stage 4, 16 samples: 1x1 17.0 -> 9.4, 3x3 23.8 -> 14.0)
 //   t <= 1000   64 x 64 tiles, 8 shares, for 24 slabs and more (stage 3, 16 samples: 3x3 15.2 -> 12.6), 32 x 64 tiles and 4
-//               shares (1x1 11.6 -> 9.3; stage 1, four samples: 3x3 8.3 -> 9.4, the one layer that loses), two column tiles and 2 shares
+//               shares (1x1 11.6 -> 9.3; stage 1, four samples: 3x3 8.3 -> 9.4, the one measured layer that loses), two column tiles and 2 shares
 //               up to four slabs (stage 3, four samples, last 1x1 7.8 -> 6.6)
 //   ordered     one wavefront walks a tile's whole reduction, three slabs ahead, two tiles per workgroup, up to 1700 tiles
 //               (patch embedding of DS-ViT, twelve slabs, 1 / 5 / 16 images 13.6 -> 9.3 / 15.6 -> 10.5 / 14.6 -> 10.5)

@@ -296,9 +296,9 @@ int32_t launch(const VitTailArgs& a, int64_t tiles, hipStream_t s) {
 // units do so at once the L2s give each about 30 bytes a clock, half of what 64 rows could use; so more rows each are better --
 // as long as there is a workgroup for nearly every compute unit and the last ones end together.  Us a pass of DS-ViT, 32 / 64 rows: 56
 // images (219 tiles of 64 rows) 1012 / 1036, 60 images (231) 1074 / 1039, 96 images 1421 / 1251, 256 images 3135 / 2530; DS-ViT++ 64 images
-// (202) 1417 / 1493, 96 images (299) 1893 / 1718: the line is at 224.  96 rows leave no LDS for the LayerNorm weights: 64 images 1267 us against 1046
-// with 64 rows, 192 images 2016 against 2039, 256 images 2587 against 2530 on one card and 2492 against 2485 on another.  (Profiles:
-// dispatch_choices.txt.  The parts of a batch are not counted together here: 128 images in four take 1886 us, 1664 with 64 rows.)
+// (204) 1417 / 1493, 96 images (303) 1893 / 1718: the line is at 224.  96 rows leave no LDS for the LayerNorm weights: 64 images 1267 us against 1046
+// with 64 rows, 192 images 2016 against 2039, 256 images 2587 against 2530 on one card and 2492 against 2485 on another.  (See
+// profiles/dispatch_choices.txt.  The parts of a batch are not counted together here: 128 images in four take 1886 us, 1664 with 64 rows.)
 // Two workgroups a compute unit (four wavefronts of three column blocks each, 64 rows) were slower, 2780 us when 64 rows took 2600 and
 // 96 rows 2710: eight wavefronts do not cover the weights' latency.
 int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {

@@ -27,6 +27,7 @@ import csv
 import hashlib
 import json
 import os
+import re
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -43,7 +44,8 @@ GEMM_KERNELS = ("gemm_kernel", "conv3_kernel", "thin_kernel", "gemm_small_kernel
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
     for f in KERNEL_SOURCES:
-        h.update(open(os.path.join(HERE, f), "rb").read())
+        code = open(os.path.join(HERE, f)).read()
+        h.update("\n".join(l for l in (re.sub(r"//.*", "", l).strip() for l in code.splitlines()) if l).encode())   # comments aside
     return h.hexdigest()[:16]
 
 
