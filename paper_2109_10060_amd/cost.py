@@ -6,7 +6,7 @@ it avoids).  bytes: each kernel reads its valid input once and writes its valid 
 once per launch.  These are the numerators of the roofline fractions bench.py reports.
 
 The records follow the launches: which layers run as one kernel depends on sizes, and the rules of the library's dispatch
-are repeated here (_tiles, _few_samples, _separable, _tail).  Work that happens inside a launch of another class (the
+are repeated here (_tiles, _few_samples, _separable, _front, _tail).  Work that happens inside a launch of another class (the
 LayerNorms of a transformer block) is kept under "inside", without bytes or launches of its own.
 """
 from __future__ import annotations
@@ -80,6 +80,15 @@ def _few_separable(r, ci, co, B):
     return _sliced_separable(r, ci) and -(-B // 8) * -(-r // (32 // r)) * -(-co // 256) <= 32
 
 
+def _front(arch):
+    """The stem and the first two separable blocks run as one kernel."""
+    b = arch["blocks"]
+    k = int(arch["ksize"][0, 0]) if "ksize" in arch else 3
+    return (arch["image"] % 4 == 0 and arch["gate_after"] >= 2 and (b[0][2], b[1][2]) == (1, 2) and ("ksize" not in arch or arch["ksize"][0, 1] == k)
+            and b[0][0] == arch["stem_out"] and b[1][0] == b[0][1] and b[1][1] % 8 == 0
+            and (k, b[0][0], b[0][1], b[1][1] <= (128 if k == 3 else 64)) in ((3, 32, 64, True), (5, 16, 32, True)))
+
+
 def _sliced_separable(r, ci):
     """A block behind the gate (3x3 filters) that runs as one kernel: output size, stored channels."""
     return r <= 32 and -(-ci // 64) * 64 <= 2048
@@ -104,10 +113,21 @@ def mbnet_cost(arch, routes) -> Cost:
     c = Cost()
     r = _osz(arch["image"], 3, 2, 1)
     so = arch["stem_out"]
-    c.add("stem", 2.0 * B * r * r * 27 * so, B * (3 * arch["image"] ** 2 * 2 + r * r * so * 2), name="stem 3x3/2")
+    if _front(arch):
+        # counted as one launch of the depthwise class that reads the images and writes the second block's output
+        k2 = float(arch["ksize"][0, 0]) ** 2 if "ksize" in arch else 9.0
+        (c0, c1, _), (_, f, _) = arch["blocks"][:2]
+        r2 = _osz(r, 3, 2, 1)
+        c.add("dwconv", 2.0 * B * (r * r * (27.0 * so + k2 * c0 + c0 * c1) + r2 * r2 * (k2 * c1 + c1 * f)),
+              2.0 * B * (3 * arch["image"] ** 2 + r2 * r2 * f) + 2.0 * (27 * so + c0 * c1 + c1 * f), name="stem + ds0 + ds1 fused",
+              shape=f"{arch['image']}x{arch['image']}x3 -> {r2}x{r2}x{f}")
+    else:
+        c.add("stem", 2.0 * B * r * r * 27 * so, B * (3 * arch["image"] ** 2 * 2 + r * r * so * 2), name="stem 3x3/2")
     for i, (_ci, _co, s) in enumerate(arch["blocks"]):
         rin = r
         r = _osz(r, 3, s, 1)
+        if i < 2 and _front(arch):
+            continue
         ci, co = arch["cin"][routes, i].astype(np.float64), arch["cout"][routes, i].astype(np.float64)
         kk = arch["ksize"][routes, i].astype(np.float64) ** 2 if "ksize" in arch else 9.0
         cif, cof = int(_ci), int(_co)

@@ -44,9 +44,9 @@ __device__ __forceinline__ void band_operand(short4_t (&A)[N][band_steps(N, STRI
     }
 }
 
-// RO output rows of a strip: every input row (at p, nq quads a row) is read once and added to the outputs it touches
-template <int N, int STRIDE, int RO>
-__device__ __forceinline__ void band_rows(f32x4_t (&acc)[RO], const short4_t (&A)[N][band_steps(N, STRIDE)], const char* p, int nq) {
+// RO output rows of a strip: every input row (r-th at p + at(r)) is read once and added to the outputs it touches
+template <int N, int STRIDE, int RO, typename At>
+__device__ __forceinline__ void band_rows_at(f32x4_t (&acc)[RO], const short4_t (&A)[N][band_steps(N, STRIDE)], const char* p, At at) {
     constexpr int T = band_steps(N, STRIDE), ROWS = (RO - 1) * STRIDE + N;
 #pragma unroll
     for (int y = 0; y < RO; ++y) acc[y] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -54,7 +54,7 @@ __device__ __forceinline__ void band_rows(f32x4_t (&acc)[RO], const short4_t (&A
     for (int r = 0; r < ROWS; ++r) {
         short4_t B[T];
 #pragma unroll
-        for (int t = 0; t < T; ++t) B[t] = *(const short4_t*)(p + (r * nq + t) * 8);
+        for (int t = 0; t < T; ++t) B[t] = *(const short4_t*)(p + at(r) + t * 8);
 #pragma unroll
         for (int t = 0; t < T; ++t)
 #pragma unroll
@@ -62,6 +62,12 @@ __device__ __forceinline__ void band_rows(f32x4_t (&acc)[RO], const short4_t (&A
                 if (r - y * STRIDE >= 0 && r - y * STRIDE < N)
                     acc[y] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(A[r - y * STRIDE][t], B[t], acc[y], 0, 0, 0);
     }
+}
+
+// rows of nq quads one behind the other
+template <int N, int STRIDE, int RO>
+__device__ __forceinline__ void band_rows(f32x4_t (&acc)[RO], const short4_t (&A)[N][band_steps(N, STRIDE)], const char* p, int nq) {
+    band_rows_at<N, STRIDE, RO>(acc, A, p, [nq](int r) { return r * nq * 8; });
 }
 
 // Batch-norm, activation and rounding of a strip's outputs: o[y] = four packed bf16 of row y.
@@ -89,17 +95,17 @@ __device__ __forceinline__ float band_finish(uint2 (&o)[RO], const f32x4_t (&acc
     return chk[0];
 }
 
-// the same outputs tap by tap; f, p, nq: as for band_operand and band_rows
-template <int N, int STRIDE, int RO>
-__device__ __forceinline__ void band_exact(uint2 (&o)[RO], float sc, float sh, bool relu, const char* f, const char* p, int nq) {
+// the same outputs tap by tap; weight(i, j): the channel's filter; p, at: as for band_rows_at
+template <int N, int STRIDE, int RO, typename Weight, typename At>
+__device__ __forceinline__ void band_exact_at(uint2 (&o)[RO], float sc, float sh, bool relu, Weight weight, const char* p, At at) {
 #pragma unroll
     for (int y = 0; y < RO; ++y) {
         float v[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
         for (int t = 0; t < N * N; ++t) {
             const int i = t / N, j = t - i * N;
-            const float w = bf2f(((const bf16_t*)f)[i * band_row_dwords(STRIDE) * 2 + band_lead(STRIDE) + j]);
-            const bf16_t* px = (const bf16_t*)(p + (y * STRIDE + i) * nq * 8) + j;
+            const float w = bf2f(weight(i, j));
+            const bf16_t* px = (const bf16_t*)(p + at(y * STRIDE + i)) + j;
 #pragma unroll
             for (int k = 0; k < 4; ++k) v[k] = fmaf(w, bf2f(px[k * STRIDE]), v[k]);
         }
@@ -110,6 +116,13 @@ __device__ __forceinline__ void band_exact(uint2 (&o)[RO], float sc, float sh, b
         }
         o[y] = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
     }
+}
+
+// f: as for band_operand; rows of nq quads one behind the other
+template <int N, int STRIDE, int RO>
+__device__ __forceinline__ void band_exact(uint2 (&o)[RO], float sc, float sh, bool relu, const char* f, const char* p, int nq) {
+    band_exact_at<N, STRIDE, RO>(o, sc, sh, relu, [f](int i, int j) { return ((const bf16_t*)f)[i * band_row_dwords(STRIDE) * 2 + band_lead(STRIDE) + j]; }, p,
+                                 [nq](int r) { return r * nq * 8; });
 }
 
 // Four outputs of a channel after batch-norm and activation -> two of the channel pair: the lane trades half of them with

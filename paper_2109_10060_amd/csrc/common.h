@@ -266,6 +266,14 @@ int32_t ds_launch_bandpw(const bf16_t* x, int32_t B, int32_t H, int32_t W, int32
 int32_t ds_launch_sepconv(ActView x, bf16_t* y, int64_t y_ss, const bf16_t* wd, const float* sd, const float* hd, int32_t C,
                           const bf16_t* wp, const float* sp, const float* hp, int32_t F, const int32_t* slot_group,
                           const GroupTable& gt, int32_t B, int32_t H, int32_t W, int32_t stride, hipStream_t s);
+// 3x3 stride-2 stem, a separable block at stride 1 and one at stride 2 (taps x taps filters cropped from KS x KS ones) as one
+// kernel; wp0, wp1 in operand tiles.  DS_EUNSUPPORTED for shapes it is not written for
+struct FrontLayers {
+    const bf16_t *ws, *wd0, *wp0, *wd1, *wp1;
+    const float *ss, *hs, *sd0, *hd0, *sp0, *hp0, *sd1, *hd1, *sp1, *hp1;
+    int32_t C0, C1, F, KS0, KS1, taps;
+};
+int32_t ds_launch_front(const bf16_t* img, int32_t B, int32_t H, int32_t W, const FrontLayers& l, bf16_t* y, hipStream_t s);
 int32_t ds_launch_layernorm(ActView x, ActView y, const float* gamma, const float* beta, float eps,
                             const int32_t* slot_group, const GroupTable& gt, int32_t B, int32_t rows,
                             int32_t row0, int32_t n_rows, hipStream_t s);

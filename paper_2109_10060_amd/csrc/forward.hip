@@ -87,6 +87,12 @@ __global__ void unpack_slots_kernel(const bf16_t* x, int64_t x_sstride, int x_ld
     }
 }
 
+bool tapped(const Taps* taps, int id) {
+    for (int i = 0; taps && i < taps->n; ++i)
+        if (taps->ids[i] == id) return true;
+    return false;
+}
+
 // copies block `id`'s output when it is among the requested taps
 int32_t tap_block(const Taps* taps, int id, const bf16_t* x, int64_t x_sstride, int x_ld, const int32_t* perm,
                   const int32_t* slot_group, const GroupTable& gt, int B, int rows, int c_full, hipStream_t s) {
@@ -251,10 +257,32 @@ int32_t forward_mb(const ds_net* net, const MbDesc& d, const bf16_t* images, int
                    const Taps* taps) {
     const void* const* P = net->params;
     int r = (d.image + 2 - 3) / 2 + 1;
-    RC(ds_launch_stem(images, nullptr, p.bufA, (const bf16_t*)P[0], (const float*)P[1], (const float*)P[2], B, d.image,
-                      d.image, 3, 2, 1, d.stem_out, s));
     bf16_t *cur = p.bufA, *oth = p.bufB;
-    for (int i = 0; i < d.nb; ++i) {
+    // stem and the first two blocks in one kernel where the shapes allow and nobody asks for the first block's output
+    int32_t front = DS_EUNSUPPORTED;
+    if (d.tiled && d.gate_after >= 2 && d.blk[2] == 1 && d.blk[5] == 2 && !tapped(taps, 0) && (!d.kfull || d.ksize[0] == d.ksize[1])) {
+        const void* const* T = P + 3 + 6 * d.nb + 6;
+        FrontLayers l;
+        l.ws = (const bf16_t*)P[0]; l.ss = (const float*)P[1]; l.hs = (const float*)P[2];
+        l.wd0 = (const bf16_t*)P[3]; l.sd0 = (const float*)P[4]; l.hd0 = (const float*)P[5];
+        l.wp0 = (const bf16_t*)T[0]; l.sp0 = (const float*)P[7]; l.hp0 = (const float*)P[8];
+        l.wd1 = (const bf16_t*)P[9]; l.sd1 = (const float*)P[10]; l.hd1 = (const float*)P[11];
+        l.wp1 = (const bf16_t*)T[1]; l.sp1 = (const float*)P[13]; l.hp1 = (const float*)P[14];
+        l.C0 = d.blk[0]; l.C1 = d.blk[1]; l.F = d.blk[4];
+        l.KS0 = d.kfull ? d.kfull[0] : 3; l.KS1 = d.kfull ? d.kfull[1] : 3; l.taps = d.kfull ? d.ksize[0] : 3;
+        if (l.C0 == d.stem_out && l.C1 == d.blk[3]) front = ds_launch_front(images, B, d.image, d.image, l, p.bufA, s);
+        if (front != DS_OK && front != DS_EUNSUPPORTED) return front;
+    }
+    int first_block = 0;
+    if (front == DS_OK) {
+        r = (r + 2 - 3) / 2 + 1;
+        first_block = 2;
+        RC(tap_block(taps, 1, cur, (int64_t)r * r * d.blk[4], d.blk[4], nullptr, nullptr, table1(d.blk[3], d.blk[4]), B, r * r, d.blk[4], s));
+    } else {
+        RC(ds_launch_stem(images, nullptr, p.bufA, (const bf16_t*)P[0], (const float*)P[1], (const float*)P[2], B, d.image,
+                          d.image, 3, 2, 1, d.stem_out, s));
+    }
+    for (int i = first_block; i < d.nb; ++i) {
         const int ci = d.blk[3 * i], co = d.blk[3 * i + 1], st = d.blk[3 * i + 2];
         const void* const* Q = P + 3 + 6 * i;
         const int phase = i >= d.gate_after;

@@ -95,7 +95,7 @@ def traffic(fetch_csv, write_csv, copy_fetch_csv, copy_write_csv, copy_bytes, ou
 
 # kernel-name fragments -> class of the per-launch work list (cost.py)
 CLASS_OF = (("attention_kernel", "attention"), ("layernorm", "layernorm"), ("dwconv", "dwconv"), ("dwpw_kernel", "dwconv"),
-            ("dwband_kernel", "dwconv"), ("bandpw_kernel", "dwconv"), ("sepconv_kernel", "dwconv"),
+            ("dwband_kernel", "dwconv"), ("bandpw_kernel", "dwconv"), ("sepconv_kernel", "dwconv"), ("front_kernel", "dwconv"),
             ("stem_", "stem"), ("maxpool_kernel", "maxpool"))
 PEAK_TFLOPS, PEAK_GBS = 2500.0, 8000.0
 

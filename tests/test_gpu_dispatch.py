@@ -276,6 +276,49 @@ def test_mbnet_front_blocks(gpu_lib, pp, image, B):
     assert relerr(host(logits), host(want)) < 1e-2
 
 
+# The stem and the first two blocks in one kernel against the three launches (asked for by a tap of the first block's output):
+# one strip to several, narrow ones, a ragged last one; odd maps; bands of one row, of several, of all; a pixel that overflows.
+# Both sides round every layer to bf16 from fp32 sums of 27..128 products; where the sums' order differs in the stem, its last bit
+# may flip (2^-8 of a value, in fewer than 1 of 1e5 values): 1e-3 of the norm is far above that.
+@pytest.mark.parametrize("pp", [False, True])
+@pytest.mark.parametrize("image,B", [(224, 1), (224, 35), (224, 200), (216, 3), (228, 2), (100, 9), (60, 33), (28, 2)])
+def test_mbnet_first_layers_in_one_kernel(gpu_lib, pp, image, B):
+    arch = (WL.mbnet_pp_arch if pp else WL.mbnet_arch)(image=image)
+    net = gpu_lib.build_mbnet(arch, WL.mbnet_params(arch, 12), DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(image + B)
+    imgs = torch.randn((B, 3, image, image), generator=gen, device=DEV).to(torch.bfloat16)
+    over = (torch.arange(B, device=DEV, dtype=torch.int32) % arch["T"])[None].contiguous()
+    r1 = (image + 1) // 2
+    r2 = (r1 + 1) // 2
+
+    def run(x, *blocks):
+        shape = {0: (B, r1 * r1, arch["blocks"][0][1]), 1: (B, r2 * r2, arch["blocks"][1][1])}
+        taps = {i: torch.full(shape[i], float("nan"), dtype=torch.bfloat16, device=DEV) for i in blocks}
+        gpu_lib.ds_forward_taps(net, x, taps, route_override=over)
+        return taps[1].reshape(B, r2, r2, -1)
+
+    one, apart = run(imgs, 1), run(imgs, 0, 1)
+    assert torch.isfinite(one).all() and one.abs().max() > 0
+    assert (one.double() - apart.double()).norm() < 1e-3 * apart.double().norm()
+    assert torch.equal(one, run(imgs, 1))
+    # the reach of an image's pixel: 3x3 at stride 2, k x k, k x k at stride 2 (and the column left of the stem's filter)
+    bad = imgs.clone()
+    bad[B // 2, 1, image // 2, image // 2] = 3e38
+    got, k = run(bad, 1), 5 if pp else 3
+    lo = hi = image // 2
+    for half, s in ((2, 2), (k // 2, 1), (k // 2, 2)):
+        lo, hi = (lo - half) // s, -(-(hi + half) // s)
+    reach = torch.zeros((B, r2, r2), dtype=torch.bool, device=DEV)
+    reach[B // 2, max(lo, 0):hi + 1, max(lo, 0):hi + 1] = True
+    assert not torch.equal(got[reach], one[reach]) and torch.isfinite(got[~reach]).all()
+    near = torch.zeros_like(reach)
+    near[B // 2] = True
+    assert torch.equal(got[~near], one[~near])
+    a, b = got[near & ~reach].double(), one[near & ~reach].double()
+    assert (a - b).norm() <= 4e-3 * b.norm()
+
+
 # blocks behind the gate in one kernel against the layers apart: the four tiles (32 pixels and 256 or 512 filters, 64 and 112
 # pixels), maps of one row and one pixel, odd maps, a map too wide for a tile next to one that is not
 @pytest.mark.parametrize("image,B", [(224, 2), (224, 20), (224, 50), (224, 70), (224, 140), (150, 33), (34, 9), (640, 1)])
