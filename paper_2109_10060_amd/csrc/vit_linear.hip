@@ -5,12 +5,18 @@
 // A workgroup owns BM = 32 R token rows (whole rows: the LayerNorm is computed in place, the arithmetic of
 // layernorm16_kernel) and a run of 32-column blocks of the output, NW at a time, one per wavefront.  A wavefront reads its
 // weight operands as contiguous kilobytes straight into registers, D in flight, so neither the weights nor the partial
-// sums touch LDS; finished blocks leave through an LDS tile as 16-byte pieces of whole row runs.
-// Two uses.  Large batches: the Q/K/V layer with 12 wavefronts and 96 or 64 rows, all columns in one workgroup (the rows
-// are read once; gemm_kernel read them once per 64 columns).  Few images: all four layers of a block with 4 wavefronts and
-// 32 rows, where a launch is bound by latency and by how many compute units share the weights' way in; the LayerNorm
-// launches disappear.  A LayerNorm there is a chain in front of the products: its weights are asked for beside the rows and its sums
-// run over rotations within 16 lanes instead of exchanges through LDS (rows and LayerNorm 3.4 -> 2 us of a launch of 7.5).
+// sums touch LDS.  Two uses.
+// Large batches: the Q/K/V layer with 8 wavefronts and 64 rows, all columns in one workgroup (the rows are read once;
+// gemm_kernel read them once per 64 columns).  A finished block is traded between the halves of the wavefront and stored from
+// its registers, 16 bytes a lane (DIRECT): pieces of 64 bytes where a stage in LDS would make whole lines, but without the stage
+// two workgroups share a compute unit, one normalises rows while the other multiplies, and no wavefront waits for another
+// between blocks.  Us a pass, 12 wavefronts, 64 or 96 rows and a stage -> here: DS-ViT 64 images 1058 -> 1041, 140 images 1697
+// -> 1657, 256 images 2663 -> 2643; DS-ViT++ 64 images 1418 -> 1396, 256 images 3947 -> 3801 (eight operands in flight instead of four
+// 3760, but the others 1049, 1681, 2652 and 1399; 32 rows 256 images 2700 and 3906).
+// Few images: all four layers of a block with 4 wavefronts and 32 rows, where a launch is bound by latency and by how many
+// compute units share the weights' way in; finished blocks leave through an LDS tile as 16-byte pieces of whole row runs.  The
+// LayerNorm launches disappear.  A LayerNorm there is a chain in front of the products: its weights are asked for beside the rows
+// and its sums run over rotations within 16 lanes instead of exchanges through LDS (rows and LayerNorm 3.4 -> 2 us of a launch of 7.5).
 // Sums are in gemm_kernel's order: the same bits.
 #include "gelu.h"
 #include "vit_rows.h"
@@ -18,9 +24,9 @@
 
 namespace {
 
-// KM: channels of the reduction, at most.  FEW: a launch of a few images, a chain of latencies: everything asked for as early as it can be
-template <int NW, int R, int D, int KM, bool FEW>
-__global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const VitLinearArgs a, const int runs, const int run_blocks) {
+// KM: channels of the reduction, at most.  DIRECT: stores from registers (no residual, no activation).  FEW: a launch of a few images, a chain of latencies: everything asked for as early as it can be
+template <int NW, int R, int D, int KM, bool FEW, bool DIRECT>
+__global__ __launch_bounds__(64 * NW, DIRECT ? NW / 2 : (NW + 3) / 4) void vit_linear_kernel(const VitLinearArgs a, const int runs, const int run_blocks) {
     constexpr int PITCH = tile_pitch(KM, D);
     constexpr int BM = 32 * R, SP = 32 * NW + 8, RP = 4 * NW, NI = (BM + RP - 1) / RP, KIT = (PITCH - 8 + 127) / 128, NS = 4 * NW;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -104,6 +110,80 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
         }
     }
 
+    // the products of column block p; every step is straight-line code, the operands of the next one on their way
+    auto walk = [&](f32x16_t (&acc)[R], int p) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t rw = weights(p);
+        const bf16_t* base = As + l32 * PITCH + lhi * 8;
+        bf16x8_t f[2][R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) f[0][r] = *(const bf16x8_t*)(base + r * 32 * PITCH);
+        uint32_t off = lane16 + D * 1024;
+        for (int k0 = 0; k0 < kin; k0 += 16 * D, off += D * 1024) {       // rounded up to D: zero weights, zeros behind the slice (tile_pitch)
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) f[(j + 1) & 1][r] = *(const bf16x8_t*)(base + r * 32 * PITCH + k0 + (j + 1) * 16);
+#pragma unroll
+                for (int r = 0; r < R; ++r) acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[j], f[j & 1][r], acc[r], 0, 0, 0);
+                ring[j] = weight_tile(rw, off + j * 1024);
+                __builtin_amdgcn_sched_barrier(0);       // (the compiler would sink the reads to their use)
+            }
+        }
+    };
+    auto clear = [](f32x16_t (&acc)[R]) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[r][v] = 0.f;
+    };
+    if constexpr (DIRECT) {
+        // ---- column blocks, each wavefront its own: no stage, so no wavefront waits for another ----
+        __syncthreads();
+        bf16_t* yrow[R];
+        bool in[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int m = grow0 + r * 32 + l32;
+            in[r] = m < rows_g;
+            const int mm = in[r] ? m : grow0, sl = mm / rows;
+            yrow[r] = y + (int64_t)(slot0 + sl) * y_ss + (int64_t)(mm - sl * rows) * y_ld;
+        }
+        for (int p = blk0 + w; p < blk1; p += NW) {
+            const int seg = p / nb, n0 = (p - seg * nb) * 32;
+            f32x16_t acc[R];
+            clear(acc);
+            walk(acc, p);
+            if (p + NW < blk1) start(p + NW);
+            const float* bias = bias0 + (int64_t)seg * bias_seg;
+            const int64_t so = (int64_t)seg * y_seg;
+#pragma unroll
+            for (int q = 0; q < 4; q += 2) {
+                float4 h[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const int n = n0 + 8 * (q + e) + 4 * lhi;
+                    h[e] = n < k_out ? *(const float4*)(bias + n) : make_float4(0.f, 0.f, 0.f, 0.f);
+                }
+                const int n = n0 + 8 * q + 8 * lhi;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    uint32_t lo[2], hi[2];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const f32x16_t& t = acc[r];
+                        const int b = 4 * (q + e);
+                        lo[e] = f2bf2(t[b] + h[e].x, t[b + 1] + h[e].y);
+                        hi[e] = f2bf2(t[b + 2] + h[e].z, t[b + 3] + h[e].w);
+                    }
+                    // channels 8 q .. + 7 to the lower half's lane, the next eight to the upper half's
+                    const auto a0 = __builtin_amdgcn_permlane32_swap(lo[0], lo[1], false, false);
+                    const auto a1 = __builtin_amdgcn_permlane32_swap(hi[0], hi[1], false, false);
+                    if (in[r] && n < k_out) *(uint4*)(yrow[r] + so + n) = make_uint4(a0[0], a1[0], a0[1], a1[1]);
+                }
+            }
+        }
+        return;
+    }
     // ---- column blocks, NW at a time ------------------------------------------------------------------------------------------
     for (int b0 = blk0; b0 < blk1; b0 += NW) {
         const int p = b0 + w, seg = p / nb, n0 = (p - seg * nb) * 32;
@@ -122,12 +202,8 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
         }
         __syncthreads();                                 // rows (and residual) are in place
         f32x16_t acc[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[r][v] = 0.f;
+        clear(acc);
         if (on) {
-            const __amdgpu_buffer_rsrc_t rw = weights(p);
             const float* bias = bias0 + (int64_t)seg * bias_seg;
             float4 hb[FEW ? 4 : 1];
             if constexpr (FEW) {
@@ -137,22 +213,7 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
                     hb[q] = n < k_out ? *(const float4*)(bias + n) : make_float4(0.f, 0.f, 0.f, 0.f);
                 }
             }
-            const bf16_t* base = As + l32 * PITCH + lhi * 8;
-            bf16x8_t f[2][R];
-#pragma unroll
-            for (int r = 0; r < R; ++r) f[0][r] = *(const bf16x8_t*)(base + r * 32 * PITCH);
-            uint32_t off = lane16 + D * 1024;
-            for (int k0 = 0; k0 < kin; k0 += 16 * D, off += D * 1024) {   // rounded up to D: zero weights, zeros behind the slice (tile_pitch)
-#pragma unroll
-                for (int j = 0; j < D; ++j) {
-#pragma unroll
-                    for (int r = 0; r < R; ++r) f[(j + 1) & 1][r] = *(const bf16x8_t*)(base + r * 32 * PITCH + k0 + (j + 1) * 16);
-#pragma unroll
-                    for (int r = 0; r < R; ++r) acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[j], f[j & 1][r], acc[r], 0, 0, 0);
-                    ring[j] = weight_tile(rw, off + j * 1024);
-                    __builtin_amdgcn_sched_barrier(0);   // (the compiler would sink the reads to their use)
-                }
-            }
+            walk(acc, p);
             if (p + NW < blk1) start(p + NW);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -192,15 +253,15 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_linear_kernel(const
     }
 }
 
-template <int NW, int R, int D, int KM, bool FEW>
+template <int NW, int R, int D, int KM, bool FEW, bool DIRECT = false>
 int32_t launch(const VitLinearArgs& a, int64_t tiles, int max_blocks, int run_blocks, hipStream_t s) {
-    constexpr int SMEM = 32 * R * (tile_pitch(KM, D) + 32 * NW + 8) * 2;
+    constexpr int SMEM = 32 * R * (tile_pitch(KM, D) + (DIRECT ? 0 : 32 * NW + 8)) * 2 + (DIRECT ? 32 : 0);
     static_assert(SMEM <= 160 * 1024, "LDS of a compute unit");
-    const int32_t rc = ds_reserve_lds((const void*)vit_linear_kernel<NW, R, D, KM, FEW>, SMEM, "tiled linear layer");
+    const int32_t rc = ds_reserve_lds((const void*)vit_linear_kernel<NW, R, D, KM, FEW, DIRECT>, SMEM, "tiled linear layer");
     if (rc) return rc;
     const int runs = (max_blocks + run_blocks - 1) / run_blocks;
     ProfScope prof(DS_K_VIT_LINEAR, s);
-    hipLaunchKernelGGL((vit_linear_kernel<NW, R, D, KM, FEW>), dim3((unsigned)(tiles * runs)), dim3(64 * NW), SMEM, s, a, runs, run_blocks);
+    hipLaunchKernelGGL((vit_linear_kernel<NW, R, D, KM, FEW, DIRECT>), dim3((unsigned)(tiles * runs)), dim3(64 * NW), SMEM, s, a, runs, run_blocks);
     DS_CHECK_LAUNCH("tiled linear layer");
     return DS_OK;
 }
@@ -208,8 +269,9 @@ int32_t launch(const VitLinearArgs& a, int64_t tiles, int max_blocks, int run_bl
 }  // namespace
 
 // Measured on DS-ViT's Q/K/V layer with its LayerNorm (us, profiles/dispatch_choices.txt): 1 / 5 / 9 / 16 images with 4 column blocks
-// a workgroup 6.6 / 8.0 / 9.6 / 15.0, 8 blocks 9.2 / 9.6 / 10.8 / 12.3; 64 images with 12 wavefronts and 64 rows 23.2, 96 rows
-// 27.0, 4 wavefronts and 32 rows 29.9; 256 images 57.5 with 64 rows, 54.5 with 96.  Reductions beyond 416 channels (fc2) are for the few-image path alone: 113 KiB of rows.
+// a workgroup 6.6 / 8.0 / 9.6 / 15.0, 8 blocks 9.2 / 9.6 / 10.8 / 12.3.  From 160 tiles of 64 rows on the
+// large form: a pass of DS-ViT of 36 / 42 / 48 images, the line at 100 tiles 885 / 894 / 981, at 160 899 / 894 / 981, at 200 900 / 921 / 1017;
+// DS-ViT++ 36 / 46 / 60 images 1262 / 1294 / 1351, 1232 / 1305 / 1352, 1233 / 1305 / 1405.  Reductions beyond 416 channels (fc2) are for the few-image path alone: 113 KiB of rows.
 int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s) {
     int kmax = 0, nmax = 0;
     for (int t = 0; t < a.gt.T; ++t) {
@@ -223,8 +285,13 @@ int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s) {
     auto tiles = [&](int bm) { return (n - groups) / bm + groups; };
     const int blocks = (nmax + 31) / 32 * a.n_seg;
     if (kmax <= VIT_K_MAX) {
-        if (tiles(96) >= 448) return launch<12, 3, 4, VIT_K_MAX, false>(a, tiles(96), blocks, blocks, s);
-        if (tiles(64) >= 160) return launch<12, 2, 4, VIT_K_MAX, false>(a, tiles(64), blocks, blocks, s);
+        if (!a.res && a.act == DS_ACT_NONE && tiles(64) >= 160) {
+            // parts of a batch, each with a workgroup a compute unit at most: two small ones would share the compute units that the other
+            // part leaves free.  DS-ViT in two parts, 8 / 12 wavefronts: 96 images 1410 / 1319, 128 images 1420 / 1333; 160 images 1670 / 1663,
+            // 200 images 1891 / 1934, 256 images 2316 / 2525
+            if (a.crowd > 1 && tiles(64) <= 256) return launch<12, 2, 4, VIT_K_MAX, false>(a, tiles(64), blocks, blocks, s);
+            return launch<8, 2, 4, VIT_K_MAX, false, true>(a, tiles(64), blocks, blocks, s);
+        }
         // (the early requests cost 50 registers, a third of the workgroups a compute unit holds: not where there are enough of them,
         // nor beside the launches of a batch's other parts -- 1 / 5 / 16 images 494 / 562 / 673 us a pass, 506 / 569 / 690 without them; 64
         // images in four parts 1181 with them, 1101 without; 24 images, beyond the line, 805 either way)

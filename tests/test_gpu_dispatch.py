@@ -191,6 +191,23 @@ def test_vit_logits_do_not_depend_on_the_batch(gpu_lib, big):
     assert torch.equal(plain, full)
 
 
+# Q/K/V of a part: up to a workgroup a compute unit through an LDS stage, beyond it from registers; slices that end inside a
+# 32-column block (five and seven heads of 48 channels): the same bits as the batch whole
+@pytest.mark.parametrize("big", [False, True])
+@pytest.mark.parametrize("B,parts", [(104, 2), (129, 2), (180, 2), (250, 4)])
+def test_vit_parts_have_the_bits_of_the_batch(gpu_lib, big, B, parts):
+    kw = dict(embed=416, heads=8, head_dim=48, mlp=1664, depth=2, routes="pp") if big else dict(depth=2)
+    arch = WL.vit_arch(**kw)
+    net = gpu_lib.build_vit(arch, WL.vit_params(arch, 6), DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(B)
+    imgs = torch.randn((B, 3, arch["image"], arch["image"]), generator=gen, device=DEV).to(torch.bfloat16)
+    over = (torch.arange(B, device=DEV, dtype=torch.int32) * 5 % arch["T"])[None].contiguous()
+    whole, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
+    shares, _ = gpu_lib.ds_forward_parts(net, imgs, parts, route_override=over)
+    assert torch.isfinite(whole).all() and relerr(host(shares), host(whole)) < 1e-5       # (the classifier's sums, as above)
+
+
 # hidden activations around the limits of the GELU's short evaluation: every bf16 result equals the exact one's
 def test_gelu_rounding_matches_the_linear_layer(gpu_lib):
     arch = WL.vit_arch(depth=1)
