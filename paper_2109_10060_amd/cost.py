@@ -179,6 +179,14 @@ def resnet_cost(arch, routes) -> Cost:
         chain = bool(mids.max() <= 128 and outs.max() >= 128 and not (mids % 8).any() and not (outs % 8).any()
                      and not _few_samples(B, rs * rs, groups, int(outs.max()))
                      and _tiles(B, rs * rs, groups) >= (150 if mids.max() <= 64 else 400))
+        # 3x3 layer, last convolution and the next block's first one of a stride-1 block as one launch, in the first stage's first
+        # block with the projection too
+        fits = lambda nb_: mids.max() <= 32 * nb_ and outs.max() <= 128 * nb_ and _tiles(B, rs * rs, groups) >= (40 if nb_ == 2 else 300)  # noqa: E731
+        rest = bool(rs <= 59 and not (mids % 8).any() and not (outs % 8).any() and fits(2 if mids.max() <= 64 else 4))
+        # few samples: the first layer of a stage is one launch with the projection
+        paired = _paired(_tiles(B, rs * rs, groups, 32) * -(-int(outs.max()) // 32), _tiles(B, r * r, groups, 32) * -(-int(mids.max()) // 32),
+                         -(-int(arch["out"][s - 1].max() if s else so) // 64))
+        inside = bool(rest and s == 0 and so <= 64 and so % 8 == 0 and mids.max() <= 64 and not paired)
         for b in range(nb):
             # dynamic depth: samples whose route has run its blocks of this stage contribute nothing
             on = (arch["nblk"][s][routes[s]] > b).astype(np.float64) if arch.get("nblk") is not None else np.ones(B)
@@ -188,15 +196,16 @@ def resnet_cost(arch, routes) -> Cost:
             ro = _osz(r, 3, stride, 1)
             cin = (cprev if b == 0 else out) * on
             m, o = mid * on, out * on
-            if b == 0:
+            one = rest and stride == 1
+            if b == 0 and not inside:
                 _gemm(c, "gemm", ro * ro, ro * ro, 1, cin, o, name=f"s{s}.b{b}.proj")      # 1x1 projection reads only the strided pixels
-            # few samples: the first layer of a stage is one launch with the projection
-            paired = b == 0 and _paired(_tiles(B, ro * ro, groups, 32) * -(-int(outs.max()) // 32),
-                                        _tiles(B, r * r, groups, 32) * -(-int(mids.max()) // 32),
-                                        -(-int(arch["out"][s - 1].max() if s else so) // 64))
-            _gemm(c, "gemm", r * r, r * r, 1, cin, m, chained=chain and b > 0 or paired, name=f"s{s}.b{b}.c1")
-            _gemm(c, "gemm_taps", r * r, ro * ro, 9, m, m, name=f"s{s}.b{b}.c2 3x3" + ("/2" if stride == 2 else ""))
-            _gemm(c, "gemm", ro * ro, ro * ro, 1, m, o, residual=True, name=f"s{s}.b{b}.c3+res")
+            _gemm(c, "gemm", r * r, r * r, 1, cin, m, chained=(rest and b > (s > 0) or chain) and b > 0 or b == 0 and paired,
+                  name=f"s{s}.b{b}.c1")
+            _gemm(c, "gemm" if one else "gemm_taps", r * r, ro * ro, 9, m, m, name=f"s{s}.b{b}.c2 3x3" + ("/2" if stride == 2 else ""))
+            if b == 0 and inside:
+                c.add("gemm", 2.0 * ro * ro * np.sum(cin * o), 2.0 * r * r * np.sum(cin) + 2.0 * float(cin.max() * o.max()), name=f"s{s}.b{b}.proj",
+                      merge=True)
+            _gemm(c, "gemm", ro * ro, ro * ro, 1, m, o, residual=not (b == 0 and inside), chained=one, name=f"s{s}.b{b}.c3" + ("" if b == 0 and inside else "+res"))
             r = ro
         cprev = out
     c.add("head", 2.0 * arch["num_classes"] * cprev.sum(),

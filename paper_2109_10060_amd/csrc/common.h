@@ -186,6 +186,27 @@ int32_t ds_launch_gemm_small_pair(const GemmArgs& a, int32_t mtiles_a, int32_t k
                                   hipStream_t s);
 // 3x3 stride-1 padding-1 layers on maps up to 59 pixels wide; DS_EUNSUPPORTED for any other shape
 int32_t ds_launch_conv3(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s);
+// the rest of a bottleneck block behind its first 1x1 layer (stride 1, packed rows, slot order): 3x3 layer, last 1x1 layer with its
+// shortcut, the next block's first 1x1 layer; every one with batch-norm and ReLU.  DS_EUNSUPPORTED for shapes it is not written for and
+// launches too small for it
+struct BneckArgs {
+    const bf16_t *y1, *w2, *w3, *w1;     // input; filters [mid_full][3][3][mid_full], [][mid_full], next block's [][out_full] (nullable)
+    const float *s2, *h2, *s3, *h3, *s1, *h1;   // tables [row][mid_full], [row][tab3], [row][mid_full]
+    const bf16_t* shortcut;              // addressed like z, may be z; or
+    const bf16_t *x, *wp;                // (x not null) the stage's input and the projection's filters [][x_full]
+    const float *sp, *hp;                // its tables [row][tab3]
+    const int32_t* x_index;              // slot -> block of x
+    bf16_t *z, *y1_next;
+    int64_t y1_ss, z_ss, x_ss;           // elements per slot (y1_next as y1)
+    int32_t mid_full, out_full, x_full, tab3, H, W;
+    const int4* mtiles;
+    const int32_t* n_mtiles;
+    int32_t crowd;                       // as in GemmArgs
+    GroupTable gt;                       // k_in = mid slice, k_out = output slice
+    int32_t kx[DS_MAX_GROUPS], next[DS_MAX_GROUPS];   // slice of x; slice of the next block's first layer (<= 0: none)
+};
+bool ds_bneck_runs(const BneckArgs& a, int32_t B, int32_t max_mtiles);
+int32_t ds_launch_bneck(const BneckArgs& a, int32_t B, int32_t max_mtiles, hipStream_t s);
 
 static inline const int4* ds_mtile_entries(const void* list) { return (const int4*)((const char*)list + 16); }
 static inline const int32_t* ds_mtile_count(const void* list) { return (const int32_t*)list; }

@@ -601,31 +601,6 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
             const int32_t* in_idx = first ? src : nullptr;
             const int64_t in_ss = first ? x_ss : (int64_t)rout * rout * 4 * w;
             const int in_full = first ? c_prev_full : 4 * w;
-            const bf16_t* shortcut;
-            if (first) {
-                const GemmArgs pj = conv_args(in, in_idx, in_ss, 0, (const bf16_t*)L[9], in_full, 1, bs, 0, rb, rb, (const float*)L[10],
-                                              (const float*)L[11], 4 * w, nullptr, Pj, (int64_t)rout * rout * 4 * w, 0, p.offs[st],
-                                              ml_out, gpj, DS_ACT_NONE);
-                // few samples: both layers that read the stage's input as one launch
-                const GemmArgs c1 = conv_args(in, in_idx, in_ss, 0, (const bf16_t*)L[0], in_full, 1, 1, 0, rb, rb, (const float*)L[1],
-                                              (const float*)L[2], w, nullptr, Y1, (int64_t)rb * rb * w, 0, p.offs[st], ml_in, g1f,
-                                              DS_ACT_RELU);
-                const int32_t rc = ds_launch_gemm_small_pair(pj, ml_out.cap, max_out(gpj), c1, ml_in.cap, max_out(g1f), s);
-                if (rc != DS_OK && rc != DS_EUNSUPPORTED) return rc;
-                y1_ready = rc == DS_OK;
-                if (!y1_ready) RC(launch_conv(pj, ml_out, s));
-                shortcut = Pj;
-            } else {
-                shortcut = Z;
-            }
-            if (!y1_ready)
-                RC(conv_gemm(in, in_idx, in_ss, 0, (const bf16_t*)L[0], in_full, 1, 1, 0, rb, rb, (const float*)L[1],
-                             (const float*)L[2], w, nullptr, Y1, (int64_t)rb * rb * w, 0, p.offs[st], first ? ml_in : ml_out,
-                             first ? g1f : g1, DS_ACT_RELU, s));
-            y1_ready = false;
-            RC(conv_gemm(Y1, nullptr, (int64_t)rb * rb * w, 0, (const bf16_t*)L[3], w, 3, bs, 1, rb, rb, (const float*)L[4],
-                         (const float*)L[5], w, nullptr, Y2, (int64_t)rout * rout * w, 0, p.offs[st], ml_out, g2,
-                         DS_ACT_RELU, s));
             // the next block's first convolution reads the rows this block's last one writes: where the slices are
             // narrow enough the two run as one launch and Y1 is ready when the next block starts
             ThinChain ch;
@@ -642,10 +617,74 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
                     next_any = next_any || on;
                 }
             }
-            // c3 adds the shortcut; later blocks update Z in place (each element is read and written by one thread)
-            RC(conv_gemm(Y2, nullptr, (int64_t)rout * rout * w, 0, (const bf16_t*)L[6], w, 1, 1, 0, rout, rout,
-                         (const float*)L[7], (const float*)L[8], 4 * w, shortcut, Z, (int64_t)rout * rout * 4 * w, 0,
-                         p.offs[st], ml_out, g3, DS_ACT_RELU, s, next_any ? &ch : nullptr, &y1_ready));
+            // stride 1: everything behind the first convolution as one launch where the slices are narrow; the next block's first
+            // convolution then goes to Y2, since neighbouring rows of Y1 are still being read
+            BneckArgs bn;
+            memset(&bn, 0, sizeof(bn));
+            if (bs == 1) {
+                bn.y1 = Y1; bn.w2 = (const bf16_t*)L[3]; bn.s2 = (const float*)L[4]; bn.h2 = (const float*)L[5];
+                bn.w3 = (const bf16_t*)L[6]; bn.s3 = (const float*)L[7]; bn.h3 = (const float*)L[8];
+                bn.z = Z; bn.y1_ss = (int64_t)rout * rout * w; bn.z_ss = (int64_t)rout * rout * 4 * w;
+                bn.mid_full = w; bn.out_full = bn.tab3 = 4 * w; bn.H = bn.W = rout;
+                bn.mtiles = ds_mtile_entries(ml_out.list); bn.n_mtiles = ds_mtile_count(ml_out.list); bn.crowd = crowd; bn.gt = g3;
+                if (next_any) {
+                    bn.w1 = ch.Wt; bn.s1 = ch.scale; bn.h1 = ch.shift; bn.y1_next = Y2;
+                    memcpy(bn.next, ch.k_out, sizeof(bn.next));
+                }
+            }
+            const bf16_t* shortcut = Z;
+            int32_t rest = DS_EUNSUPPORTED;        // whether the layers behind the first one have run
+            if (first) {
+                const GemmArgs pj = conv_args(in, in_idx, in_ss, 0, (const bf16_t*)L[9], in_full, 1, bs, 0, rb, rb, (const float*)L[10],
+                                              (const float*)L[11], 4 * w, nullptr, Pj, (int64_t)rout * rout * 4 * w, 0, p.offs[st],
+                                              ml_out, gpj, DS_ACT_NONE);
+                // few samples: both layers that read the stage's input as one launch
+                const GemmArgs c1 = conv_args(in, in_idx, in_ss, 0, (const bf16_t*)L[0], in_full, 1, 1, 0, rb, rb, (const float*)L[1],
+                                              (const float*)L[2], w, nullptr, Y1, (int64_t)rb * rb * w, 0, p.offs[st], ml_in, g1f,
+                                              DS_ACT_RELU);
+                const int32_t rc = ds_launch_gemm_small_pair(pj, ml_out.cap, max_out(gpj), c1, ml_in.cap, max_out(g1f), s);
+                if (rc != DS_OK && rc != DS_EUNSUPPORTED) return rc;
+                y1_ready = rc == DS_OK;
+                if (!y1_ready && bs == 1) {
+                    // the projection inside the rest of the block
+                    bn.x = in; bn.x_index = in_idx; bn.x_ss = in_ss; bn.x_full = in_full;
+                    bn.wp = (const bf16_t*)L[9]; bn.sp = (const float*)L[10]; bn.hp = (const float*)L[11];
+                    memcpy(bn.kx, gpj.k_in, sizeof(bn.kx));
+                    if (ds_bneck_runs(bn, B, ml_out.cap)) {
+                        RC(launch_conv(c1, ml_in, s));
+                        y1_ready = true;
+                        rest = ds_launch_bneck(bn, B, ml_out.cap, s);
+                        if (rest != DS_OK) return rest;
+                    }
+                    bn.x = nullptr;
+                }
+                if (!y1_ready) RC(launch_conv(pj, ml_out, s));
+                shortcut = Pj;
+            }
+            if (!y1_ready)
+                RC(conv_gemm(in, in_idx, in_ss, 0, (const bf16_t*)L[0], in_full, 1, 1, 0, rb, rb, (const float*)L[1],
+                             (const float*)L[2], w, nullptr, Y1, (int64_t)rb * rb * w, 0, p.offs[st], first ? ml_in : ml_out,
+                             first ? g1f : g1, DS_ACT_RELU, s));
+            y1_ready = false;
+            if (rest != DS_OK && bs == 1) {
+                bn.shortcut = shortcut;
+                rest = ds_launch_bneck(bn, B, ml_out.cap, s);
+                if (rest != DS_OK && rest != DS_EUNSUPPORTED) return rest;
+            }
+            if (rest == DS_OK) {
+                if (next_any) {
+                    bf16_t* t = Y1; Y1 = Y2; Y2 = t;
+                    y1_ready = true;
+                }
+            } else {
+                RC(conv_gemm(Y1, nullptr, (int64_t)rb * rb * w, 0, (const bf16_t*)L[3], w, 3, bs, 1, rb, rb, (const float*)L[4],
+                             (const float*)L[5], w, nullptr, Y2, (int64_t)rout * rout * w, 0, p.offs[st], ml_out, g2,
+                             DS_ACT_RELU, s));
+                // c3 adds the shortcut; later blocks update Z in place (each element is read and written by one thread)
+                RC(conv_gemm(Y2, nullptr, (int64_t)rout * rout * w, 0, (const bf16_t*)L[6], w, 1, 1, 0, rout, rout,
+                             (const float*)L[7], (const float*)L[8], 4 * w, shortcut, Z, (int64_t)rout * rout * 4 * w, 0,
+                             p.offs[st], ml_out, g3, DS_ACT_RELU, s, next_any ? &ch : nullptr, &y1_ready));
+            }
             RC(tap_block(taps, block_id, Z, (int64_t)rout * rout * 4 * w, 0, p.perm[st], p.slot_group[st], gpj, B, rout * rout,
                          4 * w, s));
         }

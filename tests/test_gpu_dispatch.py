@@ -451,3 +451,40 @@ def test_resnet_paired_layers(gpu_lib, image, B):
         a, b = host(torch.where(n, t, 0)), host(torch.where(n, ref[i][:B], 0))
         assert np.linalg.norm(a - b) < 2.0 ** -9 * (4 * (i + 1)) ** 0.5 * np.linalg.norm(b) and relerr_max(a, b) < TOL_BF16, i
     assert relerr_max(host(logits), host(want)[:B]) < TOL_BF16
+
+
+# the rest of a bottleneck block as one launch (projection inside, next block's first layer behind) against the separate launches of
+# one image: both slice limits, the widest map, odd maps, maps smaller than a tile, routes of different depth, narrow networks
+@pytest.mark.parametrize("which,image,B", [("width", 224, 2), ("width", 224, 60), ("width", 236, 50), ("width", 150, 130), ("width", 50, 300),
+                                           ("pp", 224, 33), ("pp", 224, 60), ("pp", 129, 150), ("depth", 224, 56), ("half", 224, 60), ("half", 90, 90)])
+def test_resnet_rest_of_a_block(gpu_lib, which, image, B):
+    kw = {"width": {}, "pp": dict(blocks=(3, 4, 8, 3), routes="pp"), "depth": dict(routes="depth"), "half": dict(width_div=2)}[which]
+    arch = WL.resnet_arch(image=image, **kw)
+    net = gpu_lib.build_resnet(arch, WL.resnet_params(arch, 29), DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(image + B)
+    kinds = min(B, 2 * arch["T"])
+    imgs = torch.randn((kinds, 3, image, image), generator=gen, device=DEV).to(torch.bfloat16)
+    n = torch.arange(kinds, device=DEV, dtype=torch.int32)
+    over = torch.stack([(n + st * (not arch.get("single_gate"))) % arch["T"] for st in range(4)])
+    blocks = arch["blocks"][0] + arch["blocks"][1]
+
+    def run(which):
+        taps, r = {}, ((image + 1) // 2 + 1) // 2
+        for i in range(blocks):
+            st = int(i >= arch["blocks"][0])
+            rb = (r - 1) // 2 + 1 if st else r
+            taps[i] = torch.zeros((len(which), rb * rb, int(arch["out"][st].max())), dtype=torch.bfloat16, device=DEV)
+        return taps, gpu_lib.ds_forward_taps(net, imgs[which].contiguous(), taps, route_override=over[:, which].contiguous())[0]
+
+    got, logits = run(torch.arange(B, device=DEV) % kinds)
+    assert torch.isfinite(logits).all()
+    for k in range(kinds):
+        ref, want = run(torch.tensor([k], device=DEV))
+        for i, t in got.items():
+            # up to 4 roundings a block before it may go the other way: 2^-9 sqrt(4 (i + 1)) in the 2-norm if all of them did
+            b = host(ref[i][0])
+            for j in range(k, B, max(kinds, (B - k - 1) // kinds * kinds)):      # the image's first and last place
+                a = host(t[j])
+                assert np.linalg.norm(a - b) < 2.0 ** -9 * (4 * (i + 1)) ** 0.5 * np.linalg.norm(b) and relerr_max(a, b) < TOL_BF16, (i, k, j)
+        assert relerr_max(host(logits[k]), host(want[0])) < TOL_BF16
