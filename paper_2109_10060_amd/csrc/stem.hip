@@ -13,6 +13,8 @@
 
 namespace {
 
+constexpr int STEM_POOL_ROWS = 3;              // pooled rows of a tile of the fused stem and max-pool
+
 typedef short i16x2_t __attribute__((ext_vector_type(2)));
 
 // Input patch of one tile: 3 x PR rows of PC pixels, fetched as 8-byte pieces.  Which piece a thread
@@ -23,37 +25,36 @@ template <int PR, int PC, int NTH, int XOFF>
 struct PatchLoader {
     static constexpr int NCH = 3 * PR * (PC / 4), NL = (NCH + NTH - 1) / NTH;
     static constexpr uint32_t OOB = 0x80000000u;
-    int r[NL], x[NL], plane[NL], lds[NL];
+    int at[NL], rx[NL];                               // offset in the image; patch row, column in the upper half (NCH and beyond: a row too far)
     uint2 v[NL];
     __device__ void init(int tid, int H, int W) {
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
             const int c = tid + i * NTH;
             const int row = c / (PC / 4), ch = c - row * (PC / 4);
-            const int cc = row / PR;
-            r[i] = row - cc * PR;
-            x[i] = ch * 4 - XOFF;
-            plane[i] = cc * H * W;
-            lds[i] = c < NCH ? row * PC + ch * 4 : -1;
+            const int cc = row / PR, r = row - cc * PR;
+            at[i] = cc * H * W + r * W + ch * 4 - XOFF;
+            rx[i] = c < NCH ? r | ch << 18 : 0x7fff;
         }
     }
     // iy0, ix0: image row / column of patch row 0 / the patch's column XOFF
     __device__ void issue(const bf16_t* img, int sample, int iy0, int ix0, int H, int W) {
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
             (void*)(img + (int64_t)sample * 3 * H * W), 0, 0x7fffffff, 0x00020000);
+        const int o = iy0 * W + ix0;
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-            const int iy = iy0 + r[i], col0 = ix0 + x[i];
-            const bool ok = lds[i] >= 0 && iy >= 0 && iy < H && col0 >= 0 && col0 + 3 < W;
-            const uint32_t off = ok ? (uint32_t)((plane[i] + iy * W + col0) * 2) : OOB;
-            const auto t = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)off, 0, 0);
+            const int r = rx[i] & 0xffff, iy = iy0 + r, col0 = ix0 - XOFF + (rx[i] >> 16);
+            const bool ok = r < PR && iy >= 0 && iy < H && col0 >= 0 && col0 + 3 < W;
+            const auto t = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)(ok ? (uint32_t)((at[i] + o) * 2) : OOB), 0, 0);
             v[i] = make_uint2(t[0], t[1]);
         }
     }
-    __device__ void store(bf16_t* patch) const {
+    // (pieces go row by row, so piece c is at 4 c)
+    __device__ void store(bf16_t* patch, int tid) const {
 #pragma unroll
         for (int i = 0; i < NL; ++i)
-            if (lds[i] >= 0) *(uint2*)(patch + lds[i]) = v[i];
+            if (tid + i * NTH < NCH) *(uint2*)(patch + (tid + i * NTH) * 4) = v[i];
     }
 };
 
@@ -118,7 +119,7 @@ __global__ __launch_bounds__(256) void stem_mfma_kernel(const bf16_t* __restrict
         const int oy0 = ty * TH, ox0 = tx * TW;
         fetch(tile);      // all pieces in flight together
         __syncthreads();  // filter bank ready / previous patch no longer read
-        pl.store(patch);
+        pl.store(patch, tid);
         __syncthreads();
         f32x16_t acc[NTILES];
 #pragma unroll
@@ -169,72 +170,92 @@ __global__ __launch_bounds__(256) void stem_mfma_kernel(const bf16_t* __restrict
 }
 
 // 7x7 stride-2 stem fused with the 3x3 stride-2 padding-1 max-pool that follows it (the ResNet
-// layout): the 112x112 map is never written.  A workgroup of 5 wavefronts computes the 9 x 17
-// convolution pixels (153 of its 160 matrix rows) under a 4 x 8 tile of pooled pixels, applies
+// layout): the 112x112 map is never written.  A workgroup of 4 wavefronts computes the 7 x 17
+// convolution pixels (119 of its 128 matrix columns) under a 3 x 8 tile of pooled pixels, applies
 // batch-norm and ReLU, rounds to bf16 (the value the unfused path would have stored) into LDS,
 // and pools from there with 16-byte stores.  Convolution pixels outside the map are stored as 0:
 // after the ReLU every value is >= 0 and every pooling window holds at least its centre pixel,
 // so 0 acts as the pool's padding.
+// The filter bank is repacked in LDS once (eight filters of a tap a load) and then lives in registers, 88 of a lane's: read from LDS
+// for every tile it was two thirds of the LDS traffic, which bounded the kernel.  The next patch goes to a second buffer, two
+// barriers a tile.  256 / 33 / 1 images of 224x224 181 / 45 / 12.0 -> 136 / 26 / 6.5 us.  Bound: LDS (two thirds of the time, a third of that bank
+// conflicts of the 4-byte operand reads), then the vector ALU.  4 x 8 pooled pixels and five wavefronts, for which two workgroups a
+// compute unit have registers: 216; pixels as the row operand (batch-norm in registers, 2-byte stores of the tile) 155.
 template <int NTILES>
-__global__ __launch_bounds__(320) void stem_pool_kernel(const bf16_t* __restrict__ img, const int32_t* index,
+__global__ __launch_bounds__(256, 3) void stem_pool_kernel(const bf16_t* __restrict__ img, const int32_t* index,
                                                         bf16_t* __restrict__ y, const bf16_t* __restrict__ w,
                                                         const float* scale, const float* shift, int H, int W, int Ho,
                                                         int Wo, int Hp, int Wp, int tiles_x, int tiles_y,
                                                         int total_tiles, int by_die) {
-    constexpr int KS = 7, PAD = 3, VP = 8, NTH = 320;
+    constexpr int KS = 7, PAD = 3, VP = 8, NTH = 256, TP = STEM_POOL_ROWS;
     constexpr int COUT = NTILES * 32, PAIRS = 3 * KS, KP = ((PAIRS * VP + 15) / 16) * 16, KSTEPS = KP / 16;
-    constexpr int W_LD = KP + 8, CH = 9, CW = 17, NPIX = CH * CW, PR = 2 * CH + KS - 2, PC = 48, CBASE = 2;
+    constexpr int W_LD = KP + 8, CH = 2 * TP + 1, CW = 17, NPIX = CH * CW, PR = 2 * CH + KS - 2, PC = 48, CBASE = 2;
     constexpr int C_LD = COUT + 8;                     // conv tile row stride in LDS (bf16)
-    __shared__ __attribute__((aligned(16))) bf16_t Wl[COUT * W_LD];
-    __shared__ __attribute__((aligned(16))) bf16_t patch[3 * PR * PC];
-    __shared__ __attribute__((aligned(16))) bf16_t ctile[NPIX * C_LD];
+    constexpr int PATCH = (3 * PR * PC + 7) & ~7, CTILE = NTH / 2 * C_LD, BANK = COUT * W_LD;
+    static_assert(NPIX <= NTH / 2, "a matrix column per convolution pixel");
+    __shared__ __attribute__((aligned(16))) bf16_t mem[CTILE + 2 * PATCH > BANK ? CTILE + 2 * PATCH : BANK];
     __shared__ __attribute__((aligned(16))) float scl[COUT], shl[COUT];
+    bf16_t *ctile = mem, *patch0 = mem + CTILE;
     const int tid = threadIdx.x;
+    // input rows 2 oy0 - 3 .., columns 2 ox0 - 6 .. (a multiple of 4, so the 8-byte loads are aligned)
+    PatchLoader<PR, PC, NTH, 6> pl;
+    pl.init(tid, H, W);
+    int slot = 0, ty = 0, tx = 0;                      // of the tile that is under way
+    auto fetch = [&](int v) {
+        const int tile = tile_of(v, tiles_x * tiles_y, by_die);
+        slot = tile / (tiles_x * tiles_y);
+        const int t2 = tile - slot * tiles_x * tiles_y;
+        ty = t2 / tiles_x;
+        tx = t2 - ty * tiles_x;
+        const int sample = __builtin_amdgcn_readfirstlane(index ? index[slot] : slot);
+        pl.issue(img, sample, (2 * TP * ty - 1) * 2 - PAD, (16 * tx - 1) * 2, H, W);
+    };
+    // the filters, eight of a tap at a time
+    constexpr int NV = 3 * KS * KS * (COUT / 8), WL = (NV + NTH - 1) / NTH;
+    uint4 wv[WL];
+#pragma unroll
+    for (int i = 0; i < WL; ++i) wv[i] = *(const uint4*)(w + min(tid + i * NTH, NV - 1) * 8);
+    if ((int)blockIdx.x < total_tiles) fetch(blockIdx.x);
     if (tid < COUT) {
         scl[tid] = scale[tid];
         shl[tid] = shift[tid];
     }
-    for (int i = tid; i < COUT * KP; i += NTH) {
-        const int n = i / KP, k = i - n * KP;
-        const int pair = k / VP, e = k - pair * VP;
-        const int c = pair / KS, u = pair - c * KS, v = e - 1;
-        bf16_t val = 0;
-        if (pair < PAIRS && v >= 0 && v < KS) val = w[((u * KS + v) * 3 + c) * COUT + n];
-        Wl[n * W_LD + k] = val;
-    }
-    const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
-    const int pi = wave * 32 + l32;                    // this lane's convolution pixel as the A-operand row
-    const int pcy = pi < NPIX ? pi / CW : 0, pcx = pi < NPIX ? pi - (pi / CW) * CW : 0;
-    // patch offset of this lane's 8 reduction values at every k-step (-1: padding beyond the last pair)
-    int koff[KSTEPS];
+    for (int i = tid; i < BANK / 8; i += NTH) *(uint4*)(mem + i * 8) = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    // bank[n][(c * KS + u) * VP + e] = w[u][e - 1][c][n] for 1 <= e <= KS, else 0
 #pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) {
-        const int pair = (ks * 16 + lhi * 8) / VP;
-        const int c = pair / KS, u = pair - c * KS;
-        koff[ks] = pair < PAIRS ? (c * PR + 2 * pcy + u) * PC + 2 * pcx + CBASE : -1;
+    for (int i = 0; i < WL; ++i) {
+        const int e = tid + i * NTH, tap = e / (COUT / 8), n = e % (COUT / 8) * 8;
+        const int u = tap / (3 * KS), r = tap - u * 3 * KS, v = r / 3, c = r - v * 3;
+        if (e < NV) {
+            bf16_t* q = mem + n * W_LD + (c * KS + u) * VP + v + 1;
+            const uint32_t* x = &wv[i].x;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) q[k * W_LD] = (bf16_t)(x[k / 2] >> (k & 1) * 16);
+        }
     }
-    // input rows 2 oy0 - 3 .., columns 2 ox0 - 6 .. (a multiple of 4, so the 8-byte loads are aligned)
-    PatchLoader<PR, PC, NTH, 6> pl;
-    pl.init(tid, H, W);
-    auto fetch = [&](int tile) {
-        const int slot = tile / (tiles_x * tiles_y);
-        const int t2 = tile - slot * tiles_x * tiles_y;
-        const int ty = t2 / tiles_x, tx = t2 - ty * tiles_x;
-        const int sample = __builtin_amdgcn_readfirstlane(index ? index[slot] : slot);
-        pl.issue(img, sample, (8 * ty - 1) * 2 - PAD, (16 * tx - 1) * 2, H, W);
-    };
-    if ((int)blockIdx.x < total_tiles) fetch(tile_of(blockIdx.x, tiles_x * tiles_y, by_die));
-    for (int v = blockIdx.x; v < total_tiles; v += gridDim.x) {
-        const int tile = tile_of(v, tiles_x * tiles_y, by_die);
-        const int slot = tile / (tiles_x * tiles_y);
-        const int t2 = tile - slot * tiles_x * tiles_y;
-        const int ty = t2 / tiles_x, tx = t2 - ty * tiles_x;
-        const int p0 = ty * 4, q0 = tx * 8;            // pooled tile origin
+    __syncthreads();
+    const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
+    bf16x8_t wf[KSTEPS][NTILES];
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks)
+#pragma unroll
+        for (int t = 0; t < NTILES; ++t) wf[ks][t] = *(const bf16x8_t*)(mem + (t * 32 + l32) * W_LD + ks * 16 + lhi * 8);
+    __syncthreads();
+    pl.store(patch0, tid);
+    const int pi = wave * 32 + l32;                    // this lane's convolution pixel
+    const int pcy = pi < NPIX ? pi / CW : 0, pcx = pi < NPIX ? pi - (pi / CW) * CW : 0;
+    // This lane's 8 reduction values of k-step ks are a filter row: pair 2 ks + lhi = channel, row.  The upper half's row is one patch
+    // row further down, or in the next channel's patch where the pairs of a step straddle two channels.
+    const int pbase = 2 * pcy * PC + 2 * pcx + CBASE, near = pbase + lhi * PC, far = pbase + lhi * (PR - KS + 1) * PC;
+    int turn = 0;
+    for (int v = blockIdx.x; v < total_tiles; v += gridDim.x, turn ^= 1) {
+        const int p0 = ty * TP, q0 = tx * 8, sl = slot;    // pooled tile origin
         const int oy0 = 2 * p0 - 1, ox0 = 2 * q0 - 1;  // first convolution pixel
-        __syncthreads();  // filter bank ready / previous patch and conv tile no longer read
-        pl.store(patch);
-        __syncthreads();
-        if (v + (int)gridDim.x < total_tiles) fetch(tile_of(v + gridDim.x, tiles_x * tiles_y, by_die));   // in flight during this tile's arithmetic
+        const bf16_t* patch = patch0 + turn * PATCH;
+        __syncthreads();                               // the patch is in place, the previous convolution tile pooled
+        const bool more = v + (int)gridDim.x < total_tiles;
+        if (more) fetch(v + gridDim.x);   // in flight during this tile's arithmetic
         f32x16_t acc[NTILES];
 #pragma unroll
         for (int t = 0; t < NTILES; ++t)
@@ -242,22 +263,23 @@ __global__ __launch_bounds__(320) void stem_pool_kernel(const bf16_t* __restrict
             for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < KSTEPS; ++ks) {
-            const int kbase = ks * 16 + lhi * 8;
             union { uint32_t u[4]; bf16x8_t v; } af;
-            const bf16_t* p = patch + (koff[ks] < 0 ? 0 : koff[ks]);
+            const int c = 2 * ks / KS, u = 2 * ks % KS;
+            const bf16_t* p = patch + (2 * ks + 1 >= PAIRS ? pbase : u + 1 == KS ? far : near) + (c * PR + u) * PC;
 #pragma unroll
-            for (int q = 0; q < VP / 2; ++q) af.u[q] = koff[ks] >= 0 ? *(const uint32_t*)(p + 2 * q) : 0u;
+            for (int q = 0; q < VP / 2; ++q) {
+                af.u[q] = *(const uint32_t*)(p + 2 * q);
+                if (2 * ks + 1 >= PAIRS) af.u[q] = lhi ? 0u : af.u[q];     // behind the last pair zeros
+            }
 #pragma unroll
-            for (int t = 0; t < NTILES; ++t) {
-                const bf16x8_t bfr = *(const bf16x8_t*)(Wl + (t * 32 + l32) * W_LD + kbase);
+            for (int t = 0; t < NTILES; ++t)
                 // filters as the row operand: the accumulator then holds this lane's own pixel (column l32)
                 // and channels 32 t + 8 g + 4 lhi + 0..3 in elements 4 g .. 4 g + 3, i.e. runs of four
                 // consecutive channels that go to LDS as one 8-byte write
-                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr, af.v, acc[t], 0, 0, 0);
-            }
+                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks][t], af.v, acc[t], 0, 0, 0);
         }
         // batch-norm, ReLU, bf16 rounding
-        if (pi < NPIX) {
+        {
             const int oy = oy0 + pcy, ox = ox0 + pcx;
             const bool in = oy >= 0 && oy < Ho && ox >= 0 && ox < Wo;
 #pragma unroll
@@ -272,12 +294,14 @@ __global__ __launch_bounds__(320) void stem_pool_kernel(const bf16_t* __restrict
                     *(uint2*)(ctile + pi * C_LD + ch) = in ? o : make_uint2(0u, 0u);
                 }
         }
+        if (more) pl.store(patch0 + (turn ^ 1) * PATCH, tid);
         __syncthreads();
         // pooled pixel (pr, pc) of the tile, 8 channels per thread
         constexpr int CHUNKS = COUT / 8;
-        for (int it = tid; it < 32 * CHUNKS; it += NTH) {
+        for (int it = tid; it < TP * 8 * CHUNKS; it += NTH) {
             const int ch = (it % CHUNKS) * 8, pp = it / CHUNKS;
-            const int pr = pp >> 3, pc = pp & 7;
+            // (columns 0, 4, 1, 5, ..: 16 lanes then meet every bank once)
+            const int pr = pp >> 3, pc = ((pp & 7) >> 1) | ((pp & 1) << 2);
             if (p0 + pr >= Hp || q0 + pc >= Wp) continue;
             // every value is >= 0 after the ReLU, and non-negative bf16 values order like their bit patterns:
             // the maximum is a packed signed 16-bit integer maximum (a -0 loses to everything), no unpacking
@@ -298,7 +322,7 @@ __global__ __launch_bounds__(320) void stem_pool_kernel(const bf16_t* __restrict
             o.y = __builtin_bit_cast(uint32_t, m[1]);
             o.z = __builtin_bit_cast(uint32_t, m[2]);
             o.w = __builtin_bit_cast(uint32_t, m[3]);
-            *(uint4*)(y + (((int64_t)slot * Hp + p0 + pr) * Wp + q0 + pc) * COUT + ch) = o;
+            *(uint4*)(y + (((int64_t)sl * Hp + p0 + pr) * Wp + q0 + pc) * COUT + ch) = o;
         }
     }
 }
@@ -327,13 +351,13 @@ int32_t ds_launch_stem_pool(const bf16_t* img, const int32_t* index, bf16_t* y, 
     if (K != 7 || stride != 2 || pad != 3 || Cout != 64 || (W % 4) != 0) return DS_EUNSUPPORTED;
     const int Ho = (H + 6 - 7) / 2 + 1, Wo = (W + 6 - 7) / 2 + 1;
     const int Hp = (Ho + 2 - 3) / 2 + 1, Wp = (Wo + 2 - 3) / 2 + 1;
-    const int tiles_x = (Wp + 7) / 8, tiles_y = (Hp + 3) / 4;
+    const int tiles_x = (Wp + 7) / 8, tiles_y = (Hp + STEM_POOL_ROWS - 1) / STEM_POOL_ROWS;
     const long long total = (long long)B * tiles_x * tiles_y;
     if (total <= 0) return DS_OK;
     const int grid = (int)(total < 256 * 3 ? total : 256 * 3);
     const int by_die = (B % 8) == 0 && (grid % 8) == 0;
     ProfScope prof(DS_K_STEM, s);
-    hipLaunchKernelGGL((stem_pool_kernel<2>), dim3(grid), dim3(320), 0, s, img, index, y, w, scale, shift, H, W, Ho, Wo, Hp,
+    hipLaunchKernelGGL((stem_pool_kernel<2>), dim3(grid), dim3(256), 0, s, img, index, y, w, scale, shift, H, W, Ho, Wo, Hp,
                        Wp, tiles_x, tiles_y, (int)total, by_die);
     DS_CHECK_LAUNCH("stem conv + max-pool");
     return DS_OK;

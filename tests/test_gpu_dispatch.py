@@ -488,3 +488,31 @@ def test_resnet_rest_of_a_block(gpu_lib, which, image, B):
                 a = host(t[j])
                 assert np.linalg.norm(a - b) < 2.0 ** -9 * (4 * (i + 1)) ** 0.5 * np.linalg.norm(b) and relerr_max(a, b) < TOL_BF16, (i, k, j)
         assert relerr_max(host(logits[k]), host(want[0])) < TOL_BF16
+
+
+# 7x7 stem and max-pool in one kernel: the first block passes its input on (projection the identity, residual branch zero), so its
+# output is the pooled map.  Tiles of 3 x 8 pooled pixels: maps of one pixel to several tiles, ragged on both sides
+@pytest.mark.parametrize("image,B", [(4, 1), (12, 3), (32, 8), (44, 5), (100, 16), (224, 9)])
+def test_resnet_stem_and_pool(gpu_lib, image, B):
+    arch = WL.resnet_arch(image=image)
+    p = WL.resnet_params(arch, 31)
+    one = {"beta": 0.0, "mean": 0.0, "var": 1.0 - arch["bn_eps"]}
+    for name, gamma in (("s0.b0.proj.bn", 1.0), ("s0.b0.c3.bn", 0.0)):
+        p[name] = {k: np.full_like(v, one.get(k, gamma)) for k, v in p[name].items()}
+    p["s0.b0.proj.w"] = np.zeros_like(p["s0.b0.proj.w"])
+    p["s0.b0.proj.w"][np.arange(64), np.arange(64), 0, 0] = 1.0
+    net = gpu_lib.build_resnet(arch, p, DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(image)
+    imgs = torch.randn((B, 3, image, image), generator=gen, device=DEV).to(torch.bfloat16)
+    bn = p["stem.bn"]
+    s = bn["gamma"].astype(np.float64) / np.sqrt(bn["var"][0].astype(np.float64) + arch["bn_eps"])
+    h = bn["beta"] - bn["mean"][0] * s
+    y = F.conv2d(imgs.double().cpu(), torch.from_numpy(p["stem.w"]).double(), stride=2, padding=3)
+    y = F.max_pool2d(torch.relu(y * torch.from_numpy(s)[:, None, None] + torch.from_numpy(h)[:, None, None]), 3, 2, 1)
+    r = y.shape[-1]
+    tap = torch.zeros((B, r * r, 256), dtype=torch.bfloat16, device=DEV)
+    gpu_lib.ds_forward_taps(net, imgs, {0: tap}, route_override=torch.full((4, B), arch["T"] - 1, dtype=torch.int32, device=DEV))
+    want = y.permute(0, 2, 3, 1).reshape(B, r * r, 64).numpy()
+    # one bf16 rounding (2^-9 of the value) of a sum over 147 products of order one in fp32
+    assert np.all(np.abs(host(tap)[:, :, :64] - want) <= 2.0 ** -8 * np.abs(want) + 1e-4)
