@@ -199,13 +199,16 @@ def resnet_cost(arch, routes) -> Cost:
             one = rest and stride == 1
             if b == 0 and not inside:
                 _gemm(c, "gemm", ro * ro, ro * ro, 1, cin, o, name=f"s{s}.b{b}.proj")      # 1x1 projection reads only the strided pixels
-            _gemm(c, "gemm", r * r, r * r, 1, cin, m, chained=(rest and b > (s > 0) or chain) and b > 0 or b == 0 and paired,
+            behind = rest and b > (s > 0)               # the block before it was one launch, this block's first layer at its end
+            _gemm(c, "gemm_taps" if behind else "gemm", r * r, r * r, 1, cin, m, chained=(behind or chain) and b > 0 or b == 0 and paired,
                   name=f"s{s}.b{b}.c1")
-            _gemm(c, "gemm" if one else "gemm_taps", r * r, ro * ro, 9, m, m, name=f"s{s}.b{b}.c2 3x3" + ("/2" if stride == 2 else ""))
             if b == 0 and inside:
-                c.add("gemm", 2.0 * ro * ro * np.sum(cin * o), 2.0 * r * r * np.sum(cin) + 2.0 * float(cin.max() * o.max()), name=f"s{s}.b{b}.proj",
-                      merge=True)
-            _gemm(c, "gemm", ro * ro, ro * ro, 1, m, o, residual=not (b == 0 and inside), chained=one, name=f"s{s}.b{b}.c3" + ("" if b == 0 and inside else "+res"))
+                # (1x1 work, so in the record of the 1x1 launch ahead of the one that does it)
+                c.add("gemm", 2.0 * ro * ro * np.sum(cin * o), 2.0 * r * r * np.sum(cin) + 2.0 * float(cin.max() * o.max()),
+                      name=f"s{s}.b{b}.proj (in the next launch)", merge=True)
+            _gemm(c, "gemm_taps", r * r, ro * ro, 9, m, m, name=f"s{s}.b{b}.c2 3x3" + ("/2" if stride == 2 else ""))
+            _gemm(c, "gemm_taps" if one else "gemm", ro * ro, ro * ro, 1, m, o, residual=not (b == 0 and inside), chained=one,
+                  name=f"s{s}.b{b}.c3" + ("" if b == 0 and inside else "+res"))
             r = ro
         cprev = out
     c.add("head", 2.0 * arch["num_classes"] * cprev.sum(),
