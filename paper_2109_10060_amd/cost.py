@@ -255,6 +255,7 @@ def vit_cost(arch, routes) -> Cost:
         c.add("index", 0.0, 2.0 * 2 * B * (N - 1) * kp, name="patch extraction")
         _gemm(c, "gemm", N - 1, N - 1, 1, np.full(B, kp), de, name="patch embed")
     full = tab[:, :3].copy()
+    ahead = False                                       # this block's Q/K/V rode along with the block before it
     for l in range(arch["depth"]):
         # dynamic depth: a route that runs fewer than l + 1 blocks contributes nothing to this layer
         on = (tab[:, 3] > l).astype(np.float64) if tab.shape[1] > 3 else np.ones(B)
@@ -269,7 +270,8 @@ def vit_cost(arch, routes) -> Cost:
             c.add("inside", ln[0], 0.0, name=f"l{l}.ln1", launch=False)
         else:
             c.add("layernorm", *ln, name=f"l{l}.ln1")
-        _gemm(c, "gemm", N, N, 1, de, 3 * hd, name=("" if not fused else f"l{l}.ln1+") + f"l{l}.qkv")
+        _gemm(c, "gemm", N, N, 1, de, 3 * hd, name=("" if not fused else f"l{l}.ln1+") + f"l{l}.qkv", chained=ahead)
+        ahead = behind == "one" and _tiles(B, arch["tokens"], arch["T"], 32) >= (140 if live[:, 0].max() > 384 else 60)
         c.add("attention", 4.0 * N * N * hd.sum(), 2.0 * 4 * N * hd.sum(), name=f"l{l}.attention")
         if behind == "one":
             # rows in, the residual stream read and written; both hidden maps stay in the compute unit

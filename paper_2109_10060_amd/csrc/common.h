@@ -354,6 +354,13 @@ struct VitTailArgs {
     const float *bp, *b1, *b2, *g2, *be2;
     float eps;
     const int32_t* offsets;
+    // the next block's Q/K/V of the same rows, LayerNorm in front, where a group runs it (bit g of next)
+    unsigned long long next;
+    const bf16_t* wq;
+    const float *bq, *g1, *be1;
+    int32_t kbq, segq, q_ld;             // tiles per 32-row block, 32-row blocks and biases per segment (q_ld also the outputs' row stride)
+    bf16_t* qkv;
+    int64_t q_ss, q_seg;                 // elements per slot, per segment
     GroupTable gt;                       // k_in = heads * head_dim, k_out = embedding slice, row = hidden slice
 };
 // y = act(LN(x) W^T + b) + residual on tiled weights
@@ -375,6 +382,8 @@ struct VitLinearArgs {
 };
 // DS_EUNSUPPORTED beyond 416 input channels with a LayerNorm, 1664 without
 int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s);
+// whether the next block's Q/K/V is to ride along; gt as in VitTailArgs
+bool ds_vit_tail_qkv(const GroupTable& gt, int32_t B, int32_t rows, int32_t crowd);
 // DS_EUNSUPPORTED where a slice exceeds 416 channels (hidden: any) or its alignment
 int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s);
 

@@ -811,9 +811,9 @@ int32_t linear_gemm(const bf16_t* A, int64_t a_ss, int a_ld, const bf16_t* Wt, i
     return ds_launch_gemm(a, ml.cap, max_out(gt), s);
 }
 
-// projection, LN2 and MLP of one block on the tiled weights Q; L: the block's other parameters
-int32_t vit_behind_attention(const VitDesc& d, const void* const* L, const void* const* Q, const VitPlan& p, const GroupTable& gp,
-                             const GroupTable& g1, const GroupTable& g2, int B, int crowd, float eps, hipStream_t s) {
+// projection, LN2 and MLP of block l on the tiled weights Q; L: the block's other parameters.  ahead: the next block's Q/K/V came with it
+int32_t vit_behind_attention(const VitDesc& d, int l, const void* const* L, const void* const* Q, const VitPlan& p, const GroupTable& gp,
+                             const GroupTable& g1, const GroupTable& g2, int B, int crowd, float eps, hipStream_t s, bool* ahead) {
     const int Hd = d.H * d.dh;
     const int64_t x_ss = (int64_t)d.N * d.D;
     const int kbp = (Hd + 15) / 16 | 1, kb1 = (d.D + 15) / 16 | 1, kb2 = (d.M + 15) / 16 | 1;
@@ -838,7 +838,17 @@ int32_t vit_behind_attention(const VitDesc& d, const void* const* L, const void*
         ta.eps = eps; ta.offsets = p.offs;
         ta.gt = gp;
         for (int t = 0; t < d.T; ++t) ta.gt.row[t] = gp.k_out[t] > 0 ? g1.k_out[t] : 0;
-        return ds_launch_vit_tail(ta, B, s);
+        if (l + 1 < d.depth && ds_vit_tail_qkv(gp, B, d.N, crowd)) {
+            const void* const* Ln = L + 12;
+            ta.wq = (const bf16_t*)Q[4 + 3]; ta.bq = (const float*)Ln[3]; ta.g1 = (const float*)Ln[0]; ta.be1 = (const float*)Ln[1];
+            ta.kbq = kb1; ta.segq = (Hd + 31) / 32; ta.q_ld = Hd;
+            ta.qkv = p.qkv; ta.q_ss = (int64_t)d.N * Hd; ta.q_seg = (int64_t)p.qkv_seg;
+            for (int t = 0; t < d.T; ++t)
+                if (gp.k_out[t] > 0 && (d.rs != 4 || d.routes[4 * t + 3] > l + 1)) ta.next |= 1ull << t;
+        }
+        const int32_t rc = ds_launch_vit_tail(ta, B, s);
+        *ahead = rc == DS_OK && ta.next;
+        return rc;
     }
     VitLinearArgs la;
     memset(&la, 0, sizeof(la));
@@ -966,6 +976,7 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
     RC(ds_launch_cls_rows(xv, (const bf16_t*)P[2], (const bf16_t*)P[3], p.slot_group, gq, B, s));
     const float eps = 1e-6f;
     const GroupTable fq = gq;      // every route, for the final LayerNorm and the classifier
+    bool ahead = false;            // this block's Q/K/V are there
     for (int l = 0; l < d.depth; ++l) {
         const void* const* L = P + 4 + 12 * l;
         // dynamic depth: a route that runs fewer than l + 1 blocks gets empty slices from here on, so
@@ -982,8 +993,9 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
             }
             if (!any) break;
         }
-        bool qkv = false;
-        if (d.tiled) {
+        bool qkv = ahead;
+        ahead = false;
+        if (d.tiled && !qkv) {
             // LN1 in the Q/K/V layer, the rest of the block behind the attention as one or three launches
             const void* const* Q = P + d.tiled + 4 * l;
             VitLinearArgs la;
@@ -1008,7 +1020,7 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
                                (int64_t)d.N * Hd, p.slot_group, gq, B, d.N, d.H, d.dh, s));
         if (qkv) {
             const void* const* Q = P + d.tiled + 4 * l;
-            const int32_t rc = vit_behind_attention(d, L, Q, p, gp, g1, g2, B, (Bs + B - 1) / B, eps, s);
+            const int32_t rc = vit_behind_attention(d, l, L, Q, p, gp, g1, g2, B, (Bs + B - 1) / B, eps, s, &ahead);
             if (rc == DS_OK) {
                 RC(tap_block(taps, l, p.x, x_ss, 0, p.perm, p.slot_group, g2, B, d.N, d.D, s));
                 continue;

@@ -1,5 +1,5 @@
 // The rest of a transformer block behind its attention, in one kernel (Section 3.2, Eq. 15-19):
-//   x += proj(o);  x += fc2(gelu(fc1(LN2(x))))
+//   x += proj(o);  x += fc2(gelu(fc1(LN2(x))));  and where it pays the next block's Q/K/V of LN1(x)
 // for every route group, slices as everywhere: the leading block of the stored weights.
 //
 // As four launches (projection, LayerNorm, two linear layers) a block moved the residual stream five times and the hidden
@@ -18,6 +18,15 @@
 // a pass: LayerNorm weights from memory -> from LDS 16 images 676 -> 672, 64 images 1047 -> 1043, 256 images 2509 -> 2485 (DS-ViT++
 // 3688 -> 3666); biases where they are used -> in registers 64 images 1050 -> 1043, 128 images 1472 -> 1468, 256 images no change.
 //
+// The products of a wavefront are one stream of operands: the last turn of each asks for the first operands of the next (across
+// LayerNorm, GELU and barriers), which no longer wait for L2 at every start.  DS-ViT 16 / 32 / 64 images 673 / 880 / 1050 -> 648 / 845 / 1040 us a
+// pass, DS-ViT++ 64 / 256 images 1416 / 3900 -> 1388 / 3820.  Behind the block a workgroup still has its rows: it normalises them for
+// the next block and multiplies them with that block's Q/K/V weights, stored from registers as vit_linear_kernel stores them.
+// Measured with parts left out, 256 images of DS-ViT, us a launch without Q/K/V: all 110; no weights asked for 99; no GELU 95; neither
+// 79; no LDS reads 110; no MLP 40.  A step of the 12 wavefronts takes 12 KiB through the compute unit's first cache, at 50 bytes a clock a
+// quarter longer than its 24 matrix instructions.  GELU of a chunk between the turns of the product before it: 108 with 12 wavefronts, 142 for
+// 139 with 13 (spills).
+//
 // Sums run in the order of gemm_kernel's and layernorm16_kernel's, so the results are the same bits.
 #include "gelu.h"
 #include "vit_rows.h"
@@ -31,6 +40,12 @@ struct TailTile {
     static constexpr int NORM = 32 * R * (PA + PH) + 8;     // LayerNorm weights: gamma, then beta
     static constexpr int SMEM = NORM * 2 + 2 * VIT_K_MAX * 4;
     static_assert(SMEM <= 160 * 1024, "LDS of a compute unit");
+};
+
+// k channels of weights of a 32-column block
+struct Stream {
+    const bf16_t* w;
+    int k;
 };
 
 // NW wavefronts (one column block of 32 each), 32 R rows, D operands of a wavefront in flight
@@ -120,18 +135,22 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     // LDS reads of a step are issued ahead of the products of the step before it.  The number of steps is rounded up to D; the
     // extra steps multiply zero weights with the zeros behind the slice (tile_pitch).
     const uint32_t lane16 = (uint32_t)lane * 16;
+    // A product's last turn asks for the first operands of the one behind it, so a ring is started once.
     bf16x8_t ring[D];
-    auto start = [&](bf16x8_t (&ring)[D], const __amdgpu_buffer_rsrc_t& rs) {
+    auto start = [&](const Stream& t) {
+        const __amdgpu_buffer_rsrc_t rs = weight_row(t.w, 0, t.k);
 #pragma unroll
         for (int j = 0; j < D; ++j) ring[j] = weight_tile(rs, lane16 + j * 1024);
     };
-    auto walk = [&](f32x16_t (&acc)[R], bf16x8_t (&ring)[D], const __amdgpu_buffer_rsrc_t& rs, int K, const bf16_t* act, int pitch) {
+    auto walk = [&](f32x16_t (&acc)[R], const Stream& t, const Stream& next, const bf16_t* act, int pitch) __attribute__((always_inline)) {
         const bf16_t* base = act + l32 * pitch + lhi * 8;
         bf16x8_t f[2][R];
 #pragma unroll
         for (int r = 0; r < R; ++r) f[0][r] = *(const bf16x8_t*)(base + r * 32 * pitch);
-        uint32_t off = lane16 + D * 1024;
-        for (int k0 = 0; k0 < K; k0 += 16 * D, off += D * 1024) {
+        for (int k0 = 0; k0 < t.k; k0 += 16 * D) {
+            const bool more = k0 + 16 * D < t.k;
+            const __amdgpu_buffer_rsrc_t rs = weight_row(more ? t.w : next.w, 0, more ? t.k : next.k);
+            const uint32_t off = lane16 + (more ? k0 * 64 + D * 1024 : 0);
 #pragma unroll
             for (int j = 0; j < D; ++j) {
 #pragma unroll
@@ -181,12 +200,15 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     if constexpr (PADS > 0)
         for (int i = tid; i < BM * PADS; i += 64 * NW) *(uint4*)(Hs + i / PADS * PH + HC + i % PADS * 8) = make_uint4(0, 0, 0, 0);
     clear2();
-    const __amdgpu_buffer_rsrc_t rp = weight_row(a.wp, w * a.kbp, kin);
-    if (con) start(ring, rp);
+    // (no channels: no traffic)
+    auto stream = [](const bf16_t* w, int t0, int k) { return Stream{w + (int64_t)t0 * 512, k}; };
+    auto fc1 = [&](int hb) { return stream(a.w1, hb * a.kb1, hb * 32 < hid ? de : 0); };
+    const Stream sp = stream(a.wp, w * a.kbp, con ? kin : 0);
+    start(con ? sp : fc1(w));
     float4 cst[4];
     if (CST) constants(cst, a.bp, w * 32, de);
     __syncthreads();
-    if (con) walk(acc2, ring, rp, kin, As, PA);
+    if (con) walk(acc2, sp, fc1(w), As, PA);
     add_columns(cst, a.bp, Hs, PH);                            // x waits in the hidden tile
     __syncthreads();
     // ---- x to memory, LN2 in place ---------------------------------------------------------------------------------------
@@ -219,20 +241,23 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     // ---- MLP, HC hidden columns at a time ----------------------------------------------------------------------------------
     clear2();
     const int nchunk = (hid + HC - 1) / HC;
-    if (w * 32 < hid) start(ring, weight_row(a.w1, w * a.kb1, de));
+    const bool more = (a.next >> g) & 1;
+    // the next block's Q/K/V: three segments of nb column blocks, NW blocks at a time
+    const int nb = (kin + 31) / 32;
+    auto qkv = [&](int p) { return stream(a.wq, (p / nb * a.segq + p % nb) * a.kbq, more && p < 3 * nb ? de : 0); };
     for (int hc = 0; hc < nchunk; ++hc) {
         const int hb = hc * NW + w;                      // 32-column block of the hidden layer
         const bool hon = hb * 32 < hid, last = hc + 1 == nchunk;
         const int K2 = min(HC, hid - hc * HC);
-        const __amdgpu_buffer_rsrc_t r1 = weight_row(a.w1, hb * a.kb1, de), r2 = weight_row(a.w2, w * a.kb2 + hc * 2 * NW, K2);
+        const Stream ahead = last ? qkv(w) : fc1(hb + NW), s2 = stream(a.w2, w * a.kb2 + hc * 2 * NW, con ? K2 : 0), next = con ? s2 : ahead;
         f32x16_t acc1[R];
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc1[r][v] = 0.f;
         if (CST) constants(cst, a.b1, hb * 32, hid);
-        if (hon) walk(acc1, ring, r1, de, As, PA);
-        if (con) start(ring, r2);                        // under way during the GELU and the barriers
+        if (hon) walk(acc1, fc1(hb), next, As, PA);
+        else start(next);
         uint2 ho[4][R];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -261,20 +286,76 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
             if (CST) constants(cst, a.b2, w * 32, de);
         }
         __syncthreads();
-        if (con) walk(acc2, ring, r2, K2, Hs, PH);
-        if ((hb + NW) * 32 < hid) start(ring, weight_row(a.w1, (hb + NW) * a.kb1, de));
+        if (con) walk(acc2, s2, ahead, Hs, PH);
     }
     add_columns(cst, a.b2, As, PA);
+    if (more)
+        for (int i = tid; i < de; i += 64 * NW) {
+            gs[i] = a.g1[i];
+            gs[VIT_K_MAX + i] = a.be1[i];
+        }
     __syncthreads();
-    // ---- x to memory ------------------------------------------------------------------------------------------------------
+    // ---- x to memory, the next block's LN1 in place -------------------------------------------------------------------------
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-        if (!live[i]) continue;
-        const bf16_t* row = As + (prow + RP * i) * PA;
+        if (BM % RP != 0 && prow + RP * i >= BM) continue;     // whole 16-lane groups
+        bf16_t* row = As + (prow + RP * i) * PA;
+        float v[4][8];
+        uint4 o[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int ch = (k * 16 + l16) * 8;
-            if (ch < de) *(uint4*)(a.x + xoff[i] + ch) = *(const uint4*)(row + ch);
+            if (ch < de) {
+                const uint4 q = *(const uint4*)(row + ch);
+                if (live[i]) *(uint4*)(a.x + xoff[i] + ch) = q;
+                unpack8(q, v[k]);
+            }
+        }
+        if (!more) continue;
+        row_norm(v, de, l16, a.eps, gs, gs + VIT_K_MAX, o);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int ch = (k * 16 + l16) * 8;
+            if (ch < de) *(uint4*)(row + ch) = o[k];           // (zeros behind the slice are still there)
+        }
+    }
+    if (!more) return;
+    __syncthreads();
+    bf16_t* qrow[R];
+    bool in[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int m = grow0 + r * 32 + l32;
+        in[r] = m < rows_g;
+        const int mm = in[r] ? m : grow0, sl = mm / a.rows;
+        qrow[r] = a.qkv + (int64_t)(slot0 + sl) * a.q_ss + (int64_t)(mm - sl * a.rows) * a.q_ld;
+    }
+    for (int p = w; p < 3 * nb; p += NW) {
+        const int seg = p / nb, n0 = (p - seg * nb) * 32;
+        clear2();
+        float4 h[4];
+        if (CST) constants(h, a.bq + (int64_t)seg * a.q_ld, n0, kin);
+        walk(acc2, qkv(p), qkv(p + NW), As, PA);
+        if (!CST) constants(h, a.bq + (int64_t)seg * a.q_ld, n0, kin);
+        const int64_t so = (int64_t)seg * a.q_seg;
+#pragma unroll
+        for (int q = 0; q < 4; q += 2) {
+            const int n = n0 + 8 * q + 8 * lhi;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                uint32_t lo[2], hi[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const f32x16_t& t = acc2[r];
+                    const int b = 4 * (q + e);
+                    lo[e] = f2bf2(t[b] + h[q + e].x, t[b + 1] + h[q + e].y);
+                    hi[e] = f2bf2(t[b + 2] + h[q + e].z, t[b + 3] + h[q + e].w);
+                }
+                // channels 8 q .. + 7 to the lower half's lane, the next eight to the upper half's
+                const auto a0 = __builtin_amdgcn_permlane32_swap(lo[0], lo[1], false, false);
+                const auto a1 = __builtin_amdgcn_permlane32_swap(hi[0], hi[1], false, false);
+                if (in[r] && n < kin) *(uint4*)(qrow[r] + so + n) = make_uint4(a0[0], a1[0], a0[1], a1[1]);
+            }
         }
     }
 }
@@ -291,6 +372,19 @@ int32_t launch(const VitTailArgs& a, int64_t tiles, hipStream_t s) {
 }
 
 }  // namespace
+
+// The next block's Q/K/V behind the block, or in a launch of its own (vit_linear_kernel), which reads the rows again and takes a
+// generation of workgroups more, but spreads over more of them.  So it rides along from about the tiles on at which a launch of its own no longer has
+// compute units to spread to; with 13 wavefronts, where 36 column blocks are three rounds of which one is mostly idle, later.  Us a pass of
+// DS-ViT, own launch / here: 8 images (57 tiles of 32 rows) 545 / 571, 9 images (64) 642 / 627, 16 images 648 / 651, 17 images 750 / 682, 32
+// images 845 / 748, 64 images 1045 / 972, 256 images 2576 / 2447; DS-ViT++ 19 images (135) 1025 / 1047, 24 images (170) 1041 / 1033, 32 images
+// 1110 / 1051, 256 images 3817 / 3652.  Parts of a batch count together: 32 images in two 800 / 751, 128 in four 1910 / 1657; 256 in two 2325 / 2440.
+bool ds_vit_tail_qkv(const GroupTable& gt, int32_t B, int32_t rows, int32_t crowd) {
+    int dmax = 0;
+    for (int t = 0; t < gt.T; ++t) dmax = gt.k_out[t] > dmax ? gt.k_out[t] : dmax;
+    const int64_t groups = B < gt.T ? B : gt.T, tiles = ((int64_t)B * rows - groups) / 32 + groups;
+    return tiles * (crowd > 1 ? crowd : 1) >= (dmax > 384 ? 140 : 60);
+}
 
 // Rows per workgroup.  A workgroup streams all weights of the block whatever its rows (2.7 MB at full width), and when all compute
 // units do so at once the L2s give each about 30 bytes a clock, half of what 64 rows could use; so more rows each are better --

@@ -516,3 +516,21 @@ def test_resnet_stem_and_pool(gpu_lib, image, B):
     want = y.permute(0, 2, 3, 1).reshape(B, r * r, 64).numpy()
     # one bf16 rounding (2^-9 of the value) of a sum over 147 products of order one in fp32
     assert np.all(np.abs(host(tap)[:, :, :64] - want) <= 2.0 ** -8 * np.abs(want) + 1e-4)
+
+
+# the next block's Q/K/V behind a block, on both sides of its line and with 32 and 64 rows a workgroup, routes that end before the
+# deepest one among them: the bits of the launches on the row-major weights, which have none of it
+@pytest.mark.parametrize("which,B", [("cross", 8), ("cross", 9), ("cross", 80), ("pp", 19), ("pp", 20), ("pp", 90), ("depth", 12), ("depth", 77)])
+def test_vit_qkv_behind_a_block(gpu_lib, which, B):
+    kw = {"cross": dict(depth=3), "depth": dict(depth=4, routes="depth"),
+          "pp": dict(embed=416, heads=8, head_dim=48, mlp=1664, depth=4, routes="pp")}[which]
+    arch = WL.vit_arch(**kw)
+    net = gpu_lib.build_vit(arch, WL.vit_params(arch, 8), DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(B)
+    imgs = torch.randn((B, 3, arch["image"], arch["image"]), generator=gen, device=DEV).to(torch.bfloat16)
+    over = (torch.arange(B, device=DEV, dtype=torch.int32) * 5 % arch["T"])[None].contiguous()
+    got, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
+    net.c_struct.n_params -= 4 * arch["depth"]
+    want, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
+    assert torch.isfinite(want).all() and torch.equal(got, want)
