@@ -10,7 +10,7 @@
 // gathered from the shifted input pixels (zero outside the image).
 //
 // Tiling: 128 x 64 output tile per 256-thread workgroup, 4 wavefronts, each holding a 32 x 64 grid of
-// v_mfma_f32_32x32x16_bf16 accumulators (the dispatcher uses this shape for every layer: with ragged route
+// v_mfma_f32_32x32x16_bf16 accumulators (the dispatcher uses this shape for nearly every layer: with ragged route
 // groups and slices as narrow as 64 channels the wider 128 x 128 / 128 x 256 instantiations lose more to
 // quantisation and residency than their lower operand traffic gains).  Operands go through one LDS tile in
 // 32-deep slabs, 64-deep ones for reductions of 256 steps and more, or 128-deep ones where a launch is about one
@@ -449,6 +449,20 @@ int32_t ds_launch_gemm(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, 
                  : launch<__VA_ARGS__, true, false>(a, max_mtiles, max_kout, s))                       \
           : (a.R ? launch<__VA_ARGS__, false, true>(a, max_mtiles, max_kout, s)                        \
                  : launch<__VA_ARGS__, false, false>(a, max_mtiles, max_kout, s)))
+    // 128 columns a workgroup, two wavefronts of 64 x 64 either way, so that rows go through LDS half as often, where a launch still has
+    // several generations of such workgroups and few of them are half empty.
+    // - layers of at most 256 channels whose columns are all in one such tile: DS-ResNet stage 2, first 1x1, 256 images 110 -> 95 us (its
+    //   512-column projection 75 -> 90 the other way); a pass of 64 / 96 / 128 / 180 images (1569 .. 4411 row tiles) with the line at 768 tiles
+    //   1102 / 1326 / 1600 / 2025 -> 1107 / 1336 / 1597 / 2012, so it stands at 3000
+    // - strided KxK layers: DS-ResNet 3x3/2 of stages 2 and 3, 256 images 81.5 -> 70.5 and 56.2 -> 49.9; stage 4 (392 tiles) 54.6 -> 71; the line at 250
+    //   tiles 256 images 2620 -> 2637 a pass, 128 images 1597 -> 1625
+    // Together 256 images of DS-ResNet 2647 -> 2620, of DS-ResNet++ 3037 -> 3007.  With a residual, or more columns at stride 1, they lose (stage 3,
+    // last 1x1 39.5 -> 49.7, stage 4, first 1x1 28.4 -> 37.5).
+    const long long tiles128 = (long long)max_mtiles * a.n_seg * ((max_kout + 127) / 128) * (a.crowd > 1 ? a.crowd : 1);
+    if (!a.R && max_kout > 64) {
+        if (!conv && !deep && kmax > 128 && max_kout <= 128 && tiles128 >= 3000) return launch<2, 2, 2, 2, 32, 1, false, false>(a, max_mtiles, max_kout, s);
+        if (taps > 1 && deep && tiles128 >= 768) return launch<2, 2, 2, 2, 64, 1, true, false>(a, max_mtiles, max_kout, s);
+    }
     if (!deep) return DS_GEMM_DISPATCH(4, 1, 1, 2, 32, 1);   // 64-wide tile, 32-deep slabs
     // launches of about one generation with long reductions (below): 128-deep slabs halve the number of dependent rounds (256 images of
     // DS-ResNet, stage 4: strided 3x3 64.3 -> 55.7 us, first 1x1 32.3 -> 28.5, pass 3028 -> 3013; without the bound of six workgroups a compute
