@@ -461,6 +461,10 @@ int32_t ds_launch_gemm(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, 
     const long long tiles128 = (long long)max_mtiles * a.n_seg * ((max_kout + 127) / 128) * (a.crowd > 1 ? a.crowd : 1);
     if (!a.R && max_kout > 64) {
         if (!conv && !deep && kmax > 128 && max_kout <= 128 && tiles128 >= 3000) return launch<2, 2, 2, 2, 32, 1, false, false>(a, max_mtiles, max_kout, s);
+        // - linear layers of 768 channels and more: 64 images of 197 tokens 768 -> 3072 (2376 tiles) 70 -> 65.5, 256 of 256 tokens 308 -> 278, with GELU
+        //   128 of 197 tokens 131 -> 125.  From 1200 tiles on they gain as well, but there a stage of sixteen route groups loses (DS-ResNet stage 4, first
+        //   1x1 of the strided block, 256 images, 1568 tiles, 41.8 -> 50.5); 384 channels lose at any size (64 images of 197 tokens 28.8 -> 31).
+        if (!conv && kmax >= 768 && tiles128 >= 2048) return launch<2, 2, 2, 2, 64, 1, false, false>(a, max_mtiles, max_kout, s);
         if (taps > 1 && deep && tiles128 >= 768) return launch<2, 2, 2, 2, 64, 1, true, false>(a, max_mtiles, max_kout, s);
     }
     if (!deep) return DS_GEMM_DISPATCH(4, 1, 1, 2, 32, 1);   // 64-wide tile, 32-deep slabs

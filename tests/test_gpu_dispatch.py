@@ -100,7 +100,7 @@ def test_sliced_conv_bf16_taps(gpu_lib, B, K, stride, pad, H, W, c_in, c_out, re
 # large launches on tiles of 128 columns: slices that end inside either half, ragged rows, a narrow group beside a wide one
 @pytest.mark.parametrize("B,K,stride,pad,H,W,c_in,c_out,res", [
     (125, 1, 1, 0, 56, 56, (136, 40), (128, 72), False), (126, 1, 1, 0, 55, 57, (144, 8), (104, 8), False),
-    (64, 3, 2, 1, 55, 56, (72, 24), (136, 200), False), (130, 3, 2, 1, 57, 55, (64, 8), (72, 128), False)])
+    (33, 1, 1, 0, 28, 29, (776, 40), (1240, 72), False), (64, 3, 2, 1, 55, 56, (72, 24), (136, 200), False), (130, 3, 2, 1, 57, 55, (64, 8), (72, 128), False)])
 def test_sliced_conv_bf16_wide(gpu_lib, B, K, stride, pad, H, W, c_in, c_out, res):
     _conv_case(gpu_lib, B, K, stride, pad, H, W, c_in, c_out, res, False)
 
