@@ -36,7 +36,9 @@ struct Layout {
     static constexpr int OUT = TILE_BYTES + SLAB;
     static constexpr int MAIN = CONV > OUT ? CONV : OUT;
     static constexpr int N_OUT = 128 * NB;                      // output columns the constants have room for
-    static constexpr int CST = MAIN, ROWS = CST + (PROJ ? 4 : 2) * N_OUT * 4, CST2 = ROWS + 2 * BM * 4, SMEM = CST2 + (CHAIN ? 4 : 2) * NB * 32 * 4;
+    static constexpr int CST = MAIN, ROWS = CST + (PROJ ? 4 : 2) * N_OUT * 4, CST2 = ROWS + 2 * BM * 4, SUMS = CST2 + (CHAIN ? 4 : 2) * NB * 32 * 4;
+    // without a next block: column sums of each wavefront's rows, of the tile's first and of its second sample
+    static constexpr int SMEM = SUMS, SMEM_SUMS = SUMS + 4 * 2 * N_OUT * 4;
 };
 
 __device__ __forceinline__ int sw(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
@@ -54,6 +56,15 @@ __device__ __forceinline__ void add_bf16x4(float (&v)[4], const uint2 r) {
     v[1] += __uint_as_float(r.x & 0xffff0000u);
     v[2] += __uint_as_float(r.y << 16);
     v[3] += __uint_as_float(r.y & 0xffff0000u);
+}
+
+// sum over the lanes 8, 16, 24, .. away, all of them get it: a rotation within 16 lanes, then rows and halves of the wavefront traded
+__device__ __forceinline__ float sum_of_8(float v) {
+    v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x128, 0xf, 0xf, true));
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 template <int NB, bool PROJ, bool CHAIN>
@@ -304,6 +315,9 @@ __global__ __launch_bounds__(NT, NB == 2 ? 3 : 2) void bneck_kernel(const BneckA
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc1[t][v] = 0.f;
     char *W3 = smem + TILE_BYTES, *WP = W3 + L::W3, *W1 = WP + L::WP;
+    // the tile's first row of another sample than its first one's (at least 128 rows a sample: two at the most)
+    const int split = ((grow0 / rows) + 1) * rows - grow0;
+    float* colsum = (float*)(smem + L::SUMS);
     char* my_row = tile + prow * 128;
     const int px7 = prow & 7;
     for (int n0 = 0; n0 < out; n0 += 64) {
@@ -383,6 +397,35 @@ __global__ __launch_bounds__(NT, NB == 2 ? 3 : 2) void bneck_kernel(const BneckA
             const int r = srow + 8 * i, z = rowZ[r];
             if (z >= 0 && n0 + sc8 < out) *(uint4*)(a.z + z + n0 + sc8) = *(const uint4*)(tile + r * 128 + (((lane & 7) ^ (r & 7)) * 16));
         }
+        if constexpr (!CHAIN) {
+            if (a.sums) {
+                // sums over this wavefront's rows (as stored), 8 columns a lane, then over the 8 lanes that share the columns
+#pragma unroll
+                for (int side = 0; side < 2; ++side) {
+                    if (side && split >= BM) break;
+                    float t[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int r = srow + 8 * i;
+                        if (rowZ[r] < 0 || (r >= split) != (side == 1)) continue;
+                        const uint4 q = *(const uint4*)(tile + r * 128 + (((lane & 7) ^ (r & 7)) * 16));
+                        const uint32_t u[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            t[2 * k] += __uint_as_float(u[k] << 16);
+                            t[2 * k + 1] += __uint_as_float(u[k] & 0xffff0000u);
+                        }
+                    }
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) t[k] = sum_of_8(t[k]);
+                    if (lane < 8) {
+                        float* p = colsum + (wave * 2 + side) * L::N_OUT + n0 + lane * 8;
+                        *(float4*)p = make_float4(t[0], t[1], t[2], t[3]);
+                        *(float4*)(p + 4) = make_float4(t[4], t[5], t[6], t[7]);
+                    }
+                }
+            }
+        }
         if constexpr (CHAIN) {
             if (next > 0) {
                 const int nk = out - n0;
@@ -402,6 +445,26 @@ __global__ __launch_bounds__(NT, NB == 2 ? 3 : 2) void bneck_kernel(const BneckA
             }
         }
         wave_sync();
+    }
+    if constexpr (!CHAIN) {
+        if (!a.sums) return;
+        __syncthreads();
+        const int S = (rows + BM - 1) / BM + 1, sl = grow0 / rows, first = grow0 / BM - sl * rows / BM;     // this tile's place among the first sample's
+        float* to = a.sums + (int64_t)(slot0 + sl) * S * a.out_full;
+        for (int i = tid; i < out; i += NT) {
+            float t[2];
+#pragma unroll
+            for (int side = 0; side < 2; ++side) {
+                t[side] = 0.f;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) t[side] += colsum[(w * 2 + side) * L::N_OUT + i];
+            }
+            to[(int64_t)first * a.out_full + i] = t[0];
+            // a sample whose last row is here in its last tile but one leaves the last place empty
+            if (split <= BM && first == S - 2) to[(int64_t)(S - 1) * a.out_full + i] = 0.f;
+            if (split < BM && grow0 + split < rows_g) to[(int64_t)S * a.out_full + i] = t[1];
+        }
+        return;
     }
     if constexpr (CHAIN) {
         if (next <= 0) return;
@@ -434,8 +497,10 @@ __global__ __launch_bounds__(NT, NB == 2 ? 3 : 2) void bneck_kernel(const BneckA
 
 template <int NB, bool PROJ, bool CHAIN>
 int32_t launch(const BneckArgs& a, int32_t max_mtiles, hipStream_t s) {
-    constexpr int SMEM = Layout<NB, PROJ, CHAIN>::SMEM;
-    const int32_t rc = ds_reserve_lds((const void*)bneck_kernel<NB, PROJ, CHAIN>, SMEM, "bottleneck block");
+    using L = Layout<NB, PROJ, CHAIN>;
+    constexpr int MOST = CHAIN ? L::SMEM : L::SMEM_SUMS;
+    const int SMEM = !CHAIN && a.sums ? L::SMEM_SUMS : L::SMEM;
+    const int32_t rc = ds_reserve_lds((const void*)bneck_kernel<NB, PROJ, CHAIN>, MOST, "bottleneck block");
     if (rc) return rc;
     ProfScope prof(DS_K_CONV3, s);
     hipLaunchKernelGGL((bneck_kernel<NB, PROJ, CHAIN>), dim3((unsigned)((max_mtiles + 63) / 64 * 64)), dim3(NT), SMEM, s, a, max_mtiles);
@@ -452,7 +517,7 @@ int blocks_of(const BneckArgs& a) {
 }  // namespace
 
 bool ds_bneck_runs(const BneckArgs& a, int32_t B, int32_t max_mtiles) {
-    if (BM + 2 * (a.W + 1) > RMAX) return false;
+    if (BM + 2 * (a.W + 1) > RMAX || (a.sums && (a.w1 || a.H * a.W < BM))) return false;
     int mmax = 0, omax = 0, xmax = 0, nmax = 0;
     for (int t = 0; t < a.gt.T; ++t) {
         const int x = a.x ? a.kx[t] : 0, n = a.w1 ? a.next[t] : 0;

@@ -197,6 +197,7 @@ struct BneckArgs {
     const float *sp, *hp;                // its tables [row][tab3]
     const int32_t* x_index;              // slot -> block of x
     bf16_t *z, *y1_next;
+    float* sums;                         // null, or (no next block, at least 128 rows a slot) sums of z over rows [slot][ds_bneck_splits][out_full]
     int64_t y1_ss, z_ss, x_ss;           // elements per slot (y1_next as y1)
     int32_t mid_full, out_full, x_full, tab3, H, W;
     const int4* mtiles;
@@ -207,6 +208,8 @@ struct BneckArgs {
 };
 bool ds_bneck_runs(const BneckArgs& a, int32_t B, int32_t max_mtiles);
 int32_t ds_launch_bneck(const BneckArgs& a, int32_t B, int32_t max_mtiles, hipStream_t s);
+// most row tiles that a sample of `rows` rows has a part in
+inline int32_t ds_bneck_splits(int32_t rows) { return (rows + DS_GEMM_BM - 1) / DS_GEMM_BM + 1; }
 
 static inline const int4* ds_mtile_entries(const void* list) { return (const int4*)((const char*)list + 16); }
 static inline const int32_t* ds_mtile_count(const void* list) { return (const int32_t*)list; }
@@ -229,7 +232,10 @@ struct GateArgs {
     float* logits;
     int32_t* route;
     float* partial;           // [B][splits][C] scratch
+    int32_t splits;           // > 0: the map's partial sums are there already
 };
+// whether a gate of these sizes takes partial sums made by the launch that wrote its map
+bool ds_gate_takes_sums(const GateArgs& a);
 size_t ds_gate_partial_bytes(int32_t B, int32_t C);
 // y[b][p][c] = x[b][p][c] * scale[b][c] on the valid channels (NHWC) / y[b][c][p] (NCHW); fp32 or bf16
 int32_t ds_launch_channel_scale(const void* x, void* y, const float* scale, const int32_t* c_in, int32_t dtype,

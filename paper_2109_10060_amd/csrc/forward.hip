@@ -449,6 +449,7 @@ bool parse_rn(const ds_net* net, RnDesc* d) {
 
 struct RnPlan {
     bf16_t* buf[5];
+    int gate_c;                   // channels that gate_partial has room for
     float *gate_logits, *gate_partial;
     int32_t *offs[4], *perm[4], *inv[4], *slot_group[4], *route[4], *key, *src_index, *slot_c;
     void* lists[8];
@@ -469,6 +470,7 @@ void plan_rn(const RnDesc& d, int B, Bump& bp, RnPlan* p) {
     int cmax = d.stem_out;
     for (int s = 0; s < 4; ++s) cmax = cmax > 4 * d.widths[s] ? cmax : 4 * d.widths[s];
     p->gate_logits = bp.take<float>((size_t)B * d.T);
+    p->gate_c = cmax;
     p->gate_partial = bp.take<float>(ds_gate_partial_bytes(B, cmax) / sizeof(float));
     for (int s = 0; s < 4; ++s) {
         p->offs[s] = bp.take<int32_t>(rn_groups(d) + 1);
@@ -513,6 +515,7 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
     int c_prev_full = d.stem_out;
     const void* const* Q = P + 3;
     int block_id = 0;              // blocks counted over all stages, in execution order
+    int32_t map_splits = 0;        // partial sums of the stage input, made by the launch that wrote it
     for (int st = 0; st < 4; ++st) {
         const int w = d.widths[st], nb = d.blocks[st];
         const int rin = r;
@@ -531,6 +534,8 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
         g.out_index = st > 0 ? p.perm[st - 1] : nullptr;
         g.route_override = route_override ? route_override + (size_t)st * Bs : nullptr;
         g.logits = p.gate_logits; g.route = route; g.partial = p.gate_partial;
+        g.splits = map_splits;
+        map_splits = 0;
         if (d.single_gate && st > 0) {
             // the first stage's decision stands: no pooling, no MLP, the route is copied
             g.x = nullptr; g.logit_bias = nullptr; g.out_index = nullptr;
@@ -631,6 +636,15 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
                     bn.w1 = ch.Wt; bn.s1 = ch.scale; bn.h1 = ch.shift; bn.y1_next = Y2;
                     memcpy(bn.next, ch.k_out, sizeof(bn.next));
                 }
+                // A stage's last block, which every route runs, sums its output for the next gate's pooling, which then reads no map: DS-ResNet
+                // 96 / 128 / 256 images 1386 / 1685 / 2717 -> 1381 / 1657 / 2690 us a pass, 256 in four parts 2650 -> 2618.  Of fewer images the pool finds
+                // the map in the caches and the sums only make the block longer: 33 / 64 images 844 / 1149 -> 848 / 1151, 64 in two parts 1092 -> 1099.
+                if (b + 1 == nb && st < 3 && !d.single_gate && !d.nblk && rout * rout >= DS_GEMM_BM) {
+                    GateArgs gn = g;
+                    gn.C = 4 * w; gn.C_mlp = d.hidden[st + 1]; gn.x_sample_stride = bn.z_ss;
+                    if (Bs >= 96 && B > 2 && ds_gate_takes_sums(gn) && (size_t)B * ds_bneck_splits(rout * rout) * 4 * w * sizeof(float) <= ds_gate_partial_bytes(B, p.gate_c))
+                        bn.sums = p.gate_partial;
+                }
             }
             const bf16_t* shortcut = Z;
             int32_t rest = DS_EUNSUPPORTED;        // whether the layers behind the first one have run
@@ -672,6 +686,7 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
                 if (rest != DS_OK && rest != DS_EUNSUPPORTED) return rest;
             }
             if (rest == DS_OK) {
+                if (bn.sums) map_splits = ds_bneck_splits(rout * rout);
                 if (next_any) {
                     bf16_t* t = Y1; Y1 = Y2; Y2 = t;
                     y1_ready = true;

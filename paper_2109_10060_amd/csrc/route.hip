@@ -684,16 +684,16 @@ int32_t launch_gate(const GateArgs& a, const Bucket& bucket, hipStream_t s) {
         // 928); first gate of DS-ResNet (64 channels of 56x56), 1 image 10.4 / 4.0 + 6.9.  Above, the pool kernel's several workgroups
         // per item first: its second gate (up to 256 channels of 56x56, 1.5 MiB), 1 / 33 images 20.0 / 22.1 against 3.8 + 8.2 / 7.6 + 8.4, 256 images
         // 49.3 / 46.4 + 9.2; its third (784 KiB) 16.4 / 17.3 / 26.9 against 3.5 + 9.2 / 5.3 + 9.8 / 20.5 + 11.3 (profiles/dispatch_choices.txt).
-        const bool pooled = map_bytes <= (512 << 10) && a.C <= 512;
-        int splits = 1;
-        if (!pooled) {
+        const bool pooled = a.splits <= 0 && map_bytes <= (512 << 10) && a.C <= 512;
+        int splits = a.splits > 0 ? a.splits : 1;
+        if (!pooled && a.splits <= 0) {
             const int32_t rc = ds_launch_pool(a, DS_K_GATE, &splits, s);
             if (rc) return rc;
         }
         int lcl = 0;
         while ((8 << lcl) < a.C && lcl < 6) ++lcl;
         // one or two items with 1 MiB of hidden weights: 12.9 / 15.0 us in one workgroup, 4.4 + 6.6 / 6.9 + 5.8 with a wavefront per unit
-        if (!pooled && a.B <= 2 && (int64_t)a.C * a.C_mlp >= (256 << 10)) {
+        if (!pooled && a.splits <= 0 && a.B <= 2 && (int64_t)a.C * a.C_mlp >= (256 << 10)) {
             float* hid = a.partial + (size_t)a.B * a.C * POOL_SPLIT_MAX;
             FcArgs f = {};
             f.v_partial = a.partial; f.splits = splits; f.v_scale = 1.0f / (float)a.HW;
@@ -734,8 +734,14 @@ int32_t launch_gate(const GateArgs& a, const Bucket& bucket, hipStream_t s) {
 }
 }  // namespace
 
+bool ds_gate_takes_sums(const GateArgs& a) {
+    return a.x && a.layout == DS_NHWC && a.C <= GF_CMAX && a.C_mlp <= GF_HMAX && a.T <= 64 && (a.C % 8) == 0 && (a.x_ld <= 0 || (a.x_ld % 8) == 0) &&
+           (a.x_sample_stride % 8) == 0;
+}
+
 int32_t ds_launch_gate(const GateArgs& a, hipStream_t s, const BucketArgs* bucket_of_one) {
     if (a.B <= 0) return DS_OK;
+    if (a.splits > 0 && !ds_gate_takes_sums(a)) DS_FAIL(DS_EINVAL, "gate: partial sums for a shape that does not take them");
     if (!bucket_of_one) return launch_gate(a, NoBucket{}, s);
     if (a.B != 1 || bucket_of_one->B != 1 || bucket_of_one->T > 64) DS_FAIL(DS_EINVAL, "gate: only one sample is bucketed by the gate itself");
     if (a.x && (a.layout != DS_NHWC || a.dtype != DS_BF16)) DS_FAIL(DS_EINVAL, "gate: only networks' maps (bf16, NHWC) are bucketed by the gate itself");

@@ -542,3 +542,44 @@ def test_vit_qkv_behind_a_block(gpu_lib, which, B):
     net.c_struct.n_params -= 4 * arch["depth"]
     want, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
     assert torch.isfinite(want).all() and torch.equal(got, want)
+
+
+# gates that take the sums of the stage's last block, against a float64 mean of that block's output: samples that start inside a tile
+# of 128 rows, that end in it, maps of a few tiles
+@pytest.mark.parametrize("image,B", [(224, 100), (150, 131), (236, 97)])
+def test_resnet_gates_on_the_last_blocks_sums(gpu_lib, image, B):
+    arch = WL.resnet_arch(image=image)
+    p = WL.resnet_params(arch, 37)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(image)
+    # (images of different contrast, so that their means differ)
+    imgs = (torch.randn((B, 3, image, image), generator=gen, device=DEV) * torch.linspace(0.2, 3.0, B, device=DEV)[:, None, None, None]).to(torch.bfloat16)
+    over = torch.stack([(torch.arange(B, device=DEV, dtype=torch.int32) + s) % arch["T"] for s in range(4)])
+    r0 = ((image + 1) // 2 + 1) // 2
+    last = {0: (arch["blocks"][0] - 1, r0, 256), 1: (arch["blocks"][0] + arch["blocks"][1] - 1, (r0 - 1) // 2 + 1, 512)}
+
+    def run(bias):
+        net = gpu_lib.build_resnet(arch, p, DEV)
+        taps = {i: torch.zeros((B, r * r, c), dtype=torch.bfloat16, device=DEV) for i, r, c in last.values()}
+        return taps, gpu_lib.ds_forward_taps(net, imgs, taps, logit_bias=bias, route_override=None)[1]
+
+    # the first two gates' routes are forced by their scores, the third's and second's own scores are brought to zero mean
+    bias = torch.zeros((4, B, arch["T"]), device=DEV)
+    bias[0].scatter_(1, over[0].long()[:, None], 1000.0)
+    bias[3].scatter_(1, over[3].long()[:, None], 1000.0)
+    for st in (0, 1):
+        def scores(taps):
+            i, r, c = last[st]
+            mean = host(taps[i]).mean(1)
+            w = {k: p[f"s{st + 1}.gate.{k}"].astype(np.float64) for k in ("w1", "b1", "w2", "b2")}
+            return np.maximum(mean @ w["w1"].T + w["b1"], 0.0) @ w["w2"].T + w["b2"]
+        z = scores(run(bias)[0])
+        p[f"s{st + 1}.gate.b2"] = (p[f"s{st + 1}.gate.b2"] - z.mean(0)).astype(np.float32)
+        taps, routes = run(bias)
+        z = scores(taps)
+        top = np.sort(z, 1)
+        # fp32 sums of up to 3481 values and one bf16-free mean: 1e-5 of the scores' size is far above their error
+        clear = top[:, -1] - top[:, -2] > 1e-5 * np.abs(z).max()
+        got = routes[st + 1].cpu().numpy()
+        assert clear.sum() > 0.9 * B and len(set(z.argmax(1)[clear])) > 1
+        assert np.array_equal(got[clear], z.argmax(1)[clear])
