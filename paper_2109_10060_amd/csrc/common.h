@@ -367,6 +367,7 @@ struct VitTailArgs {
     int32_t kbq, segq, q_ld;             // tiles per 32-row block, 32-row blocks and biases per segment (q_ld also the outputs' row stride)
     bf16_t* qkv;
     int64_t q_ss, q_seg;                 // elements per slot, per segment
+    int32_t crowd;                       // as in GemmArgs
     GroupTable gt;                       // k_in = heads * head_dim, k_out = embedding slice, row = hidden slice
 };
 // y = act(LN(x) W^T + b) + residual on tiled weights

@@ -850,7 +850,7 @@ int32_t vit_behind_attention(const VitDesc& d, int l, const void* const* L, cons
         ta.wp = (const bf16_t*)Q[0]; ta.w1 = (const bf16_t*)Q[1]; ta.w2 = (const bf16_t*)Q[2];
         ta.bp = (const float*)L[5]; ta.g2 = (const float*)L[6]; ta.be2 = (const float*)L[7];
         ta.b1 = (const float*)L[9]; ta.b2 = (const float*)L[11];
-        ta.eps = eps; ta.offsets = p.offs;
+        ta.eps = eps; ta.offsets = p.offs; ta.crowd = crowd;
         ta.gt = gp;
         for (int t = 0; t < d.T; ++t) ta.gt.row[t] = gp.k_out[t] > 0 ? g1.k_out[t] : 0;
         if (l + 1 < d.depth && ds_vit_tail_qkv(gp, B, d.N, crowd)) {

@@ -392,7 +392,11 @@ bool ds_vit_tail_qkv(const GroupTable& gt, int32_t B, int32_t rows, int32_t crow
 // images (219 tiles of 64 rows) 1012 / 1036, 60 images (231) 1074 / 1039, 96 images 1421 / 1251, 256 images 3135 / 2530; DS-ViT++ 64 images
 // (204) 1417 / 1493, 96 images (303) 1893 / 1718: the line is at 224.  96 rows leave no LDS for the LayerNorm weights: 64 images 1267 us against 1046
 // with 64 rows, 192 images 2016 against 2039, 256 images 2587 against 2530 on one card and 2492 against 2485 on another.  (See
-// profiles/dispatch_choices.txt.  The parts of a batch are not counted together here: 128 images in four take 1886 us, 1664 with 64 rows.)
+// profiles/dispatch_choices.txt.)  Parts of a batch that run side by side fill the compute units together, if not
+// evenly.  Us a pass, 32 / 64 rows, two parts and four (tiles of 64 rows in all of them): DS-ViT 64 images (260, 260) 941 / 979 and 954 / 1019, 72
+// images (292, 292) 1034 / 958 and 996 / 1014, 80 images (324, 324) 1090 / 999 and 1126 / 1092, 96 images 1228 / 1107 and 1269 / 1122, 160 images
+// 1937 / 1605 in four; DS-ViT++ 64 images in two (212) 1277 / 1379, 72 images (236) 1351 / 1402, 80 images (262, 276) 1458 / 1457 and 1530 / 1475, 96
+// images 1700 / 1590 and 1734 / 1616.
 // Two workgroups a compute unit (four wavefronts of three column blocks each, 64 rows) were slower, 2780 us when 64 rows took 2600 and
 // 96 rows 2710: eight wavefronts do not cover the weights' latency.
 int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {
@@ -406,7 +410,7 @@ int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {
     }
     const int64_t groups = B < a.gt.T ? B : a.gt.T, n = (int64_t)B * a.rows;
     auto tiles = [&](int bm) { return (n - groups) / bm + groups; };
-    const bool two = tiles(64) >= 224;
+    const bool two = tiles(64) >= 224 || (a.crowd > 1 && tiles(64) * a.crowd >= (dmax > 384 ? 270 : 300));
     if (dmax > 384)                                      // 13 column blocks: 128 registers per lane, at most 64 rows
         return two ? launch<13, 2, 4>(a, tiles(64), s) : launch<13, 1, 4>(a, tiles(32), s);
     return two ? launch<12, 2, 4>(a, tiles(64), s) : launch<12, 1, 8>(a, tiles(32), s);

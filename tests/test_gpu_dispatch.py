@@ -544,6 +544,22 @@ def test_vit_qkv_behind_a_block(gpu_lib, which, B):
     assert torch.isfinite(want).all() and torch.equal(got, want)
 
 
+# parts of a batch that count their tiles of 64 rows together, on both sides of the line, parts of unequal sizes: as above
+@pytest.mark.parametrize("which,B,parts", [("cross", 73, 2), ("cross", 77, 2), ("cross", 78, 4), ("pp", 79, 3), ("pp", 86, 2)])
+def test_vit_blocks_of_parts(gpu_lib, which, B, parts):
+    kw = {"cross": dict(depth=3), "pp": dict(embed=416, heads=8, head_dim=48, mlp=1664, depth=3, routes="pp")}[which]
+    arch = WL.vit_arch(**kw)
+    net = gpu_lib.build_vit(arch, WL.vit_params(arch, 9), DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(B)
+    imgs = torch.randn((B, 3, arch["image"], arch["image"]), generator=gen, device=DEV).to(torch.bfloat16)
+    over = (torch.arange(B, device=DEV, dtype=torch.int32) * 5 % arch["T"])[None].contiguous()
+    got, _ = gpu_lib.ds_forward_parts(net, imgs, parts, route_override=over)
+    net.c_struct.n_params -= 4 * arch["depth"]
+    want, _ = gpu_lib.ds_forward_parts(net, imgs, parts, route_override=over)
+    assert torch.isfinite(want).all() and torch.equal(got, want)
+
+
 # gates that take the sums of the stage's last block, against a float64 mean of that block's output: samples that start inside a tile
 # of 128 rows, that end in it, maps of a few tiles
 @pytest.mark.parametrize("image,B", [(224, 100), (150, 131), (236, 97)])
