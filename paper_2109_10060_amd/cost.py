@@ -63,6 +63,21 @@ def _paired(ta, tb, nk):
     return ta + tb <= 1000 and big != 3 and (nk <= 1 or choice(ta) == choice(tb))
 
 
+def _paired_wide(ta, na, tb, nb, k, few, strided):
+    """A projection of ta and a first layer of tb row tiles, na and nb columns and k channels as one launch of the 128-row kernel."""
+    def tile(t, n, conv):
+        if not conv and (128 < k < 320 and 64 < n <= 128 and t >= 3000 or k >= 768 and n > 64 and t * -(-n // 128) >= 2048):
+            return "wide"
+        wgs, slabs = t * -(-n // 64), -(-k // 64)
+        if k < 320:
+            return "32"
+        if slabs >= 8 and wgs <= (512 if slabs >= 32 else 256):
+            return "four shares"
+        return "two shares" if wgs <= 512 else "128" if k >= 512 and wgs <= 1536 else "64"
+    one = tile(ta, na, strided)
+    return k > 128 and few > 1000 and one == tile(tb, nb, False) and one not in ("wide", "four shares")
+
+
 def _separable(r, ci, co, s, k, kfull, tiled):
     """An unsliced depthwise + pointwise block that runs as one kernel: output size, channels, stride, filter size."""
     if ci % 8 or co % 8:
@@ -187,6 +202,11 @@ def resnet_cost(arch, routes) -> Cost:
         paired = _paired(_tiles(B, rs * rs, groups, 32) * -(-int(outs.max()) // 32), _tiles(B, r * r, groups, 32) * -(-int(mids.max()) // 32),
                          -(-int(arch["out"][s - 1].max() if s else so) // 64))
         inside = bool(rest and s == 0 and so <= 64 and so % 8 == 0 and mids.max() <= 64 and not paired)
+        # (beyond them too, where both take the same tile of the 128-row kernel)
+        paired = paired or not inside and _paired_wide(_tiles(B, rs * rs, groups), int(outs.max()), _tiles(B, r * r, groups), int(mids.max()),
+                                                       int(arch["out"][s - 1].max() if s else so),
+                                                       min(_tiles(B, rs * rs, groups, 32) * -(-int(outs.max()) // 32),
+                                                           _tiles(B, r * r, groups, 32) * -(-int(mids.max()) // 32)), s > 0)
         for b in range(nb):
             # dynamic depth: samples whose route has run its blocks of this stage contribute nothing
             on = (arch["nblk"][s][routes[s]] > b).astype(np.float64) if arch.get("nblk") is not None else np.ones(B)

@@ -184,6 +184,10 @@ int32_t ds_launch_gemm_small(const GemmArgs& a, int32_t max_mtiles, int32_t max_
 // two 1x1 layers of a few samples as one launch; neither reads what the other writes
 int32_t ds_launch_gemm_small_pair(const GemmArgs& a, int32_t mtiles_a, int32_t kout_a, const GemmArgs& b, int32_t mtiles_b, int32_t kout_b,
                                   hipStream_t s);
+// whether ds_launch_gemm_small runs this layer
+bool ds_gemm_small_takes(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout);
+// both as one launch of the 128-row kernel; DS_EUNSUPPORTED where either layer alone would take another kernel or another tile
+int32_t ds_launch_gemm_pair(const GemmArgs& a, int32_t mtiles_a, int32_t kout_a, const GemmArgs& b, int32_t mtiles_b, int32_t kout_b, hipStream_t s);
 // 3x3 stride-1 padding-1 layers on maps up to 59 pixels wide; DS_EUNSUPPORTED for any other shape
 int32_t ds_launch_conv3(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s);
 // the rest of a bottleneck block behind its first 1x1 layer (stride 1, packed rows, slot order): 3x3 layer, last 1x1 layer with its

@@ -672,7 +672,13 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
                     }
                     bn.x = nullptr;
                 }
-                if (!y1_ready) RC(launch_conv(pj, ml_out, s));
+                if (!y1_ready) {
+                    // (more of them too, where both take the same tile)
+                    const int32_t rc2 = ds_launch_gemm_pair(c1, ml_in.cap, max_out(g1f), pj, ml_out.cap, max_out(gpj), s);
+                    if (rc2 != DS_OK && rc2 != DS_EUNSUPPORTED) return rc2;
+                    y1_ready = rc2 == DS_OK;
+                    if (!y1_ready) RC(launch_conv(pj, ml_out, s));
+                }
                 shortcut = Pj;
             }
             if (!y1_ready)

@@ -27,6 +27,7 @@
 // a contiguous run of work items and the blocks that share an activation tile hit
 // the same L2.
 #include "gelu.h"
+#include <type_traits>
 
 namespace {
 
@@ -57,9 +58,34 @@ struct Tile {
     static_assert(WROWS * WCOLS == 4 && WROWS * WMT * 32 == BM, "4 wavefronts cover a 128-row tile");
 };
 
+// Two 1x1 layers of one input (a stage's first layer and its projection) as one launch: the first layer's workgroups, then the other's.
+// Apart, each of them starts with empty compute units and ends with most of them idle, 7 to 9 us together, and neither waits for the
+// other.  DS-ResNet, us a pass, two launches -> here: 33 images 837 -> 823, 48 images 963 -> 941, 64 images 1122 -> 1101, 96 images 1335 ->
+// 1320, 256 images 2603 -> 2597; DS-ResNet++ 64 images 1227 -> 1216, 256 images 3022 -> 3022.  Only pairs of up to 4000 or 8000
+// workgroups: 48 images 951 and 941, 96 images 1340 and 1331, 256 images 2611 and 2605.
+struct GemmPair {
+    GemmArgs p[2];
+    uint32_t split;                      // workgroups of the first layer
+    int32_t ny[2], mtiles[2];
+};
+__device__ __forceinline__ unsigned layer_of(const GemmArgs&) { return 0; }
+__device__ __forceinline__ unsigned layer_of(const GemmPair& p) { return blockIdx.x >= p.split; }
+__device__ __forceinline__ const GemmArgs& args_of(const GemmArgs& a, unsigned) { return a; }
+__device__ __forceinline__ const GemmArgs& args_of(const GemmPair& p, unsigned q) { return p.p[q]; }
+
 // KS: shares of the reduction, four wavefronts each; a share takes every KS-th slab
-template <int WROWS, int WCOLS, int WMT, int WNT, int BK, int KS, bool CONV, bool HASR>
-__global__ __launch_bounds__(NT * KS, KS > 1 ? 1 : BK == 128 ? 3 : (WMT * WNT == 2 && !CONV) ? (BK == 32 ? (HASR ? 5 : 6) : 5) : 1) void gemm_kernel(const GemmArgs a, const int ny, const int max_mtiles) {
+template <int WROWS, int WCOLS, int WMT, int WNT, int BK, int KS, bool CONV, bool HASR, class Args = GemmArgs>
+__global__ __launch_bounds__(NT * KS, KS > 1 ? 1 : BK == 128 ? 3 : (WMT * WNT == 2 && !CONV) ? (BK == 32 ? (HASR ? 5 : 6) : 5) : 1) void gemm_kernel(const Args args, const int ny0, const int max_mtiles0) {
+    constexpr bool PAIR = std::is_same<Args, GemmPair>::value;
+    const unsigned q = layer_of(args);
+    const GemmArgs& a = args_of(args, q);
+    unsigned block = blockIdx.x;
+    int ny = ny0, max_mtiles = max_mtiles0;
+    if constexpr (PAIR) {
+        if (q) block -= args.split;
+        ny = args.ny[q];
+        max_mtiles = args.mtiles[q];
+    }
     using TL = Tile<WROWS, WCOLS, WMT, WNT, BK, KS>;
     constexpr int BN = TL::BN, LDS_LD = BK, CPR = BK / 8, RPT = NT / CPR;   // chunks per row, rows per pass
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -81,9 +107,9 @@ __global__ __launch_bounds__(NT * KS, KS > 1 ? 1 : BK == 128 ? 3 : (WMT * WNT ==
     // ---- work item ------------------------------------------------------------------
     // m-tiles are dealt to the 8 XCDs round-robin; on one XCD consecutive blocks walk the n-tiles
     // of one m-tile, so the activation tile they share stays in that XCD's L2
-    const int j = (int)(blockIdx.x >> 3);
+    const int j = (int)(block >> 3);
     const int jm = j / ny, y = j - jm * ny;
-    const int mt = jm * 8 + (int)(blockIdx.x & 7);
+    const int mt = jm * 8 + (int)(block & 7);
     if (mt >= max_mtiles) return;
     const int4 me = ds_tile_record(a, mt);
     if (me.x < 0) return;
@@ -404,6 +430,26 @@ int32_t launch(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStrea
     return DS_OK;
 }
 
+template <int BK, int KS>
+int32_t launch_pair(GemmPair& p, const int32_t* kout, hipStream_t s) {
+    using TL = Tile<4, 1, 1, 2, BK, KS>;
+    auto kern = gemm_kernel<4, 1, 1, 2, BK, KS, true, false, GemmPair>;
+    {
+        const int32_t rc = ds_reserve_lds((const void*)kern, TL::SMEM, "sliced gemm");
+        if (rc) return rc;
+    }
+    unsigned grid[2];
+    for (int q = 0; q < 2; ++q) {
+        p.ny[q] = (kout[q] + TL::BN - 1) / TL::BN;
+        grid[q] = (unsigned)(((p.mtiles[q] + 7) / 8) * p.ny[q] * 8);
+    }
+    p.split = grid[0];
+    ProfScope prof(DS_K_GEMM, s);
+    hipLaunchKernelGGL(kern, dim3(grid[0] + grid[1]), dim3(NT * KS), TL::SMEM, s, p, 0, 0);
+    DS_CHECK_LAUNCH("sliced gemm");
+    return DS_OK;
+}
+
 }  // namespace
 
 // The most tiles B samples of `rows` rows can make in T groups: every non-empty group (at most min(B, T)) adds at most
@@ -414,8 +460,14 @@ size_t ds_mtile_capacity(int32_t B, int32_t rows, int32_t T) {
     return (size_t)((n - g) / BM + g);
 }
 
-int32_t ds_launch_gemm(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
-    if (max_mtiles <= 0 || max_kout <= 0) return DS_OK;
+namespace {
+
+enum GemmTile { SLAB32, SLAB64, SLAB64_2, SLAB64_4, SLAB128, WIDE32, WIDE64, WIDE64_CONV };
+
+bool is_conv(const GemmArgs& a) { return a.K > 1 || a.stride > 1 || a.pad > 0; }
+
+GemmTile tile_of(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout) {
+    const bool conv = is_conv(a);
     // ragged route slices favour the narrow 128x64 tile at high occupancy in every layer of the batch-256 networks.
     // Its slabs are 32 deep for short reductions and 64 deep from 256 reduction steps on: half the barriers and
     // twice the bytes in flight per workgroup outweigh the lower residency there.  256 images, us a launch, 32 -> 64 deep: DS-ResNet
@@ -429,26 +481,6 @@ int32_t ds_launch_gemm(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, 
     // workgroups per compute unit: DS-ResNet stage 2, 256 images, projection 83.9 -> 76.2 us with 32, first 1x1 105.3 -> 112.7; passes of
     // 64 images 1264 -> 1251, DS-ResNet++ 33 images 972 -> 961, 256 images 3006 / 3013)
     const bool deep = kmax >= 64 && (kmax * taps >= 320 || (kmax * taps >= 256 && a.R != nullptr));
-    // 32-bit byte offsets inside the kernel: activations and weights must each span less than 2 GiB
-    const long long slots = (long long)max_mtiles * BM / (a.rows > 0 ? a.rows : 1) + 1;
-    if (slots * a.a_sample_stride * 2 >= 0x7fffffffLL)
-        DS_FAIL(DS_EUNSUPPORTED, "sliced gemm: activation tensor spans 2 GiB or more");
-    if (((long long)a.n_seg * a.w_seg_stride + (long long)max_kout * a.w_ld + taps * a.w_tap_stride + kmax) * 2 >= 0x7fffffffLL)
-        DS_FAIL(DS_EUNSUPPORTED, "sliced gemm: weight tensor spans 2 GiB or more");
-    const bool conv = a.K > 1 || a.stride > 1 || a.pad > 0;
-    {
-        const int32_t rc = ds_launch_gemm_small(a, max_mtiles, max_kout, s);
-        if (rc != DS_EUNSUPPORTED) return rc;
-    }
-    if (conv) {
-        const int32_t rc = ds_launch_conv3(a, max_mtiles, max_kout, s);
-        if (rc != DS_EUNSUPPORTED) return rc;
-    }
-#define DS_GEMM_DISPATCH(...)                                                                          \
-    (conv ? (a.R ? launch<__VA_ARGS__, true, true>(a, max_mtiles, max_kout, s)                         \
-                 : launch<__VA_ARGS__, true, false>(a, max_mtiles, max_kout, s))                       \
-          : (a.R ? launch<__VA_ARGS__, false, true>(a, max_mtiles, max_kout, s)                        \
-                 : launch<__VA_ARGS__, false, false>(a, max_mtiles, max_kout, s)))
     // 128 columns a workgroup, two wavefronts of 64 x 64 either way, so that rows go through LDS half as often, where a launch still has
     // several generations of such workgroups and few of them are half empty.
     // - layers of at most 256 channels whose columns are all in one such tile: DS-ResNet stage 2, first 1x1, 256 images 110 -> 95 us (its
@@ -460,14 +492,14 @@ int32_t ds_launch_gemm(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, 
     // last 1x1 39.5 -> 49.7, stage 4, first 1x1 28.4 -> 37.5).
     const long long tiles128 = (long long)max_mtiles * a.n_seg * ((max_kout + 127) / 128) * (a.crowd > 1 ? a.crowd : 1);
     if (!a.R && max_kout > 64) {
-        if (!conv && !deep && kmax > 128 && max_kout <= 128 && tiles128 >= 3000) return launch<2, 2, 2, 2, 32, 1, false, false>(a, max_mtiles, max_kout, s);
+        if (!conv && !deep && kmax > 128 && max_kout <= 128 && tiles128 >= 3000) return WIDE32;
         // - linear layers of 768 channels and more: 64 images of 197 tokens 768 -> 3072 (2376 tiles) 70 -> 65.5, 256 of 256 tokens 308 -> 278, with GELU
         //   128 of 197 tokens 131 -> 125.  From 1200 tiles on they gain as well, but there a stage of sixteen route groups loses (DS-ResNet stage 4, first
         //   1x1 of the strided block, 256 images, 1568 tiles, 41.8 -> 50.5); 384 channels lose at any size (64 images of 197 tokens 28.8 -> 31).
-        if (!conv && kmax >= 768 && tiles128 >= 2048) return launch<2, 2, 2, 2, 64, 1, false, false>(a, max_mtiles, max_kout, s);
-        if (taps > 1 && deep && tiles128 >= 768) return launch<2, 2, 2, 2, 64, 1, true, false>(a, max_mtiles, max_kout, s);
+        if (!conv && kmax >= 768 && tiles128 >= 2048) return WIDE64;
+        if (taps > 1 && deep && tiles128 >= 768) return WIDE64_CONV;
     }
-    if (!deep) return DS_GEMM_DISPATCH(4, 1, 1, 2, 32, 1);   // 64-wide tile, 32-deep slabs
+    if (!deep) return SLAB32;   // 64-wide tile, 32-deep slabs
     // launches of about one generation with long reductions (below): 128-deep slabs halve the number of dependent rounds (256 images of
     // DS-ResNet, stage 4: strided 3x3 64.3 -> 55.7 us, first 1x1 32.3 -> 28.5, pass 3028 -> 3013; without the bound of six workgroups a compute
     // unit the projections of stages 3 and 4 49.0 -> 58.7 and 45.3 -> 50.1, pass 3070, DS-MBNet++ 921 -> 970)
@@ -481,9 +513,77 @@ int32_t ds_launch_gemm(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, 
     // whatever the slabs: DS-ResNet 33 images 903 / 901 / 913, 64 images 1261 / 1253 / 1264, 96 images 1544 / 1533 / 1532; DS-ResNet++ 33
     // images 948 / 948 / 970, 64 images 1351 / 1356 / 1379; DS-MBNet++ 40 images 332 / 332 / 343.  Twice all these lines: DS-ResNet 16 / 33 / 64 / 96
     // images 715 / 905 / 1248 / 1523 -> 701 / 912 / 1265 / 1537, DS-ResNet++ 33 images 948 -> 990, DS-MBNet++ 40 images 331 -> 356.
-    if (!a.ordered && slabs >= 8 && all <= (slabs >= 32 ? 512 : 256)) return DS_GEMM_DISPATCH(4, 1, 1, 2, 64, 4);
-    if (!a.ordered && slabs >= 4 && all <= 512) return DS_GEMM_DISPATCH(4, 1, 1, 2, 64, 2);
-    if (kmax >= 512 && wgs <= 256 * 6) return DS_GEMM_DISPATCH(4, 1, 1, 2, 128, 1);
-    return DS_GEMM_DISPATCH(4, 1, 1, 2, 64, 1);
+    if (!a.ordered && slabs >= 8 && all <= (slabs >= 32 ? 512 : 256)) return SLAB64_4;
+    if (!a.ordered && slabs >= 4 && all <= 512) return SLAB64_2;
+    if (kmax >= 512 && wgs <= 256 * 6) return SLAB128;
+    return SLAB64;
+}
+
+}  // namespace
+
+int32_t ds_launch_gemm(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
+    if (max_mtiles <= 0 || max_kout <= 0) return DS_OK;
+    int kmax = 0;
+    for (int t = 0; t < a.gt.T; ++t) kmax = a.gt.k_in[t] > kmax ? a.gt.k_in[t] : kmax;
+    const long long taps = (long long)a.K * (a.Kw > 0 ? a.Kw : a.K);
+    // 32-bit byte offsets inside the kernel: activations and weights must each span less than 2 GiB
+    const long long slots = (long long)max_mtiles * BM / (a.rows > 0 ? a.rows : 1) + 1;
+    if (slots * a.a_sample_stride * 2 >= 0x7fffffffLL)
+        DS_FAIL(DS_EUNSUPPORTED, "sliced gemm: activation tensor spans 2 GiB or more");
+    if (((long long)a.n_seg * a.w_seg_stride + (long long)max_kout * a.w_ld + taps * a.w_tap_stride + kmax) * 2 >= 0x7fffffffLL)
+        DS_FAIL(DS_EUNSUPPORTED, "sliced gemm: weight tensor spans 2 GiB or more");
+    const bool conv = is_conv(a);
+    {
+        const int32_t rc = ds_launch_gemm_small(a, max_mtiles, max_kout, s);
+        if (rc != DS_EUNSUPPORTED) return rc;
+    }
+    if (conv) {
+        const int32_t rc = ds_launch_conv3(a, max_mtiles, max_kout, s);
+        if (rc != DS_EUNSUPPORTED) return rc;
+    }
+#define DS_GEMM_DISPATCH(...)                                                                          \
+    (conv ? (a.R ? launch<__VA_ARGS__, true, true>(a, max_mtiles, max_kout, s)                         \
+                 : launch<__VA_ARGS__, true, false>(a, max_mtiles, max_kout, s))                       \
+          : (a.R ? launch<__VA_ARGS__, false, true>(a, max_mtiles, max_kout, s)                        \
+                 : launch<__VA_ARGS__, false, false>(a, max_mtiles, max_kout, s)))
+    switch (tile_of(a, max_mtiles, max_kout)) {
+        case WIDE32: return launch<2, 2, 2, 2, 32, 1, false, false>(a, max_mtiles, max_kout, s);
+        case WIDE64: return launch<2, 2, 2, 2, 64, 1, false, false>(a, max_mtiles, max_kout, s);
+        case WIDE64_CONV: return launch<2, 2, 2, 2, 64, 1, true, false>(a, max_mtiles, max_kout, s);
+        case SLAB32: return DS_GEMM_DISPATCH(4, 1, 1, 2, 32, 1);   // 64-wide tile, 32-deep slabs
+        case SLAB64_4: return DS_GEMM_DISPATCH(4, 1, 1, 2, 64, 4);
+        case SLAB64_2: return DS_GEMM_DISPATCH(4, 1, 1, 2, 64, 2);
+        case SLAB128: return DS_GEMM_DISPATCH(4, 1, 1, 2, 128, 1);
+        default: return DS_GEMM_DISPATCH(4, 1, 1, 2, 64, 1);
+    }
 #undef DS_GEMM_DISPATCH
+}
+
+int32_t ds_launch_gemm_pair(const GemmArgs& a, int32_t mtiles_a, int32_t kout_a, const GemmArgs& b, int32_t mtiles_b, int32_t kout_b, hipStream_t s) {
+    if (mtiles_a <= 0 || mtiles_b <= 0 || kout_a <= 0 || kout_b <= 0 || a.B <= 0 || b.B <= 0) return DS_EUNSUPPORTED;
+    const GemmArgs* ps[2] = {&a, &b};
+    const int32_t mt[2] = {mtiles_a, mtiles_b}, ko[2] = {kout_a, kout_b};
+    for (int q = 0; q < 2; ++q) {
+        const GemmArgs& p = *ps[q];
+        if (p.K != 1 || p.Kw > 1 || p.pad || p.R || p.ordered || p.n_seg != 1) return DS_EUNSUPPORTED;
+        int kmax = 0;
+        for (int t = 0; t < p.gt.T; ++t) kmax = p.gt.k_in[t] > kmax ? p.gt.k_in[t] : kmax;
+        // (shorter ones are thin_kernel's; spans as in ds_launch_gemm)
+        const long long slots = (long long)mt[q] * BM / (p.rows > 0 ? p.rows : 1) + 1;
+        if (kmax <= 128 || slots * p.a_sample_stride * 2 >= 0x7fffffffLL || ((long long)ko[q] * p.w_ld + kmax) * 2 >= 0x7fffffffLL ||
+            ds_gemm_small_takes(p, mt[q], ko[q]))
+            return DS_EUNSUPPORTED;
+    }
+    // the tile that either layer takes alone, so that pairing changes no sum
+    const GemmTile tile = tile_of(a, mtiles_a, kout_a);
+    if (tile != tile_of(b, mtiles_b, kout_b)) return DS_EUNSUPPORTED;
+    GemmPair p;
+    for (int q = 0; q < 2; ++q) { p.p[q] = *ps[q]; p.mtiles[q] = mt[q]; }
+    switch (tile) {
+        case SLAB32: return launch_pair<32, 1>(p, ko, s);
+        case SLAB64: return launch_pair<64, 1>(p, ko, s);
+        case SLAB128: return launch_pair<128, 1>(p, ko, s);
+        case SLAB64_2: return launch_pair<64, 2>(p, ko, s);
+        default: return DS_EUNSUPPORTED;
+    }
 }

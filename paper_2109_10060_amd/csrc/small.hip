@@ -390,16 +390,21 @@ bool small_in_reach(const GemmArgs& a, const SmallSize& z, int32_t max_mtiles, i
 //               (patch embedding of DS-ViT, twelve slabs, 1 / 5 / 16 images 13.6 -> 9.3 / 15.6 -> 10.5 / 14.6 -> 10.5)
 //   beyond      the 128-row kernels have enough workgroups and read less per product -- except the strided KxK layers
 //               (no staged patch for them), which stay here up to 1700 tiles (stage 4, 33 samples 34.3 -> 20.1)
+bool ds_gemm_small_takes(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout) {
+    if (max_mtiles <= 0 || max_kout <= 0 || a.B <= 0) return false;
+    if (a.K > 15 || a.Kw > 15) return false;                  // tap masks of 16 bits
+    const SmallSize z = small_size(a, max_kout);
+    const bool strided = z.taps > 1 && a.stride > 1;
+    if (z.t > 1700 || (z.t > 1000 && !a.ordered && !(strided && z.nk >= 24))) return false;
+    return small_in_reach(a, z, max_mtiles, max_kout);
+}
+
 int32_t ds_launch_gemm_small(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
-    if (max_mtiles <= 0 || max_kout <= 0 || a.B <= 0) return DS_EUNSUPPORTED;
-    if (a.K > 15 || a.Kw > 15) return DS_EUNSUPPORTED;        // tap masks of 16 bits
+    if (!ds_gemm_small_takes(a, max_mtiles, max_kout)) return DS_EUNSUPPORTED;
     const bool conv = a.K > 1 || a.stride > 1 || a.pad > 0;
     const SmallSize z = small_size(a, max_kout);
     const int nk = z.nk;
     const long long t = z.t;
-    const bool strided = z.taps > 1 && a.stride > 1;
-    if (t > 1700 || (t > 1000 && !a.ordered && !(strided && nk >= 24))) return DS_EUNSUPPORTED;
-    if (!small_in_reach(a, z, max_mtiles, max_kout)) return DS_EUNSUPPORTED;
 #define DS_SMALL(...)                                                                       \
     (conv ? (a.R ? launch<__VA_ARGS__, true, true>(a, max_mtiles, max_kout, s)               \
                  : launch<__VA_ARGS__, true, false>(a, max_mtiles, max_kout, s))             \

@@ -498,6 +498,40 @@ def test_resnet_rest_of_a_block(gpu_lib, which, image, B):
         assert relerr_max(host(logits[k]), host(want[0])) < TOL_BF16
 
 
+# a stage's projection and first layer as one launch of the 128-row kernel, in each of its tiles (two shares, slabs of 32, 64 and 128
+# channels), and where the two take different ones, against one image alone
+@pytest.mark.parametrize("which,image,B", [("width", 224, 12), ("width", 224, 33), ("width", 224, 65), ("width", 90, 130), ("pp", 224, 33),
+                                           ("depth", 150, 70), ("half", 224, 90)])
+def test_resnet_first_layers_of_a_stage(gpu_lib, which, image, B):
+    kw = {"width": {}, "pp": dict(blocks=(3, 4, 8, 3), routes="pp"), "depth": dict(routes="depth"), "half": dict(width_div=2)}[which]
+    arch = WL.resnet_arch(image=image, **kw)
+    net = gpu_lib.build_resnet(arch, WL.resnet_params(arch, 41), DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(image + B)
+    kinds = min(B, 2 * arch["T"])
+    imgs = torch.randn((kinds, 3, image, image), generator=gen, device=DEV).to(torch.bfloat16)
+    n = torch.arange(kinds, device=DEV, dtype=torch.int32)
+    over = torch.stack([(n + st * (not arch.get("single_gate"))) % arch["T"] for st in range(4)])
+
+    def run(which):
+        taps, r = {}, ((image + 1) // 2 + 1) // 2
+        for st in range(1, 4):
+            r = (r - 1) // 2 + 1
+            taps[sum(arch["blocks"][:st])] = torch.zeros((len(which), r * r, int(arch["out"][st].max())), dtype=torch.bfloat16, device=DEV)
+        gpu_lib.ds_forward_taps(net, imgs[which].contiguous(), taps, route_override=over[:, which].contiguous())
+        return taps
+
+    got = run(torch.arange(B, device=DEV) % kinds)
+    for k in range(kinds):
+        ref = run(torch.tensor([k], device=DEV))
+        for i, t in got.items():
+            # (as for the rest of a block)
+            b = host(ref[i][0])
+            for j in range(k, B, max(kinds, (B - k - 1) // kinds * kinds)):
+                a = host(t[j])
+                assert np.linalg.norm(a - b) < 2.0 ** -9 * (4 * (i + 1)) ** 0.5 * np.linalg.norm(b) and relerr_max(a, b) < TOL_BF16, (i, k, j)
+
+
 # 7x7 stem and max-pool in one kernel: the first block passes its input on (projection the identity, residual branch zero), so its
 # output is the pooled map.  Tiles of 3 x 8 pooled pixels: maps of one pixel to several tiles, ragged on both sides
 @pytest.mark.parametrize("image,B", [(4, 1), (12, 3), (32, 8), (44, 5), (100, 16), (224, 9)])
