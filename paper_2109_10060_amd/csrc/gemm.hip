@@ -60,9 +60,9 @@ struct Tile {
 
 // Two 1x1 layers of one input (a stage's first layer and its projection) as one launch: the first layer's workgroups, then the other's.
 // Apart, each of them starts with empty compute units and ends with most of them idle, 7 to 9 us together, and neither waits for the
-// other.  DS-ResNet, us a pass, two launches -> here: 33 images 837 -> 823, 48 images 963 -> 941, 64 images 1122 -> 1101, 96 images 1335 ->
-// 1320, 256 images 2603 -> 2597; DS-ResNet++ 64 images 1227 -> 1216, 256 images 3022 -> 3022.  Only pairs of up to 4000 or 8000
-// workgroups: 48 images 951 and 941, 96 images 1340 and 1331, 256 images 2611 and 2605.
+// other.  DS-ResNet, us a pass, two launches -> here: 33 images 838 -> 816, 48 images 976 -> 937, 64 images 1125 -> 1096, 96 images 1346 ->
+// 1320, 256 images 2629 -> 2617; DS-ResNet++ 64 images 1227 -> 1216, 256 images 3051 -> 3056 and 3022 -> 3022.  Only pairs of up to 4000 or 8000
+// workgroups (96 images 1320 without a limit): 1340 and 1331, 256 images (2597) 2611 and 2605.
 struct GemmPair {
     GemmArgs p[2];
     uint32_t split;                      // workgroups of the first layer

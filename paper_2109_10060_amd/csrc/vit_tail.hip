@@ -378,7 +378,8 @@ int32_t launch(const VitTailArgs& a, int64_t tiles, hipStream_t s) {
 // compute units to spread to; with 13 wavefronts, where 36 column blocks are three rounds of which one is mostly idle, later.  Us a pass of
 // DS-ViT, own launch / here: 8 images (57 tiles of 32 rows) 545 / 571, 9 images (64) 642 / 627, 16 images 648 / 651, 17 images 750 / 682, 32
 // images 845 / 748, 64 images 1045 / 972, 256 images 2576 / 2447; DS-ViT++ 19 images (135) 1025 / 1047, 24 images (170) 1041 / 1033, 32 images
-// 1110 / 1051, 256 images 3817 / 3652.  Parts of a batch count together: 32 images in two 800 / 751, 128 in four 1910 / 1657; 256 in two 2325 / 2440.
+// 1110 / 1051, 256 images 3817 / 3652.  Parts of a batch count together: 32 images in two 800 / 751, 128 in four 1674 /
+// 1409, 256 in four 2624 / 2454, in three 2387 / 2315, in two 2342 / 2436 (224 and 384 images in two 2182 / 2097 and 3236 / 3206).
 bool ds_vit_tail_qkv(const GroupTable& gt, int32_t B, int32_t rows, int32_t crowd) {
     int dmax = 0;
     for (int t = 0; t < gt.T; ++t) dmax = gt.k_out[t] > dmax ? gt.k_out[t] : dmax;
