@@ -1,6 +1,6 @@
 // Grouped prefix-slice linear / 1x1 layer with a short reduction (slices of at most 64, with a residual 128, input channels): Section 3.2,
-// Eq. 8 / Eq. 9 with split batch-norm (Eq. 14), optional residual and ReLU -- the third convolution of the first-stage
-// bottlenecks (64 r -> 256 r channels on 56x56 maps) and that stage's projection shortcut.
+// Eq. 8 / Eq. 9 with split batch-norm (Eq. 14), optional residual and ReLU -- the third convolution of bottlenecks with
+// narrow slices (behind a strided 3x3 layer, on maps wider than 59 pixels, or in batches below bneck_kernel's line) and their projection shortcut.
 //
 // With so short a reduction these layers are streams: per output element one residual read, one write and a handful
 // of multiply-adds.  gemm_kernel runs them as one workgroup per (128 rows, 64 columns) whose lifetime is its fixed

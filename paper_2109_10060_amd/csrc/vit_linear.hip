@@ -6,11 +6,12 @@
 // layernorm16_kernel) and a run of 32-column blocks of the output, NW at a time, one per wavefront.  A wavefront reads its
 // weight operands as contiguous kilobytes straight into registers, D in flight, so neither the weights nor the partial
 // sums touch LDS.  Two uses.
-// Large batches: the Q/K/V layer with 8 wavefronts and 64 rows, all columns in one workgroup (the rows are read once;
+// Large batches: the first block's Q/K/V layer (the others come with the block in front, from a few dozen tiles on) with 8
+// wavefronts and 64 rows, all columns in one workgroup (the rows are read once;
 // gemm_kernel read them once per 64 columns).  A finished block is traded between the halves of the wavefront and stored from
 // its registers, 16 bytes a lane (DIRECT): pieces of 64 bytes where a stage in LDS would make whole lines, but without the stage
 // two workgroups share a compute unit, one normalises rows while the other multiplies, and no wavefront waits for another
-// between blocks.  Us a pass, 12 wavefronts, 64 or 96 rows and a stage -> here: DS-ViT 64 images 1058 -> 1041, 140 images 1697
+// between blocks.  Us a pass with it in every block, 12 wavefronts, 64 or 96 rows and a stage -> here: DS-ViT 64 images 1058 -> 1041, 140 images 1697
 // -> 1657, 256 images 2663 -> 2643; DS-ViT++ 64 images 1418 -> 1396, 256 images 3947 -> 3801 (eight operands in flight instead of four
 // 3760, but the others 1049, 1681, 2652 and 1399; 32 rows 256 images 2700 and 3906).
 // Few images: all four layers of a block with 4 wavefronts and 32 rows, where a launch is bound by latency and by how many
