@@ -23,8 +23,9 @@
 
 namespace {
 
-constexpr int BM = DS_GEMM_BM, NT = 256;
+constexpr int BM = DS_GEMM_BM, NT = 256, SUM_ROWS = DS_BNECK_SUM_ROWS;
 constexpr uint32_t OOB = 0x80000000u;
+static_assert(SUM_ROWS == 64 && BM == 2 * SUM_ROWS, "a half of the tile, two wavefronts, a piece of the sums");
 constexpr int RMAX = 248, ZROW = RMAX;         // patch rows: 128 + 2 (W + 1), W <= 59; one more of zeros
 constexpr int NR = (RMAX * 4 + NT - 1) / NT;
 constexpr int TILE_BYTES = BM * 128;           // [128 rows][64 columns], 16-byte chunk c of row r at c ^ (r & 7)
@@ -37,8 +38,8 @@ struct Layout {
     static constexpr int MAIN = CONV > OUT ? CONV : OUT;
     static constexpr int N_OUT = 128 * NB;                      // output columns the constants have room for
     static constexpr int CST = MAIN, ROWS = CST + (PROJ ? 4 : 2) * N_OUT * 4, CST2 = ROWS + 2 * BM * 4, SUMS = CST2 + (CHAIN ? 4 : 2) * NB * 32 * 4;
-    // without a next block: column sums of each wavefront's rows, of the tile's first and of its second sample
-    static constexpr int SMEM = SUMS, SMEM_SUMS = SUMS + 4 * 2 * N_OUT * 4;
+    // without a next block: column sums of each wavefront's rows
+    static constexpr int SMEM = SUMS, SMEM_SUMS = SUMS + 4 * N_OUT * 4;
 };
 
 __device__ __forceinline__ int sw(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
@@ -315,8 +316,6 @@ __global__ __launch_bounds__(NT, NB == 2 ? 3 : 2) void bneck_kernel(const BneckA
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc1[t][v] = 0.f;
     char *W3 = smem + TILE_BYTES, *WP = W3 + L::W3, *W1 = WP + L::WP;
-    // the tile's first row of another sample than its first one's (at least 128 rows a sample: two at the most)
-    const int split = ((grow0 / rows) + 1) * rows - grow0;
     float* colsum = (float*)(smem + L::SUMS);
     char* my_row = tile + prow * 128;
     const int px7 = prow & 7;
@@ -400,29 +399,25 @@ __global__ __launch_bounds__(NT, NB == 2 ? 3 : 2) void bneck_kernel(const BneckA
         if constexpr (!CHAIN) {
             if (a.sums) {
                 // sums over this wavefront's rows (as stored), 8 columns a lane, then over the 8 lanes that share the columns
+                float t[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int side = 0; side < 2; ++side) {
-                    if (side && split >= BM) break;
-                    float t[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                for (int i = 0; i < 4; ++i) {
+                    const int r = srow + 8 * i;
+                    if (rowZ[r] < 0) continue;
+                    const uint4 q = *(const uint4*)(tile + r * 128 + (((lane & 7) ^ (r & 7)) * 16));
+                    const uint32_t u[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int r = srow + 8 * i;
-                        if (rowZ[r] < 0 || (r >= split) != (side == 1)) continue;
-                        const uint4 q = *(const uint4*)(tile + r * 128 + (((lane & 7) ^ (r & 7)) * 16));
-                        const uint32_t u[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            t[2 * k] += __uint_as_float(u[k] << 16);
-                            t[2 * k + 1] += __uint_as_float(u[k] & 0xffff0000u);
-                        }
+                    for (int k = 0; k < 4; ++k) {
+                        t[2 * k] += __uint_as_float(u[k] << 16);
+                        t[2 * k + 1] += __uint_as_float(u[k] & 0xffff0000u);
                     }
+                }
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) t[k] = sum_of_8(t[k]);
-                    if (lane < 8) {
-                        float* p = colsum + (wave * 2 + side) * L::N_OUT + n0 + lane * 8;
-                        *(float4*)p = make_float4(t[0], t[1], t[2], t[3]);
-                        *(float4*)(p + 4) = make_float4(t[4], t[5], t[6], t[7]);
-                    }
+                for (int k = 0; k < 8; ++k) t[k] = sum_of_8(t[k]);
+                if (lane < 8) {
+                    float* p = colsum + wave * L::N_OUT + n0 + lane * 8;
+                    *(float4*)p = make_float4(t[0], t[1], t[2], t[3]);
+                    *(float4*)(p + 4) = make_float4(t[4], t[5], t[6], t[7]);
                 }
             }
         }
@@ -449,20 +444,13 @@ __global__ __launch_bounds__(NT, NB == 2 ? 3 : 2) void bneck_kernel(const BneckA
     if constexpr (!CHAIN) {
         if (!a.sums) return;
         __syncthreads();
-        const int S = (rows + BM - 1) / BM + 1, sl = grow0 / rows, first = grow0 / BM - sl * rows / BM;     // this tile's place among the first sample's
-        float* to = a.sums + (int64_t)(slot0 + sl) * S * a.out_full;
-        for (int i = tid; i < out; i += NT) {
-            float t[2];
+        // a tile starts at a multiple of 64 rows of a sample, so either half is one piece of one sample, whoever its neighbours are
 #pragma unroll
-            for (int side = 0; side < 2; ++side) {
-                t[side] = 0.f;
-#pragma unroll
-                for (int w = 0; w < 4; ++w) t[side] += colsum[(w * 2 + side) * L::N_OUT + i];
-            }
-            to[(int64_t)first * a.out_full + i] = t[0];
-            // a sample whose last row is here in its last tile but one leaves the last place empty
-            if (split <= BM && first == S - 2) to[(int64_t)(S - 1) * a.out_full + i] = 0.f;
-            if (split < BM && grow0 + split < rows_g) to[(int64_t)S * a.out_full + i] = t[1];
+        for (int h = 0; h < 2; ++h) {
+            const int m = grow0 + h * SUM_ROWS, sl = m / rows;
+            if (m >= rows_g) break;
+            float* to = a.sums + ((int64_t)(slot0 + sl) * (rows / SUM_ROWS) + (m - sl * rows) / SUM_ROWS) * a.out_full;
+            for (int i = tid; i < out; i += NT) to[i] = colsum[2 * h * L::N_OUT + i] + colsum[(2 * h + 1) * L::N_OUT + i];
         }
         return;
     }
@@ -517,7 +505,7 @@ int blocks_of(const BneckArgs& a) {
 }  // namespace
 
 bool ds_bneck_runs(const BneckArgs& a, int32_t B, int32_t max_mtiles) {
-    if (BM + 2 * (a.W + 1) > RMAX || (a.sums && (a.w1 || a.H * a.W < BM))) return false;
+    if (BM + 2 * (a.W + 1) > RMAX || (a.sums && (a.w1 || (a.H * a.W) % SUM_ROWS))) return false;
     int mmax = 0, omax = 0, xmax = 0, nmax = 0;
     for (int t = 0; t < a.gt.T; ++t) {
         const int x = a.x ? a.kx[t] : 0, n = a.w1 ? a.next[t] : 0;

@@ -201,7 +201,7 @@ struct BneckArgs {
     const float *sp, *hp;                // its tables [row][tab3]
     const int32_t* x_index;              // slot -> block of x
     bf16_t *z, *y1_next;
-    float* sums;                         // null, or (no next block, at least 128 rows a slot) sums of z over rows [slot][ds_bneck_splits][out_full]
+    float* sums;                         // null, or (no next block, slots of whole pieces) sums of z over pieces of 64 rows of a slot [slot][piece][out_full]
     int64_t y1_ss, z_ss, x_ss;           // elements per slot (y1_next as y1)
     int32_t mid_full, out_full, x_full, tab3, H, W;
     const int4* mtiles;
@@ -212,8 +212,7 @@ struct BneckArgs {
 };
 bool ds_bneck_runs(const BneckArgs& a, int32_t B, int32_t max_mtiles);
 int32_t ds_launch_bneck(const BneckArgs& a, int32_t B, int32_t max_mtiles, hipStream_t s);
-// most row tiles that a sample of `rows` rows has a part in
-inline int32_t ds_bneck_splits(int32_t rows) { return (rows + DS_GEMM_BM - 1) / DS_GEMM_BM + 1; }
+constexpr int DS_BNECK_SUM_ROWS = 64;    // rows of a slot in a piece of BneckArgs::sums
 
 static inline const int4* ds_mtile_entries(const void* list) { return (const int4*)((const char*)list + 16); }
 static inline const int32_t* ds_mtile_count(const void* list) { return (const int32_t*)list; }

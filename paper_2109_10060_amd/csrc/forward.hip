@@ -637,12 +637,14 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
                     memcpy(bn.next, ch.k_out, sizeof(bn.next));
                 }
                 // A stage's last block, which every route runs, sums its output for the next gate's pooling, which then reads no map: DS-ResNet
-                // 96 / 128 / 256 images 1386 / 1685 / 2717 -> 1381 / 1657 / 2690 us a pass, 256 in four parts 2650 -> 2618.  Of fewer images the pool finds
-                // the map in the caches and the sums only make the block longer: 33 / 64 images 844 / 1149 -> 848 / 1151, 64 in two parts 1092 -> 1099.
-                if (b + 1 == nb && st < 3 && !d.single_gate && !d.nblk && rout * rout >= DS_GEMM_BM) {
+                // 96 / 128 / 256 images 1322 / 1610 / 2630 -> 1320 / 1595 / 2610 us a pass, 256 in two and four parts 2517 / 2581 -> 2506 / 2566.  Of fewer
+                // images the pool finds the map in the caches and the sums only make the block longer: 33 / 64 images 817 / 1106 -> 822 / 1108, 64 in two
+                // parts 1082 -> 1086.  Maps of whole pieces of 64 rows (56x56; not 28x28): a score is the sample's alone, so pieces are cut
+                // by the sample, and with 16 rows a piece 28x28 maps cost the block and the gate what the pool does (256 images 2578 -> 2586).
+                if (b + 1 == nb && st < 3 && !d.single_gate && !d.nblk && rout * rout % DS_BNECK_SUM_ROWS == 0) {
                     GateArgs gn = g;
                     gn.C = 4 * w; gn.C_mlp = d.hidden[st + 1]; gn.x_sample_stride = bn.z_ss;
-                    if (Bs >= 96 && B > 2 && ds_gate_takes_sums(gn) && (size_t)B * ds_bneck_splits(rout * rout) * 4 * w * sizeof(float) <= ds_gate_partial_bytes(B, p.gate_c))
+                    if (Bs >= 96 && B > 2 && ds_gate_takes_sums(gn) && (size_t)B * (rout * rout / DS_BNECK_SUM_ROWS) * 4 * w * sizeof(float) <= ds_gate_partial_bytes(B, p.gate_c))
                         bn.sums = p.gate_partial;
                 }
             }
@@ -692,7 +694,7 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
                 if (rest != DS_OK && rest != DS_EUNSUPPORTED) return rest;
             }
             if (rest == DS_OK) {
-                if (bn.sums) map_splits = ds_bneck_splits(rout * rout);
+                if (bn.sums) map_splits = rout * rout / DS_BNECK_SUM_ROWS;
                 if (next_any) {
                     bf16_t* t = Y1; Y1 = Y2; Y2 = t;
                     y1_ready = true;

@@ -594,9 +594,9 @@ def test_vit_blocks_of_parts(gpu_lib, which, B, parts):
     assert torch.isfinite(want).all() and torch.equal(got, want)
 
 
-# gates that take the sums of the stage's last block, against a float64 mean of that block's output: samples that start inside a tile
-# of 128 rows, that end in it, maps of a few tiles
-@pytest.mark.parametrize("image,B", [(224, 100), (150, 131), (236, 97)])
+# gates that take the sums of the stage's last block (maps of whole pieces of 64 rows: the first stage's at 224 and 96 pixels), samples
+# that start in the middle of a tile of 128 rows, and gates that pool the map, against a float64 mean of that block's output
+@pytest.mark.parametrize("image,B", [(224, 100), (96, 100), (150, 131), (236, 97)])
 def test_resnet_gates_on_the_last_blocks_sums(gpu_lib, image, B):
     arch = WL.resnet_arch(image=image)
     p = WL.resnet_params(arch, 37)
@@ -633,3 +633,46 @@ def test_resnet_gates_on_the_last_blocks_sums(gpu_lib, image, B):
         got = routes[st + 1].cpu().numpy()
         assert clear.sum() > 0.9 * B and len(set(z.argmax(1)[clear])) > 1
         assert np.array_equal(got[clear], z.argmax(1)[clear])
+
+
+# An image's gate scores are the same bits beside other neighbours.  The gate is made to show its pooled mean of one channel: a route's
+# score is that mean, another's a threshold per image, so that bisecting over the floats finds its bits; then other orders of the batch.
+@pytest.mark.parametrize("stage", [1, 2])
+@pytest.mark.parametrize("image,B", [(224, 97), (96, 104), (160, 96), (208, 96), (72, 100)])
+def test_resnet_gate_scores_do_not_depend_on_the_neighbours(gpu_lib, image, B, stage):
+    arch = WL.resnet_arch(image=image, blocks=(2, 2, 1, 1))
+    p = WL.resnet_params(arch, 43)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(image)
+    # (contrast over four decades, and layers without the shifts that would hide it: a map's fp32 sum then depends on its order)
+    for name in p:
+        if name.endswith(".bn"):
+            p[name] = {k: v * (k not in ("beta", "mean")) for k, v in p[name].items()}
+    contrast = 10.0 ** (4.0 * torch.rand((B, 1, image // 4, image // 4), generator=gen, device=DEV).repeat_interleave(4, 2).repeat_interleave(4, 3) - 3.0)
+    imgs = (torch.randn((B, 3, image, image), generator=gen, device=DEV) * contrast).to(torch.bfloat16)
+    bias = torch.zeros((4, B, arch["T"]), device=DEV)
+    for st in range(4):
+        bias[st].scatter_(1, ((torch.arange(B, device=DEV) * 7 + st) % arch["T"])[:, None], 1e4)
+    bias[stage] = torch.tensor([0.0, 0.0] + [-1e30] * (arch["T"] - 2), device=DEV)
+    plain = torch.arange(B, device=DEV)
+    orders = [plain.flip(0), plain.roll(1), *(torch.randperm(B, generator=gen, device=DEV) for _ in range(4))]
+    for channel in range(5, 11):
+        for k in ("w1", "b1", "w2", "b2"):
+            p[f"s{stage}.gate.{k}"] = np.zeros_like(p[f"s{stage}.gate.{k}"])
+        p[f"s{stage}.gate.w1"][0, channel] = p[f"s{stage}.gate.w2"][0, 0] = 1.0
+        net = gpu_lib.build_resnet(arch, p, DEV)
+        ws = net.workspace(B)
+
+        def at_least(bits, order):
+            b = bias[:, order].clone()
+            b[stage, :, 1] = bits[order].to(torch.int32).view(torch.float32)
+            return gpu_lib.ds_forward(net, imgs[order].contiguous(), logit_bias=b.contiguous(), ws=ws)[1][stage] == 0
+
+        lo, hi = torch.zeros(B, dtype=torch.int64, device=DEV), torch.full((B,), 0x4b000000, dtype=torch.int64, device=DEV)
+        while int((hi - lo).max()) > 1:
+            mid = (lo + hi) // 2
+            up = at_least(mid, plain)
+            lo, hi = torch.where(up, mid, lo), torch.where(up, hi, mid)
+        assert int((lo > 0).sum()) > B // 2
+        changed = sum(int((~at_least(lo, order)).sum()) + int(at_least(hi, order).sum()) for order in orders)
+        assert changed == 0, channel
