@@ -176,8 +176,8 @@ def test_pool_head_shapes(gpu_lib, B, C, n_out):
         assert relerr(got[b], want) < 1e-4
 
 
-# Token networks: an image's logits are the same bits in every batch size (tiles of 32, 64 and 96 rows behind the attention,
-# short and 128-row linear layers, 12 and 13 wavefronts), and with or without the weights in operand order.
+# Token networks: an image's logits are the same bits in every batch size (tiles of 32 and 64 rows behind the attention, linear
+# layers of 4 wavefronts and 32 rows and of 8 and 64, 12 and 13 column blocks), and with or without the weights in operand order.
 @pytest.mark.parametrize("big", [False, True])
 def test_vit_logits_do_not_depend_on_the_batch(gpu_lib, big):
     kw = dict(embed=416, heads=8, head_dim=48, mlp=1664, depth=2, routes="pp", stem_dim=24, patch=8) if big else dict(depth=2)
@@ -199,8 +199,9 @@ def test_vit_logits_do_not_depend_on_the_batch(gpu_lib, big):
     assert torch.equal(plain, full)
 
 
-# Q/K/V of a part: up to a workgroup a compute unit through an LDS stage, beyond it from registers; slices that end inside a
-# 32-column block (five and seven heads of 48 channels): the same bits as the batch whole
+# The first block's Q/K/V of a part: up to a workgroup a compute unit through an LDS stage of 12 wavefronts (parts of 48 to 64 images,
+# 72 with 13 column blocks), beyond it from registers of 8 (72 and 96 images); slices that end inside a 32-column block (five and seven
+# heads of 48 channels): every row of the last block has the bits of the batch whole
 @pytest.mark.parametrize("big", [False, True])
 @pytest.mark.parametrize("B,parts", [(104, 2), (129, 2), (180, 2), (250, 4)])
 def test_vit_parts_have_the_bits_of_the_batch(gpu_lib, big, B, parts):
@@ -211,9 +212,26 @@ def test_vit_parts_have_the_bits_of_the_batch(gpu_lib, big, B, parts):
     gen.manual_seed(B)
     imgs = torch.randn((B, 3, arch["image"], arch["image"]), generator=gen, device=DEV).to(torch.bfloat16)
     over = (torch.arange(B, device=DEV, dtype=torch.int32) * 5 % arch["T"])[None].contiguous()
-    whole, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
-    shares, _ = gpu_lib.ds_forward_parts(net, imgs, parts, route_override=over)
+    N, D = arch["tokens"], arch["embed"]
+    taps = {i: torch.zeros((B, N, D), dtype=torch.bfloat16, device=DEV) for i in range(2)}
+    whole, _ = gpu_lib.ds_forward_taps(net, imgs, taps, route_override=over)
+    ws = net.workspace(B, parts).zero_()
+    shares, _ = gpu_lib.ds_forward_parts(net, imgs, parts, route_override=over, ws=ws)
     assert torch.isfinite(whole).all() and relerr(host(shares), host(whole)) < 1e-5       # (the classifier's sums, as above)
+    # what every sample's last block left is still in its part's workspace: samples by route, rows of the route's width one behind the other
+    last, ws, routes = [taps[i].view(torch.int16).cpu().numpy() for i in range(2)], ws.cpu().numpy(), over[0].cpu().numpy()
+    h = -(-(-(-B // parts)) // 8) * 8
+    for p0, space in zip(range(0, B, h), np.split(ws, -(-B // h))):
+        space, at = space.view(np.int16), None
+        for j, b in enumerate(p0 + np.argsort(routes[p0:p0 + h], kind="stable")):
+            width, depth = (int([*arch["routes"][routes[b]], 2][i]) for i in (0, 3))
+            if depth == 0:
+                continue
+            want = last[depth - 1][b, :, :width]
+            if at is None:
+                at = space.tobytes().find(want[:1].tobytes()) - j * N * D * 2
+                assert at >= 0 and at % 256 == 0, p0
+            assert np.array_equal(space[at // 2 + j * N * D:][:N * width].reshape(N, width), want), (p0, b)
 
 
 # hidden activations around the limits of the GELU's short evaluation: every bf16 result equals the exact one's

@@ -40,7 +40,7 @@ def test_vit_attention_wider_than_the_embedding(gpu_lib, B):
 
 
 # Row tiles hold the rows of several samples side by side: one sample that is not finite must not reach another.  Batches for
-# the few-image launches, 32-, 64- and 96-row tiles, 12 and 13 column blocks behind the attention
+# the few-image launches, 32- and 64-row tiles, 12 and 13 column blocks behind the attention
 @pytest.mark.parametrize("kw,B", [(PP, 3), (PP, 120), (PP, 900), (PP, 2600), (WIDE_HEADS, 4), (WIDE_HEADS, 120), (WIDE_HEADS, 2600)],
                          ids=lambda v: str(v) if isinstance(v, int) else ("stem416" if "stem_dim" in v else "heads13"))
 def test_vit_samples_stay_apart(gpu_lib, kw, B):
