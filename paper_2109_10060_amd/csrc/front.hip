@@ -15,11 +15,16 @@
 // empty; a band computes the rows above it again and sets up its own filters (5 us).
 //
 // Us, three launches before (stem_mfma_kernel, bandpw_kernel twice) -> here (what reading the images and writing the output
-// takes at the 5.1 TB/s of a large copy): DS-MBNet 256 images 66 + 134 + 148 -> 170 (55), one image 4.9 + 5.6 + 5.1 -> 8.6;
+// takes at the 5.1 TB/s of a large copy): DS-MBNet 256 images 66 + 134 + 148 -> 170 (55), one image 4.9 + 5.6 + 5.1 -> 9.6;
 // DS-MBNet++ 96 images 20 + 33 + 25 -> 46 (14).  Bound by the instructions of a turn: one workgroup in a compute unit takes 1.15
 // us a turn, three take 1.8, about 0.6 each.  162 registers hold it at three workgroups; held to 128 for four of them it
 // spills: 261 us.  With each ring row's place a constant (six turns laid out one behind the other) a turn has a third fewer
 // instructions and took no less time (189 us, 34 KB of code).
+//
+// Operands, fp32 sums and roundings are the three launches'; the stem, both pointwise layers and the second depthwise layer give the same bits.
+// In the first depthwise layer the strips of four outputs start P columns left of an even column, so the taps of a filter row fall into
+// other steps of v_mfma_f32_4x4x4 and a sum can end a last bit away: alone it changes 4 of 25.7e6 values behind it (3x3 filters, 64
+// images) and 9 of 9.6e6 (5x5).
 #include <algorithm>
 #include <type_traits>
 
