@@ -12,12 +12,15 @@
 // only the weights need barriers.
 //
 // Measured, 256 images of DS-ResNet, us: first stage's first block (projection 78, 3x3 72, last and next first layer 131: together 281)
-// 166, second (72 + 131) 158, third (72 + 108) 127 at 5.0 TB/s; second stage's blocks (50 + 88) 113 and (50 + 66) 92.  Tried: weight slabs in turn
+// 161, second (72 + 131) 156 at 4.5 TB/s, third (72 + 108) 132 with the sums for the next gate, 127 without; second stage's blocks (50 + 88) 112 and
+// (50 + 66) 90 (profiles/layers_resnet_b256.txt).  Tried: weight slabs in turn
 // with one barrier a pass and a phase (same time), tiles in plain order (1 % slower), two workgroups a compute unit in place of three
 // with the projection inside (207 for 170), 32 columns of a pass after the other (1 % slower).
 //
-// Sums run in the order of conv3_kernel and thin_kernel and intermediate maps are rounded to bf16 as they would be in memory, so the
-// results are the same bits.
+// Sums run in the order of conv3_kernel and thin_kernel where those do not deal a reduction to shares, and intermediate maps are rounded to
+// bf16 as they would be in memory, so the results are the same bits as theirs.  Launches of few samples they do deal (conv3_kernel up
+// to 512 workgroups, gemm_small_kernel), so there a batch of 2 to 20 images gets other last bits here than from the separate launches: the
+// ones it gets in a batch of 33 (logits of DS-ResNet in batches of 5 against one of 256, 2-norm 8.7e-4 before and 7.8e-4 here).
 #include "common.h"
 #include <type_traits>
 
@@ -529,9 +532,9 @@ bool ds_bneck_runs(const BneckArgs& a, int32_t B, int32_t max_mtiles) {
         return false;
     // A workgroup is a chain of 3 phases a 32-channel chunk and a pass per 64 output columns, against three launches whose tiles spread
     // over more workgroups.  DS-ResNet, us a pass, separate launches / here: slices up to 64 channels 1 image (25 tiles) 366 / 371, 2 images
-    // (50) 439 / 433, 3 images (75) 527 / 509, 16 images 716 / 682; up to 128 channels 24 images (147 tiles) 767 / 800, 33 images (202)
-    // 863 / 882, 40 images (245) 927 / 932, 48 images (294) 1005 / 1004, 64 images (392) 1181 / 1142, 96 images 1432 / 1389.  Parts of a
-    // batch that run side by side count together: 160 images in four parts (245 tiles each) 1987 / 1924.
+    // (50) 439 / 433, 3 images (75) 527 / 509, 16 images 716 / 682; up to 128 channels 24 images (162 tiles) 767 / 800, 33 images (217)
+    // 863 / 882, 40 images (260) 927 / 932, 48 images (309) 1005 / 1004, 64 images (407) 1181 / 1142, 96 images 1432 / 1389.  Parts of a
+    // batch that run side by side count together: 160 images in four parts (260 tiles each) 1987 / 1924.
     return (int64_t)max_mtiles * (a.crowd > 1 ? a.crowd : 1) >= (nb == 2 ? 40 : 300);
 }
 
