@@ -388,7 +388,9 @@ int32_t ds_launch_thin_chain(const GemmArgs& a, const ThinChain& ch, int32_t max
         (((uintptr_t)ch.scale | (uintptr_t)ch.shift | (uintptr_t)ch.C | (uintptr_t)ch.Wt) & 15))
         return DS_EUNSUPPORTED;
     // (as above, for the pair: 64 channels 101 tiles 16.2 against 15.8 us as two launches, 203 tiles 16.9 / 19.4, 407 tiles
-    // 17.8 / 26.0; 128 channels 218 tiles 32.7 against 23.6)
+    // 17.8 / 26.0; 128 channels 218 tiles 32.7 against 23.6.  With bneck_kernel in front one launch a pass is left, behind the strided
+    // block of stage 2.  Us a pass of DS-ResNet, two launches / one: 48 images (309 tiles) 934 / 935, 56 images (358) 1004 / 1006, 64 images
+    // (407) 1101 / 1092, 96 images 1352 / 1336, 256 images 2642 / 2627, in four parts 2600 / 2574)
     if (max_mtiles < (kmax <= 64 ? 150 : 400)) return DS_EUNSUPPORTED;
     int k2max = 0;
     for (int t = 0; t < a.gt.T; ++t) {

@@ -11,9 +11,10 @@
 // gemm_kernel read them once per 64 columns).  A finished block is traded between the halves of the wavefront and stored from
 // its registers, 16 bytes a lane (DIRECT): pieces of 64 bytes where a stage in LDS would make whole lines, but without the stage
 // two workgroups share a compute unit, one normalises rows while the other multiplies, and no wavefront waits for another
-// between blocks.  Us a pass with it in every block, 12 wavefronts, 64 or 96 rows and a stage -> here: DS-ViT 64 images 1058 -> 1041, 140 images 1697
-// -> 1657, 256 images 2663 -> 2643; DS-ViT++ 64 images 1418 -> 1396, 256 images 3947 -> 3801 (eight operands in flight instead of four
-// 3760, but the others 1049, 1681, 2652 and 1399; 32 rows 256 images 2700 and 3906).
+// between blocks.  Us a pass, 12 wavefronts, 64 rows and a stage -> here: DS-ViT 64 / 140 / 256 images 980 / 1535 / 2488 -> 979 / 1534 / 2485,
+// DS-ViT++ 1283 / 2248 / 3865 -> 1282 / 2248 / 3817.  (In every block, before the block in front brought Q/K/V: DS-ViT 1058 / 1697 / 2663
+// -> 1041 / 1657 / 2643, DS-ViT++ 64 and 256 images 1418 / 3947 -> 1396 / 3801; eight operands in flight instead of four 3760, but the
+// others 1049, 1681, 2652 and 1399; 32 rows 256 images 2700 and 3906.)
 // Few images: all four layers of a block with 4 wavefronts and 32 rows, where a launch is bound by latency and by how many
 // compute units share the weights' way in; finished blocks leave through an LDS tile as 16-byte pieces of whole row runs.  The
 // LayerNorm launches disappear.  A LayerNorm there is a chain in front of the products: its weights are asked for beside the rows
@@ -271,8 +272,9 @@ int32_t launch(const VitLinearArgs& a, int64_t tiles, int max_blocks, int run_bl
 
 // Measured on DS-ViT's Q/K/V layer with its LayerNorm (us, profiles/dispatch_choices.txt): 1 / 5 / 9 / 16 images with 4 column blocks
 // a workgroup 6.6 / 8.0 / 9.6 / 15.0, 8 blocks 9.2 / 9.6 / 10.8 / 12.3.  From 160 tiles of 64 rows on the
-// large form: a pass of DS-ViT of 36 / 42 / 48 images, the line at 100 tiles 885 / 894 / 981, at 160 899 / 894 / 981, at 200 900 / 921 / 1017;
-// DS-ViT++ 36 / 46 / 60 images 1262 / 1294 / 1351, 1232 / 1305 / 1352, 1233 / 1305 / 1405.  Reductions beyond 416 channels (fc2) are for the few-image path alone: 113 KiB of rows.
+// large form, which is then the first block's alone: a pass of DS-ViT of 36 / 40 / 50 / 60 images, the line at 100 tiles 752 / 762 / 870 / 956, at 160
+// 754 / 760 / 869 / 955, at 260 754 / 765 / 875 / 963; DS-ViT++ 40 / 60 / 66 images 1113 / 1265 / 1322, 1113 / 1264 / 1322, 1114 / 1270 / 1331.
+// Reductions beyond 416 channels (fc2) are for the few-image path alone: 113 KiB of rows.
 int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s) {
     int kmax = 0, nmax = 0;
     for (int t = 0; t < a.gt.T; ++t) {
@@ -288,14 +290,14 @@ int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s) {
     if (kmax <= VIT_K_MAX) {
         if (!a.res && a.act == DS_ACT_NONE && tiles(64) >= 160) {
             // parts of a batch, each with a workgroup a compute unit at most: two small ones would share the compute units that the other
-            // part leaves free.  DS-ViT in two parts, 8 / 12 wavefronts: 96 images 1410 / 1319, 128 images 1420 / 1333; 160 images 1670 / 1663,
-            // 200 images 1891 / 1934, 256 images 2316 / 2525
+            // part leaves free.  Us a pass, 8 / 12 wavefronts: DS-ViT in two parts, 96 images 1121 / 1112, 128 images 1366 / 1356, 160 images (293
+            // tiles a part) 1633 / 1638, 200 images 1976 / 1970, 200 in four (219 tiles) 1968 / 1976; DS-ViT++ in two, 96 / 128 images 1588 / 1587, 1888 / 1883
             if (a.crowd > 1 && tiles(64) <= 256) return launch<12, 2, 4, VIT_K_MAX, false>(a, tiles(64), blocks, blocks, s);
             return launch<8, 2, 4, VIT_K_MAX, false, true>(a, tiles(64), blocks, blocks, s);
         }
         // (the early requests cost 50 registers, a third of the workgroups a compute unit holds: not where there are enough of them,
-        // nor beside the launches of a batch's other parts -- 1 / 5 / 16 images 494 / 562 / 673 us a pass, 506 / 569 / 690 without them; 64
-        // images in four parts 1181 with them, 1101 without; 24 images, beyond the line, 805 either way)
+        // nor beside the launches of a batch's other parts -- 1 / 5 images 494 / 562 us a pass, 506 / 569 without them; 12 / 16 images 675 / 652
+        // and 675 / 653; DS-ViT++ 9 / 12 / 18 images, where every block has one, 955 / 1001 / 1023 and 971 / 1008 / 1037)
         const int run = tiles(32) > 64 ? 8 : 4;
         // up to a workgroup a compute unit eight wavefronts: half as many rows each to fetch and normalise, four of them multiply
         // (1 / 3 / 5 images 494 / 535 / 562 -> 474 / 515 / 558 us a pass; with two workgroups for some compute units 5 / 8 images 617 / 592)
