@@ -45,14 +45,14 @@ template <int WROWS, int WCOLS, int WMT, int WNT, int BK, int KS>
 struct Tile {
     static constexpr int BN = WCOLS * WNT * 32, LDS_LD = BK;
     static constexpr int COLS = WNT * 32;                      // columns staged per wavefront
-    static constexpr int SROWS = 16;                           // rows staged per pass
-    static constexpr int ST_LD = COLS + 4;
+    static constexpr int ST_LD = COLS + 8;                     // of the bf16 stage: an odd number of 16-byte chunks
+    static constexpr int PT_LD = BN + 4;                       // of a share's partial tile (fp32)
     static constexpr int LOOP_BYTES = (BM + BN) * LDS_LD * 2;
-    static constexpr int STAGE_BYTES = 4 * SROWS * ST_LD * 4;
-    static constexpr int PART_BYTES = KS > 1 ? BM * (BN + 4) * 4 : 0;   // a share's partial tile
+    static constexpr int STAGE_BYTES = KS > 1 ? 0 : 4 * 32 * ST_LD * 2;
+    static constexpr int PART_BYTES = KS > 1 ? BM * PT_LD * 4 : 0;
     static constexpr int MAIN0 = LOOP_BYTES > STAGE_BYTES ? LOOP_BYTES : STAGE_BYTES;
     static constexpr int MAIN_BYTES = MAIN0 > PART_BYTES ? MAIN0 : PART_BYTES;    // of a share
-    static constexpr int TABLE_BYTES = BM * (4 + 8 + 8 + 8) + 2 * BN * 4;   // row tables + scale / shift of the tile's columns
+    static constexpr int TABLE_BYTES = BM * (8 + 8) + 2 * BN * 4;   // output and residual rows, scale / shift of the tile's columns
     static constexpr int SMEM = KS * MAIN_BYTES + TABLE_BYTES;
     static_assert(KS == 1 || (WCOLS == 1 && WMT == 1 && SMEM <= 160 * 1024), "");
     static_assert(WROWS * WCOLS == 4 && WROWS * WMT * 32 == BM, "4 wavefronts cover a 128-row tile");
@@ -72,6 +72,42 @@ __device__ __forceinline__ unsigned layer_of(const GemmArgs&) { return 0; }
 __device__ __forceinline__ unsigned layer_of(const GemmPair& p) { return blockIdx.x >= p.split; }
 __device__ __forceinline__ const GemmArgs& args_of(const GemmArgs& a, unsigned) { return a; }
 __device__ __forceinline__ const GemmArgs& args_of(const GemmPair& p, unsigned q) { return p.p[q]; }
+
+// LDS written and read by one wavefront: its accesses complete in order, only the compiler has to be kept in line
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+__device__ __forceinline__ void add_residual(float (&v)[4], const uint2 r) {
+    v[0] += __uint_as_float(r.x << 16);
+    v[1] += __uint_as_float(r.x & 0xffff0000u);
+    v[2] += __uint_as_float(r.y << 16);
+    v[3] += __uint_as_float(r.y & 0xffff0000u);
+}
+template <int ACT>
+__device__ __forceinline__ void activate(float (&v)[4]) {
+    if constexpr (ACT == DS_ACT_RELU) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
+    } else if constexpr (ACT == DS_ACT_GELU) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = gelu_erf(v[e]);
+    }
+}
+template <int ACT>
+__device__ __forceinline__ uint2 activate_bf16(float (&v)[4]) {
+    if constexpr (ACT == DS_ACT_GELU) return gelu_bf16x4(v[0], v[1], v[2], v[3]);
+    activate<ACT>(v);
+    return make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
+}
+// f with the activation as a constant
+template <class F>
+__device__ __forceinline__ void with_act(int act, F&& f) {
+    if (act == DS_ACT_RELU) f(std::integral_constant<int, DS_ACT_RELU>());
+    else if (act == DS_ACT_GELU) f(std::integral_constant<int, DS_ACT_GELU>());
+    else f(std::integral_constant<int, DS_ACT_NONE>());
+}
 
 // KS: shares of the reduction, four wavefronts each; a share takes every KS-th slab
 template <int WROWS, int WCOLS, int WMT, int WNT, int BK, int KS, bool CONV, bool HASR, class Args = GemmArgs>
@@ -94,93 +130,113 @@ __global__ __launch_bounds__(NT * KS, KS > 1 ? 1 : BK == 128 ? 3 : (WMT * WNT ==
     bf16_t* Bs = As + BM * LDS_LD;                    // [BN][BK]
     long long* rowC = (long long*)(smem + KS * TL::MAIN_BYTES);
     long long* rowR = rowC + BM;
-    int2* rowYX = (int2*)(rowR + BM);
-    uint32_t* rowA = (uint32_t*)(rowYX + BM);
-    float* scl = (float*)(rowA + BM);                 // [BN] scale, then [BN] shift of this tile's output columns
+    float* scl = (float*)(rowR + BM);                 // [BN] scale, then [BN] shift of this tile's output columns
     // operands are fetched with buffer loads: 32-bit byte offsets against a uniform base, and an
     // offset beyond the descriptor's range returns zeros, which supplies every tail (rows beyond
     // the group, channels beyond the slice, taps outside the image) without branches
     constexpr uint32_t OOB = 0x80000000u;
-    const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc((void*)a.A, 0, 0x7fffffff, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc((void*)a.Wt, 0, 0x7fffffff, 0x00020000);
 
     // ---- work item ------------------------------------------------------------------
     // m-tiles are dealt to the 8 XCDs round-robin; on one XCD consecutive blocks walk the n-tiles
     // of one m-tile, so the activation tile they share stays in that XCD's L2
+    const GroupLanes lanes(a.gt);
+    const bf16_t *A = a.A, *Wt = a.Wt, *R = a.R;
+    void* C = a.C;
+    const float *scale = a.scale, *shift = a.shift;
+    const int32_t *a_index = a.a_index, *c_index = a.c_index;
+    int64_t a_ss = a.a_sample_stride, c_ss = a.c_sample_stride, r_ss = a.r_sample_stride, c_segs = a.c_seg_stride;
+    int64_t w_ld = a.w_ld, w_tap = a.w_tap_stride, w_seg = a.w_seg_stride;
+    int a_ld = a.a_ld, c_ld = a.c_ld, r_ld = a.r_ld, c_row0 = a.c_row0, r_use = a.r_use_index;
+    int n_seg = a.n_seg, tab_ld = a.tab_ld, tab_seg = a.tab_seg_stride, rows = a.rows, act = a.act, out_f32 = a.out_f32;
+    int KH = a.K, KW = a.Kw, H = a.H, W = a.W, Wo = a.Wo, sy = a.stride, sx = a.stride_w, pad = a.pad;
     const int j = (int)(block >> 3);
     const int jm = j / ny, y = j - jm * ny;
     const int mt = jm * 8 + (int)(block & 7);
     if (mt >= max_mtiles) return;
     const int4 me = ds_tile_record(a, mt);
+    ds_hold(A, Wt, R, C, scale, shift, a_index, c_index, a_ss, c_ss, r_ss, c_segs, w_ld, w_tap, w_seg, a_ld, c_ld, r_ld, c_row0, r_use,
+            n_seg, tab_ld, tab_seg, rows, act, out_f32, KH, KW);
+    if constexpr (CONV) ds_hold(H, W, Wo, sy, sx, pad);
     if (me.x < 0) return;
     const int g = me.x, grow0 = me.y, slot0 = me.z, rows_g = me.w;
-    const int k_in = a.gt.k_in[g], k_out = a.gt.k_out[g];
+    const int k_in = lanes.k_in(g), k_out = lanes.k_out(g);
     if (k_in <= 0 || k_out <= 0) return;
-    const int ntiles = (k_out + BN - 1) / BN;
-    const int seg = y / ntiles;
-    if (seg >= a.n_seg) return;
-    const int n0 = (y - seg * ntiles) * BN;
-
-    const int tid = KS > 1 ? threadIdx.x & (NT - 1) : threadIdx.x;   // of the share
-    const int a_ld = a.a_ld > 0 ? a.a_ld : k_in;
-    const int c_ld = a.c_ld > 0 ? a.c_ld : k_out;
-    const int r_ld = a.r_ld > 0 ? a.r_ld : k_out;
-
-    // ---- per-row table: where each of the 128 rows lives --------------------------------
-    if (threadIdx.x < BM) {
-        const int m = grow0 + tid;
-        long long rc = -1, rr = 0;
-        uint32_t ra = OOB;
-        int2 yx = make_int2(0, 0);
-        if (m < rows_g) {
-            const int sl = m / a.rows;
-            const int p = m - sl * a.rows;
-            const int slot = slot0 + sl;
-            const int sa = a.a_index ? a.a_index[slot] : slot;
-            const int cs = a.c_index ? a.c_index[slot] : slot;
-            const int oy = p / a.Wo, ox = p - oy * a.Wo;
-            // byte offset of the sample (convolution) or of the row itself (linear layers)
-            ra = (uint32_t)(((long long)sa * a.a_sample_stride + (CONV ? 0 : (long long)p * a_ld)) * 2);
-            yx = make_int2(oy * a.stride - a.pad, ox * (a.stride_w > 0 ? a.stride_w : a.stride) - a.pad);
-            const long long pc = p + a.c_row0;
-            rc = (long long)cs * a.c_sample_stride + pc * c_ld + (long long)seg * a.c_seg_stride;
-            rr = (long long)(a.r_use_index ? cs : 0) * a.r_sample_stride + pc * r_ld;
-        }
-        rowA[tid] = ra;
-        rowC[tid] = rc;
-        rowR[tid] = rr;
-        rowYX[tid] = yx;
+    int seg = 0, n0 = y * BN;
+    if (n_seg > 1) {
+        const int ntiles = (k_out + BN - 1) / BN;
+        seg = y / ntiles;
+        if (seg >= n_seg) return;
+        n0 -= seg * ntiles * BN;
     }
-    __syncthreads();
+    if (n0 >= k_out) return;
 
-    // ---- load assignment: a thread owns chunk (tid % CPR) of rows (tid / CPR) + RPT i ----
-    constexpr int NA = BM / RPT, NB = BN / RPT;
+    const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, 0x7fffffff, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc((void*)Wt, 0, 0x7fffffff, 0x00020000);
+    const int tid = KS > 1 ? threadIdx.x & (NT - 1) : threadIdx.x;   // of the share
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int wm = wave / WCOLS, wn = wave - wm * WCOLS;
+    const int l32 = lane & 31, lhi = lane >> 5;
+    if (a_ld <= 0) a_ld = k_in;
+    if (c_ld <= 0) c_ld = k_out;
+    if (r_ld <= 0) r_ld = k_out;
+    if (KW <= 0) KW = KH;
+    if (sx <= 0) sx = sy;
+
+    // ---- rows: a lane works out row l32 of the 32 its wavefront loads; the lanes that load a row get its address from that lane ------
+    uint32_t my_a = OOB;
+    int2 my_yx = make_int2(0, 0);
+    {
+        const int m = grow0 + 32 * wave + l32;
+        long long rc = -1, rr = 0;
+        if (m < rows_g) {
+            const int sl = m / rows;
+            const int p = m - sl * rows;
+            const int slot = slot0 + sl;
+            const int sa = a_index ? a_index[slot] : slot;
+            const int cs = c_index ? c_index[slot] : slot;
+            // byte offset of the sample (convolution) or of the row itself (linear layers)
+            my_a = (uint32_t)(((long long)sa * a_ss + (CONV ? 0 : (long long)p * a_ld)) * 2);
+            if constexpr (CONV) {
+                const int oy = p / Wo, ox = p - oy * Wo;
+                my_yx = make_int2(oy * sy - pad, ox * sx - pad);
+            }
+            const long long pc = p + c_row0;
+            rc = (long long)cs * c_ss + pc * c_ld + (long long)seg * c_segs;
+            rr = (long long)(r_use ? cs : 0) * r_ss + pc * r_ld;
+        }
+        if (lane < 32 && (KS == 1 || share == 0)) {           // read behind the loop's barriers
+            rowC[32 * wave + l32] = rc;
+            if constexpr (HASR) rowR[32 * wave + l32] = rr;
+        }
+    }
+
+    // ---- load assignment: a lane owns chunk (lane % CPR) of rows (lane / CPR) + RPW i of its wavefront's 32, and of rows (tid / CPR) + RPT i of the weights
+    constexpr int NA = BM / RPT, NB = BN / RPT, RPW = 64 / CPR;
     const int lchunk = tid % CPR;
     const int kc8 = lchunk * 8;
-    const int lrow = tid / CPR;
+    const int lrow = tid / CPR, arow = lane / CPR;
     uint32_t aoff[NA], apix[NA], woff[NB];
-    int2 ayx[NA];
+    int2 ayx[CONV ? NA : 1];
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
-        aoff[i] = rowA[lrow + RPT * i];
-        ayx[i] = rowYX[lrow + RPT * i];
+        aoff[i] = (uint32_t)__shfl((int)my_a, arow + RPW * i, 64);
+        if constexpr (CONV) ayx[i] = make_int2(__shfl(my_yx.x, arow + RPW * i, 64), __shfl(my_yx.y, arow + RPW * i, 64));
         apix[i] = aoff[i] == OOB ? OOB : aoff[i] + kc8 * 2;
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         const int n = n0 + lrow + RPT * i;
-        woff[i] = n < k_out ? (uint32_t)(((long long)seg * a.w_seg_stride + (long long)n * a.w_ld + kc8) * 2) : OOB;
+        woff[i] = n < k_out ? (uint32_t)(((long long)seg * w_seg + (long long)n * w_ld + kc8) * 2) : OOB;
     }
     // per filter tap: byte offset of the input pixel each owned row reads (OOB outside the image)
     auto set_tap = [&](int tap) {
         if constexpr (CONV) {
-            const int kw = a.Kw > 0 ? a.Kw : a.K;
-            const int u = tap / kw, v = tap - u * kw;
+            const int u = tap / KW, v = tap - u * KW;
 #pragma unroll
             for (int i = 0; i < NA; ++i) {
                 const int iy = ayx[i].x + u, ix = ayx[i].y + v;
-                const bool ok = aoff[i] != OOB && iy >= 0 && iy < a.H && ix >= 0 && ix < a.W;
-                apix[i] = ok ? aoff[i] + (uint32_t)(((iy * a.W + ix) * a_ld + kc8) * 2) : OOB;
+                const bool ok = aoff[i] != OOB && iy >= 0 && iy < H && ix >= 0 && ix < W;
+                apix[i] = ok ? aoff[i] + (uint32_t)(((iy * W + ix) * a_ld + kc8) * 2) : OOB;
             }
         }
     };
@@ -189,7 +245,7 @@ __global__ __launch_bounds__(NT * KS, KS > 1 ? 1 : BK == 128 ? 3 : (WMT * WNT ==
     auto load_global = [&](int tap, int kc, bool on) {
         const bool kok = on && (kc + kc8) < k_in;
         const int soff_a = kc * 2;
-        const int soff_w = (int)((tap * a.w_tap_stride + kc) * 2);
+        const int soff_w = (int)((tap * w_tap + kc) * 2);
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
             const auto t = __builtin_amdgcn_raw_buffer_load_b128(rsrc_a, (int)(kok ? apix[i] : OOB), soff_a, 0);
@@ -204,7 +260,7 @@ __global__ __launch_bounds__(NT * KS, KS > 1 ? 1 : BK == 128 ? 3 : (WMT * WNT ==
     auto store_lds = [&]() {
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
-            const int r = lrow + RPT * i;
+            const int r = 32 * wave + arow + RPW * i;
             *(uint4*)(As + r * LDS_LD + ((lchunk ^ swz<BK>(r)) * 8)) = ra[i];
         }
 #pragma unroll
@@ -213,10 +269,6 @@ __global__ __launch_bounds__(NT * KS, KS > 1 ? 1 : BK == 128 ? 3 : (WMT * WNT ==
             *(uint4*)(Bs + r * LDS_LD + ((lchunk ^ swz<BK>(r)) * 8)) = rb[i];
         }
     };
-
-    const int wave = tid >> 6, lane = tid & 63;
-    const int wm = wave / WCOLS, wn = wave - wm * WCOLS;
-    const int l32 = lane & 31, lhi = lane >> 5;
 
     f32x16_t acc[WMT][WNT];
 #pragma unroll
@@ -234,7 +286,7 @@ __global__ __launch_bounds__(NT * KS, KS > 1 ? 1 : BK == 128 ? 3 : (WMT * WNT ==
     constexpr int TK = BK == 64 ? 4 : 0;   // 256-byte rows: the key is the row's low four bits, the same 32 rows on
 
     const int kchunks = (k_in + BK - 1) / BK;
-    const int nk = a.K * (a.Kw > 0 ? a.Kw : a.K) * kchunks;
+    const int nk = KH * KW * kchunks;
     int tap = 0, kc = share * BK;
     if constexpr (KS > 1)
         while (kc >= kchunks * BK) {
@@ -247,65 +299,48 @@ __global__ __launch_bounds__(NT * KS, KS > 1 ? 1 : BK == 128 ? 3 : (WMT * WNT ==
     // The first operand slab is requested before anything else: loads return in order, so whatever is issued
     // ahead of it would have to arrive before the slab can go to LDS.
     // epilogue constants, loaded now so their latency hides behind the main loop
-    constexpr int COLS = TL::COLS, SROWS = TL::SROWS, ST_LD = TL::ST_LD;
-    constexpr int CG = COLS / 4, RPP = 64 / CG, PASSES = 32 / SROWS, VPP = 16 / PASSES;
-    const int cg = lane % CG, rr0 = lane / CG;
-    const int ncol = n0 + wn * COLS + cg * 4;
-    const bool nok = ncol < k_out;
+    constexpr int COLS = TL::COLS, ST_LD = TL::ST_LD;
     // scale and shift of the tile's columns wait in LDS, not in registers, until the epilogue (registers set the residency)
     if (threadIdx.x < BN) {
         const int n = n0 + tid;
         float vs = 1.f, vh = 0.f;
         if (n < k_out) {
-            const long long ti = (long long)a.gt.row[g] * a.tab_ld + (long long)seg * a.tab_seg_stride + n;
-            if (a.scale) vs = a.scale[ti];
-            if (a.shift) vh = a.shift[ti];
+            const long long ti = (long long)lanes.row(g) * tab_ld + (long long)seg * tab_seg + n;
+            if (scale) vs = scale[ti];
+            if (shift) vh = shift[ti];
         }
         scl[tid] = vs;
         scl[BN + tid] = vh;
     }
 
-    // the residual rows this lane will add are fetched ahead of the main loop, so that their latency hides behind it
+    // The residual pieces this lane will add are fetched ahead of the main loop, so that their latency hides behind it
     // instead of sitting between the last matrix instruction and the stores -- except with the 64-deep slabs, where
-    // their 16 registers would cost a resident workgroup: there they are requested right after the loop
-    // (with several shares a thread finishes every 16 KS-th row of the tile, few enough to ask for them early)
+    // their 16 registers would cost a resident workgroup: there they are requested right after the loop.
+    // One share: 8 channels of rows (lane / 8) + 8 i of the wavefront's 32; several: 4 channels of every 16 KS-th row of the tile, few
+    // enough to ask for them early.
     constexpr bool RES_EARLY = BK == 32 || KS > 1;
-    constexpr int NE = KS == 1 ? WMT * PASSES * (SROWS / RPP) : BM / (16 * KS);
-    auto my_row = [&](int i) {
-        if constexpr (KS == 1) return wm * WMT * 32 + (i / (SROWS / RPP)) * SROWS + rr0 + (i % (SROWS / RPP)) * RPP;
-        else return ((int)threadIdx.x >> 4) + i * 16 * KS;
-    };
-    uint2 rres[HASR ? NE : 1];
-    auto fetch_residual = [&]() {
+    constexpr int NE = KS == 1 ? 4 : BM / (16 * KS);
+    const int srow = lane >> 3, ncol8 = n0 + wn * COLS + (lane & 7) * 8;
+    const int ncol4 = n0 + (threadIdx.x & 15) * 4;           // (several shares: one column tile)
+    static_assert(COLS == 64, "eight 16-byte pieces a row of the stage");
+    using Piece = typename std::conditional<KS == 1, uint4, uint2>::type;
+    Piece rres[HASR ? NE : 1];
+    auto fetch_residual = [&](int tm) {
 #pragma unroll
         for (int i = 0; i < NE; ++i) {
-            const int r = my_row(i);
-            uint2 t = make_uint2(0, 0);
-            if (nok && rowC[r] >= 0) t = *(const uint2*)(a.R + rowR[r] + ncol);
+            const int r = KS == 1 ? wm * WMT * 32 + tm * 32 + srow + 8 * i : ((int)threadIdx.x >> 4) + i * 16 * KS;
+            const int n = KS == 1 ? ncol8 : ncol4;
+            Piece t = {};
+            if (n < k_out && rowC[r] >= 0) t = *(const Piece*)(R + rowR[r] + n);
             rres[i] = t;
         }
     };
-    if constexpr (HASR && RES_EARLY) fetch_residual();
-    // four channels of a row: scale and shift, residual, activation, store
-    auto finish = [&](const float4 t, long long coff, const uint2 q) {
-        const float4 s4 = *(const float4*)(scl + wn * COLS + cg * 4), h4 = *(const float4*)(scl + BN + wn * COLS + cg * 4);
-        float val[4] = {t.x * s4.x + h4.x, t.y * s4.y + h4.y, t.z * s4.z + h4.z, t.w * s4.w + h4.w};
-        if constexpr (HASR) {
-            val[0] += __uint_as_float(q.x << 16);
-            val[1] += __uint_as_float(q.x & 0xffff0000u);
-            val[2] += __uint_as_float(q.y << 16);
-            val[3] += __uint_as_float(q.y & 0xffff0000u);
-        }
-        if (a.act == DS_ACT_RELU) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) val[e] = fmaxf(val[e], 0.f);
-        } else if (a.act == DS_ACT_GELU) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) val[e] = gelu_erf(val[e]);
-        }
-        if (a.out_f32) *(float4*)((float*)a.C + coff + ncol) = make_float4(val[0], val[1], val[2], val[3]);
-        else *(uint2*)((bf16_t*)a.C + coff + ncol) = make_uint2(f2bf2(val[0], val[1]), f2bf2(val[2], val[3]));
-    };
+    // (asked for ahead of the loop's first barrier: the rows of the table are the wavefront's own, or all wavefronts')
+    if constexpr (HASR && RES_EARLY) {
+        if constexpr (KS > 1 || WCOLS > 1) __syncthreads();
+        else wave_sync();
+        fetch_residual(0);
+    }
 
     store_lds();
     __syncthreads();
@@ -342,7 +377,7 @@ __global__ __launch_bounds__(NT * KS, KS > 1 ? 1 : BK == 128 ? 3 : (WMT * WNT ==
             for (int i = 0; i < WMT; ++i)
 #pragma unroll
                 for (int jj = 0; jj < WNT; ++jj)
-                    acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[jj], acc[i][jj], 0, 0, 0);
+                    acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[jj], af[i], acc[i][jj], 0, 0, 0);
         }
         __syncthreads();
         if (more) {
@@ -351,66 +386,91 @@ __global__ __launch_bounds__(NT * KS, KS > 1 ? 1 : BK == 128 ? 3 : (WMT * WNT ==
         }
     }
 
-    if constexpr (HASR && !RES_EARLY) fetch_residual();
-
+    // Filters are the instruction's row operand, so a lane holds 4 channels of one row at a time: channels 32 tn + 8 q + 4 lhi of row l32.
     if constexpr (KS > 1) {
         // ---- partial tiles to LDS, added in share order (the loop's last barrier has retired every read of the slabs there)
         float* part = (float*)As;
 #pragma unroll
         for (int tn = 0; tn < WNT; ++tn)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) part[(wm * 32 + 8 * (v >> 2) + 4 * lhi + (v & 3)) * ST_LD + tn * 32 + l32] = acc[0][tn][v];
+            for (int q = 0; q < 4; ++q)
+                *(float4*)(part + (wm * 32 + l32) * TL::PT_LD + tn * 32 + 8 * q + 4 * lhi) =
+                    make_float4(acc[0][tn][4 * q], acc[0][tn][4 * q + 1], acc[0][tn][4 * q + 2], acc[0][tn][4 * q + 3]);
         __syncthreads();
+        const int cg = threadIdx.x & 15;
+        const float4 s4 = *(const float4*)(scl + cg * 4), h4 = *(const float4*)(scl + BN + cg * 4);
+        with_act(act, [&](auto actc) {
+            constexpr int ACT = decltype(actc)::value;
 #pragma unroll
-        for (int i = 0; i < NE; ++i) {
-            const int r = my_row(i);
-            const long long coff = rowC[r];
-            if (!nok || coff < 0) continue;
-            float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int i = 0; i < NE; ++i) {
+                const int r = ((int)threadIdx.x >> 4) + i * 16 * KS;
+                const long long coff = rowC[r];
+                if (ncol4 >= k_out || coff < 0) continue;
+                float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-            for (int k = 0; k < KS; ++k) {
-                const float4 q = *(const float4*)((const float*)(smem + k * TL::MAIN_BYTES) + r * ST_LD + cg * 4);
-                t.x += q.x; t.y += q.y; t.z += q.z; t.w += q.w;
+                for (int k = 0; k < KS; ++k) {
+                    const float4 p = *(const float4*)((const float*)(smem + k * TL::MAIN_BYTES) + r * TL::PT_LD + cg * 4);
+                    t.x += p.x; t.y += p.y; t.z += p.z; t.w += p.w;
+                }
+                float val[4] = {t.x * s4.x + h4.x, t.y * s4.y + h4.y, t.z * s4.z + h4.z, t.w * s4.w + h4.w};
+                if constexpr (HASR) add_residual(val, make_uint2(rres[i].x, rres[i].y));
+                if (out_f32) {
+                    activate<ACT>(val);
+                    *(float4*)((float*)C + coff + ncol4) = make_float4(val[0], val[1], val[2], val[3]);
+                } else {
+                    *(uint2*)((bf16_t*)C + coff + ncol4) = activate_bf16<ACT>(val);
+                }
             }
-            finish(t, coff, rres[HASR ? i : 0]);
-        }
+        });
         return;
     }
-    // ---- epilogue through LDS: each lane finishes 4 consecutive channels of one row -----
-    // The staging rows belong to one wavefront (written and read back by its own lanes, and the main loop's last
-    // barrier has already retired every read of the operand tiles they alias), and a wavefront's LDS accesses
-    // complete in order, so the passes only need the compiler kept from moving LDS accesses across them.
-    auto wave_sync = [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
-    float* st = (float*)smem + wave * SROWS * ST_LD;
+    // ---- epilogue: a wavefront's 32 x 64 tile through LDS as bf16.  A residual is parked there and every lane adds to its own runs of
+    // 4 channels in place; the tile leaves as 16-byte pieces, eight lanes a row.
+    // The stage belongs to one wavefront (written and read back by its own lanes, and the main loop's last
+    // barrier has already retired every read of the operand tiles it aliases), and a wavefront's LDS accesses
+    // complete in order, so only the compiler has to be kept from moving them.
+    bf16_t* st = (bf16_t*)smem + wave * 32 * ST_LD;
 #pragma unroll
     for (int tm = 0; tm < WMT; ++tm) {
+        const int row0 = wm * WMT * 32 + tm * 32;
+        if constexpr (HASR) {
+            if (!RES_EARLY || tm > 0) fetch_residual(tm);
 #pragma unroll
-        for (int ps = 0; ps < PASSES; ++ps) {
+            for (int i = 0; i < 4; ++i) *(Piece*)(st + (srow + 8 * i) * ST_LD + (lane & 7) * 8) = rres[i];
+            wave_sync();
+        }
+        with_act(act, [&](auto actc) {
+            constexpr int ACT = decltype(actc)::value;
 #pragma unroll
             for (int tn = 0; tn < WNT; ++tn)
 #pragma unroll
-                for (int vv = 0; vv < VPP; ++vv) {
-                    const int v = ps * VPP + vv;
-                    const int lr = 8 * ((v >> 2) - ps * (4 / PASSES)) + 4 * lhi + (v & 3);
-                    st[lr * ST_LD + tn * 32 + l32] = acc[tm][tn][v];
+                for (int q = 0; q < 4; ++q) {
+                    const int ch = tn * 32 + 8 * q + 4 * lhi;
+                    const float4 s4 = *(const float4*)(scl + wn * COLS + ch), h4 = *(const float4*)(scl + BN + wn * COLS + ch);
+                    const f32x16_t& t = acc[tm][tn];
+                    float val[4] = {t[4 * q] * s4.x + h4.x, t[4 * q + 1] * s4.y + h4.y, t[4 * q + 2] * s4.z + h4.z, t[4 * q + 3] * s4.w + h4.w};
+                    uint2* p = (uint2*)(st + l32 * ST_LD + ch);
+                    if constexpr (HASR) add_residual(val, *p);
+                    if (out_f32) {
+                        const long long coff = rowC[row0 + l32];
+                        const int n = n0 + wn * COLS + ch;
+                        activate<ACT>(val);
+                        if (coff >= 0 && n < k_out) *(float4*)((float*)C + coff + n) = make_float4(val[0], val[1], val[2], val[3]);
+                    } else {
+                        *p = activate_bf16<ACT>(val);
+                    }
                 }
-            wave_sync();
-            if (nok) {
+        });
+        if (out_f32) continue;
+        wave_sync();
+        if (ncol8 < k_out) {
 #pragma unroll
-                for (int rr = rr0; rr < SROWS; rr += RPP) {
-                    const int r = wm * WMT * 32 + tm * 32 + ps * SROWS + rr;
-                    const long long coff = rowC[r];
-                    if (coff < 0) continue;
-                    finish(*(const float4*)(st + rr * ST_LD + cg * 4), coff,
-                           rres[HASR ? (tm * PASSES + ps) * (SROWS / RPP) + (rr - rr0) / RPP : 0]);
-                }
+            for (int i = 0; i < 4; ++i) {
+                const long long coff = rowC[row0 + srow + 8 * i];
+                if (coff >= 0) *(uint4*)((bf16_t*)C + coff + ncol8) = *(const uint4*)(st + (srow + 8 * i) * ST_LD + (lane & 7) * 8);
             }
-            wave_sync();
         }
+        wave_sync();
     }
 }
 
