@@ -103,18 +103,24 @@ struct GemmArgs {
 };
 
 #ifdef __HIPCC__
+// inclusive sum over the lanes of a wavefront, without LDS round trips: rows of 16 lanes, then the last lane of each to the rows behind it
+__device__ __forceinline__ int ds_scan64(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return v;
+}
 // Record of the bm-row tile mt, found in the group offsets by the 64 lanes of the calling wavefront side by side; groups
 // from the last to the first, as the tile lists have them.  .x < 0: there is no such tile.
 __device__ __forceinline__ int4 ds_tile_record_of(const int32_t* offsets, int T, int rows, int mt, int bm) {
-    const int lane = (int)(threadIdx.x & 63), g = T - 1 - lane;
-    const int o0 = g >= 0 ? offsets[g] : 0, o1 = g >= 0 ? offsets[g + 1] : 0;
+    const int lane = (int)(threadIdx.x & 63), g = T - 1 - lane, at = g >= 0 ? g : 0;
+    int o0 = offsets[at], o1 = offsets[at + 1];
+    if (g < 0) o0 = o1 = 0;
     const int rg = (o1 - o0) * rows, n = (rg + bm - 1) / bm;
-    int upto = n;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int t = __shfl_up(upto, d, 64);
-        if (lane >= d) upto += t;
-    }
+    const int upto = ds_scan64(n);
     const unsigned long long past = __ballot(upto > mt);
     if (past == 0) return make_int4(-1, 0, 0, 0);
     const int q = __builtin_ctzll(past);
@@ -126,6 +132,13 @@ __device__ __forceinline__ int4 ds_tile_record_of(const int32_t* offsets, int T,
 // scalar loads of cold cache lines; held together they are one round trip.
 template <typename T>
 __device__ __forceinline__ void ds_hold1(T& v) { asm volatile("" : "+s"(v)); }
+// (a pointer stays known as one to global memory: behind the asm it would be a generic one and its accesses flat)
+template <typename T>
+__device__ __forceinline__ void ds_hold1(T*& p) {
+    uint64_t v = (uint64_t)p;
+    asm volatile("" : "+s"(v));
+    p = (T*)(__attribute__((address_space(1))) T*)v;
+}
 template <typename... T>
 __device__ __forceinline__ void ds_hold(T&... v) { (ds_hold1(v), ...); }
 // The group table by lanes: lane g holds group g's entries, requested together and ahead of the tile record, so that the
@@ -143,19 +156,28 @@ struct GroupLanes {
     __device__ __forceinline__ int k_out(int g) const { return __builtin_amdgcn_readlane(ko, __builtin_amdgcn_readfirstlane(g)); }
     __device__ __forceinline__ int row(int g) const { return __builtin_amdgcn_readlane(ro, __builtin_amdgcn_readfirstlane(g)); }
 };
-// Record of 128-row tile mt: read from the list, or worked out where there is none (no offsets either: one group of B
-// samples in slot order)
-__device__ __forceinline__ int4 ds_tile_record(const GemmArgs& a, int mt) {
-    if (a.mtiles) {
-        const int4 me = a.mtiles[mt];            // in bounds even beyond the live count; checked next
-        const int n = *a.n_mtiles;
-        int x = __builtin_amdgcn_readfirstlane(me.x);
-        ds_hold(x);                              // asked for beside the count, not behind it
-        return mt < n ? make_int4(x, me.y, me.z, me.w) : make_int4(-1, 0, 0, 0);
+// Where the records of 128-row tiles come from, read with the other arguments (ds_hold).
+struct TileSource {
+    const int4* mtiles;
+    const int32_t *n_mtiles, *offsets;
+    int T, B, rows;
+    __device__ __forceinline__ explicit TileSource(const GemmArgs& a)
+        : mtiles(a.mtiles), n_mtiles(a.n_mtiles), offsets(a.offsets), T(a.gt.T), B(a.B), rows(a.rows) {}
+    __device__ __forceinline__ void hold() { ds_hold(mtiles, n_mtiles, offsets, T, B, rows); }
+    // record of tile mt: read from the list, or worked out where there is none (no offsets either: one group of B samples in slot order)
+    __device__ __forceinline__ int4 record(int mt) const {
+        if (mtiles) {
+            const int4 me = mtiles[mt];          // in bounds even beyond the live count; checked next
+            const int n = *n_mtiles;
+            int x = __builtin_amdgcn_readfirstlane(me.x);
+            ds_hold(x);                          // asked for beside the count, not behind it
+            return mt < n ? make_int4(x, me.y, me.z, me.w) : make_int4(-1, 0, 0, 0);
+        }
+        if (!offsets) return mt * DS_GEMM_BM < B * rows ? make_int4(0, mt * DS_GEMM_BM, 0, B * rows) : make_int4(-1, 0, 0, 0);
+        return ds_tile_record_of(offsets, T, rows, mt, DS_GEMM_BM);
     }
-    if (!a.offsets) return mt * DS_GEMM_BM < a.B * a.rows ? make_int4(0, mt * DS_GEMM_BM, 0, a.B * a.rows) : make_int4(-1, 0, 0, 0);
-    return ds_tile_record_of(a.offsets, a.gt.T, a.rows, mt, DS_GEMM_BM);
-}
+};
+__device__ __forceinline__ int4 ds_tile_record(const GemmArgs& a, int mt) { return TileSource(a).record(mt); }
 #endif
 
 size_t ds_mtile_capacity(int32_t B, int32_t rows, int32_t T);

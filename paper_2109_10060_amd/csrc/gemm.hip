@@ -149,14 +149,16 @@ __global__ __launch_bounds__(NT * KS, KS > 1 ? 1 : BK == 128 ? 3 : (WMT * WNT ==
     int a_ld = a.a_ld, c_ld = a.c_ld, r_ld = a.r_ld, c_row0 = a.c_row0, r_use = a.r_use_index;
     int n_seg = a.n_seg, tab_ld = a.tab_ld, tab_seg = a.tab_seg_stride, rows = a.rows, act = a.act, out_f32 = a.out_f32;
     int KH = a.K, KW = a.Kw, H = a.H, W = a.W, Wo = a.Wo, sy = a.stride, sx = a.stride_w, pad = a.pad;
+    TileSource source(a);
+    source.hold();
+    ds_hold(ny, max_mtiles, A, Wt, R, C, scale, shift, a_index, c_index, a_ss, c_ss, r_ss, c_segs, w_ld, w_tap, w_seg, a_ld, c_ld, r_ld, c_row0, r_use,
+            n_seg, tab_ld, tab_seg, rows, act, out_f32, KH, KW);
+    if constexpr (CONV) ds_hold(H, W, Wo, sy, sx, pad);
     const int j = (int)(block >> 3);
     const int jm = j / ny, y = j - jm * ny;
     const int mt = jm * 8 + (int)(block & 7);
     if (mt >= max_mtiles) return;
-    const int4 me = ds_tile_record(a, mt);
-    ds_hold(A, Wt, R, C, scale, shift, a_index, c_index, a_ss, c_ss, r_ss, c_segs, w_ld, w_tap, w_seg, a_ld, c_ld, r_ld, c_row0, r_use,
-            n_seg, tab_ld, tab_seg, rows, act, out_f32, KH, KW);
-    if constexpr (CONV) ds_hold(H, W, Wo, sy, sx, pad);
+    const int4 me = source.record(mt);
     if (me.x < 0) return;
     const int g = me.x, grow0 = me.y, slot0 = me.z, rows_g = me.w;
     const int k_in = lanes.k_in(g), k_out = lanes.k_out(g);
