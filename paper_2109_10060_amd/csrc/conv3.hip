@@ -13,7 +13,7 @@
 // activation traffic from L2 drops from 9 x 128 rows per chunk to 128 + 2 (W+1).
 // Launches of fewer workgroups than run at once deal the chunks of a tile to two or four shares of four wavefronts, each with slabs of
 // its own in LDS; the partial tiles are added there in share order.
-#include "gelu.h"
+#include "tile_out.h"
 
 namespace {
 
@@ -23,12 +23,13 @@ constexpr int ZROW = RMAX;                     // one more row, all zeros
 constexpr int TPP = 3;                         // taps staged per phase: 3 (one filter row) or 9 (the whole filter)
 constexpr int PPC = 9 / TPP;                   // phases per channel chunk
 constexpr int A_BYTES = (RMAX + 1) * 64, B_BYTES = TPP * BN * 64;
-constexpr int SROWS = 16, ST_LD = BN + 4, STAGE_BYTES = 4 * SROWS * ST_LD * 4;
-constexpr int TABLE_BYTES = BM * 16;
+constexpr int ST_LD = BN + 8, STAGE_BYTES = 4 * 32 * ST_LD * 2;   // bf16 stage: an odd number of 16-byte chunks a row
+constexpr int PT_LD = BN + 4;                  // of a share's partial tile (fp32)
+constexpr int TABLE_BYTES = BM * 16 + 2 * BN * 4;   // output and residual rows, scale and shift
 // LDS of a share: its slabs, and with several shares its partial tile
 constexpr int main_bytes(int ks) {
     const int m = A_BYTES + B_BYTES > STAGE_BYTES ? A_BYTES + B_BYTES : STAGE_BYTES;
-    return ks > 1 && BM * ST_LD * 4 > m ? BM * ST_LD * 4 : m;
+    return ks > 1 && BM * PT_LD * 4 > m ? BM * PT_LD * 4 : m;
 }
 constexpr int smem_bytes(int ks) { return ks * main_bytes(ks) + TABLE_BYTES; }
 constexpr int NR = (RMAX * 4 + NT - 1) / NT;   // 16-byte patch loads per thread and chunk
@@ -41,19 +42,17 @@ __device__ __forceinline__ int sw(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
 
 // KS: shares of the reduction, four wavefronts each; a share takes every KS-th chunk of 32 channels
 template <bool HASR, int KS>
-__global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const int ny, const int max_mtiles) {
+__global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const int ny0, const int max_mtiles0) {
+    int ny = ny0, max_mtiles = max_mtiles0;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int share = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NT) : 0;
     char* As = smem + share * main_bytes(KS);          // [RMAX + 1][32] bf16
     char* Bs = As + A_BYTES;                           // [TPP][BN][32] bf16
     long long* rowC = (long long*)(smem + KS * main_bytes(KS));
     long long* rowR = rowC + BM;
+    float* scl = (float*)(rowR + BM);                  // [BN] scale, then [BN] shift
     constexpr uint32_t OOB = 0x80000000u;
 
-    const int j = (int)(blockIdx.x >> 3);
-    const int jm = j / ny, y = j - jm * ny;
-    const int mt = jm * 8 + (int)(blockIdx.x & 7);
-    if (mt >= max_mtiles) return;
     const GroupLanes lanes(a.gt);
     const bf16_t *A = a.A, *Wt = a.Wt, *res = a.R;
     void* C = a.C;
@@ -62,9 +61,15 @@ __global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const 
     int64_t a_ss = a.a_sample_stride, c_ss = a.c_sample_stride, r_ss = a.r_sample_stride;
     int a_ld = a.a_ld, c_ld = a.c_ld, r_ld = a.r_ld, c_row0 = a.c_row0, r_use = a.r_use_index, w_ld = (int)a.w_ld;
     int w_tap = (int)a.w_tap_stride, tab_ld = a.tab_ld, W = a.W, H = a.H, rows = a.rows, act = a.act, out_f32 = a.out_f32;
-    const int4 me = ds_tile_record(a, mt);
+    TileSource source(a);
+    source.hold();
     ds_hold(A, Wt, res, C, scale, shift, a_index, c_index, a_ss, c_ss, r_ss, a_ld, c_ld, r_ld, c_row0, r_use, w_ld, w_tap, tab_ld, W, H,
-            rows, act, out_f32);
+            rows, act, out_f32, ny, max_mtiles);
+    const int j = (int)(blockIdx.x >> 3);
+    const int jm = j / ny, y = j - jm * ny;
+    const int mt = jm * 8 + (int)(blockIdx.x & 7);
+    if (mt >= max_mtiles) return;
+    const int4 me = source.record(mt);
     if (me.x < 0) return;
     const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, 0x7fffffff, 0x00020000);
     const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc((void*)Wt, 0, 0x7fffffff, 0x00020000);
@@ -82,12 +87,14 @@ __global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const 
 
     if (tid < 4) *(uint4*)(As + ZROW * 64 + tid * 16) = make_uint4(0, 0, 0, 0);
 
-    // ---- patch loader: item e = tid + 256 i is chunk (e & 3) of patch row (e >> 2) --------------
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
+    // ---- patch loader: item e = tid + 256 i is chunk (e & 3) of patch row (e >> 2).  A wavefront loads 64 rows, 16 of every 64: a lane works
+    // out one of them, the lanes that load it get its address from there -------------------------------------------------------------
+    static_assert(NR == 4, "a patch row per lane");
     const int lchunk = tid & 3;
     uint32_t poff[NR];
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-        const int jr = (tid + NT * i) >> 2;
+    {
+        const int jr = 16 * wave + (lane & 15) + 64 * (lane >> 4);
         const int L = grow0 - halo + jr;              // pixel index in the group's row-major order
         uint32_t o = OOB;
         if (jr < R && L >= 0 && L < rows_g) {
@@ -95,9 +102,13 @@ __global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const 
             const int p = L - sl * rows;
             const int slot = slot0 + sl;
             const int sa = a_index ? a_index[slot] : slot;
-            o = (uint32_t)(((long long)sa * a_ss + (long long)p * a_ld + lchunk * 8) * 2);
+            o = (uint32_t)(((long long)sa * a_ss + (long long)p * a_ld) * 2);
         }
-        poff[i] = o;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const uint32_t q = (uint32_t)__shfl((int)o, (lane >> 2) + 16 * i, 64);
+            poff[i] = q == OOB ? OOB : q + lchunk * 16;
+        }
     }
     // ---- weight loader: chunk (tid & 3) of filter row n0 + (tid >> 2), one load per tap ---------
     const int wn_row = tid >> 2;
@@ -137,8 +148,11 @@ __global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const 
     // row table, tap mask, epilogue constants) is worked out while they travel
     load_phase(share, 0);
 
-    if (threadIdx.x < BM) {
-        const int m = grow0 + tid;
+    // ---- this lane's output pixel: where it goes, which taps are inside the image ---------------------------
+    const int trow = wave * 32 + l32;
+    int tapmask = 0;
+    {
+        const int m = grow0 + trow;
         long long rc = -1, rr = 0;
         if (m < rows_g) {
             const int sl = m / rows;
@@ -147,26 +161,14 @@ __global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const 
             const int cs = c_index ? c_index[slot] : slot;
             rc = (long long)cs * c_ss + (long long)(p + c_row0) * c_ld;
             rr = (long long)(r_use ? cs : 0) * r_ss + (long long)(p + c_row0) * r_ld;
-        }
-        rowC[tid] = rc;
-        rowR[tid] = rr;
-    }
-    const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
-    // ---- this lane's output pixel: which taps are inside the image ---------------------------
-    const int trow = wave * 32 + l32;
-    int tapmask = 0;
-    {
-        const int m = grow0 + trow;
-        if (m < rows_g) {
-            const int p = m % rows;
             const int oy = p / W, ox = p - oy * W;
-#pragma unroll
-            for (int u = 0; u < 3; ++u)
-#pragma unroll
-                for (int v = 0; v < 3; ++v) {
-                    const int iy = oy + u - 1, ix = ox + v - 1;
-                    if (iy >= 0 && iy < H && ix >= 0 && ix < W) tapmask |= 1 << (u * 3 + v);
-                }
+            // filter columns, filter rows inside the map
+            const int cols = (ox > 0 ? 1 : 0) | 2 | (ox + 1 < W ? 4 : 0);
+            tapmask = (oy > 0 ? cols : 0) | cols << 3 | (oy + 1 < H ? cols << 6 : 0);
+        }
+        if (lane < 32 && share == 0) {
+            rowC[trow] = rc;
+            if constexpr (HASR) rowR[trow] = rr;
         }
     }
 
@@ -177,57 +179,34 @@ __global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const 
         for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
 
     // epilogue constants and residual rows, fetched early so that their latency hides behind the loop
-    constexpr int COLS = BN, CG = COLS / 4, RPP = 64 / CG, PASSES = 32 / SROWS, VPP = 16 / PASSES;
-    const int cg = lane % CG, rr0 = lane / CG;
-    const int ncol = n0 + cg * 4;
-    const bool nok = ncol < k_out;
-    float sc[4] = {1.f, 1.f, 1.f, 1.f}, sh[4] = {0.f, 0.f, 0.f, 0.f};
-    if (nok) {
-        const long long ti = (long long)lanes.row(g) * tab_ld + ncol;
-        if (scale) {
-            const float4 t = *(const float4*)(scale + ti);
-            sc[0] = t.x; sc[1] = t.y; sc[2] = t.z; sc[3] = t.w;
+    if (threadIdx.x < BN) {
+        const int n = n0 + tid;
+        float vs = 1.f, vh = 0.f;
+        if (n < k_out) {
+            const long long ti = (long long)lanes.row(g) * tab_ld + n;
+            if (scale) vs = scale[ti];
+            if (shift) vh = shift[ti];
         }
-        if (shift) {
-            const float4 t = *(const float4*)(shift + ti);
-            sh[0] = t.x; sh[1] = t.y; sh[2] = t.z; sh[3] = t.w;
-        }
+        scl[tid] = vs;
+        scl[BN + tid] = vh;
     }
-    __syncthreads();                                   // row table visible
-    // rows that this thread finishes: one share 8 of its wavefront's own, several shares every 16 KS-th of the tile
-    constexpr int NE = KS == 1 ? PASSES * (SROWS / RPP) : BM / (16 * KS);
-    auto my_row = [&](int i) {
-        if constexpr (KS == 1) return wave * 32 + (i / (SROWS / RPP)) * SROWS + rr0 + (i % (SROWS / RPP)) * RPP;
-        else return ((int)threadIdx.x >> 4) + i * 16 * KS;
-    };
-    uint2 rres[HASR ? NE : 1];
+    // One share: 8 channels of rows (lane / 8) + 8 i of the wavefront's 32; several: 4 channels of every 16 KS-th row of the tile.
+    constexpr int NE = KS == 1 ? 4 : BM / (16 * KS);
+    const int srow = lane >> 3, ncol8 = n0 + (lane & 7) * 8, ncol4 = n0 + ((int)threadIdx.x & 15) * 4;
+    using Piece = typename std::conditional<KS == 1, uint4, uint2>::type;
+    Piece rres[HASR ? NE : 1];
     if constexpr (HASR) {
+        if constexpr (KS > 1) __syncthreads();         // row table visible
+        else wave_sync();                              // (a wavefront's own rows)
 #pragma unroll
         for (int i = 0; i < NE; ++i) {
-            const int r = my_row(i);
-            rres[i] = make_uint2(0, 0);
-            if (nok && rowC[r] >= 0) rres[i] = *(const uint2*)(res + rowR[r] + ncol);
+            const int r = KS == 1 ? wave * 32 + srow + 8 * i : ((int)threadIdx.x >> 4) + i * 16 * KS;
+            const int n = KS == 1 ? ncol8 : ncol4;
+            Piece t = {};
+            if (n < k_out && rowC[r] >= 0) t = *(const Piece*)(res + rowR[r] + n);
+            rres[i] = t;
         }
     }
-    // four channels of a row: batch-norm, residual, activation, store
-    auto finish = [&](const float4 t, long long coff, const uint2 q) {
-        float val[4] = {t.x * sc[0] + sh[0], t.y * sc[1] + sh[1], t.z * sc[2] + sh[2], t.w * sc[3] + sh[3]};
-        if constexpr (HASR) {
-            val[0] += __uint_as_float(q.x << 16);
-            val[1] += __uint_as_float(q.x & 0xffff0000u);
-            val[2] += __uint_as_float(q.y << 16);
-            val[3] += __uint_as_float(q.y & 0xffff0000u);
-        }
-        if (act == DS_ACT_RELU) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) val[e] = fmaxf(val[e], 0.f);
-        } else if (act == DS_ACT_GELU) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) val[e] = gelu_erf(val[e]);
-        }
-        if (out_f32) *(float4*)((float*)C + coff + ncol) = make_float4(val[0], val[1], val[2], val[3]);
-        else *(uint2*)((bf16_t*)C + coff + ncol) = make_uint2(f2bf2(val[0], val[1]), f2bf2(val[2], val[3]));
-    };
 
     // every share goes through as many phases; one past its last chunk multiplies zeros
     const int nph = (((k_in + 31) / 32 + KS - 1) / KS) * PPC;
@@ -260,7 +239,7 @@ __global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const 
                     bfr[t] = *(const bf16x8_t*)(Bs + (v * BN + nr) * 64 + ((ch ^ sw(nr)) * 16));
                 }
 #pragma unroll
-                for (int t = 0; t < 2; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bfr[t], acc[t], 0, 0, 0);
+                for (int t = 0; t < 2; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[t], af, acc[t], 0, 0, 0);
             }
         }
         __syncthreads();
@@ -272,58 +251,80 @@ __global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const 
         u = un;
     }
 
+    // Filters are the instruction's row operand: a lane holds channels 32 tn + 8 q + 4 lhi .. + 3 of row l32 (gemm_kernel's epilogue)
     if constexpr (KS > 1) {
-        // ---- partial tiles to LDS, added in share order ------------------------------------------------------------------
-        // (the loop's last barrier has retired every read of the slabs they take the place of)
+        // ---- partial tiles to LDS, added in share order (the loop's last barrier has retired every read of the slabs they take the place of)
         float* part = (float*)As;
 #pragma unroll
         for (int tn = 0; tn < 2; ++tn)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) part[(wave * 32 + 8 * (v >> 2) + 4 * lhi + (v & 3)) * ST_LD + tn * 32 + l32] = acc[tn][v];
+            for (int q = 0; q < 4; ++q)
+                *(float4*)(part + trow * PT_LD + tn * 32 + 8 * q + 4 * lhi) =
+                    make_float4(acc[tn][4 * q], acc[tn][4 * q + 1], acc[tn][4 * q + 2], acc[tn][4 * q + 3]);
         __syncthreads();
+        const int cg = threadIdx.x & 15;
+        const float4 s4 = *(const float4*)(scl + cg * 4), h4 = *(const float4*)(scl + BN + cg * 4);
+        with_act(act, [&](auto actc) {
+            constexpr int ACT = decltype(actc)::value;
 #pragma unroll
-        for (int i = 0; i < NE; ++i) {
-            const int r = my_row(i);
-            const long long coff = rowC[r];
-            if (!nok || coff < 0) continue;
-            float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int i = 0; i < NE; ++i) {
+                const int r = ((int)threadIdx.x >> 4) + i * 16 * KS;
+                const long long coff = rowC[r];
+                if (ncol4 >= k_out || coff < 0) continue;
+                float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-            for (int k = 0; k < KS; ++k) {
-                const float4 q = *(const float4*)((const float*)(smem + k * main_bytes(KS)) + r * ST_LD + cg * 4);
-                t.x += q.x; t.y += q.y; t.z += q.z; t.w += q.w;
+                for (int k = 0; k < KS; ++k) {
+                    const float4 p = *(const float4*)((const float*)(smem + k * main_bytes(KS)) + r * PT_LD + cg * 4);
+                    t.x += p.x; t.y += p.y; t.z += p.z; t.w += p.w;
+                }
+                float val[4] = {t.x * s4.x + h4.x, t.y * s4.y + h4.y, t.z * s4.z + h4.z, t.w * s4.w + h4.w};
+                if constexpr (HASR) add_residual(val, make_uint2(rres[i].x, rres[i].y));
+                if (out_f32) {
+                    activate<ACT>(val);
+                    *(float4*)((float*)C + coff + ncol4) = make_float4(val[0], val[1], val[2], val[3]);
+                } else {
+                    *(uint2*)((bf16_t*)C + coff + ncol4) = activate_bf16<ACT>(val);
+                }
             }
-            finish(t, coff, rres[HASR ? i : 0]);
-        }
+        });
     } else {
-        // ---- epilogue through LDS: each lane finishes 4 consecutive channels of one row -----------
-        // staging rows are private to a wavefront and the loop's last barrier has retired every read of the tiles they
-        // alias: between the passes only the compiler has to be kept from moving LDS accesses
-        auto wave_sync = [] {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        };
-        float* st = (float*)smem + wave * SROWS * ST_LD;
+        // ---- a wavefront's 32 x 64 tile through LDS as bf16, a residual parked there beforehand; it leaves as 16-byte pieces.  The stage is
+        // private to a wavefront and the loop's last barrier has retired every read of the tiles it aliases
+        bf16_t* st = (bf16_t*)smem + wave * 32 * ST_LD;
+        if constexpr (HASR) {
 #pragma unroll
-        for (int ps = 0; ps < PASSES; ++ps) {
+            for (int i = 0; i < 4; ++i) *(Piece*)(st + (srow + 8 * i) * ST_LD + (lane & 7) * 8) = rres[i];
+            wave_sync();
+        }
+        with_act(act, [&](auto actc) {
+            constexpr int ACT = decltype(actc)::value;
 #pragma unroll
             for (int tn = 0; tn < 2; ++tn)
 #pragma unroll
-                for (int vv = 0; vv < VPP; ++vv) {
-                    const int v = ps * VPP + vv;
-                    const int lr = 8 * ((v >> 2) - ps * (4 / PASSES)) + 4 * lhi + (v & 3);
-                    st[lr * ST_LD + tn * 32 + l32] = acc[tn][v];
+                for (int q = 0; q < 4; ++q) {
+                    const int ch = tn * 32 + 8 * q + 4 * lhi;
+                    const float4 s4 = *(const float4*)(scl + ch), h4 = *(const float4*)(scl + BN + ch);
+                    const f32x16_t& t = acc[tn];
+                    float val[4] = {t[4 * q] * s4.x + h4.x, t[4 * q + 1] * s4.y + h4.y, t[4 * q + 2] * s4.z + h4.z, t[4 * q + 3] * s4.w + h4.w};
+                    uint2* p = (uint2*)(st + l32 * ST_LD + ch);
+                    if constexpr (HASR) add_residual(val, *p);
+                    if (out_f32) {
+                        const long long coff = rowC[trow];
+                        activate<ACT>(val);
+                        if (coff >= 0 && n0 + ch < k_out) *(float4*)((float*)C + coff + n0 + ch) = make_float4(val[0], val[1], val[2], val[3]);
+                    } else {
+                        *p = activate_bf16<ACT>(val);
+                    }
                 }
-            wave_sync();
-            if (nok) {
+        });
+        if (out_f32) return;
+        wave_sync();
+        if (ncol8 < k_out) {
 #pragma unroll
-                for (int rr = rr0; rr < SROWS; rr += RPP) {
-                    const long long coff = rowC[wave * 32 + ps * SROWS + rr];
-                    if (coff < 0) continue;
-                    finish(*(const float4*)(st + rr * ST_LD + cg * 4), coff, rres[HASR ? ps * (SROWS / RPP) + (rr - rr0) / RPP : 0]);
-                }
+            for (int i = 0; i < 4; ++i) {
+                const long long coff = rowC[wave * 32 + srow + 8 * i];
+                if (coff >= 0) *(uint4*)((bf16_t*)C + coff + ncol8) = *(const uint4*)(st + (srow + 8 * i) * ST_LD + (lane & 7) * 8);
             }
-            wave_sync();
         }
     }
 }

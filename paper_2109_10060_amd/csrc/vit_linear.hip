@@ -62,22 +62,18 @@ __global__ __launch_bounds__(64 * NW, DIRECT ? NW / 2 : (NW + 3) / 4) void vit_l
 
     bf16x8_t ring[D];
     auto weights = [&](int p) { return weight_row(wt, ((p / nb) * seg_blocks + p % nb) * kb, kin); };
-    auto start = [&](int p) {
-        const __amdgpu_buffer_rsrc_t rw = weights(p);
+    auto start = [&](int p, bool on = true) {            // (off: no traffic)
+        const __amdgpu_buffer_rsrc_t rw = on ? weights(p) : weight_row(wt, 0, 0);
 #pragma unroll
         for (int j = 0; j < D; ++j) ring[j] = weight_tile(rw, lane16 + j * 1024);
     };
-    if (blk0 + w < blk1) start(blk0 + w);                // the weights are under way while the rows are fetched
+    if (!FEW && blk0 + w < blk1) start(blk0 + w);        // the weights are under way while the rows are fetched
 
     // ---- rows -------------------------------------------------------------------------------------------------------------
     int64_t yoff[NI];
     bool live[NI];
-    NormWeights nw;
-    if constexpr (FEW && KIT <= 4) {
-        if (gamma) nw.load(gamma, beta, kin, l16);
-    }
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
+    uint4 q[NI][KIT];
+    auto fetch_rows = [&](int i) {
         const bool in = BM % RP == 0 || prow + RP * i < BM;
         const int m = grow0 + prow + RP * i;
         live[i] = in && m < rows_g;
@@ -85,30 +81,68 @@ __global__ __launch_bounds__(64 * NW, DIRECT ? NW / 2 : (NW + 3) / 4) void vit_l
         const int sl = mm / rows, p = mm - sl * rows, slot = slot0 + sl;
         yoff[i] = (int64_t)slot * y_ss + (int64_t)p * y_ld;
         const bf16_t* xrow = x + (int64_t)slot * x_ss + (int64_t)p * x_ld;
-        uint4 q[KIT];
 #pragma unroll
         for (int k = 0; k < KIT; ++k) {
             const int ch = (k * 16 + l16) * 8;
-            q[k] = make_uint4(0, 0, 0, 0);
-            if (ch < kin) q[k] = *(const uint4*)(xrow + ch);
+            if constexpr (FEW) {
+                q[i][k] = *(const uint4*)(xrow + (ch < kin ? ch : 0));       // no branch around a request: see below
+            } else {
+                q[i][k] = make_uint4(0, 0, 0, 0);
+                if (ch < kin) q[i][k] = *(const uint4*)(xrow + ch);
+            }
         }
-        if constexpr (KIT <= 4) {
+    };
+    constexpr bool NORM = KM <= VIT_K_MAX;
+    constexpr int KN = KIT < 4 ? KIT : 4;                // 16-byte chunks of a lane inside the widest slice
+    float* gs = (float*)(Ss + BM * SP);                  // (FEW) LayerNorm weights: gamma, then beta
+    if constexpr (FEW) {
+        // Loads return in order, so what a wavefront needs first is asked for first: its rows, the LayerNorm weights (a share of them each,
+        // through LDS: read by every wavefront for itself they were 16 KiB each ahead of the rows), then the operands of the first products.
+        // Rows and operands without a branch around them: behind one the number in flight is not known, and the rows would wait for
+        // the operands as well.
+#pragma unroll
+        for (int i = 0; i < NI; ++i) fetch_rows(i);
+        if constexpr (NORM) {
+            if (gamma)
+                for (int c = tid * 4; c < kin; c += 64 * NW * 4) {
+                    *(float4*)(gs + c) = *(const float4*)(gamma + c);
+                    *(float4*)(gs + VIT_K_MAX + c) = *(const float4*)(beta + c);
+                }
+        }
+        start(blk0 + w, blk0 + w < blk1);
+        if constexpr (NORM) {
+            if (gamma) __syncthreads();
+        }
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int k = 0; k < KIT; ++k)
+            {
+                const uint32_t keep = (k * 16 + l16) * 8 < kin ? ~0u : 0u;
+                q[i][k] = make_uint4(q[i][k].x & keep, q[i][k].y & keep, q[i][k].z & keep, q[i][k].w & keep);
+            }
+    }
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        if constexpr (!FEW) fetch_rows(i);
+        const bool in = BM % RP == 0 || prow + RP * i < BM;
+        if constexpr (NORM) {
             if (gamma) {
                 float v[4][8];
                 uint4 o[4];
 #pragma unroll
-                for (int k = 0; k < KIT; ++k) unpack8(q[k], v[k]);
-                if constexpr (FEW) row_norm(v, kin, l16, eps, nw, o);
+                for (int k = 0; k < KN; ++k) RCH(k, kin) unpack8(q[i][k], v[k]);
+                if constexpr (FEW) row_norm(v, kin, l16, eps, gs, gs + VIT_K_MAX, o);
                 else row_norm(v, kin, l16, eps, gamma, beta, o);
 #pragma unroll
-                for (int k = 0; k < KIT; ++k)
-                    if ((k * 16 + l16) * 8 < kin) q[k] = o[k];
+                for (int k = 0; k < KN; ++k)
+                    if ((k * 16 + l16) * 8 < kin) q[i][k] = o[k];
             }
         }
 #pragma unroll
         for (int k = 0; k < KIT; ++k) {
             const int ch = (k * 16 + l16) * 8;
-            if (in && ch < PITCH) *(uint4*)(As + (prow + RP * i) * PITCH + ch) = q[k];     // zeros beyond the slice
+            if (in && ch < PITCH) *(uint4*)(As + (prow + RP * i) * PITCH + ch) = q[i][k];     // zeros beyond the slice
         }
     }
 
@@ -257,7 +291,7 @@ __global__ __launch_bounds__(64 * NW, DIRECT ? NW / 2 : (NW + 3) / 4) void vit_l
 
 template <int NW, int R, int D, int KM, bool FEW, bool DIRECT = false>
 int32_t launch(const VitLinearArgs& a, int64_t tiles, int max_blocks, int run_blocks, hipStream_t s) {
-    constexpr int SMEM = 32 * R * (tile_pitch(KM, D) + (DIRECT ? 0 : 32 * NW + 8)) * 2 + (DIRECT ? 32 : 0);
+    constexpr int SMEM = 32 * R * (tile_pitch(KM, D) + (DIRECT ? 0 : 32 * NW + 8)) * 2 + (DIRECT ? 32 : 0) + (FEW && KM <= VIT_K_MAX ? 2 * VIT_K_MAX * 4 : 0);
     static_assert(SMEM <= 160 * 1024, "LDS of a compute unit");
     const int32_t rc = ds_reserve_lds((const void*)vit_linear_kernel<NW, R, D, KM, FEW, DIRECT>, SMEM, "tiled linear layer");
     if (rc) return rc;
@@ -307,5 +341,5 @@ int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s) {
         return launch<4, 1, 8, VIT_K_MAX, false>(a, tiles(32), blocks, run, s);
     }
     if (kmax > 1664 || a.gamma) return DS_EUNSUPPORTED;
-    return launch<4, 1, 16, 1664, true>(a, tiles(32), blocks, 4, s);
+    return launch<8, 1, 16, 1664, true>(a, tiles(32), blocks, 2, s);
 }

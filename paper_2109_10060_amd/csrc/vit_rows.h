@@ -24,34 +24,15 @@ __device__ __forceinline__ float row16_sum(float s) {
     s += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(s), 0x121, 0xf, 0xf, true));
     return s;
 }
-// LayerNorm weights of a lane's chunks, asked for beside the rows: behind the statistics they are one more round trip
-struct NormWeights {
-    float g[4][8], b[4][8];
-    __device__ __forceinline__ void load(const float* gamma, const float* beta, int d, int l16) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int ch = (k * 16 + l16) * 8;
-#pragma unroll
-            for (int i = 0; i < 8; i += 4) {
-                float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
-                if (ch < d) {
-                    x = *(const float4*)(gamma + ch + i);
-                    y = *(const float4*)(beta + ch + i);
-                }
-                g[k][i] = x.x; g[k][i + 1] = x.y; g[k][i + 2] = x.z; g[k][i + 3] = x.w;
-                b[k][i] = y.x; b[k][i + 1] = y.y; b[k][i + 2] = y.z; b[k][i + 3] = y.w;
-            }
-        }
-    }
-};
-
 // LayerNorm of one row held by 16 lanes, lane l with the 8-channel chunks l, l + 16, l + 32, l + 48; the arithmetic and
-// the order of layernorm16_kernel
+// the order of layernorm16_kernel.  Chunks that begin behind the slice are skipped by a branch of the whole wavefront (RCH): a normalised row
+// is about 450 vector instructions of a lane, and of the four chunks a slice of 192 or 256 channels has two.
+#define RCH(k, d) if (128 * (k) < (d))
 __device__ __forceinline__ float row_stats(const float (&v)[4][8], int d, int l16, float eps, float* mean) {
     float s = 0.f;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-        if ((k * 16 + l16) * 8 < d) {
+        RCH(k, d) if ((k * 16 + l16) * 8 < d) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) s += v[k][i];
         }
@@ -60,7 +41,7 @@ __device__ __forceinline__ float row_stats(const float (&v)[4][8], int d, int l1
     float q = 0.f;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-        if ((k * 16 + l16) * 8 < d) {
+        RCH(k, d) if ((k * 16 + l16) * 8 < d) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const float t = v[k][i] - mu;
@@ -69,18 +50,6 @@ __device__ __forceinline__ float row_stats(const float (&v)[4][8], int d, int l1
         }
     return 1.0f / sqrtf(row16_sum(q) / (float)d + eps);
 }
-__device__ __forceinline__ void row_norm(const float (&v)[4][8], int d, int l16, float eps, const NormWeights& w, uint4 (&out)[4]) {
-    float mu;
-    const float rstd = row_stats(v, d, l16, eps, &mu);
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-        if ((k * 16 + l16) * 8 < d) {
-            float o8[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) o8[i] = (v[k][i] - mu) * rstd * w.g[k][i] + w.b[k][i];
-            out[k] = pack8(o8);
-        }
-}
 __device__ __forceinline__ void row_norm(const float (&v)[4][8], int d, int l16, float eps, const float* gamma,
                                          const float* beta, uint4 (&out)[4]) {
     float mu;
@@ -88,7 +57,7 @@ __device__ __forceinline__ void row_norm(const float (&v)[4][8], int d, int l16,
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int ch = (k * 16 + l16) * 8;
-        if (ch < d) {
+        RCH(k, d) if (ch < d) {
             const float4 g0 = *(const float4*)(gamma + ch), g1 = *(const float4*)(gamma + ch + 4);
             const float4 b0 = *(const float4*)(beta + ch), b1 = *(const float4*)(beta + ch + 4);
             const float gm[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
