@@ -72,7 +72,7 @@ __device__ __forceinline__ float sum_of_8(float v) {
 }
 
 template <int NB, bool PROJ, bool CHAIN>
-__global__ __launch_bounds__(NT, NB == 2 ? 3 : 2) void bneck_kernel(const BneckArgs a, const int max_mtiles) {
+__global__ __launch_bounds__(NT, NB == 2 ? 3 : 2) void bneck_kernel(const BneckArgs args, const int max_mtiles0) {
     using L = Layout<NB, PROJ, CHAIN>;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     char* As = smem;                                   // [RMAX + 1][32] bf16: the patch of a chunk
@@ -85,16 +85,39 @@ __global__ __launch_bounds__(NT, NB == 2 ? 3 : 2) void bneck_kernel(const BneckA
 
     // Eight neighbouring tiles to a die (workgroups are dealt to the dies in turn): the patches of neighbours overlap by almost half.
     const int b = (int)blockIdx.x, mt = (b & ~63) | ((b & 7) << 3) | ((b >> 3) & 7);
+    const GroupLanes lanes(args.gt);
+    const int next_g = CHAIN ? args.next[threadIdx.x & 63] : 0, kx_g = PROJ ? args.kx[threadIdx.x & 63] : 0;
+    struct {                                           // the arguments, asked for together (ds_hold)
+        const bf16_t *y1, *w2, *w3, *w1, *wp, *shortcut, *x;
+        const float *s2, *h2, *s3, *h3, *s1, *h1, *sp, *hp;
+        const int32_t* x_index;
+        bf16_t *z, *y1_next;
+        float* sums;
+        int64_t y1_ss, z_ss, x_ss;
+        int mid_full, out_full, x_full, tab3, H, W;
+        const int4* mtiles;
+        const int32_t* n_mtiles;
+    } a = {args.y1, args.w2, args.w3, args.w1, args.wp, args.shortcut, args.x, args.s2, args.h2, args.s3, args.h3, args.s1, args.h1, args.sp,
+           args.hp, args.x_index, args.z, args.y1_next, args.sums, args.y1_ss, args.z_ss, args.x_ss, args.mid_full, args.out_full, args.x_full,
+           args.tab3, args.H, args.W, args.mtiles, args.n_mtiles};
+    int max_mtiles = max_mtiles0;
+    ds_hold(max_mtiles, a.mtiles, a.n_mtiles, a.y1, a.w2, a.w3, a.s2, a.h2, a.s3, a.h3, a.z, a.y1_ss, a.z_ss, a.mid_full, a.tab3, a.H, a.W);
+    if constexpr (CHAIN) ds_hold(a.w1, a.s1, a.h1, a.y1_next, a.out_full);
+    else ds_hold(a.sums, a.out_full);
+    if constexpr (PROJ) ds_hold(a.x, a.wp, a.sp, a.hp, a.x_index, a.x_ss, a.x_full);
+    else ds_hold(a.shortcut);
     if (mt >= max_mtiles) return;
-    const GroupLanes lanes(a.gt);
     const int4 me = a.mtiles[mt];
-    if (mt >= *a.n_mtiles) return;
-    const int g = __builtin_amdgcn_readfirstlane(me.x), grow0 = me.y, slot0 = me.z, rows_g = me.w;
+    const int n_mtiles = *a.n_mtiles;
+    int first = __builtin_amdgcn_readfirstlane(me.x);
+    ds_hold(first);                                    // asked for beside the count, not behind it
+    if (mt >= n_mtiles) return;
+    const int g = first, grow0 = me.y, slot0 = me.z, rows_g = me.w;
     const int mid = lanes.k_in(g), out = lanes.k_out(g), trow = lanes.row(g);
     if (mid <= 0 || out <= 0) return;
     const int W = a.W, H = a.H, rows = W * H, halo = W + 1, R = BM + 2 * halo;
-    const int next = CHAIN ? a.next[g] : 0;            // <= 0: this group ends with the block
-    const int kx = PROJ ? a.kx[g] : 0;
+    const int next = CHAIN ? __builtin_amdgcn_readlane(next_g, g) : 0;            // <= 0: this group ends with the block
+    const int kx = PROJ ? __builtin_amdgcn_readlane(kx_g, g) : 0;
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const __amdgpu_buffer_rsrc_t rs_y1 = __builtin_amdgcn_make_buffer_rsrc((void*)a.y1, 0, 0x7fffffff, 0x00020000);
@@ -106,13 +129,19 @@ __global__ __launch_bounds__(NT, NB == 2 ? 3 : 2) void bneck_kernel(const BneckA
     // ---- 3x3 layer: as conv3_kernel, filters as the row operand ---------------------------------------------------------------
     const int lchunk = tid & 3, wrow = tid >> 2;
     uint32_t poff[NR], woff[NB / 2];
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-        const int jr = (tid + NT * i) >> 2, px = grow0 - halo + jr;
-        poff[i] = OOB;
+    {
+        // a wavefront loads 64 patch rows, 16 of every 64: a lane works out one of them, the lanes that load it get its address from there
+        static_assert(NR == 4, "a patch row per lane");
+        const int jr = 16 * wave + (lane & 15) + 64 * (lane >> 4), px = grow0 - halo + jr;
+        uint32_t o = OOB;
         if (jr < R && px >= 0 && px < rows_g) {
             const int sl = px / rows;
-            poff[i] = (uint32_t)(((slot0 + sl) * a.y1_ss + (int64_t)(px - sl * rows) * mid + lchunk * 8) * 2);
+            o = (uint32_t)(((slot0 + sl) * a.y1_ss + (int64_t)(px - sl * rows) * mid) * 2);
+        }
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const uint32_t q = (uint32_t)__shfl((int)o, (lane >> 2) + 16 * i, 64);
+            poff[i] = q == OOB ? OOB : q + lchunk * 16;
         }
     }
 #pragma unroll
@@ -172,13 +201,9 @@ __global__ __launch_bounds__(NT, NB == 2 ? 3 : 2) void bneck_kernel(const BneckA
         if (m < rows_g) {
             const int sl = m / rows, p = m - sl * rows, slot = slot0 + sl;
             const int oy = p / W, ox = p - oy * W;
-#pragma unroll
-            for (int u = 0; u < 3; ++u)
-#pragma unroll
-                for (int v = 0; v < 3; ++v) {
-                    const int iy = oy + u - 1, ix = ox + v - 1;
-                    if (iy >= 0 && iy < H && ix >= 0 && ix < W) tapmask |= 1 << (u * 3 + v);
-                }
+            // filter columns, filter rows inside the map
+            const int cols = (ox > 0 ? 1 : 0) | 2 | (ox + 1 < W ? 4 : 0);
+            tapmask = (oy > 0 ? cols : 0) | cols << 3 | (oy + 1 < H ? cols << 6 : 0);
             z = (int)(slot * a.z_ss + (int64_t)p * out);
             y = (int)(slot * a.y1_ss + (int64_t)p * next);
             if constexpr (PROJ) {
