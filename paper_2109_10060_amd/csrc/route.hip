@@ -389,16 +389,8 @@ __global__ __launch_bounds__(1024) void bucket64_kernel(const BucketArgs a) {
         if (k >= 0) atomicAdd(&base[k], 1);
     }
     __syncthreads();
-    auto scan = [&](int v) {                             // inclusive, over the wavefront
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int t = __shfl_up(v, d, 64);
-            if (lane >= d) v += t;
-        }
-        return v;
-    };
     if (wave == 0) {
-        const int h = base[lane], end = scan(h);
+        const int h = base[lane], end = ds_scan64(h);
         base[lane] = start[lane] = end - h;
         if (lane == 63) start[64] = end;
     }
@@ -409,7 +401,7 @@ __global__ __launch_bounds__(1024) void bucket64_kernel(const BucketArgs a) {
     if (wave < a.n_lists) {
         const int g = T - 1 - lane;
         const int n = g >= 0 ? ((start[g + 1] - start[g]) * a.list_rows[wave] + DS_GEMM_BM - 1) / DS_GEMM_BM : 0;
-        const int end = scan(n);
+        const int end = ds_scan64(n);
         pre[wave][lane + 1] = end;
         if (lane == 0) pre[wave][0] = 0;
         if (lane == 63) *(int32_t*)a.lists[wave] = end;
