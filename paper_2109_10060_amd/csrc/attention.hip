@@ -10,19 +10,26 @@
 // lane^32.  The probabilities are rounded to bf16 in registers and fed straight back as the B
 // operand of  O^T = V^T . P^T  (normalised by the row sum afterwards, in fp32); the key order an accumulator
 // holds (runs of 4 keys) is reproduced on the V^T side with two 8-byte LDS reads,
-// so no shuffle or LDS round trip of P is needed.
+// so no shuffle or LDS round trip of P is needed.  V stays in rows in LDS and is transposed on the way out (read_keys): scattered into V^T two
+// bytes at a time, the staging was a third of a workgroup's life.
 #include <type_traits>
 
 #include "common.h"
 
 namespace {
 
-// V_LD: 228 elements put the eight channel octets that a wavefront scatters at once on four groups of banks (232: on two) and the 32
-// channels of a product's operand on different ones; 256 images of DS-ViT 38.1 -> 36.4 us a launch, 64 images 1056 -> 1043 us a pass, 5 images 563 -> 559
-constexpr int NKT = 7, KEYS = NKT * 32, V_LD = KEYS + 4;
+constexpr int NKT = 7, KEYS = NKT * 32;
 
-// DH: head dimension, a multiple of 16.  The output tiles are 32 channels tall, so V^T is padded with
-// zero rows to DT * 32 channels and the channels past DH are computed and dropped.
+// Four keys of one channel out of rows of V: a group of 16 lanes reads 4 rows x 16 channels, 8 bytes a lane (row l16 / 4, channels 4 (l16 % 4) ..),
+// and lane i gets channel i of the four rows.
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint2 read_keys(const bf16_t* p) {
+    const s16x4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)p);
+    return __builtin_bit_cast(uint2, v);
+}
+
+// DH: head dimension, a multiple of 16.  The output tiles are 32 channels tall; the channels past DH are computed from whatever lies
+// there and dropped (they are rows of the product's first operand, so nothing else depends on them).
 template <int DH>
 __global__ __launch_bounds__(448) __attribute__((amdgpu_waves_per_eu(4, 4))) void attention_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                         const bf16_t* __restrict__ v, bf16_t* __restrict__ o,
@@ -30,12 +37,14 @@ __global__ __launch_bounds__(448) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
                                                         int64_t o_sample_stride, const int32_t* slot_group,
                                                         const GroupTable gt, int N, float scale) {
     constexpr int K_LD = DH + 8, KK = DH / 16, DT = (DH + 31) / 32, CPR = DH / 8;
+    constexpr int V_LD = DT * 32 + 16;        // the four rows of a group of lanes on different banks
     static_assert(DH % 16 == 0 && DH <= 64, "head dimension");
     __shared__ __attribute__((aligned(16))) bf16_t Ks[KEYS * K_LD];
-    __shared__ __attribute__((aligned(16))) bf16_t Vt[DT * 32 * V_LD];
+    __shared__ __attribute__((aligned(16))) bf16_t Vs[KEYS * V_LD];
     const int slot = blockIdx.x, head = blockIdx.y;
+    const int width = gt.k_out[threadIdx.x & 63];            // (a lane per group: beside the group's number, not behind it)
     const int g = slot_group ? slot_group[slot] : 0;
-    if (head * DH >= gt.k_out[g]) return;
+    if (head * DH >= __builtin_amdgcn_readlane(width, __builtin_amdgcn_readfirstlane(g))) return;
     const int tid = threadIdx.x;
     const int64_t base = (int64_t)slot * sample_stride + head * DH;
 
@@ -51,8 +60,6 @@ __global__ __launch_bounds__(448) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     }
 
     const int nthreads = blockDim.x;          // one wavefront per 32-query tile
-    if constexpr (DH % 32 != 0)
-        for (int c = tid; c < (DT * 32 - DH) * V_LD / 2; c += nthreads) ((uint32_t*)(Vt + DH * V_LD))[c] = 0u;
     // A lane's pieces of K and V, four at a time (all there are with seven wavefronts of a 64-wide head), without a branch around a
     // request: rows past the sequence are past the descriptor and give zeros.  That is what lets them travel together; one at a time
     // measures the same (256 images 36.4 and 36.6 us a launch), one at a time behind a test of the row, at the pitch of
@@ -75,15 +82,12 @@ __global__ __launch_bounds__(448) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
             const int c = c0 + i * nthreads, row = c / CPR, ch = (c - row * CPR) * 8;
             if (c >= KEYS * CPR) break;
             *(uint4*)(Ks + row * K_LD + ch) = kv[i];
-            const uint32_t w[4] = {vv[i].x, vv[i].y, vv[i].z, vv[i].w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                Vt[(ch + 2 * j) * V_LD + row] = (bf16_t)(w[j] & 0xffffu);
-                Vt[(ch + 2 * j + 1) * V_LD + row] = (bf16_t)(w[j] >> 16);
-            }
+            *(uint4*)(Vs + row * V_LD + ch) = vv[i];
         }
     }
     __syncthreads();
+    // with few heads a workgroup multiplies for half of the query tiles only, one wavefront a SIMD
+    if (gridDim.z > 1 && (wave >= 4) != (blockIdx.z > 0)) return;
 
     {
         // The keys are taken in two parts (tiles 0..3, then 4..6) with a running maximum and sum, so that only four
@@ -99,6 +103,7 @@ __global__ __launch_bounds__(448) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
             for (int e = 0; e < 16; ++e) oacc[dt][e] = 0.f;
+        const int vrow = 4 * lhi + ((lane & 15) >> 2), vcol = (lane & 16) + 4 * (lane & 3);   // what this lane reads for its group
         int krow = l32;                           // first key row of this lane; re-derived after each part (below)
         auto part = [&](auto lo_c, auto hi_c) {
             constexpr int LO = decltype(lo_c)::value, HI = decltype(hi_c)::value, NP = HI - LO;
@@ -170,10 +175,10 @@ __global__ __launch_bounds__(448) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
                     for (int e = 0; e < 4; ++e) pv.u[e] = pf[i][4 * half + e];
 #pragma unroll
                     for (int dt = 0; dt < DT; ++dt) {
-                        const bf16_t* vp = Vt + (dt * 32 + l32) * V_LD + kt * 32 + 16 * half + 4 * lhi;
+                        const bf16_t* vp = Vs + (kt * 32 + 16 * half + vrow) * V_LD + dt * 32 + vcol;
                         union { uint2 h[2]; bf16x8_t v; } vf;
-                        vf.h[0] = *(const uint2*)vp;
-                        vf.h[1] = *(const uint2*)(vp + 8);
+                        vf.h[0] = read_keys(vp);
+                        vf.h[1] = read_keys(vp + 8 * V_LD);
                         oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.v, pv.v, oacc[dt], 0, 0, 0);
                     }
                 }
@@ -190,20 +195,20 @@ __global__ __launch_bounds__(448) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
             for (int e = 0; e < 16; ++e) oacc[dt][e] *= inv;
-        // oacc[dt][e] = O[q = l32][d = dt*32 + 8*(e>>2) + 4*lhi + (e&3)]: 4 consecutive channels per store
-        if (qrow < N) {
-            bf16_t* op = o + (int64_t)slot * o_sample_stride + (int64_t)qrow * o_ld + head * DH + 4 * lhi;
+        // oacc[dt][e] = O[q = l32][d = dt*32 + 8*(e>>2) + 4*lhi + (e&3)]: the halves of the wavefront trade runs of 4 channels, so that
+        // a lane stores 8 of them
+        bf16_t* op = o + (int64_t)slot * o_sample_stride + (int64_t)qrow * o_ld + head * DH + 8 * lhi;
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
+        for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-                for (int g4 = 0; g4 < 4; ++g4) {
-                    if (dt * 32 + 8 * g4 >= DH) continue;   // padding channels of the last tile
-                    uint2 w;
-                    w.x = f2bf2(oacc[dt][4 * g4], oacc[dt][4 * g4 + 1]);
-                    w.y = f2bf2(oacc[dt][4 * g4 + 2], oacc[dt][4 * g4 + 3]);
-                    *(uint2*)(op + dt * 32 + 8 * g4) = w;
-                }
-        }
+            for (int g4 = 0; g4 < 4; g4 += 2) {
+                if (dt * 32 + 8 * g4 >= DH) continue;   // padding channels of the last tile
+                const uint32_t lo0 = f2bf2(oacc[dt][4 * g4], oacc[dt][4 * g4 + 1]), hi0 = f2bf2(oacc[dt][4 * g4 + 2], oacc[dt][4 * g4 + 3]);
+                const uint32_t lo1 = f2bf2(oacc[dt][4 * g4 + 4], oacc[dt][4 * g4 + 5]), hi1 = f2bf2(oacc[dt][4 * g4 + 6], oacc[dt][4 * g4 + 7]);
+                const auto a0 = __builtin_amdgcn_permlane32_swap(lo0, lo1, false, false);
+                const auto a1 = __builtin_amdgcn_permlane32_swap(hi0, hi1, false, false);
+                if (qrow < N) *(uint4*)(op + dt * 32 + 8 * g4) = make_uint4(a0[0], a1[0], a0[1], a1[1]);
+            }
     }
 }
 
@@ -217,7 +222,8 @@ int32_t ds_launch_attention(const bf16_t* q, const bf16_t* k, const bf16_t* v, b
     if (head_dim != 32 && head_dim != 48 && head_dim != 64)
         DS_FAIL(DS_EUNSUPPORTED, "attention: head dimension %d (32, 48 or 64)", head_dim);
     ProfScope prof(DS_K_ATTENTION, s);
-    const dim3 grid((unsigned)B, (unsigned)H), block(64 * ((N + 31) / 32));
+    const int waves = (N + 31) / 32;
+    const dim3 grid((unsigned)B, (unsigned)H, waves > 4 && (int64_t)B * H * 2 <= 256 ? 2u : 1u), block(64 * waves);
     const float scale = 1.0f / sqrtf((float)head_dim);
 #define DS_ATT(D)                                                                                                  \
     hipLaunchKernelGGL(attention_kernel<D>, grid, block, 0, s, q, k, v, o, sample_stride, ld, o_ld, o_sample_stride, \
