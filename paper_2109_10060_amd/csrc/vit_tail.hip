@@ -14,18 +14,20 @@
 // Each of the NW = 12 (13 above 384 channels) wavefronts owns one 32-column block of the block's width and of every
 // HC = 32 NW columns of the hidden layer; R row blocks share every weight operand.
 // Around the products a workgroup has nothing beside it on its compute unit, so what it waits for is kept off its path: the
-// residual rows wait in the hidden tile, which is free until the MLP, LayerNorm weights in LDS, biases in registers.  DS-ViT, us
-// a pass: LayerNorm weights from memory -> from LDS 16 images 676 -> 672, 64 images 1047 -> 1043, 256 images 2509 -> 2485 (DS-ViT++
-// 3688 -> 3666); biases where they are used -> in registers 64 images 1050 -> 1043, 128 images 1472 -> 1468, 256 images no change.
+// residual rows wait in a hidden tile, which is free until the MLP, LayerNorm weights in LDS, biases in a register a lane.
 //
-// The products of a wavefront are one stream of operands: the last turn of each asks for the first operands of the next (across
-// LayerNorm, GELU and barriers), which no longer wait for L2 at every start.  DS-ViT 16 / 32 / 64 images 673 / 880 / 1050 -> 648 / 845 / 1040 us a
-// pass, DS-ViT++ 64 / 256 images 1416 / 3900 -> 1388 / 3820.  Behind the block a workgroup still has its rows: it normalises them for
-// the next block and multiplies them with that block's Q/K/V weights, stored from registers as vit_linear_kernel stores them.
-// Measured with parts left out, 256 images of DS-ViT, us a launch without Q/K/V: all 110; no weights asked for 99; no GELU 95; neither
-// 79; no LDS reads 110; no MLP 40.  A step of the 12 wavefronts takes 12 KiB through the compute unit's first cache, at 50 bytes a clock a
-// quarter longer than its 24 matrix instructions.  GELU of a chunk between the turns of the product before it: 108 with 12 wavefronts, 142 for
-// 139 with 13 (spills).
+// The products of a wavefront are one stream of operands: the last turn of each asks for the first operands of the next, across
+// LayerNorm, GELU and barriers.  Behind the block a workgroup still has its rows: it normalises them for the next block and multiplies
+// them with that block's Q/K/V weights, stored from registers as vit_linear_kernel stores them.
+// A workgroup of 384 channels and 1536 hidden ones lives 122 thousand clocks: rows 9, projection 8, LayerNorm 5, MLP 65, rows out and
+// LayerNorm 7, Q/K/V 22; the matrix pipe is busy for 55 of them, the vector ALU for about 45.  A loop of these loads, LDS reads and products
+// alone takes 57 bytes a clock from L2 and keeps the pipe at 90 %; here the mean is 35 to 45, because a wait for one operand is a wait for
+// everything asked for before it.  What that took: LDS reads issued a step ahead (the compiler sank them behind the products), no branch
+// that gives out the operands under way (they were moved there, and a move waits for them), requests for rows and constants and stores
+// without branches, six operands in flight for four, two hidden tiles and so one barrier a tile for two.  us a pass, before -> now: 256
+// images of DS-ViT 2322 -> 2217, on another card 2444 -> 2322; 60 to 100 images 1074 -> 988; 256 images of DS-ViT++ (13 wavefronts: one
+// hidden tile, four in flight) 3522 -> 3512.  Eight operands in flight 2350 for 2322 at 256 images.  Q/K/V blocks dealt out as wavefronts
+// come free instead of in turn: no change.
 //
 // Sums run in the order of gemm_kernel's and layernorm16_kernel's, so the results are the same bits.
 #include "gelu.h"
@@ -33,12 +35,19 @@
 
 namespace {
 
-// pitches of the activation and the hidden tile; 8 elements behind the hidden tile for the read-ahead of its last row
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+// Pitches of the activation tile and of the hidden tiles: two of them, or one where 13 wavefronts leave no LDS for a second (two of 12 column
+// blocks are five rounds for 1664 hidden channels where one of 13 is four: 256 images of DS-ViT++ 3512 us a pass, 3616 with two); 8
+// elements behind the last one for the read-ahead of its last row.
 template <int NW, int R, int D>
 struct TailTile {
-    static constexpr int PA = tile_pitch(VIT_K_MAX, D), PH = tile_pitch(32 * NW, D);
-    static constexpr int NORM = 32 * R * (PA + PH) + 8;     // LayerNorm weights: gamma, then beta
-    static constexpr int SMEM = NORM * 2 + 2 * VIT_K_MAX * 4;
+    static constexpr bool TWO = NW <= 12;
+    static constexpr int KA = NW > 12 ? VIT_K_MAX : 384;    // channels of a row
+    static constexpr int PA = tile_pitch(KA, D), PH = tile_pitch(32 * NW, D);
+    static constexpr int NORM = 32 * R * (PA + (TWO ? 2 : 1) * PH) + 8; // LayerNorm weights: gamma, then beta
+    static constexpr int BIAS = NORM + 2 * 2 * KA;          // of each wavefront's columns
+    static constexpr int SMEM = BIAS * 2 + NW * 32 * 4;
     static_assert(SMEM <= 160 * 1024, "LDS of a compute unit");
 };
 
@@ -52,14 +61,12 @@ struct Stream {
 template <int NW, int R, int D>
 __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const VitTailArgs a) {
     using Tile = TailTile<NW, R, D>;
-    // biases travel during the products; not with 13 wavefronts (no registers for them) and not with 32 rows, where a smaller kernel
-    // leaves room for those of a batch's other parts (128 images in four parts 1888 us a pass, 1959 with them; 16 images alone 672 and 666)
-    constexpr bool CST = NW <= 12 && R == 2;
-    constexpr int BM = 32 * R, HC = 32 * NW, PA = Tile::PA, PH = Tile::PH, RP = 4 * NW, NI = (BM + RP - 1) / RP;   // RP: rows of a row phase
+    constexpr int BM = 32 * R, HC = 32 * NW, PA = Tile::PA, PH = Tile::PH, KA = Tile::KA, RP = 4 * NW, NI = (BM + RP - 1) / RP;   // RP: rows of a row phase
     extern __shared__ __attribute__((aligned(16))) char smem[];
     bf16_t* As = (bf16_t*)smem;                         // [BM][PA]
-    bf16_t* Hs = As + BM * PA;                          // [BM][PH]
-    float* gs = (float*)(As + Tile::NORM);              // [2][VIT_K_MAX]
+    constexpr bool TWO = Tile::TWO;
+    bf16_t* Hs = As + BM * PA;                          // [TWO ? 2 : 1][BM][PH]
+    float* gs = (float*)(As + Tile::NORM);              // [2][KA]
 
     const int4 me = ds_tile_record_of(a.offsets, a.gt.T, a.rows, (int)blockIdx.x, BM);
     if (me.x < 0) return;
@@ -73,18 +80,23 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
 
 
     // ---- rows of this thread's 16-lane group: attention output and residual rows to the two tiles ---------------------------
-    int64_t xoff[NI];
-    bool live[NI];
+    // Rows, constants and outputs go through descriptors of the tile's first sample: what lies outside a slice or a group is an offset out
+    // of range.  Without a branch around them the requests travel together, and the number in flight is known wherever one is waited
+    // for -- behind a branch every wait for the weights' ring would be one for the rows and stores as well.
+    constexpr uint32_t OOB = 0x80000000u;
+    const int first = grow0 / a.rows;                    // (of the group; rows of a tile count from there)
+    auto window = [](const void* p, int64_t elements) {
+        return __builtin_amdgcn_make_buffer_rsrc((void*)((const bf16_t*)p + elements), 0, 0x7fffffff, 0x00020000);
+    };
+    const __amdgpu_buffer_rsrc_t rx = window(a.x, (int64_t)(slot0 + first) * a.x_ss);
+    uint32_t xoff[NI];                                   // of this lane's first 8 channels; out of range: no such row
     // rows of x, the residual of both sums, in a tile of LDS
     auto x_rows = [&](uint4 (&q)[NI][4]) {
 #pragma unroll
         for (int i = 0; i < NI; ++i)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int ch = (k * 16 + l16) * 8;
-                q[i][k] = make_uint4(0, 0, 0, 0);
-                if (ch < de && live[i]) q[i][k] = *(const uint4*)(a.x + xoff[i] + ch);
-            }
+            for (int k = 0; k < 4; ++k)
+                q[i][k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rx, (int)((k * 16 + l16) * 8 < de ? xoff[i] + k * 256 : OOB), 0, 0));
     };
     auto to_tile = [&](const uint4 (&q)[NI][4], bf16_t* tile, int pitch, int width) {
 #pragma unroll
@@ -97,30 +109,29 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     };
     {
         uint4 q[NI][4], xr[NI][4];
+        const __amdgpu_buffer_rsrc_t ro = window(a.o, (int64_t)(slot0 + first) * a.o_ss);
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             const bool in = BM % RP == 0 || prow + RP * i < BM;
-            const int m = grow0 + prow + RP * i;
-            live[i] = in && m < rows_g;
-            const int mm = live[i] ? m : grow0;
-            const int sl = mm / a.rows, p = mm - sl * a.rows, slot = slot0 + sl;
-            xoff[i] = (int64_t)slot * a.x_ss + (int64_t)p * de;
-            const bf16_t* orow = a.o + (int64_t)slot * a.o_ss + (int64_t)p * a.o_ld;
+            const int m = grow0 + prow + RP * i, sl = m / a.rows, p = m - sl * a.rows;
+            const bool live = in && m < rows_g;
+            xoff[i] = live ? (uint32_t)(((sl - first) * a.x_ss + (int64_t)p * de + l16 * 8) * 2) : OOB;
+            const uint32_t ooff = live ? (uint32_t)(((sl - first) * a.o_ss + (int64_t)p * a.o_ld + l16 * 8) * 2) : OOB;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int ch = (k * 16 + l16) * 8;
-                q[i][k] = make_uint4(0, 0, 0, 0);
-                if (ch < kin) q[i][k] = *(const uint4*)(orow + ch);
-            }
+            for (int k = 0; k < 4; ++k)
+                q[i][k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(ro, (int)((k * 16 + l16) * 8 < kin ? ooff + k * 256 : OOB), 0, 0));
         }
         x_rows(xr);
         for (int i = tid; i < de; i += 64 * NW) {
             gs[i] = a.g2[i];
-            gs[VIT_K_MAX + i] = a.be2[i];
+            gs[KA + i] = a.be2[i];
         }
         to_tile(q, As, PA, PA);                          // zeros beyond the slice
         to_tile(xr, Hs, PH, de);
     }
+    auto x_out = [&](int i, int k, const uint4& q) {     // 8 channels of a row that this thread fetched
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, q), rx, (int)((k * 16 + l16) * 8 < de ? xoff[i] + k * 256 : OOB), 0, 0);
+    };
 
     // ---- acc2[r] += W[column block w] . act^T over K channels, 16 a step -----------------------------------------------------
     f32x16_t acc2[R];
@@ -147,38 +158,42 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
         bf16x8_t f[2][R];
 #pragma unroll
         for (int r = 0; r < R; ++r) f[0][r] = *(const bf16x8_t*)(base + r * 32 * pitch);
-        for (int k0 = 0; k0 < t.k; k0 += 16 * D) {
-            const bool more = k0 + 16 * D < t.k;
+        int k0 = 0;
+        bool more;
+        do {                                             // (no channels: one turn of zero weights, its sums are not used)
+            more = k0 + 16 * D < t.k;
             const __amdgpu_buffer_rsrc_t rs = weight_row(more ? t.w : next.w, 0, more ? t.k : next.k);
             const uint32_t off = lane16 + (more ? k0 * 64 + D * 1024 : 0);
 #pragma unroll
             for (int j = 0; j < D; ++j) {
 #pragma unroll
                 for (int r = 0; r < R; ++r) f[(j + 1) & 1][r] = *(const bf16x8_t*)(base + r * 32 * pitch + k0 + (j + 1) * 16);
+                __builtin_amdgcn_sched_barrier(0);       // (the compiler would sink the reads to their use)
 #pragma unroll
                 for (int r = 0; r < R; ++r) acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[j], f[j & 1][r], acc[r], 0, 0, 0);
                 ring[j] = weight_tile(rs, off + j * 1024);
-                __builtin_amdgcn_sched_barrier(0);       // (the compiler would sink the reads to their use)
+                __builtin_amdgcn_sched_barrier(0);
             }
-        }
+            k0 += 16 * D;
+        } while (more);
     };
-    // this lane's columns: 4 channels of a row at a time
-    auto constants = [&](float4 (&h)[4], const float* v, int c0, int n) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int ch = c0 + 8 * q + 4 * lhi;         // (4 channels are inside a slice or outside it)
-            h[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (ch < n) h[q] = *(const float4*)(v + ch);
-        }
+    // Biases of a wavefront's 32 columns travel beside a product in one register a lane and reach the lanes that add them, 4 channels at a
+    // time, through the wavefront's own line of LDS.
+    float* line = (float*)(As + Tile::BIAS) + w * 32;
+    auto columns = [&](const float* v, int c0, int n) {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)v, 0, n * 4, 0x00020000);
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (c0 + l32) * 4, 0, 0));
     };
+    auto bias_of = [&](int q) { return *(const float4*)(line + 8 * q + 4 * lhi); };
     // tile (in LDS, bf16) = tile + acc2 + bias on the elements this lane accumulated
-    auto add_columns = [&](const float4 (&cst)[4], const float* bias, bf16_t* tile, int pitch) {
+    auto add_columns = [&](float cst, bf16_t* tile, int pitch) {
         if (!con) return;
+        line[l32] = cst;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int ch = w * 32 + 8 * q + 4 * lhi;
             if (ch >= de) continue;
-            const float4 h = CST ? cst[q] : *(const float4*)(bias + ch);
+            const float4 h = bias_of(q);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 uint2* p = (uint2*)(tile + (r * 32 + l32) * pitch + ch);
@@ -202,14 +217,18 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     clear2();
     // (no channels: no traffic)
     auto stream = [](const bf16_t* w, int t0, int k) { return Stream{w + (int64_t)t0 * 512, k}; };
-    auto fc1 = [&](int hb) { return stream(a.w1, hb * a.kb1, hb * 32 < hid ? de : 0); };
+    // (held: read again from the arguments they cost a round trip to the scalar cache at every product)
+    const bf16_t *w1 = a.w1 + (int64_t)(w * a.kb1) * 512, *w2 = a.w2 + (int64_t)(w * a.kb2) * 512;
+    const float *b1 = a.b1, *b2 = a.b2;
+    int step1 = NW * a.kb1;
+    ds_hold(w1, w2, b1, b2, step1);
+    const Stream first_fc1 = stream(w1, 0, w * 32 < hid ? de : 0);
     const Stream sp = stream(a.wp, w * a.kbp, con ? kin : 0);
-    start(con ? sp : fc1(w));
-    float4 cst[4];
-    if (CST) constants(cst, a.bp, w * 32, de);
+    start(con ? sp : first_fc1);
+    float cst = columns(a.bp, w * 32, de);
     __syncthreads();
-    if (con) walk(acc2, sp, fc1(w), As, PA);
-    add_columns(cst, a.bp, Hs, PH);                            // x waits in the hidden tile
+    if (con) walk(acc2, sp, first_fc1, As, PA);
+    add_columns(cst, Hs, PH);                            // x waits in the hidden tile
     __syncthreads();
     // ---- x to memory, LN2 in place ---------------------------------------------------------------------------------------
 #pragma unroll
@@ -224,11 +243,11 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
             const int ch = (k * 16 + l16) * 8;
             if (ch < de) {
                 const uint4 q = *(const uint4*)(sum + ch);
-                if (live[i]) *(uint4*)(a.x + xoff[i] + ch) = q;
+                x_out(i, k, q);
                 unpack8(q, v[k]);
             }
         }
-        row_norm(v, de, l16, a.eps, gs, gs + VIT_K_MAX, o);
+        row_norm(v, de, l16, a.eps, gs, gs + KA, o);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int ch = (k * 16 + l16) * 8;
@@ -239,60 +258,64 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     __syncthreads();
 
     // ---- MLP, HC hidden columns at a time ----------------------------------------------------------------------------------
+    // With two hidden tiles there is one barrier a tile: a wavefront that is through with fc2 of one makes its block of the next, its GELU
+    // beside the others' products.
     clear2();
     const int nchunk = (hid + HC - 1) / HC;
     const bool more = (a.next >> g) & 1;
     // the next block's Q/K/V: three segments of nb column blocks, NW blocks at a time
     const int nb = (kin + 31) / 32;
     auto qkv = [&](int p) { return stream(a.wq, (p / nb * a.segq + p % nb) * a.kbq, more && p < 3 * nb ? de : 0); };
+    // (Every wavefront multiplies at every turn, whether it has columns or not, and nothing else stands around the products: where the
+    // operands under way come out of a branch they are moved, and a move waits for them.)
+    auto fc1 = [&](int hc) { return stream(w1, hc * step1, hid - hc * HC > w * 32 ? de : 0); };
+    auto fc2 = [&](int hc) { return stream(w2, hc * 2 * NW, con ? min(HC, hid - hc * HC) : 0); };
+    Stream cur = fc1(0);
     for (int hc = 0; hc < nchunk; ++hc) {
+        const bool last = hc + 1 == nchunk;
         const int hb = hc * NW + w;                      // 32-column block of the hidden layer
-        const bool hon = hb * 32 < hid, last = hc + 1 == nchunk;
-        const int K2 = min(HC, hid - hc * HC);
-        const Stream ahead = last ? qkv(w) : fc1(hb + NW), s2 = stream(a.w2, w * a.kb2 + hc * 2 * NW, con ? K2 : 0), next = con ? s2 : ahead;
+        const Stream s2 = fc2(hc), next = last ? qkv(w) : fc1(hc + 1);
+        bf16_t* tile = Hs + (TWO ? hc & 1 : 0) * (BM * PH);
         f32x16_t acc1[R];
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc1[r][v] = 0.f;
-        if (CST) constants(cst, a.b1, hb * 32, hid);
-        if (hon) walk(acc1, fc1(hb), next, As, PA);
-        else start(next);
-        uint2 ho[4][R];
+        cst = columns(b1, hb * 32, hid);
+        walk(acc1, cur, s2, As, PA);
+        cur = next;
+        if (!TWO && hc > 0) __syncthreads();             // the previous columns have been read
+        line[l32] = cst;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int ch = hb * 32 + 8 * q + 4 * lhi;
-            float4 h = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (CST) h = cst[q];
-            else if (ch < hid) h = *(const float4*)(a.b1 + ch);
+            const float4 h = bias_of(q);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                ho[q][r] = make_uint2(0, 0);
+                uint2 o = make_uint2(0, 0);
                 if (ch < hid)
-                    ho[q][r] = gelu_bf16x4(acc1[r][4 * q] + h.x, acc1[r][4 * q + 1] + h.y, acc1[r][4 * q + 2] + h.z, acc1[r][4 * q + 3] + h.w);
+                    o = gelu_bf16x4(acc1[r][4 * q] + h.x, acc1[r][4 * q + 1] + h.y, acc1[r][4 * q + 2] + h.z, acc1[r][4 * q + 3] + h.w);
+                *(uint2*)(tile + (r * 32 + l32) * PH + w * 32 + 8 * q + 4 * lhi) = o;
             }
         }
-        __syncthreads();                                 // the previous columns have been read
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int r = 0; r < R; ++r) *(uint2*)(Hs + (r * 32 + l32) * PH + w * 32 + 8 * q + 4 * lhi) = ho[q][r];
+        __syncthreads();
         if (last) {
             // the residual rows of the last sum (this thread wrote them itself after the projection): every wavefront is past its
             // last read of the activation tile
             uint4 xr[NI][4];
             x_rows(xr);
             to_tile(xr, As, PA, de);
-            if (CST) constants(cst, a.b2, w * 32, de);
+            __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0), here and not behind the branch, where it would be one for the operands under way
         }
-        __syncthreads();
-        if (con) walk(acc2, s2, ahead, Hs, PH);
+        walk(acc2, s2, next, tile, PH);
     }
-    add_columns(cst, a.b2, As, PA);
+    cst = columns(b2, w * 32, de);
+    __syncthreads();
+    add_columns(cst, As, PA);
     if (more)
         for (int i = tid; i < de; i += 64 * NW) {
             gs[i] = a.g1[i];
-            gs[VIT_K_MAX + i] = a.be1[i];
+            gs[KA + i] = a.be1[i];
         }
     __syncthreads();
     // ---- x to memory, the next block's LN1 in place -------------------------------------------------------------------------
@@ -307,12 +330,12 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
             const int ch = (k * 16 + l16) * 8;
             if (ch < de) {
                 const uint4 q = *(const uint4*)(row + ch);
-                if (live[i]) *(uint4*)(a.x + xoff[i] + ch) = q;
+                x_out(i, k, q);
                 unpack8(q, v[k]);
             }
         }
         if (!more) continue;
-        row_norm(v, de, l16, a.eps, gs, gs + VIT_K_MAX, o);
+        row_norm(v, de, l16, a.eps, gs, gs + KA, o);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int ch = (k * 16 + l16) * 8;
@@ -321,26 +344,24 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     }
     if (!more) return;
     __syncthreads();
-    bf16_t* qrow[R];
-    bool in[R];
+    const bf16_t* q0 = a.qkv + (int64_t)(slot0 + first) * a.q_ss;
+    uint32_t qoff[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int m = grow0 + r * 32 + l32;
-        in[r] = m < rows_g;
-        const int mm = in[r] ? m : grow0, sl = mm / a.rows;
-        qrow[r] = a.qkv + (int64_t)(slot0 + sl) * a.q_ss + (int64_t)(mm - sl * a.rows) * a.q_ld;
+        const int m = grow0 + r * 32 + l32, sl = m / a.rows;
+        qoff[r] = m < rows_g ? (uint32_t)(((sl - first) * a.q_ss + (int64_t)(m - sl * a.rows) * a.q_ld + 8 * lhi) * 2) : OOB;
     }
     for (int p = w; p < 3 * nb; p += NW) {
         const int seg = p / nb, n0 = (p - seg * nb) * 32;
         clear2();
-        float4 h[4];
-        if (CST) constants(h, a.bq + (int64_t)seg * a.q_ld, n0, kin);
+        cst = columns(a.bq + (int64_t)seg * a.q_ld, n0, kin);
         walk(acc2, qkv(p), qkv(p + NW), As, PA);
-        if (!CST) constants(h, a.bq + (int64_t)seg * a.q_ld, n0, kin);
-        const int64_t so = (int64_t)seg * a.q_seg;
+        line[l32] = cst;
+        const __amdgpu_buffer_rsrc_t rq = window(q0, (int64_t)seg * a.q_seg + n0);
 #pragma unroll
         for (int q = 0; q < 4; q += 2) {
-            const int n = n0 + 8 * q + 8 * lhi;
+            const bool in = n0 + 8 * q + 8 * lhi < kin;
+            const float4 h[2] = {bias_of(q), bias_of(q + 1)};
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 uint32_t lo[2], hi[2];
@@ -348,13 +369,13 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
                 for (int e = 0; e < 2; ++e) {
                     const f32x16_t& t = acc2[r];
                     const int b = 4 * (q + e);
-                    lo[e] = f2bf2(t[b] + h[q + e].x, t[b + 1] + h[q + e].y);
-                    hi[e] = f2bf2(t[b + 2] + h[q + e].z, t[b + 3] + h[q + e].w);
+                    lo[e] = f2bf2(t[b] + h[e].x, t[b + 1] + h[e].y);
+                    hi[e] = f2bf2(t[b + 2] + h[e].z, t[b + 3] + h[e].w);
                 }
                 // channels 8 q .. + 7 to the lower half's lane, the next eight to the upper half's
                 const auto a0 = __builtin_amdgcn_permlane32_swap(lo[0], lo[1], false, false);
                 const auto a1 = __builtin_amdgcn_permlane32_swap(hi[0], hi[1], false, false);
-                if (in[r] && n < kin) *(uint4*)(qrow[r] + so + n) = make_uint4(a0[0], a1[0], a0[1], a1[1]);
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{a0[0], a1[0], a0[1], a1[1]}, rq, (int)(in ? qoff[r] + 16 * q : OOB), 0, 0);
             }
         }
     }
@@ -405,6 +426,7 @@ int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {
     for (int t = 0; t < a.gt.T; ++t) {
         if (a.gt.k_out[t] <= 0) continue;
         dmax = a.gt.k_out[t] > dmax ? a.gt.k_out[t] : dmax;
+        dmax = a.gt.k_in[t] > dmax ? a.gt.k_in[t] : dmax;
         if (a.gt.k_in[t] > VIT_K_MAX || a.gt.k_out[t] > VIT_K_MAX || a.gt.row[t] <= 0 || (a.gt.k_in[t] % 16) || (a.gt.k_out[t] % 8) ||
             (a.gt.row[t] % 8))
             return DS_EUNSUPPORTED;
@@ -414,5 +436,5 @@ int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {
     const bool two = tiles(64) >= 224 || (a.crowd > 1 && tiles(64) * a.crowd >= (dmax > 384 ? 270 : 300));
     if (dmax > 384)                                      // 13 column blocks: 128 registers per lane, at most 64 rows
         return two ? launch<13, 2, 4>(a, tiles(64), s) : launch<13, 1, 4>(a, tiles(32), s);
-    return two ? launch<12, 2, 4>(a, tiles(64), s) : launch<12, 1, 8>(a, tiles(32), s);
+    return two ? launch<12, 2, 6>(a, tiles(64), s) : launch<12, 1, 8>(a, tiles(32), s);
 }
