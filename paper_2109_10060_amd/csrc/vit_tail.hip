@@ -25,8 +25,8 @@
 // everything asked for before it.  What that took: LDS reads issued a step ahead (the compiler sank them behind the products), no branch
 // that gives out the operands under way (they were moved there, and a move waits for them), requests for rows and constants and stores
 // without branches, six operands in flight for four, two hidden tiles and so one barrier a tile for two.  us a pass, before -> now: 256
-// images of DS-ViT 2322 -> 2217, on another card 2444 -> 2322; 60 to 100 images 1074 -> 988; 256 images of DS-ViT++ (13 wavefronts: one
-// hidden tile, four in flight) 3522 -> 3512.  Eight operands in flight 2350 for 2322 at 256 images.  Q/K/V blocks dealt out as wavefronts
+// images of DS-ViT 2322 -> 2217, on another card 2444 -> 2322; 60 to 100 images 1074 -> 975; 256 images of DS-ViT++ (13 wavefronts: one
+// hidden tile, four in flight) 3522 -> 3440.  Eight operands in flight 2350 for 2322 at 256 images.  Q/K/V blocks dealt out as wavefronts
 // come free instead of in turn: no change.
 //
 // Sums run in the order of gemm_kernel's and layernorm16_kernel's, so the results are the same bits.
@@ -259,7 +259,8 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
 
     // ---- MLP, HC hidden columns at a time ----------------------------------------------------------------------------------
     // With two hidden tiles there is one barrier a tile: a wavefront that is through with fc2 of one makes its block of the next, its GELU
-    // beside the others' products.
+    // beside the others' products.  Of a SIMD's three wavefronts the second makes its block first (late): 60 to 100 images of DS-ViT 985 -> 975
+    // us a pass, 256 images 2281 -> 2276.
     clear2();
     const int nchunk = (hid + HC - 1) / HC;
     const bool more = (a.next >> g) & 1;
@@ -270,11 +271,21 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     // operands under way come out of a branch they are moved, and a move waits for them.)
     auto fc1 = [&](int hc) { return stream(w1, hc * step1, hid - hc * HC > w * 32 ? de : 0); };
     auto fc2 = [&](int hc) { return stream(w2, hc * 2 * NW, con ? min(HC, hid - hc * HC) : 0); };
+    const bool late = TWO && w >> 2 == 1;
+    auto residual = [&]() {
+        // the residual rows of the last sum (this thread wrote them itself after the projection): every wavefront is past its
+        // last read of the activation tile
+        uint4 xr[NI][4];
+        x_rows(xr);
+        to_tile(xr, As, PA, de);
+        __builtin_amdgcn_s_waitcnt(0x0f70);              // vmcnt(0), here and not behind the branch, where it would be one for the operands under way
+    };
     Stream cur = fc1(0);
     for (int hc = 0; hc < nchunk; ++hc) {
         const bool last = hc + 1 == nchunk;
         const int hb = hc * NW + w;                      // 32-column block of the hidden layer
-        const Stream s2 = fc2(hc), next = last ? qkv(w) : fc1(hc + 1);
+        const int two = late ? hc - 1 : hc;              // whose fc2
+        const Stream ahead = last ? (late ? fc2(hc) : qkv(w)) : fc1(hc + 1), s2 = two < 0 ? ahead : fc2(two);
         bf16_t* tile = Hs + (TWO ? hc & 1 : 0) * (BM * PH);
         f32x16_t acc1[R];
 #pragma unroll
@@ -283,7 +294,7 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
             for (int v = 0; v < 16; ++v) acc1[r][v] = 0.f;
         cst = columns(b1, hb * 32, hid);
         walk(acc1, cur, s2, As, PA);
-        cur = next;
+        cur = ahead;
         if (!TWO && hc > 0) __syncthreads();             // the previous columns have been read
         line[l32] = cst;
 #pragma unroll
@@ -298,16 +309,16 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
                 *(uint2*)(tile + (r * 32 + l32) * PH + w * 32 + 8 * q + 4 * lhi) = o;
             }
         }
-        __syncthreads();
-        if (last) {
-            // the residual rows of the last sum (this thread wrote them itself after the projection): every wavefront is past its
-            // last read of the activation tile
-            uint4 xr[NI][4];
-            x_rows(xr);
-            to_tile(xr, As, PA, de);
-            __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0), here and not behind the branch, where it would be one for the operands under way
+        if (!late) {
+            __syncthreads();
+            if (last) residual();
         }
-        walk(acc2, s2, next, tile, PH);
+        if (two >= 0) walk(acc2, s2, ahead, Hs + (TWO ? two & 1 : 0) * (BM * PH), PH);
+        if (late) __syncthreads();
+    }
+    if (late) {
+        residual();
+        walk(acc2, cur, qkv(w), Hs + ((nchunk - 1) & 1) * (BM * PH), PH);
     }
     cst = columns(b2, w * 32, de);
     __syncthreads();
