@@ -695,3 +695,47 @@ def test_resnet_gate_scores_do_not_depend_on_the_neighbours(gpu_lib, image, B, s
         assert int((lo > 0).sum()) > B // 2
         changed = sum(int((~at_least(lo, order)).sum()) + int(at_least(hi, order).sum()) for order in orders)
         assert changed == 0, channel
+
+
+# hidden layers of one column piece, of exactly a tile of 384 or 416 columns, a few columns more, two tiles and the most there are, behind
+# 32 and 64 rows a workgroup and 12 and 13 column blocks: as above
+@pytest.mark.parametrize("B", [120, 1000])
+@pytest.mark.parametrize("embed", [384, 416])
+def test_vit_hidden_tiles(gpu_lib, embed, B):
+    if embed == 384:
+        arch = WL.vit_arch(image=64, depth=2)                # 17 tokens
+        routes = [(384, 6, 8), (384, 6, 384), (264, 4, 392), (192, 3, 768), (384, 5, 776), (384, 6, 1536)]
+    else:
+        arch = WL.vit_arch(image=64, embed=416, heads=8, head_dim=48, mlp=1664, depth=2)
+        routes = [(392, 7, 8), (416, 8, 416), (416, 8, 424), (400, 8, 832), (416, 5, 840), (416, 8, 1664)]
+    arch["routes"], arch["T"] = np.array(routes, np.int32), len(routes)
+    net = gpu_lib.build_vit(arch, WL.vit_params(arch, 10), DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(B)
+    imgs = torch.randn((B, 3, arch["image"], arch["image"]), generator=gen, device=DEV).to(torch.bfloat16)
+    over = (torch.arange(B, device=DEV, dtype=torch.int32) * 5 % arch["T"])[None].contiguous()
+    got, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
+    net.c_struct.n_params -= 4 * arch["depth"]
+    want, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
+    assert torch.isfinite(want).all() and torch.equal(got, want)
+
+
+# heads over two workgroups, four query tiles and the rest: the largest number of heads that are (128) and one sample more, as many
+# wavefronts as a workgroup of one half has and one more
+@pytest.mark.parametrize("dh,H,N,B", [(48, 8, 197, 16), (48, 8, 197, 17), (64, 2, 224, 3), (32, 4, 128, 32), (32, 4, 129, 32), (32, 4, 129, 33)])
+def test_attention_in_two_workgroups(gpu_lib, dh, H, N, B):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(dh + B)
+    D = H * dh
+    x = torch.randn((B, N, D), generator=gen, device=DEV).to(torch.bfloat16)
+    w = (torch.randn((4, D, D), generator=gen, device=DEV) * 0.06).to(torch.bfloat16)
+    bias = 0.1 * torch.randn((4, D), generator=gen, device=DEV)
+    perm, inv, off = gpu_lib.ds_route_bucket(torch.zeros(B, dtype=torch.int32, device=DEV), 1)
+    g = gpu_lib.make_groups(off, perm, [D], [D])
+    y = torch.empty_like(x)
+    gpu_lib.ds_sliced_mhsa(x, w[:3].contiguous(), bias[:3].contiguous(), w[3].contiguous(), bias[3].contiguous(), H, dh, g, residual=x, y=y)
+    bf = lambda a: a.astype(np.float32)
+    xh, wh, bh, yh = host(x), host(w), host(bias), host(y)
+    for b in sorted({0, 1, B // 2, B - 1}):
+        att = O.sliced_mhsa(bf(xh[b]), wh[0], bh[0], wh[1], bh[1], wh[2], bh[2], wh[3], bh[3], H, dh, store="bf16")
+        assert relerr(yh[b], O.bf16_round(xh[b] + att)) < TOL_BF16, b
