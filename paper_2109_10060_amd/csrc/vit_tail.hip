@@ -421,9 +421,10 @@ bool ds_vit_tail_qkv(const GroupTable& gt, int32_t B, int32_t rows, int32_t crow
 
 // Rows per workgroup.  A workgroup streams all weights of the block whatever its rows (2.7 MB at full width), and when all compute
 // units do so at once the L2s give each about 30 bytes a clock, half of what 64 rows could use; so more rows each are better --
-// as long as there is a workgroup for nearly every compute unit and the last ones end together.  Us a pass of DS-ViT, 32 / 64 rows: 56
-// images (219 tiles of 64 rows) 1012 / 1036, 60 images (231) 1074 / 1039, 96 images 1421 / 1251, 256 images 3135 / 2530; DS-ViT++ 64 images
-// (204) 1417 / 1493, 96 images (303) 1893 / 1718: the line is at 224.  96 rows leave no LDS for the LayerNorm weights: 64 images 1267 us against 1046
+// as long as there is a workgroup for nearly every compute unit and the last ones end together.  Us a pass of DS-ViT, 32 / 64 rows: 57
+// images (221 tiles of 64 rows) 909 / 962, 60 images (231) 932 / 965, 64 images (244) 939 / 977, 66 images (250) 1022 / 982, 71 images
+// (265) 1058 / 996, 80 images (290) 1226 / 1033; DS-ViT++ 72 images (229) 1454 / 1526, 76 images (241) 1589 / 1587, 82 images (260) 1636 / 1624,
+// 86 images (272) 1797 / 1646: the line is at 248.  96 rows leave no LDS for the LayerNorm weights: 64 images 1267 us against 1046
 // with 64 rows, 192 images 2016 against 2039, 256 images 2587 against 2530 on one card and 2492 against 2485 on another.  (See
 // profiles/dispatch_choices.txt.)  Parts of a batch that run side by side fill the compute units together, if not
 // evenly.  Us a pass, 32 / 64 rows, two parts and four (tiles of 64 rows in all of them): DS-ViT 64 images (260, 260) 941 / 979 and 954 / 1019, 72
@@ -444,7 +445,7 @@ int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {
     }
     const int64_t groups = B < a.gt.T ? B : a.gt.T, n = (int64_t)B * a.rows;
     auto tiles = [&](int bm) { return (n - groups) / bm + groups; };
-    const bool two = tiles(64) >= 224 || (a.crowd > 1 && tiles(64) * a.crowd >= (dmax > 384 ? 270 : 300));
+    const bool two = tiles(64) >= 248 || (a.crowd > 1 && tiles(64) * a.crowd >= (dmax > 384 ? 270 : 300));
     if (dmax > 384)                                      // 13 column blocks: 128 registers per lane, at most 64 rows
         return two ? launch<13, 2, 4>(a, tiles(64), s) : launch<13, 1, 4>(a, tiles(32), s);
     return two ? launch<12, 2, 6>(a, tiles(64), s) : launch<12, 1, 8>(a, tiles(32), s);
