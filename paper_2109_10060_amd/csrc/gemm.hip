@@ -19,8 +19,8 @@
 // stores and reads are bank-conflict free); the next slab's global loads are issued into
 // registers before the current slab's matrix instructions and stored to LDS after them, and 5-6 resident
 // workgroups per compute unit hide each other's round trips.  The epilogue (split batch-norm scale and
-// shift or bias, residual, ReLU/GELU, bf16 rounding) re-reads the accumulators through LDS so that every lane
-// stores 4 consecutive channels of one row.
+// shift or bias, residual, ReLU/GELU, bf16 rounding) passes a wavefront's tile through LDS as bf16, and it leaves as
+// 16-byte pieces, eight lanes a row.
 //
 // Work items are (m-tile, n-tile) pairs with the n-tile fastest; the linear block
 // index is dealt round-robin to the 8 XCDs by the hardware, so each XCD is given
