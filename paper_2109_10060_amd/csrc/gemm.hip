@@ -72,9 +72,19 @@ __device__ __forceinline__ unsigned layer_of(const GemmPair& p) { return blockId
 __device__ __forceinline__ const GemmArgs& args_of(const GemmArgs& a, unsigned) { return a; }
 __device__ __forceinline__ const GemmArgs& args_of(const GemmPair& p, unsigned q) { return p.p[q]; }
 
+// Wavefronts a SIMD that the registers have to leave room for.  The 32-deep slabs live on residency: left to itself the convolution form takes
+// 104 registers, four wavefronts, where six fit in 80 without scratch (256 -> 512 channels, 1x1/2 on 56x56, 256 images 109.8 -> 95.2 us, 64
+// images 28.7 -> 24.9).  The 128-column tile of the same slabs measures the same with three and with four (256 -> 128 channels, 142.3 and 142.7).
+constexpr int residency(int tiles, int bk, int shares, bool conv, bool res) {
+    if (shares > 1 || tiles == 4) return 1;
+    if (bk == 128) return 3;
+    if (bk == 32) return res ? (conv ? 1 : 5) : 6;
+    return conv ? 1 : 5;
+}
+
 // KS: shares of the reduction, four wavefronts each; a share takes every KS-th slab
 template <int WROWS, int WCOLS, int WMT, int WNT, int BK, int KS, bool CONV, bool HASR, class Args = GemmArgs>
-__global__ __launch_bounds__(NT * KS, KS > 1 ? 1 : BK == 128 ? 3 : (WMT * WNT == 2 && !CONV) ? (BK == 32 ? (HASR ? 5 : 6) : 5) : 1) void gemm_kernel(const Args args, const int ny0, const int max_mtiles0) {
+__global__ __launch_bounds__(NT * KS, residency(WMT * WNT, BK, KS, CONV, HASR)) void gemm_kernel(const Args args, const int ny0, const int max_mtiles0) {
     constexpr bool PAIR = std::is_same<Args, GemmPair>::value;
     const unsigned q = layer_of(args);
     const GemmArgs& a = args_of(args, q);
