@@ -82,8 +82,9 @@ constexpr int residency(int tiles, int bk, int shares, bool conv, bool res) {
     return conv ? 1 : 5;
 }
 
-// KS: shares of the reduction, four wavefronts each; a share takes every KS-th slab
-template <int WROWS, int WCOLS, int WMT, int WNT, int BK, int KS, bool CONV, bool HASR, class Args = GemmArgs>
+// KS: shares of the reduction, four wavefronts each; a share takes every KS-th slab.  F32: fp32 results, of linear layers (several shares
+// look at the argument instead: their way out is the same but for the store)
+template <int WROWS, int WCOLS, int WMT, int WNT, int BK, int KS, bool CONV, bool HASR, bool F32, class Args = GemmArgs>
 __global__ __launch_bounds__(NT * KS, residency(WMT * WNT, BK, KS, CONV, HASR)) void gemm_kernel(const Args args, const int ny0, const int max_mtiles0) {
     constexpr bool PAIR = std::is_same<Args, GemmPair>::value;
     const unsigned q = layer_of(args);
@@ -120,12 +121,13 @@ __global__ __launch_bounds__(NT * KS, residency(WMT * WNT, BK, KS, CONV, HASR)) 
     int64_t a_ss = a.a_sample_stride, c_ss = a.c_sample_stride, r_ss = a.r_sample_stride, c_segs = a.c_seg_stride;
     int64_t w_ld = a.w_ld, w_tap = a.w_tap_stride, w_seg = a.w_seg_stride;
     int a_ld = a.a_ld, c_ld = a.c_ld, r_ld = a.r_ld, c_row0 = a.c_row0, r_use = a.r_use_index;
-    int n_seg = a.n_seg, tab_ld = a.tab_ld, tab_seg = a.tab_seg_stride, rows = a.rows, act = a.act, out_f32 = a.out_f32;
+    int n_seg = a.n_seg, tab_ld = a.tab_ld, tab_seg = a.tab_seg_stride, rows = a.rows, act = a.act, out_f32 = KS > 1 && !CONV ? a.out_f32 : 0;
     int KH = a.K, KW = a.Kw, H = a.H, W = a.W, Wo = a.Wo, sy = a.stride, sx = a.stride_w, pad = a.pad;
     TileSource source(a);
     source.hold();
     ds_hold(ny, max_mtiles, A, Wt, R, C, scale, shift, a_index, c_index, a_ss, c_ss, r_ss, c_segs, w_ld, w_tap, w_seg, a_ld, c_ld, r_ld, c_row0, r_use,
-            n_seg, tab_ld, tab_seg, rows, act, out_f32, KH, KW);
+            n_seg, tab_ld, tab_seg, rows, act, KH, KW);
+    if constexpr (KS > 1 && !CONV) ds_hold(out_f32);
     if constexpr (CONV) ds_hold(H, W, Wo, sy, sx, pad);
     const int j = (int)(block >> 3);
     const int jm = j / ny, y = j - jm * ny;
@@ -298,15 +300,24 @@ __global__ __launch_bounds__(NT * KS, residency(WMT * WNT, BK, KS, CONV, HASR)) 
     const int srow = lane >> 3, ncol8 = n0 + wn * COLS + (lane & 7) * 8;
     const int ncol4 = n0 + (threadIdx.x & 15) * 4;           // (several shares: one column tile)
     static_assert(COLS == 64, "eight 16-byte pieces a row of the stage");
+    static_assert(!F32 || (KS == 1 && !CONV), "fp32 results of linear layers, one share");
     using Piece = typename std::conditional<KS == 1, uint4, uint2>::type;
     Piece rres[HASR ? NE : 1];
     auto fetch_residual = [&](int tm) {
 #pragma unroll
         for (int i = 0; i < NE; ++i) {
             const int r = KS == 1 ? wm * WMT * 32 + tm * 32 + srow + 8 * i : ((int)threadIdx.x >> 4) + i * 16 * KS;
-            const int n = KS == 1 ? ncol8 : ncol4;
             Piece t = {};
-            if (n < k_out && rowC[r] >= 0) t = *(const Piece*)(R + rowR[r] + n);
+            if constexpr (F32) {                             // channels 4 (lane % 8) .. + 3 of either half of the columns
+                const int n = n0 + wn * COLS + (lane & 7) * 4;
+                if (rowC[r] >= 0) {
+                    if (n < k_out) *(uint2*)&t.x = *(const uint2*)(R + rowR[r] + n);
+                    if (n + 32 < k_out) *(uint2*)&t.z = *(const uint2*)(R + rowR[r] + n + 32);
+                }
+            } else {
+                const int n = KS == 1 ? ncol8 : ncol4;
+                if (n < k_out && rowC[r] >= 0) t = *(const Piece*)(R + rowR[r] + n);
+            }
             rres[i] = t;
         }
     };
@@ -410,6 +421,51 @@ __global__ __launch_bounds__(NT * KS, residency(WMT * WNT, BK, KS, CONV, HASR)) 
         const int row0 = wm * WMT * 32 + tm * 32;
         if constexpr (HASR) {
             if (!RES_EARLY || tm > 0) fetch_residual(tm);
+        }
+        if constexpr (F32) {
+            // fp32 results go through the stage 32 columns at a time and leave as whole lines, eight lanes a row; a residual is added on the
+            // way out.  Stored by the lanes that hold the sums, 16 bytes on each of 32 rows at once -> here, us: 64 images of 197 tokens,
+            // 192 -> 768 channels 14.4 -> 11.7, 768 -> 3072 with residual 75.2 -> 68.3; 256 images, 384 -> 1536 100.8 -> 93.4, with residual 136
+            // -> 120.  Instances of their own: decided by the argument, this way out spills in the bf16 kernels (the last of these in bf16
+            // 88 -> 96).
+            constexpr int F_LD = ST_LD / 2;
+            float* sf = (float*)st;
+            with_act(act, [&](auto actc) {
+                constexpr int ACT = decltype(actc)::value;
+#pragma unroll
+                for (int tn = 0; tn < WNT; ++tn) {
+                    const f32x16_t& t = acc[tm][tn];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int ch = 8 * q + 4 * lhi;
+                        const float4 s4 = *(const float4*)(scl + wn * COLS + tn * 32 + ch), h4 = *(const float4*)(scl + BN + wn * COLS + tn * 32 + ch);
+                        float val[4] = {t[4 * q] * s4.x + h4.x, t[4 * q + 1] * s4.y + h4.y, t[4 * q + 2] * s4.z + h4.z, t[4 * q + 3] * s4.w + h4.w};
+                        if constexpr (!HASR) activate<ACT>(val);
+                        *(float4*)(sf + l32 * F_LD + ch) = make_float4(val[0], val[1], val[2], val[3]);
+                    }
+                    wave_sync();
+                    const int n = n0 + wn * COLS + tn * 32 + (lane & 7) * 4;
+                    if (n < k_out) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int row = srow + 8 * i;
+                            const long long coff = rowC[row0 + row];
+                            float4 v = *(const float4*)(sf + row * F_LD + (lane & 7) * 4);
+                            if constexpr (HASR) {
+                                float val[4] = {v.x, v.y, v.z, v.w};
+                                add_residual(val, tn ? make_uint2(rres[i].z, rres[i].w) : make_uint2(rres[i].x, rres[i].y));
+                                activate<ACT>(val);
+                                v = make_float4(val[0], val[1], val[2], val[3]);
+                            }
+                            if (coff >= 0) *(float4*)((float*)C + coff + n) = v;
+                        }
+                    }
+                    wave_sync();
+                }
+            });
+            continue;
+        }
+        if constexpr (HASR) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) *(Piece*)(st + (srow + 8 * i) * ST_LD + (lane & 7) * 8) = rres[i];
             wave_sync();
@@ -426,17 +482,9 @@ __global__ __launch_bounds__(NT * KS, residency(WMT * WNT, BK, KS, CONV, HASR)) 
                     float val[4] = {t[4 * q] * s4.x + h4.x, t[4 * q + 1] * s4.y + h4.y, t[4 * q + 2] * s4.z + h4.z, t[4 * q + 3] * s4.w + h4.w};
                     uint2* p = (uint2*)(st + l32 * ST_LD + ch);
                     if constexpr (HASR) add_residual(val, *p);
-                    if (out_f32) {
-                        const long long coff = rowC[row0 + l32];
-                        const int n = n0 + wn * COLS + ch;
-                        activate<ACT>(val);
-                        if (coff >= 0 && n < k_out) *(float4*)((float*)C + coff + n) = make_float4(val[0], val[1], val[2], val[3]);
-                    } else {
-                        *p = activate_bf16<ACT>(val);
-                    }
+                    *p = activate_bf16<ACT>(val);
                 }
         });
-        if (out_f32) continue;
         wave_sync();
         if (ncol8 < k_out) {
 #pragma unroll
@@ -449,10 +497,13 @@ __global__ __launch_bounds__(NT * KS, residency(WMT * WNT, BK, KS, CONV, HASR)) 
     }
 }
 
-template <int WROWS, int WCOLS, int WMT, int WNT, int BK, int KS, bool CONV, bool HASR>
+template <int WROWS, int WCOLS, int WMT, int WNT, int BK, int KS, bool CONV, bool HASR, bool F32 = false>
 int32_t launch(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
     using TL = Tile<WROWS, WCOLS, WMT, WNT, BK, KS>;
-    auto kern = gemm_kernel<WROWS, WCOLS, WMT, WNT, BK, KS, CONV, HASR>;
+    if constexpr (KS == 1 && !CONV && !F32) {
+        if (a.out_f32) return launch<WROWS, WCOLS, WMT, WNT, BK, KS, CONV, HASR, true>(a, max_mtiles, max_kout, s);
+    }
+    auto kern = gemm_kernel<WROWS, WCOLS, WMT, WNT, BK, KS, CONV, HASR, F32>;
     {
         const int32_t rc = ds_reserve_lds((const void*)kern, TL::SMEM, "sliced gemm");
         if (rc) return rc;
@@ -468,7 +519,7 @@ int32_t launch(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStrea
 template <int BK, int KS>
 int32_t launch_pair(GemmPair& p, const int32_t* kout, hipStream_t s) {
     using TL = Tile<4, 1, 1, 2, BK, KS>;
-    auto kern = gemm_kernel<4, 1, 1, 2, BK, KS, true, false, GemmPair>;
+    auto kern = gemm_kernel<4, 1, 1, 2, BK, KS, true, false, false, GemmPair>;
     {
         const int32_t rc = ds_reserve_lds((const void*)kern, TL::SMEM, "sliced gemm");
         if (rc) return rc;

@@ -739,3 +739,38 @@ def test_attention_in_two_workgroups(gpu_lib, dh, H, N, B):
     for b in sorted({0, 1, B // 2, B - 1}):
         att = O.sliced_mhsa(bf(xh[b]), wh[0], bh[0], wh[1], bh[1], wh[2], bh[2], wh[3], bh[3], H, dh, store="bf16")
         assert relerr(yh[b], O.bf16_round(xh[b] + att)) < TOL_BF16, b
+
+
+# fp32 results with and without a residual and GELU, on every tile of the grouped GEMM: slices that end inside a tile's 64 columns and inside
+# either half of them, ragged last rows.  fp32 sums of up to 776 products: at most 776 x 2^-24 = 4.6e-5 of the sum of their magnitudes
+@pytest.mark.parametrize("res,act", [(False, 0), (True, 0), (False, 2), (True, 2), (True, 1)])
+@pytest.mark.parametrize("B,rows,k_in,k_out", [
+    (20, 131, (200, 72, 8), (488, 104, 40)),                         # 32-deep slabs
+    (70, 131, (392, 136), (504, 72)),                                # 64-deep slabs
+    (20, 131, (328, 40), (488, 104)),                                # two shares of the reduction
+    (20, 131, (584, 8), (488, 72)),                                  # four
+    (70, 131, (520, 264), (504, 40)),                                # 128-deep slabs
+    (1960, 197, (136, 40), (128, 72)),                               # 128 columns, 32-deep slabs
+    (134, 197, (776, 40), (1240, 72)),                               # 128 columns, 64-deep slabs
+    (1, 5, (72, 8), (40, 8))])                                       # a few rows
+def test_sliced_linear_fp32_results(gpu_lib, B, rows, k_in, k_out, res, act):
+    T, K, N = len(k_in), max(k_in), max(k_out)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(B + K)
+    rn = lambda *s: torch.randn(s, generator=gen, device=DEV)  # noqa: E731
+    x, w, bias = rn(B, rows, K).to(torch.bfloat16), (rn(N, K) * K ** -0.5).to(torch.bfloat16), rn(N)
+    r = rn(B, rows, N).to(torch.bfloat16) if res else None
+    route = torch.arange(B, device=DEV, dtype=torch.int32) % T
+    perm, inv, off = gpu_lib.ds_route_bucket(route, T)
+    y = torch.full((B, rows, N), float("nan"), device=DEV)
+    gpu_lib.ds_sliced_linear(x, w, bias, gpu_lib.make_groups(off, perm, k_in, k_out), act=act, residual=r, y=y)
+    inside = torch.arange(N, device=DEV)[None] < torch.tensor(k_out, device=DEV)[route.long()][:, None]
+    assert torch.equal(torch.isfinite(y), inside[:, None, :].expand_as(y))
+    wh, bh = host(w), host(bias)
+    for b in sorted({0, min(1, B - 1), B // 2, B - 1}):
+        ki, ko = k_in[b % T], k_out[b % T]
+        want = host(x[b])[:, :ki] @ wh[:ko, :ki].T + bh[:ko]
+        if res:
+            want = want + host(r[b])[:, :ko]
+        want = O.gelu(want) if act == 2 else np.maximum(want, 0.0) if act == 1 else want
+        assert relerr(host(y[b])[:, :ko], want) < 1e-4, b

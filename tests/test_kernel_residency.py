@@ -9,10 +9,15 @@ def waves(kernel):
     return min(8, 512 // ((kernel[".vgpr_count"] + 7) // 8 * 8))
 
 
-# the grouped GEMM on 64 columns and 32-deep slabs: six without a residual, linear layers, strided ones and pairs alike
+GEMM = re.compile(r"11gemm_kernelILi(.)ELi.ELi.ELi.ELi(\d+)ELi(.)ELb(.)ELb(.)ELb(.)E.*Gemm(Args|Pair)")
+
+
+# the grouped GEMM on 64 columns and 32-deep slabs: six without a residual, linear layers, strided ones and pairs, bf16 and fp32 results
 def test_short_slabs_of_the_grouped_gemm():
-    form = re.compile(r"11gemm_kernelILi4ELi1ELi1ELi2ELi32ELi1ELb(.)ELb0E.*Gemm(Args|Pair)")
-    found = {m.groups(): k for m, k in ((form.search(n), k) for n, k in kernels().items()) if m}
-    assert set(found) == {("0", "Args"), ("1", "Args"), ("1", "Pair")}
+    found = {m.groups(): k for m, k in ((GEMM.search(n), k) for n, k in kernels().items()) if m}
+    short = {g[3:]: k for g, k in found.items() if g[:3] == ("4", "32", "1") and g[4] == "0"}
+    assert set(short) == {("0", "0", "0", "Args"), ("0", "0", "1", "Args"), ("1", "0", "0", "Args"), ("1", "0", "0", "Pair")}
+    for name, k in short.items():
+        assert waves(k) >= 6, name
     for name, k in found.items():
-        assert waves(k) >= 6 and k[".private_segment_fixed_size"] == 0, name
+        assert k[".private_segment_fixed_size"] == 0, name
