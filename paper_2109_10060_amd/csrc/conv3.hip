@@ -55,16 +55,16 @@ __global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const 
 
     const GroupLanes lanes(a.gt);
     const bf16_t *A = a.A, *Wt = a.Wt, *res = a.R;
-    void* C = a.C;
+    bf16_t* C = (bf16_t*)a.C;
     const float *scale = a.scale, *shift = a.shift;
     const int32_t *a_index = a.a_index, *c_index = a.c_index;
     int64_t a_ss = a.a_sample_stride, c_ss = a.c_sample_stride, r_ss = a.r_sample_stride;
     int a_ld = a.a_ld, c_ld = a.c_ld, r_ld = a.r_ld, c_row0 = a.c_row0, r_use = a.r_use_index, w_ld = (int)a.w_ld;
-    int w_tap = (int)a.w_tap_stride, tab_ld = a.tab_ld, W = a.W, H = a.H, rows = a.rows, act = a.act, out_f32 = a.out_f32;
+    int w_tap = (int)a.w_tap_stride, tab_ld = a.tab_ld, W = a.W, H = a.H, rows = a.rows, act = a.act;
     TileSource source(a);
     source.hold();
     ds_hold(A, Wt, res, C, scale, shift, a_index, c_index, a_ss, c_ss, r_ss, a_ld, c_ld, r_ld, c_row0, r_use, w_ld, w_tap, tab_ld, W, H,
-            rows, act, out_f32, ny, max_mtiles);
+            rows, act, ny, max_mtiles);
     const int j = (int)(blockIdx.x >> 3);
     const int jm = j / ny, y = j - jm * ny;
     const int mt = jm * 8 + (int)(blockIdx.x & 7);
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const 
         __syncthreads();
         const int cg = threadIdx.x & 15;
         const float4 s4 = *(const float4*)(scl + cg * 4), h4 = *(const float4*)(scl + BN + cg * 4);
-        with_act(act, [&](auto actc) {
+        with_act<false>(act, [&](auto actc) {
             constexpr int ACT = decltype(actc)::value;
 #pragma unroll
             for (int i = 0; i < NE; ++i) {
@@ -279,12 +279,7 @@ __global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const 
                 }
                 float val[4] = {t.x * s4.x + h4.x, t.y * s4.y + h4.y, t.z * s4.z + h4.z, t.w * s4.w + h4.w};
                 if constexpr (HASR) add_residual(val, make_uint2(rres[i].x, rres[i].y));
-                if (out_f32) {
-                    activate<ACT>(val);
-                    *(float4*)((float*)C + coff + ncol4) = make_float4(val[0], val[1], val[2], val[3]);
-                } else {
-                    *(uint2*)((bf16_t*)C + coff + ncol4) = activate_bf16<ACT>(val);
-                }
+                *(uint2*)(C + coff + ncol4) = activate_bf16<ACT>(val);
             }
         });
     } else {
@@ -296,7 +291,7 @@ __global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const 
             for (int i = 0; i < 4; ++i) *(Piece*)(st + (srow + 8 * i) * ST_LD + (lane & 7) * 8) = rres[i];
             wave_sync();
         }
-        with_act(act, [&](auto actc) {
+        with_act<false>(act, [&](auto actc) {
             constexpr int ACT = decltype(actc)::value;
 #pragma unroll
             for (int tn = 0; tn < 2; ++tn)
@@ -308,22 +303,15 @@ __global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const 
                     float val[4] = {t[4 * q] * s4.x + h4.x, t[4 * q + 1] * s4.y + h4.y, t[4 * q + 2] * s4.z + h4.z, t[4 * q + 3] * s4.w + h4.w};
                     uint2* p = (uint2*)(st + l32 * ST_LD + ch);
                     if constexpr (HASR) add_residual(val, *p);
-                    if (out_f32) {
-                        const long long coff = rowC[trow];
-                        activate<ACT>(val);
-                        if (coff >= 0 && n0 + ch < k_out) *(float4*)((float*)C + coff + n0 + ch) = make_float4(val[0], val[1], val[2], val[3]);
-                    } else {
-                        *p = activate_bf16<ACT>(val);
-                    }
+                    *p = activate_bf16<ACT>(val);
                 }
         });
-        if (out_f32) return;
         wave_sync();
         if (ncol8 < k_out) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const long long coff = rowC[wave * 32 + srow + 8 * i];
-                if (coff >= 0) *(uint4*)((bf16_t*)C + coff + ncol8) = *(const uint4*)(st + (srow + 8 * i) * ST_LD + (lane & 7) * 8);
+                if (coff >= 0) *(uint4*)(C + coff + ncol8) = *(const uint4*)(st + (srow + 8 * i) * ST_LD + (lane & 7) * 8);
             }
         }
     }
@@ -346,10 +334,10 @@ int32_t launch(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStrea
 
 }  // namespace
 
-// 3x3, stride 1, padding 1, one segment, maps up to 59 pixels wide; DS_EUNSUPPORTED otherwise
+// 3x3, stride 1, padding 1, one segment, bf16 results without GELU, maps up to 59 pixels wide; DS_EUNSUPPORTED otherwise
 int32_t ds_launch_conv3(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
     if (a.K != 3 || a.stride != 1 || a.pad != 1 || a.n_seg != 1 || a.Ho != a.H || a.Wo != a.W || a.rows != a.H * a.W ||
-        BM + 2 * (a.W + 1) > RMAX)
+        BM + 2 * (a.W + 1) > RMAX || !conv_result(a))
         return DS_EUNSUPPORTED;
     if (((long long)max_kout * a.w_ld + 9 * a.w_tap_stride) * 2 >= 0x7fffffffLL) return DS_EUNSUPPORTED;   // 32-bit weight offsets
     int kmax = 0;

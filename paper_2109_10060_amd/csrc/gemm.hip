@@ -385,7 +385,7 @@ __global__ __launch_bounds__(NT * KS, residency(WMT * WNT, BK, KS, CONV, HASR)) 
         __syncthreads();
         const int cg = threadIdx.x & 15;
         const float4 s4 = *(const float4*)(scl + cg * 4), h4 = *(const float4*)(scl + BN + cg * 4);
-        with_act(act, [&](auto actc) {
+        with_act<!CONV>(act, [&](auto actc) {
             constexpr int ACT = decltype(actc)::value;
 #pragma unroll
             for (int i = 0; i < NE; ++i) {
@@ -433,7 +433,7 @@ __global__ __launch_bounds__(NT * KS, residency(WMT * WNT, BK, KS, CONV, HASR)) 
             // 88 -> 96).
             constexpr int F_LD = ST_LD / 2;
             float* sf = (float*)st;
-            with_act(act, [&](auto actc) {
+            with_act<!CONV>(act, [&](auto actc) {
                 constexpr int ACT = decltype(actc)::value;
 #pragma unroll
                 for (int tn = 0; tn < WNT; ++tn) {
@@ -473,7 +473,7 @@ __global__ __launch_bounds__(NT * KS, residency(WMT * WNT, BK, KS, CONV, HASR)) 
             for (int i = 0; i < 4; ++i) *(Piece*)(st + (srow + 8 * i) * ST_LD + (lane & 7) * 8) = rres[i];
             wave_sync();
         }
-        with_act(act, [&](auto actc) {
+        with_act<!CONV>(act, [&](auto actc) {
             constexpr int ACT = decltype(actc)::value;
 #pragma unroll
             for (int tn = 0; tn < WNT; ++tn)
@@ -627,6 +627,7 @@ int32_t ds_launch_gemm(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, 
         if (rc != DS_EUNSUPPORTED) return rc;
     }
     if (conv) {
+        if (!conv_result(a)) DS_FAIL(DS_EUNSUPPORTED, "sliced gemm: convolutions give bf16, without GELU");
         const int32_t rc = ds_launch_conv3(a, max_mtiles, max_kout, s);
         if (rc != DS_EUNSUPPORTED) return rc;
     }

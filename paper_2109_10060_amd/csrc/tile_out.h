@@ -32,10 +32,13 @@ __device__ __forceinline__ uint2 activate_bf16(float (&v)[4]) {
     activate<ACT>(v);
     return make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
 }
-// f with the activation as a constant
-template <class F>
+// f with the activation as a constant; linear layers alone have GELU
+template <bool LINEAR, class F>
 __device__ __forceinline__ void with_act(int act, F&& f) {
-    if (act == DS_ACT_RELU) f(std::integral_constant<int, DS_ACT_RELU>());
-    else if (act == DS_ACT_GELU) f(std::integral_constant<int, DS_ACT_GELU>());
-    else f(std::integral_constant<int, DS_ACT_NONE>());
+    if (act == DS_ACT_RELU) return f(std::integral_constant<int, DS_ACT_RELU>());
+    if constexpr (LINEAR) {
+        if (act == DS_ACT_GELU) return f(std::integral_constant<int, DS_ACT_GELU>());
+    }
+    f(std::integral_constant<int, DS_ACT_NONE>());
 }
+inline bool conv_result(const GemmArgs& a) { return !a.out_f32 && a.act != DS_ACT_GELU; }
