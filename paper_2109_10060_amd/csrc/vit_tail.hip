@@ -30,7 +30,7 @@
 // come free instead of in turn: no change.
 //
 // Sums run in the order of gemm_kernel's and layernorm16_kernel's, so the results are the same bits.
-#include "gelu.h"
+#include "tile_out.h"
 #include "vit_rows.h"
 
 namespace {
@@ -185,10 +185,15 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
         return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (c0 + l32) * 4, 0, 0));
     };
     auto bias_of = [&](int q) { return *(const float4*)(line + 8 * q + 4 * lhi); };
+    auto to_line = [&](float v) {
+        wave_sync();                                     // (what was there has been read)
+        line[l32] = v;
+        wave_sync();
+    };
     // tile (in LDS, bf16) = tile + acc2 + bias on the elements this lane accumulated
     auto add_columns = [&](float cst, bf16_t* tile, int pitch) {
         if (!con) return;
-        line[l32] = cst;
+        to_line(cst);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int ch = w * 32 + 8 * q + 4 * lhi;
@@ -280,6 +285,13 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
         to_tile(xr, As, PA, de);
         __builtin_amdgcn_s_waitcnt(0x0f70);              // vmcnt(0), here and not behind the branch, where it would be one for the operands under way
     };
+    // The barrier of a turn.  The hardware counts arrivals, wherever in the code they are: a late wavefront comes to it behind its fc2, the
+    // others ahead of theirs, and every wavefront comes once a turn.  (Inside one wavefront the place is the same for all lanes.)
+    auto turn = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    };
     Stream cur = fc1(0);
     for (int hc = 0; hc < nchunk; ++hc) {
         const bool last = hc + 1 == nchunk;
@@ -296,7 +308,7 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
         walk(acc1, cur, s2, As, PA);
         cur = ahead;
         if (!TWO && hc > 0) __syncthreads();             // the previous columns have been read
-        line[l32] = cst;
+        to_line(cst);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int ch = hb * 32 + 8 * q + 4 * lhi;
@@ -310,11 +322,11 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
             }
         }
         if (!late) {
-            __syncthreads();
+            turn();
             if (last) residual();
         }
         if (two >= 0) walk(acc2, s2, ahead, Hs + (TWO ? two & 1 : 0) * (BM * PH), PH);
-        if (late) __syncthreads();
+        if (late) turn();
     }
     if (late) {
         residual();
@@ -367,7 +379,7 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
         clear2();
         cst = columns(a.bq + (int64_t)seg * a.q_ld, n0, kin);
         walk(acc2, qkv(p), qkv(p + NW), As, PA);
-        line[l32] = cst;
+        to_line(cst);
         const __amdgpu_buffer_rsrc_t rq = window(q0, (int64_t)seg * a.q_seg + n0);
 #pragma unroll
         for (int q = 0; q < 4; q += 2) {
