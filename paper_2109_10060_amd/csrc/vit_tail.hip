@@ -40,10 +40,10 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 // Pitches of the activation tile and of the hidden tiles: two of them, or one where 13 wavefronts leave no LDS for a second (two of 12 column
 // blocks are five rounds for 1664 hidden channels where one of 13 is four: 256 images of DS-ViT++ 3512 us a pass, 3616 with two); 8
 // elements behind the last one for the read-ahead of its last row.
-template <int NW, int R, int D>
+template <int NW, int R, int D, int KR>
 struct TailTile {
     static constexpr bool TWO = NW <= 12;
-    static constexpr int KA = NW > 12 ? VIT_K_MAX : 384;    // channels of a row
+    static constexpr int KA = KR;                           // channels of a row
     static constexpr int PA = tile_pitch(KA, D), PH = tile_pitch(32 * NW, D);
     static constexpr int NORM = 32 * R * (PA + (TWO ? 2 : 1) * PH) + 8; // LayerNorm weights: gamma, then beta
     static constexpr int BIAS = NORM + 2 * 2 * KA;          // of each wavefront's columns
@@ -57,10 +57,10 @@ struct Stream {
     int k;
 };
 
-// NW wavefronts (one column block of 32 each), 32 R rows, D operands of a wavefront in flight
-template <int NW, int R, int D>
+// NW wavefronts (one column block of 32 each), 32 R rows, D operands of a wavefront in flight, rows of up to KR channels
+template <int NW, int R, int D, int KR>
 __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const VitTailArgs a) {
-    using Tile = TailTile<NW, R, D>;
+    using Tile = TailTile<NW, R, D, KR>;
     constexpr int BM = 32 * R, HC = 32 * NW, PA = Tile::PA, PH = Tile::PH, KA = Tile::KA, RP = 4 * NW, NI = (BM + RP - 1) / RP;   // RP: rows of a row phase
     extern __shared__ __attribute__((aligned(16))) char smem[];
     bf16_t* As = (bf16_t*)smem;                         // [BM][PA]
@@ -404,13 +404,13 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     }
 }
 
-template <int NW, int R, int D>
+template <int NW, int R, int D, int KR>
 int32_t launch(const VitTailArgs& a, int64_t tiles, hipStream_t s) {
-    constexpr int SMEM = TailTile<NW, R, D>::SMEM;
-    const int32_t rc = ds_reserve_lds((const void*)vit_tail_kernel<NW, R, D>, SMEM, "transformer block tail");
+    constexpr int SMEM = TailTile<NW, R, D, KR>::SMEM;
+    const int32_t rc = ds_reserve_lds((const void*)vit_tail_kernel<NW, R, D, KR>, SMEM, "transformer block tail");
     if (rc) return rc;
     ProfScope prof(DS_K_TAIL, s);
-    hipLaunchKernelGGL((vit_tail_kernel<NW, R, D>), dim3((unsigned)tiles), dim3(64 * NW), SMEM, s, a);
+    hipLaunchKernelGGL((vit_tail_kernel<NW, R, D, KR>), dim3((unsigned)tiles), dim3(64 * NW), SMEM, s, a);
     DS_CHECK_LAUNCH("transformer block tail");
     return DS_OK;
 }
@@ -446,11 +446,11 @@ bool ds_vit_tail_qkv(const GroupTable& gt, int32_t B, int32_t rows, int32_t crow
 // Two workgroups a compute unit (four wavefronts of three column blocks each, 64 rows) were slower, 2780 us when 64 rows took 2600 and
 // 96 rows 2710: eight wavefronts do not cover the weights' latency.
 int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {
-    int dmax = 0;
+    int dmax = 0, kmax = 0;
     for (int t = 0; t < a.gt.T; ++t) {
         if (a.gt.k_out[t] <= 0) continue;
         dmax = a.gt.k_out[t] > dmax ? a.gt.k_out[t] : dmax;
-        dmax = a.gt.k_in[t] > dmax ? a.gt.k_in[t] : dmax;
+        kmax = a.gt.k_in[t] > kmax ? a.gt.k_in[t] : kmax;
         if (a.gt.k_in[t] > VIT_K_MAX || a.gt.k_out[t] > VIT_K_MAX || a.gt.row[t] <= 0 || (a.gt.k_in[t] % 16) || (a.gt.k_out[t] % 8) ||
             (a.gt.row[t] % 8))
             return DS_EUNSUPPORTED;
@@ -459,6 +459,10 @@ int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {
     auto tiles = [&](int bm) { return (n - groups) / bm + groups; };
     const bool two = tiles(64) >= 248 || (a.crowd > 1 && tiles(64) * a.crowd >= (dmax > 384 ? 270 : 300));
     if (dmax > 384)                                      // 13 column blocks: 128 registers per lane, at most 64 rows
-        return two ? launch<13, 2, 4>(a, tiles(64), s) : launch<13, 1, 4>(a, tiles(32), s);
-    return two ? launch<12, 2, 6>(a, tiles(64), s) : launch<12, 1, 8>(a, tiles(32), s);
+        return two ? launch<13, 2, 4, VIT_K_MAX>(a, tiles(64), s) : launch<13, 1, 4, VIT_K_MAX>(a, tiles(32), s);
+    // attention wider than the output's twelve column blocks: rows of 416 channels leave LDS for four operands' turns beside two hidden tiles.
+    // 13 wavefronts -> here, 13 heads of 32 beside an embedding of 384, us a pass: 16 images 719 -> 670, 64 images 1040 -> 1010, 128 images 1688 ->
+    // 1532, 256 images 3049 -> 2835
+    if (kmax > 384) return two ? launch<12, 2, 4, VIT_K_MAX>(a, tiles(64), s) : launch<12, 1, 8, VIT_K_MAX>(a, tiles(32), s);
+    return two ? launch<12, 2, 6, 384>(a, tiles(64), s) : launch<12, 1, 8, 384>(a, tiles(32), s);
 }

@@ -26,8 +26,9 @@ def _vit(gpu_lib, kw, depth=2, seed=21):
     return arch, WL.vit_params(arch, seed)
 
 
-# 13 heads of 32 beside an embedding of 384: the reduction of the projection is wider than the residual rows
-@pytest.mark.parametrize("B", [5, 120, 900])
+# 13 heads of 32 beside an embedding of 384: the reduction of the projection is wider than the residual rows.  The few-image launches, tiles of
+# 32 rows and of 64
+@pytest.mark.parametrize("B", [5, 120, 900, 1000])
 def test_vit_attention_wider_than_the_embedding(gpu_lib, B):
     arch, params = _vit(gpu_lib, WIDE_HEADS)
     net = gpu_lib.build_vit(arch, params, DEV)
