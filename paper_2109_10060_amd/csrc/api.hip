@@ -336,7 +336,7 @@ extern "C" int32_t ds_sliced_mhsa(const void* x, int32_t B, int32_t N, int32_t D
 
     const int64_t seg = (int64_t)(bufsz / sizeof(bf16_t));
     rc = ds_launch_attention(qkv, qkv + seg, qkv + 2 * seg, obuf, (int64_t)N * Hd, Hd, Hd, (int64_t)N * Hd, slot_group,
-                             gt, B, N, H, head_dim, s);
+                             gt, B, N, H, head_dim, 1, s);
     if (rc) return rc;
 
     GemmArgs b;

@@ -216,14 +216,20 @@ __global__ __launch_bounds__(448) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 
 int32_t ds_launch_attention(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* o, int64_t sample_stride,
                             int32_t ld, int32_t o_ld, int64_t o_sample_stride, const int32_t* slot_group,
-                            const GroupTable& gt, int32_t B, int32_t N, int32_t H, int32_t head_dim, hipStream_t s) {
+                            const GroupTable& gt, int32_t B, int32_t N, int32_t H, int32_t head_dim, int32_t crowd, hipStream_t s) {
     if (B <= 0 || H <= 0) return DS_OK;
     if (N < 1 || N > KEYS) DS_FAIL(DS_EUNSUPPORTED, "attention: sequence length %d outside 1..%d", N, KEYS);
     if (head_dim != 32 && head_dim != 48 && head_dim != 64)
         DS_FAIL(DS_EUNSUPPORTED, "attention: head dimension %d (32, 48 or 64)", head_dim);
     ProfScope prof(DS_K_ATTENTION, s);
     const int waves = (N + 31) / 32;
-    const dim3 grid((unsigned)B, (unsigned)H, waves > 4 && (int64_t)B * H * 2 <= 256 ? 2u : 1u), block(64 * waves);
+    // Two workgroups a head, each with all keys and half of the query tiles, where that makes at most a workgroup a compute unit and the parts
+    // of a batch that run side by side have no more heads than there are compute units.  Us a pass, one / two: DS-ViT, 20 images in two parts
+    // (120 heads) 649 / 629, 32 in four (192) 726 / 714, 48 in four (288) 761 / 762, 64 in four (384) 869 / 900; DS-ViT++ 32 images in two (256) 1034
+    // / 1022, 48 in four (384) 1118 / 1128
+    const int64_t heads = (int64_t)B * H;
+    const bool halves = waves > 4 && heads <= 128 && heads * (crowd > 1 ? crowd : 1) <= 256;
+    const dim3 grid((unsigned)B, (unsigned)H, halves ? 2u : 1u), block(64 * waves);
     const float scale = 1.0f / sqrtf((float)head_dim);
 #define DS_ATT(D)                                                                                                  \
     hipLaunchKernelGGL(attention_kernel<D>, grid, block, 0, s, q, k, v, o, sample_stride, ld, o_ld, o_sample_stride, \

@@ -371,7 +371,7 @@ int32_t ds_launch_lookup(const int32_t* idx, const GroupTable& gt, int32_t which
 // head_dim Dh: 32, 48 or 64
 int32_t ds_launch_attention(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* o, int64_t sample_stride,
                             int32_t ld, int32_t o_ld, int64_t o_sample_stride, const int32_t* slot_group,
-                            const GroupTable& gt, int32_t B, int32_t N, int32_t H, int32_t head_dim, hipStream_t s);
+                            const GroupTable& gt, int32_t B, int32_t N, int32_t H, int32_t head_dim, int32_t crowd, hipStream_t s);
 
 // everything of a transformer block behind its attention.  Weights in operand order: [ceil(N / 32)][kb] tiles of 1 KiB, element (half h, row r, i) of a tile = W[32 nb + r][16 kb + 8 h + i], zeros
 // beyond the stored matrix

@@ -1040,7 +1040,7 @@ int32_t forward_vit(const ds_net* net, const VitDesc& d, const bf16_t* images, i
                            DS_ACT_NONE, s));
         }
         RC(ds_launch_attention(p.qkv, p.qkv + p.qkv_seg, p.qkv + 2 * p.qkv_seg, p.o, (int64_t)d.N * Hd, Hd, Hd,
-                               (int64_t)d.N * Hd, p.slot_group, gq, B, d.N, d.H, d.dh, s));
+                               (int64_t)d.N * Hd, p.slot_group, gq, B, d.N, d.H, d.dh, (Bs + B - 1) / B, s));
         if (qkv) {
             const void* const* Q = P + d.tiled + 4 * l;
             const int32_t rc = vit_behind_attention(d, l, L, Q, p, gp, g1, g2, B, (Bs + B - 1) / B, eps, s, &ahead);

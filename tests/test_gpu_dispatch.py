@@ -774,3 +774,25 @@ def test_sliced_linear_fp32_results(gpu_lib, B, rows, k_in, k_out, res, act):
             want = want + host(r[b])[:, :ko]
         want = O.gelu(want) if act == 2 else np.maximum(want, 0.0) if act == 1 else want
         assert relerr(host(y[b])[:, :ko], want) < 1e-4, b
+
+
+# two workgroups a head (up to 128 heads: 21 images of six heads, 16 of eight) and one: every row of every block has the same bits
+@pytest.mark.parametrize("big,B", [(False, 1), (False, 21), (True, 3), (True, 16)])
+def test_attention_halves_have_the_bits_of_the_whole(gpu_lib, big, B):
+    kw = dict(embed=416, heads=8, head_dim=48, mlp=1664, depth=2, routes="pp") if big else dict(depth=2)
+    arch = WL.vit_arch(**kw)
+    net = gpu_lib.build_vit(arch, WL.vit_params(arch, 6), DEV)
+    whole = 40                                                       # 240 and 320 heads: one workgroup each
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(B)
+    imgs = torch.randn((whole, 3, arch["image"], arch["image"]), generator=gen, device=DEV).to(torch.bfloat16)
+    over = ((arch["T"] - 1 - 3 * torch.arange(whole, device=DEV, dtype=torch.int32)) % arch["T"])[None].contiguous()      # (the deepest first)
+
+    def blocks(n):
+        taps = {i: torch.zeros((n, arch["tokens"], arch["embed"]), dtype=torch.bfloat16, device=DEV) for i in range(2)}
+        gpu_lib.ds_forward_taps(net, imgs[:n].contiguous(), taps, route_override=over[:, :n].contiguous())
+        return taps
+
+    few, many = blocks(B), blocks(whole)
+    for i in range(2):
+        assert few[i].abs().max() > 0 and torch.equal(few[i], many[i][:B]), i
