@@ -697,26 +697,44 @@ def test_resnet_gate_scores_do_not_depend_on_the_neighbours(gpu_lib, image, B, s
         assert changed == 0, channel
 
 
-# hidden layers of one column piece, of exactly a tile of 384 or 416 columns, a few columns more, two tiles and the most there are, behind
-# 32 and 64 rows a workgroup and 12 and 13 column blocks: as above
-@pytest.mark.parametrize("B", [120, 1000])
-@pytest.mark.parametrize("embed", [384, 416])
+# hidden layers of one column piece, of exactly a tile of 384 or 416 columns, a few columns more, two tiles and the most there are: the three
+# launches of a few images, 32 and 64 rows a workgroup behind the attention, 12 and 13 column blocks, attention wider than 12 of them: as above
+@pytest.mark.parametrize("B", [3, 7, 120, 1000])
+@pytest.mark.parametrize("embed", [384, 416, "wide heads"])
 def test_vit_hidden_tiles(gpu_lib, embed, B):
     if embed == 384:
         arch = WL.vit_arch(image=64, depth=2)                # 17 tokens
         routes = [(384, 6, 8), (384, 6, 384), (264, 4, 392), (192, 3, 768), (384, 5, 776), (384, 6, 1536)]
-    else:
+    elif embed == 416:
         arch = WL.vit_arch(image=64, embed=416, heads=8, head_dim=48, mlp=1664, depth=2)
         routes = [(392, 7, 8), (416, 8, 416), (416, 8, 424), (400, 8, 832), (416, 5, 840), (416, 8, 1664)]
+    else:
+        arch = WL.vit_arch(image=64, heads=13, head_dim=32, depth=2)
+        routes = [(384, 13, 8), (384, 13, 384), (264, 12, 392), (192, 10, 768), (384, 13, 776), (384, 13, 1536)]
     arch["routes"], arch["T"] = np.array(routes, np.int32), len(routes)
     net = gpu_lib.build_vit(arch, WL.vit_params(arch, 10), DEV)
     gen = torch.Generator(device=DEV)
     gen.manual_seed(B)
     imgs = torch.randn((B, 3, arch["image"], arch["image"]), generator=gen, device=DEV).to(torch.bfloat16)
     over = (torch.arange(B, device=DEV, dtype=torch.int32) * 5 % arch["T"])[None].contiguous()
-    got, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
+
+    def run():
+        gpu_lib.ds_profile_reset()
+        gpu_lib.ds_profile_enable(True)
+        try:
+            logits, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
+        finally:
+            gpu_lib.ds_profile_enable(False)
+        kinds = [k for k, _ in gpu_lib.ds_profile_launches()]
+        gpu_lib.ds_profile_reset()
+        return logits, kinds.count("tail"), kinds.count("vit_linear")
+
+    got, tails, linears = run()
+    # a launch a block, the first block's Q/K/V in one of its own (and the next one's, where it does not ride along) -- or four a block
+    assert (tails, linears) == (0, 8) if B < 10 else (tails == 2 and linears in (1, 2)), (tails, linears)
     net.c_struct.n_params -= 4 * arch["depth"]
-    want, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
+    want, tails, linears = run()
+    assert (tails, linears) == (0, 0)
     assert torch.isfinite(want).all() and torch.equal(got, want)
 
 

@@ -11,7 +11,7 @@ PROGRAM = r"""
 #include "vit_run.h"
 int main() {
     for (int nw : {4, 8, 12})
-        for (int run_blocks : {1, 4, 8, 12})
+        for (int run_blocks : {1, 2, 4, 8, 12})
             for (int total = 1; total <= 52; ++total) {
                 std::vector<int> owner(4 * total, -1);
                 for (int run = 0; run * run_blocks < total; ++run) {
