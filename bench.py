@@ -235,7 +235,8 @@ def match_launches(cost, launches, sampled):
     """Joins the recorded launches (class, ms) of `sampled` identical steps with the cost model's per-launch records, class
     by class in launch order.  Returns the cost records with 'class', 'kernel' and 'us' (mean over the sampled steps) filled in."""
     per_step = len(launches) // sampled
-    rows = [dict(r) for r in cost.launches]
+    from paper_2109_10060_amd.cost import as_launched
+    rows = as_launched(cost.launches)
     want = {}
     for i, r in enumerate(rows):
         want.setdefault("gemm*" if r["kind"] in ("gemm", "gemm_taps") else r["kind"], []).append(i)

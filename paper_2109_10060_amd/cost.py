@@ -23,8 +23,9 @@ class Cost(defaultdict):
         super().__init__(lambda: {"flops": 0.0, "bytes": 0.0, "launches": 0})
         self.launches = []
 
-    def add(self, kind, flops, nbytes, name="", shape="", merge=False, launch=True):
-        """merge: the work rides along in the previous launch of this kind (a chained layer): no new launch.
+    def add(self, kind, flops, nbytes, name="", shape="", merge=False, launch=True, later=False):
+        """merge: the work rides along in the previous launch of this kind (a chained layer): no new launch.  later: it is counted there
+        because of its class, but the contraction launched next does it (as_launched).
         launch=False: totals only, the work happens inside a launch of another kind."""
         e = self[kind]
         e["flops"] += float(flops)
@@ -35,10 +36,27 @@ class Cost(defaultdict):
             last = next(r for r in reversed(self.launches) if r["kind"] == kind)
             last["flops"] += float(flops)
             last["bytes"] += float(nbytes)
+            if later:
+                last.setdefault("later", []).append({"name": name, "flops": float(flops), "bytes": float(nbytes)})
+                name += " (in the next launch)"
             last["name"] += " + " + name
             return
         e["launches"] += 1
         self.launches.append({"kind": kind, "name": name, "shape": shape, "flops": float(flops), "bytes": float(nbytes)})
+
+
+def as_launched(records):
+    """The records with every piece of work in the launch that does it, whatever its class."""
+    rows = [dict(r) for r in records]
+    for i, r in enumerate(rows):
+        for work in r.pop("later", ()):
+            into = next(q for q in rows[i + 1:] if q["kind"] in ("gemm", "gemm_taps"))
+            for key in ("flops", "bytes"):
+                r[key] -= work[key]
+                into[key] += work[key]
+            r["name"] = r["name"].replace(f" + {work['name']} (in the next launch)", "")
+            into["name"] += " + " + work["name"]
+    return rows
 
 
 def _osz(n, k, s, p):
@@ -223,9 +241,8 @@ def resnet_cost(arch, routes) -> Cost:
             _gemm(c, "gemm_taps" if behind else "gemm", r * r, r * r, 1, cin, m, chained=(behind or chain) and b > 0 or b == 0 and paired,
                   name=f"s{s}.b{b}.c1")
             if b == 0 and inside:
-                # (1x1 work, so in the record of the 1x1 launch ahead of the one that does it)
                 c.add("gemm", 2.0 * ro * ro * np.sum(cin * o), 2.0 * r * r * np.sum(cin) + 2.0 * float(cin.max() * o.max()),
-                      name=f"s{s}.b{b}.proj (in the next launch)", merge=True)
+                      name=f"s{s}.b{b}.proj", merge=True, later=True)
             _gemm(c, "gemm_taps", r * r, ro * ro, 9, m, m, name=f"s{s}.b{b}.c2 3x3" + ("/2" if stride == 2 else ""))
             _gemm(c, "gemm_taps" if one else "gemm", ro * ro, ro * ro, 1, m, o, residual=not (b == 0 and inside), chained=one,
                   name=f"s{s}.b{b}.c3" + ("" if b == 0 and inside else "+res"))

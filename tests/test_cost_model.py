@@ -79,3 +79,27 @@ def test_records_add_up_to_the_class_totals_and_name_no_work_twice():
     c = C.vit_cost(v, np.full(64, v["T"] - 1))
     assert c["layernorm"]["bytes"] == 4 * 64 * 384 and c["layernorm"]["launches"] == 1
     assert c["inside"]["bytes"] == 0 and c["inside"]["flops"] == 8 * 64 * v["tokens"] * 384 * 24
+
+
+# the projection of a bottleneck block that is one launch counts with the 1x1 work, but its bytes are not those of the launch before it
+def test_work_is_booked_to_the_launch_that_does_it():
+    r = WL.resnet_arch()
+    c = C.resnet_cost(r, np.full((4, 256), 3))
+    rows = C.as_launched(c.launches)
+    assert [x["kind"] for x in rows] == [x["kind"] for x in c.launches] and not any("next launch" in x["name"] for x in rows)
+    first, block = (next(x for x in rows if x["name"].startswith(n)) for n in ("s0.b0.c1", "s0.b0.c2"))
+    assert first["name"] == "s0.b0.c1" and "s0.b0.proj" in block["name"]
+    px, m, o = 256 * 56 * 56, int(r["mid"][0, 3]), int(r["out"][0, 3])
+    assert first["flops"] == 2 * px * 64 * m and first["bytes"] == 2 * px * (64 + m) + 2 * 64 * m
+    assert block["flops"] >= 2 * px * (9 * m * m + m * o + 64 * o)
+    for key in ("flops", "bytes"):
+        assert abs(sum(x[key] for x in rows) - sum(x[key] for x in c.launches)) < 1e-9 * sum(x[key] for x in rows)
+
+
+def test_the_hash_of_the_contraction_kernels_covers_their_headers():
+    import re
+    from paper_2109_10060_amd import profiling
+    own = set(os.listdir(os.path.join(profiling.HERE, "csrc")))
+    for f in profiling.KERNEL_SOURCES:
+        for h in re.findall(r'#include "([^"]+)"', open(os.path.join(profiling.HERE, f)).read()):
+            assert h not in own or "csrc/" + h in profiling.KERNEL_SOURCES, (f, h)
