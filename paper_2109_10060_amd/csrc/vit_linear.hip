@@ -341,5 +341,8 @@ int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s) {
         return launch<4, 1, 8, VIT_K_MAX, false>(a, tiles(32), blocks, run, s);
     }
     if (kmax > 1664 || a.gamma) return DS_EUNSUPPORTED;
-    return launch<8, 1, 16, 1664, true>(a, tiles(32), blocks, 2, s);
+    // (a workgroup has its compute unit to itself: where runs of two column blocks would fill the chip, four.  Us a pass, two / four: DS-ViT 3 / 5
+    // images 432 / 487 and 433 / 487, 6 / 7 images (252 and 294 workgroups of two) 505 / 540 and 499 / 504, 7 on the widest route 668 and 584; DS-ViT++
+    // 3 / 5 images (245) 552 / 616 and 556 / 616, 7 images 723 and 681, 6 on the widest route 781 and 673)
+    return launch<8, 1, 16, 1664, true>(a, tiles(32), blocks, tiles(32) * ((blocks + 1) / 2) <= 224 ? 2 : 4, s);
 }
