@@ -93,6 +93,7 @@ __global__ __launch_bounds__(64 * NW, DIRECT ? NW / 2 : (NW + 3) / 4) void vit_l
         }
     };
     constexpr bool NORM = KM <= VIT_K_MAX;
+    constexpr bool SKIP = !DIRECT && !(FEW && NW == 8);  // (row_stats)
     constexpr int KN = KIT < 4 ? KIT : 4;                // 16-byte chunks of a lane inside the widest slice
     float* gs = (float*)(Ss + BM * SP);                  // (FEW) LayerNorm weights: gamma, then beta
     if constexpr (FEW) {
@@ -131,9 +132,10 @@ __global__ __launch_bounds__(64 * NW, DIRECT ? NW / 2 : (NW + 3) / 4) void vit_l
                 float v[4][8];
                 uint4 o[4];
 #pragma unroll
-                for (int k = 0; k < KN; ++k) RCH(k, kin) unpack8(q[i][k], v[k]);
-                if constexpr (FEW) row_norm(v, kin, l16, eps, gs, gs + VIT_K_MAX, o);
-                else row_norm(v, kin, l16, eps, gamma, beta, o);
+                for (int k = 0; k < KN; ++k)
+                    if (row_has<SKIP>(k, kin)) unpack8(q[i][k], v[k]);
+                if constexpr (FEW) row_norm<SKIP>(v, kin, l16, eps, gs, gs + VIT_K_MAX, o);
+                else row_norm<SKIP>(v, kin, l16, eps, gamma, beta, o);
 #pragma unroll
                 for (int k = 0; k < KN; ++k)
                     if ((k * 16 + l16) * 8 < kin) q[i][k] = o[k];

@@ -25,14 +25,18 @@ __device__ __forceinline__ float row16_sum(float s) {
     return s;
 }
 // LayerNorm of one row held by 16 lanes, lane l with the 8-channel chunks l, l + 16, l + 32, l + 48; the arithmetic and
-// the order of layernorm16_kernel.  Chunks that begin behind the slice are skipped by a branch of the whole wavefront (RCH): a normalised row
-// is about 450 vector instructions of a lane, and of the four chunks a slice of 192 or 256 channels has two.
-#define RCH(k, d) if (128 * (k) < (d))
+// the order of layernorm16_kernel.  SKIP: chunks that begin behind the slice are skipped by a branch of the whole wavefront (a normalised row
+// is about 450 vector instructions of a lane, and of the four chunks a slice of 192 or 256 channels has two).  Not with eight wavefronts in
+// vit_linear_kernel: there the branches cost more than they save.  With them / without: the first block's Q/K/V layer of 256 images of DS-ViT++
+// 63.8 / 62.6 us, passes of 1 / 3 images of DS-ViT 399.0 / 432.5 and 397.5 / 430.5 us.
+template <bool SKIP>
+__device__ __forceinline__ bool row_has(int k, int d) { return !SKIP || 128 * k < d; }
+template <bool SKIP>
 __device__ __forceinline__ float row_stats(const float (&v)[4][8], int d, int l16, float eps, float* mean) {
     float s = 0.f;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-        RCH(k, d) if ((k * 16 + l16) * 8 < d) {
+        if (row_has<SKIP>(k, d)) if ((k * 16 + l16) * 8 < d) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) s += v[k][i];
         }
@@ -41,7 +45,7 @@ __device__ __forceinline__ float row_stats(const float (&v)[4][8], int d, int l1
     float q = 0.f;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-        RCH(k, d) if ((k * 16 + l16) * 8 < d) {
+        if (row_has<SKIP>(k, d)) if ((k * 16 + l16) * 8 < d) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const float t = v[k][i] - mu;
@@ -50,14 +54,15 @@ __device__ __forceinline__ float row_stats(const float (&v)[4][8], int d, int l1
         }
     return 1.0f / sqrtf(row16_sum(q) / (float)d + eps);
 }
+template <bool SKIP = true>
 __device__ __forceinline__ void row_norm(const float (&v)[4][8], int d, int l16, float eps, const float* gamma,
                                          const float* beta, uint4 (&out)[4]) {
     float mu;
-    const float rstd = row_stats(v, d, l16, eps, &mu);
+    const float rstd = row_stats<SKIP>(v, d, l16, eps, &mu);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int ch = (k * 16 + l16) * 8;
-        RCH(k, d) if (ch < d) {
+        if (row_has<SKIP>(k, d)) if (ch < d) {
             const float4 g0 = *(const float4*)(gamma + ch), g1 = *(const float4*)(gamma + ch + 4);
             const float4 b0 = *(const float4*)(beta + ch), b1 = *(const float4*)(beta + ch + 4);
             const float gm[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
