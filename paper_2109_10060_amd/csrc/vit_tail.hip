@@ -433,10 +433,14 @@ bool ds_vit_tail_qkv(const GroupTable& gt, int32_t B, int32_t rows, int32_t crow
 
 // Rows per workgroup.  A workgroup streams all weights of the block whatever its rows (2.7 MB at full width), and when all compute
 // units do so at once the L2s give each about 30 bytes a clock, half of what 64 rows could use; so more rows each are better --
-// as long as there is a workgroup for nearly every compute unit and the last ones end together.  Us a pass of DS-ViT, 32 / 64 rows: 57
-// images (221 tiles of 64 rows) 909 / 962, 60 images (231) 932 / 965, 64 images (244) 939 / 977, 66 images (250) 1022 / 982, 71 images
-// (265) 1058 / 996, 80 images (290) 1226 / 1033; DS-ViT++ 72 images (229) 1454 / 1526, 76 images (241) 1589 / 1587, 82 images (260) 1636 / 1624,
-// 86 images (272) 1797 / 1646: the line is at 248.  96 rows leave no LDS for the LayerNorm weights: 64 images 1267 us against 1046
+// as long as there is a workgroup for nearly every compute unit and the last ones end together.  How many tiles there are, and how long each
+// takes, is up to the routes, which the host does not know: the line goes by the most there can be.  Us a pass, 32 / 64 rows, routes spread
+// evenly | half of the images on the narrowest | all on the narrowest | all on the widest: DS-ViT 56 images (219 tiles) 815 / 853 | 735 / 855 |
+// 574 / 468 | 1298 / 908, 60 images (231) 856 / 854 | 784 / 855 | 574 / 472 | 1303 / 925, 64 images (244) 872 / 864 | 788 / 860 | 577 / 478 | 1308 /
+// 943, 71 images (265) 965 / 913 evenly; DS-ViT++ 70 images (223) 1304 / 1389 | 1157 / 1373 | 814 / 717 | 2043 / 1530, 72 images (229) 1271 / 1351 | 1131 /
+// 1339 | 782 / 680 | 2004 / 1517, 78 images (247) 1413 / 1455 | 1200 / 1408 | 834 / 738 | 2099 / 1689, 86 images (272) 1649 / 1553 evenly.  On one route,
+// 32 rows are more tiles than compute units, all of one length: a second generation that is half empty, 15 to 39 % of a pass here, where 64 rows cost
+// up to 19 %.  The line is at 224; at 248 batches on one route took up to a quarter more than they had.  96 rows leave no LDS for the LayerNorm weights: 64 images 1267 us against 1046
 // with 64 rows, 192 images 2016 against 2039, 256 images 2587 against 2530 on one card and 2492 against 2485 on another.  (See
 // profiles/dispatch_choices.txt.)  Parts of a batch that run side by side fill the compute units together, if not
 // evenly.  Us a pass, 32 / 64 rows, two parts and four (tiles of 64 rows in all of them): DS-ViT 64 images (260, 260) 941 / 979 and 954 / 1019, 72
@@ -457,7 +461,7 @@ int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {
     }
     const int64_t groups = B < a.gt.T ? B : a.gt.T, n = (int64_t)B * a.rows;
     auto tiles = [&](int bm) { return (n - groups) / bm + groups; };
-    const bool two = tiles(64) >= 248 || (a.crowd > 1 && tiles(64) * a.crowd >= (dmax > 384 ? 270 : 300));
+    const bool two = tiles(64) >= 224 || (a.crowd > 1 && tiles(64) * a.crowd >= (dmax > 384 ? 270 : 300));
     if (dmax > 384)                                      // 13 column blocks: 128 registers per lane, at most 64 rows
         return two ? launch<13, 2, 4, VIT_K_MAX>(a, tiles(64), s) : launch<13, 1, 4, VIT_K_MAX>(a, tiles(32), s);
     // attention wider than the output's twelve column blocks: rows of 416 channels leave LDS for four operands' turns beside two hidden tiles.
