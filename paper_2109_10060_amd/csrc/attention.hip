@@ -3,7 +3,7 @@
 // (DS-ViT++ stores 8 heads of 48: its Q-K-V widths 192..384 in steps of 48 go with 4..8 heads),
 // sequence length up to 224 (7 key tiles of 32).
 //
-// K and V^T of the head live in LDS.  One wavefront per 32-query tile (up to 7 per workgroup):
+// K and V of the head live in LDS.  One wavefront per 32-query tile (up to 7 per workgroup):
 //   S^T[key][q] = K . Q^T   (v_mfma_f32_32x32x16_bf16; A = K rows from LDS, B = Q rows from global)
 // so that one lane owns a fixed query column and half of its keys: the row
 // maximum and sum of the softmax are in-lane reductions plus one exchange with
@@ -62,8 +62,7 @@ __global__ __launch_bounds__(448) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     const int nthreads = blockDim.x;          // one wavefront per 32-query tile
     // A lane's pieces of K and V, four at a time (all there are with seven wavefronts of a 64-wide head), without a branch around a
     // request: rows past the sequence are past the descriptor and give zeros.  That is what lets them travel together; one at a time
-    // measures the same (256 images 36.4 and 36.6 us a launch), one at a time behind a test of the row, at the pitch of
-    // 232, 40.0.
+    // measures the same (us a pass, four and one: 64 / 256 images of DS-ViT 892 / 2293 and 889 / 2289, 256 images of DS-ViT++ 3631 and 3639).
     constexpr int AT = 4;
     const int bytes = ((N - 1) * ld + DH) * 2;
     const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc((void*)(k + base), 0, bytes, 0x00020000);
@@ -91,7 +90,7 @@ __global__ __launch_bounds__(448) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 
     {
         // The keys are taken in two parts (tiles 0..3, then 4..6) with a running maximum and sum, so that only four
-        // score tiles are alive at a time: 128 registers instead of 160, which lets two workgroups share a compute
+        // score tiles are alive at a time: 110 registers instead of 160, which lets two workgroups share a compute
         // unit and one of them stage its K and V while the other multiplies.  p = 2^((s - max) * scale * log2(e)),
         // masked keys get -inf; the scale is positive, so the maximum is taken on the raw scores.  The part's
         // probabilities are rounded to bf16 (relative to the running maximum), multiplied into O^T, and when the

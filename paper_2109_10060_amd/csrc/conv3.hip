@@ -344,11 +344,10 @@ int32_t ds_launch_conv3(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout,
     for (int t = 0; t < a.gt.T; ++t) kmax = a.gt.k_in[t] > kmax ? a.gt.k_in[t] : kmax;
     const int64_t wgs = (int64_t)max_mtiles * ((max_kout + BN - 1) / BN) * (a.crowd > 1 ? a.crowd : 1);
     // Shares of the reduction.  A workgroup is a chain of 3 phases a chunk, about 0.9 us each, whatever else runs; with fewer
-    // workgroups than the compute units could hold, shares shorten it.  DS-ResNet, 33 images, us a launch, one share -> here: 28x28
-    // maps (up to 4 chunks, 436 workgroups) 14.8 -> 12.3, 14x14 (8, 268) 22.2 -> 17.1, 7x7 (16, 232) 37.3 -> 24.0; 64 images 14x14
-    // 24.4 -> 18.3, 7x7 40.8 -> 28.  Twice these lines: 33 / 64 / 96 images 905 / 1248 / 1523 -> 931 / 1291 / 1515 us a pass (the shares of a
-    // workgroup wait for each other); four shares of 16 chunks up to 512 workgroups in place of 256: 64 / 96 images 1253 / 1530 -> 1248 / 1523.  Parts of a batch that run side by side count together: 256 images in
-    // four parts 2894 us, 3097 with shares.
+    // workgroups than the compute units could hold, shares shorten it.  DS-ResNet, us a pass, one share -> here: 16 / 33 / 64 / 96 images 609 / 789 /
+    // 1059 / 1245 -> 601 / 737 / 1006 / 1217, DS-ResNet++ 33 / 64 images 838 / 1165 -> 793 / 1109.  Half and twice these lines: 33 / 64 / 96 images 765 /
+    // 1063 / 1243 and 746 / 1034 / 1203 (the shares of a workgroup wait for each other); four shares of 16 chunks up to 256 workgroups in place of 512: 64 /
+    // 96 images 1011 / 1222.  Parts of a batch that run side by side count together: 256 images in four parts took 2894 us, 3097 with shares.
     const int ks = kmax > 64 && wgs <= (kmax > 256 ? 512 : 256) ? 4 : kmax > 32 && wgs <= 512 ? 2 : 1;
 #define DS_CONV3(KS) (a.R ? launch<true, KS>(a, max_mtiles, max_kout, s) : launch<false, KS>(a, max_mtiles, max_kout, s))
     return ks == 4 ? DS_CONV3(4) : ks == 2 ? DS_CONV3(2) : DS_CONV3(1);

@@ -842,12 +842,12 @@ int32_t vit_behind_attention(const VitDesc& d, int l, const void* const* L, cons
     const int kbp = (Hd + 15) / 16 | 1, kb1 = (d.D + 15) / 16 | 1, kb2 = (d.M + 15) / 16 | 1;
     const int nbd = (d.D + 31) / 32, nbm = (d.M + 31) / 32;
     // Up to 56 tiles of 32 rows (7 images) three launches over many workgroups instead of one whose every workgroup streams all
-    // weights.  The routes are on the device, so this cannot depend on them.  Us a pass, three launches / one: 5 images 559 / 629 on
-    // routes evenly spread, 7 images 582 / 707; DS-ViT++ 7 images 771 / 953, on the narrowest route, where a block's weights are a
-    // tenth, 565 / 490.  Beyond the line the launches cost what their extra passes and workgroups do, but not at once: evenly spread, 8
-    // images take 558 / 544, 10 images 672 / 614 (DS-ViT++ 783 / 955 and 906 / 997, 14 images 960 / 1004, all on the narrowest route 573 / 487, 678 /
-    // 527 and 783 / 545, 14 images on the widest 1232 / 1039, 32 images in four parts 1351 / 1114).  The line stands where none of the
-    // measured mixes loses more than a quarter by it (profiles/dispatch_choices.txt).
+    // weights.  The routes are on the device, so this cannot depend on them.  Us a pass, three launches / one: 3 / 5 / 7 images
+    // 430 / 488 / 502 and 527 / 559 / 620 on routes evenly spread, 7 images on the widest route 585 / 639, on the narrowest, where a block's weights
+    // are a tenth, 439 / 360; DS-ViT++ 7 images 684 / 896, 758 / 936 and 510 / 446.  Beyond the line the launches cost what their extra passes and
+    // workgroups do, but not at once: evenly spread, 8 images take 486 / 484, 10 images 587 / 538 (DS-ViT++ 697 / 896 and 803 / 931, 14 images 858 /
+    // 938, all on the narrowest route 513 / 442, 600 / 476 and 696 / 495, 14 images on the widest 1079 / 995, 32 images in four parts 1181 to 1245 / 700).
+    // The line stands where none of the measured mixes loses more than a quarter by it (profiles/dispatch_choices.txt).
     const int groups = B < d.T ? B : d.T;
     const bool few = d.M <= 1664 && ((int64_t)B * d.N - groups) / 32 + groups <= 56;
     if (!few) {

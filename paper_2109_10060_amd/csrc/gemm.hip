@@ -17,8 +17,8 @@
 // generation of workgroups and a filter tap has 512 channels or more (the last ResNet stage: half as many dependent
 // load -> LDS -> barrier rounds per workgroup; 64-, 128- or 256-byte rows, 16-byte chunks XOR-swizzled by row so
 // stores and reads are bank-conflict free); the next slab's global loads are issued into
-// registers before the current slab's matrix instructions and stored to LDS after them, and 5-6 resident
-// workgroups per compute unit hide each other's round trips.  The epilogue (split batch-norm scale and
+// registers before the current slab's matrix instructions and stored to LDS after them, and four to seven resident
+// workgroups per compute unit (residency) hide each other's round trips.  The epilogue (split batch-norm scale and
 // shift or bias, residual, ReLU/GELU, bf16 rounding) passes a wavefront's tile through LDS as bf16, and it leaves as
 // 16-byte pieces, eight lanes a row.
 //
@@ -59,9 +59,9 @@ struct Tile {
 
 // Two 1x1 layers of one input (a stage's first layer and its projection) as one launch: the first layer's workgroups, then the other's.
 // Apart, each of them starts with empty compute units and ends with most of them idle, 7 to 9 us together, and neither waits for the
-// other.  DS-ResNet, us a pass, two launches -> here: 33 images 838 -> 816, 48 images 976 -> 937, 64 images 1125 -> 1096, 96 images 1346 ->
-// 1320, 256 images 2629 -> 2617; DS-ResNet++ 64 images 1227 -> 1216, 256 images 3051 -> 3056 and 3022 -> 3022.  Only pairs of up to 4000 or 8000
-// workgroups (96 images 1320 without a limit): 1340 and 1331, 256 images (2597) 2611 and 2605.
+// other.  DS-ResNet, us a pass, two launches -> here: 33 images 750 -> 736, 64 images 1022 -> 1009, 96 images 1221 -> 1214, 256 images 2428 ->
+// 2418; DS-ResNet++ 33 / 64 / 256 images 805 / 1124 / 2816 -> 793 / 1108 / 2800.  Only pairs of up to 4000 or 8000 workgroups, before tiles left
+// as 16-byte pieces (96 images 1320 without a limit): 1340 and 1331, 256 images (2597) 2611 and 2605.
 struct GemmPair {
     GemmArgs p[2];
     uint32_t split;                      // workgroups of the first layer
@@ -559,49 +559,48 @@ GemmTile tile_of(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout) {
     const bool conv = is_conv(a);
     // ragged route slices favour the narrow 128x64 tile at high occupancy in every layer of the batch-256 networks.
     // Its slabs are 32 deep for short reductions and 64 deep from 256 reduction steps on: half the barriers and
-    // twice the bytes in flight per workgroup outweigh the lower residency there.  256 images, us a launch, 32 -> 64 deep: DS-ResNet
-    // stage 3, first 1x1 44.2 -> 40.0, strided 3x3 61.4 -> 57.3, stage 4, last 1x1 36.0 -> 30.5, DS-MBNet++ 288..640 channels 51.7 ->
-    // 45.5 (passes 3131 -> 3013, 955 -> 921); its 96-channel layer 26.0 -> 28.7 the other way.
+    // twice the bytes in flight per workgroup outweigh the lower residency there.  Us a pass, 32 deep everywhere -> here: DS-ResNet 33 / 64 /
+    // 256 images 811 / 1142 / 2617 -> 737 / 1009 / 2454, DS-ResNet++ 256 images 3002 -> 2848, DS-MBNet++ 96 / 256 images 427 / 797 -> 399 / 753.
     // (a slab never crosses a filter tap: with fewer than 64 channels per tap the deep slab would be mostly padding)
     int kmax = 0;
     for (int t = 0; t < a.gt.T; ++t) kmax = a.gt.k_in[t] > kmax ? a.gt.k_in[t] : kmax;
     const long long taps = (long long)a.K * (a.Kw > 0 ? a.Kw : a.K);
     // (exactly 256 steps: the 64-deep slabs pay only where a residual is streamed as well -- without one the 32-deep kernel keeps six
-    // workgroups per compute unit: DS-ResNet stage 2, 256 images, projection 83.9 -> 76.2 us with 32, first 1x1 105.3 -> 112.7; passes of
-    // 64 images 1264 -> 1251, DS-ResNet++ 33 images 972 -> 961, 256 images 3006 / 3013)
+    // workgroups per compute unit.  64 deep there too / here: DS-ResNet 64 / 96 / 256 images 1012 / 1219 / 2443 and 1008 / 1214 / 2421, DS-ResNet++
+    // 64 / 256 images 1107 / 2819 and 1102 / 2802.  From 512 steps on in place of 320 no pass differs)
     const bool deep = kmax >= 64 && (kmax * taps >= 320 || (kmax * taps >= 256 && a.R != nullptr));
     // 128 columns a workgroup, two wavefronts of 64 x 64 either way, so that rows go through LDS half as often, where a launch still has
     // several generations of such workgroups and few of them are half empty.
-    // - layers of at most 256 channels whose columns are all in one such tile: DS-ResNet stage 2, first 1x1, 256 images 110 -> 95 us (its
-    //   512-column projection 75 -> 90 the other way); a pass of 64 / 96 / 128 / 180 images (1569 .. 4411 row tiles) with the line at 768 tiles
-    //   1102 / 1326 / 1600 / 2025 -> 1107 / 1336 / 1597 / 2012, so it stands at 3000
-    // - strided KxK layers: DS-ResNet 3x3/2 of stages 2 and 3, 256 images 81.5 -> 70.5 and 56.2 -> 49.9; stage 4 (392 tiles) 54.6 -> 71; the line at 250
-    //   tiles 256 images 2620 -> 2637 a pass, 128 images 1597 -> 1625
-    // Together 256 images of DS-ResNet 2647 -> 2620, of DS-ResNet++ 3037 -> 3007.  With a residual, or more columns at stride 1, they lose (stage 3,
-    // last 1x1 39.5 -> 49.7, stage 4, first 1x1 28.4 -> 37.5).
+    // - layers of at most 256 channels whose columns are all in one such tile: 256 images of DS-ResNet 2440 -> 2423 us a pass; with the line at 768
+    //   tiles 64 / 96 images (1569 and 2353 row tiles) 1009 / 1213 -> 1015 / 1224, so it stands at 3000
+    // - strided KxK layers: 256 images of DS-ResNet 2443 -> 2423, of DS-ResNet++ 2826 -> 2805; with the line at 250 tiles (stage 4's) 128 / 256 images of
+    //   DS-ResNet 1469 / 2423 -> 1491 / 2441
+    // With a residual, or more columns at stride 1, they lost (stage 3, last 1x1 39.5 -> 49.7 us a launch, stage 4, first 1x1 28.4 -> 37.5,
+    // measured before tiles left as 16-byte pieces).
     const long long tiles128 = (long long)max_mtiles * a.n_seg * ((max_kout + 127) / 128) * (a.crowd > 1 ? a.crowd : 1);
     if (!a.R && max_kout > 64) {
         if (!conv && !deep && kmax > 128 && max_kout <= 128 && tiles128 >= 3000) return WIDE32;
-        // - linear layers of 768 channels and more: 64 images of 197 tokens 768 -> 3072 (2376 tiles) 70 -> 65.5, 256 of 256 tokens 308 -> 278, with GELU
-        //   128 of 197 tokens 131 -> 125.  From 1200 tiles on they gain as well, but there a stage of sixteen route groups loses (DS-ResNet stage 4, first
-        //   1x1 of the strided block, 256 images, 1568 tiles, 41.8 -> 50.5); 384 channels lose at any size (64 images of 197 tokens 28.8 -> 31).
+        // - linear layers of 768 channels and more, us a call with its bucketing done: 64 / 128 / 256 images of 197 tokens, 768 -> 3072 (2376 tiles and
+        //   more) 55.2 / 107.9 / 217.7 -> 49.2 / 93.4 / 191.5; with GELU 67.5 / 130.2 / 265.5 -> 70.2 / 128.6 / 258.0.  From 1000 tiles on they gain as well
+        //   without GELU (40 images 36.0 -> 33.1, with it 45.0 -> 47.9), but there a stage of sixteen route groups lost (DS-ResNet stage 4, first
+        //   1x1 of the strided block, 256 images, 1568 tiles, 41.8 -> 50.5).  384 channels: 64 / 128 / 256 images 18.7 / 32.5 / 60.3 -> 19.9 / 33.3 / 60.1, with
+        //   GELU 27.1 / 43.9 / 82.6 -> 33.0 / 49.6 / 91.3.
         if (!conv && kmax >= 768 && tiles128 >= 2048) return WIDE64;
         if (taps > 1 && deep && tiles128 >= 768) return WIDE64_CONV;
     }
     if (!deep) return SLAB32;   // 64-wide tile, 32-deep slabs
-    // launches of about one generation with long reductions (below): 128-deep slabs halve the number of dependent rounds (256 images of
-    // DS-ResNet, stage 4: strided 3x3 64.3 -> 55.7 us, first 1x1 32.3 -> 28.5, pass 3028 -> 3013; without the bound of six workgroups a compute
-    // unit the projections of stages 3 and 4 49.0 -> 58.7 and 45.3 -> 50.1, pass 3070, DS-MBNet++ 921 -> 970)
+    // launches of about one generation with long reductions (below): 128-deep slabs halve the number of dependent rounds.  Us a pass, without
+    // them / here / without the bound of six workgroups a compute unit: DS-ResNet 96 / 128 / 256 images 1226 / 1479 / 2438, 1214 / 1469 / 2421 and
+    // 1225 / 1485 / 2459 (33 / 64 images 732 / 1006, 736 / 1008, 735 / 1012), DS-ResNet++ 256 images 2789 / 2802 / 2854, DS-MBNet++ 256 images 741 / 740 / 783
     const long long wgs = (long long)max_mtiles * a.n_seg * ((max_kout + 63) / 64), slabs = taps * ((kmax + 63) / 64);
     const long long all = wgs * (a.crowd > 1 ? a.crowd : 1);
     // Fewer workgroups than run at once: the slabs of a tile dealt to shares of four wavefronts (not where sums keep one order).
-    // DS-ResNet, us a launch, one share -> here: 8 images, 64 -> 256 channels with residual 9.6 -> 8.4, 14x14 3x3/2 13.0 -> 11.2; 33
-    // images, 1024 -> 256 14.1 -> 12.6, 2048 -> 512 21.9 -> 17.2, 3x3/2 29.6 -> 24.0; 64 images 3x3/2 35.7 -> 26.6.  A workgroup of four
-    // shares has a compute unit to itself, so beyond 256 of them there are two generations: worth it only where a share of half the
-    // slabs is a long chain, from 32 slabs on.  Us a pass, four shares up to 256 workgroups whatever the slabs / here / up to 512
-    // whatever the slabs: DS-ResNet 33 images 903 / 901 / 913, 64 images 1261 / 1253 / 1264, 96 images 1544 / 1533 / 1532; DS-ResNet++ 33
-    // images 948 / 948 / 970, 64 images 1351 / 1356 / 1379; DS-MBNet++ 40 images 332 / 332 / 343.  Twice all these lines: DS-ResNet 16 / 33 / 64 / 96
-    // images 715 / 905 / 1248 / 1523 -> 701 / 912 / 1265 / 1537, DS-ResNet++ 33 images 948 -> 990, DS-MBNet++ 40 images 331 -> 356.
+    // A workgroup of four shares has a compute unit to itself, so beyond 256 of them there are two generations: worth it only where a share
+    // of half the slabs is a long chain, from 32 slabs on.  Us a pass, one share everywhere / four shares up to 256 workgroups whatever the
+    // slabs / here / up to 512 whatever the slabs: DS-ResNet 33 images 760 / 738 / 737 / 752, 64 images 1031 / 1017 / 1009 / 1017, 96 images 1233 /
+    // 1230 / 1218 / 1217; DS-ResNet++ 33 images 802 / 793 / 793 / 814, 64 images 1110 / 1102 / 1108 / 1131; DS-MBNet++ 40 images 301 / 301 / 301 / 312.
+    // Half and twice all these lines: DS-ResNet 8 / 16 / 33 / 64 / 96 images 533 / 587 / 752 / 1030 / 1231 and 528 / 601 / 760 / 1030 / 1227 (here 526 /
+    // 602 / 736 / 1009 / 1214), DS-ResNet++ 33 images 791 and 853 (793), DS-MBNet++ 40 images 301 and 324 (301).
     if (!a.ordered && slabs >= 8 && all <= (slabs >= 32 ? 512 : 256)) return SLAB64_4;
     if (!a.ordered && slabs >= 4 && all <= 512) return SLAB64_2;
     if (kmax >= 512 && wgs <= 256 * 6) return SLAB128;

@@ -11,14 +11,16 @@
 // gemm_kernel read them once per 64 columns).  A finished block is traded between the halves of the wavefront and stored from
 // its registers, 16 bytes a lane (DIRECT): pieces of 64 bytes where a stage in LDS would make whole lines, but without the stage
 // two workgroups share a compute unit, one normalises rows while the other multiplies, and no wavefront waits for another
-// between blocks.  Us a pass, 12 wavefronts, 64 rows and a stage -> here: DS-ViT 64 / 140 / 256 images 980 / 1535 / 2488 -> 979 / 1534 / 2485,
-// DS-ViT++ 1283 / 2248 / 3865 -> 1282 / 2248 / 3817.  (In every block, before the block in front brought Q/K/V: DS-ViT 1058 / 1697 / 2663
+// between blocks.  Us a pass, 12 wavefronts, 64 rows and a stage -> here: DS-ViT 64 / 140 / 256 images 880 / 1398 / 2284 -> 879 / 1391 / 2277,
+// DS-ViT++ 1222 / 2142 / 3610 -> 1223 / 2135 / 3565.  (In every block, before the block in front brought Q/K/V: DS-ViT 1058 / 1697 / 2663
 // -> 1041 / 1657 / 2643, DS-ViT++ 64 and 256 images 1418 / 3947 -> 1396 / 3801; eight operands in flight instead of four 3760, but the
 // others 1049, 1681, 2652 and 1399; 32 rows 256 images 2700 and 3906.)
-// Few images: all four layers of a block with 4 wavefronts and 32 rows, where a launch is bound by latency and by how many
-// compute units share the weights' way in; finished blocks leave through an LDS tile as 16-byte pieces of whole row runs.  The
-// LayerNorm launches disappear.  A LayerNorm there is a chain in front of the products: its weights are asked for beside the rows
-// and its sums run over rotations within 16 lanes instead of exchanges through LDS (rows and LayerNorm 3.4 -> 2 us of a launch of 7.5).
+// Few images: all four layers of a block on 32 rows, where a launch is bound by latency and by how many compute units share the
+// weights' way in: runs of four or eight column blocks with 4 wavefronts, or with 8 that fetch and normalise half as many rows each
+// while four of them multiply, and two blocks a workgroup with 8 wavefronts in fc2, whose rows are the longest.  Finished blocks leave
+// through an LDS tile as 16-byte pieces of whole row runs.  The LayerNorm launches disappear.  A LayerNorm there is a chain in front of
+// the products: rows, then its weights (through LDS) and the first operands are asked for together, and its sums run over rotations
+// within 16 lanes instead of exchanges through LDS.
 // Sums are in gemm_kernel's order: the same bits.
 #include "gelu.h"
 #include "vit_rows.h"
@@ -306,11 +308,12 @@ int32_t launch(const VitLinearArgs& a, int64_t tiles, int max_blocks, int run_bl
 
 }  // namespace
 
-// Measured on DS-ViT's Q/K/V layer with its LayerNorm (us, profiles/dispatch_choices.txt): 1 / 5 / 9 / 16 images with 4 column blocks
-// a workgroup 6.6 / 8.0 / 9.6 / 15.0, 8 blocks 9.2 / 9.6 / 10.8 / 12.3.  From 160 tiles of 64 rows on the
-// large form, which is then the first block's alone: a pass of DS-ViT of 36 / 40 / 50 / 60 images, the line at 100 tiles 752 / 762 / 870 / 956, at 160
-// 754 / 760 / 869 / 955, at 260 754 / 765 / 875 / 963; DS-ViT++ 40 / 60 / 66 images 1113 / 1265 / 1322, 1113 / 1264 / 1322, 1114 / 1270 / 1331.
-// Reductions beyond 416 channels (fc2) are for the few-image path alone: 113 KiB of rows.
+// Column blocks a workgroup, us a pass (profiles/dispatch_choices.txt), four / eight: DS-ViT 1 / 5 / 8 images 398 / 487 / 484 and 504 / 550 / 502, 12 / 16
+// images 600 / 578 and 598 / 576; DS-ViT++ 7 / 9 images 682 / 905 and 726 / 931, 12 / 18 images 961 / 1002 and 937 / 965.  From 160 tiles of 64 rows on the
+// large form, which is then the first block's alone: a pass of DS-ViT of 32 / 40 / 50 / 60 images, the line at 100 tiles 666 / 678 / 785 / 860, at 160
+// 666 / 678 / 784 / 862, at 260 667 / 681 / 789 / 869; DS-ViT++ 40 / 60 / 66 images 1066 / 1189 / 1262, 1067 / 1190 / 1263, 1066 / 1193 / 1270.
+// Reductions beyond 416 channels (fc2) are for the few-image path alone: 113 KiB of rows.  Us a pass, 4 wavefronts and four blocks a workgroup / 8 and
+// two: DS-ViT 1 / 3 / 5 images 404 / 437 / 490 and 399 / 432 / 487, DS-ViT++ 1 / 5 images 489 / 618 and 484 / 616.
 int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s) {
     int kmax = 0, nmax = 0;
     for (int t = 0; t < a.gt.T; ++t) {
@@ -326,17 +329,19 @@ int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s) {
     if (kmax <= VIT_K_MAX) {
         if (!a.res && a.act == DS_ACT_NONE && tiles(64) >= 160) {
             // parts of a batch, each with a workgroup a compute unit at most: two small ones would share the compute units that the other
-            // part leaves free.  Us a pass, 8 / 12 wavefronts: DS-ViT in two parts, 96 images 1121 / 1112, 128 images 1366 / 1356, 160 images (293
-            // tiles a part) 1633 / 1638, 200 images 1976 / 1970, 200 in four (219 tiles) 1968 / 1976; DS-ViT++ in two, 96 / 128 images 1588 / 1587, 1888 / 1883
+            // part leaves free.  Us a pass, 8 / 12 wavefronts: DS-ViT in two parts, 96 images 1028 / 1021, 128 images 1225 / 1210, 160 images (293
+            // tiles a part) 1488 / 1485, 200 images 1808 / 1792, 200 in four (219 tiles) 1838 / 1842; DS-ViT++ in two, 96 / 128 images 1562 / 1559, 1809 / 1803
             if (a.crowd > 1 && tiles(64) <= 256) return launch<12, 2, 4, VIT_K_MAX, false>(a, tiles(64), blocks, blocks, s);
             return launch<8, 2, 4, VIT_K_MAX, false, true>(a, tiles(64), blocks, blocks, s);
         }
-        // (the early requests cost 50 registers, a third of the workgroups a compute unit holds: not where there are enough of them,
-        // nor beside the launches of a batch's other parts -- 1 / 5 images 494 / 562 us a pass, 506 / 569 without them; 12 / 16 images 675 / 652
-        // and 675 / 653; DS-ViT++ 9 / 12 / 18 images, where every block has one, 955 / 1001 / 1023 and 971 / 1008 / 1037)
+        // (everything asked for early takes 10 registers more, 170 for 160, and with them the third workgroup of a compute unit.  Us a pass,
+        // never early / here: DS-ViT 5 / 7 / 8 / 12 / 16 images 513 / 528 / 496 / 600 / 578 and 486 / 502 / 484 / 598 / 576, DS-ViT++ 5 / 9 / 12 / 18 images, where
+        // every block has one, 653 / 931 / 962 / 999 and 614 / 905 / 936 / 964.  Beyond 128 tiles no batch differs; beside the launches of a batch's
+        // other parts 32 / 48 / 64 images of DS-ViT in four 699 / 733 / 870 without, 703 / 731 / 869 with)
         const int run = tiles(32) > 64 ? 8 : 4;
         // up to a workgroup a compute unit eight wavefronts: half as many rows each to fetch and normalise, four of them multiply
-        // (1 / 3 / 5 images 494 / 535 / 562 -> 474 / 515 / 558 us a pass; with two workgroups for some compute units 5 / 8 images 617 / 592)
+        // (1 / 3 / 5 images 494 / 535 / 562 -> 474 / 515 / 558 us a pass when a wavefront asked for its LayerNorm weights itself; since they come
+        // through LDS, up to two for some compute units measure better: 5 / 7 images 486 / 502 and 467 / 491, DS-ViT++ 614 / 681 and 586 / 667)
         if (a.crowd <= 1 && run == 4 && tiles(32) * ((blocks + 3) / 4) <= 256)
             return launch<8, 1, 8, VIT_K_MAX, true>(a, tiles(32), blocks, run, s);
         if (a.crowd <= 1 && tiles(32) <= 128) return launch<4, 1, 8, VIT_K_MAX, true>(a, tiles(32), blocks, run, s);

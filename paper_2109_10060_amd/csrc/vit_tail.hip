@@ -26,7 +26,8 @@
 // that gives out the operands under way (they were moved there, and a move waits for them), requests for rows and constants and stores
 // without branches, six operands in flight for four, two hidden tiles and so one barrier a tile for two.  us a pass, before -> now: 256
 // images of DS-ViT 2322 -> 2217, on another card 2444 -> 2322; 60 to 100 images 1074 -> 975; 256 images of DS-ViT++ (13 wavefronts: one
-// hidden tile, four in flight) 3522 -> 3440.  Eight operands in flight 2350 for 2322 at 256 images.  Q/K/V blocks dealt out as wavefronts
+// hidden tile, four in flight; of its 128 registers a lane 16 leave for scratch ahead of the hidden columns and come back behind them, once a
+// workgroup) 3522 -> 3440.  Eight operands in flight 2350 for 2322 at 256 images.  Q/K/V blocks dealt out as wavefronts
 // come free instead of in turn: no change.
 //
 // Sums run in the order of gemm_kernel's and layernorm16_kernel's, so the results are the same bits.
@@ -420,10 +421,10 @@ int32_t launch(const VitTailArgs& a, int64_t tiles, hipStream_t s) {
 // The next block's Q/K/V behind the block, or in a launch of its own (vit_linear_kernel), which reads the rows again and takes a
 // generation of workgroups more, but spreads over more of them.  So it rides along from about the tiles on at which a launch of its own no longer has
 // compute units to spread to; with 13 wavefronts, where 36 column blocks are three rounds of which one is mostly idle, later.  Us a pass of
-// DS-ViT, own launch / here: 8 images (57 tiles of 32 rows) 545 / 571, 9 images (64) 642 / 627, 16 images 648 / 651, 17 images 750 / 682, 32
-// images 845 / 748, 64 images 1045 / 972, 256 images 2576 / 2447; DS-ViT++ 19 images (135) 1025 / 1047, 24 images (170) 1041 / 1033, 32 images
-// 1110 / 1051, 256 images 3817 / 3652.  Parts of a batch count together: 32 images in two 800 / 751, 128 in four 1674 /
-// 1409, 256 in four 2624 / 2454, in three 2387 / 2315, in two 2342 / 2436 (224 and 384 images in two 2182 / 2097 and 3236 / 3206).
+// DS-ViT, own launch / here: 8 images (57 tiles of 32 rows) 484 / 506, 9 images (64) 561 / 546, 10 images 586 / 538, 16 images 574 / 575, 17 images 668 / 603, 32
+// images 772 / 667, 64 images 969 / 879, 256 images 2445 / 2292; DS-ViT++ 15 / 19 images (107, 135) 946 / 970 and 973 / 995, 20 images (142) 1002 / 985, 32
+// images 1073 / 1004, 256 images 3717 / 3561; 13 heads of 32 beside 384 channels, 10 / 16 images 652 / 657 and 672 / 671, 18 images 721 / 682.  Parts of a batch
+// count together: 32 images in two 731 / 669, 128 in four 1500 / 1286, 256 in four 2420 / 2290, in two 2205 / 2264.
 bool ds_vit_tail_qkv(const GroupTable& gt, int32_t B, int32_t rows, int32_t crowd) {
     int dmax = 0;
     for (int t = 0; t < gt.T; ++t) dmax = gt.k_out[t] > dmax ? gt.k_out[t] : dmax;
@@ -443,10 +444,11 @@ bool ds_vit_tail_qkv(const GroupTable& gt, int32_t B, int32_t rows, int32_t crow
 // up to 19 %.  The line is at 224; at 248 batches on one route took up to a quarter more than they had.  96 rows leave no LDS for the LayerNorm weights: 64 images 1267 us against 1046
 // with 64 rows, 192 images 2016 against 2039, 256 images 2587 against 2530 on one card and 2492 against 2485 on another.  (See
 // profiles/dispatch_choices.txt.)  Parts of a batch that run side by side fill the compute units together, if not
-// evenly.  Us a pass, 32 / 64 rows, two parts and four (tiles of 64 rows in all of them): DS-ViT 64 images (260, 260) 941 / 979 and 954 / 1019, 72
-// images (292, 292) 1034 / 958 and 996 / 1014, 80 images (324, 324) 1090 / 999 and 1126 / 1092, 96 images 1228 / 1107 and 1269 / 1122, 160 images
-// 1937 / 1605 in four; DS-ViT++ 64 images in two (212) 1277 / 1379, 72 images (236) 1351 / 1402, 80 images (262, 276) 1458 / 1457 and 1530 / 1475, 96
-// images 1700 / 1590 and 1734 / 1616.
+// evenly.  Us a pass, 32 / 64 rows, two parts and four (tiles of 64 rows in all of them): DS-ViT 64 images (260, 260) 853 / 837 and 907 / 882, 72
+// images (292, 292) 924 / 884 and 893 / 887, 80 images (324, 324) 997 / 908 and 1016 / 965, 96 images 1108 / 1025 and 1137 / 1038, 160 images
+// 1750 / 1503 in four; DS-ViT++ 64 images in two (212) 1147 / 1308, 80 images (262, 276) 1388 / 1421 and 1467 / 1423, 96 images 1586 / 1555 and 1641 /
+// 1582.  (Parts of unequal size each count the others as being of their own: 72 images of DS-ViT++ in two are 40 and 32, which take one each, 1431
+// where both with 32 rows take 1272 and both with 64 take 1356.)
 // Two workgroups a compute unit (four wavefronts of three column blocks each, 64 rows) were slower, 2780 us when 64 rows took 2600 and
 // 96 rows 2710: eight wavefronts do not cover the weights' latency.
 int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {
