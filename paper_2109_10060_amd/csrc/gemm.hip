@@ -654,7 +654,7 @@ int32_t ds_launch_gemm_pair(const GemmArgs& a, int32_t mtiles_a, int32_t kout_a,
     const int32_t mt[2] = {mtiles_a, mtiles_b}, ko[2] = {kout_a, kout_b};
     for (int q = 0; q < 2; ++q) {
         const GemmArgs& p = *ps[q];
-        if (p.K != 1 || p.Kw > 1 || p.pad || p.R || p.ordered || p.n_seg != 1) return DS_EUNSUPPORTED;
+        if (p.K != 1 || p.Kw > 1 || p.pad || p.R || p.ordered || p.n_seg != 1 || !conv_result(p)) return DS_EUNSUPPORTED;
         int kmax = 0;
         for (int t = 0; t < p.gt.T; ++t) kmax = p.gt.k_in[t] > kmax ? p.gt.k_in[t] : kmax;
         // (shorter ones are thin_kernel's; spans as in ds_launch_gemm)

@@ -16,7 +16,7 @@
 // WM*32 rows and a part beyond the group's rows ends at once.
 // Column tiles are the fastest index of the launch: neighbouring workgroups land on different dies, so a die's L2 holds
 // an eighth of the weights, which are most of what such a launch reads.
-#include "gelu.h"
+#include "tile_out.h"
 
 namespace {
 
@@ -189,11 +189,6 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, char* smem, int y,
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
     // LDS written and read by one wavefront: its accesses complete in order, only the compiler has to be kept in line
-    auto wave_sync = [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
     bf16_t* As = (bf16_t*)(smem + wave * PER_WAVE);
     bf16_t* Bs = As + BM * BK;
     auto stage = [&](const uint4 (&va)[NA], const uint4 (&vb)[NB]) {
