@@ -404,8 +404,10 @@ __global__ __launch_bounds__(NT * KS, residency(WMT * WNT, BK, KS, CONV, HASR)) 
                     activate<ACT>(val);
                     *(float4*)((float*)C + coff + ncol4) = make_float4(val[0], val[1], val[2], val[3]);
                 } else {
-                    // (GELU by erff here, the same bits: a lane has two or four groups of values, and the few that activate_bf16 has to do
-                    // over cost more than it saves.  16 images of 197 tokens, 1536 -> 384 with GELU 16.1 -> 15.1 us, 33 images 384 -> 192 9.7 -> 8.8)
+                    // (GELU by erff here, the same bits: a lane has two or four groups of values, too few for what activate_bf16 saves on them to
+                    // be worth the groups it has to do over.  With activate_bf16 -> here, 16 images of 197 tokens, 768 -> 384, sums of a standard
+                    // deviation of 0.5 and of 1.2, which put one beyond its range in nearly every wavefront: 10.1 and 11.5 -> 10.3 and 10.7 us; 33 images,
+                    // 384 -> 192 8.0 and 9.6 -> 8.0 and 8.8)
                     activate<ACT>(val);
                     *(uint2*)((bf16_t*)C + coff + ncol4) = make_uint2(f2bf2(val[0], val[1]), f2bf2(val[2], val[3]));
                 }
@@ -581,10 +583,10 @@ GemmTile tile_of(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout) {
     if (!a.R && max_kout > 64) {
         if (!conv && !deep && kmax > 128 && max_kout <= 128 && tiles128 >= 3000) return WIDE32;
         // - linear layers of 768 channels and more, us a call with its bucketing done: 64 / 128 / 256 images of 197 tokens, 768 -> 3072 (2376 tiles and
-        //   more) 55.2 / 107.9 / 217.7 -> 49.2 / 93.4 / 191.5; with GELU 67.5 / 130.2 / 265.5 -> 70.2 / 128.6 / 258.0.  From 1000 tiles on they gain as well
-        //   without GELU (40 images 36.0 -> 33.1, with it 45.0 -> 47.9), but there a stage of sixteen route groups lost (DS-ResNet stage 4, first
-        //   1x1 of the strided block, 256 images, 1568 tiles, 41.8 -> 50.5).  384 channels: 64 / 128 / 256 images 18.7 / 32.5 / 60.3 -> 19.9 / 33.3 / 60.1, with
-        //   GELU 27.1 / 43.9 / 82.6 -> 33.0 / 49.6 / 91.3.
+        //   more) 58.1 / 109.9 / 220.6 -> 52.1 / 95.4 / 192.4; with GELU 63.1 / 120.0 / 242.5 -> 60.5 / 111.3 / 221.8.  From 1000 tiles on they gain as well
+        //   (40 images 39.1 -> 35.1, with GELU no change), but there a stage of sixteen route groups lost (DS-ResNet stage 4, first
+        //   1x1 of the strided block, 256 images, 1568 tiles, 41.8 -> 50.5).  384 channels: 64 / 128 / 256 images 20.8 / 35.1 / 64.0 -> 21.9 / 34.6 / 62.4, with
+        //   GELU 25.8 / 42.2 / 78.0 -> 28.3 / 44.9 / 82.2.
         if (!conv && kmax >= 768 && tiles128 >= 2048) return WIDE64;
         if (taps > 1 && deep && tiles128 >= 768) return WIDE64_CONV;
     }
