@@ -1,4 +1,4 @@
-// GELU with the exact erf, and its bf16 rounding without the cost of erff.
+// GELU with the exact erf: by erff, and for bf16 results by one polynomial of the same precision.
 #pragma once
 
 #include "common.h"
@@ -6,25 +6,30 @@
 
 __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 
-// Four values -> packed bf16, bit for bit f2bf2 of gelu_erf.  erff costs about 25 vector instructions and two branches a
-// value; between two and three of four rounded results are decided by far less precision.  gelu_poly is within GELU_SLACK |x|
-// of gelu_erf up to |x| = 2.5; where the bounds of that interval round to the same bf16, so does gelu_erf.  A group of lanes
-// with a value outside, or too close to a rounding boundary (about one value in 3000), takes gelu_erf itself.
-__device__ __forceinline__ uint2 gelu_bf16x4(float x0, float x1, float x2, float x3) {
-    const float x[4] = {x0, x1, x2, x3};
-    float lo[4], hi[4], top = 0.f;
-#pragma unroll
+// Four values -> packed bf16: gelu_poly inside its range, gelu_erf outside, each value for itself.  erff costs about 25 vector instructions
+// and two branches a value, gelu_poly 15.  (A shorter polynomial, with a check that its bf16 result is that of erff and erff itself where
+// that is open, cost 16 and the check: of the groups of 64 lanes x 4 values one in twelve was done over.)
+// the values outside the range again, one erff after the other (a loop: the code of a kernel holds many such groups)
+template <int SCALE = 1>
+__device__ __forceinline__ uint2 gelu_bf16x4_far(uint2 q, float x0, float x1, float x2, float x3) {
+    const uint2 far = make_uint2((fabsf(x0) > GELU_LIMIT ? 0xffffu : 0u) | (fabsf(x1) > GELU_LIMIT ? 0xffff0000u : 0u),
+                                 (fabsf(x2) > GELU_LIMIT ? 0xffffu : 0u) | (fabsf(x3) > GELU_LIMIT ? 0xffff0000u : 0u));
+    float y0 = 0.f, y1 = 0.f, y2 = 0.f, y3 = 0.f;
+#pragma unroll 1
     for (int i = 0; i < 4; ++i) {
-        const float r = gelu_poly(x[i]), a = fabsf(x[i]);
-        lo[i] = fmaf(-GELU_SLACK, a, r);
-        hi[i] = fmaf(GELU_SLACK, a, r);
-        top = fmaxf(top, a);
+        const float y = SCALE * gelu_erf(x0);
+        x0 = x1, x1 = x2, x2 = x3;
+        y0 = y1, y1 = y2, y2 = y3, y3 = y;
     }
-    uint2 q = make_uint2(f2bf2(lo[0], lo[1]), f2bf2(lo[2], lo[3]));
-    const uint32_t d = (q.x ^ f2bf2(hi[0], hi[1])) | (q.y ^ f2bf2(hi[2], hi[3]));
-    if (d != 0 || !(top <= GELU_LIMIT)) {
-        q.x = f2bf2(gelu_erf(x0), gelu_erf(x1));
-        q.y = f2bf2(gelu_erf(x2), gelu_erf(x3));
-    }
-    return q;
+    return make_uint2((q.x & ~far.x) | (f2bf2(y0, y1) & far.x), (q.y & ~far.y) | (f2bf2(y2, y3) & far.y));
+}
+__device__ __forceinline__ float gelu_top(float x0, float x1, float x2, float x3) {
+    return fmaxf(fmaxf(fabsf(x0), fabsf(x1)), fmaxf(fabsf(x2), fabsf(x3)));      // (a NaN is one by gelu_poly too)
+}
+__device__ __forceinline__ uint2 gelu_bf16x4_near(float x0, float x1, float x2, float x3) {
+    return make_uint2(f2bf2(gelu_poly(x0), gelu_poly(x1)), f2bf2(gelu_poly(x2), gelu_poly(x3)));
+}
+__device__ __forceinline__ uint2 gelu_bf16x4(float x0, float x1, float x2, float x3) {
+    const uint2 q = gelu_bf16x4_near(x0, x1, x2, x3);
+    return gelu_top(x0, x1, x2, x3) > GELU_LIMIT ? gelu_bf16x4_far(q, x0, x1, x2, x3) : q;
 }

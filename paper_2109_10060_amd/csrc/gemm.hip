@@ -404,12 +404,7 @@ __global__ __launch_bounds__(NT * KS, residency(WMT * WNT, BK, KS, CONV, HASR)) 
                     activate<ACT>(val);
                     *(float4*)((float*)C + coff + ncol4) = make_float4(val[0], val[1], val[2], val[3]);
                 } else {
-                    // (GELU by erff here, the same bits: a lane has two or four groups of values, too few for what activate_bf16 saves on them to
-                    // be worth the groups it has to do over.  With activate_bf16 -> here, 16 images of 197 tokens, 768 -> 384, sums of a standard
-                    // deviation of 0.5 and of 1.2, which put one beyond its range in nearly every wavefront: 10.1 and 11.5 -> 10.3 and 10.7 us; 33 images,
-                    // 384 -> 192 8.0 and 9.6 -> 8.0 and 8.8)
-                    activate<ACT>(val);
-                    *(uint2*)((bf16_t*)C + coff + ncol4) = make_uint2(f2bf2(val[0], val[1]), f2bf2(val[2], val[3]));
+                    *(uint2*)((bf16_t*)C + coff + ncol4) = activate_bf16<ACT>(val);
                 }
             }
         });

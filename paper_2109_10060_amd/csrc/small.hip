@@ -266,17 +266,15 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, char* smem, int y,
         if (act == DS_ACT_RELU) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) val[q] = fmaxf(val[q], 0.f);
-        } else if (act == DS_ACT_GELU) {
+        } else if (act == DS_ACT_GELU && out_f32) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) val[q] = gelu_erf(val[q]);
         }
         if (out_f32) {
             *(float4*)((float*)C + coff[i] + n) = make_float4(val[0], val[1], val[2], val[3]);
         } else {
-            uint2 q;
-            q.x = f2bf2(val[0], val[1]);
-            q.y = f2bf2(val[2], val[3]);
-            *(uint2*)((bf16_t*)C + coff[i] + n) = q;
+            *(uint2*)((bf16_t*)C + coff[i] + n) =
+                act == DS_ACT_GELU ? gelu_bf16x4(val[0], val[1], val[2], val[3]) : make_uint2(f2bf2(val[0], val[1]), f2bf2(val[2], val[3]));
         }
     }
 }
