@@ -418,6 +418,8 @@ int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s);
 bool ds_vit_tail_qkv(const GroupTable& gt, int32_t B, int32_t rows, int32_t crowd);
 // DS_EUNSUPPORTED where a slice exceeds 416 channels (hidden: any) or its alignment
 int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s);
+// the same in tiles of 64 rows, two workgroups a compute unit; width: the widest slice of either kind (ds_launch_vit_tail's choice)
+int32_t ds_launch_vit_duo(const VitTailArgs& a, int64_t tiles, int width, hipStream_t s);
 
 // ---- per-kernel timing with HIP events (off unless ds_profile_enable(1)) ---------
 enum {

@@ -464,6 +464,14 @@ int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {
     const int64_t groups = B < a.gt.T ? B : a.gt.T, n = (int64_t)B * a.rows;
     auto tiles = [&](int bm) { return (n - groups) / bm + groups; };
     const bool two = tiles(64) >= 224 || (a.crowd > 1 && tiles(64) * a.crowd >= (dmax > 384 ? 270 : 300));
+    // Two workgroups a compute unit from about a generation of them on (512): below, a tile alone on its compute unit takes longer there (384 channels 78
+    // us against 67, 192 channels 36 against 30).  How many tiles there are is up to the routes (as many as groups fewer than counted here).
+    // us a pass, one workgroup | two: DS-ViT 128 images (441 tiles counted) 1197 | 1248, 144 (490) 1331 | 1344, 160 (540) 1546 | 1450, 176 (589) 1631 |
+    // 1625, 216 (712) 1867 | 1867, 256 (836) 2197 | 2081; half of the images on the narrowest route 160 images 1226 | 1268, 192 (638) 1380 | 1383, 256 1773 |
+    // 1702; all on the widest 128 images 1752 | 1678, on the narrowest 767 | 715.  DS-ViT++ 144 images (451) 2079 | 2164, 160 (500) 2224 | 2247, 168 (525) 2511 |
+    // 2341, 184 (574) 2580 | 2402; half on the narrowest 160 images 1896 | 2131, 192 (599) 2242 | 2247.  Parts of a batch count together: DS-ViT
+    // 128 images in two (490) 1228 | 1317, 192 in two (685) 1707 | 1627, in four (780) 1759 | 1657, DS-ViT++ 160 in two (508) 2080 | 2218, 192 in two (606) 2544 | 2410.
+    if (tiles(64) * (a.crowd > 1 ? a.crowd : 1) >= 576) return ds_launch_vit_duo(a, tiles(64), dmax > kmax ? dmax : kmax, s);
     if (dmax > 384)                                      // 13 column blocks: 128 registers per lane, at most 64 rows
         return two ? launch<13, 2, 4, VIT_K_MAX>(a, tiles(64), s) : launch<13, 1, 4, VIT_K_MAX>(a, tiles(32), s);
     // attention wider than the output's twelve column blocks: rows of 416 channels leave LDS for four operands' turns beside two hidden tiles.

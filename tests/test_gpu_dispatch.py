@@ -738,6 +738,39 @@ def test_vit_hidden_tiles(gpu_lib, embed, B):
     assert torch.isfinite(want).all() and torch.equal(got, want)
 
 
+# blocks in two workgroups a compute unit, two, three and four column blocks a wavefront: embeddings that end at either side of their edges and
+# inside a block, attention narrower and wider than them, hidden layers of one piece, of a tile of 128 columns, a piece more and the most
+# there are, GELU far outside the polynomial's range, a sample that is not finite: the bits of the launches on the row-major weights
+@pytest.mark.parametrize("embed", [384, 416, "wide heads"])
+def test_vit_two_workgroups(gpu_lib, embed):
+    if embed == 384:
+        arch = WL.vit_arch(image=64, depth=2)                # 17 tokens
+        routes = [(8, 1, 8), (136, 6, 128), (192, 3, 136), (256, 4, 384), (264, 2, 520), (320, 5, 1280), (384, 1, 264), (384, 6, 1536)]
+    elif embed == 416:
+        arch = WL.vit_arch(image=64, embed=416, heads=8, head_dim=48, mlp=1664, depth=2)
+        routes = [(248, 8, 8), (256, 5, 1024), (288, 6, 1008), (384, 8, 256), (392, 7, 8), (400, 1, 904), (416, 5, 1160), (416, 8, 1664)]
+    else:
+        arch = WL.vit_arch(image=64, heads=13, head_dim=32, depth=2)
+        routes = [(8, 13, 8), (224, 13, 384), (256, 1, 776), (264, 12, 392), (328, 11, 128), (384, 10, 120), (384, 13, 1400), (384, 13, 1536)]
+    arch["routes"], arch["T"] = np.array(routes, np.int32), len(routes)
+    p = WL.vit_params(arch, 12)
+    for k in ("l1.fc1.w", "l1.fc1.b"):
+        p[k] = p[k] * 8.0                                    # pre-activations far beyond +-3.5 beside small ones
+    net = gpu_lib.build_vit(arch, p, DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(12)
+    B = 2300                                                 # 618 tiles of 64 rows
+    imgs = torch.randn((B, 3, arch["image"], arch["image"]), generator=gen, device=DEV).to(torch.bfloat16)
+    imgs[5, 0, 0, 0], imgs[1234, 2, 9, 9] = float("nan"), float("inf")
+    over = (torch.arange(B, device=DEV, dtype=torch.int32) * 5 % arch["T"])[None].contiguous()
+    got, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
+    net.c_struct.n_params -= 4 * arch["depth"]
+    want, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
+    odd = ~torch.isfinite(want).all(dim=1)
+    assert odd.nonzero().flatten().tolist() == [5, 1234]
+    assert torch.equal(torch.isnan(got[odd]), torch.isnan(want[odd])) and torch.equal(got[~odd], want[~odd])
+
+
 # heads over two workgroups, four query tiles and the rest: the largest number of heads that are (128) and one sample more, as many
 # wavefronts as a workgroup of one half has and one more
 @pytest.mark.parametrize("dh,H,N,B", [(48, 8, 197, 16), (48, 8, 197, 17), (64, 2, 224, 3), (32, 4, 128, 32), (32, 4, 129, 32), (32, 4, 129, 33)])

@@ -21,3 +21,12 @@ def test_short_slabs_of_the_grouped_gemm():
         assert waves(k) >= 6, name
     for name, k in found.items():
         assert k[".private_segment_fixed_size"] == 0, name
+
+
+# transformer blocks with two workgroups of four wavefronts a compute unit: two wavefronts a SIMD, and nothing in scratch up to 384 channels
+def test_transformer_blocks_of_two_workgroups():
+    found = {n: k for n, k in kernels().items() if "vit_duo_kernel" in n}
+    assert len(found) == 2
+    for name, k in found.items():
+        assert waves(k) >= 2, name
+        assert k[".private_segment_fixed_size"] == 0 or "Li416E" in name, name
