@@ -410,12 +410,14 @@ int32_t forward_mb(const ds_net* net, const MbDesc& d, const bf16_t* images, int
 //             c3.w [4w][w] bf16, c3.scale, c3.shift [T][4w], and for the first block
 //             proj.w [4w][C_in] bf16, proj.scale, proj.shift,
 //          fc.w [classes][4*w_last] bf16, fc.b
+//          [, per block c2.w in operand order (conv3t.hip)]
 // =====================================================================================
 struct RnDesc {
     int image, stem_out, T, classes;
     const int32_t *widths, *blocks, *hidden, *mid, *out;
     const int32_t* nblk;     // [4][T] blocks of a stage that a route runs, or null: every stored block
     int single_gate;         // 1: the first stage's gate decides for all four stages (DS-ResNet++)
+    const void* const* tiles;   // per block: c2.w in operand order, or null
 };
 
 // route groups of a stage: (this stage's route, previous stage's route) pairs, or the route alone when one gate
@@ -442,9 +444,13 @@ bool parse_rn(const ds_net* net, RnDesc* d) {
         for (int st = 0; st < 4; ++st)
             for (int q = 0; q < d->T; ++q)
                 if (d->nblk[st * d->T + q] < 1 || d->nblk[st * d->T + q] > d->blocks[st]) return false;
-    int np = 3 + 2;
-    for (int s = 0; s < 4; ++s) np += 4 + 9 * d->blocks[s] + 3;
-    return net->n_params == np;
+    int np = 3 + 2, nb = 0;
+    for (int s = 0; s < 4; ++s) {
+        np += 4 + 9 * d->blocks[s] + 3;
+        nb += d->blocks[s];
+    }
+    d->tiles = net->n_params == np + nb ? net->params + np : nullptr;
+    return net->n_params == np || d->tiles;
 }
 
 struct RnPlan {
@@ -700,9 +706,17 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
                     y1_ready = true;
                 }
             } else {
-                RC(conv_gemm(Y1, nullptr, (int64_t)rb * rb * w, 0, (const bf16_t*)L[3], w, 3, bs, 1, rb, rb, (const float*)L[4],
-                             (const float*)L[5], w, nullptr, Y2, (int64_t)rout * rout * w, 0, p.offs[st], ml_out, g2,
-                             DS_ACT_RELU, s));
+                int32_t rc = DS_EUNSUPPORTED;
+                if (d.tiles && bs == 1)
+                    rc = ds_launch_conv3_tiled(conv_args(Y1, nullptr, (int64_t)rb * rb * w, 0, (const bf16_t*)L[3], w, 3, 1, 1, rb, rb,
+                                                         (const float*)L[4], (const float*)L[5], w, nullptr, Y2, (int64_t)rout * rout * w, 0,
+                                                         p.offs[st], ml_out, g2, DS_ACT_RELU),
+                                               (const bf16_t*)d.tiles[block_id], w, ml_out.cap, max_out(g2), s);
+                if (rc != DS_OK && rc != DS_EUNSUPPORTED) return rc;
+                if (rc != DS_OK)
+                    RC(conv_gemm(Y1, nullptr, (int64_t)rb * rb * w, 0, (const bf16_t*)L[3], w, 3, bs, 1, rb, rb, (const float*)L[4],
+                                 (const float*)L[5], w, nullptr, Y2, (int64_t)rout * rout * w, 0, p.offs[st], ml_out, g2,
+                                 DS_ACT_RELU, s));
                 // c3 adds the shortcut; later blocks update Z in place (each element is read and written by one thread)
                 RC(conv_gemm(Y2, nullptr, (int64_t)rout * rout * w, 0, (const bf16_t*)L[6], w, 1, 1, 0, rout, rout,
                              (const float*)L[7], (const float*)L[8], 4 * w, shortcut, Z, (int64_t)rout * rout * 4 * w, 0,

@@ -83,6 +83,19 @@ def _pointwise_tiles(w):
     return t.view(nb, 4, 2, 4, kb, 4, 8).permute(0, 4, 2, 5, 1, 3, 6).contiguous()
 
 
+def _conv3_tiles(w):
+    """[N, 3, 3, K] bf16 -> [ceil(N/32)][18 ceil(K/32) + 1] tiles of 32 x 16 in the order of a matrix instruction's lanes: of every
+    32 channels the nine taps, of a tap two halves of 16 channels.  The tile at the end of a block of filters keeps the blocks,
+    which the wavefronts of a workgroup stream side by side, off the same L2 channels."""
+    n, _, _, k = w.shape
+    nb, kc = (n + 31) // 32, (k + 31) // 32
+    t = torch.zeros((nb * 32, 9, kc * 32), dtype=w.dtype, device=w.device)
+    t[:n, :, :k] = w.reshape(n, 9, k)
+    out = torch.zeros((nb, 18 * kc + 1, 512), dtype=w.dtype, device=w.device)
+    out[:, :-1] = t.view(nb, 32, 9, kc, 2, 2, 8).permute(0, 3, 2, 4, 5, 1, 6).reshape(nb, 18 * kc, 512)
+    return out
+
+
 def build_mbnet(arch: dict, p: dict, device="cuda:0") -> Net:
     from . import DS_ARCH_MBNET
     bf, f32 = torch.bfloat16, torch.float32
@@ -130,6 +143,13 @@ def build_resnet(arch: dict, p: dict, device="cuda:0") -> Net:
                 t.append(_ohwi(p[f"{pre}.{c}.w"], device))
                 t += list(_fold(p[f"{pre}.{c}.bn"], eps, device))
     t += [_dev(p["fc.w"], bf, device), _dev(p["fc.b"], f32, device)]
+    # the 3x3 filters of stride 1 once more in operand order (the first blocks' entries behind the first stage are not read)
+    at = 3
+    for s, nb in enumerate(arch["blocks"]):
+        at += 4
+        for b in range(nb):
+            t.append(_conv3_tiles(t[at + 3]) if s == 0 or b > 0 else t[at + 3])
+            at += 12 if b == 0 else 9
     return Net(DS_ARCH_RESNET, ints, t, arch["num_classes"], 4, T)
 
 
