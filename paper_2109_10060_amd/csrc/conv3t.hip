@@ -14,8 +14,8 @@
 //     behind have it on: with tiles dealt over all dies the 3x3 layers of DS-ResNet took 13 us less each and the pass nothing less.
 //   * Quotients by reciprocals: with integer divisions a workgroup spent 14 of 25 us ahead of its first product and behind its last.
 // us a launch, mixed routes of 256 images, conv3_kernel -> here: 14x14 pixels, 64..256 channels 44 -> 31, 7x7 pixels, 128..512 channels 44 -> 31.
-// us a pass: DS-ResNet 16 / 33 / 64 / 96 / 128 / 256 images 612 / 750 / 1022 / 1223 / 1491 / 2465 -> 606 / 702 / 1001 / 1180 / 1462 / 2398, 256 in four parts 2420 -> 2330,
-// DS-ResNet++ 33 / 64 / 256 images 801 / 1123 / 2840 -> 751 / 1089 / 2770.
+// us a pass: DS-ResNet 64 / 96 / 128 / 256 images 1022 / 1223 / 1491 / 2465 -> 1001 / 1180 / 1462 / 2398, 256 in four parts 2420 -> 2330, DS-ResNet++ 64 / 256 images
+// 1123 / 2840 -> 1089 / 2770; three networks in turn, DS-ResNet 16 / 24 / 33 / 48 images 652 / 726 / 800 / 920 -> 646 / 714 / 778 / 904, DS-ResNet++ 33 images 850 -> 836.
 #include "tile_out.h"
 #include "conv3_fit.h"
 
@@ -249,10 +249,12 @@ int32_t launch(const GemmArgs& a, const Conv3T& t, int32_t max_mtiles, int32_t m
 
 }  // namespace
 
-// tiles: filters [ceil(N / 32)][18 ceil(K / 32) + 1] tiles of 1 KiB; channels: K as stored.  Launches of a few samples stay with
-// gemm_small_kernel, which has up to eight wavefronts on a tile's reduction: us a pass, there / here, DS-ResNet 1 / 4 / 8 images 364 / 468 / 529 and
-// 384 / 491 / 536, DS-ResNet++ 4 / 8 images 460 / 541 and 481 / 544; from 600 of its 32 x 32 tiles on here: DS-ResNet 16 images 611 and 606, DS-ResNet++
-// 16 / 33 images 621 / 762 and 613 / 751.
+// tiles: filters [ceil(N / 32)][18 ceil(K / 32) + 1] tiles of 1 KiB; channels: K as stored.  Launches of up to 600 of gemm_small_kernel's 32 x 32 tiles
+// stay there, with up to eight wavefronts on a tile's reduction: us a pass, there / here, DS-ResNet 1 / 4 / 8 images 364 / 468 / 529 and 384 / 491 / 536,
+// DS-ResNet++ 4 / 8 images 460 / 541 and 481 / 544.  With all of its launches there, 33 images of DS-ResNet++ 851 (networks in turn, 762 one
+// network's), here from 600 on 836 (751); DS-ResNet 16 / 24 images 641 / 712 and 646 / 714 (611 / 655 and 606 / 650).  Filters that come from
+// memory are what these launches wait for (256 channels, 13 us a launch with one network, 16 with three in turn); the reduction dealt to two groups
+// of wavefronts does not change that (838 and 849 a pass).
 // Tiles of 64 pixels until there are enough of 128 to go round: DS-ResNet 128 / 160 / 256 images, 256 in four parts, the line at 500 workgroups of 128 x 64 1430 / 1639 / 2337 / 2300,
 // at 700 1423 / 1632 / 2333 / 2302, at 1200 1432 / 1653 / 2347 / 2295, at 1700 1432 / 1652 / 2372 / 2314.
 int32_t ds_launch_conv3_tiled(const GemmArgs& a, const bf16_t* tiles, int32_t channels, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
