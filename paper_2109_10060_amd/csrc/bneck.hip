@@ -135,7 +135,7 @@ __global__ __launch_bounds__(NT, NB == 2 ? 3 : 2) void bneck_kernel(const BneckA
         const int jr = 16 * wave + (lane & 15) + 64 * (lane >> 4), px = grow0 - halo + jr;
         uint32_t o = OOB;
         if (jr < R && px >= 0 && px < rows_g) {
-            const int sl = px / rows;
+            const int sl = ds_quotient(px, rows);
             o = (uint32_t)(((slot0 + sl) * a.y1_ss + (int64_t)(px - sl * rows) * mid) * 2);
         }
 #pragma unroll
@@ -199,8 +199,8 @@ __global__ __launch_bounds__(NT, NB == 2 ? 3 : 2) void bneck_kernel(const BneckA
         const int m = grow0 + prow;
         int z = -1, y = -1;
         if (m < rows_g) {
-            const int sl = m / rows, p = m - sl * rows, slot = slot0 + sl;
-            const int oy = p / W, ox = p - oy * W;
+            const int sl = ds_quotient(m, rows), p = m - sl * rows, slot = slot0 + sl;
+            const int oy = ds_quotient(p, W), ox = p - oy * W;
             // filter columns, filter rows inside the map
             const int cols = (ox > 0 ? 1 : 0) | 2 | (ox + 1 < W ? 4 : 0);
             tapmask = (oy > 0 ? cols : 0) | cols << 3 | (oy + 1 < H ? cols << 6 : 0);

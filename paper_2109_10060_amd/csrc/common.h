@@ -6,12 +6,18 @@
 #include <stdio.h>
 
 #include "dsnet.h"
+#include "quotient.h"
 
 typedef uint16_t bf16_t;  // raw bfloat16 bits
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
+
+// n / d, n not negative
+__device__ __forceinline__ int ds_quotient(int n, int d) { return quotient(n, d, __builtin_amdgcn_rcpf((float)d)); }
+
+__device__ __forceinline__ int ds_quotient_uniform(int n, int d) { return __builtin_amdgcn_readfirstlane(ds_quotient(n, d)); }
 
 __device__ __forceinline__ float bf2f(bf16_t v) { return __uint_as_float(((uint32_t)v) << 16); }
 

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const 
     ds_hold(A, Wt, res, C, scale, shift, a_index, c_index, a_ss, c_ss, r_ss, a_ld, c_ld, r_ld, c_row0, r_use, w_ld, w_tap, tab_ld, W, H,
             rows, act, ny, max_mtiles);
     const int j = (int)(blockIdx.x >> 3);
-    const int jm = j / ny, y = j - jm * ny;
+    const int jm = ds_quotient_uniform(j, ny), y = j - jm * ny;
     const int mt = jm * 8 + (int)(blockIdx.x & 7);
     if (mt >= max_mtiles) return;
     const int4 me = source.record(mt);
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const 
         const int L = grow0 - halo + jr;              // pixel index in the group's row-major order
         uint32_t o = OOB;
         if (jr < R && L >= 0 && L < rows_g) {
-            const int sl = L / rows;
+            const int sl = ds_quotient(L, rows);
             const int p = L - sl * rows;
             const int slot = slot0 + sl;
             const int sa = a_index ? a_index[slot] : slot;
@@ -155,13 +155,13 @@ __global__ __launch_bounds__(NT * KS) void conv3_kernel(const GemmArgs a, const 
         const int m = grow0 + trow;
         long long rc = -1, rr = 0;
         if (m < rows_g) {
-            const int sl = m / rows;
+            const int sl = ds_quotient(m, rows);
             const int p = m - sl * rows;
             const int slot = slot0 + sl;
             const int cs = c_index ? c_index[slot] : slot;
             rc = (long long)cs * c_ss + (long long)(p + c_row0) * c_ld;
             rr = (long long)(r_use ? cs : 0) * r_ss + (long long)(p + c_row0) * r_ld;
-            const int oy = p / W, ox = p - oy * W;
+            const int oy = ds_quotient(p, W), ox = p - oy * W;
             // filter columns, filter rows inside the map
             const int cols = (ox > 0 ? 1 : 0) | 2 | (ox + 1 < W ? 4 : 0);
             tapmask = (oy > 0 ? cols : 0) | cols << 3 | (oy + 1 < H ? cols << 6 : 0);

@@ -33,12 +33,6 @@ struct Conv3T {
     int32_t ntile;                             // 18 a chunk and one that keeps the blocks' streams off the same L2 channels
 };
 
-// n / d for n below 2^22, r = about 1 / d
-__device__ __forceinline__ int quotient(int n, int d, float r) {
-    const int q = (int)((float)n * r), m = n - q * d;
-    return q + (m >= d) - (m < 0);
-}
-
 // CW of the four wavefronts side by side, 32 filters each, 4 / CW below each other, 32 R pixels each; DS steps of filters on their way, pixels read FA - 1 steps ahead
 template <int R, int CW, int DS, int FA>
 __device__ __forceinline__ void body(const GemmArgs& a, const Conv3T& t, const int g0, const int slot0, const int rows_g, const int n0, const int k_in, const int k_out, const int row, char* smem) {
@@ -63,11 +57,11 @@ __device__ __forceinline__ void body(const GemmArgs& a, const Conv3T& t, const i
     const uint32_t lane16 = (uint32_t)lane * 16;
     const int nchunk = (k_in + 31) / 32;
     auto padded = [&](int m) {
-        const int sl = quotient(m, rows, r_rows), p = m - sl * rows, y = quotient(p, W, r_w);
+        const int sl = quotient22(m, rows, r_rows), p = m - sl * rows, y = quotient22(p, W, r_w);
         return conv3_padded(sl, y, p - y * W, W, H);
     };
     const int first = padded(g0) - (Q + 1), span = padded(min(g0 + BM, rows_g) - 1) + Q + 2 - first;
-    const int RB = W * PITCH + CONV3_GAP, row0 = quotient(first, Q, r_q);
+    const int RB = W * PITCH + CONV3_GAP, row0 = quotient22(first, Q, r_q);
     uint32_t poff[NI];
     int loff[NI];
     {
@@ -75,7 +69,7 @@ __device__ __forceinline__ void body(const GemmArgs& a, const Conv3T& t, const i
 #pragma unroll
         for (int k = 0; k < NC; ++k) {
             const int j = 16 * w + 16 * NW * (4 * k + (lane >> 4)) + (lane & 15), P = first + j;
-            const int pr = quotient(P, Q, r_q), x = P - pr * Q - 1, sl = quotient(pr, H + 1, r_h), y = pr - sl * (H + 1) - 1, p = y * W + x;
+            const int pr = quotient22(P, Q, r_q), x = P - pr * Q - 1, sl = quotient22(pr, H + 1, r_h), y = pr - sl * (H + 1) - 1, p = y * W + x;
             o[k] = OOB;
             l[k] = (uint32_t)(j < span ? conv3_byte(pr, x + 1, row0, W) : -1);
             if (j < span && x >= 0 && y >= 0 && sl * rows + p < rows_g) {
@@ -103,7 +97,7 @@ __device__ __forceinline__ void body(const GemmArgs& a, const Conv3T& t, const i
             if (loff[i] >= 0) *(uint4*)(smem + buf * PB + loff[i]) = pv[i];
     };
     // the zeros behind a map row (those ahead of it come with the patch)
-    const int nrow = quotient(first + span - 1, Q, r_q) - row0 + 1;
+    const int nrow = quotient22(first + span - 1, Q, r_q) - row0 + 1;
     for (int i = tid; i < nrow * 8; i += NT)
         *(uint4*)(smem + (i >> 2 & 1) * PB + (i >> 3) * RB + (W + 1) * PITCH + (i & 3) * 16) = make_uint4(0, 0, 0, 0);
     bf16x8_t ring[DS];
@@ -127,7 +121,7 @@ __device__ __forceinline__ void body(const GemmArgs& a, const Conv3T& t, const i
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int m = g0 + (rw * R + r) * 32 + l32;
-        const int P = (m < rows_g ? padded(m) : padded(g0)) - (Q + 1), pr = quotient(P, Q, r_q);
+        const int P = (m < rows_g ? padded(m) : padded(g0)) - (Q + 1), pr = quotient22(P, Q, r_q);
         base[r] = conv3_byte(pr, P - pr * Q, row0, W) + lhi * 16;
     }
     f32x16_t acc[R];
@@ -174,7 +168,7 @@ __device__ __forceinline__ void body(const GemmArgs& a, const Conv3T& t, const i
         bf16_t* out[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int m = g0 + (rw * R + r) * 32 + l32, sl = m < rows_g ? quotient(m, rows, r_rows) : 0, p = m - sl * rows, slot = slot0 + sl;
+            const int m = g0 + (rw * R + r) * 32 + l32, sl = m < rows_g ? quotient22(m, rows, r_rows) : 0, p = m - sl * rows, slot = slot0 + sl;
             const int cs = a.c_index ? a.c_index[slot] : slot;
             out[r] = m < rows_g ? (bf16_t*)a.C + (long long)cs * a.c_sample_stride + (long long)(p + a.c_row0) * c_ld : nullptr;
         }
@@ -221,7 +215,7 @@ __global__ __launch_bounds__(256, 2) void conv3_tiled_kernel(const GemmArgs a, c
     const int rank = b < FOLD ? min(FOLD, total) - 1 - b : b;
     const int q = __builtin_ctzll(__ballot(upto > rank));
     const int i = rank - __builtin_amdgcn_readlane(upto - cnt, q), np = __builtin_amdgcn_readlane(parts, q);
-    const int k = i / np, part = i - k * np, sub = BM < DS_GEMM_BM ? part & 1 : 0, n0 = (BM < DS_GEMM_BM ? part >> 1 : part) * BN;
+    const int k = ds_quotient_uniform(i, np), part = i - k * np, sub = BM < DS_GEMM_BM ? part & 1 : 0, n0 = (BM < DS_GEMM_BM ? part >> 1 : part) * BN;
     const int slot0 = __builtin_amdgcn_readlane(o0, q), rows_g = (__builtin_amdgcn_readlane(o1, q) - slot0) * rows;
     const int g0 = (8 * (__builtin_amdgcn_readlane(k0, q) + k) + die - __builtin_amdgcn_readlane(mend - nm, q)) * DS_GEMM_BM + sub * BM;
     if (g0 >= rows_g) return;

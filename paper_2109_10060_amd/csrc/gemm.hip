@@ -130,7 +130,7 @@ __global__ __launch_bounds__(NT * KS, residency(WMT * WNT, BK, KS, CONV, HASR)) 
     if constexpr (KS > 1 && !CONV) ds_hold(out_f32);
     if constexpr (CONV) ds_hold(H, W, Wo, sy, sx, pad);
     const int j = (int)(block >> 3);
-    const int jm = j / ny, y = j - jm * ny;
+    const int jm = ds_quotient_uniform(j, ny), y = j - jm * ny;
     const int mt = jm * 8 + (int)(block & 7);
     if (mt >= max_mtiles) return;
     const int4 me = source.record(mt);
@@ -166,7 +166,7 @@ __global__ __launch_bounds__(NT * KS, residency(WMT * WNT, BK, KS, CONV, HASR)) 
         const int m = grow0 + 32 * wave + l32;
         long long rc = -1, rr = 0;
         if (m < rows_g) {
-            const int sl = m / rows;
+            const int sl = ds_quotient(m, rows);
             const int p = m - sl * rows;
             const int slot = slot0 + sl;
             const int sa = a_index ? a_index[slot] : slot;
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(NT * KS, residency(WMT * WNT, BK, KS, CONV, HASR)) 
             // byte offset of the sample (convolution) or of the row itself (linear layers)
             my_a = (uint32_t)(((long long)sa * a_ss + (CONV ? 0 : (long long)p * a_ld)) * 2);
             if constexpr (CONV) {
-                const int oy = p / Wo, ox = p - oy * Wo;
+                const int oy = ds_quotient(p, Wo), ox = p - oy * Wo;
                 my_yx = make_int2(oy * sy - pad, ox * sx - pad);
             }
             const long long pc = p + c_row0;

@@ -88,12 +88,12 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, char* smem, int y,
     if (lane < BM) {
         const int m = grow0 + lane;
         if (m < rows_g) {
-            const int sl = m / rows, p = m - sl * rows, slot = slot0 + sl;
+            const int sl = ds_quotient(m, rows), p = m - sl * rows, slot = slot0 + sl;
             const int sa = a_index ? a_index[slot] : slot;
             const int cs = c_index ? c_index[slot] : slot;
             int pix = p;
             if constexpr (CONV) {
-                const int oy = p / Wo, ox = p - oy * Wo;
+                const int oy = ds_quotient(p, Wo), ox = p - oy * Wo;
                 const int iy = oy * sy, ix = ox * sx;         // counted from the corner
                 auto inside = [&](int i, int n, int k) {      // taps t < k with pad <= i + t < pad + n
                     const int lo = pad - i > 0 ? pad - i : 0, hi = pad + n - i < k ? pad + n - i : k;

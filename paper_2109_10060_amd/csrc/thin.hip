@@ -72,7 +72,7 @@ __global__ __launch_bounds__(NT, CHAIN ? (KCH == 4 ? 2 : 3) : 1) void thin_kerne
         long long rc = -1, rr = 0;
         uint32_t ra = OOB;
         if (m < rows_g) {
-            const int sl = m / a.rows;
+            const int sl = ds_quotient(m, a.rows);
             const int p = m - sl * a.rows;
             const int slot = slot0 + sl;
             const int sa = a.a_index ? a.a_index[slot] : slot;

@@ -73,7 +73,7 @@ __device__ __forceinline__ void body(const VitTailArgs& a, const int4 me, char* 
         return Place{t & 15, t >> 4, t & 31, (t >> 5) & 1, t & 63};
     };
     constexpr uint32_t OOB = 0x80000000u;
-    const int first = grow0 / a.rows;                    // (of the group; rows of a tile count from there)
+    const int first = ds_quotient(grow0, a.rows);                    // (of the group; rows of a tile count from there)
     auto window = [](const void* p, int64_t elements) {
         return __builtin_amdgcn_make_buffer_rsrc((void*)((const bf16_t*)p + elements), 0, 0x7fffffff, 0x00020000);
     };
@@ -107,7 +107,7 @@ __device__ __forceinline__ void body(const VitTailArgs& a, const int4 me, char* 
         const __amdgpu_buffer_rsrc_t ro = window(a.o, (int64_t)(slot0 + first) * a.o_ss);
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
-            const int m = grow0 + prow + RP * i, sl = m / a.rows, p = m - sl * a.rows;
+            const int m = grow0 + prow + RP * i, sl = ds_quotient(m, a.rows), p = m - sl * a.rows;
             const bool live = m < rows_g;
             if (l16 == 0) rowx[prow + RP * i] = live ? (uint32_t)(((sl - first) * a.x_ss + (int64_t)p * de) * 2) : OOB;
             const uint32_t ooff = live ? (uint32_t)(((sl - first) * a.o_ss + (int64_t)p * a.o_ld + l16 * 8) * 2) : OOB;
@@ -511,7 +511,7 @@ __device__ __forceinline__ void body(const VitTailArgs& a, const int4 me, char* 
     uint32_t qoff[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int m = grow0 + r * 32 + q32, sl = m / a.rows;
+        const int m = grow0 + r * 32 + q32, sl = ds_quotient(m, a.rows);
         qoff[r] = m < rows_g ? (uint32_t)(((sl - first) * a.q_ss + (int64_t)(m - sl * a.rows) * a.q_ld + 8 * qhi) * 2) : OOB;
     }
     for (int p = 0; p * NW * NQ + w < 3 * nb; ++p) {

@@ -37,7 +37,7 @@ __global__ __launch_bounds__(64 * NW, DIRECT ? NW / 2 : (NW + 3) / 4) void vit_l
     bf16_t* As = (bf16_t*)smem;                          // [BM][PITCH]
     bf16_t* Ss = As + BM * PITCH;                        // [BM][SP] output stage
 
-    const int run = (int)blockIdx.x % runs;
+    const int tile = ds_quotient_uniform((int)blockIdx.x, runs), run = (int)blockIdx.x - tile * runs;
     const GroupLanes lanes(a.gt);
     const bf16_t *x = a.x, *wt = a.w, *res = a.res;
     bf16_t* y = a.y;
@@ -45,7 +45,7 @@ __global__ __launch_bounds__(64 * NW, DIRECT ? NW / 2 : (NW + 3) / 4) void vit_l
     int64_t x_ss = a.x_ss, y_ss = a.y_ss, y_seg = a.y_seg;
     int x_ld = a.x_ld, y_ld = a.y_ld, rows = a.rows, kb = a.kb, seg_blocks = a.seg_blocks, n_seg = a.n_seg, bias_seg = a.bias_seg, act = a.act;
     float eps = a.eps;
-    const int4 me = ds_tile_record_of(a.offsets, a.gt.T, rows, (int)blockIdx.x / runs, BM);
+    const int4 me = ds_tile_record_of(a.offsets, a.gt.T, rows, tile, BM);
     if constexpr (FEW)
         ds_hold(x, wt, res, y, gamma, beta, bias0, x_ss, y_ss, y_seg, x_ld, y_ld, rows, kb, seg_blocks, n_seg, bias_seg, act, eps);
     if (me.x < 0) return;
@@ -63,7 +63,11 @@ __global__ __launch_bounds__(64 * NW, DIRECT ? NW / 2 : (NW + 3) / 4) void vit_l
     if (y_ld <= 0) y_ld = k_out;
 
     bf16x8_t ring[D];
-    auto weights = [&](int p) { return weight_row(wt, ((p / nb) * seg_blocks + p % nb) * kb, kin); };
+    auto segment = [&](int p) { return (p >= nb) + (p >= 2 * nb); };       // of up to three
+    auto weights = [&](int p) {
+        const int s = segment(p);
+        return weight_row(wt, (s * seg_blocks + p - s * nb) * kb, kin);
+    };
     auto start = [&](int p, bool on = true) {            // (off: no traffic)
         const __amdgpu_buffer_rsrc_t rw = on ? weights(p) : weight_row(wt, 0, 0);
 #pragma unroll
@@ -80,7 +84,7 @@ __global__ __launch_bounds__(64 * NW, DIRECT ? NW / 2 : (NW + 3) / 4) void vit_l
         const int m = grow0 + prow + RP * i;
         live[i] = in && m < rows_g;
         const int mm = live[i] ? m : grow0;
-        const int sl = mm / rows, p = mm - sl * rows, slot = slot0 + sl;
+        const int sl = ds_quotient(mm, rows), p = mm - sl * rows, slot = slot0 + sl;
         yoff[i] = (int64_t)slot * y_ss + (int64_t)p * y_ld;
         const bf16_t* xrow = x + (int64_t)slot * x_ss + (int64_t)p * x_ld;
 #pragma unroll
@@ -185,11 +189,11 @@ __global__ __launch_bounds__(64 * NW, DIRECT ? NW / 2 : (NW + 3) / 4) void vit_l
         for (int r = 0; r < R; ++r) {
             const int m = grow0 + r * 32 + l32;
             in[r] = m < rows_g;
-            const int mm = in[r] ? m : grow0, sl = mm / rows;
+            const int mm = in[r] ? m : grow0, sl = ds_quotient(mm, rows);
             yrow[r] = y + (int64_t)(slot0 + sl) * y_ss + (int64_t)(mm - sl * rows) * y_ld;
         }
         for (int p = blk0 + w; p < blk1; p += NW) {
-            const int seg = p / nb, n0 = (p - seg * nb) * 32;
+            const int seg = segment(p), n0 = (p - seg * nb) * 32;
             f32x16_t acc[R];
             clear(acc);
             walk(acc, p);
@@ -226,7 +230,7 @@ __global__ __launch_bounds__(64 * NW, DIRECT ? NW / 2 : (NW + 3) / 4) void vit_l
     }
     // ---- column blocks, NW at a time ------------------------------------------------------------------------------------------
     for (int b0 = blk0; b0 < blk1; b0 += NW) {
-        const int p = b0 + w, seg = p / nb, n0 = (p - seg * nb) * 32;
+        const int p = b0 + w, seg = segment(p), n0 = (p - seg * nb) * 32;
         const bool on = p < blk1;
         if (res) {
             // the residual of these columns waits in the stage, where the sums are added in place; this run's columns only: res may be
@@ -286,7 +290,7 @@ __global__ __launch_bounds__(64 * NW, DIRECT ? NW / 2 : (NW + 3) / 4) void vit_l
             for (int k = 0; k < (NS + 15) / 16; ++k) {
                 const int c = k * 16 + l16, pb = b0 + (c >> 2);
                 if (!run_chunk(c, NW, b0, blk1) || !live[i]) continue;
-                const int sg = pb / nb, n = (pb - sg * nb) * 32 + (c & 3) * 8;
+                const int sg = segment(pb), n = (pb - sg * nb) * 32 + (c & 3) * 8;
                 if (n < k_out) *(uint4*)(y + yoff[i] + (int64_t)sg * y_seg + n) = *(const uint4*)(Ss + (prow + RP * i) * SP + c * 8);
             }
         if (b0 + NW < blk1) __syncthreads();             // the stage is free again

@@ -85,7 +85,7 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     // of range.  Without a branch around them the requests travel together, and the number in flight is known wherever one is waited
     // for -- behind a branch every wait for the weights' ring would be one for the rows and stores as well.
     constexpr uint32_t OOB = 0x80000000u;
-    const int first = grow0 / a.rows;                    // (of the group; rows of a tile count from there)
+    const int first = ds_quotient(grow0, a.rows);                    // (of the group; rows of a tile count from there)
     auto window = [](const void* p, int64_t elements) {
         return __builtin_amdgcn_make_buffer_rsrc((void*)((const bf16_t*)p + elements), 0, 0x7fffffff, 0x00020000);
     };
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             const bool in = BM % RP == 0 || prow + RP * i < BM;
-            const int m = grow0 + prow + RP * i, sl = m / a.rows, p = m - sl * a.rows;
+            const int m = grow0 + prow + RP * i, sl = ds_quotient(m, a.rows), p = m - sl * a.rows;
             const bool live = in && m < rows_g;
             xoff[i] = live ? (uint32_t)(((sl - first) * a.x_ss + (int64_t)p * de + l16 * 8) * 2) : OOB;
             const uint32_t ooff = live ? (uint32_t)(((sl - first) * a.o_ss + (int64_t)p * a.o_ld + l16 * 8) * 2) : OOB;
@@ -372,7 +372,7 @@ __global__ __launch_bounds__(64 * NW, (NW + 3) / 4) void vit_tail_kernel(const V
     uint32_t qoff[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int m = grow0 + r * 32 + l32, sl = m / a.rows;
+        const int m = grow0 + r * 32 + l32, sl = ds_quotient(m, a.rows);
         qoff[r] = m < rows_g ? (uint32_t)(((sl - first) * a.q_ss + (int64_t)(m - sl * a.rows) * a.q_ld + 8 * lhi) * 2) : OOB;
     }
     for (int p = w; p < 3 * nb; p += NW) {
