@@ -273,6 +273,7 @@ size_t ds_gate_partial_bytes(int32_t B, int32_t C);
 // y[b][p][c] = x[b][p][c] * scale[b][c] on the valid channels (NHWC) / y[b][c][p] (NCHW); fp32 or bf16
 int32_t ds_launch_channel_scale(const void* x, void* y, const float* scale, const int32_t* c_in, int32_t dtype,
                                 int32_t layout, int32_t B, int32_t C, int32_t HW, hipStream_t s);
+constexpr int DS_BUCKET_LISTS = 4;
 struct BucketArgs {
     const int32_t* route;     // [B]
     const int32_t* lo;        // nullable: key = route * mul + lo
@@ -280,11 +281,14 @@ struct BucketArgs {
     int32_t *perm, *inv_perm, *offsets, *slot_group;   // inv_perm, slot_group nullable
     const int32_t* inv_prev;  // with src_index: src_index[slot] = inv_prev ? inv_prev[sample] : sample
     int32_t* src_index;       // nullable
-    // optional extras done by the same launch (T <= DS_MAX_GROUPS): up to two m-tile lists for the new offsets (count, then
-    // from byte 16 on one record per tile, ds_mtile_capacity() at most; list_rows[i] rows per sample) and slot_lut[slot] = lut[group of slot]
-    int32_t n_lists, list_rows[2];
-    void* lists[2];
+    // optional extras done by the same launch (T <= DS_MAX_GROUPS): up to four m-tile lists for the new offsets (count, then
+    // from byte 16 on one record per tile, ds_mtile_capacity() at most; list_rows[i] rows per sample), slot_lut[slot] = lut[group of slot], and the
+    // routes once more: copy_to[i * copy_stride + sample], i < copies
+    int32_t n_lists, list_rows[DS_BUCKET_LISTS];
+    void* lists[DS_BUCKET_LISTS];
     int32_t* slot_lut;        // nullable
+    int32_t* copy_to;
+    int32_t copies, copy_stride;
     int32_t lut[DS_MAX_GROUPS];
 };
 int32_t ds_launch_bucket_ex(const BucketArgs& a, hipStream_t s);

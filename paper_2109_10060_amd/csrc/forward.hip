@@ -528,44 +528,61 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
         const int stride = st > 0 ? 2 : 1;
         const int rout = (rin + 2 - 3) / stride + 1;
         int32_t* route = routes_out ? routes_out + (size_t)st * Bs : p.route[st];
-        // ---- gate on the stage input (previous slot order), routes land in original sample order
+        const int crowd = (Bs + B - 1) / B;
+        // One gate for all stages: its bucket, and every stage finds its samples where the last one left them.  The launch makes the lists of all
+        // resolutions and the routes' other rows.  With a gate that copied its route and a bucket of the same routes in every stage, two launches more
+        // each -> here, us a pass, three networks in turn: DS-ResNet++ 4 / 16 / 33 / 64 / 256 images 463 / 669 / 843 / 1106 / 2874 -> 438 / 645 / 818 / 1083 / 2847.
+        const bool gated = !d.single_gate || st == 0;
+        const int own = d.single_gate ? 0 : st;                  // whose bucket
+        // a list a resolution with one gate (the first stage keeps its own), else two a stage
+        auto list = [&](int out_of) { return p.lists[out_of > 0 ? 2 * out_of + 1 : 0]; };
+        MList ml_in = {d.single_gate ? list(st - 1) : p.lists[2 * st], (int)ds_mtile_capacity(B, rin * rin, G), rin * rin, B, crowd};
+        MList ml_out = {d.single_gate ? list(st) : p.lists[2 * st + 1], (int)ds_mtile_capacity(B, rout * rout, G), rout * rout, B, crowd};
         GateArgs g;
         memset(&g, 0, sizeof(g));
-        g.x = X; g.dtype = DS_BF16; g.layout = DS_NHWC; g.B = B; g.C = c_prev_full; g.HW = rin * rin;
-        g.c_in = st > 0 ? p.slot_c : nullptr;
-        g.x_sample_stride = (int64_t)rin * rin * c_prev_full; g.x_ld = 0;
-        g.w1 = (const float*)Q[0]; g.b1 = (const float*)Q[1]; g.w2 = (const float*)Q[2]; g.b2 = (const float*)Q[3];
-        g.C_mlp = d.hidden[st]; g.T = T;
-        g.logit_bias = logit_bias ? logit_bias + (size_t)st * Bs * T : nullptr;
-        g.out_index = st > 0 ? p.perm[st - 1] : nullptr;
-        g.route_override = route_override ? route_override + (size_t)st * Bs : nullptr;
-        g.logits = p.gate_logits; g.route = route; g.partial = p.gate_partial;
-        g.splits = map_splits;
-        map_splits = 0;
-        if (d.single_gate && st > 0) {
-            // the first stage's decision stands: no pooling, no MLP, the route is copied
-            g.x = nullptr; g.logit_bias = nullptr; g.out_index = nullptr;
-            g.route_override = routes_out ? routes_out : p.route[0];
+        if (gated) {
+            // ---- gate on the stage input (previous slot order), routes land in original sample order
+            g.x = X; g.dtype = DS_BF16; g.layout = DS_NHWC; g.B = B; g.C = c_prev_full; g.HW = rin * rin;
+            g.c_in = st > 0 ? p.slot_c : nullptr;
+            g.x_sample_stride = (int64_t)rin * rin * c_prev_full; g.x_ld = 0;
+            g.w1 = (const float*)Q[0]; g.b1 = (const float*)Q[1]; g.w2 = (const float*)Q[2]; g.b2 = (const float*)Q[3];
+            g.C_mlp = d.hidden[st]; g.T = T;
+            g.logit_bias = logit_bias ? logit_bias + (size_t)st * Bs * T : nullptr;
+            g.out_index = st > 0 ? p.perm[st - 1] : nullptr;
+            g.route_override = route_override ? route_override + (size_t)st * Bs : nullptr;
+            g.logits = p.gate_logits; g.route = route; g.partial = p.gate_partial;
+            g.splits = map_splits;
+            map_splits = 0;
+            // ---- bucket by (this stage's route, previous stage's route)
+            const int32_t* route_prev = st > 0 ? (routes_out ? routes_out + (size_t)(st - 1) * Bs : p.route[st - 1]) : nullptr;
+            BucketArgs ba = {};
+            ba.route = route; ba.lo = pairs ? route_prev : nullptr; ba.mul = pairs ? T : 1; ba.B = B; ba.T = G;
+            ba.perm = p.perm[st]; ba.inv_perm = p.inv[st]; ba.offsets = p.offs[st]; ba.slot_group = p.slot_group[st];
+            ba.inv_prev = st > 0 ? p.inv[st - 1] : nullptr;
+            ba.src_index = p.src_index;          // slot of this stage -> slot of the previous stage's layout
+            // the same launch builds the tile lists and the per-slot output width of the stage
+            ba.slot_lut = p.slot_c;
+            if (pairs) {
+                ba.n_lists = 2;
+                ba.list_rows[0] = rin * rin; ba.lists[0] = ml_in.list;
+                ba.list_rows[1] = rout * rout; ba.lists[1] = ml_out.list;
+                for (int id = 0; id < G; ++id) ba.lut[id] = d.out[st * T + id / T];
+            } else {
+                static_assert(DS_BUCKET_LISTS >= 4, "a list a stage");
+                ba.n_lists = 4;
+                int q = rin;
+                for (int i = 0; i < 4; ++i) {
+                    if (i > 0) q = (q + 2 - 3) / 2 + 1;
+                    ba.list_rows[i] = q * q;
+                    ba.lists[i] = list(i);
+                }
+                if (routes_out) { ba.copies = 3; ba.copy_to = routes_out + Bs; ba.copy_stride = Bs; }
+                for (int id = 0; id < G; ++id) ba.lut[id] = d.out[3 * T + id];       // (of the last stage: only the classifier asks)
+            }
+            RC(gate_and_bucket(g, ba, s));
         }
         Q += 4;
-        // ---- bucket by (this stage's route, previous stage's route)
-        const int32_t* route_prev = st > 0 ? (routes_out ? routes_out + (size_t)(st - 1) * Bs : p.route[st - 1]) : nullptr;
-        BucketArgs ba = {};
-        ba.route = route; ba.lo = pairs ? route_prev : nullptr; ba.mul = pairs ? T : 1; ba.B = B; ba.T = G;
-        ba.perm = p.perm[st]; ba.inv_perm = p.inv[st]; ba.offsets = p.offs[st]; ba.slot_group = p.slot_group[st];
-        ba.inv_prev = st > 0 ? p.inv[st - 1] : nullptr;
-        ba.src_index = p.src_index;          // slot of this stage -> slot of the previous stage's layout
-        // the same launch builds the tile lists at both resolutions and the per-slot output width of the stage
-        const int crowd = (Bs + B - 1) / B;
-        MList ml_in = {p.lists[2 * st], (int)ds_mtile_capacity(B, rin * rin, G), rin * rin, B, crowd};
-        MList ml_out = {p.lists[2 * st + 1], (int)ds_mtile_capacity(B, rout * rout, G), rout * rout, B, crowd};
-        ba.n_lists = 2;
-        ba.list_rows[0] = rin * rin; ba.lists[0] = ml_in.list;
-        ba.list_rows[1] = rout * rout; ba.lists[1] = ml_out.list;
-        ba.slot_lut = p.slot_c;
-        for (int id = 0; id < G; ++id) ba.lut[id] = d.out[st * T + (pairs ? id / T : id)];
-        RC(gate_and_bucket(g, ba, s));
-        const int32_t* src = p.src_index;
+        const int32_t* src = gated ? p.src_index : nullptr;
         // ---- group tables: group id = q * T + q_prev
         GroupTable g1f, gpj, g1, g2, g3;
         memset(&g1f, 0, sizeof(g1f));
@@ -658,11 +675,11 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
             int32_t rest = DS_EUNSUPPORTED;        // whether the layers behind the first one have run
             if (first) {
                 const GemmArgs pj = conv_args(in, in_idx, in_ss, 0, (const bf16_t*)L[9], in_full, 1, bs, 0, rb, rb, (const float*)L[10],
-                                              (const float*)L[11], 4 * w, nullptr, Pj, (int64_t)rout * rout * 4 * w, 0, p.offs[st],
+                                              (const float*)L[11], 4 * w, nullptr, Pj, (int64_t)rout * rout * 4 * w, 0, p.offs[own],
                                               ml_out, gpj, DS_ACT_NONE);
                 // few samples: both layers that read the stage's input as one launch
                 const GemmArgs c1 = conv_args(in, in_idx, in_ss, 0, (const bf16_t*)L[0], in_full, 1, 1, 0, rb, rb, (const float*)L[1],
-                                              (const float*)L[2], w, nullptr, Y1, (int64_t)rb * rb * w, 0, p.offs[st], ml_in, g1f,
+                                              (const float*)L[2], w, nullptr, Y1, (int64_t)rb * rb * w, 0, p.offs[own], ml_in, g1f,
                                               DS_ACT_RELU);
                 const int32_t rc = ds_launch_gemm_small_pair(pj, ml_out.cap, max_out(gpj), c1, ml_in.cap, max_out(g1f), s);
                 if (rc != DS_OK && rc != DS_EUNSUPPORTED) return rc;
@@ -691,7 +708,7 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
             }
             if (!y1_ready)
                 RC(conv_gemm(in, in_idx, in_ss, 0, (const bf16_t*)L[0], in_full, 1, 1, 0, rb, rb, (const float*)L[1],
-                             (const float*)L[2], w, nullptr, Y1, (int64_t)rb * rb * w, 0, p.offs[st], first ? ml_in : ml_out,
+                             (const float*)L[2], w, nullptr, Y1, (int64_t)rb * rb * w, 0, p.offs[own], first ? ml_in : ml_out,
                              first ? g1f : g1, DS_ACT_RELU, s));
             y1_ready = false;
             if (rest != DS_OK && bs == 1) {
@@ -710,19 +727,19 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
                 if (d.tiles && bs == 1)
                     rc = ds_launch_conv3_tiled(conv_args(Y1, nullptr, (int64_t)rb * rb * w, 0, (const bf16_t*)L[3], w, 3, 1, 1, rb, rb,
                                                          (const float*)L[4], (const float*)L[5], w, nullptr, Y2, (int64_t)rout * rout * w, 0,
-                                                         p.offs[st], ml_out, g2, DS_ACT_RELU),
+                                                         p.offs[own], ml_out, g2, DS_ACT_RELU),
                                                (const bf16_t*)d.tiles[block_id], w, ml_out.cap, max_out(g2), s);
                 if (rc != DS_OK && rc != DS_EUNSUPPORTED) return rc;
                 if (rc != DS_OK)
                     RC(conv_gemm(Y1, nullptr, (int64_t)rb * rb * w, 0, (const bf16_t*)L[3], w, 3, bs, 1, rb, rb, (const float*)L[4],
-                                 (const float*)L[5], w, nullptr, Y2, (int64_t)rout * rout * w, 0, p.offs[st], ml_out, g2,
+                                 (const float*)L[5], w, nullptr, Y2, (int64_t)rout * rout * w, 0, p.offs[own], ml_out, g2,
                                  DS_ACT_RELU, s));
                 // c3 adds the shortcut; later blocks update Z in place (each element is read and written by one thread)
                 RC(conv_gemm(Y2, nullptr, (int64_t)rout * rout * w, 0, (const bf16_t*)L[6], w, 1, 1, 0, rout, rout,
                              (const float*)L[7], (const float*)L[8], 4 * w, shortcut, Z, (int64_t)rout * rout * 4 * w, 0,
-                             p.offs[st], ml_out, g3, DS_ACT_RELU, s, next_any ? &ch : nullptr, &y1_ready));
+                             p.offs[own], ml_out, g3, DS_ACT_RELU, s, next_any ? &ch : nullptr, &y1_ready));
             }
-            RC(tap_block(taps, block_id, Z, (int64_t)rout * rout * 4 * w, 0, p.perm[st], p.slot_group[st], gpj, B, rout * rout,
+            RC(tap_block(taps, block_id, Z, (int64_t)rout * rout * 4 * w, 0, p.perm[own], p.slot_group[own], gpj, B, rout * rout,
                          4 * w, s));
         }
         X = Z;
@@ -732,7 +749,7 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
         r = rout;
     }
     ActView xv = {X, nullptr, (int64_t)r * r * c_prev_full, 0};   // slot_c holds the stage-4 output widths
-    return ds_launch_head(xv, r * r, (const bf16_t*)Q[0], c_prev_full, (const float*)Q[1], d.classes, p.slot_c, p.perm[3],
+    return ds_launch_head(xv, r * r, (const bf16_t*)Q[0], c_prev_full, (const float*)Q[1], d.classes, p.slot_c, p.perm[d.single_gate ? 0 : 3],
                           logits, p.gate_partial, B, c_prev_full, s);
 }
 

@@ -15,6 +15,7 @@ namespace {
 // One image, first gate of DS-ResNet: 8.9 + 3.8 us in two launches, 10.2 in one, and a gap between launches less.
 __device__ __forceinline__ void bucket_one(const BucketArgs& a, int route) {
     const int lane = threadIdx.x & 63;
+    if (lane < a.copies) a.copy_to[lane * a.copy_stride] = route;
     int k = route * a.mul + (a.lo ? a.lo[0] : 0);
     if (k < 0 || k >= a.T) k = -1;
     for (int t = lane; t <= a.T; t += 64) a.offsets[t] = k >= 0 && t > k;
@@ -33,7 +34,7 @@ __device__ __forceinline__ void bucket_one(const BucketArgs& a, int route) {
         if (a.slot_lut) a.slot_lut[0] = a.lut[k];
     }
 }
-// Every other gate, ds_gate's among them: no bucket, and none of its 376 bytes among the launch's arguments.
+// Every other gate, ds_gate's among them: no bucket, and none of its 416 bytes among the launch's arguments.
 struct NoBucket {};
 __device__ __forceinline__ void bucket_one(const NoBucket&, int) {}
 
@@ -357,7 +358,7 @@ __global__ __launch_bounds__(GF_NT) void gate_fused_kernel(const GateArgs a, con
 __global__ __launch_bounds__(1024) void bucket64_kernel(const BucketArgs a) {
     __shared__ int cnt[16][64];                          // samples per wavefront and key of the current 1024
     __shared__ int base[65], start[65];                  // next free slot of a key; first slot of a key
-    __shared__ int pre[2][65];
+    __shared__ int pre[DS_BUCKET_LISTS][65];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int B = a.B, T = a.T;
     auto key_of = [&](int b) {
@@ -376,6 +377,8 @@ __global__ __launch_bounds__(1024) void bucket64_kernel(const BucketArgs a) {
     };
     const int k0 = tid < B ? key_of(tid) : -1;           // the first 1024 samples' keys stay in registers
     const unsigned long long m0 = same(k0);
+    for (int b = tid; a.copies > 0 && b < B; b += 1024)
+        for (int i = 0; i < a.copies; ++i) a.copy_to[(int64_t)i * a.copy_stride + b] = a.route[b];
     if (tid <= 64) base[tid] = 0;
     cnt[wave][lane] = 0;
     __syncthreads();
@@ -741,8 +744,8 @@ int32_t ds_launch_gate(const GateArgs& a, hipStream_t s, const BucketArgs* bucke
 }
 
 int32_t ds_launch_bucket_ex(const BucketArgs& a, hipStream_t s) {
-    if ((a.n_lists > 0 || a.slot_lut) && a.T > DS_MAX_GROUPS) DS_FAIL(DS_EINVAL, "route bucket: fused lists need T <= %d", DS_MAX_GROUPS);
-    if (a.n_lists < 0 || a.n_lists > 2) DS_FAIL(DS_EINVAL, "route bucket: at most two m-tile lists");
+    if ((a.n_lists > 0 || a.slot_lut || a.copies > 0) && a.T > DS_MAX_GROUPS) DS_FAIL(DS_EINVAL, "route bucket: fused lists need T <= %d", DS_MAX_GROUPS);
+    if (a.n_lists < 0 || a.n_lists > DS_BUCKET_LISTS) DS_FAIL(DS_EINVAL, "route bucket: at most %d m-tile lists", DS_BUCKET_LISTS);
     ProfScope prof(DS_K_BUCKET, s);
     if (a.T <= 64) hipLaunchKernelGGL(bucket64_kernel, dim3(1), dim3(1024), 0, s, a);
     else hipLaunchKernelGGL(bucket_kernel, dim3(1), dim3(1024), 0, s, a);

@@ -877,3 +877,34 @@ def test_resnet_tiled_filters(gpu_lib, image, B, routes, blocks, same):
         assert torch.equal(tiled, plain)
     else:
         assert relerr(host(tiled), host(plain)) < 2e-2    # (whole networks: the oracle's bound; a sum's order is 2^-24 of it and flips bf16 roundings)
+
+
+# one gate for all stages: one bucket makes the four stages' lists and the routes' four rows -- a sample bucketed by the gate itself, batches
+# within and beyond the 1024 samples of a turn, parts with rows of their own, routes out of range, which come back as they were given
+@pytest.mark.parametrize("B,parts", [(1, 1), (7, 1), (1100, 1), (40, 2)])
+def test_resnet_single_gate_bucket(gpu_lib, B, parts):
+    arch = WL.resnet_arch(image=32, blocks=(2, 2, 3, 2), routes="pp")
+    net = gpu_lib.build_resnet(arch, WL.resnet_params(arch, 9), DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(B)
+    imgs = torch.randn((B, 3, 32, 32), generator=gen, device=DEV).to(torch.bfloat16)
+    lb = torch.zeros((4, B, arch["T"]), device=DEV)
+    want = torch.arange(B, device=DEV) * 4 % arch["T"]
+    lb[0].scatter_(1, want[:, None], 50.0)
+    call = (lambda **k: gpu_lib.ds_forward(net, imgs, **k)) if parts == 1 else (lambda **k: gpu_lib.ds_forward_parts(net, imgs, parts, **k))
+    routes = torch.full((4, B), -7, dtype=torch.int32, device=DEV)
+    logits, _ = call(logit_bias=lb, routes=routes)
+    assert torch.isfinite(logits).all() and all(torch.equal(routes[s], want.int()) for s in range(4))
+    over = torch.full((4, B), -7, dtype=torch.int32, device=DEV)
+    over[0] = want.int()
+    same, r2 = call(route_override=over)
+    assert torch.equal(same, logits) and torch.equal(r2, routes)
+    # a sample's logits are its own
+    pick = B - 1
+    one, _ = gpu_lib.ds_forward(net, imgs[pick:].contiguous(), route_override=over[:, pick:].contiguous())
+    assert relerr(host(one), host(logits[pick:])) < 2e-2
+    if B > 4:
+        over[0, 2] = arch["T"] + 3
+        some, r3 = call(route_override=over)
+        keep = torch.arange(B, device=DEV) != 2
+        assert all(torch.equal(r3[s], over[0]) for s in range(4)) and relerr(host(some[keep]), host(logits[keep])) < 2e-2
