@@ -291,7 +291,7 @@ int32_t ds_sliced_mhsa(const void* x, int32_t B, int32_t N, int32_t D_e, const v
  *           fc.w bf16 [num_classes][4*w_last], fc.b fp32,
  *           optionally, per block: c2.w once more as [ceil(w/32)][18 ceil(w/32) + 1] tiles of 1 KiB (bf16; of every 32 input channels
  *             the nine taps, of a tap two halves of 16 channels, a tile [half of the 16][32 filters][8 channels]; zeros beyond the
- *             matrix, the last tile of a block of filters is not read); of blocks with stride 2 the entry is not read (any pointer). */
+ *             matrix, the last tile of a block of filters is not read). */
 #define DS_ARCH_RESNET 2
 /* DS_ARCH_VIT: pre-LN vision transformer, one route per image chosen before the patch embedding (DS-ViT).
  *   ints:   image, patch, embed, heads, head_dim, mlp, depth, tokens, T, num_classes,

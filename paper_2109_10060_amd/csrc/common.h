@@ -218,7 +218,7 @@ bool ds_gemm_small_takes(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout
 int32_t ds_launch_gemm_pair(const GemmArgs& a, int32_t mtiles_a, int32_t kout_a, const GemmArgs& b, int32_t mtiles_b, int32_t kout_b, hipStream_t s);
 // 3x3 stride-1 padding-1 layers on maps up to 59 pixels wide; DS_EUNSUPPORTED for any other shape
 int32_t ds_launch_conv3(const GemmArgs& a, int32_t max_mtiles, int32_t max_kout, hipStream_t s);
-// the same on filters in operand order (channels: as stored) without residual; DS_EUNSUPPORTED for other shapes and launches too small for it
+// the same and those of stride 2 on filters in operand order (channels: as stored), without residual; DS_EUNSUPPORTED for other shapes and where another kernel is faster
 int32_t ds_launch_conv3_tiled(const GemmArgs& a, const bf16_t* tiles, int32_t channels, int32_t max_mtiles, int32_t max_kout, hipStream_t s);
 // the rest of a bottleneck block behind its first 1x1 layer (stride 1, packed rows, slot order): 3x3 layer, last 1x1 layer with its
 // shortcut, the next block's first 1x1 layer; every one with batch-norm and ReLU.  DS_EUNSUPPORTED for shapes it is not written for and

@@ -1,4 +1,4 @@
-// conv3_kernel's layers (3x3, stride 1, padding 1, bf16, no residual) with the filters in operand order: they stream into registers, and only the
+// 3x3 layers (padding 1, bf16, no residual: conv3_kernel's of stride 1, and those of stride 2) with the filters in operand order: they stream into registers, and only the
 // input patch, staged once a chunk of 32 channels, goes through LDS.  Sums in conv3_kernel's order: chunk, tap, half of the chunk.
 //
 // What bounds it: matrix rate, while a SIMD has two wavefronts.  One wavefront alone gets an instruction out of 61 clocks where the pipe takes 32: all four
@@ -25,7 +25,8 @@ constexpr int BN = 128;
 constexpr int PITCH = CONV3_PITCH;
 constexpr int CHUNK = 18;                      // steps of a chunk: 9 taps of two 16-channel halves
 constexpr int FOLD = 32;                       // compute units of a die
-constexpr int smem_bytes(int bm) { return 2 * conv3_bytes(bm) + 2 * BN * 4; }
+constexpr int patch_bytes(int stride, int bm) { return stride == 2 ? CONV3_BYTES2 : conv3_bytes(bm); }
+constexpr int smem_bytes(int stride, int bm) { return 2 * patch_bytes(stride, bm) + 2 * BN * 4; }
 constexpr uint32_t OOB = 0x80000000u;
 
 struct Conv3T {
@@ -34,15 +35,15 @@ struct Conv3T {
 };
 
 // CW of the four wavefronts side by side, 32 filters each, 4 / CW below each other, 32 R pixels each; DS steps of filters on their way, pixels read FA - 1 steps ahead
-template <int R, int CW, int DS, int FA>
+template <int S, int R, int CW, int DS, int FA>
 __device__ __forceinline__ void body(const GemmArgs& a, const Conv3T& t, const int g0, const int slot0, const int rows_g, const int n0, const int k_in, const int k_out, const int row, char* smem) {
-    constexpr int NW = 4, RW = NW / CW, BM = 32 * R * RW, RMAX = conv3_pixels(BM), PB = conv3_bytes(BM), NT = 64 * NW, NI = (RMAX + 16 * NW - 1) / (16 * NW), NC = (NI + 3) / 4;
+    constexpr int NW = 4, RW = NW / CW, BM = 32 * R * RW, RMAX = S == 2 ? CONV3_PIXELS2 : conv3_pixels(BM), PB = patch_bytes(S, BM), NT = 64 * NW, NI = (RMAX + 16 * NW - 1) / (16 * NW), NC = (NI + 3) / 4;
     static_assert(CHUNK % DS == 0 && CHUNK % FA == 0, "whole turns");
     float* scl = (float*)(smem + 2 * PB);    // [BN] scale, then [BN] shift
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int cw = w % CW, rw = w / CW;
-    const int W = a.W, H = a.H, Q = W + 1, rows = a.rows;
-    const float r_rows = __builtin_amdgcn_rcpf((float)rows), r_w = __builtin_amdgcn_rcpf((float)W), r_q = __builtin_amdgcn_rcpf((float)Q), r_h = __builtin_amdgcn_rcpf((float)(H + 1));
+    const int W = a.W, H = a.H, Wo = a.Wo, Q = S == 2 ? conv3_pitch2(W) : W + 1, rows = a.rows;
+    const float r_rows = __builtin_amdgcn_rcpf((float)rows), r_w = __builtin_amdgcn_rcpf((float)Wo), r_q = __builtin_amdgcn_rcpf((float)Q), r_h = __builtin_amdgcn_rcpf((float)(H + 1));
     static_assert(NT >= BN, "a lane a column");
     float vs = 1.f, vh = 0.f;
     if (tid < BN && n0 + tid < k_out) {
@@ -56,12 +57,13 @@ __device__ __forceinline__ void body(const GemmArgs& a, const Conv3T& t, const i
     const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void*)(t.w + (int64_t)blk * t.ntile * 512), 0, blk * 32 < k_out ? t.ntile * 1024 : 0, 0x00020000);
     const uint32_t lane16 = (uint32_t)lane * 16;
     const int nchunk = (k_in + 31) / 32;
+    // padded index of tap (0, 0) of a pixel
     auto padded = [&](int m) {
-        const int sl = quotient22(m, rows, r_rows), p = m - sl * rows, y = quotient22(p, W, r_w);
-        return conv3_padded(sl, y, p - y * W, W, H);
+        const int sl = quotient22(m, rows, r_rows), p = m - sl * rows, y = quotient22(p, Wo, r_w);
+        return S == 2 ? conv3_padded2(sl, y, p - y * Wo, W, H) : conv3_padded(sl, y, p - y * W, W, H) - (Q + 1);
     };
-    const int first = padded(g0) - (Q + 1), span = padded(min(g0 + BM, rows_g) - 1) + Q + 2 - first;
-    const int RB = W * PITCH + CONV3_GAP, row0 = quotient22(first, Q, r_q);
+    const int first = padded(g0), span = padded(min(g0 + BM, rows_g) - 1) + 2 * Q + 3 - first;
+    const int RB = W * PITCH + CONV3_GAP, row0 = S == 2 ? 0 : quotient22(first, Q, r_q);
     uint32_t poff[NI];
     int loff[NI];
     {
@@ -71,8 +73,8 @@ __device__ __forceinline__ void body(const GemmArgs& a, const Conv3T& t, const i
             const int j = 16 * w + 16 * NW * (4 * k + (lane >> 4)) + (lane & 15), P = first + j;
             const int pr = quotient22(P, Q, r_q), x = P - pr * Q - 1, sl = quotient22(pr, H + 1, r_h), y = pr - sl * (H + 1) - 1, p = y * W + x;
             o[k] = OOB;
-            l[k] = (uint32_t)(j < span ? conv3_byte(pr, x + 1, row0, W) : -1);
-            if (j < span && x >= 0 && y >= 0 && sl * rows + p < rows_g) {
+            l[k] = (uint32_t)(j < span ? (S == 2 ? conv3_byte2(P, first) : conv3_byte(pr, x + 1, row0, W)) : -1);
+            if (j < span && x >= 0 && x < W && y >= 0 && sl * rows < rows_g) {
                 const int slot = slot0 + sl, sa = a.a_index ? a.a_index[slot] : slot;
                 o[k] = ((uint32_t)sa * (uint32_t)a.a_sample_stride + (uint32_t)(p * a_ld)) * 2;
             }
@@ -96,10 +98,12 @@ __device__ __forceinline__ void body(const GemmArgs& a, const Conv3T& t, const i
         for (int i = 0; i < NI; ++i)
             if (loff[i] >= 0) *(uint4*)(smem + buf * PB + loff[i]) = pv[i];
     };
-    // the zeros behind a map row (those ahead of it come with the patch)
-    const int nrow = quotient22(first + span - 1, Q, r_q) - row0 + 1;
-    for (int i = tid; i < nrow * 8; i += NT)
-        *(uint4*)(smem + (i >> 2 & 1) * PB + (i >> 3) * RB + (W + 1) * PITCH + (i & 3) * 16) = make_uint4(0, 0, 0, 0);
+    if constexpr (S == 1) {
+        // the zeros behind a map row (those ahead of it come with the patch)
+        const int nrow = quotient22(first + span - 1, Q, r_q) - row0 + 1;
+        for (int i = tid; i < nrow * 8; i += NT)
+            *(uint4*)(smem + (i >> 2 & 1) * PB + (i >> 3) * RB + (W + 1) * PITCH + (i & 3) * 16) = make_uint4(0, 0, 0, 0);
+    }
     bf16x8_t ring[DS];
     uint32_t vo[2], vn[2];                             // of the chunk at hand, of the next one: nothing behind the slice
     auto reach = [&](uint32_t (&v)[2], int c) {
@@ -121,8 +125,8 @@ __device__ __forceinline__ void body(const GemmArgs& a, const Conv3T& t, const i
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int m = g0 + (rw * R + r) * 32 + l32;
-        const int P = (m < rows_g ? padded(m) : padded(g0)) - (Q + 1), pr = quotient22(P, Q, r_q);
-        base[r] = conv3_byte(pr, P - pr * Q, row0, W) + lhi * 16;
+        const int P = m < rows_g ? padded(m) : first, pr = S == 2 ? 0 : quotient22(P, Q, r_q);
+        base[r] = (S == 2 ? conv3_byte2(P, first) : conv3_byte(pr, P - pr * Q, row0, W)) + lhi * 16;
     }
     f32x16_t acc[R];
 #pragma unroll
@@ -137,7 +141,7 @@ __device__ __forceinline__ void body(const GemmArgs& a, const Conv3T& t, const i
         bf16x8_t f[FA][R];
         auto read = [&](int s, int r) __attribute__((always_inline)) {
             const int u = s / 6, v = s / 2 % 3, kk = s & 1;
-            f[s % FA][r] = *(const bf16x8_t*)(cur + base[r] + u * RB + v * PITCH + kk * 32);
+            f[s % FA][r] = *(const bf16x8_t*)(cur + base[r] + (S == 2 ? conv3_tap2(u, v, W) : u * RB + v * PITCH) + kk * 32);
         };
 #pragma unroll
         for (int s = 0; s < FA - 1; ++s)
@@ -195,7 +199,7 @@ __device__ __forceinline__ void body(const GemmArgs& a, const Conv3T& t, const i
     });
 }
 
-template <int BM>
+template <int S, int BM>
 __global__ __launch_bounds__(256, 2) void conv3_tiled_kernel(const GemmArgs a, const Conv3T t) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const GroupLanes lanes(a.gt);
@@ -222,21 +226,21 @@ __global__ __launch_bounds__(256, 2) void conv3_tiled_kernel(const GemmArgs a, c
     const int k_in = __builtin_amdgcn_readlane(ki, q), k_out = __builtin_amdgcn_readlane(ko, q), row = lanes.row(T - 1 - q);
     // (up to 64 filters left: two wavefronts side by side, so that none is without)
     if constexpr (BM == 128) {
-        if (k_out - n0 > 64) body<4, 4, 9, 3>(a, t, g0, slot0, rows_g, n0, k_in, k_out, row, smem);
-        else body<2, 2, 9, 3>(a, t, g0, slot0, rows_g, n0, k_in, k_out, row, smem);
+        if (k_out - n0 > 64) body<S, 4, 4, 9, 3>(a, t, g0, slot0, rows_g, n0, k_in, k_out, row, smem);
+        else body<S, 2, 2, 9, 3>(a, t, g0, slot0, rows_g, n0, k_in, k_out, row, smem);
     } else {
-        if (k_out - n0 > 64) body<2, 4, 18, 3>(a, t, g0, slot0, rows_g, n0, k_in, k_out, row, smem);
-        else body<1, 2, 18, 3>(a, t, g0, slot0, rows_g, n0, k_in, k_out, row, smem);
+        if (k_out - n0 > 64) body<S, 2, 4, 18, 3>(a, t, g0, slot0, rows_g, n0, k_in, k_out, row, smem);
+        else body<S, 1, 2, 18, 3>(a, t, g0, slot0, rows_g, n0, k_in, k_out, row, smem);
     }
 }
 
-template <int BM>
+template <int S, int BM>
 int32_t launch(const GemmArgs& a, const Conv3T& t, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
-    const int32_t rc = ds_reserve_lds((const void*)conv3_tiled_kernel<BM>, smem_bytes(BM), "sliced 3x3 conv on tiled filters");
+    const int32_t rc = ds_reserve_lds((const void*)conv3_tiled_kernel<S, BM>, smem_bytes(S, BM), "sliced 3x3 conv on tiled filters");
     if (rc) return rc;
     const int die = (max_mtiles + 7) / 8 * (DS_GEMM_BM / BM) * ((max_kout + BN - 1) / BN);
     ProfScope prof(DS_K_CONV3, s);
-    hipLaunchKernelGGL(conv3_tiled_kernel<BM>, dim3((unsigned)(8 * die)), dim3(256), smem_bytes(BM), s, a, t);
+    hipLaunchKernelGGL((conv3_tiled_kernel<S, BM>), dim3((unsigned)(8 * die)), dim3(256), smem_bytes(S, BM), s, a, t);
     DS_CHECK_LAUNCH("sliced 3x3 conv on tiled filters");
     return DS_OK;
 }
@@ -251,14 +255,23 @@ int32_t launch(const GemmArgs& a, const Conv3T& t, int32_t max_mtiles, int32_t m
 // of wavefronts does not change that (838 and 849 a pass).
 // Tiles of 64 pixels until there are enough of 128 to go round: DS-ResNet 128 / 160 / 256 images, 256 in four parts, the line at 500 workgroups of 128 x 64 1430 / 1639 / 2337 / 2300,
 // at 700 1423 / 1632 / 2333 / 2302, at 1200 1432 / 1653 / 2347 / 2295, at 1700 1432 / 1652 / 2372 / 2314.
+// Stride 2, where gemm_kernel gathers the input of each tap again: us a launch, there / here, 256 images, 128 to 256 channels 50 / 48, 512 58 / 47, 33 images of
+// DS-ResNet++ 22 / 18, 25 (gemm_small_kernel) / 19, 28 / 29.  Up to 128 filters gemm_kernel reads the input once as well and here 64 pixels of it feed one column tile only:
+// 256 images 70 / 73, so from 768 row tiles on it stays there.  us a pass: DS-ResNet 64 / 96 / 256 images 1011 / 1200 / 2457 -> 989 / 1171 / 2433, 256 in four
+// parts 2336 -> 2322, DS-ResNet++ 33 / 256 images 813 / 2815 -> 803 / 2775.
 int32_t ds_launch_conv3_tiled(const GemmArgs& a, const bf16_t* tiles, int32_t channels, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
-    if (a.K != 3 || a.stride != 1 || a.pad != 1 || a.n_seg != 1 || a.Ho != a.H || a.Wo != a.W || a.rows != a.H * a.W || a.R || !conv_result(a) || !a.offsets)
+    if (a.K != 3 || a.Kw > 3 || (a.stride != 1 && a.stride != 2) || a.stride_w > 0 || a.pad != 1 || a.n_seg != 1 || a.Ho != (a.H - 1) / a.stride + 1 ||
+        a.Wo != (a.W - 1) / a.stride + 1 || a.rows != a.Ho * a.Wo || a.R || !conv_result(a) || !a.offsets)
         return DS_EUNSUPPORTED;
     // quotients in fp32, byte offsets of 31 bits
-    if (a.B <= 0 || (int64_t)a.B * (a.H + 1) * (a.W + 1) >= 1 << 21 || (int64_t)a.B * a.a_sample_stride * 2 >= 0x7fffffffLL) return DS_EUNSUPPORTED;
-    if (!conv3_fits(128, a.W, a.H) || !conv3_fits(64, a.W, a.H)) return DS_EUNSUPPORTED;
-    if ((int64_t)a.B * a.rows / 32 * ((max_kout + 31) / 32) <= 600 && ds_gemm_small_takes(a, max_mtiles, max_kout)) return DS_EUNSUPPORTED;
+    if (a.B <= 0 || (int64_t)a.B * (a.H + 1) * (a.W + 3) >= 1 << 21 || (int64_t)a.B * a.a_sample_stride * 2 >= 0x7fffffffLL) return DS_EUNSUPPORTED;
+    if (a.stride == 1 ? !conv3_fits(128, a.W, a.H) || !conv3_fits(64, a.W, a.H) : !conv3_fits2(a.W, a.H)) return DS_EUNSUPPORTED;
+    const int64_t small = (int64_t)a.B * a.rows / 32 * ((max_kout + 31) / 32);
+    if (small <= 600 && ds_gemm_small_takes(a, max_mtiles, max_kout)) return DS_EUNSUPPORTED;
     const Conv3T t = {tiles, (channels + 31) / 32 * CHUNK + 1};
-    const int64_t wgs = (int64_t)max_mtiles * ((max_kout + 63) / 64) * (a.crowd > 1 ? a.crowd : 1);
-    return wgs > 700 ? launch<128>(a, t, max_mtiles, max_kout, s) : launch<64>(a, t, max_mtiles, max_kout, s);
+    const int64_t crowd = a.crowd > 1 ? a.crowd : 1;
+    if (a.stride == 2 && max_kout <= BN && max_mtiles * crowd >= 768) return DS_EUNSUPPORTED;
+    if (a.stride == 2) return launch<2, 64>(a, t, max_mtiles, max_kout, s);
+    const int64_t wgs = (int64_t)max_mtiles * ((max_kout + 63) / 64) * crowd;
+    return wgs > 700 ? launch<1, 128>(a, t, max_mtiles, max_kout, s) : launch<1, 64>(a, t, max_mtiles, max_kout, s);
 }

@@ -724,8 +724,8 @@ int32_t forward_rn(const ds_net* net, const RnDesc& d, const bf16_t* images, int
                 }
             } else {
                 int32_t rc = DS_EUNSUPPORTED;
-                if (d.tiles && bs == 1)
-                    rc = ds_launch_conv3_tiled(conv_args(Y1, nullptr, (int64_t)rb * rb * w, 0, (const bf16_t*)L[3], w, 3, 1, 1, rb, rb,
+                if (d.tiles)
+                    rc = ds_launch_conv3_tiled(conv_args(Y1, nullptr, (int64_t)rb * rb * w, 0, (const bf16_t*)L[3], w, 3, bs, 1, rb, rb,
                                                          (const float*)L[4], (const float*)L[5], w, nullptr, Y2, (int64_t)rout * rout * w, 0,
                                                          p.offs[own], ml_out, g2, DS_ACT_RELU),
                                                (const bf16_t*)d.tiles[block_id], w, ml_out.cap, max_out(g2), s);

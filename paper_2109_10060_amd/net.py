@@ -143,12 +143,12 @@ def build_resnet(arch: dict, p: dict, device="cuda:0") -> Net:
                 t.append(_ohwi(p[f"{pre}.{c}.w"], device))
                 t += list(_fold(p[f"{pre}.{c}.bn"], eps, device))
     t += [_dev(p["fc.w"], bf, device), _dev(p["fc.b"], f32, device)]
-    # the 3x3 filters of stride 1 once more in operand order (the first blocks' entries behind the first stage are not read)
+    # the 3x3 filters once more in operand order
     at = 3
-    for s, nb in enumerate(arch["blocks"]):
+    for nb in arch["blocks"]:
         at += 4
         for b in range(nb):
-            t.append(_conv3_tiles(t[at + 3]) if s == 0 or b > 0 else t[at + 3])
+            t.append(_conv3_tiles(t[at + 3]))
             at += 12 if b == 0 else 9
     return Net(DS_ARCH_RESNET, ints, t, arch["num_classes"], 4, T)
 

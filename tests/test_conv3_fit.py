@@ -41,7 +41,30 @@ int main() {
                     }
                 }
             }
-    return fit > 500 ? 0 : (printf("%d shapes\n", fit), 1);
+    int fit2 = 0;
+    for (int w = 1; w <= 64; ++w)
+        for (int h = 1; h <= 64; h += h < 10 ? 1 : 5) {
+            if (!conv3_fits2(w, h)) continue;
+            ++fit2;
+            const int wo = (w - 1) / 2 + 1, ho = (h - 1) / 2 + 1, rows = wo * ho, q = conv3_pitch2(w);
+            auto padded = [&](int m) { return conv3_padded2(m / rows, m % rows / wo, m % rows % wo, w, h); };
+            for (int g0 = 0; g0 < 2 * rows + 128; ++g0) {
+                const int first = padded(g0), last = padded(g0 + 63) + 2 * q + 2;
+                if (first & 1 || last - first + 1 > CONV3_PIXELS2) return printf("stride 2 %dx%d at %d: %d pixels\n", w, h, g0, last - first + 1), 1;
+                for (int m = g0; m < g0 + 64; ++m)
+                    for (int u = 0; u < 3; ++u)
+                        for (int v = 0; v < 3; ++v) {
+                            const int p = padded(m) + u * q + v, at = conv3_byte2(padded(m), first) + conv3_tap2(u, v, w);
+                            // the pixel's place in the patch, and its map pixel or zeros as the loader has it
+                            const int iy = 2 * (m % rows / wo) + u - 1, ix = 2 * (m % rows % wo) + v - 1, s = m / rows, pr = p / q;
+                            if (p < first || p > last || at != conv3_byte2(p, first) || at + 64 > CONV3_BYTES2) return printf("stride 2 %dx%d at %d: tap of %d\n", w, h, g0, m), 1;
+                            const int ls = pr / (h + 1), ly = pr % (h + 1) - 1, lx = p % q - 1;
+                            const bool in = iy >= 0 && iy < h && ix >= 0 && ix < w, have = lx >= 0 && lx < w && ly >= 0;
+                            if (in != have || (in && (ls != s || ly != iy || lx != ix))) return printf("stride 2 %dx%d at %d: pixel of %d\n", w, h, g0, m), 1;
+                        }
+            }
+        }
+    return fit > 500 && fit2 > 500 ? 0 : (printf("%d %d shapes\n", fit, fit2), 1);
 }
 """
 

@@ -850,11 +850,11 @@ def test_attention_halves_have_the_bits_of_the_whole(gpu_lib, big, B):
 
 
 # 3x3 layers on tiled filters against those on the row-major ones: tiles of 64 and of 128 pixels, of one sample's rows and across samples, maps of 28x28
-# to 3x4 pixels' width, slices that end inside a 32-channel chunk and inside a block of 32 filters, routes that end early; where conv3_kernel has one share
-# the same bits, with shares or gemm_small_kernel one more order of fp32 sums in bf16 layers.  Filters behind the widest slice in use may hold anything.
-@pytest.mark.parametrize("image,B,routes,blocks,same", [(224, 150, "width", (1, 1, 2, 2), True), (224, 60, "pp", (2, 2, 3, 2), False), (112, 230, "pp", (2, 3, 2, 2), False),
-                                                        (104, 33, "depth", (1, 2, 3, 2), False), (96, 300, "width", (1, 2, 2, 2), False)])
-def test_resnet_tiled_filters(gpu_lib, image, B, routes, blocks, same):
+# to 3x4 pixels' width, stride 1 and 2, slices that end inside a 32-channel chunk and inside a block of 32 filters, routes that end early; another order of
+# fp32 sums in bf16 layers.  Filters behind the widest slice in use may hold anything.
+@pytest.mark.parametrize("image,B,routes,blocks", [(224, 150, "width", (1, 1, 2, 2)), (224, 60, "pp", (2, 2, 3, 2)), (112, 230, "pp", (2, 3, 2, 2)),
+                                                   (104, 33, "depth", (1, 2, 3, 2)), (96, 300, "width", (1, 2, 2, 2))])
+def test_resnet_tiled_filters(gpu_lib, image, B, routes, blocks):
     arch = WL.resnet_arch(image=image, blocks=blocks, routes=routes)
     p = WL.resnet_params(arch, image + B)
     T, top = arch["T"], arch["T"] - 2                     # the widest route stays out (of "depth": the deepest of the widest slices)
@@ -873,10 +873,7 @@ def test_resnet_tiled_filters(gpu_lib, image, B, routes, blocks, same):
     net.c_struct.n_params -= sum(blocks)
     plain, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
     assert torch.isfinite(plain).all() and plain.abs().max() > 0
-    if same:
-        assert torch.equal(tiled, plain)
-    else:
-        assert relerr(host(tiled), host(plain)) < 2e-2    # (whole networks: the oracle's bound; a sum's order is 2^-24 of it and flips bf16 roundings)
+    assert relerr(host(tiled), host(plain)) < 2e-2        # (whole networks: the oracle's bound; a sum's order is 2^-24 of it and flips bf16 roundings)
 
 
 # one gate for all stages: one bucket makes the four stages' lists and the routes' four rows -- a sample bucketed by the gate itself, batches
