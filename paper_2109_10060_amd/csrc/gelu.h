@@ -10,14 +10,15 @@ __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + e
 // and two branches a value, gelu_poly 15.  (A shorter polynomial, with a check that its bf16 result is that of erff and erff itself where
 // that is open, cost 16 and the check: of the groups of 64 lanes x 4 values one in twelve was done over.)
 // the values outside the range again, one erff after the other (a loop: the code of a kernel holds many such groups)
-template <int SCALE = 1>
+template <bool HALF = false>
 __device__ __forceinline__ uint2 gelu_bf16x4_far(uint2 q, float x0, float x1, float x2, float x3) {
-    const uint2 far = make_uint2((fabsf(x0) > GELU_LIMIT ? 0xffffu : 0u) | (fabsf(x1) > GELU_LIMIT ? 0xffff0000u : 0u),
-                                 (fabsf(x2) > GELU_LIMIT ? 0xffffu : 0u) | (fabsf(x3) > GELU_LIMIT ? 0xffff0000u : 0u));
+    constexpr float LIMIT = HALF ? GELU_LIMIT / 2 : GELU_LIMIT;
+    const uint2 far = make_uint2((fabsf(x0) > LIMIT ? 0xffffu : 0u) | (fabsf(x1) > LIMIT ? 0xffff0000u : 0u),
+                                 (fabsf(x2) > LIMIT ? 0xffffu : 0u) | (fabsf(x3) > LIMIT ? 0xffff0000u : 0u));
     float y0 = 0.f, y1 = 0.f, y2 = 0.f, y3 = 0.f;
 #pragma unroll 1
     for (int i = 0; i < 4; ++i) {
-        const float y = SCALE * gelu_erf(x0);
+        const float y = gelu_erf(HALF ? 2.f * x0 : x0);
         x0 = x1, x1 = x2, x2 = x3;
         y0 = y1, y1 = y2, y2 = y3, y3 = y;
     }

@@ -21,10 +21,22 @@ constexpr float GELU_P[GELU_TERMS] = {0.19400054216384888f, -0.01373322121798992
                                       9.342209523310885e-06f, -6.737686817359645e-07f, 4.3392351045667965e-08f, -2.5126627445359873e-09f,
                                       1.3000769905069376e-10f, -6.042295136454712e-12f, 3.1192103479120437e-13f, -1.460037636852405e-14f};
 
+// The steps of a value, 0 .. GELU_TERMS; the last one leaves the result in p.  HALF: of x / 2 in place of x, an instruction less.  With the terms' powers of
+// four in the constants every sum is the other one's times a power of two, and so the result is the same bits (|x| < 2^-125: to the last of a subnormal).
+constexpr float gelu_term(int i, bool half) { return half ? GELU_P[i] * (float)(4u << 2 * i) : GELU_P[i]; }
+template <bool HALF>
+GELU_FN void gelu_step(int l, float x, float& u, float& s, float& p) {
+    if (l == 0) {
+        u = x * x;
+        s = fmaf(x, x, HALF ? -GELU_MIDDLE / 4 : -GELU_MIDDLE);
+        p = gelu_term(GELU_TERMS - 1, HALF);
+    } else if (l < GELU_TERMS) p = fmaf(p, s, gelu_term(GELU_TERMS - 1 - l, HALF));
+    else p = fmaf(u, p, HALF ? x : 0.5f * x);
+}
+
 GELU_FN float gelu_poly(float x) {
-    const float u = x * x, s = fmaf(x, x, -GELU_MIDDLE);
-    float p = GELU_P[GELU_TERMS - 1];
+    float u, s, p;
 #pragma GCC unroll 16
-    for (int i = GELU_TERMS - 2; i >= 0; --i) p = fmaf(p, s, GELU_P[i]);
-    return fmaf(u, p, 0.5f * x);
+    for (int l = 0; l <= GELU_TERMS; ++l) gelu_step<false>(l, x, u, s, p);
+    return p;
 }

@@ -260,7 +260,7 @@ __device__ __forceinline__ void body(const VitTailArgs& a, const int4 me, char* 
         wave_sync();
     };
     // As (bf16) += acc2 + bias on the elements this lane accumulated
-    auto add_columns = [&](float scale, float cst, float cst2) {
+    auto add_columns = [&](float cst, float cst2) {
         const auto [l16, prow, l32, lhi, lane] = place();
         to_line(cst, cst2);
 #pragma unroll
@@ -275,7 +275,7 @@ __device__ __forceinline__ void body(const VitTailArgs& a, const int4 me, char* 
                     uint2* p = (uint2*)(As + (r * 32 + l32) * PA + ch);
                     const uint2 res = *p;
                     const f32x16_t& t = acc2[b][r];
-                    float v0 = fmaf(t[4 * q], scale, h.x), v1 = fmaf(t[4 * q + 1], scale, h.y), v2 = fmaf(t[4 * q + 2], scale, h.z), v3 = fmaf(t[4 * q + 3], scale, h.w);
+                    float v0 = t[4 * q] + h.x, v1 = t[4 * q + 1] + h.y, v2 = t[4 * q + 2] + h.z, v3 = t[4 * q + 3] + h.w;
                     v0 += __uint_as_float(res.x << 16);
                     v1 += __uint_as_float(res.x & 0xffff0000u);
                     v2 += __uint_as_float(res.y << 16);
@@ -381,7 +381,7 @@ __device__ __forceinline__ void body(const VitTailArgs& a, const int4 me, char* 
     __syncthreads();                                     // every wavefront is past its last read of the attention output
     to_tile(xr);
     __syncthreads();
-    add_columns(1.0f, cst, cst2);
+    add_columns(cst, cst2);
     __syncthreads();
     norm_rows(true);
     __syncthreads();
@@ -410,17 +410,18 @@ __device__ __forceinline__ void body(const VitTailArgs& a, const int4 me, char* 
     };
     f32x16_t acc1[1][R];
     uint2 o[4][R];                                       // hidden values of this lane, 4 a piece
-    float top;                                           // the largest value of the lane
+    float top;                                           // half of the largest value of the lane
     auto make = [&](int hc, const Stream& next) __attribute__((always_inline)) {
         const int l32 = place().l32;
         cst = columns(b1, (hc * NW + w) * 32 + l32, hid);
         walk(acc1, fc1(hc), next, all, As, PA);
-        to_line(cst, 0.f);
+        to_line(-0.5f * cst, 0.f);                      // (see activate)
         top = 0.f;
     };
-    // Part m of the NB R parts of piece s (4 consecutive columns of a row): bias, twice the GELU (a multiplication less; the sums of fc2 are
-    // halved where its bias is added, with the same bits) and rounding, the four values side by side.  One value at
-    // a time is a chain of dependent instructions, and as a whole a piece would leave the matrix pipe idle.
+    // Part m of the NB R parts of piece s (4 consecutive columns of a row): bias, gelu_poly and rounding, the four values side by side.  One value at
+    // a time is a chain of dependent instructions, and as a whole a piece would leave the matrix pipe idle.  The values are halved where sum and bias meet and
+    // gelu_step starts from the halves: the same bits, where a multiplication a value at its end cost 256 images of DS-ViT 0.8 % (2145 us a pass).  (The line
+    // holds minus the half bias: with a plus the compiler adds to the bias's registers and has to move the sums, 56 of them through scratch.)
     float gu[4], gv[4], gp[4];
     auto activate = [&](int s, int m) __attribute__((always_inline)) {
         constexpr int LEVELS = GELU_TERMS + 1, M = NB * R;
@@ -430,39 +431,31 @@ __device__ __forceinline__ void body(const VitTailArgs& a, const int4 me, char* 
         for (int l = m * LEVELS / M; l < (m + 1) * LEVELS / M; ++l) {
             if (l == 0) {
                 const float4 h = bias_of(0, q);
-                t[4 * q] += h.x, t[4 * q + 1] += h.y, t[4 * q + 2] += h.z, t[4 * q + 3] += h.w;
+                t[4 * q] = fmaf(t[4 * q], 0.5f, -h.x), t[4 * q + 1] = fmaf(t[4 * q + 1], 0.5f, -h.y);
+                t[4 * q + 2] = fmaf(t[4 * q + 2], 0.5f, -h.z), t[4 * q + 3] = fmaf(t[4 * q + 3], 0.5f, -h.w);
                 top = fmaxf(fmaxf(top, fabsf(t[4 * q])), fabsf(t[4 * q + 1]));
                 top = fmaxf(fmaxf(top, fabsf(t[4 * q + 2])), fabsf(t[4 * q + 3]));
+            }
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float x = t[4 * q + e];
-                    gu[e] = x * x;
-                    gv[e] = fmaf(x, x, -GELU_MIDDLE);
-                    gp[e] = 2 * GELU_P[GELU_TERMS - 1];
-                }
-            } else if (l < GELU_TERMS) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) gp[e] = fmaf(gp[e], gv[e], 2 * GELU_P[GELU_TERMS - 1 - l]);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) gp[e] = fmaf(gu[e], gp[e], t[4 * q + e]);
+            for (int e = 0; e < 4; ++e) gelu_step<true>(l, t[4 * q + e], gu[e], gv[e], gp[e]);
+            if (l == GELU_TERMS) {
                 o[q][r] = make_uint2(f2bf2(gp[0], gp[1]), f2bf2(gp[2], gp[3]));
                 asm volatile("" : "+v"(o[q][r].x), "+v"(o[q][r].y));
             }
         }
         asm volatile("" : "+v"(gp[0]), "+v"(gp[1]), "+v"(gp[2]), "+v"(gp[3]), "+v"(top));     // (here, and not where it is used)
     };
-    // hidden values outside the polynomial's range, and all of them to the tile
+    // hidden values outside the polynomial's range (from their halves), and all of them to the tile
     auto to_hidden = [&](int hc) __attribute__((always_inline)) {
         const auto [l16, prow, l32, lhi, lane] = place();
-        if (top > GELU_LIMIT) {
+        if (top > GELU_LIMIT / 2) {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     const f32x16_t& t = acc1[0][r];
-                    if (gelu_top(t[4 * q], t[4 * q + 1], t[4 * q + 2], t[4 * q + 3]) > GELU_LIMIT)
-                        o[q][r] = gelu_bf16x4_far<2>(o[q][r], t[4 * q], t[4 * q + 1], t[4 * q + 2], t[4 * q + 3]);
+                    if (gelu_top(t[4 * q], t[4 * q + 1], t[4 * q + 2], t[4 * q + 3]) > GELU_LIMIT / 2)
+                        o[q][r] = gelu_bf16x4_far<true>(o[q][r], t[4 * q], t[4 * q + 1], t[4 * q + 2], t[4 * q + 3]);
                 }
         }
         if ((hc * NW + w) * 32 + 32 > hid) {
@@ -496,7 +489,7 @@ __device__ __forceinline__ void body(const VitTailArgs& a, const int4 me, char* 
     walk_tile(fc2(nchunk - 1), qkv(0), some, [](int, int) {});
     both(b2, cst, cst2);
     __syncthreads();
-    add_columns(0.5f, cst, cst2);
+    add_columns(cst, cst2);
     if (more)
         for (int i = tid; i < de; i += 64 * NW) {
             gs[i] = a.g1[i];

@@ -56,3 +56,36 @@ def test_short_gelu_is_inside_its_slack(tmp_path):
     assert 1e-8 < error < 1.6e-7
     # the bounds lo and hi round once each: half an ulp of a value below |x|
     assert error + ERF_FORM + 2.0 ** -24 < slack
+
+
+HALVES = r"""
+#include <cstdint>
+#include <cstdio>
+#include <cstring>
+#include "gelu_poly.h"
+
+static float value(uint32_t b) { float x; memcpy(&x, &b, 4); return x; }
+
+int main() {
+    uint32_t hi;
+    const float limit = GELU_LIMIT;
+    memcpy(&hi, &limit, 4);
+    for (uint32_t b = 0x01000000u; b <= hi; b += b < 0x38000000u ? 997 : 7)          // from 2^-125 on
+        for (int minus = 0; minus < 2; ++minus) {
+            const float x = minus ? -value(b) : value(b), want = gelu_poly(x);
+            float u, s, p;
+            for (int l = 0; l <= GELU_TERMS; ++l) gelu_step<true>(l, 0.5f * x, u, s, p);
+            if (memcmp(&p, &want, 4)) return printf("%.9g: %.9g %.9g\n", x, p, want), 1;
+        }
+}
+"""
+
+
+# transformer blocks evaluate it from half of a value (gelu_step<true>): the same bits, and nothing on the way is larger than the value
+def test_halves_have_the_bits_of_the_values(tmp_path):
+    src, exe = tmp_path / "halves.cpp", tmp_path / "halves"
+    src.write_text(HALVES)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-march=native", "-ffp-contract=off", "-I",
+                    os.path.join(ROOT, "paper_2109_10060_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout

@@ -771,6 +771,32 @@ def test_vit_two_workgroups(gpu_lib, embed):
     assert torch.equal(torch.isnan(got[odd]), torch.isnan(want[odd])) and torch.equal(got[~odd], want[~odd])
 
 
+# the same where hidden values, or their products with the weights of fc2, reach 2^127 and stay finite: nothing that a sum goes through on the way may
+# be larger than it is in the launches on the row-major weights
+@pytest.mark.parametrize("large", ["hidden values", "sums"])
+def test_vit_two_workgroups_large_values(gpu_lib, large):
+    arch = WL.vit_arch(image=64, depth=2)                    # 17 tokens
+    arch["routes"], arch["T"] = np.array([(384, 6, 1536), (200, 3, 808)], np.int32), 2
+    p = WL.vit_params(arch, 13)
+    for l in range(2):
+        b1, w2 = p[f"l{l}.fc1.b"], p[f"l{l}.fc2.w"]
+        if large == "hidden values":
+            b1[[3, 500, 807]], w2[:, [3, 500, 807]] = 2.5e38, 2.0 ** -125       # (2^127 is 1.7e38)
+        else:
+            b1[[3, 500]] = 2.0 ** 20                         # (GELU of it, rounded: the same, whatever the rows add)
+            w2[:, 3], w2[:, 500] = 1.1875 * 2.0 ** 107, -1.1875 * 2.0 ** 107
+    net = gpu_lib.build_vit(arch, p, DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(13)
+    B = 2300                                                 # 612 tiles of 64 rows
+    imgs = torch.randn((B, 3, arch["image"], arch["image"]), generator=gen, device=DEV).to(torch.bfloat16)
+    over = (torch.arange(B, device=DEV, dtype=torch.int32) % 2)[None].contiguous()
+    got, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
+    net.c_struct.n_params -= 4 * arch["depth"]
+    want, _ = gpu_lib.ds_forward(net, imgs, route_override=over)
+    assert torch.isfinite(want).all() and want.abs().max() > 0 and torch.equal(got, want)
+
+
 # heads over two workgroups, four query tiles and the rest: the largest number of heads that are (128) and one sample more, as many
 # wavefronts as a workgroup of one half has and one more
 @pytest.mark.parametrize("dh,H,N,B", [(48, 8, 197, 16), (48, 8, 197, 17), (64, 2, 224, 3), (32, 4, 128, 32), (32, 4, 129, 32), (32, 4, 129, 33)])
