@@ -8,12 +8,13 @@
 #endif
 
 // n / d for 0 <= n < 2^31, d > 0; r within two units in the last place of 1 / d.  The first guess is off by n / d 2^-22 and one, the second, of what it leaves, by one.
-// About a dozen vector instructions one behind the other, the compiler's division 30.
+// (Unsigned, since the first guess and its product may lie beyond 2^31.)  About a dozen vector instructions one behind the other, the compiler's division 30.
 QUOTIENT_FN int quotient(int n, int d, float r) {
-    int q = (int)((float)n * r);
-    q += (int)((float)(n - q * d) * r);
-    const int m = n - q * d;
-    return q + (m >= d) - (m < 0);
+    unsigned q = (unsigned)((float)n * r);
+    auto left = [&]() { return (int)((unsigned)n - q * (unsigned)d); };
+    q += (unsigned)(int)((float)left() * r);
+    const int m = left();
+    return (int)q + (m >= d) - (m < 0);
 }
 // the same for n < 2^22, where the first guess is off by one at most
 QUOTIENT_FN int quotient22(int n, int d, float r) {

@@ -38,6 +38,8 @@ int main() {
 def test_quotients(tmp_path):
     src, exe = tmp_path / "q.cpp", tmp_path / "q"
     src.write_text(PROGRAM)
-    subprocess.run(["g++", "-O2", "-ffp-contract=off", "-std=c++17", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    # (conversions and products out of an int's range are errors, not whatever this machine makes of them)
+    subprocess.run(["g++", "-O2", "-ffp-contract=off", "-std=c++17", "-fsanitize=undefined,float-cast-overflow", "-fno-sanitize-recover=all", "-I", CSRC,
+                    str(src), "-o", str(exe)], check=True)
     out = subprocess.run([str(exe)], capture_output=True, text=True)
-    assert out.returncode == 0, out.stdout
+    assert out.returncode == 0, out.stdout + out.stderr
