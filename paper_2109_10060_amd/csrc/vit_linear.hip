@@ -63,9 +63,8 @@ __global__ __launch_bounds__(64 * NW, DIRECT ? NW / 2 : (NW + 3) / 4) void vit_l
     if (y_ld <= 0) y_ld = k_out;
 
     bf16x8_t ring[D];
-    auto segment = [&](int p) { return (p >= nb) + (p >= 2 * nb); };       // of up to three
     auto weights = [&](int p) {
-        const int s = segment(p);
+        const int s = run_segment(p, nb);
         return weight_row(wt, (s * seg_blocks + p - s * nb) * kb, kin);
     };
     auto start = [&](int p, bool on = true) {            // (off: no traffic)
@@ -193,7 +192,7 @@ __global__ __launch_bounds__(64 * NW, DIRECT ? NW / 2 : (NW + 3) / 4) void vit_l
             yrow[r] = y + (int64_t)(slot0 + sl) * y_ss + (int64_t)(mm - sl * rows) * y_ld;
         }
         for (int p = blk0 + w; p < blk1; p += NW) {
-            const int seg = segment(p), n0 = (p - seg * nb) * 32;
+            const int seg = run_segment(p, nb), n0 = (p - seg * nb) * 32;
             f32x16_t acc[R];
             clear(acc);
             walk(acc, p);
@@ -230,7 +229,7 @@ __global__ __launch_bounds__(64 * NW, DIRECT ? NW / 2 : (NW + 3) / 4) void vit_l
     }
     // ---- column blocks, NW at a time ------------------------------------------------------------------------------------------
     for (int b0 = blk0; b0 < blk1; b0 += NW) {
-        const int p = b0 + w, seg = segment(p), n0 = (p - seg * nb) * 32;
+        const int p = b0 + w, seg = run_segment(p, nb), n0 = (p - seg * nb) * 32;
         const bool on = p < blk1;
         if (res) {
             // the residual of these columns waits in the stage, where the sums are added in place; this run's columns only: res may be
@@ -290,7 +289,7 @@ __global__ __launch_bounds__(64 * NW, DIRECT ? NW / 2 : (NW + 3) / 4) void vit_l
             for (int k = 0; k < (NS + 15) / 16; ++k) {
                 const int c = k * 16 + l16, pb = b0 + (c >> 2);
                 if (!run_chunk(c, NW, b0, blk1) || !live[i]) continue;
-                const int sg = segment(pb), n = (pb - sg * nb) * 32 + (c & 3) * 8;
+                const int sg = run_segment(pb, nb), n = (pb - sg * nb) * 32 + (c & 3) * 8;
                 if (n < k_out) *(uint4*)(y + yoff[i] + (int64_t)sg * y_seg + n) = *(const uint4*)(Ss + (prow + RP * i) * SP + c * 8);
             }
         if (b0 + NW < blk1) __syncthreads();             // the stage is free again
@@ -326,7 +325,7 @@ int32_t ds_launch_vit_linear(const VitLinearArgs& a, int32_t B, hipStream_t s) {
         if ((a.gt.k_in[t] % 8) || (a.gt.k_out[t] % 8)) return DS_EUNSUPPORTED;
     }
     if (kmax <= 0 || nmax <= 0) return DS_OK;
-    if (a.n_seg > 1 && a.res) return DS_EUNSUPPORTED;
+    if ((a.n_seg > 1 && a.res) || a.n_seg > RUN_SEGMENTS) return DS_EUNSUPPORTED;
     const int64_t groups = B < a.gt.T ? B : a.gt.T, n = (int64_t)B * a.rows;
     auto tiles = [&](int bm) { return (n - groups) / bm + groups; };
     const int blocks = (nmax + 31) / 32 * a.n_seg;

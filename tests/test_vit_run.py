@@ -45,3 +45,26 @@ def test_residual_and_output_ask_the_same_question():
     for access in (r"= \*\(const uint4\*\)\(res \+", r"\*\(uint4\*\)\(y \+"):
         at = [m.start() for m in re.finditer(access, kernel)]
         assert len(at) == 1 and "run_chunk(c, NW, b0, blk1)" in kernel[at[0] - 500:at[0]], access
+
+
+SEGMENTS = r"""
+#include <cstdio>
+#include "vit_run.h"
+int main() {
+    for (int nb = 1; nb <= 52; ++nb)
+        for (int p = 0; p < RUN_SEGMENTS * nb; ++p)
+            if (run_segment(p, nb) != p / nb) return printf("%d of %d\n", p, nb), 1;
+    return run_segment(RUN_SEGMENTS, 1) == RUN_SEGMENTS;       // (one more is beyond it)
+}
+"""
+
+
+# the segment of a block by comparisons holds for as many segments as the launcher takes
+def test_segments(tmp_path):
+    src, exe = tmp_path / "seg.cpp", tmp_path / "seg"
+    src.write_text(SEGMENTS)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
+    launcher = open(os.path.join(CSRC, "vit_linear.hip")).read().split("int32_t ds_launch_vit_linear")[1]
+    assert "a.n_seg > RUN_SEGMENTS) return DS_EUNSUPPORTED" in launcher.split("launch<")[0]
