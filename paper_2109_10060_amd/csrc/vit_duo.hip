@@ -8,7 +8,7 @@
 //   * a wavefront owns every fourth 32-column block, up to NB of them (2 up to 256 channels, 3 up to 384, 4 up to 416; each in a body of its
 //     own): an operand read from LDS serves NB products, and the weights (operand order, straight into registers, D tiles in flight) come at
 //     the 64 bytes a clock of the vector cache that 64 rows need at the full matrix rate;
-//   * the hidden layer goes by 128 columns (HC), one block a wavefront, through one tile of LDS: 73 KiB a workgroup;
+//   * the hidden layer goes by 128 columns (HC), one block a wavefront, through one tile of LDS: 71 KiB a workgroup, 76 above 384 channels;
 //   * GELU of the next columns stands between the products of fc2 of the last ones, an instruction stream of a dozen vector instructions a
 //     product (walk_tile); by one polynomial without a check (gelu_poly.h) it is 16 instructions a value;
 //   * LayerNorms and sums run without branches, two rows side by side.
@@ -166,8 +166,8 @@ __device__ __forceinline__ void body(const VitTailArgs& a, const int4 me, char* 
     // product has M blocks or one
     auto walk = [&](auto& acc, const Stream& t, const Stream& next, auto M, const bf16_t* act, int pitch) __attribute__((always_inline)) {
         constexpr int N = sizeof(acc) / sizeof(acc[0]), S = D / N;       // blocks, steps a turn
-        static_assert((N > 1 || S % 4 == 0) && D % N == 0, "whole turns, of one block whole pairs of pairs");
-        constexpr int P = S % 2 ? 1 : 2;                 // steps that are skipped together behind the slice
+        static_assert(D % N == 0 && S % (N > 1 ? 2 : 4) == 0, "whole turns of whole pairs, of one block whole pairs of pairs");
+        constexpr int P = 2;                             // steps that are skipped together behind the slice
         const auto [l16, prow, l32, lhi, lane] = place();
         const bf16_t* base = act + l32 * pitch + lhi * 8;
         // a pair of steps is read ahead of the products of the pair before it (one block), a step ahead of those of a step (several)
@@ -208,10 +208,6 @@ __device__ __forceinline__ void body(const VitTailArgs& a, const int4 me, char* 
 #pragma unroll
                 for (int j = p * N; j < (p + P) * N; ++j) ask(j, from, off, single, m);
             }
-            if constexpr (S % 2) {                       // the next turn starts with the other set
-#pragma unroll
-                for (int r = 0; r < R; ++r) f[0][0][r] = f[1][0][r];
-            }
         };
         for (; k0 + 16 * S < t.k; k0 += 16 * S) turn(mine, lane16 + k0 * 64 + S * 1024, N == 1, N);
         turn(other, lane16, one, M.value);
@@ -219,7 +215,7 @@ __device__ __forceinline__ void body(const VitTailArgs& a, const int4 me, char* 
     // the product of a whole hidden tile (HC channels, zeros behind the slice in both operands), one piece of other work beside each of its steps
     auto walk_tile = [&](const Stream& t, const Stream& next, auto M, auto piece) __attribute__((always_inline)) {
         constexpr int S = D / NB, STEPS = HC / 16;
-                const auto [l16, prow, l32, lhi, lane] = place();
+        const auto [l16, prow, l32, lhi, lane] = place();
         const bf16_t* base = Hs + l32 * PH + lhi * 8;
         bf16x8_t f[2][R];
         const Rows mine = rows_of(t), other = rows_of(next);

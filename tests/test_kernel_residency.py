@@ -23,13 +23,14 @@ def test_short_slabs_of_the_grouped_gemm():
         assert k[".private_segment_fixed_size"] == 0, name
 
 
-# transformer blocks with two workgroups of four wavefronts a compute unit: two wavefronts a SIMD, and nothing in scratch up to 384 channels
+# transformer blocks with two workgroups of four wavefronts a compute unit: two wavefronts a SIMD, and nothing in scratch up to 384 channels (what waits
+# there is waited for like the operands asked for before it), above them, with four column blocks a wavefront, two registers a lane at most
 def test_transformer_blocks_of_two_workgroups():
     found = {n: k for n, k in kernels().items() if "vit_duo_kernel" in n}
     assert len(found) == 2
     for name, k in found.items():
         assert waves(k) >= 2, name
-        assert k[".private_segment_fixed_size"] == 0 or "Li416E" in name, name
+        assert k[".private_segment_fixed_size"] <= (8 if "Li416E" in name else 0), name
 
 
 # 3x3 layers on tiled filters: two wavefronts a SIMD, nothing in scratch
