@@ -6,10 +6,8 @@
 
 __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 
-// Four values -> packed bf16: gelu_poly inside its range, gelu_erf outside, each value for itself.  erff costs about 25 vector instructions
-// and two branches a value, gelu_poly 15.  (A shorter polynomial, with a check that its bf16 result is that of erff and erff itself where
-// that is open, cost 16 and the check: of the groups of 64 lanes x 4 values one in twelve was done over.)
-// the values outside the range again, one erff after the other (a loop: the code of a kernel holds many such groups)
+// A group of four values of which one or more lie outside gelu_poly's range: those by gelu_erf in place of q's, one erff after the other (a loop: the code
+// of a kernel holds many such groups).  HALF: the x are halves of the values.
 template <bool HALF = false>
 __device__ __forceinline__ uint2 gelu_bf16x4_far(uint2 q, float x0, float x1, float x2, float x3) {
     constexpr float LIMIT = HALF ? GELU_LIMIT / 2 : GELU_LIMIT;
@@ -30,6 +28,9 @@ __device__ __forceinline__ float gelu_top(float x0, float x1, float x2, float x3
 __device__ __forceinline__ uint2 gelu_bf16x4_near(float x0, float x1, float x2, float x3) {
     return make_uint2(f2bf2(gelu_poly(x0), gelu_poly(x1)), f2bf2(gelu_poly(x2), gelu_poly(x3)));
 }
+// Four values -> packed bf16: gelu_poly inside its range, gelu_erf outside, each value for itself.  erff costs about 25 vector instructions
+// and two branches a value, gelu_poly 15.  (A shorter polynomial, with a check that its bf16 result is that of erff and erff itself where
+// that is open, cost 16 and the check: of the groups of 64 lanes x 4 values one in twelve was done over.)
 __device__ __forceinline__ uint2 gelu_bf16x4(float x0, float x1, float x2, float x3) {
     const uint2 q = gelu_bf16x4_near(x0, x1, x2, x3);
     return gelu_top(x0, x1, x2, x3) > GELU_LIMIT ? gelu_bf16x4_far(q, x0, x1, x2, x3) : q;

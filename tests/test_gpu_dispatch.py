@@ -234,12 +234,12 @@ def test_vit_parts_have_the_bits_of_the_batch(gpu_lib, big, B, parts):
             assert np.array_equal(space[at // 2 + j * N * D:][:N * width].reshape(N, width), want), (p0, b)
 
 
-# hidden activations around the limits of the GELU's short evaluation: every bf16 result equals the exact one's
+# hidden activations inside and outside the range of GELU's polynomial: the bits of the linear layers on row-major weights
 def test_gelu_rounding_matches_the_linear_layer(gpu_lib):
     arch = WL.vit_arch(depth=1)
     p = WL.vit_params(arch, 6)
     for k in ("l0.fc1.w", "l0.fc1.b"):
-        p[k] = p[k] * 8.0                                   # pre-activations far beyond +-2.5 beside small ones
+        p[k] = p[k] * 8.0                                   # pre-activations far beyond +-3.5 beside small ones
     net = gpu_lib.build_vit(arch, p, DEV)
     B = 48
     gen = torch.Generator(device=DEV)

@@ -182,6 +182,41 @@ def test_sliced_linear_gelu_residual_ragged_small(gpu_lib):
     assert _linear_case(gpu_lib, c, torch.float32) < 1e-4
 
 
+# GELU of every bf16 value (identity weights: a sum is the value itself), values inside and outside the polynomial's range beside each other in a lane, the few-image
+# launches and the others: the nearest bf16, but where the exact result lies closer to the middle of two than fp32's own error, 1.25e-7 of |x|
+@pytest.mark.parametrize("copies", [1, 64])
+@pytest.mark.parametrize("y_dtype", [torch.bfloat16, torch.float32])
+def test_gelu_of_every_value(gpu_lib, copies, y_dtype):
+    from scipy.special import erfc
+    every = (torch.arange(1 << 16, dtype=torch.int32) << 16).view(torch.float32)
+    finite = every[torch.isfinite(every)]                          # 65280 = 1020 rows of 64
+    B, rows, W = 4 * copies, 256, 64
+    gen = torch.Generator().manual_seed(3)
+    dense = [finite[torch.randperm(finite.numel(), generator=gen)] if i else finite for i in range(copies)]
+    x = torch.stack([torch.cat([d, torch.zeros(4 * W)]) for d in dense]).view(B, rows, W)
+    off = torch.tensor([0, B], dtype=torch.int32, device=DEV)
+    g = gpu_lib.make_groups(off, None, [W])
+    eye = torch.eye(W, dtype=torch.bfloat16, device=DEV)
+    for shift in (0.0, 0.0078125 / 3):                             # (the second: values that are no bf16)
+        bias = torch.full((W,), shift, device=DEV)
+        y = gpu_lib.ds_sliced_linear(x.to(DEV).to(torch.bfloat16), eye, bias, g, act=gpu_lib.DS_ACT_GELU, y_dtype=y_dtype)
+        v = (x + bias.cpu()).double().numpy()                      # (one rounding, as in the kernel)
+        want, got = 0.5 * v * erfc(v * -0.5 ** 0.5), host(y)
+        most = 3.38e38                                             # (what rounds to infinity is not compared)
+        ulp = 2.0 ** (np.floor(np.log2(np.maximum(np.abs(want), 2.0 ** -120))) - (8 if y_dtype == torch.bfloat16 else 24))
+        ok = (np.abs(got - want) <= ulp + 1.25e-7 * np.abs(v)) | (np.abs(want) > most)
+        assert ok.all(), (v[~ok][:5], got[~ok][:5], want[~ok][:5])
+    # what is not finite, one a row
+    odd = torch.tensor([float("inf"), float("-inf"), float("nan")])
+    x = torch.zeros((B, rows, W))
+    for i in range(3):
+        x[:, i::3, 5 * i] = odd[i]
+    y = gpu_lib.ds_sliced_linear(x.to(DEV).to(torch.bfloat16), eye, torch.zeros(W, device=DEV), g, act=gpu_lib.DS_ACT_GELU, y_dtype=y_dtype)
+    # (0 times what is not finite is NaN in the row's other columns; minus infinity times an erfc of zero as well)
+    got = y.float().cpu()
+    assert torch.isposinf(got[:, 0::3, 0]).all() and torch.isnan(got[:, 1::3, 5]).all() and torch.isnan(got[:, 2::3, 10]).all()
+
+
 def test_sliced_linear_one_bucket_gets_everything_and_empty_batch(gpu_lib):
     c = WL.config2(seed=79, B=6, N=50, K=48)
     c["route"][:] = 2
