@@ -214,8 +214,8 @@ def run_linear(args):
 
 # kernel classes whose launches are the cost model's gemm / gemm_taps records
 GEMM_CLASSES = ("gemm", "gemm_taps", "conv3", "thin", "tail", "small", "vit_linear")
-KERNEL_OF = {"gemm": "gemm_kernel", "gemm_taps": "gemm_kernel", "conv3": "conv3_kernel", "thin": "thin_kernel",
-             "tail": "vit_tail_kernel", "small": "gemm_small_kernel", "vit_linear": "vit_linear_kernel"}
+KERNEL_OF = {"gemm": "gemm_kernel", "gemm_taps": "gemm_kernel", "conv3": "conv3_kernel/conv3_tiled_kernel/bneck_kernel", "thin": "thin_kernel",
+             "tail": "vit_tail_kernel/vit_duo_kernel", "small": "gemm_small_kernel", "vit_linear": "vit_linear_kernel"}
 RIDGE = PEAK_MFMA_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9)     # flop per byte above which the matrix peak is the roof
 
 

@@ -446,9 +446,9 @@ enum {
     DS_K_GATE,
     DS_K_BUCKET,
     DS_K_MISC,
-    DS_K_CONV3,      // conv3_kernel (3x3 stride-1 layers with the input patch staged once)
+    DS_K_CONV3,      // conv3_kernel, conv3_tiled_kernel (3x3 layers with the input patch staged once), bneck_kernel (a bottleneck block behind its first layer)
     DS_K_THIN,       // thin_kernel (short reductions, one workgroup per row tile; with or without a chained second layer)
-    DS_K_TAIL,       // vit_tail_kernel (projection, MLP and LayerNorms of a transformer block)
+    DS_K_TAIL,       // vit_tail_kernel, vit_duo_kernel (projection, MLP and LayerNorms of a transformer block)
     DS_K_SMALL,      // gemm_small_kernel (launches of a few samples, any filter size)
     DS_K_VIT_LINEAR, // vit_linear_kernel (linear layers on tiled weights, with or without the LayerNorm)
     DS_K_COUNT

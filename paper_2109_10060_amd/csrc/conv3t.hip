@@ -1,5 +1,6 @@
 // 3x3 layers (padding 1, bf16, no residual: conv3_kernel's of stride 1, and those of stride 2) with the filters in operand order: they stream into registers, and only the
-// input patch, staged once a chunk of 32 channels, goes through LDS.  Sums in conv3_kernel's order: chunk, tap, half of the chunk.
+// input patch, staged once a chunk of 32 channels, goes through LDS.  Sums in conv3_kernel's order: chunk, tap, half of the chunk
+// (gemm_kernel takes a strided layer tap by tap, so the last bits differ where a batch's size sends one there).
 //
 // What bounds it: matrix rate, while a SIMD has two wavefronts.  One wavefront alone gets an instruction out of 61 clocks where the pipe takes 32: all four
 // of a workgroup ask LDS and the vector cache at once, and its products wait behind the requests in program order (245 clocks a step of four products, with
@@ -13,9 +14,13 @@
 //     to the widest, so that the widest ones share with the narrowest or with none.  A row tile stays on the die that gemm_kernel's layers in front and
 //     behind have it on: with tiles dealt over all dies the 3x3 layers of DS-ResNet took 13 us less each and the pass nothing less.
 //   * Quotients by reciprocals: with integer divisions a workgroup spent 14 of 25 us ahead of its first product and behind its last.
-// us a launch, mixed routes of 256 images, conv3_kernel -> here: 14x14 pixels, 64..256 channels 44 -> 31, 7x7 pixels, 128..512 channels 44 -> 31.
-// us a pass: DS-ResNet 64 / 96 / 128 / 256 images 1022 / 1223 / 1491 / 2465 -> 1001 / 1180 / 1462 / 2398, 256 in four parts 2420 -> 2330, DS-ResNet++ 64 / 256 images
-// 1123 / 2840 -> 1089 / 2770; three networks in turn, DS-ResNet 16 / 24 / 33 / 48 images 652 / 726 / 800 / 920 -> 646 / 714 / 778 / 904, DS-ResNet++ 33 images 850 -> 836.
+// us a launch, mixed routes of 256 images, conv3_kernel -> here: 14x14 pixels, 64..256 channels 46 -> 32, 7x7 pixels, 128..512 channels 46 -> 32.
+// us a pass, without this kernel | its layers of stride 1 | all of them (one card, in turn, a second each): DS-ResNet 8 / 16 / 24 / 33 / 48 images 521 / 611 / 681 / 747 / 872 |
+// 516 / 597 / 654 / 699 / 841 | 516 / 594 / 646 / 690 / 822, 64 / 96 / 128 / 160 / 256 images 1026 / 1224 / 1477 / 1693 / 2434 | 1000 / 1183 / 1425 / 1635 / 2339 | 976 / 1156 / 1395 /
+// 1609 / 2327, 256 in four parts 2422 | 2344 | 2318, DS-ResNet++ 8 / 16 / 33 / 64 / 128 / 256 images 514 / 601 / 775 / 1099 / 1646 / 2776 | 507 / 583 / 729 / 1067 / 1581 / 2677 | 505 / 579 / 714 /
+// 1039 / 1547 / 2637.  Of the 125 us that the launches of 256 images save under events the pass keeps 107; on other cards it kept 30 to 60 (2478 -> 2449, 2461 -> 2398).
+// Three networks in turn, so that filters come from memory: DS-ResNet 16 / 24 / 33 / 48 / 256 images 650 / 723 / 798 / 917 / 2434 | 653 / 711 / 776 / 900 / 2338 | 653 / 706 / 773 / 890 / 2326,
+// DS-ResNet++ 33 images 825 | 811 | 802.
 #include "tile_out.h"
 #include "conv3_fit.h"
 
@@ -248,17 +253,18 @@ int32_t launch(const GemmArgs& a, const Conv3T& t, int32_t max_mtiles, int32_t m
 }  // namespace
 
 // tiles: filters [ceil(N / 32)][18 ceil(K / 32) + 1] tiles of 1 KiB; channels: K as stored.  Launches of up to 600 of gemm_small_kernel's 32 x 32 tiles
-// stay there, with up to eight wavefronts on a tile's reduction: us a pass, there / here, DS-ResNet 1 / 4 / 8 images 364 / 468 / 529 and 384 / 491 / 536,
-// DS-ResNet++ 4 / 8 images 460 / 541 and 481 / 544.  With all of its launches there, 33 images of DS-ResNet++ 851 (networks in turn, 762 one
-// network's), here from 600 on 836 (751); DS-ResNet 16 / 24 images 641 / 712 and 646 / 714 (611 / 655 and 606 / 650).  Filters that come from
-// memory are what these launches wait for (256 channels, 13 us a launch with one network, 16 with three in turn); the reduction dealt to two groups
-// of wavefronts does not change that (838 and 849 a pass).
-// Tiles of 64 pixels until there are enough of 128 to go round: DS-ResNet 128 / 160 / 256 images, 256 in four parts, the line at 500 workgroups of 128 x 64 1430 / 1639 / 2337 / 2300,
-// at 700 1423 / 1632 / 2333 / 2302, at 1200 1432 / 1653 / 2347 / 2295, at 1700 1432 / 1652 / 2372 / 2314.
-// Stride 2, where gemm_kernel gathers the input of each tap again: us a launch, there / here, 256 images, 128 to 256 channels 50 / 48, 512 58 / 47, 33 images of
-// DS-ResNet++ 22 / 18, 25 (gemm_small_kernel) / 19, 28 / 29.  Up to 128 filters gemm_kernel reads the input once as well and here 64 pixels of it feed one column tile only:
-// 256 images 70 / 73, so from 768 row tiles on it stays there.  us a pass: DS-ResNet 64 / 96 / 256 images 1011 / 1200 / 2457 -> 989 / 1171 / 2433, 256 in four
-// parts 2336 -> 2322, DS-ResNet++ 33 / 256 images 813 / 2815 -> 803 / 2775.
+// stay there, with up to eight wavefronts on a tile's reduction: us a pass, there / here, DS-ResNet 1 / 4 / 8 / 16 / 24 images 352 / 459 / 516 / 594 / 646 and 389 / 501 / 543 / 604 /
+// 644, DS-ResNet++ 4 / 8 / 16 images 430 / 505 / 579 and 469 / 532 / 589.  With all of its launches there (up to 1000 tiles) DS-ResNet 14 / 16 / 18 / 33 images 597 / 601 / 633 / 687, as
+// it is 590 / 594 / 620 / 690; three networks in turn 636 / 642 / 676 / 766 and 645 / 650 / 680 / 773: there filters come from memory, and more wavefronts ask for them.
+// (The reduction dealt to two groups of wavefronts here: 33 images of DS-ResNet++ in turn 849 where 838 without.)
+// Tiles of 64 pixels until there are enough of 128 to go round, us a pass, the line at 500 / 700 / 1200 / 1700 workgroups of 128 x 64: DS-ResNet 96 images 1164 / 1156 / 1156 / 1156, 128
+// images 1401 / 1395 / 1403 / 1403, 160 images 1616 / 1609 / 1629 / 1629, 192 images 1860 / 1860 / 1856 / 1880, 256 images 2328 / 2327 / 2336 / 2359, in four parts 2317 / 2318 / 2315 / 2302.
+// Stride 2, where gemm_kernel gathers the input of each tap again: us a launch, there / here, 256 images, 256 filters 50 / 46, 512 filters 56 / 45, 33 images of
+// DS-ResNet++, 128 / 256 / 512 filters 22 / 17, 25 (gemm_small_kernel) / 16, 27 (the same) / 26.  Up to 128 filters gemm_kernel reads the input once as well and here 64 pixels of it feed
+// one column tile only, so from 768 row tiles on it stays there: a launch of 128 / 160 / 256 images 40 / 51 / 70 and 38 / 45 / 72.  us a pass,
+// there / here: DS-ResNet 128 images (799 row tiles) 1395 / 1394, 144 (898) 1504 / 1500, 160 (996) 1609 / 1603, 192 (1191) 1860 / 1858, 224 (1387) 2086 / 2089, 256 (1583) 2327 / 2330, in four
+// parts 2318 / 2326, on uneven routes 2269 / 2277; DS-ResNet++ 128 images 1547 / 1544, 192 2089 / 2089, 256 2637 / 2640.  (Up to 1200 row tiles either is as good to 0.4 %, beyond
+// them gemm_kernel by as much.)
 int32_t ds_launch_conv3_tiled(const GemmArgs& a, const bf16_t* tiles, int32_t channels, int32_t max_mtiles, int32_t max_kout, hipStream_t s) {
     if (a.K != 3 || a.Kw > 3 || (a.stride != 1 && a.stride != 2) || a.stride_w > 0 || a.pad != 1 || a.n_seg != 1 || a.Ho != (a.H - 1) / a.stride + 1 ||
         a.Wo != (a.W - 1) / a.stride + 1 || a.rows != a.Ho * a.Wo || a.R || !conv_result(a) || !a.offsets)

@@ -449,8 +449,6 @@ bool ds_vit_tail_qkv(const GroupTable& gt, int32_t B, int32_t rows, int32_t crow
 // 1750 / 1503 in four; DS-ViT++ 64 images in two (212) 1147 / 1308, 80 images (262, 276) 1388 / 1421 and 1467 / 1423, 96 images 1586 / 1555 and 1641 /
 // 1582.  (Parts of unequal size each count the others as being of their own: 72 images of DS-ViT++ in two are 40 and 32, which take one each, 1431
 // where both with 32 rows take 1272 and both with 64 take 1356.)
-// Two workgroups a compute unit (four wavefronts of three column blocks each, 64 rows) were slower, 2780 us when 64 rows took 2600 and
-// 96 rows 2710: eight wavefronts do not cover the weights' latency.
 int32_t ds_launch_vit_tail(const VitTailArgs& a, int32_t B, hipStream_t s) {
     int dmax = 0, kmax = 0;
     for (int t = 0; t < a.gt.T; ++t) {

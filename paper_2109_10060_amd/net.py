@@ -7,7 +7,9 @@ in place (channels-last filters [C_O, K, K, C_I], depthwise [3, 3, C], stem
 [K*K*3, C_O], stacked Q/K/V), split batch-norm statistics are folded to per-route
 scale/shift tables by the library's own ds_bn_fold kernel, and the integer
 description plus the device pointers are laid out in the order include/dsnet.h
-documents for each architecture.
+documents for each architecture.  Filters and linear weights that kernels read in operand
+order are held twice, row-major and tiled, and a launch reads the copy its kernel is written
+for: other weights are another Net.
 """
 from __future__ import annotations
 

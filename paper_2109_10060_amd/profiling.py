@@ -33,8 +33,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 KERNEL_SOURCES = ["csrc/gemm.hip", "csrc/conv3.hip", "csrc/conv3t.hip", "csrc/conv3_fit.h", "csrc/bneck.hip", "csrc/thin.hip", "csrc/small.hip", "csrc/vit_linear.hip", "csrc/vit_tail.hip", "csrc/vit_duo.hip",
                   "csrc/vit_rows.h", "csrc/vit_run.h", "csrc/tile_out.h", "csrc/quotient.h", "csrc/gelu.h", "csrc/gelu_poly.h", "csrc/common.h"]
-# the grouped GEMM is several kernels: gemm_kernel (linear, 1x1, strided and KxK layers), conv3_kernel and conv3_tiled_kernel (3x3 stride-1
-# layers), bneck_kernel (a bottleneck block behind its first layer), thin_kernel (1x1 layers with at most 64 / 128 input channels), gemm_small_kernel and gemm_small_pair_kernel (launches
+# the grouped GEMM is several kernels: gemm_kernel (linear, 1x1, strided and KxK layers), conv3_kernel (3x3 stride-1
+# layers), conv3_tiled_kernel (those and the strided ones, on tiled filters), bneck_kernel (a bottleneck block behind its first layer), thin_kernel (1x1 layers with at most 64 / 128 input channels), gemm_small_kernel and gemm_small_pair_kernel (launches
 # of a few samples), vit_linear_kernel, vit_tail_kernel and vit_duo_kernel (transformer blocks on weights in operand order); the summaries treat
 # them as one kernel class, as bench.py does
 GEMM_KERNELS = ("gemm_kernel", "conv3_kernel", "conv3_tiled_kernel", "bneck_kernel", "thin_kernel", "gemm_small_kernel", "gemm_small_pair_kernel", "vit_linear_kernel",

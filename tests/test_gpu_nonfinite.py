@@ -49,8 +49,8 @@ def test_vit_samples_stay_apart(gpu_lib, kw, B):
     _samples_stay_apart(gpu_lib, gpu_lib.build_vit(arch, params, DEV), B, 64)
 
 
-@pytest.mark.parametrize("B", [5, 67])
-@pytest.mark.parametrize("kind", ["mbnet", "mbnet_pp", "resnet"])
+# (300 images of a ResNet: 3x3 layers on tiled filters, of either stride)
+@pytest.mark.parametrize("kind,B", [(k, B) for k in ("mbnet", "mbnet_pp", "resnet") for B in (5, 67)] + [("resnet", 300)])
 def test_cnn_samples_stay_apart(gpu_lib, kind, B):
     if kind == "resnet":
         arch = WL.resnet_arch(image=64, blocks=(2, 2, 2, 2))
