@@ -281,15 +281,15 @@ struct BucketArgs {
     int32_t *perm, *inv_perm, *offsets, *slot_group;   // inv_perm, slot_group nullable
     const int32_t* inv_prev;  // with src_index: src_index[slot] = inv_prev ? inv_prev[sample] : sample
     int32_t* src_index;       // nullable
-    // optional extras done by the same launch (T <= DS_MAX_GROUPS): up to four m-tile lists for the new offsets (count, then
-    // from byte 16 on one record per tile, ds_mtile_capacity() at most; list_rows[i] rows per sample), slot_lut[slot] = lut[group of slot], and the
-    // routes once more: copy_to[i * copy_stride + sample], i < copies
+    // optional extras done by the same launch (T <= DS_MAX_GROUPS): slot_lut[slot] = lut[group of slot], up to four m-tile lists for the new offsets (count, then
+    // from byte 16 on one record per tile, ds_mtile_capacity() at most; list_rows[i] rows per sample), and the routes once more:
+    // copy_to[i * copy_stride + sample], i < copies.  (What every launch reads comes first, in two lines of the scalar cache.)
+    int32_t* slot_lut;        // nullable
     int32_t n_lists, list_rows[DS_BUCKET_LISTS];
     void* lists[DS_BUCKET_LISTS];
-    int32_t* slot_lut;        // nullable
+    int32_t lut[DS_MAX_GROUPS];
     int32_t* copy_to;
     int32_t copies, copy_stride;
-    int32_t lut[DS_MAX_GROUPS];
 };
 int32_t ds_launch_bucket_ex(const BucketArgs& a, hipStream_t s);
 // bucket (one sample, T <= 64): made by the gate's last launch itself, its route field is not read

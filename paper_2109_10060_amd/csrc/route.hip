@@ -15,7 +15,6 @@ namespace {
 // One image, first gate of DS-ResNet: 8.9 + 3.8 us in two launches, 10.2 in one, and a gap between launches less.
 __device__ __forceinline__ void bucket_one(const BucketArgs& a, int route) {
     const int lane = threadIdx.x & 63;
-    if (lane < a.copies) a.copy_to[lane * a.copy_stride] = route;
     int k = route * a.mul + (a.lo ? a.lo[0] : 0);
     if (k < 0 || k >= a.T) k = -1;
     for (int t = lane; t <= a.T; t += 64) a.offsets[t] = k >= 0 && t > k;
@@ -33,6 +32,7 @@ __device__ __forceinline__ void bucket_one(const BucketArgs& a, int route) {
         if (a.src_index) a.src_index[0] = src;
         if (a.slot_lut) a.slot_lut[0] = a.lut[k];
     }
+    if (lane < a.copies) a.copy_to[lane * a.copy_stride] = route;
 }
 // Every other gate, ds_gate's among them: no bucket, and none of its 416 bytes among the launch's arguments.
 struct NoBucket {};
@@ -355,6 +355,8 @@ __global__ __launch_bounds__(GF_NT) void gate_fused_kernel(const GateArgs a, con
 // Up to 64 groups (bucket64_kernel) nothing is counted serially: the scans run over the lanes of a wavefront, and a rank is
 // the number of earlier lanes with the same key -- six ballots, one per key bit -- plus the counts of the earlier
 // wavefronts.  16 / 48 groups of 256 samples with two tile lists: 11 / 20 -> 5 to 8 / 5 us; one sample 6 -> 4 us (a forward of one sample: bucket_one).
+// COPIES: the routes once more, in an instance of its own and last (with the loop ahead of the first barrier every launch took 2.11 us for 2.01).
+template <bool COPIES>
 __global__ __launch_bounds__(1024) void bucket64_kernel(const BucketArgs a) {
     __shared__ int cnt[16][64];                          // samples per wavefront and key of the current 1024
     __shared__ int base[65], start[65];                  // next free slot of a key; first slot of a key
@@ -377,8 +379,6 @@ __global__ __launch_bounds__(1024) void bucket64_kernel(const BucketArgs a) {
     };
     const int k0 = tid < B ? key_of(tid) : -1;           // the first 1024 samples' keys stay in registers
     const unsigned long long m0 = same(k0);
-    for (int b = tid; a.copies > 0 && b < B; b += 1024)
-        for (int i = 0; i < a.copies; ++i) a.copy_to[(int64_t)i * a.copy_stride + b] = a.route[b];
     if (tid <= 64) base[tid] = 0;
     cnt[wave][lane] = 0;
     __syncthreads();
@@ -462,6 +462,9 @@ __global__ __launch_bounds__(1024) void bucket64_kernel(const BucketArgs a) {
         __syncthreads();
         if (k >= 0) place(b, k, cnt[wave][k] + __builtin_popcountll(m & below));
     }
+    if constexpr (COPIES)
+        for (int b = tid; b < B; b += 1024)
+            for (int i = 0; i < a.copies; ++i) a.copy_to[(int64_t)i * a.copy_stride + b] = a.route[b];
 }
 
 // any number of groups (ds_route_bucket up to 1024)
@@ -747,7 +750,8 @@ int32_t ds_launch_bucket_ex(const BucketArgs& a, hipStream_t s) {
     if ((a.n_lists > 0 || a.slot_lut || a.copies > 0) && a.T > DS_MAX_GROUPS) DS_FAIL(DS_EINVAL, "route bucket: fused lists need T <= %d", DS_MAX_GROUPS);
     if (a.n_lists < 0 || a.n_lists > DS_BUCKET_LISTS) DS_FAIL(DS_EINVAL, "route bucket: at most %d m-tile lists", DS_BUCKET_LISTS);
     ProfScope prof(DS_K_BUCKET, s);
-    if (a.T <= 64) hipLaunchKernelGGL(bucket64_kernel, dim3(1), dim3(1024), 0, s, a);
+    if (a.T <= 64 && a.copies > 0) hipLaunchKernelGGL(bucket64_kernel<true>, dim3(1), dim3(1024), 0, s, a);
+    else if (a.T <= 64) hipLaunchKernelGGL(bucket64_kernel<false>, dim3(1), dim3(1024), 0, s, a);
     else hipLaunchKernelGGL(bucket_kernel, dim3(1), dim3(1024), 0, s, a);
     DS_CHECK_LAUNCH("route bucket");
     return DS_OK;
