@@ -18,7 +18,7 @@
 // us a pass, without this kernel | its layers of stride 1 | all of them (one card, in turn, a second each): DS-ResNet 8 / 16 / 24 / 33 / 48 images 521 / 611 / 681 / 747 / 872 |
 // 516 / 597 / 654 / 699 / 841 | 516 / 594 / 646 / 690 / 822, 64 / 96 / 128 / 160 / 256 images 1026 / 1224 / 1477 / 1693 / 2434 | 1000 / 1183 / 1425 / 1635 / 2339 | 976 / 1156 / 1395 /
 // 1609 / 2327, 256 in four parts 2422 | 2344 | 2318, DS-ResNet++ 8 / 16 / 33 / 64 / 128 / 256 images 514 / 601 / 775 / 1099 / 1646 / 2776 | 507 / 583 / 729 / 1067 / 1581 / 2677 | 505 / 579 / 714 /
-// 1039 / 1547 / 2637.  Of the 125 us that the launches of 256 images save under events the pass keeps 107; on other cards it kept 30 to 60 (2478 -> 2449, 2461 -> 2398).
+// 1039 / 1547 / 2637.  Of the 125 us that the launches of 256 images save under events the pass keeps 107; on cards of lower clocks it kept 30 to 65 (2478 -> 2449, 2494 -> 2429).
 // Three networks in turn, so that filters come from memory: DS-ResNet 16 / 24 / 33 / 48 / 256 images 650 / 723 / 798 / 917 / 2434 | 653 / 711 / 776 / 900 / 2338 | 653 / 706 / 773 / 890 / 2326,
 // DS-ResNet++ 33 images 825 | 811 | 802.
 #include "tile_out.h"
